@@ -1,4 +1,6 @@
-"""ctypes binding of libglowmi.so with the same names as the C ABI (argument marshalling only)."""
+"""Python binding of libglowmi.so with the same names as the C ABI (argument marshalling only): the calls that take
+tensors go through the native module _native (csrc/python_binding.cpp), which checks the tensors and costs a fraction
+of what marshalling them with ctypes does; the structures and the host-side queries are ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -10,6 +12,7 @@ ACT_RELU = 1
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libglowmi.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 STATUS_NAMES = {0: "GLOWMI_OK", 1: "GLOWMI_ERR_NULL", 2: "GLOWMI_ERR_SHAPE", 3: "GLOWMI_ERR_UNSUPPORTED",
                 4: "GLOWMI_ERR_ALIGN", 5: "GLOWMI_ERR_QUANT", 6: "GLOWMI_ERR_HIP"}
@@ -55,6 +58,7 @@ class GlowmiError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def library_path() -> str:
@@ -62,13 +66,14 @@ def library_path() -> str:
 
 
 def library() -> ctypes.CDLL:
-    """Load libglowmi.so.  There is no fallback: a missing library is an error."""
-    global _lib
+    """Load libglowmi.so and its native binding.  There is no fallback: a missing library is an error."""
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_1805_00907_amd.build` "
-                          "(glowmi has no CPU or PyTorch fallback)")
+    for path in (_LIB_PATH, _NATIVE_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: build it with `python -m paper_1805_00907_amd.build` "
+                              "(glowmi has no CPU or PyTorch fallback)")
     # torch ships its own HIP runtime; import it first so that this library binds to the same
     # runtime instance that owns the device memory and streams handed to it.
     import torch  # noqa: F401
@@ -131,8 +136,17 @@ def library() -> ctypes.CDLL:
     L.glowmi_status_string.restype = ctypes.c_char_p
     L.glowmi_last_error.restype = ctypes.c_char_p
     L.glowmi_last_variant.restype = ctypes.c_char_p
+    from . import _native as native      # linked against the library just loaded
+    _native = native
     _lib = L
     return L
+
+
+def _calls():
+    """The native entry points (loads the library on first use)."""
+    if _native is None:
+        library()
+    return _native
 
 
 def _check(status: int) -> None:
@@ -144,27 +158,6 @@ def last_variant() -> str:
     return library().glowmi_last_variant().decode()
 
 
-def _ptr(t, dtype: Optional[str] = None, count: Optional[int] = None, what: str = "tensor") -> Optional[int]:
-    """Device address of a torch tensor (None -> NULL); a raw integer address is passed through.
-
-    For a tensor, the facts the C side cannot see are checked here, because a mismatch would become
-    an out-of-bounds access on the device: it must live on a GPU, be contiguous, have the element
-    type `dtype` ("float32", "int8", "int32") and hold at least `count` elements."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return t
-    if not t.is_cuda:
-        raise ValueError(f"{what}: expected a device tensor, got one on {t.device}")
-    if not t.is_contiguous():
-        raise ValueError(f"{what}: tensor is not contiguous")
-    if dtype is not None and str(t.dtype) != "torch." + dtype:
-        raise ValueError(f"{what}: expected {dtype}, got {t.dtype}")
-    if count is not None and t.numel() < count:
-        raise ValueError(f"{what}: {t.numel()} elements, the call needs {count}")
-    return t.data_ptr()
-
-
 def _conv_counts(desc: ConvDesc) -> Tuple[int, int, int]:
     """(input, filter, output) element counts of a descriptor; zeros when the library will reject it."""
     oh, ow = ctypes.c_int32(0), ctypes.c_int32(0)
@@ -172,24 +165,6 @@ def _conv_counts(desc: ConvDesc) -> Tuple[int, int, int]:
         return 0, 0, 0
     return (desc.n * desc.h * desc.w * desc.c, desc.k * desc.r * desc.s * (desc.c // desc.groups),
             desc.n * oh.value * ow.value * desc.k)
-
-
-def _ws(workspace) -> Tuple[Optional[int], int]:
-    if workspace is None:
-        return None, 0
-    if not workspace.is_cuda or not workspace.is_contiguous():
-        raise ValueError("workspace: expected a contiguous device tensor")
-    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
-
-
-def _stream(stream) -> Optional[int]:
-    """hipStream_t handle: a torch stream, a raw handle, or torch's current stream when None."""
-    if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
-    if isinstance(stream, int):
-        return stream
-    return stream.cuda_stream
 
 
 def conv_out_shape(desc: ConvDesc) -> Tuple[int, int]:
@@ -203,11 +178,7 @@ def conv2d_workspace_bytes(desc: ConvDesc) -> int:
 
 
 def conv2d(x, w, bias, y, desc: ConvDesc, act: int = ACT_NONE, workspace=None, stream=None) -> None:
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    _check(library().glowmi_conv2d(_ptr(x, "float32", nx, "x"), _ptr(w, "float32", nw, "w"),
-                                   _ptr(bias, "float32", desc.k, "bias"), _ptr(y, "float32", ny, "y"),
-                                   ctypes.byref(desc), act, wp, wb, _stream(stream)))
+    _check(_calls().conv2d_packed(x, w, None, bias, y, desc, None, act, workspace, stream))
 
 
 def fc_workspace_bytes(M: int, K: int, N: int) -> int:
@@ -215,17 +186,12 @@ def fc_workspace_bytes(M: int, K: int, N: int) -> int:
 
 
 def fc(a, w, bias, y, M: int, K: int, N: int, act: int = ACT_NONE, workspace=None, stream=None) -> None:
-    wp, wb = _ws(workspace)
-    _check(library().glowmi_fc(_ptr(a, "float32", M * K, "a"), _ptr(w, "float32", K * N, "w"),
-                               _ptr(bias, "float32", N, "bias"), _ptr(y, "float32", M * N, "y"), M, K, N, act, wp,
-                               wb, _stream(stream)))
+    _check(_calls().fc_packed(a, w, None, bias, y, M, K, N, act, workspace, stream))
 
 
 def fc_noalloc(a, w, bias, y, M: int, K: int, N: int, act: int = ACT_NONE, stream=None) -> None:
     """glowmi_fc without a workspace argument and without any allocation (library-owned static scratch)."""
-    _check(library().glowmi_fc_noalloc(_ptr(a, "float32", M * K, "a"), _ptr(w, "float32", K * N, "w"),
-                                       _ptr(bias, "float32", N, "bias"), _ptr(y, "float32", M * N, "y"), M, K, N,
-                                       act, _stream(stream)))
+    _check(_calls().fc_noalloc(a, w, bias, y, M, K, N, act, stream))
 
 
 def fc_noalloc_max_scratch_bytes() -> int:
@@ -248,34 +214,13 @@ def qconv2d_workspace_bytes(desc: ConvDesc) -> int:
 
 def qconv2d(x, xq: QParam, w, wq: QParam, bias, y, yq: QParam, desc: ConvDesc, act: int = ACT_NONE,
             workspace=None, stream=None) -> None:
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    _check(library().glowmi_qconv2d(_ptr(x, "int8", nx, "x"), xq, _ptr(w, "int8", nw, "w"), wq,
-                                    _ptr(bias, "int32", desc.k, "bias"), _ptr(y, "int8", ny, "y"), yq,
-                                    ctypes.byref(desc), act, wp, wb, _stream(stream)))
+    _check(_calls().qconv2d_chain(x, xq, w, wq, bias, y, yq, desc, None, None, act, workspace, stream))
 
 
 def conv2d_chain(x, w, bias, y, desc: ConvDesc, addend=None, act: int = ACT_NONE, workspace=None,
                  stream=None) -> None:
     """y = act(conv + bias + addend); addend is a float tensor of y's shape (may be y) or None."""
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    chain = Chain(_ptr(addend, "float32", ny, "addend"), QParam(1.0, 0), act)
-    _check(library().glowmi_conv2d_chain(_ptr(x, "float32", nx, "x"), _ptr(w, "float32", nw, "w"),
-                                         _ptr(bias, "float32", desc.k, "bias"), _ptr(y, "float32", ny, "y"),
-                                         ctypes.byref(desc), ctypes.byref(chain), wp, wb, _stream(stream)))
-
-
-def _planes(planes, need: int) -> Tuple[Optional[int], int]:
-    """Address and size of a plane buffer (any element type); it must hold `need` bytes when that is known."""
-    if planes is None:
-        return None, 0
-    if not planes.is_cuda or not planes.is_contiguous():
-        raise ValueError("planes: expected a contiguous device tensor")
-    have = planes.numel() * planes.element_size()
-    if need and have < need:
-        raise ValueError(f"planes: {have} bytes, the filter's planes take {need}")
-    return planes.data_ptr(), have
+    _check(_calls().conv2d_packed(x, w, None, bias, y, desc, addend, act, workspace, stream))
 
 
 def conv2d_filter_planes_bytes(desc: ConvDesc) -> int:
@@ -284,10 +229,7 @@ def conv2d_filter_planes_bytes(desc: ConvDesc) -> int:
 
 def conv2d_pack_filter(w, desc: ConvDesc, planes, stream=None) -> None:
     """Writes the fp16 planes of the filter `w` (made once, ahead of the calls that use them) to `planes`."""
-    _, nw, _ = _conv_counts(desc)
-    pp, pb = _planes(planes, 0)
-    _check(library().glowmi_conv2d_pack_filter(_ptr(w, "float32", nw, "w"), ctypes.byref(desc), pp, pb,
-                                               _stream(stream)))
+    _check(_calls().conv2d_pack_filter(w, desc, planes, stream))
 
 
 def conv2d_packed_workspace_bytes(desc: ConvDesc) -> int:
@@ -297,13 +239,7 @@ def conv2d_packed_workspace_bytes(desc: ConvDesc) -> int:
 def conv2d_packed(x, w, w_planes, bias, y, desc: ConvDesc, addend=None, act: int = ACT_NONE, workspace=None,
                   stream=None) -> None:
     """conv2d_chain with the filter's planes from conv2d_pack_filter (None: the plain call)."""
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    pp, _ = _planes(w_planes, conv2d_filter_planes_bytes(desc))
-    chain = Chain(_ptr(addend, "float32", ny, "addend"), QParam(1.0, 0), act)
-    _check(library().glowmi_conv2d_packed(_ptr(x, "float32", nx, "x"), _ptr(w, "float32", nw, "w"), pp,
-                                          _ptr(bias, "float32", desc.k, "bias"), _ptr(y, "float32", ny, "y"),
-                                          ctypes.byref(desc), ctypes.byref(chain), wp, wb, _stream(stream)))
+    _check(_calls().conv2d_packed(x, w, w_planes, bias, y, desc, addend, act, workspace, stream))
 
 
 def fc_filter_planes_bytes(K: int, N: int) -> int:
@@ -312,8 +248,7 @@ def fc_filter_planes_bytes(K: int, N: int) -> int:
 
 def fc_pack_filter(w, K: int, N: int, planes, stream=None) -> None:
     """Writes the fp16 planes of the [K][N] weight `w` (transposed to [N][K]) to `planes`."""
-    pp, pb = _planes(planes, 0)
-    _check(library().glowmi_fc_pack_filter(_ptr(w, "float32", K * N, "w"), K, N, pp, pb, _stream(stream)))
+    _check(_calls().fc_pack_filter(w, K, N, planes, stream))
 
 
 def fc_packed_workspace_bytes(M: int, K: int, N: int) -> int:
@@ -323,22 +258,13 @@ def fc_packed_workspace_bytes(M: int, K: int, N: int) -> int:
 def fc_packed(a, w, w_planes, bias, y, M: int, K: int, N: int, act: int = ACT_NONE, workspace=None,
               stream=None) -> None:
     """fc with the weight's planes from fc_pack_filter (None: the plain call)."""
-    wp, wb = _ws(workspace)
-    pp, _ = _planes(w_planes, fc_filter_planes_bytes(K, N))
-    _check(library().glowmi_fc_packed(_ptr(a, "float32", M * K, "a"), _ptr(w, "float32", K * N, "w"), pp,
-                                      _ptr(bias, "float32", N, "bias"), _ptr(y, "float32", M * N, "y"), M, K, N,
-                                      act, wp, wb, _stream(stream)))
+    _check(_calls().fc_packed(a, w, w_planes, bias, y, M, K, N, act, workspace, stream))
 
 
 def qconv2d_chain(x, xq: QParam, w, wq: QParam, bias, y, yq: QParam, desc: ConvDesc, addend=None,
                   addend_q: Optional[QParam] = None, act: int = ACT_NONE, workspace=None, stream=None) -> None:
     """Quantized form: addend is an int8 tensor of y's shape with scale/offset addend_q."""
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    chain = Chain(_ptr(addend, "int8", ny, "addend"), addend_q if addend_q is not None else QParam(1.0, 0), act)
-    _check(library().glowmi_qconv2d_chain(_ptr(x, "int8", nx, "x"), xq, _ptr(w, "int8", nw, "w"), wq,
-                                          _ptr(bias, "int32", desc.k, "bias"), _ptr(y, "int8", ny, "y"), yq,
-                                          ctypes.byref(desc), ctypes.byref(chain), wp, wb, _stream(stream)))
+    _check(_calls().qconv2d_chain(x, xq, w, wq, bias, y, yq, desc, addend, addend_q, act, workspace, stream))
 
 
 def chain_ops(ops, dtype: str = "float32", count: Optional[int] = None):
@@ -348,7 +274,7 @@ def chain_ops(ops, dtype: str = "float32", count: Optional[int] = None):
     for i, o in enumerate(ops):
         if o[0] == "add":
             q = o[2] if len(o) > 2 else QParam(1.0, 0)
-            arr[i] = ChainOp(OP_ADD_TENSOR, 0.0, 0.0, _ptr(o[1], dtype, count, f"op {i} tensor"), q)
+            arr[i] = ChainOp(OP_ADD_TENSOR, 0.0, 0.0, _calls().address(o[1], dtype, count, f"op {i} tensor"), q)
         elif o[0] == "mul":
             arr[i] = ChainOp(OP_MUL_SCALAR, o[1], 0.0, None, QParam(1.0, 0))
         elif o[0] == "max":
@@ -367,12 +293,7 @@ def conv2d_chainv_workspace_bytes(desc: ConvDesc, ops) -> int:
 
 def conv2d_chainv(x, w, bias, y, desc: ConvDesc, ops, workspace=None, stream=None) -> None:
     """y = ops applied in order to (conv + bias): a general stack of data-parallel operators."""
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    arr = chain_ops(ops, "float32", ny)
-    _check(library().glowmi_conv2d_chainv(_ptr(x, "float32", nx, "x"), _ptr(w, "float32", nw, "w"),
-                                          _ptr(bias, "float32", desc.k, "bias"), _ptr(y, "float32", ny, "y"),
-                                          ctypes.byref(desc), arr, len(ops), wp, wb, _stream(stream)))
+    _check(_calls().conv2d_chainv(x, w, bias, y, desc, ops, workspace, stream))
 
 
 def qconv2d_chainv_workspace_bytes(desc: ConvDesc, ops) -> int:
@@ -383,12 +304,7 @@ def qconv2d_chainv_workspace_bytes(desc: ConvDesc, ops) -> int:
 def qconv2d_chainv(x, xq: QParam, w, wq: QParam, bias, y, yq: QParam, desc: ConvDesc, ops, workspace=None,
                    stream=None) -> None:
     """Quantized general chain: the ops act on the int32 accumulator, then one requantize."""
-    wp, wb = _ws(workspace)
-    nx, nw, ny = _conv_counts(desc)
-    arr = chain_ops(ops, "int8", ny)
-    _check(library().glowmi_qconv2d_chainv(_ptr(x, "int8", nx, "x"), xq, _ptr(w, "int8", nw, "w"), wq,
-                                           _ptr(bias, "int32", desc.k, "bias"), _ptr(y, "int8", ny, "y"), yq,
-                                           ctypes.byref(desc), arr, len(ops), wp, wb, _stream(stream)))
+    _check(_calls().qconv2d_chainv(x, xq, w, wq, bias, y, yq, desc, ops, workspace, stream))
 
 
 def qfc_workspace_bytes(M: int, K: int, N: int) -> int:
@@ -397,10 +313,7 @@ def qfc_workspace_bytes(M: int, K: int, N: int) -> int:
 
 def qfc(a, aq: QParam, w, wq: QParam, bias, y, yq: QParam, M: int, K: int, N: int, act: int = ACT_NONE,
         workspace=None, stream=None) -> None:
-    wp, wb = _ws(workspace)
-    _check(library().glowmi_qfc(_ptr(a, "int8", M * K, "a"), aq, _ptr(w, "int8", K * N, "w"), wq,
-                                _ptr(bias, "int32", N, "bias"), _ptr(y, "int8", M * N, "y"), yq, M, K, N, act, wp,
-                                wb, _stream(stream)))
+    _check(_calls().qfc(a, aq, w, wq, bias, y, yq, M, K, N, act, workspace, stream))
 
 
 def requant_params(x_scale: float, w_scale: float, y_scale: float) -> Tuple[int, int]:
@@ -417,20 +330,16 @@ def rescale_params(r_scale: float, x_scale: float, w_scale: float) -> Tuple[int,
 
 def quantize(x, q, qp: QParam, count: Optional[int] = None, stream=None) -> None:
     """float32 device tensor x -> int8 device tensor q with scale/offset qp."""
-    n = x.numel() if count is None else count
-    _check(library().glowmi_quantize(_ptr(x, "float32", n, "x"), _ptr(q, "int8", n, "q"), n, qp, _stream(stream)))
+    _check(_calls().quantize(x, q, qp, count, stream))
 
 
 def dequantize(q, x, qp: QParam, count: Optional[int] = None, stream=None) -> None:
-    n = q.numel() if count is None else count
-    _check(library().glowmi_dequantize(_ptr(q, "int8", n, "q"), _ptr(x, "float32", n, "x"), n, qp, _stream(stream)))
+    _check(_calls().dequantize(q, x, qp, count, stream))
 
 
 def rescale(q_in, from_q: QParam, q_out, to_q: QParam, count: Optional[int] = None, stream=None) -> None:
     """The same real values on another scale/offset; q_out may be q_in."""
-    n = q_in.numel() if count is None else count
-    _check(library().glowmi_rescale(_ptr(q_in, "int8", n, "q_in"), from_q, _ptr(q_out, "int8", n, "q_out"), to_q, n,
-                                    _stream(stream)))
+    _check(_calls().rescale(q_in, from_q, q_out, to_q, count, stream))
 
 
 def fold_batchnorm(w, bias, gamma, beta, mean, var, eps: float):
@@ -455,8 +364,8 @@ def seq_layers(layers) -> "ctypes.Array":
         quantized = len(l) > 5
         wq, yq = (l[5], l[6]) if quantized else (QParam(1.0, 0), QParam(1.0, 0))
         _, nw, _ = _conv_counts(desc)
-        arr[i] = SeqLayer(desc, _ptr(w, "int8" if quantized else "float32", nw, f"layer {i} w"),
-                          _ptr(bias, "int32" if quantized else "float32", desc.k, f"layer {i} bias"), wq, yq, act,
+        arr[i] = SeqLayer(desc, _calls().address(w, "int8" if quantized else "float32", nw, f"layer {i} w"),
+                          _calls().address(bias, "int32" if quantized else "float32", desc.k, f"layer {i} bias"), wq, yq, act,
                           1 if add_input else 0)
     return arr
 
@@ -466,20 +375,8 @@ def seq_arena_bytes(arr, quantized: bool) -> int:
 
 
 def seq_conv2d(x, arr, y, arena, stream=None) -> None:
-    ap, ab = _ws(arena)
-    nx, _, _ = _conv_counts(arr[0].desc)
-    _, _, ny = _conv_counts(arr[len(arr) - 1].desc)
-    st = library().glowmi_seq_conv2d(_ptr(x, "float32", nx, "x"), arr, len(arr), _ptr(y, "float32", ny, "y"), ap, ab,
-                                     _stream(stream))
-    if st != 0:
-        raise GlowmiError(st, library().glowmi_last_error().decode() or "sequence rejected")
+    _check(_calls().seq_conv2d(x, arr, y, arena, stream))
 
 
 def seq_qconv2d(x, xq: QParam, arr, y, arena, stream=None) -> None:
-    ap, ab = _ws(arena)
-    nx, _, _ = _conv_counts(arr[0].desc)
-    _, _, ny = _conv_counts(arr[len(arr) - 1].desc)
-    st = library().glowmi_seq_qconv2d(_ptr(x, "int8", nx, "x"), xq, arr, len(arr), _ptr(y, "int8", ny, "y"), ap, ab,
-                                      _stream(stream))
-    if st != 0:
-        raise GlowmiError(st, library().glowmi_last_error().decode() or "sequence rejected")
+    _check(_calls().seq_qconv2d(x, xq, arr, y, arena, stream))
