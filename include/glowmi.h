@@ -279,7 +279,9 @@ glowmi_status glowmi_fc_packed(const float* a, const float* w, const void* w_pla
  *                                  in the mantissa/shift form of glowmi_chain (shift in [12, 62])
  *     at the end                   y = saturate(round(acc * s_final / y.scale) + y.offset) to [-128, 127]
  * Lists that are one of the fixed shapes ({}, {max 0}, {add}, {add, max 0}) give exactly the results of
- * glowmi_(q)conv2d(_chain) and take the same kernels; any other list runs on the generic tiled kernels.
+ * glowmi_(q)conv2d(_chain).  Those, and lists of at most one tensor add followed by any number of MAX / CLIP bounds
+ * (quantized: with multiplies anywhere), take every kernel the fixed chains take; any other list runs on the generic
+ * tiled kernels.
  * Errors: GLOWMI_ERR_UNSUPPORTED for n_ops > GLOWMI_MAX_CHAIN_OPS or an unknown kind, GLOWMI_ERR_NULL /
  * GLOWMI_ERR_ALIGN for a tensor, GLOWMI_ERR_QUANT for scalars or scales outside the stated ranges
  * (quantized) and GLOWMI_ERR_SHAPE for NaN scalars or a > b (fp32).  Workspace: at least

@@ -186,6 +186,13 @@ glowmi_status check_act(glowmi_act act) {
   return GLOWMI_OK;
 }
 
+// Relu is the clamp to [0, inf]; the kernels know only the bounds.
+void set_act(glowmi::Problem& p, glowmi_act act) {
+  p.act = act == GLOWMI_ACT_RELU ? 1 : 0;
+  p.act_lo = act == GLOWMI_ACT_RELU ? 0.0f : -INFINITY;
+  p.act_hi = INFINITY;
+}
+
 glowmi_status check_ptrs(const void* x, const void* w, const void* bias, const void* y) {
   if (!x || !w || !y) return fail(GLOWMI_ERR_NULL, "input, weight and output pointers must not be NULL");
   if (!aligned(x, 16) || !aligned(w, 16) || !aligned(y, 16))
@@ -238,6 +245,7 @@ glowmi_status quant_setup(glowmi::Problem& p, glowmi_qparam xq, glowmi_qparam wq
   p.x_off = xq.offset; p.w_off = wq.offset; p.y_off = yq.offset;
   p.mant = mant; p.shift = shift;
   p.lo = (act == GLOWMI_ACT_RELU && yq.offset > -128) ? yq.offset : -128;
+  p.hi = 127;
   return GLOWMI_OK;
 }
 
@@ -313,7 +321,7 @@ glowmi_status setup_fc_f32(const float* a, const float* w, const float* bias, fl
   if ((st = check_act(act)) != GLOWMI_OK) return st;
   fill_fc(p, M, K, N);
   if ((st = set_operand_bytes(p, (long long)M * K, (long long)K * N, 4)) != GLOWMI_OK) return st;
-  p.x = a; p.w = w; p.bias = bias; p.y = y; p.act = (int)act;
+  p.x = a; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
   return GLOWMI_OK;
 }
 
@@ -370,7 +378,7 @@ glowmi_status prepare_conv2d_chain(const float* x, const float* w, const float* 
   Problem& p = out->p;
   fill_conv(p, d, geo);
   if ((st = set_operand_bytes(p, geo.x_elems, geo.w_elems, 4)) != GLOWMI_OK) return st;
-  p.x = x; p.w = w; p.bias = bias; p.y = y; p.act = (int)act;
+  p.x = x; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
   p.w_packed = w_planes;
   p.addend = chain->addend;
   out->plan = plan_with_workspace(p, plan_f32, workspace, workspace_bytes);
@@ -394,7 +402,7 @@ glowmi_status prepare_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int
   fill_conv(p, d, geo);
   if ((st = set_operand_bytes(p, geo.x_elems, geo.w_elems, 1)) != GLOWMI_OK) return st;
   if ((st = quant_setup(p, xq, wq, yq, act)) != GLOWMI_OK) return st;
-  p.x = x; p.w = w; p.bias = bias; p.y = y; p.act = (int)act;
+  p.x = x; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
   if (chain->addend) {
     if (chain->addend_q.offset < -128 || chain->addend_q.offset > 127)
       return fail(GLOWMI_ERR_QUANT, "addend offset %d outside [-128, 127]", chain->addend_q.offset);
@@ -628,7 +636,7 @@ glowmi_status glowmi_qfc(const int8_t* a, glowmi_qparam aq, const int8_t* w, glo
   fill_fc(p, M, K, N);
   if ((st = set_operand_bytes(p, (long long)M * K, (long long)K * N, 1)) != GLOWMI_OK) return st;
   if ((st = quant_setup(p, aq, wq, yq, act)) != GLOWMI_OK) return st;
-  p.x = a; p.w = w; p.bias = bias; p.y = y; p.act = (int)act;
+  p.x = a; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
   const glowmi::Plan plan = plan_with_workspace(p, glowmi::plan_i8, workspace, workspace_bytes);
   const char* variant = "";
   return finish(glowmi::launch_i8(p, plan, stream, &variant), variant);
@@ -688,7 +696,7 @@ glowmi_status check_op_list(const glowmi_chain_op* ops, int32_t n) {
 glowmi_status fill_chain_f32(glowmi::Problem& p, const glowmi_chain_op* ops, int32_t n, const void* y, size_t y_bytes) {
   p.chain_n = n;
   p.addend = nullptr;
-  p.act = 0;
+  set_act(p, GLOWMI_ACT_NONE);
   for (int32_t i = 0; i < n; ++i) {
     glowmi::ChainOpDev& o = p.chain[i];
     o.kind = (int32_t)ops[i].kind;
@@ -730,7 +738,7 @@ glowmi_status fill_chain_i8(glowmi::Problem& p, const glowmi_chain_op* ops, int3
                             glowmi_qparam yq, const void* y, size_t y_bytes) {
   p.chain_n = n;
   p.addend = nullptr;
-  p.act = 0;
+  set_act(p, GLOWMI_ACT_NONE);
   p.lo = -128;
   double s = (double)xq.scale * (double)wq.scale;     // the accumulator's scale
   for (int32_t i = 0; i < n; ++i) {
@@ -780,6 +788,93 @@ glowmi_status fill_chain_i8(glowmi::Problem& p, const glowmi_chain_op* ops, int3
   return GLOWMI_OK;
 }
 
+// Lists that are "at most one tensor add, then bounds" are what the fixed chain's epilogues compute with the bounds of
+// the list in place of Relu's (a clip to [0, 6] behind a depthwise layer, an add and a clip at the end of a block), so
+// they take every kernel the fixed chains take.  Bounds in a row are one clamp.  In the quantized form a multiply only
+// changes the scale on the host, wherever it stands.
+bool add_then_bounds(const glowmi_chain_op* ops, int32_t n, bool quantized) {
+  bool bounded = false, added = false;
+  for (int32_t i = 0; i < n; ++i) switch (ops[i].kind) {
+      case GLOWMI_OP_ADD_TENSOR:
+        if (added || bounded) return false;
+        added = true;
+        break;
+      case GLOWMI_OP_MUL_SCALAR:
+        if (!quantized) return false;
+        break;
+      default: bounded = true;
+    }
+  return true;
+}
+
+// The clamp [*lo, *hi] followed by one more op of the list.
+template <typename T>
+void bound_more(int32_t kind, T a, T b, T* lo, T* hi) {
+  auto apply = [&](T v) {
+    v = v < a ? a : v;
+    return kind == GLOWMI_OP_CLIP && v > b ? b : v;
+  };
+  *lo = apply(*lo);
+  *hi = apply(*hi);
+}
+
+// Turn the filled op list of such a problem into the addend and the clamp of the fixed chains.
+void fold_chain_f32(glowmi::Problem& p) {
+  for (int32_t i = 0; i < p.chain_n; ++i) {
+    const glowmi::ChainOpDev& o = p.chain[i];
+    if (o.kind == GLOWMI_OP_ADD_TENSOR) {
+      p.addend = o.tensor;
+    } else {
+      p.act = 1;
+      bound_more(o.kind, o.a, o.b, &p.act_lo, &p.act_hi);
+    }
+  }
+  p.chain_n = 0;
+}
+
+// The code an accumulator value takes: requantizing is monotone, so bounds on the accumulator are bounds on the code.
+int32_t code_of(int32_t acc, const glowmi::Problem& p) {
+  const long long t = (((long long)acc * p.mant + (1LL << (p.shift - 1))) >> p.shift) + p.y_off;
+  return t < -128 ? -128 : t > 127 ? 127 : (int32_t)t;
+}
+
+void fold_chain_i8(glowmi::Problem& p) {
+  int32_t lo = INT32_MIN, hi = INT32_MAX;
+  for (int32_t i = 0; i < p.chain_n; ++i) {
+    const glowmi::ChainOpDev& o = p.chain[i];
+    if (o.kind == GLOWMI_OP_ADD_TENSOR) {
+      p.addend = o.tensor;
+      p.r_off = o.t_off; p.r_mant = o.t_mant; p.r_shift = o.t_shift;
+    } else if (o.kind != GLOWMI_OP_MUL_SCALAR) {
+      bound_more(o.kind, o.ia, o.ib, &lo, &hi);
+    }
+  }
+  p.lo = code_of(lo, p);
+  p.hi = code_of(hi, p);
+  p.chain_n = 0;
+}
+
+// What the planner has to know of an op list: a fixed chain's addend, or that the list is a general one.
+void describe_chain(glowmi::Problem& p, const glowmi_chain_op* ops, int32_t n, bool quantized) {
+  glowmi_chain chain;
+  if (fixed_shape(ops, n, &chain)) {
+    p.addend = chain.addend;
+  } else if (add_then_bounds(ops, n, quantized)) {
+    for (int32_t i = 0; i < n; ++i)
+      if (ops[i].kind == GLOWMI_OP_ADD_TENSOR) p.addend = ops[i].tensor ? ops[i].tensor : &kPlanesGiven;
+  } else {
+    p.chain_n = n;
+  }
+}
+
+// The variant's name says that the call came with an op list.
+glowmi_status finish_chainv(hipError_t e, const char* variant, bool folded) {
+  if (!folded) return finish(e, variant);
+  static thread_local char name[96];
+  snprintf(name, sizeof(name), "%s_chainv", variant);
+  return finish(e, name);
+}
+
 }  // namespace
 
 extern "C" {
@@ -787,12 +882,10 @@ extern "C" {
 size_t glowmi_conv2d_chainv_workspace_bytes(const glowmi_conv_desc* d, const glowmi_chain_op* ops, int32_t n_ops) {
   Geometry geo;
   if (check_desc(d, &geo) != GLOWMI_OK || check_op_list(ops, n_ops) != GLOWMI_OK) return 0;
-  glowmi_chain chain;
   glowmi::Problem p;
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;
-  if (fixed_shape(ops, n_ops, &chain)) p.addend = chain.addend;
-  else p.chain_n = n_ops;
+  describe_chain(p, ops, n_ops, false);
   return split_bytes(glowmi::plan_f32(p, true), p);
 }
 
@@ -811,20 +904,21 @@ glowmi_status glowmi_conv2d_chainv(const float* x, const float* w, const float* 
   if ((st = set_operand_bytes(p, geo.x_elems, geo.w_elems, 4)) != GLOWMI_OK) return st;
   p.x = x; p.w = w; p.bias = bias; p.y = y;
   if ((st = fill_chain_f32(p, ops, n_ops, y, (size_t)geo.y_elems * 4u)) != GLOWMI_OK) return st;
+  const bool folded = add_then_bounds(ops, n_ops, false);
+  if (folded) fold_chain_f32(p);
   const glowmi::Plan plan = plan_with_workspace(p, glowmi::plan_f32, workspace, workspace_bytes);
   const char* variant = "";
-  return finish(glowmi::launch_f32(p, plan, stream, &variant), variant);
+  const hipError_t e = glowmi::launch_f32(p, plan, stream, &variant);
+  return finish_chainv(e, variant, folded);
 }
 
 size_t glowmi_qconv2d_chainv_workspace_bytes(const glowmi_conv_desc* d, const glowmi_chain_op* ops, int32_t n_ops) {
   Geometry geo;
   if (check_desc(d, &geo) != GLOWMI_OK || check_op_list(ops, n_ops) != GLOWMI_OK) return 0;
-  glowmi_chain chain;
   glowmi::Problem p;
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 1) != GLOWMI_OK) return 0;
-  if (fixed_shape(ops, n_ops, &chain)) p.addend = chain.addend;
-  else p.chain_n = n_ops;
+  describe_chain(p, ops, n_ops, true);
   return split_bytes(glowmi::plan_i8(p, true), p);
 }
 
@@ -846,9 +940,12 @@ glowmi_status glowmi_qconv2d_chainv(const int8_t* x, glowmi_qparam xq, const int
   if ((st = quant_setup(p, xq, wq, yq, GLOWMI_ACT_NONE)) != GLOWMI_OK) return st;
   p.x = x; p.w = w; p.bias = bias; p.y = y;
   if ((st = fill_chain_i8(p, ops, n_ops, xq, wq, yq, y, (size_t)geo.y_elems)) != GLOWMI_OK) return st;
+  const bool folded = add_then_bounds(ops, n_ops, true);
+  if (folded) fold_chain_i8(p);
   const glowmi::Plan plan = plan_with_workspace(p, glowmi::plan_i8, workspace, workspace_bytes);
   const char* variant = "";
-  return finish(glowmi::launch_i8(p, plan, stream, &variant), variant);
+  const hipError_t e = glowmi::launch_i8(p, plan, stream, &variant);
+  return finish_chainv(e, variant, folded);
 }
 
 }  // extern "C"

@@ -110,6 +110,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
   v4f bv = {0.f, 0.f, 0.f, 0.f};
   if (bias) bv = v4f{bias[c0], bias[c0 + 1], bias[c0 + 2], bias[c0 + 3]};     // bias is only 4-byte aligned
   const bool relu = p.act == 1;
+  const float act_lo = p.act_lo, act_hi = p.act_hi;
   const unsigned col_bytes = (unsigned)p.c * 4u, row_bytes = (unsigned)p.w_ * col_bytes;
 
   for (unsigned run = (unsigned)slot; run < (unsigned)g.runs; run += (unsigned)g.slots) {
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
           for (int s = 0; s < 3; ++s) acc += x[ro * STRIDE + r][o * STRIDE + s] * w[r * 3 + s];
         if (relu) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], 0.f);
+          for (int e = 0; e < 4; ++e) acc[e] = clamp_act(acc[e], act_lo, act_hi);
         }
         if (rn.oh0 + ro < p.oh && rn.ow0 + o < p.ow)
           *reinterpret_cast<v4f*>(yrow + ((size_t)ro * p.ow + o) * p.k) = acc;
@@ -229,11 +230,11 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_i8_kernel(const Problem p,
             if (!PLAIN) xsum = __builtin_amdgcn_sdot4((int)three, 0x00010101, xsum, false);
           }
           if (PLAIN) {
-            q[e] = requantize_folded(acc, p.mant, fold, lo_v);
+            q[e] = requantize_folded(acc, p.mant, fold, lo_v, p.hi);
           } else {
             acc -= p.w_off * xsum;
-            q[e] = fast ? requantize_as<true>(acc, p.mant, p.shift, p.y_off, p.lo)
-                        : requantize_as<false>(acc, p.mant, p.shift, p.y_off, p.lo);
+            q[e] = fast ? requantize_as<true>(acc, p.mant, p.shift, p.y_off, p.lo, p.hi)
+                        : requantize_as<false>(acc, p.mant, p.shift, p.y_off, p.lo, p.hi);
           }
         }
         if (rn.oh0 + ro < p.oh && rn.ow0 + o < p.ow)

@@ -324,7 +324,7 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
             const size_t o = ((size_t)(img * p.oh + oy) * p.ow + ox) * p.k + ch;
             float v = join_sets(acc[i][j][e], acc_lo[i][j][e], sb) + bv;
             if (ADD) v += addend[o];
-            if (relu) v = fmaxf(v, 0.f);
+            if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
             Y[o] = v;
           }
         }

@@ -355,19 +355,19 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
         const bool ok = cok && oy < p.oh && ox < p.ow;
         if (ADD) {                                       // the same offsets as the addend's loads
           float v = keep[j][e] + bv + addv[e];
-          if (relu) v = fmaxf(v, 0.f);
+          if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
           const unsigned off = ok ? ((unsigned)((img * p.oh + oy) * p.ow + ox) * (unsigned)p.k + (unsigned)ch) * 4u : OOBX;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, off, 0, 0);
         } else if (EARLY) {                                     // always issued: the waits above count on it
           float v = keep[j][e] + bv;
-          if (relu) v = fmaxf(v, 0.f);
+          if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
           const unsigned off = ok ? ((unsigned)((img * p.oh + oy) * p.ow + ox) * (unsigned)p.k + (unsigned)ch) * 4u : OOBX;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, off, 0, 0);
         } else if (ok) {
           const size_t o = ((size_t)(img * p.oh + oy) * p.ow + ox) * p.k + ch;
           float v = keep[j][e] + bv;
           if (ADD) v += addend[o];
-          if (relu) v = fmaxf(v, 0.f);
+          if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
           Y[o] = v;
         }
       }

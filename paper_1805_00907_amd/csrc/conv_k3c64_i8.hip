@@ -249,8 +249,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void conv_k3c64_i8_kernel(const Prob
             if (ADD) {
               v += (unsigned)addlut[((unsigned)addq[nb][q4] >> (8 * t)) & 0xffu];
             }
-            q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v)
-                             : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo);
+            q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v, p.hi)
+                             : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo, p.hi);
           }
           out[q4] = (int)pack_codes(q[0], q[1], q[2], q[3]);
         }
@@ -492,8 +492,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void conv_k3c64_i8_tile_kernel(const
           for (int t = 0; t < 4; ++t) {
             unsigned v = (unsigned)acc[4 * q4 + t];
             if (ADD) v += (unsigned)addlut[((unsigned)addq[nb][q4] >> (8 * t)) & 0xffu];
-            q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v)
-                             : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo);
+            q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v, p.hi)
+                             : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo, p.hi);
           }
           out[q4] = (int)pack_codes(q[0], q[1], q[2], q[3]);
         }

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
 #pragma unroll
               for (int t = 0; t < 8; ++t) {
                 float v = join_sets(acc[i][j][8 * h + t], acc_lo[i][j][8 * h + t], sb) + bv + addv[t];
-                if (relu) v = fmaxf(v, 0.f);
+                if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
                 __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, offset_of(i, 8 * h + t), 0, 0);
               }
             }
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
                 const size_t o = ((size_t)(img * p.oh + oy) * p.ow + ox) * p.k + ch;
                 float v = join_sets(acc[i][j][4 * q + e4], acc_lo[i][j][4 * q + e4], sb) + bv;
                 if (ADD) v += addend[o];
-                if (relu) v = fmaxf(v, 0.f);
+                if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
                 Y[o] = v;
               }
               ++tp;

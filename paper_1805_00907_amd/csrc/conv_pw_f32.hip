@@ -93,7 +93,7 @@ __global__ __launch_bounds__(PW_THREADS, 1) void conv_pw_f32_kernel(const Proble
 
   const int ohow = p.oh * p.ow;
   const unsigned row_bytes = (unsigned)p.k * 4u;           // output pixel pitch
-  const float floor_value = p.act == 1 ? 0.f : -__builtin_inff();   // Relu as a lower bound
+  const float act_lo = p.act_lo, act_hi = p.act_hi;
 
   // (Measured and not kept: a second register set so that loads run two chunks ahead of the MFMAs --
   // 256 -> 64 on 56 x 56 at batch 32 49 -> 52 us, 128 -> 512 with the add link 47 -> 53 us: the loads
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(PW_THREADS, 1) void conv_pw_f32_kernel(const Proble
         asm volatile("" : "+v"(lane_off));                 // keep the per-register row offsets scalar
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const float v = fmaxf(acc[nb][e] + bv + (ADD ? addv[nb][e] : 0.f), floor_value);
+          const float v = clamp_act(acc[nb][e] + bv + (ADD ? addv[nb][e] : 0.f), act_lo, act_hi);
           const unsigned off = lane_off + (unsigned)((e >> 2) * 8 + (e & 3)) * row_bytes;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, off, 0, 0);
         }
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(PW_THREADS, 1) void conv_pw_f32_bf16_kernel(const P
 
   const int ohow = p.oh * p.ow;
   const unsigned row_bytes = (unsigned)p.k * 4u;
-  const float floor_value = p.act == 1 ? 0.f : -__builtin_inff();
+  const float act_lo = p.act_lo, act_hi = p.act_hi;
 
   // Staging of one chunk: load i of a lane covers pixel 8i + lane/8 of the block, 16 bytes at channel
   // chunk*32 + 4*(lane%8): eight whole 128-byte runs per instruction.
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(PW_THREADS, 1) void conv_pw_f32_bf16_kernel(const P
         asm volatile("" : "+v"(lane_off));                 // keep the per-register row offsets scalar
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const float v = fmaxf(acc[nb][e] + bv + (ADD ? addv[nb][e] : 0.f), floor_value);
+          const float v = clamp_act(acc[nb][e] + bv + (ADD ? addv[nb][e] : 0.f), act_lo, act_hi);
           const unsigned off = lane_off + (unsigned)((e >> 2) * 8 + (e & 3)) * row_bytes;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, off, 0, 0);
         }

@@ -239,8 +239,8 @@ __global__ __launch_bounds__(PWQ_THREADS, PwQ<K>::WG_PER_CU) void conv_pw_i8_ker
               if (ADD) {
                 v += (unsigned)addlut[((unsigned)addq[nb][q4] >> (8 * t)) & 0xffu];
               }
-              q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v)
-                               : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo);
+              q[t] = MODE == 2 ? requantize_folded((int)v, p.mant, fold, lo_v, p.hi)
+                               : requantize_as<MODE == 1>((int)v, p.mant, p.shift, p.y_off, p.lo, p.hi);
             }
             out[q4] = (int)pack_codes(q[0], q[1], q[2], q[3]);
           }

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(CS_THREADS, 1) void conv_small_f32_kernel(const Pro
     if (bias) v += v4f{bias[c0], bias[c0 + 1], bias[c0 + 2], bias[c0 + 3]};   // bias is only 4-byte aligned
     if (p.act == 1) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = fmaxf(v[t], 0.f);
+      for (int t = 0; t < 4; ++t) v[t] = clamp_act(v[t], p.act_lo, p.act_hi);
     }
     *reinterpret_cast<v4f*>(Y + (size_t)m * p.k + c0) = v;
   }

@@ -214,7 +214,7 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
         for (int e = 0; e < 16; ++e) {
           const int drow = e >> 3, dcol = (e & 3) + 8 * ((e >> 2) & 1);
           float v = acc[i][e] + bv;
-          if (p.act == 1) v = fmaxf(v, 0.f);
+          if (p.act == 1) v = clamp_act(v, p.act_lo, p.act_hi);
           const bool ok = dcol < cols_left && drow < rows_left;
           const unsigned soff = (unsigned)((drow * p.ow + dcol) * p.k) * 4u;   // uniform
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, ok ? base : 0x80000000u, soff, 0);
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
         for (int e = 0; e < 16; ++e) {
           const int drow = e >> 3, dcol = (e & 3) + 8 * ((e >> 2) & 1);
           float v = join_sets(acc[i][e], acc_lo[i][e], sb) + bv;
-          if (p.act == 1) v = fmaxf(v, 0.f);
+          if (p.act == 1) v = clamp_act(v, p.act_lo, p.act_hi);
           const bool ok = dcol < cols_left && drow < rows_left;
           const unsigned soff = (unsigned)((drow * p.ow + dcol) * p.k) * 4u;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, ok ? base : 0x80000000u, soff, 0);

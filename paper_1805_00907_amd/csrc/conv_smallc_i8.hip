@@ -287,8 +287,8 @@ __global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Pro
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const int v = acc[nb][4 * q4 + t];
-            q[t] = MODE == 2 ? requantize_folded(v, p.mant, fold, lo_v)
-                             : requantize_as<MODE == 1>(v, p.mant, p.shift, p.y_off, p.lo);
+            q[t] = MODE == 2 ? requantize_folded(v, p.mant, fold, lo_v, p.hi)
+                             : requantize_as<MODE == 1>(v, p.mant, p.shift, p.y_off, p.lo, p.hi);
           }
           out[q4] = (int)pack_codes(q[0], q[1], q[2], q[3]);
         }

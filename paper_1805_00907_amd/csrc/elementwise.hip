@@ -84,8 +84,8 @@ __global__ __launch_bounds__(EW_THREADS) void rescale_kernel(const signed char* 
                                                             int out_offset) {
   const long long groups = count / EW_PER_THREAD;
   auto one = [&](int code) {
-    return shift >= 33 ? requantize_as<true>(code - in_offset, mant, shift, out_offset, -128)
-                       : requantize_as<false>(code - in_offset, mant, shift, out_offset, -128);   // uniform
+    return shift >= 33 ? requantize_as<true>(code - in_offset, mant, shift, out_offset, -128, 127)
+                       : requantize_as<false>(code - in_offset, mant, shift, out_offset, -128, 127);   // uniform
   };
   for (long long g = (long long)blockIdx.x * EW_THREADS + threadIdx.x; g < groups;
        g += (long long)gridDim.x * EW_THREADS) {

@@ -178,8 +178,8 @@ __global__ __launch_bounds__(FS_THREADS, 1) void fc_small_i8_kernel(const Proble
       const int n = n0 + c0 + t;
       v += rowterm - (unsigned)p.x_off * (unsigned)wsum[c0 + t];
       if (bias && n < N) v += (unsigned)bias[n];
-      q[t] = p.shift >= 33 ? requantize_as<true>((int)v, p.mant, p.shift, p.y_off, p.lo)
-                           : requantize_as<false>((int)v, p.mant, p.shift, p.y_off, p.lo);   // uniform
+      q[t] = p.shift >= 33 ? requantize_as<true>((int)v, p.mant, p.shift, p.y_off, p.lo, p.hi)
+                           : requantize_as<false>((int)v, p.mant, p.shift, p.y_off, p.lo, p.hi);   // uniform
     }
     // N % 4 == 0: a group of four columns is wholly inside or outside
     if (m < M && n0 + c0 < N)

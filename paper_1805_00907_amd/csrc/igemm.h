@@ -96,13 +96,14 @@ struct Problem {
   int32_t slabs_per_split;  // reduction slabs each split walks
   FastDiv div_ohow, div_ow, div_cg, div_s;   // divisors oh*ow, ow, cg, s
   uint32_t x_bytes, w_bytes; // sizes of the input and weight tensors (hardware-checked buffer loads)
-  int32_t act;              // 0 none, 1 relu
+  int32_t act;              // 0 none, 1 the value is clamped to [act_lo, act_hi] (Relu: [0, inf])
+  float act_lo, act_hi;     // -inf, inf with act == 0
   int32_t b_is_kn;          // FC weight layout
   int32_t allow_pack;       // the caller's workspace may hold repacked operands (fp32 three-piece form)
   // quantized form only
   int32_t x_off, w_off, y_off;
   int32_t mant, shift;      // requantize multiplier
-  int32_t lo;               // lower clamp bound
+  int32_t lo, hi;           // clamp bounds of the output code
   int32_t r_off, r_mant, r_shift;   // quantized addend: its offset and the multiplier that brings a
                                     // code difference to the accumulator's scale, mant * 2^-shift
   // general chain (chain_n > 0): replaces addend/act; only the generic 64 x 64 tiled kernels and the
@@ -110,6 +111,12 @@ struct Problem {
   int32_t chain_n;
   ChainOpDev chain[kMaxChainOps];
 };
+
+#if defined(__HIPCC__)
+// The activation of an fp32 epilogue: one instruction whatever the bounds (Relu is [0, inf]); a NaN takes the lower
+// bound, as max and min against the bounds in turn would give it.
+__device__ __forceinline__ float clamp_act(float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); }
+#endif
 
 // Which kernel family a call takes, and how the reduction is split over workgroups.  The ABI layer
 // plans ONCE per call (with the workspace the caller gave in mind) and hands the plan to the launcher.

@@ -392,7 +392,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_f32_kernel(const
           const int r = i * 32 + (e >> 2) * 8 + (e & 3);          // compile-time row inside the wave tile
           float v = (LONGK ? total[i][j][e] : acc[i][j][e]) + bv + addv[e];
           const bool inside = full || (cok && row_base + r < p.M);
-          if (relu) v = fmaxf(v, 0.f);
+          if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
           if (inside) dst[(size_t)r * p.k] = v;
         }
       }
@@ -469,7 +469,7 @@ template <int W>
 __global__ __launch_bounds__(256) void splitk_finish_f32(const float* __restrict__ partial,
                                                          const float* __restrict__ bias,
                                                          const float* addend, float* y, int total, int k,
-                                                         int split_k, int act) {
+                                                         int split_k, int act, float lo, float hi) {
   typedef float vec __attribute__((ext_vector_type(W)));
   const int groups = total / W;                      // W divides total (the launcher checks)
   for (int gi = blockIdx.x * blockDim.x + threadIdx.x; gi < groups; gi += gridDim.x * blockDim.x) {
@@ -490,7 +490,7 @@ __global__ __launch_bounds__(256) void splitk_finish_f32(const float* __restrict
     if (addend) v += *reinterpret_cast<const vec*>(addend + i);
     if (act == 1) {
 #pragma unroll
-      for (int e = 0; e < W; ++e) v[e] = fmaxf(v[e], 0.f);
+      for (int e = 0; e < W; ++e) v[e] = clamp_act(v[e], lo, hi);
     }
     *reinterpret_cast<vec*>(y + i) = v;
   }
@@ -835,7 +835,7 @@ hipError_t launch_splitk_finish_f32(const Problem& p, const Plan& plan, hipStrea
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, stream,
                      static_cast<const float*>(p.partial), static_cast<const float*>(p.bias),
                      static_cast<const float*>(p.addend),
-                     static_cast<float*>(p.y), total, p.k, plan.split_k, p.act);
+                     static_cast<float*>(p.y), total, p.k, plan.split_k, p.act, p.act_lo, p.act_hi);
   return hipGetLastError();
 }
 

@@ -527,7 +527,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
       const int r = (e >> 2) * 8 + (e & 3);               // compile-time row inside the 32-row block
       float v = keep[j][e] + bv + addv[e];
       const bool inside = full || (cok && row_base + r < p.M);
-      if (relu) v = fmaxf(v, 0.f);
+      if (relu) v = clamp_act(v, p.act_lo, p.act_hi);
       if (inside) dst[(size_t)r * p.k] = v;
     }
   }

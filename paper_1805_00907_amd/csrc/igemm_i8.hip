@@ -55,9 +55,9 @@ __device__ __forceinline__ int sum_bytes(int packed) {   // sum of the four sign
   return __builtin_amdgcn_sdot4(packed, 0x01010101, 0, false);
 }
 
-__device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo) {
-  return shift >= 33 ? requantize_as<true>(acc, mant, shift, y_off, lo)
-                     : requantize_as<false>(acc, mant, shift, y_off, lo);   // uniform branch
+__device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo, int hi) {
+  return shift >= 33 ? requantize_as<true>(acc, mant, shift, y_off, lo, hi)
+                     : requantize_as<false>(acc, mant, shift, y_off, lo, hi);   // uniform branch
 }
 
 // The ops of a general chain on one int32 accumulator value (quantized form: a scalar multiply only
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
               const int code = (row < p.M && col < p.kg) ? (int)addend[(size_t)row * p.k + g * p.kg + col] : p.r_off;
               v += rescale_term(code - p.r_off, p.r_mant, p.r_shift);
             }
-            packed |= ((unsigned)requantize(v, p.mant, p.shift, p.y_off, p.lo) & 0xffu) << (t * 8);
+            packed |= ((unsigned)requantize(v, p.mant, p.shift, p.y_off, p.lo, p.hi) & 0xffu) << (t * 8);
           }
           *reinterpret_cast<unsigned*>(out + lr * OUT_PITCH + lc) = packed;
         }
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) void splitk_finish_i8(const int* __restrict__ 
                                                         const signed char* addend, int r_off, int r_mant,
                                                         int r_shift, signed char* y, int total, int k,
                                                         int split_k, int mant, int shift, int y_off,
-                                                        int lo) {
+                                                        int lo, int hi) {
   typedef unsigned vec __attribute__((ext_vector_type(W)));
   const int groups = total / W;                      // W divides total (the launcher checks)
   for (int gi = blockIdx.x * blockDim.x + threadIdx.x; gi < groups; gi += gridDim.x * blockDim.x) {
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(256) void splitk_finish_i8(const int* __restrict__ 
     for (int e = 0; e < W; ++e) {
       unsigned a = v[e];
       if (addend) a += (unsigned)rescale_term((int)addend[i + e] - r_off, r_mant, r_shift);
-      q[e] = requantize((int)a, mant, shift, y_off, lo);
+      q[e] = requantize((int)a, mant, shift, y_off, lo, hi);
     }
     if (W == 4) {
       *reinterpret_cast<unsigned*>(y + i) = pack_codes(q[0], q[1], q[2], q[3]);
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(256) void splitk_finish_chain_i8(const Problem p, i
     for (int s = 0; s < p.split_k; ++s) a += (unsigned)partial[(size_t)s * total + i];
     if (bias) a += (unsigned)bias[i % p.k];
     const int v = apply_chain_i8(p, (int)a, (size_t)i);
-    y[i] = (signed char)requantize(v, p.mant, p.shift, p.y_off, p.lo);
+    y[i] = (signed char)requantize(v, p.mant, p.shift, p.y_off, p.lo, p.hi);
   }
 }
 
@@ -643,7 +643,7 @@ hipError_t launch_i8(const Problem& p_in, const Plan& plan, hipStream_t stream, 
                        static_cast<const int*>(p.partial), static_cast<const int*>(p.bias),
                        static_cast<const signed char*>(p.addend), p.r_off, p.r_mant, p.r_shift,
                        static_cast<signed char*>(p.y), total, p.k, plan.split_k, p.mant, p.shift,
-                       p.y_off, p.lo);
+                       p.y_off, p.lo, p.hi);
     e = hipGetLastError();
   }
   return e;

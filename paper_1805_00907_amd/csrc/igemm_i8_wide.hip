@@ -51,9 +51,9 @@ __device__ __forceinline__ int sum4(int packed, int acc) {   // acc + the four s
   return __builtin_amdgcn_sdot4(packed, 0x01010101, acc, false);
 }
 
-__device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo) {
-  return shift >= 33 ? requantize_as<true>(acc, mant, shift, y_off, lo)
-                     : requantize_as<false>(acc, mant, shift, y_off, lo);   // uniform branch
+__device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo, int hi) {
+  return shift >= 33 ? requantize_as<true>(acc, mant, shift, y_off, lo, hi)
+                     : requantize_as<false>(acc, mant, shift, y_off, lo, hi);   // uniform branch
 }
 
 // PADDED: some filter tap of some pixel may fall on padding (otherwise the per-tap tests are dropped).
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_
             const int code = live ? (int)(signed char)(rcodes >> (8 * t)) : p.r_off;
             v += rescale_term(code - p.r_off, p.r_mant, p.r_shift);
           }
-          q[t] = requantize(v, p.mant, p.shift, p.y_off, p.lo);
+          q[t] = requantize(v, p.mant, p.shift, p.y_off, p.lo, p.hi);
         }
         *reinterpret_cast<unsigned*>(out + lr * OUT_PITCH + lc) = pack_codes(q[0], q[1], q[2], q[3]);
       }

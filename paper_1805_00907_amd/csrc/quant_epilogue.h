@@ -6,13 +6,13 @@
 
 namespace glowmi {
 
-// round_half_up(acc * mant / 2^shift) + y_off, clamped to [lo, 127].
+// round_half_up(acc * mant / 2^shift) + y_off, clamped to [lo, hi].
 // With P = acc * mant = hi * 2^32 + lo32 and shift >= 33 the rounding constant 2^(shift-1) is a
 // multiple of 2^32, so (P + 2^(shift-1)) >> shift == (hi + 2^(shift-33)) >> (shift-32) exactly:
 // one 32-bit multiply-high instead of 64-bit arithmetic.  That covers every multiplier below 1/4
 // (the usual case); larger multipliers take the 64-bit form.  FAST is uniform over a launch.
 template <bool FAST>
-__device__ __forceinline__ int requantize_as(int acc, int mant, int shift, int y_off, int lo) {
+__device__ __forceinline__ int requantize_as(int acc, int mant, int shift, int y_off, int lo, int hi) {
   int q;
   if (FAST) {
     q = (__mulhi(acc, mant) + (1 << (shift - 33))) >> (shift - 32);
@@ -25,7 +25,7 @@ __device__ __forceinline__ int requantize_as(int acc, int mant, int shift, int y
   }
   q += y_off;
   q = q < lo ? lo : q;
-  q = q > 127 ? 127 : q;
+  q = q > hi ? hi : q;
   return q;
 }
 
@@ -33,7 +33,7 @@ __device__ __forceinline__ int requantize_as(int acc, int mant, int shift, int y
 // addend  K = 2^(shift-33) + y_off * 2^(shift-32):
 //   ((hi + 2^(shift-33)) >> (shift-32)) + y_off == (hi + K) >> (shift-32)
 // exactly (a multiple of 2^(shift-32) added before an arithmetic shift adds that multiple of one
-// after it), and |hi| < 2^30, |K| < 2^30, so the sum cannot overflow.  The clamp to [lo, 127] is one
+// after it), and |hi| < 2^30, |K| < 2^30, so the sum cannot overflow.  The clamp to [lo, hi] is one
 // median-of-three; the compiler does not form it from a variable lower bound, hence the asm (VOP3
 // reads at most one scalar register here, so `lo` comes in a vector register).
 struct FoldedRequant {
@@ -47,10 +47,10 @@ __device__ __forceinline__ FoldedRequant make_folded_requant(int shift, int y_of
   f.K = (1 << (f.s - 1)) + y_off * (1 << f.s);
   return f;
 }
-__device__ __forceinline__ int requantize_folded(int acc, int mant, const FoldedRequant& f, int lo_vgpr) {
+__device__ __forceinline__ int requantize_folded(int acc, int mant, const FoldedRequant& f, int lo_vgpr, int hi) {
   const int q = (__mulhi(acc, mant) + f.K) >> f.s;
   int r;
-  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(q), "v"(lo_vgpr), "s"(127));
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(q), "v"(lo_vgpr), "s"(hi));
   return r;
 }
 
