@@ -9,12 +9,20 @@
 // are collected with dot-product instructions while the tiles are staged.  Everything after the
 // accumulator is integer arithmetic, so results are reproducible bit for bit.
 //
-// Tiling mirrors the fp32 kernel: BM x BN output tile per workgroup of 4 or 8 wavefronts, reduction
-// slabs of 128 codes staged in double-buffered LDS as K-contiguous rows of 128 + 16 pad bytes
-// (conflict-free ds_read_b128), XCD-aware workgroup order.  The MFMA is issued with the filter
-// fragment as its row operand, so a lane ends up with four consecutive output channels of one
-// pixel: they are requantized, packed into one dword, transposed through LDS and leave the chip as
-// 16-byte stores along the channel axis.
+// Tiling: BM x BN output tile per workgroup of 4 or 8 wavefronts, reduction slabs of 128 codes staged in
+// double-buffered LDS as K-contiguous rows of 128 + 16 pad bytes (conflict-free ds_read_b128), XCD-aware
+// workgroup order.  The MFMA is issued with the filter fragment as its row operand, so a lane ends up with
+// four consecutive output channels of one pixel: they are requantized, packed into one dword, transposed
+// through LDS and leave the chip as 16-byte stores along the channel axis.
+//
+// The reduction is walked in 16-code chunks that never straddle a filter tap: a tap has ceil(cg / 16) chunks,
+// the last one with cg % 16 codes (or 16).  One load then fetches a chunk at any channel count: 16 bytes at
+// whatever byte address the pixel's channels start, the bytes past the tap's channels belonging to the next
+// pixel (filter: the next tap) and meeting zeros on the filter side, which is masked while it is staged.  The
+// form before this one packed taps densely and gathered channel counts that are not a multiple of 16 byte by byte
+// (16 loads and as many tap steps per chunk): 3x3 72->120 on 33x45 at batch 5 took 31.6 us.
+// Two slabs are in flight in registers while a third is multiplied: with six to ten slabs per tile, which is
+// what most of these layers have, a load's latency per slab was most of the kernel.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -26,6 +34,7 @@
 namespace glowmi {
 namespace {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -34,25 +43,62 @@ constexpr int LDQ = BKQ + 16;            // LDS row pitch in bytes (36 dwords: c
 constexpr int KV = BKQ / 16;             // 16-byte chunks per K-contiguous row
 constexpr int INVALID_ROW = -(1 << 24);
 
-struct Tap {
+constexpr unsigned OOB = 0x80000000u;    // beyond any int8 tensor the library accepts: loads give zeros
+
+// Position of a chunk in the reduction: filter row and column, first channel.
+struct Chunk {
   int r, s, c;
-  __device__ void init(int kg, int cg, int S, const FastDiv& dcg, const FastDiv& ds) {
-    const int t = dcg.div(kg);
-    c = kg - t * cg;
-    r = ds.div(t);
-    s = t - r * S;
-  }
-  __device__ void advance(int step, int cg, int S) {
-    c += step;
-    while (c >= cg) {
-      c -= cg;
-      if (++s == S) { s = 0; ++r; }
-    }
+};
+// How the launch walks tiles and chunks, divided out on the host: a division by a number the compiler does not know
+// is about forty dependent instructions, and a kernel of a few microseconds had ten of them before its first load.
+struct Walk {
+  FastDiv div_tiles_n, div_tiles_m, div_groups, div_cpt;
+  int tiles_n, tiles_m, total_work;
+  int cpt, chunks;                       // chunks per tap, chunks of the reduction
+  int padded;                            // some row of some tile has taps outside the image, or lies past M
+  int dr, ds, dc;                        // one step of a wavefront group = (dr * S + ds) taps and dc channels
+  __device__ void step(Chunk& k, int S) const {   // one carry per digit
+    k.c += dc;
+    const bool wc = k.c >= cpt * 16;
+    k.c -= wc ? cpt * 16 : 0;
+    k.s += ds + (wc ? 1 : 0);
+    const bool ws = k.s >= S;
+    k.s -= ws ? S : 0;
+    k.r += dr + (ws ? 1 : 0);
   }
 };
 
-__device__ __forceinline__ int sum_bytes(int packed) {   // sum of the four signed bytes
-  return __builtin_amdgcn_sdot4(packed, 0x01010101, 0, false);
+// 16 bytes shifted down by `over` bytes (0..16), zeros from above.
+__device__ __forceinline__ v4i shift_down(v4i v, unsigned over) {
+  const unsigned q = over >> 2, b = over & 3u;
+  int d[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    int x = 0;
+#pragma unroll
+    for (int j = i; j < 4; ++j) x = (int)q == j - i ? v[j] : x;
+    d[i] = x;
+  }
+  return v4i{(int)__builtin_amdgcn_alignbyte((unsigned)d[1], (unsigned)d[0], b), (int)__builtin_amdgcn_alignbyte((unsigned)d[2], (unsigned)d[1], b),
+             (int)__builtin_amdgcn_alignbyte((unsigned)d[3], (unsigned)d[2], b), (int)__builtin_amdgcn_alignbyte(0u, (unsigned)d[3], b)};
+}
+
+// Mask of the first `valid` bytes (any integer; at least 16 keeps all) of 16.
+__device__ __forceinline__ v4i byte_mask(int valid) {
+  v4i m;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = valid - 4 * i;
+    m[i] = n >= 4 ? -1 : n <= 0 ? 0 : (int)((1u << (8 * n)) - 1u);
+  }
+  return m;
+}
+
+// acc plus the signed bytes of v (ones = 0x01010101), or acc (ones = 0)
+__device__ __forceinline__ int sum_bytes(v4i v, int ones, int acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_sdot4(v[i], ones, acc, false);
+  return acc;
 }
 
 __device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo, int hi) {
@@ -74,10 +120,15 @@ __device__ __forceinline__ int apply_chain_i8(const Problem& p, int v, size_t of
   return v;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool VEC, bool B_KN, bool CHAINV = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const Problem p, int tiles_m,
-                                                                         int tiles_n, int total_work) {
-  constexpr int NTHREADS = 64 * WAVES_M * WAVES_N;
+// KGRP groups of WAVES_M x WAVES_N wavefronts share a tile: group i multiplies slabs i, i + KGRP, ... in LDS buffers of
+// its own and the partial tiles are summed through LDS at the end, every group finishing its share of the outputs.
+// A grid that leaves a wavefront or two per SIMD spends a slab's time on the latency of its ~150 instructions, not
+// on issuing them, so the chain of slabs is what has to get shorter (3x3 72->120 on 33x45 at batch 5, 232 tiles of
+// six slabs: 10.6 us with one group).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KGRP, bool B_KN, bool CHAINV = false>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M * WAVES_N) <= (B_KN ? 1024 : 2048) ? 4 : 2) void igemm_i8_kernel(const Problem p, const Walk walk) {
+  constexpr int NTHREADS = 64 * WAVES_M * WAVES_N;      // of one group
+  constexpr int ALL_THREADS = NTHREADS * KGRP;
   constexpr int ROWS_PER_PASS = NTHREADS / KV;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -88,29 +139,38 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
   constexpr int B_UNITS = (BKQ / 4) * (BN / 4);         // FC weight: 4k x 4n byte blocks per slab
   constexpr int B_UPT = B_UNITS / NTHREADS;             // blocks per thread
   static_assert(B_UNITS % NTHREADS == 0, "FC weight tile does not divide over the threads");
+  static_assert(A_PASSES + B_PASSES <= 8, "four bits per load in one register");
   constexpr int A_BYTES = BM * LDQ, B_BYTES = BN * LDQ;
   constexpr int OUT_PITCH = BN + 16;                    // output tile staged in LDS, bytes per pixel row
-  static_assert(2 * (A_BYTES + B_BYTES) >= BM * OUT_PITCH + (BM + 2 * BN) * 4, "epilogue reuses the staging LDS");
+  constexpr int XCH = KGRP > 1 ? KGRP * BM * BN * 4 : 0;  // partial tiles of the groups
+  static_assert(2 * KGRP * (A_BYTES + B_BYTES) >= XCH + BM * OUT_PITCH + (BM + 2 * BN) * 4, "epilogue reuses the staging LDS");
+  static_assert(KGRP == 1 || (TM == 1 && TN == 1), "the groups share the outputs of one MFMA block per wavefront");
 
   extern __shared__ __align__(16) unsigned char ldsq[];
 
   const int per_xcd = gridDim.x >> 3;
   const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (w >= total_work) return;
-  const int tn = w % tiles_n;
-  int t_ = w / tiles_n;
-  const int tm = t_ % tiles_m;
-  t_ /= tiles_m;
-  const int g = t_ % p.groups;
-  const int split = t_ / p.groups;
+  if (w >= walk.total_work) return;
+  int t_ = walk.div_tiles_n.div(w);
+  const int tn = w - t_ * walk.tiles_n;
+  int t2_ = walk.div_tiles_m.div(t_);
+  const int tm = t_ - t2_ * walk.tiles_m;
+  const int split = walk.div_groups.div(t2_);
+  const int g = t2_ - split * p.groups;
 
-  const int tid = threadIdx.x;
+  const int all_tid = threadIdx.x;
+  const int grp = KGRP > 1 ? __builtin_amdgcn_readfirstlane(all_tid / NTHREADS) : 0;
+  const int tid = KGRP > 1 ? all_tid % NTHREADS : all_tid;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
-  const signed char* __restrict__ X = static_cast<const signed char*>(p.x);
-  const signed char* __restrict__ Wt = static_cast<const signed char*>(p.w);
+  // A 16-byte load at the end of a tensor of any size stays inside the 16-byte block of its last byte.
+  const unsigned x_size = p.x_bytes < 16u ? 16u : p.x_bytes, w_size = p.w_bytes < 16u ? 16u : p.w_bytes;
+  const __amdgpu_buffer_rsrc_t rsrc_x =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)x_size, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, (int)w_size, 0x00020000);
 
   const int kvec = tid % KV;
   const int row0 = tid / KV;
@@ -136,23 +196,43 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
     }
   }
 
+  const int cpt = walk.cpt, chunks = walk.chunks;
   const int slab_begin = split * p.slabs_per_split;
-  const int total_slabs = (p.Kgemm + BKQ - 1) / BKQ;
+  const int total_slabs = (chunks + KV - 1) / KV;
   int slab_end = slab_begin + p.slabs_per_split;
   if (slab_end > total_slabs) slab_end = total_slabs;
-  int k_hi = slab_end * BKQ;
-  if (k_hi > p.Kgemm) k_hi = p.Kgemm;
-  const int k_count = k_hi - slab_begin * BKQ;          // codes this split really reduces over
+  auto codes_before = [&](int chunk) {                  // reduction codes in the chunks before this one
+    if (chunk >= chunks) return p.Kgemm;
+    const int t = walk.div_cpt.div(chunk), c0 = (chunk - t * cpt) * 16;
+    return t * p.cg + c0;
+  };
+  const int k_count = codes_before(slab_end * KV) - codes_before(slab_begin * KV);   // codes this split really reduces over
 
-  Tap tap;
-  tap.init(slab_begin * BKQ + kvec * 16, p.cg, p.s, p.div_cg, p.div_s);
+  Chunk at;                                             // of the next slab to load
+  {
+    const int j = (slab_begin + grp) * KV + kvec;
+    const int t = walk.div_cpt.div(j);
+    at.c = (j - t * cpt) * 16;
+    at.r = p.div_s.div(t);
+    at.s = t - at.r * p.s;
+  }
 
-  const int xo_byte = p.x_off & 0xff;
-  const int xo_fill = xo_byte * 0x01010101;             // padding = the code of real zero
+  const int xo_fill = (p.x_off & 0xff) * 0x01010101;    // padding = the code of real zero
   const bool need_xsum = p.w_off != 0;
+  const bool padded = walk.padded != 0;                 // some tap of some pixel falls on padding (or a row lies past M)
+  const bool ragged = p.cg % 16 != 0;                   // a tap's last chunk has cg % 16 codes: the bytes of those
+  const v4i short_mask = byte_mask(p.cg % 16);
+  // Chunks that run past the end of a tensor (its last pixel's, or last filter's, short chunk) are fetched from its last
+  // 16 bytes and shifted: only tiles that see that pixel or filter look for them.
+  const bool at_end = p.cg % 16 != 0 && (tm * BM + BM > p.M - (p.r * p.ow + p.s) || tn * BN + BN >= p.kg);
 
-  v4i ra[A_PASSES];
-  v4i rb[B_KN ? B_UPT : B_PASSES];
+  struct Stage {                                        // one slab on its way to LDS
+    v4i a[A_PASSES], b[B_KN ? B_UPT : B_PASSES];
+    unsigned inside;                                    // bit q: the tap of row q lies inside the image; SHORT, PAST
+    unsigned over;                                      // 4 bits per load: bytes to shift down
+  };
+  constexpr unsigned SHORT = 1u << 30, PAST = 1u << 31; // the chunk is a tap's short last one, lies past the reduction
+  Stage st[2];
   int asum[A_PASSES];                                   // running sum of staged input codes per row
   int bsum[B_KN ? B_UPT * 4 : B_PASSES];                // running sum of staged filter codes
 #pragma unroll
@@ -160,112 +240,134 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
 #pragma unroll
   for (int q = 0; q < (B_KN ? B_UPT * 4 : B_PASSES); ++q) bsum[q] = 0;
 
-  auto load_global = [&](int slab) {
-    const int kg0 = slab * BKQ + kvec * 16;
-    if (VEC) {
-      const bool kok = kg0 < p.Kgemm;                   // Kgemm % 16 == 0 on this path
-      const int tap_off = (tap.r * p.w_ + tap.s) * p.c + tap.c;
+  auto load_global = [&](int slab, Stage& sg) {
+    const bool kok = at.r < p.r;                        // past the last tap: nothing of this chunk counts
+    const int tap_off = (at.r * p.w_ + at.s) * p.c + at.c;
+    sg.inside = (at.c + 16 > p.cg ? SHORT : 0u) | (kok ? 0u : PAST);
+    sg.over = 0;
+    unsigned off[A_PASSES];
+    if (padded) {
 #pragma unroll
       for (int q = 0; q < A_PASSES; ++q) {
-        const int ih = a_ih0[q] + tap.r, iw = a_iw0[q] + tap.s;
-        const bool inside = (unsigned)ih < (unsigned)p.h && (unsigned)iw < (unsigned)p.w_;
-        if (!kok) ra[q] = v4i{0, 0, 0, 0};
-        else if (inside) ra[q] = *reinterpret_cast<const v4i*>(X + a_base[q] + tap_off);
-        else ra[q] = v4i{xo_fill, xo_fill, xo_fill, xo_fill};
+        const int ih = a_ih0[q] + at.r, iw = a_iw0[q] + at.s;
+        const bool in = kok && (unsigned)ih < (unsigned)p.h && (unsigned)iw < (unsigned)p.w_;
+        sg.inside |= in ? 1u << q : 0u;
+        off[q] = in ? (unsigned)(a_base[q] + tap_off) : OOB;
       }
     } else {
-      Tap t = tap;
 #pragma unroll
-      for (int q = 0; q < A_PASSES; ++q) ra[q] = v4i{0, 0, 0, 0};
+      for (int q = 0; q < A_PASSES; ++q) off[q] = kok ? (unsigned)(a_base[q] + tap_off) : OOB;
+    }
+    if (at_end) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const bool kok = kg0 + e < p.Kgemm;
-        const int tap_off = (t.r * p.w_ + t.s) * p.c + t.c;
-#pragma unroll
-        for (int q = 0; q < A_PASSES; ++q) {
-          const int ih = a_ih0[q] + t.r, iw = a_iw0[q] + t.s;
-          const bool inside = (unsigned)ih < (unsigned)p.h && (unsigned)iw < (unsigned)p.w_;
-          int v = 0;
-          if (kok) v = inside ? ((int)X[a_base[q] + tap_off] & 0xff) : xo_byte;
-          ra[q][e >> 2] |= v << ((e & 3) * 8);
-        }
-        t.advance(1, p.cg, p.s);
+      for (int q = 0; q < A_PASSES; ++q) {
+        const unsigned last = x_size - 16u, o = off[q] != OOB && off[q] > last ? off[q] - last : 0u;
+        off[q] -= o;
+        sg.over |= o << (4 * q);
       }
     }
+#pragma unroll
+    for (int q = 0; q < A_PASSES; ++q) sg.a[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off[q], 0, 0);
     if (!B_KN) {
+      const unsigned koff = (unsigned)((at.r * p.s + at.s) * p.cg + at.c);
 #pragma unroll
       for (int q = 0; q < B_PASSES; ++q) {
         const int n = tn * BN + row0 + q * ROWS_PER_PASS;
-        const bool nok = n < p.kg;
-        const signed char* src = Wt + (size_t)(g * p.kg + n) * p.Kgemm + kg0;
-        if (VEC) {
-          rb[q] = (nok && kg0 < p.Kgemm) ? *reinterpret_cast<const v4i*>(src) : v4i{0, 0, 0, 0};
-        } else {
-          rb[q] = v4i{0, 0, 0, 0};
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int v = (nok && kg0 + e < p.Kgemm) ? ((int)src[e] & 0xff) : 0;
-            rb[q][e >> 2] |= v << ((e & 3) * 8);
-          }
+        unsigned o = kok && n < p.kg ? (unsigned)(g * p.kg + n) * (unsigned)p.Kgemm + koff : OOB;
+        if (at_end) {
+          const unsigned last = w_size - 16u, over = o != OOB && o > last ? o - last : 0u;
+          o -= over;
+          sg.over |= over << (4 * (A_PASSES + q));
         }
+        sg.b[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, o, 0, 0);
       }
     } else {
-      // FC weight [Kgemm][k], N contiguous: each thread takes 4 k-rows x 4 columns and transposes
-      // the 4x4 byte block so that every column becomes one dword of 4 consecutive k.
+      // FC weight [Kgemm][k], N contiguous: each thread takes 4 k-rows x 4 columns.  Columns past the last one: the
+      // row's last four, shifted (their results are not stored).
 #pragma unroll
       for (int q = 0; q < B_UPT; ++q) {
         const int u = tid + q * NTHREADS;
         const int ng = u % (BN / 4), kgp = u / (BN / 4);
         const int col = tn * BN + ng * 4;
-        int d[4];
+        if (p.k >= 4) {
+          const unsigned c4 = (unsigned)(col <= p.k - 4 ? col : p.k - 4);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const int kgr = slab * BKQ + kgp * 4 + kk;
-          const signed char* src = Wt + (size_t)kgr * p.k + col;
-          if (kgr >= p.Kgemm) d[kk] = 0;
-          else if (VEC) d[kk] = col < p.k ? *reinterpret_cast<const int*>(src) : 0;
-          else {
-            d[kk] = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (col + e < p.k) d[kk] |= ((int)src[e] & 0xff) << (e * 8);
+          for (int kk = 0; kk < 4; ++kk) {
+            const int kgr = slab * BKQ + kgp * 4 + kk;
+            sg.b[q][kk] = __builtin_amdgcn_raw_buffer_load_b32(rsrc_w, kgr < p.Kgemm ? (unsigned)kgr * (unsigned)p.k + c4 : OOB, 0, 0);
           }
-        }
+        } else {
 #pragma unroll
-        for (int nn = 0; nn < 4; ++nn) {
-          int o = 0;
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) o |= ((d[kk] >> (nn * 8)) & 0xff) << (kk * 8);
-          rb[q][nn] = o;
+          for (int kk = 0; kk < 4; ++kk) {
+            const int kgr = slab * BKQ + kgp * 4 + kk;
+            int d = 0;
+            for (int e = 0; e < p.k; ++e)
+              d |= (int)__builtin_amdgcn_raw_buffer_load_b8(rsrc_w, kgr < p.Kgemm && col == 0 ? (unsigned)(kgr * p.k + e) : OOB, 0, 0) << (8 * e);
+            sg.b[q][kk] = d;
+          }
         }
       }
     }
+    walk.step(at, p.s);
   };
 
-  auto store_lds = [&](int buf) {
-    unsigned char* As = ldsq + buf * (A_BYTES + B_BYTES);
+  auto store_lds = [&](int buf, Stage& sg, bool live) {
+    const int ones = live ? 0x01010101 : 0;              // uniform
+    v4i mask = {-1, -1, -1, -1};                         // (past the reduction the filter's loads gave zeros)
+    if (ragged) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mask[e] = sg.inside & SHORT ? short_mask[e] : -1;
+    }
+    unsigned char* As = ldsq + (grp * 2 + buf) * (A_BYTES + B_BYTES);
     unsigned char* Bs = As + A_BYTES;
 #pragma unroll
     for (int q = 0; q < A_PASSES; ++q) {
-      *reinterpret_cast<v4i*>(As + (row0 + q * ROWS_PER_PASS) * LDQ + kvec * 16) = ra[q];
-      if (need_xsum)
-        asum[q] += sum_bytes(ra[q][0]) + sum_bytes(ra[q][1]) + sum_bytes(ra[q][2]) + sum_bytes(ra[q][3]);
+      v4i v = sg.a[q];
+      if (at_end) v = shift_down(v, (sg.over >> (4 * q)) & 15u);
+      if (padded) {
+        const bool in = sg.inside & (1u << q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : xo_fill;
+      }
+      if (need_xsum) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = sg.inside & PAST ? 0 : v[e] & mask[e];
+        asum[q] = sum_bytes(v, ones, asum[q]);
+      }
+      *reinterpret_cast<v4i*>(As + (row0 + q * ROWS_PER_PASS) * LDQ + kvec * 16) = v;
     }
     if (!B_KN) {
 #pragma unroll
       for (int q = 0; q < B_PASSES; ++q) {
-        *reinterpret_cast<v4i*>(Bs + (row0 + q * ROWS_PER_PASS) * LDQ + kvec * 16) = rb[q];
-        bsum[q] += sum_bytes(rb[q][0]) + sum_bytes(rb[q][1]) + sum_bytes(rb[q][2]) + sum_bytes(rb[q][3]);
+        v4i v = sg.b[q];
+        if (at_end) v = shift_down(v, (sg.over >> (4 * (A_PASSES + q))) & 15u);
+        if (ragged) v &= mask;
+        *reinterpret_cast<v4i*>(Bs + (row0 + q * ROWS_PER_PASS) * LDQ + kvec * 16) = v;
+        bsum[q] = sum_bytes(v, ones, bsum[q]);
       }
     } else {
+      // transpose the 4 x 4 byte block: every column becomes one dword of 4 consecutive k
 #pragma unroll
       for (int q = 0; q < B_UPT; ++q) {
         const int u = tid + q * NTHREADS;
         const int ng = u % (BN / 4), kgp = u / (BN / 4);
+        const int col = tn * BN + ng * 4;
+        v4i d = sg.b[q];
+        if (p.k >= 4 && col > p.k - 4) {
+          const int sh = col - (p.k - 4) < 4 ? 8 * (col - (p.k - 4)) : 31;
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) d[kk] = (int)((unsigned)d[kk] >> sh);
+        }
+        const unsigned t0 = __builtin_amdgcn_perm((unsigned)d[1], (unsigned)d[0], 0x05010400u);
+        const unsigned t1 = __builtin_amdgcn_perm((unsigned)d[3], (unsigned)d[2], 0x05010400u);
+        const unsigned t2 = __builtin_amdgcn_perm((unsigned)d[1], (unsigned)d[0], 0x07030602u);
+        const unsigned t3 = __builtin_amdgcn_perm((unsigned)d[3], (unsigned)d[2], 0x07030602u);
+        const v4i o = {(int)__builtin_amdgcn_perm(t1, t0, 0x05040100u), (int)__builtin_amdgcn_perm(t1, t0, 0x07060302u),
+                       (int)__builtin_amdgcn_perm(t3, t2, 0x05040100u), (int)__builtin_amdgcn_perm(t3, t2, 0x07060302u)};
 #pragma unroll
         for (int nn = 0; nn < 4; ++nn) {
-          *reinterpret_cast<int*>(Bs + (ng * 4 + nn) * LDQ + kgp * 4) = rb[q][nn];
-          bsum[q * 4 + nn] += sum_bytes(rb[q][nn]);
+          *reinterpret_cast<int*>(Bs + (ng * 4 + nn) * LDQ + kgp * 4) = o[nn];
+          bsum[q * 4 + nn] = __builtin_amdgcn_sdot4(o[nn], ones, bsum[q * 4 + nn], false);
         }
       }
     }
@@ -284,7 +386,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
   const int lhalf = lane >> 5;
 
   auto compute = [&](int buf) {
-    const unsigned char* As = ldsq + buf * (A_BYTES + B_BYTES);
+    const unsigned char* As = ldsq + (grp * 2 + buf) * (A_BYTES + B_BYTES);
     const unsigned char* Bs = As + A_BYTES;
 #pragma unroll
     for (int k32 = 0; k32 < BKQ / 32; ++k32) {
@@ -304,32 +406,66 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
     }
   };
 
+  // A group's slab number n is in its LDS buffer n % 2 while slab n + 1 waits in stage (n + 1) % 2 and slab n + 2 is being
+  // fetched into the stage slab n came from.  No load sits in a branch whose paths join while it is in flight (the
+  // compiler would wait for all of them there): a full pair of slabs per trip, then the one to three that are left.  The
+  // groups run in step; where group 0 has one slab more the others stage it too, without summing or multiplying it.
   if (slab_begin < slab_end) {
-    load_global(slab_begin);
-    store_lds(0);
-    __syncthreads();
-    int buf = 0;
-    for (int slab = slab_begin; slab < slab_end; ++slab) {
-      const bool more = slab + 1 < slab_end;
-      if (more) {
-        tap.advance(BKQ, p.cg, p.s);
-        load_global(slab + 1);
-      }
-      compute(buf);
-      if (more) store_lds(buf ^ 1);
+    int slab = slab_begin + grp;
+    int left = (slab_end - slab_begin + KGRP - 1) / KGRP;
+    auto advance = [&](int u, bool store) {              // multiply the slab in LDS, stage the one after it
+      if (KGRP == 1 || slab < slab_end) compute(u);
+      if (store) store_lds(u ^ 1, st[u ^ 1], KGRP == 1 || slab + KGRP < slab_end);
       __syncthreads();
-      buf ^= 1;
+      slab += KGRP;
+      --left;
+    };
+    load_global(slab, st[0]);
+    if (left > 1) {
+      load_global(slab + KGRP, st[1]);
+      store_lds(0, st[0], true);
+      __syncthreads();
+      while (left > 3) {
+        load_global(slab + 2 * KGRP, st[0]);
+        advance(0, true);
+        load_global(slab + 2 * KGRP, st[1]);
+        advance(1, true);
+      }
+      if (left == 3) {
+        load_global(slab + 2 * KGRP, st[0]);
+        advance(0, true);
+        advance(1, true);
+        advance(0, false);
+      } else {
+        advance(0, true);
+        advance(1, false);
+      }
+    } else {
+      store_lds(0, st[0], KGRP == 1 || slab < slab_end);
+      __syncthreads();
+      advance(0, false);
     }
   }
 
   // ---- epilogue.  LDS (staging buffers are free now):
   //   out   [BM][OUT_PITCH] bytes : requantized tile, pixel-major
   //   xsum  [BM] int, wsum [BN] int : code sums;  cterm [BN] int : per-channel additive term
-  unsigned char* out = ldsq;
-  int* xsum = reinterpret_cast<int*>(ldsq + BM * OUT_PITCH);
+  //   and, with several groups, their partial tiles ahead of it: [group][four registers][wavefront's lanes] of int4
+  if constexpr (KGRP > 1) {
+    v4i* xch = reinterpret_cast<v4i*>(ldsq);
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      v4i v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = acc[0][0][q4 * 4 + t];
+      xch[(grp * 4 + q4) * NTHREADS + tid] = v;
+    }
+  }
+  unsigned char* out = ldsq + XCH;
+  int* xsum = reinterpret_cast<int*>(out + BM * OUT_PITCH);
   int* wsum = xsum + BM;
   int* cterm = wsum + BN;
-  for (int i = tid; i < BM + BN; i += NTHREADS) xsum[i] = 0;
+  for (int i = all_tid; i < BM + BN; i += ALL_THREADS) xsum[i] = 0;
   __syncthreads();
   if (need_xsum) {
 #pragma unroll
@@ -351,13 +487,27 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
   // The correction terms are combined modulo 2^32 (unsigned): each may exceed the final value, the
   // true accumulator fits int32 by contract, so the wrapped sum is exact.
   const int* __restrict__ bias = static_cast<const int*>(p.bias);
-  for (int i = tid; i < BN; i += NTHREADS) {
+  for (int i = all_tid; i < BN; i += ALL_THREADS) {
     const int col = tn * BN + i;
     unsigned ct = (unsigned)k_count * (unsigned)(p.x_off * p.w_off) - (unsigned)p.x_off * (unsigned)wsum[i];
     if (p.split_k == 1 && bias && col < p.kg) ct += (unsigned)bias[g * p.kg + col];
     cterm[i] = (int)ct;
   }
   __syncthreads();
+
+  // this thread's outputs: with several groups, registers 4 q4 .. 4 q4 + 3 for the q4 of its group, summed over the groups
+  constexpr int Q4S = 4 / KGRP;
+  if constexpr (KGRP > 1) {
+    const v4i* xch = reinterpret_cast<const v4i*>(ldsq);
+#pragma unroll
+    for (int i = 0; i < Q4S; ++i) {
+      v4i v = {0, 0, 0, 0};
+#pragma unroll
+      for (int k = 0; k < KGRP; ++k) v += xch[(k * 4 + grp * Q4S + i) * NTHREADS + tid];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[0][0][i * 4 + t] = v[t];
+    }
+  }
 
   const signed char* addend = static_cast<const signed char*>(p.addend);   // may be the output itself
   if (p.split_k == 1) {
@@ -369,8 +519,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int lc = wn * WTN + j * 32 + q4 * 8 + lhalf * 4;      // first of 4 consecutive channels
+        for (int q4 = 0; q4 < Q4S; ++q4) {
+          const int lc = wn * WTN + j * 32 + (grp * Q4S + q4) * 8 + lhalf * 4;   // first of 4 consecutive channels
           const v4i ct = *reinterpret_cast<const v4i*>(cterm + lc);
           unsigned packed = 0;
 #pragma unroll
@@ -394,15 +544,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
     // copy out: 16 bytes of one pixel row per thread and pass
     signed char* __restrict__ Y = static_cast<signed char*>(p.y);
     constexpr int CHUNKS = BN / 16;
-    const bool wide = (p.kg % 16 == 0) && (p.k % 16 == 0);
-    for (int u = tid; u < BM * CHUNKS; u += NTHREADS) {
+    const int align = (p.kg | p.k) & 15;                             // rows start at multiples of its lowest set bit
+    for (int u = all_tid; u < BM * CHUNKS; u += ALL_THREADS) {
       const int lr = u / CHUNKS, ch = u % CHUNKS;
       const int row = tm * BM + lr, col = tn * BN + ch * 16;
       if (row >= p.M || col >= p.kg) continue;
       signed char* dst = Y + (size_t)row * p.k + g * p.kg + col;
       const unsigned char* src = out + lr * OUT_PITCH + ch * 16;
-      if (wide) {
+      if (align == 0) {
         *reinterpret_cast<v4i*>(dst) = *reinterpret_cast<const v4i*>(src);
+      } else if ((align & 7) == 0) {
+        for (int e = 0; e < 16 && col + e < p.kg; e += 8)
+          *reinterpret_cast<v2i*>(dst + e) = *reinterpret_cast<const v2i*>(src + e);
+      } else if ((align & 3) == 0) {
+        for (int e = 0; e < 16 && col + e < p.kg; e += 4)
+          *reinterpret_cast<int*>(dst + e) = *reinterpret_cast<const int*>(src + e);
       } else {
         for (int e = 0; e < 16 && col + e < p.kg; ++e) dst[e] = (signed char)src[e];
       }
@@ -417,8 +573,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_i8_kernel(const 
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int lc = wn * WTN + j * 32 + (e >> 2) * 8 + lhalf * 4 + (e & 3);
+        for (int e = 0; e < 4 * Q4S; ++e) {
+          const int lc = wn * WTN + j * 32 + (grp * Q4S + (e >> 2)) * 8 + lhalf * 4 + (e & 3);
           const int col = tn * BN + lc;
           if (row >= p.M || col >= p.kg) continue;
           part[((size_t)split * p.M + row) * p.k + g * p.kg + col] =
@@ -486,37 +642,54 @@ __global__ __launch_bounds__(256) void splitk_finish_chain_i8(const Problem p, i
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool VEC, bool B_KN, bool CHAINV = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KGRP, bool B_KN, bool CHAINV = false>
 hipError_t launch_variant(const Problem& p, const Plan& plan, hipStream_t stream) {
-  auto kern = igemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, VEC, B_KN, CHAINV>;
-  constexpr int lds_bytes = 2 * (BM + BN) * LDQ;
-  constexpr int nthreads = 64 * WAVES_M * WAVES_N;
+  auto kern = igemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, KGRP, B_KN, CHAINV>;
+  constexpr int lds_bytes = 2 * KGRP * (BM + BN) * LDQ;
+  constexpr int nthreads = 64 * WAVES_M * WAVES_N * KGRP;
   // once per instantiation; initialisation of a function-local static is thread-safe
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
   if (attr_status != hipSuccess) return attr_status;
   const long long total_work = (long long)plan.tiles_m * plan.tiles_n * p.groups * plan.split_k;
   const long long grid_x = ((total_work + 7) / 8) * 8;
+  Walk walk;
+  walk.div_tiles_n = make_fastdiv((uint32_t)plan.tiles_n);
+  walk.div_tiles_m = make_fastdiv((uint32_t)plan.tiles_m);
+  walk.div_groups = make_fastdiv((uint32_t)p.groups);
+  walk.cpt = (p.cg + 15) / 16;
+  walk.div_cpt = make_fastdiv((uint32_t)walk.cpt);
+  walk.tiles_n = plan.tiles_n;
+  walk.tiles_m = plan.tiles_m;
+  walk.total_work = (int)total_work;
+  walk.chunks = p.r * p.s * walk.cpt;
+  walk.padded = p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h + p.r > p.h || (p.ow - 1) * p.stride_w + p.s > p.w_ ||
+                p.M % BM != 0;
+  const int step = KV * KGRP, taps = step / walk.cpt;
+  walk.dc = (step - taps * walk.cpt) * 16;
+  walk.dr = taps / p.s;
+  walk.ds = taps - walk.dr * p.s;
   dim3 grid((unsigned)grid_x, 1, 1), block(nthreads, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, (int)total_work);
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, walk);
   return hipGetLastError();
 }
 
-struct TileI8 { int bm, bn, wm, wn; const char* name; };
+struct TileI8 { int bm, bn, wm, wn, kgrp; const char* name; };
 constexpr TileI8 kTilesI8[] = {
-    {64, 64, 2, 2, "64x64w4"},       // 0: default
-    {128, 64, 4, 2, "128x64w8"},     // 1
-    {128, 128, 2, 4, "128x128w8"},   // 2
-    {128, 128, 2, 2, "128x128w4"},   // 3
+    {64, 64, 2, 2, 1, "64x64w4"},       // 0: default
+    {128, 64, 4, 2, 1, "128x64w8"},     // 1
+    {128, 128, 2, 4, 1, "128x128w8"},   // 2
+    {128, 128, 2, 2, 1, "128x128w4"},   // 3
+    {0, 0, 0, 0, 0, ""}, {0, 0, 0, 0, 0, ""},   // 4, 5: the kernel for large contractions, 128 x 128 and 128 x 64
+    {64, 64, 2, 2, 2, "64x64w4k2"},     // 6
+    {64, 64, 2, 2, 4, "64x64w4k4"},     // 7
 };
 constexpr int kNumTilesI8 = sizeof(kTilesI8) / sizeof(kTilesI8[0]);
 
-template <int BM, int BN, int WM, int WN>
-hipError_t launch_tile(const Problem& p, const Plan& plan, hipStream_t stream, bool fc, bool vec) {
-  if (fc) return vec ? launch_variant<BM, BN, WM, WN, true, true>(p, plan, stream)
-                     : launch_variant<BM, BN, WM, WN, false, true>(p, plan, stream);
-  return vec ? launch_variant<BM, BN, WM, WN, true, false>(p, plan, stream)
-             : launch_variant<BM, BN, WM, WN, false, false>(p, plan, stream);
+template <int BM, int BN, int WM, int WN, int KGRP>
+hipError_t launch_tile(const Problem& p, const Plan& plan, hipStream_t stream, bool fc) {
+  return fc ? launch_variant<BM, BN, WM, WN, KGRP, true>(p, plan, stream)
+            : launch_variant<BM, BN, WM, WN, KGRP, false>(p, plan, stream);
 }
 
 }  // namespace
@@ -541,9 +714,9 @@ Plan plan_i8(const Problem& p, bool allow_split) {
     if (fc_small_i8_applicable(p)) { pl.kernel = KERNEL_FC_SMALL; return pl; }
   }
   pl.bk = BKQ;
-  pl.slabs = (p.Kgemm + BKQ - 1) / BKQ;
+  pl.slabs = (p.r * p.s * ((p.cg + 15) / 16) + KV - 1) / KV;
   int tile = 0;
-  if (forced >= 0 && forced < kNumTilesI8) tile = forced;
+  if (forced >= 0 && forced < kNumTilesI8 && kTilesI8[forced].bm > 0) tile = forced;
   // Large contractions (deep reduction, enough pixels and channels for 128-wide tiles) take the
   // kernel built for them.
   if (wide_i8_applicable(p)) {
@@ -556,6 +729,18 @@ Plan plan_i8(const Problem& p, bool allow_split) {
       return plan_wide_i8(p, (!p.b_is_kn && t128 <= 256) ? 64 : 128, allow_split);
     }
   }
+  if (forced < 0) {
+    const long long t64 = (long long)((p.M + 63) / 64) * ((p.kg + 63) / 64) * p.groups;
+    const long long t128 = (long long)((p.M + 127) / 128) * ((p.kg + 127) / 128) * p.groups;
+    // up to about one 64 x 64 tile per CU: several wavefront groups per tile, the chain of slabs is what counts (3x3 72->120 on
+    // 33x45 at batch 5, 232 tiles: 10.4 us with one group, 8.2 with two; FC 76x808x208, 8 tiles: 12.0, 9.6, 8.9 with four);
+    // at twice that many tiles the groups only take each other's room (3x3 19->119 on 68x94 at batch 3, 600 tiles: 10.6 -> 14.2)
+    if (t64 <= 320 && pl.slabs >= 2) tile = pl.slabs >= 8 ? 7 : 6;
+    // many tiles: the larger ones read each operand fewer times (3x3 120->128 on 56x56 at batch 16: 33 us with 64 x 64 tiles,
+    // 26 us with 128 x 128; 1x1 344->176 stride 2 on 85x86 at batch 11, three slabs: 11.1 -> 10.1 us with 128 x 64)
+    else if (!p.b_is_kn && t128 >= 256 && p.kg > 64 && pl.slabs >= 4) tile = 2;
+    else if (t64 >= 900) tile = 1;
+  }
   pl.tile = tile;
   pl.bm = kTilesI8[tile].bm;
   pl.bn = kTilesI8[tile].bn;
@@ -566,9 +751,11 @@ Plan plan_i8(const Problem& p, bool allow_split) {
   const long long t = (long long)pl.tiles_m * pl.tiles_n * p.groups;
   // Split the reduction when the tiles alone cannot fill the chip: among the split factors that keep
   // at least four slabs per workgroup, the smallest that fills >= 90 % of the resident-workgroup
-  // slots of its last round, else the one that fills them best.
-  constexpr long long slots = 1024;
-  if (allow_split && t < slots && pl.slabs >= 8) {
+  // slots of its last round, else the one that fills them best.  The second kernel a split needs costs more than three
+  // microseconds, about as much as four wavefront groups take for twenty slabs.
+  const long long slots = 1024 / kTilesI8[tile].kgrp;
+  const int min_slabs = kTilesI8[tile].kgrp > 1 ? 21 : 8;
+  if (allow_split && t < slots && pl.slabs >= min_slabs) {
     int max_split = pl.slabs / 4 < 64 ? pl.slabs / 4 : 64;
     if (t >= 256 && max_split > p.Kgemm / 3072) max_split = p.Kgemm / 3072;   // int32 partials are 4x the output
     int best = 1;
@@ -581,6 +768,11 @@ Plan plan_i8(const Problem& p, bool allow_split) {
       const double u = (double)blocks / (double)(((blocks + slots - 1) / slots) * slots);
       if (u > best_u + 1e-9) { best_u = u; best = sk; }
       if (u >= 0.9) { best = sk; break; }
+    }
+    if (knob_is_set(KNOB_I8_SPLIT)) {                      // experiments: clamped to what the slabs allow
+      best = knob(KNOB_I8_SPLIT);
+      if (best < 1) best = 1;
+      if (best > max_split) best = max_split;
     }
     if (best > 1) {
       pl.slabs_per_split = (pl.slabs + best - 1) / best;
@@ -604,25 +796,24 @@ hipError_t launch_i8(const Problem& p_in, const Plan& plan, hipStream_t stream, 
   p.split_k = plan.split_k;
   p.slabs_per_split = plan.slabs_per_split;
   const bool fc = p.b_is_kn != 0;
-  const bool vec = fc ? (p.Kgemm % 16 == 0 && p.k % 4 == 0) : (p.cg % 16 == 0 && p.c % 16 == 0);
   hipError_t e;
   if (plan.kernel == KERNEL_WIDE) {
     e = launch_wide_i8(p, plan, stream, variant);
   } else if (p.chain_n > 0) {
     if (fc || plan.tile != 0) return hipErrorInvalidValue;
-    *variant = vec ? "igemm_i8_64x64w4_conv_vec_chainv" : "igemm_i8_64x64w4_conv_scalar_chainv";
-    e = vec ? launch_variant<64, 64, 2, 2, true, false, true>(p, plan, stream)
-            : launch_variant<64, 64, 2, 2, false, false, true>(p, plan, stream);
+    *variant = "igemm_i8_64x64w4_conv_chainv";
+    e = launch_variant<64, 64, 2, 2, 1, false, true>(p, plan, stream);
   } else {
     static thread_local char name[64];
-    snprintf(name, sizeof(name), "igemm_i8_%s_%s_%s", kTilesI8[plan.tile].name, fc ? "fc" : "conv",
-             vec ? "vec" : "scalar");
+    snprintf(name, sizeof(name), "igemm_i8_%s_%s", kTilesI8[plan.tile].name, fc ? "fc" : "conv");
     *variant = name;
     switch (plan.tile) {
-      case 0: e = launch_tile<64, 64, 2, 2>(p, plan, stream, fc, vec); break;
-      case 1: e = launch_tile<128, 64, 4, 2>(p, plan, stream, fc, vec); break;
-      case 2: e = launch_tile<128, 128, 2, 4>(p, plan, stream, fc, vec); break;
-      case 3: e = launch_tile<128, 128, 2, 2>(p, plan, stream, fc, vec); break;
+      case 0: e = launch_tile<64, 64, 2, 2, 1>(p, plan, stream, fc); break;
+      case 1: e = launch_tile<128, 64, 4, 2, 1>(p, plan, stream, fc); break;
+      case 2: e = launch_tile<128, 128, 2, 4, 1>(p, plan, stream, fc); break;
+      case 3: e = launch_tile<128, 128, 2, 2, 1>(p, plan, stream, fc); break;
+      case 6: e = launch_tile<64, 64, 2, 2, 2>(p, plan, stream, fc); break;
+      case 7: e = launch_tile<64, 64, 2, 2, 4>(p, plan, stream, fc); break;
       default: return hipErrorInvalidValue;
     }
   }
