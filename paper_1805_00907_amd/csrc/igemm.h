@@ -19,7 +19,7 @@ namespace glowmi {
 enum Knob {
   KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3, KNOB_F32_P3_MIN_M, KNOB_F32_P3_RATIO, KNOB_F32_P3_BN, KNOB_F32_K3C64, KNOB_F32_K3C64_MIN_TILES, KNOB_F32_K3, KNOB_F32_K3_ANY, KNOB_F32_K3V, KNOB_F32_K3_TH, KNOB_F32_K3_TW, KNOB_F32_PW_MIN_ITEMS, KNOB_F32_PW_BF16, KNOB_F32_SMALL_MAX_TILES, KNOB_F32_SMALL_NO_SPLIT,
   KNOB_F32_SMALL_SPLIT_MAX_TILES, KNOB_F32_SMALL_MIN_WGS, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW, KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_SMALLC_TH, KNOB_F32_SMALLC_BF16,
-  KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_SMALLC_I8_WGS, KNOB_I8_PW_MIN_ITEMS,
+  KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_SMALLC_I8_WGS, KNOB_I8_PW_MIN_ITEMS,
   KNOB_I8_FC_SMALL_MAX_M, KNOB_I8_K3_MIN_BLOCKS, KNOB_I8_K3_WAVES, KNOB_I8_K3_GATHER, KNOB_DW,
   KNOB_COUNT
 };
@@ -123,7 +123,7 @@ __device__ __forceinline__ float clamp_act(float v, float lo, float hi) { return
 enum KernelKind {
   KERNEL_TILED = 0,     // generic implicit-GEMM tiles (igemm_f32.hip / igemm_i8.hip)
   KERNEL_SKINNY16,      // fp32 FullyConnected with at most 16 rows: weight stream
-  KERNEL_SMALL,         // fp32 convolution on few pixels, one launch (conv_small_f32.hip)
+  KERNEL_SMALL,         // convolution on few pixels, one launch (conv_small_f32.hip, conv_small_i8.hip)
   KERNEL_SMALL_SPLIT,   // the same with the reduction sliced over the grid
   KERNEL_SMALLC,        // 3-channel 7x7/2 first layer
   KERNEL_PW,            // pointwise convolution, persistent workgroups
@@ -204,6 +204,10 @@ bool dw_i8_applicable(const Problem& p);
 hipError_t launch_dw_i8(const Problem& p, hipStream_t stream, const char** variant);
 // Finishing kernel of a split fp32 reduction (igemm_f32.hip): sums p.partial in split order, bias, addend, activation.
 hipError_t launch_splitk_finish_f32(const Problem& p, const Plan& plan, hipStream_t stream);
+// int8 convolution on few pixels in one launch (conv_small_i8.hip); _splits > 1: its form with the reduction sliced over the grid.
+bool conv_small_i8_applicable(const Problem& p);
+int conv_small_i8_splits(const Problem& p);
+hipError_t launch_conv_small_i8(const Problem& p, hipStream_t stream, const char** variant);
 bool pw_i8_applicable(const Problem& p);
 hipError_t launch_pw_i8(const Problem& p, hipStream_t stream, const char** variant);
 // int8 3x3 convolution over 64 input channels on many pixels (conv_k3c64_i8.hip).

@@ -15,11 +15,8 @@
 // four consecutive output channels of one pixel: they are requantized, packed into one dword, transposed
 // through LDS and leave the chip as 16-byte stores along the channel axis.
 //
-// The reduction is walked in 16-code chunks that never straddle a filter tap: a tap has ceil(cg / 16) chunks,
-// the last one with cg % 16 codes (or 16).  One load then fetches a chunk at any channel count: 16 bytes at
-// whatever byte address the pixel's channels start, the bytes past the tap's channels belonging to the next
-// pixel (filter: the next tap) and meeting zeros on the filter side, which is masked while it is staged.  The
-// form before this one packed taps densely and gathered channel counts that are not a multiple of 16 byte by byte
+// The reduction is walked in 16-code chunks (i8_chunks.h), so any channel count is fetched 16 bytes at a time; the filter
+// side is masked while it is staged.  The form before this one packed taps densely and gathered channel counts that are not a multiple of 16 byte by byte
 // (16 loads and as many tap steps per chunk): 3x3 72->120 on 33x45 at batch 5 took 31.6 us.
 // Two slabs are in flight in registers while a third is multiplied: with six to ten slabs per tile, which is
 // what most of these layers have, a load's latency per slab was most of the kernel.
@@ -28,6 +25,7 @@
 #include <cstdio>
 #include <cstdlib>
 
+#include "i8_chunks.h"
 #include "igemm.h"
 #include "quant_epilogue.h"
 
@@ -35,7 +33,7 @@ namespace glowmi {
 namespace {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
+typedef i8x16 v4i;
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int BKQ = 128;                 // codes per reduction slab
@@ -45,61 +43,13 @@ constexpr int INVALID_ROW = -(1 << 24);
 
 constexpr unsigned OOB = 0x80000000u;    // beyond any int8 tensor the library accepts: loads give zeros
 
-// Position of a chunk in the reduction: filter row and column, first channel.
-struct Chunk {
-  int r, s, c;
-};
-// How the launch walks tiles and chunks, divided out on the host: a division by a number the compiler does not know
-// is about forty dependent instructions, and a kernel of a few microseconds had ten of them before its first load.
+// How the launch walks tiles and chunks.
 struct Walk {
-  FastDiv div_tiles_n, div_tiles_m, div_groups, div_cpt;
+  FastDiv div_tiles_n, div_tiles_m, div_groups;
   int tiles_n, tiles_m, total_work;
-  int cpt, chunks;                       // chunks per tap, chunks of the reduction
   int padded;                            // some row of some tile has taps outside the image, or lies past M
-  int dr, ds, dc;                        // one step of a wavefront group = (dr * S + ds) taps and dc channels
-  __device__ void step(Chunk& k, int S) const {   // one carry per digit
-    k.c += dc;
-    const bool wc = k.c >= cpt * 16;
-    k.c -= wc ? cpt * 16 : 0;
-    k.s += ds + (wc ? 1 : 0);
-    const bool ws = k.s >= S;
-    k.s -= ws ? S : 0;
-    k.r += dr + (ws ? 1 : 0);
-  }
+  ChunkWalk chunk;                       // one step: a slab of every wavefront group
 };
-
-// 16 bytes shifted down by `over` bytes (0..16), zeros from above.
-__device__ __forceinline__ v4i shift_down(v4i v, unsigned over) {
-  const unsigned q = over >> 2, b = over & 3u;
-  int d[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    int x = 0;
-#pragma unroll
-    for (int j = i; j < 4; ++j) x = (int)q == j - i ? v[j] : x;
-    d[i] = x;
-  }
-  return v4i{(int)__builtin_amdgcn_alignbyte((unsigned)d[1], (unsigned)d[0], b), (int)__builtin_amdgcn_alignbyte((unsigned)d[2], (unsigned)d[1], b),
-             (int)__builtin_amdgcn_alignbyte((unsigned)d[3], (unsigned)d[2], b), (int)__builtin_amdgcn_alignbyte(0u, (unsigned)d[3], b)};
-}
-
-// Mask of the first `valid` bytes (any integer; at least 16 keeps all) of 16.
-__device__ __forceinline__ v4i byte_mask(int valid) {
-  v4i m;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int n = valid - 4 * i;
-    m[i] = n >= 4 ? -1 : n <= 0 ? 0 : (int)((1u << (8 * n)) - 1u);
-  }
-  return m;
-}
-
-// acc plus the signed bytes of v (ones = 0x01010101), or acc (ones = 0)
-__device__ __forceinline__ int sum_bytes(v4i v, int ones, int acc) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_sdot4(v[i], ones, acc, false);
-  return acc;
-}
 
 __device__ __forceinline__ int requantize(int acc, int mant, int shift, int y_off, int lo, int hi) {
   return shift >= 33 ? requantize_as<true>(acc, mant, shift, y_off, lo, hi)
@@ -196,26 +146,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
     }
   }
 
-  const int cpt = walk.cpt, chunks = walk.chunks;
   const int slab_begin = split * p.slabs_per_split;
-  const int total_slabs = (chunks + KV - 1) / KV;
+  const int total_slabs = (walk.chunk.chunks + KV - 1) / KV;
   int slab_end = slab_begin + p.slabs_per_split;
   if (slab_end > total_slabs) slab_end = total_slabs;
-  auto codes_before = [&](int chunk) {                  // reduction codes in the chunks before this one
-    if (chunk >= chunks) return p.Kgemm;
-    const int t = walk.div_cpt.div(chunk), c0 = (chunk - t * cpt) * 16;
-    return t * p.cg + c0;
-  };
-  const int k_count = codes_before(slab_end * KV) - codes_before(slab_begin * KV);   // codes this split really reduces over
-
-  Chunk at;                                             // of the next slab to load
-  {
-    const int j = (slab_begin + grp) * KV + kvec;
-    const int t = walk.div_cpt.div(j);
-    at.c = (j - t * cpt) * 16;
-    at.r = p.div_s.div(t);
-    at.s = t - at.r * p.s;
-  }
+  const int k_count = walk.chunk.codes_before(slab_end * KV, p) - walk.chunk.codes_before(slab_begin * KV, p);   // codes of this split
+  Chunk at = walk.chunk.at((slab_begin + grp) * KV + kvec, p);   // of the next slab to load
 
   const int xo_fill = (p.x_off & 0xff) * 0x01010101;    // padding = the code of real zero
   const bool need_xsum = p.w_off != 0;
@@ -308,7 +244,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
         }
       }
     }
-    walk.step(at, p.s);
+    walk.chunk.step(at, p.s);
   };
 
   auto store_lds = [&](int buf, Stage& sg, bool live) {
@@ -657,18 +593,12 @@ hipError_t launch_variant(const Problem& p, const Plan& plan, hipStream_t stream
   walk.div_tiles_n = make_fastdiv((uint32_t)plan.tiles_n);
   walk.div_tiles_m = make_fastdiv((uint32_t)plan.tiles_m);
   walk.div_groups = make_fastdiv((uint32_t)p.groups);
-  walk.cpt = (p.cg + 15) / 16;
-  walk.div_cpt = make_fastdiv((uint32_t)walk.cpt);
   walk.tiles_n = plan.tiles_n;
   walk.tiles_m = plan.tiles_m;
   walk.total_work = (int)total_work;
-  walk.chunks = p.r * p.s * walk.cpt;
   walk.padded = p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h + p.r > p.h || (p.ow - 1) * p.stride_w + p.s > p.w_ ||
                 p.M % BM != 0;
-  const int step = KV * KGRP, taps = step / walk.cpt;
-  walk.dc = (step - taps * walk.cpt) * 16;
-  walk.dr = taps / p.s;
-  walk.ds = taps - walk.dr * p.s;
+  walk.chunk = make_chunk_walk(p, KV * KGRP);
   dim3 grid((unsigned)grid_x, 1, 1), block(nthreads, 1, 1);
   hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, walk);
   return hipGetLastError();
@@ -712,6 +642,13 @@ Plan plan_i8(const Problem& p, bool allow_split) {
     if (pw_i8_applicable(p)) { pl.kernel = KERNEL_PW; return pl; }
     if (k3c64_i8_applicable(p)) { pl.kernel = KERNEL_K3C64; return pl; }
     if (fc_small_i8_applicable(p)) { pl.kernel = KERNEL_FC_SMALL; return pl; }
+    if (conv_small_i8_applicable(p)) { pl.kernel = KERNEL_SMALL; return pl; }
+    const int slices = allow_split ? conv_small_i8_splits(p) : 0;
+    if (slices > 1) {
+      pl.kernel = KERNEL_SMALL_SPLIT;
+      pl.split_k = slices;
+      return pl;
+    }
   }
   pl.bk = BKQ;
   pl.slabs = (p.r * p.s * ((p.cg + 15) / 16) + KV - 1) / KV;
@@ -789,6 +726,7 @@ hipError_t launch_i8(const Problem& p_in, const Plan& plan, hipStream_t stream, 
     case KERNEL_PW: return launch_pw_i8(p_in, stream, variant);
     case KERNEL_K3C64: return launch_k3c64_i8(p_in, stream, variant);
     case KERNEL_FC_SMALL: return launch_fc_small_i8(p_in, stream, variant);
+    case KERNEL_SMALL: return launch_conv_small_i8(p_in, stream, variant);
     default: break;
   }
   if (plan.split_k > 1 && !p_in.partial) return hipErrorInvalidValue;   // the ABI layer never plans a split without a workspace
@@ -797,7 +735,9 @@ hipError_t launch_i8(const Problem& p_in, const Plan& plan, hipStream_t stream, 
   p.slabs_per_split = plan.slabs_per_split;
   const bool fc = p.b_is_kn != 0;
   hipError_t e;
-  if (plan.kernel == KERNEL_WIDE) {
+  if (plan.kernel == KERNEL_SMALL_SPLIT) {
+    e = launch_conv_small_i8(p, stream, variant);
+  } else if (plan.kernel == KERNEL_WIDE) {
     e = launch_wide_i8(p, plan, stream, variant);
   } else if (p.chain_n > 0) {
     if (fc || plan.tile != 0) return hipErrorInvalidValue;
