@@ -5,8 +5,7 @@
 //   dequantize  int8   -> float  v = (q - offset) * scale                             (Section 4.1)
 //   rescale     int8   -> int8   the same real values on another scale/offset         (rescale node,
 //                                Section 4.3), integer arithmetic like the fused requantize
-// All three stream their tensor once: 16 elements per thread and step, 16-byte accesses on the int8
-// side; they are bound by HBM bandwidth.
+// All three stream their tensor once; they are bound by HBM bandwidth (25.7 M elements, 129 MB: quantize 23 us, dequantize 20 us).
 #include <hip/hip_runtime.h>
 
 #include "igemm.h"
@@ -19,11 +18,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int EW_THREADS = 256;
-constexpr int EW_PER_THREAD = 16;
+constexpr int EW_PER_THREAD = 16;            // rescale: codes per thread and step
+constexpr int EW_QUADS = 4;                  // quantize, dequantize: groups of four elements per thread and step
 
 // The quotient is formed in double (the float operands are exact there and the division is correctly
 // rounded), so the rounding decision is the same wherever it is evaluated.
-__device__ __forceinline__ int quantize_one(float v, double scale, int offset) {
+__device__ __forceinline__ int quantize_exact(float v, double scale, int offset) {
   double t = __builtin_rint((double)v / scale) + (double)offset;   // ties to even
   t = t != t ? (double)offset : t;                                 // NaN has no code: it takes the code of real zero
   t = t < -128.0 ? -128.0 : t;
@@ -31,51 +31,71 @@ __device__ __forceinline__ int quantize_one(float v, double scale, int offset) {
   return (int)t;
 }
 
+// The same decision from a product with the reciprocal where that product cannot be on the wrong side of a rounding
+// boundary: for |v / scale| < 512 (beyond that the code saturates) it is within 512 * 2^-22 = 1.3e-4 of the quotient, so
+// only a value that close to a half is divided (one in four thousand).  `inverse` 0: the scale is too small or large
+// for a float reciprocal, every value is divided.
+__device__ __forceinline__ int quantize_one(float v, float inverse, double scale, int offset) {
+  const float t = __builtin_amdgcn_fmed3f(v * inverse, -512.0f, 512.0f);
+  const float n = __builtin_rintf(t);
+  if (inverse == 0.0f || !(__builtin_fabsf(__builtin_fabsf(t - n) - 0.5f) > 1.3e-4f) || v != v) return quantize_exact(v, scale, offset);
+  const int q = (int)n + offset;
+  return q < -128 ? -128 : q > 127 ? 127 : q;
+}
+
+// Consecutive lanes own consecutive groups of four elements: every load and store of a wavefront covers whole cache lines
+// (with sixteen elements per lane a wavefront's float access touched 64 lines for a quarter of their bytes: 25.7 M
+// elements, 129 MB, quantize 31 us, dequantize 36 us).
 __global__ __launch_bounds__(EW_THREADS) void quantize_kernel(const float* __restrict__ x,
                                                              signed char* __restrict__ q, long long count,
-                                                             float scale, int offset) {
+                                                             float scale, float inverse, int offset) {
   const double s = (double)scale;
-  const long long groups = count / EW_PER_THREAD;
-  for (long long g = (long long)blockIdx.x * EW_THREADS + threadIdx.x; g < groups;
-       g += (long long)gridDim.x * EW_THREADS) {
-    const v4f* src = reinterpret_cast<const v4f*>(x + g * EW_PER_THREAD);
-    v4i out;
+  const long long quads = count / 4;
+  for (long long g = (long long)blockIdx.x * (EW_THREADS * EW_QUADS) + threadIdx.x; g < quads;
+       g += (long long)gridDim.x * (EW_THREADS * EW_QUADS)) {
+    v4f v[EW_QUADS];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const v4f v = src[j];
-      out[j] = (int)pack_codes(quantize_one(v[0], s, offset), quantize_one(v[1], s, offset),
-                               quantize_one(v[2], s, offset), quantize_one(v[3], s, offset));
+    for (int j = 0; j < EW_QUADS; ++j) {
+      const long long i = g + j * EW_THREADS < quads ? g + j * EW_THREADS : g;
+      v[j] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(x) + i);
     }
-    *reinterpret_cast<v4i*>(q + g * EW_PER_THREAD) = out;
+#pragma unroll
+    for (int j = 0; j < EW_QUADS; ++j) {
+      const unsigned o = pack_codes(quantize_one(v[j][0], inverse, s, offset), quantize_one(v[j][1], inverse, s, offset),
+                                    quantize_one(v[j][2], inverse, s, offset), quantize_one(v[j][3], inverse, s, offset));
+      if (g + j * EW_THREADS < quads) reinterpret_cast<unsigned*>(q)[g + j * EW_THREADS] = o;
+    }
   }
   // ragged tail, one element per thread of the first workgroup
-  if (blockIdx.x == 0)
-    for (long long i = groups * EW_PER_THREAD + threadIdx.x; i < count; i += EW_THREADS)
-      q[i] = (signed char)quantize_one(x[i], s, offset);
+  if (blockIdx.x == 0 && threadIdx.x < count - quads * 4)
+    q[quads * 4 + threadIdx.x] = (signed char)quantize_exact(x[quads * 4 + threadIdx.x], s, offset);
 }
 
 __global__ __launch_bounds__(EW_THREADS) void dequantize_kernel(const signed char* __restrict__ q,
                                                                float* __restrict__ x, long long count,
                                                                float scale, int offset) {
-  const long long groups = count / EW_PER_THREAD;
-  for (long long g = (long long)blockIdx.x * EW_THREADS + threadIdx.x; g < groups;
-       g += (long long)gridDim.x * EW_THREADS) {
-    const v4i in = *reinterpret_cast<const v4i*>(q + g * EW_PER_THREAD);
-    v4f* dst = reinterpret_cast<v4f*>(x + g * EW_PER_THREAD);
+  const long long quads = count / 4;
+  for (long long g = (long long)blockIdx.x * (EW_THREADS * EW_QUADS) + threadIdx.x; g < quads;
+       g += (long long)gridDim.x * (EW_THREADS * EW_QUADS)) {
+    unsigned in[EW_QUADS];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < EW_QUADS; ++j)
+      in[j] = reinterpret_cast<const unsigned*>(q)[g + j * EW_THREADS < quads ? g + j * EW_THREADS : g];
+#pragma unroll
+    for (int j = 0; j < EW_QUADS; ++j) {
       v4f v;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const int code = (int)(signed char)((unsigned)in[j] >> (8 * t));
+        const int code = (int)(signed char)(in[j] >> (8 * t));
         v[t] = (float)(code - offset) * scale;        // small integer times float: one rounding
       }
-      dst[j] = v;
+      if (g + j * EW_THREADS < quads) reinterpret_cast<v4f*>(x)[g + j * EW_THREADS] = v;
     }
   }
-  if (blockIdx.x == 0)
-    for (long long i = groups * EW_PER_THREAD + threadIdx.x; i < count; i += EW_THREADS)
-      x[i] = (float)((int)q[i] - offset) * scale;
+  if (blockIdx.x == 0 && threadIdx.x < count - quads * 4) {
+    const long long i = quads * 4 + threadIdx.x;
+    x[i] = (float)((int)q[i] - offset) * scale;
+  }
 }
 
 __global__ __launch_bounds__(EW_THREADS) void rescale_kernel(const signed char* __restrict__ in,
@@ -111,12 +131,14 @@ unsigned grid_for(long long count) {
   if (blocks > 256 * 16) blocks = 256 * 16;       // grid-stride beyond 16 workgroups per CU
   return (unsigned)blocks;
 }
+static_assert(EW_PER_THREAD == 4 * EW_QUADS, "one grid rule");
 
 }  // namespace
 
 hipError_t launch_quantize(const float* x, signed char* q, long long count, float scale, int offset,
                            hipStream_t stream) {
-  hipLaunchKernelGGL(quantize_kernel, dim3(grid_for(count)), dim3(EW_THREADS), 0, stream, x, q, count, scale, offset);
+  const float inverse = scale > 0x1p-100f && scale < 0x1p100f ? 1.0f / scale : 0.0f;
+  hipLaunchKernelGGL(quantize_kernel, dim3(grid_for(count)), dim3(EW_THREADS), 0, stream, x, q, count, scale, inverse, offset);
   return hipGetLastError();
 }
 
