@@ -29,8 +29,9 @@
  *  - Every tensor must hold fewer than 2^31 elements (GLOWMI_ERR_UNSUPPORTED otherwise).
  *  - Results: fp32 entry points accumulate in fp32 (order unspecified).  Products are fp32 products:
  *    either the fp32 matrix cores' own, or -- large contractions with a workspace -- formed on the
- *    fp16 matrix cores from operands cut into two fp16 pieces each: a tensor (for the input of a 3x3 tile
- *    kernel: each patch a workgroup stages) is scaled by the power of two that brings its largest magnitude
+ *    fp16 matrix cores from operands cut into two fp16 pieces each: a tensor (in the convolution tile kernels:
+ *    each patch of the input a workgroup stages, and of a filter cut in the call each output channel) is scaled by
+ *    the power of two that brings its largest magnitude
  *    under 2^15 (exact), a scaled value v becomes h1 = fp16(v) and
  *    H2 = fp16((v - h1) * 2^11), 22 significant bits together, and a product is the three piece products
  *    h1 h1' + 2^-11 (h1 H2' + H2 h1'), multiplied exactly and accumulated in fp32; a product is then
@@ -210,8 +211,8 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
 /*
  * Filters transformed ahead of time.  Section 5.3 (the filter-layout figure and the three kinds of
  * convolution): the weights of a layer are constants, so the compiler changes their memory layout once, at
- * compile time, into the form the selected convolution reads.  The form here is the one every fp32 kernel on
- * the fp16 matrix cores reads: the weights scaled by the power of two that follows from their largest
+ * compile time, into the form the selected convolution reads.  The form here is the one the fp32 kernels for
+ * large layers on the fp16 matrix cores read: the weights scaled by the power of two that follows from their largest
  * magnitude and cut into two fp16 pieces each (see "Results" above), kept as two planes of fp16, a convolution
  * filter in its own [k][r][s][c/groups] order, a FullyConnected weight transposed to [N][K], followed by a
  * trailer that holds the largest magnitude.  glowmi_conv2d / glowmi_fc make these planes inside every call
@@ -229,7 +230,8 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  *   glowmi_conv2d_packed / glowmi_fc_packed
  *       glowmi_conv2d_chain / glowmi_fc with `w_planes` = the planes made from this very `w` for this very
  *       descriptor (or K, N); the library cannot check that and results are undefined otherwise.  `w` itself
- *       is still required: layers that take a kernel which does not read planes use it, and ignore w_planes.
+ *       is still required: layers that take a kernel which does not read planes use it, and ignore w_planes
+ *       (1x1 and 3x3 layers of ordinary size among them: their kernel reads the filter in an order of its own).
  *       w_planes = NULL makes the call the plain one.  chain of glowmi_conv2d_packed must not be NULL.
  *       GLOWMI_ERR_ALIGN for w_planes not 16-byte aligned, GLOWMI_ERR_UNSUPPORTED for w_planes != NULL on a
  *       shape without a plane form.

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
         const float v[8] = {pre[q][0][0], pre[q][0][1], pre[q][0][2], pre[q][0][3],
                             pre[q][1][0], pre[q][1][1], pre[q][1][2], pre[q][1][3]};
         v4u p1, p2;
-        cut8(v, se_x, p1, p2);
+        cut8_in_place(v, se_x, p1, p2);
         const int py = pp / KP;
         const int key = pp - 2 * py;                     // py * 16 + px: the pixel's index at the tile's own pitch
         unsigned char* dst = lds + pp * K_PIXB + ((c8 ^ ((key >> 1) & 7)) << 4);

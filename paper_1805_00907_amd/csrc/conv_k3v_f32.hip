@@ -146,7 +146,7 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
         const float v[8] = {pre[q][0][0], pre[q][0][1], pre[q][0][2], pre[q][0][3],
                             pre[q][1][0], pre[q][1][1], pre[q][1][2], pre[q][1][3]};
         v4u p1, p2;
-        cut8(v, se_x, p1, p2);
+        cut8_in_place(v, se_x, p1, p2);
         const int key = (pyx[q] >> 16) * tw + (pyx[q] & 0xffff);
         unsigned char* dst = lds + pp * V_PIXB + ((c8 ^ ((key >> 2) & 3)) << 4);
         *reinterpret_cast<v4u*>(dst) = p1;

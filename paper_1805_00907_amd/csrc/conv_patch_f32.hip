@@ -1,0 +1,677 @@
+// fp32 convolutions of ordinary size on the fp16 matrix cores: 1x1 and 3x3 filters, stride 1 or 2, any map and channel
+// counts that are multiples of eight.  The arithmetic is that of the other kernels over fp16 pieces (f16_pieces.h): three
+// exact fp16 products per fp32 product, fp32 accumulation.
+//
+// The 3x3 tile kernels (conv_k3*_f32.hip) own a CU per tile of 200 pixels x 128 channels, so they need a large map at a
+// large batch; below that, and for strides and pointwise layers, a layer ran on the contraction over planes (a pass that
+// measures the input, one that cuts it, every element then fetched once per filter tap) or on the fp32 matrix cores.
+// Here a tile is 64 or 128 pixels x 32 to 128 channels and the input is read once:
+//   - a workgroup loads the input patch of its pixel tile, CC channels at a time, measures it, scales it and cuts it into
+//     two fp16 planes in LDS, which all taps then read at shifted addresses.  The planes are double buffered and there is
+//     one barrier per chunk: while a chunk is multiplied, the next one goes from registers into the other planes and the
+//     one after it into the registers;
+//   - a wavefront multiplies 64 pixels x 32 channels: every filter fragment meets two pixel fragments.  The eight
+//     or four wavefronts of a workgroup cover the tile, and where it has fewer such blocks, KS wavefronts share one: each
+//     takes every KS-th run of 16 channels, and they add up through LDS at the end;
+//   - the filter's fragments go from memory into registers, DB steps ahead: no LDS traffic and no barrier for them.
+// What bounds it: LDS and vector memory bandwidth next to the matrix cores, and what a workgroup does before its first and
+// behind its last chunk.  A form with 32 x 32 blocks per wavefront and the filter in an LDS ring read 32 KB of fragments per
+// 32 reduction indices of a 64 x 64 tile, 256 cycles against 192 of matrix work, and did not get past a third of the matrix
+// rate; here it is 16 KB from LDS and 8 KB from memory.  The instructions that are neither go between the matrix ones.
+// Measured, microseconds with the filter cut in the call, before (igemm_f32, igemm_f32_p3) -> here: 3x3 stride 2 128 -> 128
+// on 56x56 at batch 16 48.9 -> 23.4, 3x3 128 -> 128 on 28x28 at batch 8 31 -> 14, 3x3 152 -> 152 on 57x57 at batch 13
+// 137 -> 82, 3x3 32 -> 344 on 102x102 at batch 4 103 -> 43, 1x1 608 -> 152 on 57x57 at batch 13 96 -> 61.
+// The input's scale is per patch (within a tile the exponent only goes down, the accumulators are scaled along), the
+// filter's per output channel.  Planes of the filter made ahead of time are rows of channels, which do not help here.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+
+#include "f16_pieces.h"
+#include "igemm.h"
+#include "lds_direct.h"
+
+namespace glowmi {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+constexpr unsigned OOBX = 0xFFFFFF00u;           // beyond any fp32 tensor this kernel accepts
+constexpr unsigned OOBW = 0x80000000u;           // beyond a filter plane (at most 2^29 bytes), also after adding an offset
+constexpr unsigned PASTW = 0x40000000u;          // inside one or PASTW, which itself takes any offset past the plane
+
+// R: filter extent, ST: stride, PXB: 64-pixel blocks, CHB: 32-channel blocks of a tile, W: wavefronts (8: a workgroup
+// owns a CU, 4: two share it).
+template <int R, int ST, int PXB, int CHB, int W>
+struct Patch {
+  static constexpr int THREADS = 64 * W;
+  static constexpr int PX = 64 * PXB, BN = 32 * CHB;
+  static constexpr int KS = W / (PXB * CHB);                 // wavefronts that share a block of the tile
+  // 16-channel steps per tap and wavefront: one where a 3x3 chunk's nine taps make a trip long enough; a chunk is at
+  // least 32 channels (64 for pointwise)
+  static constexpr int MS = R == 1 ? (KS == 1 ? 4 : 2) : (KS == 1 ? 2 : 1);
+  static constexpr int CC = 16 * KS * MS;                    // channels per chunk
+  static constexpr int NS = R * R * MS;                      // steps per chunk and wavefront
+  static constexpr int SETS = R == 1 ? 2 : 1;                // chunks in registers: a pointwise one is over before the next has arrived
+  static constexpr int UNROLL = SETS;                        // chunks per loop pass
+  static constexpr int DB = R == 1 ? 4 : 3;                  // steps whose filter fragments are in flight (nine: no faster)
+  static constexpr int MAXP = R == 1 ? PX : ST == 1 ? (PX == 64 ? 120 : 208) : (PX == 64 ? 320 : 600);   // patch pixels
+  static constexpr int ROW = 2 * CC;                         // bytes of a pixel in a plane
+  static constexpr int PIECES = CC / 8;                      // of eight channels, per pixel
+  static constexpr int PASSES = (MAXP * PIECES + THREADS - 1) / THREADS;
+  // rows of the planes: as many as whole passes of the workgroup write, where the LDS holds them (no branch then)
+  static constexpr int ROWS = 4 * PASSES * THREADS * 16 <= (W == 8 ? 150 : 75) * 1024 ? PASSES * THREADS / PIECES : MAXP;
+  static constexpr int ITEMS = ROWS * PIECES;
+  static constexpr int APLANE = ROWS * ROW, PAIR = 2 * APLANE;
+  static constexpr int CUT_FROM = NS > 2 ? 1 : 0;            // the steps beside which the next chunk is cut
+  static constexpr int CUT_STEPS = PASSES < NS - CUT_FROM ? PASSES : NS - CUT_FROM;
+  static constexpr int XCH = KS > 1 ? W * 8 * 64 * 16 : 0;   // exchange of partial tiles, in place of the planes
+  static constexpr int WORDS_AT = 2 * PAIR > XCH ? 2 * PAIR : XCH;
+  static constexpr int LDS = WORDS_AT + 64 + PX * 4;         // + the wavefronts' largest magnitudes, the pixels' output positions
+  static_assert(KS >= 1 && PXB * CHB * KS == W && (NS * UNROLL) % DB == 0, "work of a wavefront");
+  static_assert(LDS <= (W == 8 ? 160 : 80) * 1024, "LDS of one CU");
+  // A pixel's 16-byte pieces sit at piece ^ swizzle(key), key = the pixel's position at the tile's own pitch: 16
+  // consecutive lanes have 16 consecutive keys, and (position, piece) then names 16 different bank groups (the host
+  // makes the patch pitch congruent to the tile's columns modulo 4).
+  static __device__ __forceinline__ int swizzle(int key) { return ROW == 64 ? (key >> 2) & 3 : ROW == 128 ? (key >> 1) & 7 : key & 15; }
+};
+
+struct Tiles {
+  int th, tw, pitch, half;       // tile rows, columns; patch row pitch; 3x3 stride 2: where the odd columns start
+  int patch_h, patch_w;          // patch extents in input pixels
+  int tiles_y, tiles_x, tiles_c, total;
+  FastDiv div_tw, div_pitch, div_tiles_c, div_tiles_x, div_tiles_y;
+  int chunks;
+};
+
+template <int V> struct Const { static constexpr int value = V; };
+
+template <int R, int ST, int PXB, int CHB, int W, bool ADD>
+__global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem p, const Tiles tl) {
+  using T = Patch<R, ST, PXB, CHB, W>;
+  extern __shared__ __align__(16) unsigned char lds[];
+  unsigned* maxw = reinterpret_cast<unsigned*>(lds + T::WORDS_AT);
+  int* out_pix = reinterpret_cast<int*>(lds + T::WORDS_AT + 64);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (W == 4 && tid < 16 && (tid & 4)) maxw[tid] = 0;   // the words of wavefronts 4 .. 7, which there are not
+  const int wn = wave % CHB;
+  const int wm = (wave / CHB) % PXB;
+  const int kset = wave / (CHB * PXB);
+  const int lrow = lane & 31, lhalf = lane >> 5;
+
+  // Consecutive workgroups go round-robin to the eight XCDs: each XCD takes a contiguous run of tiles, channel tiles
+  // innermost, so that the tiles that share a patch find it in their XCD's L2.
+  const int per_xcd = gridDim.x >> 3;
+  const int t = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (t >= tl.total) return;
+  const int t1 = tl.div_tiles_c.div(t);
+  const int ct = t - t1 * tl.tiles_c;
+  int img = 0, ty = 0, tx = t1;                         // pointwise: tile tx of the whole batch's pixels
+  if (R != 1) {
+    const int t2 = tl.div_tiles_x.div(t1);
+    tx = t1 - t2 * tl.tiles_x;
+    img = tl.div_tiles_y.div(t2);
+    ty = t2 - img * tl.tiles_y;
+  }
+
+  // ---- filter fragments: planes [Kgemm / 8][k][8]; lane: channel lrow of the wavefront's 32, eight indices lhalf of the
+  // step's 16.  Step st of a chunk: tap st / MS, channels 16 ((st % MS) KS + kset) .. of the chunk.
+  const unsigned wpb = p.w_bytes >> 1;                  // bytes of one plane
+  const __amdgpu_buffer_rsrc_t rsrc_w1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w_planes), 0, (int)wpb, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<unsigned char*>(static_cast<const unsigned char*>(p.w_planes)) + wpb, 0, (int)wpb, 0x00020000);
+  const int ch = ct * T::BN + wn * 32 + lrow;
+  const unsigned k16 = 16u * (unsigned)p.k;             // bytes of eight reduction indices
+  const unsigned b_base = ch < p.k ? (unsigned)(2 * kset + lhalf) * k16 + 16u * (unsigned)ch : OOBW;
+  const unsigned tap_step = (unsigned)(p.c >> 3) * k16, chunk_step = (unsigned)(T::CC >> 3) * k16;
+  v4i fb[T::DB][2];                                     // [step in flight][plane]
+  auto load_b = [&](int slot, int chunk, int st) {      // slot, st: compile-time
+    const unsigned at = chunk < tl.chunks ? (unsigned)chunk * chunk_step + (unsigned)(st / T::MS) * tap_step +
+                                                (unsigned)(st % T::MS * 2 * T::KS) * k16
+                                          : PASTW;
+    fb[slot][0] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w1, b_base + at, 0, 0));
+    fb[slot][1] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w2, b_base + at, 0, 0));
+  };
+
+  // ---- patch: piece q of this thread is item tid + 512 q: pixel item / PIECES, channels 8 (item % PIECES) .. of a chunk;
+  // where it comes from in the input and where it goes in the planes
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)p.x_bytes, 0x00020000);
+  unsigned raw_off[T::PASSES], cut_at[T::PASSES];
+  int raw_c[T::PASSES];
+#pragma unroll
+  for (int q = 0; q < T::PASSES; ++q) {
+    const int item = tid + q * T::THREADS;
+    const int pp = item / T::PIECES, piece = item % T::PIECES;
+    raw_c[q] = 8 * piece;
+    raw_off[q] = OOBX;
+    int key = pp;
+    if (R == 1) {
+      const int m = tx * T::PX + pp;
+      if (pp < T::PX && m < p.M) {
+        int pix = m;
+        if (ST != 1 || p.oh != p.h || p.ow != p.w_) {    // uniform
+          const int im = p.div_ohow.div(m);
+          const int rem = m - im * (p.oh * p.ow);
+          const int oy = p.div_ow.div(rem);
+          pix = (im * p.h + oy * ST) * p.w_ + (rem - oy * p.ow) * ST;
+        }
+        raw_off[q] = ((unsigned)pix * (unsigned)p.c + (unsigned)raw_c[q]) * 4u;
+      }
+    } else {
+      const int py = tl.div_pitch.div(pp);
+      int px = pp - py * tl.pitch;
+      key = (ST == 2 ? py >> 1 : py) * tl.tw + px;
+      if (ST == 2) px = px < tl.half ? 2 * px : px < 2 * tl.half ? 2 * (px - tl.half) + 1 : tl.patch_w;   // even columns, then odd ones
+      const int iy = ty * tl.th * ST - p.pad_t + py, ix = tx * tl.tw * ST - p.pad_l + px;
+      if (pp < T::MAXP && py < tl.patch_h && px < tl.patch_w && (unsigned)iy < (unsigned)p.h && (unsigned)ix < (unsigned)p.w_)
+        raw_off[q] = ((unsigned)((img * p.h + iy) * p.w_ + ix) * (unsigned)p.c + (unsigned)raw_c[q]) * 4u;
+    }
+    cut_at[q] = pp * T::ROW + ((piece ^ T::swizzle(key)) << 4);
+  }
+  auto load_raw = [&](v4f (&dst)[T::PASSES][2], int chunk) {   // past the last chunk: zeros
+    const int c0 = chunk * T::CC;
+#pragma unroll
+    for (int q = 0; q < T::PASSES; ++q) {
+      const unsigned off = raw_off[q] != OOBX && c0 + raw_c[q] < p.c ? raw_off[q] + (unsigned)c0 * 4u : OOBX;   // p.c % 8 == 0
+      dst[q][0] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off, 0, 0));
+      dst[q][1] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off + 16u, 0, 0));
+    }
+  };
+  typedef v4f Raw[T::PASSES][2];                        // a chunk on its way into the planes
+  Raw pre[T::SETS];                                     // chunk j in set j % SETS
+  auto leave_max = [&](const Raw& raw, int parity) {
+    const unsigned share_max = wave_max_of(raw);
+    if (lane == 0) maxw[parity * 8 + wave] = share_max;
+  };
+  int se_x = 141;                                       // scale exponent of the planes written last
+  bool finite = true;
+  auto take_scale = [&](int parity) {                   // of the chunk whose magnitudes were left last
+    const unsigned m = max_of_eight(maxw + parity * 8);
+    finite = finite && m < 0x7f800000u;
+    const int need = scale_exponent(m);
+    se_x = need < se_x ? need : se_x;
+  };
+  auto cut = [&](const Raw& raw, int parity, int part) {   // a CUT_STEPS-th of a chunk, into the planes of that parity
+#pragma unroll
+    for (int q = 0; q < T::PASSES; ++q) {
+      if (q * T::CUT_STEPS / T::PASSES != part) continue;
+      if ((q + 1) * T::THREADS <= T::ITEMS || tid + q * T::THREADS < T::ITEMS) {
+        const float v[8] = {raw[q][0][0], raw[q][0][1], raw[q][0][2], raw[q][0][3],
+                            raw[q][1][0], raw[q][1][1], raw[q][1][2], raw[q][1][3]};
+        v4u p1, p2;
+        cut8_in_place(v, se_x, p1, p2);
+        unsigned char* dst = lds + parity * T::PAIR + cut_at[q];
+        *reinterpret_cast<v4u*>(dst) = p1;
+        *reinterpret_cast<v4u*>(dst + T::APLANE) = p2;
+      }
+    }
+  };
+
+  // ---- before the first chunk: chunk 0 in the planes, the next SETS in registers, the magnitudes of chunk 1 left behind
+  Raw pre0;
+  load_raw(pre0, 0);
+#pragma unroll
+  for (int j = 1; j <= T::SETS; ++j) load_raw(pre[j % T::SETS], j);
+#pragma unroll
+  for (int d = 0; d < T::DB; ++d) load_b(d, d / T::NS, d % T::NS);
+
+  // ---- what the epilogue needs, fetched now: the channel's bias, the filter's scale, where the pixels lie in the output
+  const float* __restrict__ bias = static_cast<const float*>(p.bias);
+  const float bv = ch < p.k && bias ? bias[ch] : 0.f;
+  const unsigned w_max_bits = p.w_range[ch < p.k ? ch : 0];
+  if (tid < T::PX) {
+    int pix = -1;
+    if (R == 1) {
+      const int m = tx * T::PX + tid;
+      if (m < p.M) pix = m;
+    } else {
+      const int r = tl.div_tw.div(tid), c = tid - r * tl.tw;
+      const int oy = ty * tl.th + r, ox = tx * tl.tw + c;
+      if (r < tl.th && oy < p.oh && ox < p.ow) pix = (img * p.oh + oy) * p.ow + ox;
+    }
+    out_pix[tid] = pix;
+  }
+
+  // ---- fragment addresses: the wavefront's two blocks of 32 pixels at tap (0, 0)
+  int pp0[2], key0[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int tp = wm * 64 + b * 32 + lrow;
+    pp0[b] = key0[b] = tp;
+    if (R != 1) {
+      int r = tl.div_tw.div(tp), c = tp - r * tl.tw;
+      if (r >= tl.th) {                                 // past the tile: any pixel of it
+        r = 0;
+        c = 0;
+      }
+      pp0[b] = r * ST * tl.pitch + c;
+      key0[b] = r * tl.tw + c;
+    }
+  }
+
+  v16f acc[2], acc_lo[2];                               // the h1 h1' products; the cross terms (weight 2^-11)
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      acc[b][e] = 0.f;
+      acc_lo[b][e] = 0.f;
+    }
+
+  leave_max(pre0, 0);
+  __syncthreads();
+  take_scale(0);
+#pragma unroll
+  for (int i = 0; i < T::CUT_STEPS; ++i) cut(pre0, 0, i);
+  int se_acc = se_x;                                    // scale exponent of the accumulators
+  leave_max(pre[1 % T::SETS], 1);
+  // The compiler's counts of loads in flight then describe the loop alone; joined with those of this part they are too low,
+  // and a chunk waited for the loads of the one before it.
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+
+  // ---- the chunks.  A step's pixel fragments are read while the step before it is multiplied.
+  auto chunk_steps = [&](int chunk, auto unrolled) {
+    constexpr int U = decltype(unrolled)::value;        // which chunk of a loop pass
+    const int parity = T::UNROLL == 2 ? U : chunk & 1;
+    Raw& next = pre[(U + 1) % T::SETS];
+    const unsigned char* planes = lds + parity * T::PAIR;
+    v8h fa[2][2][2];                                    // [set][block][plane]
+    auto read_a = [&](int st) {                         // compile-time
+      const int tap = st / T::MS, tr = R == 1 ? 0 : tap / 3, ts = R == 1 ? 0 : tap % 3;
+      const int piece = (st % T::MS * T::KS + kset) * 2 + lhalf;
+      // tap (tr, ts) in the patch: whole rows and columns; stride 2 keeps the odd columns apart
+      const int d_pp = tr * tl.pitch + (ST == 2 ? (ts & 1) * tl.half + (ts >> 1) : ts);
+      const int d_key = ST == 2 ? (tr >> 1) * tl.tw + (ts & 1) * tl.half + (ts >> 1) : tr * tl.tw + ts;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const unsigned char* at = planes + (pp0[b] + d_pp) * T::ROW + ((piece ^ T::swizzle(key0[b] + d_key)) << 4);
+        fa[st & 1][b][0] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(at));
+        fa[st & 1][b][1] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(at + T::APLANE));
+      }
+    };
+    __syncthreads();                                    // this chunk's planes and the next one's magnitudes are there
+    read_a(0);
+    if (se_x < se_acc) {                                // uniform: larger values than any chunk before
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          acc[b][e] = __builtin_ldexpf(acc[b][e], se_x - se_acc);
+          acc_lo[b][e] = __builtin_ldexpf(acc_lo[b][e], se_x - se_acc);
+        }
+      se_acc = se_x;
+    }
+    if (T::CUT_FROM == 0) take_scale(parity ^ 1);       // for the next chunk's planes
+#pragma unroll
+    for (int st = 0; st < T::NS; ++st) {
+      const int cur = st & 1, slot = (U * T::NS + st) % T::DB;
+      __builtin_amdgcn_sched_barrier(0);
+      if (st + 1 < T::NS) read_a(st + 1);
+      const v8h b1 = __builtin_bit_cast(v8h, fb[slot][0]), b2 = __builtin_bit_cast(v8h, fb[slot][1]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc_lo[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[cur][b][0], b2, acc_lo[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[cur][b][0], b1, acc[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc_lo[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[cur][b][1], b1, acc_lo[b], 0, 0, 0);
+      const int ahead = st + T::DB;                     // DB <= 2 NS
+      load_b(slot, chunk + ahead / T::NS, ahead % T::NS);
+      constexpr int LAST_CUT = T::CUT_FROM + T::CUT_STEPS - 1;
+      const bool cutting = st >= T::CUT_FROM && st <= LAST_CUT;
+      if (T::CUT_FROM == 1 && st == 0) take_scale(parity ^ 1);
+      if (cutting) cut(next, parity ^ 1, st - T::CUT_FROM);
+      if (st == LAST_CUT) load_raw(next, chunk + 1 + T::SETS);
+      if (st == T::NS - 1) leave_max(pre[U % T::SETS], parity);   // chunk + 2
+      // everything else goes between the matrix instructions: each leaves room for seven
+#pragma unroll
+      for (int m = 0; m < 6; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
+        if (cutting) __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);   // vector
+        else __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+      }
+    }
+  };
+  int chunk = 0;
+  for (; chunk + T::UNROLL <= tl.chunks; chunk += T::UNROLL) {
+    chunk_steps(chunk, Const<0>());
+    if (T::UNROLL == 2) chunk_steps(chunk + 1, Const<T::UNROLL - 1>());
+  }
+  if (T::UNROLL == 2 && chunk < tl.chunks) chunk_steps(chunk, Const<0>());   // behind the loop: a way out of its middle costs waits
+
+  // ---- epilogue.  Register e of a block is pixel (e/4)*8 + 4*lhalf + e%4 of its 32, channel ch.  The KS wavefronts of
+  // a block swap their partial sums: each finishes OQ of the block's eight quads of registers.
+  const ScaleBack sb = scale_back_of(se_acc, scale_exponent(w_max_bits), finite && w_max_bits < 0x7f800000u);
+  constexpr int OQ = 8 / T::KS;
+  float res[OQ][4];
+  float joined[32];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) joined[b * 16 + e] = __builtin_fmaf(acc_lo[b][e], kLowPieceWeight, acc[b][e]);
+  if (T::KS > 1) {
+    v4f* xch = reinterpret_cast<v4f*>(lds);
+    const int pair = wave % (PXB * CHB);
+    __syncthreads();                                    // everyone is done with the planes
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const v4f send = {joined[4 * q], joined[4 * q + 1], joined[4 * q + 2], joined[4 * q + 3]};
+      if (q / OQ != kset) xch[((pair * T::KS + kset) * 8 + q) * 64 + lane] = send;
+      else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) res[q % OQ][e] = send[e];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 1; d < T::KS; ++d) {
+      const int from = (kset + d) % T::KS;
+#pragma unroll
+      for (int q = 0; q < OQ; ++q) {
+        const v4f got = xch[((pair * T::KS + from) * 8 + kset * OQ + q) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) res[q][e] += got[e];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < OQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) res[q][e] = joined[(4 * q + e) % 32];
+  }
+  const unsigned y_bytes = (unsigned)((long long)p.M * p.k * 4);   // below 4 GiB on this kernel
+  const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)y_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_add =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ADD ? p.addend : p.y), 0, (int)y_bytes, 0x00020000);
+  unsigned off[OQ * 4];
+#pragma unroll
+  for (int q = 0; q < OQ; ++q) {
+    const int quad = kset * OQ + q;
+    const int px0 = wm * 64 + (quad >> 2) * 32 + (quad & 3) * 8 + lhalf * 4;
+    const v4i pix = *reinterpret_cast<const v4i*>(out_pix + px0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      off[q * 4 + e] = pix[e] >= 0 && ch < p.k ? ((unsigned)pix[e] * (unsigned)p.k + (unsigned)ch) * 4u : OOBX;
+  }
+  float addv[OQ * 4];
+  if (ADD) {                                            // all in flight together: one wait, not one per store
+#pragma unroll
+    for (int e = 0; e < OQ * 4; ++e)
+      addv[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_add, off[e], 0, 0));
+  }
+  const bool act = p.act == 1;
+#pragma unroll
+  for (int e = 0; e < OQ * 4; ++e) {
+    float v = __builtin_ldexpf(res[e / 4][e % 4], sb.neg_se) + sb.poison + bv;
+    if (ADD) v += addv[e];
+    if (act) v = clamp_act(v, p.act_lo, p.act_hi);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y, off[e], 0, 0);
+  }
+}
+
+// The filter [k][r][s][c] as two planes [Kgemm / 8][k][8], each output channel by a scale of its own, in one launch: WPR
+// wavefronts take a channel, hold up to 32 of its values per lane in registers (what is beyond is read twice), find the
+// largest magnitude, leave its bits in words[channel] and cut.  The eight consecutive reduction indices of a channel are 16
+// bytes and the channels lie side by side, so the fragment of 32 channels x 16 indices that a wavefront multiplies is two
+// runs of 512 bytes; as rows of one channel it is 32 lines of which 32 bytes each are wanted, and a CU fetches it at a
+// quarter of the rate (8 KB in 0.22 instead of 0.058 us).
+template <int WPR>
+__global__ __launch_bounds__(256) void cut_filter_kernel(const float* __restrict__ w, unsigned short* __restrict__ dst, int rows,
+                                                         int row8, long long plane_elems, unsigned* __restrict__ words) {
+  constexpr int HELD = 4, STEP = 64 * WPR;
+  __shared__ unsigned red[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // consecutive channels on one XCD: the 16-byte pieces of a line then meet in its L2
+  const int block = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int row = WPR == 1 ? block * 4 + wave : block;
+  if (row >= rows) return;                              // whole wavefronts; a whole workgroup where it has barriers
+  const int first = WPR == 1 ? lane : (int)threadIdx.x;
+  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(w) + (size_t)row * row8 * 2;
+  v4f held[HELD][2];
+#pragma unroll
+  for (int q = 0; q < HELD; ++q) {
+    const int g = first + q * STEP;
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    held[q][0] = g < row8 ? src[2 * g] : zero;
+    held[q][1] = g < row8 ? src[2 * g + 1] : zero;
+  }
+  unsigned m = wave_max_of(held);
+  for (int g0 = HELD * STEP; g0 < row8; g0 += STEP) {
+    const int g = g0 + first < row8 ? g0 + first : row8 - 1;
+    const v4f again[1][2] = {{src[2 * g], src[2 * g + 1]}};
+    const unsigned o = wave_max_of(again);
+    m = o > m ? o : m;
+  }
+  if (WPR > 1) {
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = red[i] > m ? red[i] : m;
+  }
+  if (first == 0) words[row] = m;
+  const int se = scale_exponent(m);
+  auto write = [&](int g, const v4f& a, const v4f& b) {
+    const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    v4u p1, p2;
+    cut8_in_place(v, se, p1, p2);
+    unsigned short* out = dst + ((size_t)g * rows + row) * 8;
+    *reinterpret_cast<v4u*>(out) = p1;
+    *reinterpret_cast<v4u*>(out + plane_elems) = p2;
+  };
+#pragma unroll
+  for (int q = 0; q < HELD; ++q)
+    if (first + q * STEP < row8) write(first + q * STEP, held[q][0], held[q][1]);
+  for (int g = first + HELD * STEP; g < row8; g += STEP) write(g, src[2 * g], src[2 * g + 1]);
+}
+
+int patch_pitch(int tw, int st) {
+  // at least the patch's columns; congruent to the tile's columns modulo 4 (stride 2, where output rows are two patch
+  // rows apart: twice the pitch, possible for even columns)
+  if (st == 1) return tw + 4;
+  int pitch = 2 * tw + 2;
+  while (tw % 2 == 0 && (2 * pitch) % 4 != tw % 4) ++pitch;
+  return pitch;
+}
+
+// The rows x columns of at most px pixels with the fewest tiles over the map whose patch fits; ties: the smaller patch.
+struct MapTile { int th, tw, tiles; };
+MapTile pick_map_tile(const Problem& p, int px, int max_patch) {
+  const int st = p.stride_h;
+  MapTile best = {0, 0, 0};
+  int best_patch = 0;
+  for (int th = 1; th <= px / 4; ++th) {
+    const int rows = (p.oh + th - 1) / th;
+    int tw = px / th;
+    while (tw > 4 && ((th - 1) * st + 3) * patch_pitch(tw, st) > max_patch) --tw;
+    const int cols = (p.ow + tw - 1) / tw;
+    const int even = (p.ow + cols - 1) / cols;           // the same number of tiles with fewer columns each
+    if (even >= 4) tw = even;
+    const int patch = ((th - 1) * st + 3) * patch_pitch(tw, st);
+    if (patch > max_patch) continue;
+    if (best.th == 0 || rows * cols < best.tiles || (rows * cols == best.tiles && patch < best_patch)) {
+      best = {th, tw, rows * cols};
+      best_patch = patch;
+    }
+    if (rows == 1) break;
+  }
+  return best;
+}
+
+template <int R, int ST, int PXB, int CHB, int W>
+void fill_tiles(const Problem& p, Tiles* t) {
+  using T = Patch<R, ST, PXB, CHB, W>;
+  t->th = 1;
+  t->tw = T::PX;
+  if (R == 1) {
+    t->pitch = T::PX;
+    t->half = 0;
+    t->patch_h = 1;
+    t->patch_w = T::PX;
+    t->tiles_y = 1;
+    t->tiles_x = (p.M + T::PX - 1) / T::PX;
+  } else {
+    const MapTile m = pick_map_tile(p, T::PX, T::MAXP);
+    t->th = m.th;
+    t->tw = m.tw;
+    t->pitch = patch_pitch(t->tw, ST);
+    t->half = ST == 2 ? t->tw + 1 : 0;
+    t->patch_h = (t->th - 1) * ST + 3;
+    t->patch_w = (t->tw - 1) * ST + 3;
+    t->tiles_y = (p.oh + t->th - 1) / t->th;
+    t->tiles_x = (p.ow + t->tw - 1) / t->tw;
+  }
+  t->tiles_c = (p.k + T::BN - 1) / T::BN;
+  t->div_tw = make_fastdiv((uint32_t)t->tw);
+  t->div_pitch = make_fastdiv((uint32_t)t->pitch);
+  t->div_tiles_c = make_fastdiv((uint32_t)t->tiles_c);
+  t->div_tiles_x = make_fastdiv((uint32_t)t->tiles_x);
+  t->div_tiles_y = make_fastdiv((uint32_t)t->tiles_y);
+  t->chunks = (p.c + T::CC - 1) / T::CC;
+  const long long total = (R == 1 ? 1LL : (long long)p.n) * t->tiles_y * t->tiles_x * t->tiles_c;
+  t->total = total < (1LL << 30) ? (int)total : -1;
+}
+
+template <int R, int ST, int PXB, int CHB, int W, bool ADD>
+hipError_t launch_patch(const Problem& p, hipStream_t stream, const char** variant) {
+  using T = Patch<R, ST, PXB, CHB, W>;
+  auto kern = conv_patch_f32_kernel<R, ST, PXB, CHB, W, ADD>;
+  static const hipError_t attr_status = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
+  if (attr_status != hipSuccess) return attr_status;
+  Tiles t;
+  fill_tiles<R, ST, PXB, CHB, W>(p, &t);
+  if (t.total <= 0) return hipErrorInvalidValue;
+  static thread_local char name[64];
+  snprintf(name, sizeof(name), "conv_patch_f32_f16x3_%dx%ds%d_%dx%dw%d%s", R, R, ST, T::PX, T::BN, W, ADD ? "_add" : "");
+  *variant = name;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((t.total + 7) / 8 * 8)), dim3(T::THREADS), T::LDS, stream, p, t);
+  return hipGetLastError();
+}
+
+// ---- forms: pixels x channels of a tile, wavefronts.  Eight wavefronts per tile where the tiles do not fill the machine
+// twice, four (and two workgroups per CU, one's start and end behind the other's middle) where they do.
+constexpr int FORMS = 7;
+
+template <int R, int ST, bool ADD>
+hipError_t launch_patch_form(const Problem& p, int form, hipStream_t stream, const char** variant) {
+  if constexpr (R == 3) {
+    if (form == 1) return launch_patch<R, ST, 1, 4, 8, ADD>(p, stream, variant);
+  }
+  if constexpr (R == 1 || ST == 1) {
+    switch (form) {
+      case 0: return launch_patch<R, ST, 1, 2, 8, ADD>(p, stream, variant);
+      case 2: return launch_patch<R, ST, 1, 1, 8, ADD>(p, stream, variant);
+      case 3: return launch_patch<R, ST, 1, 2, 4, ADD>(p, stream, variant);
+      case 4: return launch_patch<R, ST, 2, 2, 4, ADD>(p, stream, variant);
+      case 5: return launch_patch<R, ST, 1, 4, 4, ADD>(p, stream, variant);
+      case 6: return launch_patch<R, ST, 2, 1, 4, ADD>(p, stream, variant);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+template <bool ADD>
+hipError_t launch_patch_shape(const Problem& p, int form, hipStream_t stream, const char** variant) {
+  if (p.r == 1) return p.stride_h == 1 ? launch_patch_form<1, 1, ADD>(p, form, stream, variant)
+                                       : launch_patch_form<1, 2, ADD>(p, form, stream, variant);
+  return p.stride_h == 1 ? launch_patch_form<3, 1, ADD>(p, form, stream, variant)
+                         : launch_patch_form<3, 2, ADD>(p, form, stream, variant);
+}
+
+// What a form costs, in microseconds, fitted to 61 layers of 0.05 to 20 GFLOP in all forms (median error 4 %; choosing by
+// it costs 0.6 % over the best form of each layer): 4.3 for the two launches, 1 per megabyte of filter to cut, 0.1 per
+// megabyte of input and output, and per round of workgroups a start and end and so much per chunk of channels.  A
+// four-wavefront workgroup that has a CU to itself takes 0.7 of what two take that share it.
+struct FormCost { int px, bn, waves, cc1, cc3; float round1, chunk1, round3, chunk3; };
+constexpr FormCost kForms[FORMS] = {
+    {64, 64, 8, 128, 64, 3.1f, 0.84f, 2.7f, 2.55f},
+    {64, 128, 8, 0, 32, 0.f, 0.f, 3.0f, 1.94f},
+    {64, 32, 8, 256, 128, 3.8f, 1.49f, 3.3f, 3.25f},
+    {64, 64, 4, 64, 32, 2.4f, 0.89f, 2.9f, 2.18f},
+    {128, 64, 4, 64, 32, 3.2f, 1.70f, 4.6f, 3.83f},
+    {64, 128, 4, 64, 32, 2.5f, 1.21f, 4.1f, 3.33f},
+    {128, 32, 4, 64, 32, 3.0f, 1.41f, 4.1f, 2.44f},
+};
+
+// The cheapest form for the layer and its cost; a 3x3 stride-2 layer has one form (two of its patches do not fit a CU; a
+// chunk of it takes 1.35 times as long).
+int cheapest_form(const Problem& p, double* cost) {
+  const bool pointwise = p.r == 1;
+  const double fixed = 4.3 + 1e-6 * p.w_bytes + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1));
+  int best = -1;
+  MapTile map[2] = {{0, 0, 0}, {0, 0, 0}};               // of 64 and of 128 pixels
+  if (!pointwise) {
+    map[0] = pick_map_tile(p, 64, p.stride_h == 1 ? 120 : 320);
+    if (p.stride_h == 1) map[1] = pick_map_tile(p, 128, 208);
+  }
+  for (int f = 0; f < FORMS; ++f) {
+    const FormCost& c = kForms[f];
+    if (pointwise ? c.cc1 == 0 : p.stride_h == 2 && f != 1) continue;
+    const double px_tiles = pointwise ? (double)((p.M + c.px - 1) / c.px) : (double)p.n * map[c.px == 128].tiles;
+    const double rounds = px_tiles * ((p.k + c.bn - 1) / c.bn) / (c.waves == 8 ? 256 : 512);
+    const double r = c.waves == 4 && rounds <= 0.5 ? 0.7 : rounds <= 3.0 ? (double)(int)(rounds + 0.999999) : rounds + 0.5;
+    const int cc = pointwise ? c.cc1 : c.cc3;
+    const int chunks = (p.c + cc - 1) / cc;
+    const double chunk = pointwise ? c.chunk1 : p.stride_h == 2 ? 1.35 * c.chunk3 : c.chunk3;
+    const double t = fixed + r * ((pointwise ? c.round1 : c.round3) + chunks * chunk);
+    if (best < 0 || t < *cost) {
+      best = f;
+      *cost = t;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+// The form to run a layer in, -1: not a layer for this kernel.
+int patch_f32_form(const Problem& p) {
+  const int mode = knob_or(KNOB_F32_PATCH, 1);          // 0: off, 2: any size (tests)
+  if (mode == 0 || p.b_is_kn || p.chain_n > 0 || p.groups != 1) return -1;
+  if (p.r != p.s || (p.r != 1 && p.r != 3) || p.stride_h != p.stride_w || (p.stride_h != 1 && p.stride_h != 2)) return -1;
+  if (p.r == 1 && (p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h >= p.h || (p.ow - 1) * p.stride_w >= p.w_)) return -1;
+  if (p.c % 8 != 0) return -1;
+  if (p.x_bytes > 0xF0000000u || p.w_bytes > (1u << 30) || (long long)p.M * p.k * 4 > 0xF0000000LL) return -1;   // 32-bit byte offsets
+  double cost = 0.0;
+  const int form = cheapest_form(p, &cost);
+  const int forced = knob_or(KNOB_F32_PATCH_TILE, -1);
+  if (mode == 2) return forced >= 0 ? forced : form;
+  // Against what the layer would take elsewhere: on the fp32 matrix cores 8 us (6 for pointwise) and 75 TFLOP/s, or what
+  // its tensors take at 3 TB/s; on the one-launch kernel for few pixels 3.5 us and 32 TFLOP/s.  The margin covers both
+  // estimates' errors where the kernels are close.
+  const double us = 2e-6 * p.M * (double)p.k * p.Kgemm;
+  const bool small = conv_small_f32_applicable(p) || conv_small_f32_splits(p) > 0;
+  const double bytes = (double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1);
+  double other = p.r == 3 ? 8.0 + us / 75.0 : 6.0 + (us / 75.0 > bytes / 3e6 ? us / 75.0 : bytes / 3e6);
+  if (small && 3.5 + us / 32.0 < other) other = 3.5 + us / 32.0;
+  return cost + (p.r == 1 || small ? 1.6 : 0.5) < other ? (forced >= 0 ? forced : form) : -1;
+}
+
+size_t patch_f32_pack_bytes(const Problem& p) { return (p.w_bytes + 255) / 256 * 256 + 4 * (size_t)p.k; }
+
+hipError_t launch_patch_f32(const Problem& p_in, int form, hipStream_t stream, const char** variant) {
+  Problem p = p_in;
+  if (!p.planes) return hipErrorInvalidValue;           // the ABI layer never plans this kernel without a workspace
+  unsigned char* planes = static_cast<unsigned char*>(const_cast<void*>(p.planes));
+  unsigned* words = reinterpret_cast<unsigned*>(planes + (p.w_bytes + 255) / 256 * 256);
+  const int row8 = p.Kgemm / 8;
+  const float* w = static_cast<const float*>(p.w);
+  unsigned short* out = reinterpret_cast<unsigned short*>(planes);
+  const long long elems = (long long)(p.w_bytes >> 2);
+  if (row8 <= 128)                                      // two values of eight per lane: a wavefront per channel
+    hipLaunchKernelGGL(cut_filter_kernel<1>, dim3((unsigned)((p.k + 31) / 32 * 8)), dim3(256), 0, stream, w, out, p.k, row8, elems, words);
+  else
+    hipLaunchKernelGGL(cut_filter_kernel<4>, dim3((unsigned)((p.k + 7) / 8 * 8)), dim3(256), 0, stream, w, out, p.k, row8, elems, words);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  p.w_planes = planes;
+  p.w_range = words;
+  return p.addend ? launch_patch_shape<true>(p, form, stream, variant) : launch_patch_shape<false>(p, form, stream, variant);
+}
+
+}  // namespace glowmi

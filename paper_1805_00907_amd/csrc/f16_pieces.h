@@ -16,10 +16,10 @@
 //   and the sum is scaled back by 2^-(se + se').  Dropped: 2^-22 H2 H2', at most 2^-22 of |v v'|; with the cuts'
 //   own rounding a product is within 3 * 2^-22 of |v v'| in the worst case, a few times the rounding an fp32
 //   multiply-add makes anyway and far below what accumulating a long reduction in fp32 adds.
-//   Values more than 2^28 below the tensor's largest magnitude fall under fp16's normal range after scaling;
-//   they are carried by H2 alone (h1 = 0) with 11 significant bits, an absolute error below 2^-39 of the
-//   largest magnitude, and the product of two such values (one from each operand, below 2^-56 of the largest
-//   product) is dropped.
+//   Values more than 2^28 below the tensor's largest magnitude fall under fp16's normal range after scaling.  Planes in
+//   memory carry them by H2 alone (h1 = 0) with 11 significant bits, an absolute error below 2^-39 of the largest magnitude,
+//   and the product of two such values (one from each operand, below 2^-56 of the largest product) is dropped; an operand
+//   cut inside a kernel keeps the subnormal h1 and H2 with what is left, an error below 2^-50.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -28,6 +28,7 @@ namespace glowmi {
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr float kLowPieceWeight = 0x1p-11f;            // weight of the second accumulator set
 
@@ -38,6 +39,19 @@ __device__ __forceinline__ int scale_exponent(unsigned max_bits) {
   return 141 - eb;
 }
 
+// Largest of the lanes' words: every lane returns it.  Lane permutations inside the vector unit (DPP): neighbours, pairs,
+// halves of a row of 16, rows, then row ends to the rows behind them; lane 63 has seen all.
+__device__ __forceinline__ unsigned wave_max_u32(unsigned m) {
+  auto take = [&m](unsigned o) { m = o > m ? o : m; };
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0x4E, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0x141, 0xf, 0xf, false));   // row_half_mirror
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0x140, 0xf, 0xf, false));   // row_mirror
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0x142, 0xa, 0xf, false));   // row_bcast15 into rows 1 and 3
+  take((unsigned)__builtin_amdgcn_update_dpp((int)m, (int)m, 0x143, 0xc, 0xf, false));   // row_bcast31 into rows 2 and 3
+  return (unsigned)__builtin_amdgcn_readlane((int)m, 63);
+}
+
 // Largest of n words at src, by one wavefront on its own (no LDS, no barrier); every lane returns it.
 __device__ __forceinline__ unsigned wave_max_words(const unsigned* __restrict__ src, int n) {
   unsigned m = 0;
@@ -45,33 +59,22 @@ __device__ __forceinline__ unsigned wave_max_words(const unsigned* __restrict__ 
     const unsigned v = src[i];
     m = v > m ? v : m;
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const unsigned o = (unsigned)__shfl_xor((int)m, d, 64);
-    m = o > m ? o : m;
-  }
-  return (unsigned)__builtin_amdgcn_readfirstlane((int)m);
+  return wave_max_u32(m);
 }
 
-// Largest magnitude (bits) among 8 * N prefetched values held as N pairs of float4, over the whole wavefront.
+// Largest magnitude (bits) among 8 * N prefetched values held as N pairs of float4, over the whole wavefront.  A NaN
+// among numbers is left out of it (an infinity is not): it reaches the results it belongs to through its pieces.
 template <int N, typename V4>
 __device__ __forceinline__ unsigned wave_max_of(const V4 (&pre)[N][2]) {
-  unsigned m = 0;
+  float m = 0.f;
 #pragma unroll
   for (int q = 0; q < N; ++q)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned b = __builtin_bit_cast(unsigned, pre[q][h][e]) & 0x7fffffffu;
-        m = b > m ? b : m;
-      }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const unsigned o = (unsigned)__shfl_xor((int)m, d, 64);
-    m = o > m ? o : m;
-  }
-  return (unsigned)__builtin_amdgcn_readfirstlane((int)m);
+      for (int e = 0; e < 4; e += 2)                   // magnitudes are a source modifier, and no quieting in front
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(pre[q][h][e]), "v"(pre[q][h][e + 1]));
+  return wave_max_u32(__builtin_bit_cast(unsigned, m) & 0x7fffffffu);
 }
 
 // The largest of the eight words the wavefronts of a workgroup left at `words` (LDS).
@@ -85,28 +88,44 @@ __device__ __forceinline__ unsigned max_of_eight(const unsigned* words) {
   return (unsigned)__builtin_amdgcn_readfirstlane((int)m);
 }
 
+// The cut as planes in memory hold it (a form that callers may keep): below fp16's normal range h1 is zero and the second
+// piece carries the value.
+__device__ __forceinline__ void cut8(const float (&v)[8], int se, v4u& p1, v4u& p2) {
+  _Float16 h1[8], h2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float x = __builtin_ldexpf(v[i], se);
+    h1[i] = (_Float16)x;
+    if (__builtin_fabsf(x) < 0x1p-14f) h1[i] = (_Float16)0.f;
+    h2[i] = (_Float16)((x - (float)h1[i]) * 2048.f);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    p1[i] = __builtin_bit_cast(unsigned, v2h{h1[2 * i], h1[2 * i + 1]});
+    p2[i] = __builtin_bit_cast(unsigned, v2h{h2[2 * i], h2[2 * i + 1]});
+  }
+}
+
+// The cut inside a kernel: 3.5 instructions a value instead of ten (scale, 2^11 times that, half a packed conversion, and
+// the remainder as one fma from fp16 back to fp16).  A subnormal h1 stays: the matrix instructions keep it.
+__device__ __forceinline__ void cut8_in_place(const float (&x)[8], int se, v4u& p1, v4u& p2) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const v2f v = {__builtin_ldexpf(x[2 * i], se), __builtin_ldexpf(x[2 * i + 1], se)};
+    const v2h h1 = __builtin_convertvector(v, v2h);    // round to nearest
+    const v2h h2 = {(_Float16)__builtin_fmaf((float)h1[0], -2048.f, v[0] * 2048.f),
+                    (_Float16)__builtin_fmaf((float)h1[1], -2048.f, v[1] * 2048.f)};   // exact before the one rounding
+    p1[i] = __builtin_bit_cast(unsigned, h1);
+    p2[i] = __builtin_bit_cast(unsigned, h2);
+  }
+}
 struct Cut2 { _Float16 h1, h2; };
 __device__ __forceinline__ Cut2 cut2(float x, int se) {
   const float v = __builtin_ldexpf(x, se);
-  _Float16 h1 = (_Float16)v;
-  if (__builtin_fabsf(v) < 0x1p-14f) h1 = (_Float16)0.f;   // below fp16's normal range: the second piece carries it
-  const float r = v - (float)h1;
   Cut2 c;
-  c.h1 = h1;
-  c.h2 = (_Float16)(r * 2048.f);
+  c.h1 = (_Float16)v;
+  c.h2 = (_Float16)__builtin_fmaf((float)c.h1, -2048.f, v * 2048.f);
   return c;
-}
-
-// eight consecutive values -> eight fp16 (16 bytes) per piece
-__device__ __forceinline__ void cut8(const float (&v)[8], int se, v4u& p1, v4u& p2) {
-  Cut2 e[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) e[i] = cut2(v[i], se);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    p1[i] = __builtin_bit_cast(unsigned, v2h{e[2 * i].h1, e[2 * i + 1].h1});
-    p2[i] = __builtin_bit_cast(unsigned, v2h{e[2 * i].h2, e[2 * i + 1].h2});
-  }
 }
 
 // The two operands' largest magnitudes (bits) -> what the accumulators are scaled back by, and what is added to

@@ -706,6 +706,17 @@ Plan plan_f32(const Problem& p, bool allow_split) {
       pl.pack_bytes = k3_f32_pack_bytes(p);
       return pl;
     }
+    // 1x1 and 3x3 of ordinary size, the input cut tile by tile, the filter into the workspace; pointwise layers over few
+    // channels on many pixels are faster on the kernel that keeps the filter in registers
+    if (allow_split && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p))) {
+      const int form = patch_f32_form(p);
+      if (form >= 0) {
+        pl.kernel = KERNEL_PATCH;
+        pl.tile = form;
+        pl.pack_bytes = patch_f32_pack_bytes(p);
+        return pl;
+      }
+    }
     // large contractions with a workspace to repack the operands into: the kernel over fp16 planes
     if (allow_split && p.allow_pack && p3_f32_applicable(p)) return plan_p3_f32(p);
     if (pw_f32_applicable(p)) { pl.kernel = KERNEL_PW; return pl; }
@@ -849,6 +860,7 @@ hipError_t launch_f32(const Problem& p_in, const Plan& plan, hipStream_t stream,
     case KERNEL_P3: return launch_p3_f32(p_in, plan, stream, variant);
     case KERNEL_K3C64: return launch_k3c64_f32(p_in, stream, variant);
     case KERNEL_K3: return launch_k3_f32(p_in, stream, variant);
+    case KERNEL_PATCH: return launch_patch_f32(p_in, plan.tile, stream, variant);
     default: break;
   }
   if (plan.split_k > 1 && !p_in.partial) return hipErrorInvalidValue;   // the ABI layer never plans a split without a workspace

@@ -1,0 +1,120 @@
+"""The fp32 convolution kernel for layers of ordinary size (conv_patch_f32: 1x1 and 3x3, stride 1 or 2, fp16 piece products)
+through the C ABI against the CPU oracle, element by element, |gpu - oracle| <= 1e-5 + 1e-4 |oracle|: every tile form on
+maps, channel counts and strides that leave it ragged, with and without the add link, plain and with the filter's planes
+made ahead of time; componentwise accuracy over 24 binades, chunks of very different magnitude in either order, and
+non-finite inputs."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import oracle
+from paper_1805_00907_amd import workloads as wl
+
+
+def _gpu():
+    import gpu_util
+    return gpu_util
+
+
+# n  h   w   c    k   r  stride pad
+SHAPES = [
+    (1, 8, 8, 8, 8, 3, 1, 1),          # one tile, one short chunk
+    (2, 9, 13, 40, 24, 3, 1, 1),       # ragged tiles, a chunk of eight channels behind a whole one
+    (1, 7, 7, 96, 72, 3, 1, 1),        # a map smaller than a tile, channel tile of eight
+    (3, 15, 10, 64, 130, 3, 1, 0),     # no padding, channel tiles of two
+    (1, 33, 21, 32, 64, 3, 1, 1),
+    (2, 16, 16, 64, 64, 3, 2, 1),      # stride 2
+    (1, 13, 17, 72, 40, 3, 2, 1),
+    (1, 9, 64, 32, 32, 3, 2, 1),
+    (2, 11, 9, 64, 100, 1, 1, 0),      # pointwise: the last tile's pixels end inside it
+    (1, 5, 5, 264, 40, 1, 1, 0),
+    (3, 14, 11, 72, 136, 1, 2, 0),     # pointwise, stride 2
+    (1, 3, 70, 8, 33, 1, 2, 0),
+]
+
+
+def _inputs(seed, n, h, w, c, k, r):
+    rng = np.random.default_rng(seed)
+    x = rng.uniform(-1, 1, size=(n, h, w, c)).astype(np.float32)
+    wt = (rng.standard_normal(size=(k, r, r, c)) / np.sqrt(r * r * c)).astype(np.float32)
+    b = rng.uniform(-0.1, 0.1, size=(k,)).astype(np.float32)
+    return x, wt, b, rng
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("tile", range(7))
+def test_conv_patch(shape, tile, knobs):
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    n, h, w, c, k, r, st, pd = shape
+    if (tile == 1 and r == 1) or (tile != 1 and (r, st) == (3, 2)):
+        pytest.skip("no such form")
+    knobs.set("F32_PATCH", 2)
+    knobs.set("F32_PATCH_TILE", tile)
+    knobs.set("F32_K3", 0)
+    knobs.set("F32_K3C64", 0)
+    x, wt, b, rng = _inputs(37000 + c + k, n, h, w, c, k, r)
+    desc = G.make_desc(x.shape, wt.shape, (st, st), (pd,) * 4, 1)
+    ref = oracle.conv2d_f32(x, wt, b, (st, st), (pd,) * 4, 1, act=wl.ACT_RELU)
+    got, variant = G.gpu_conv2d_f32(x, wt, b, desc, wl.ACT_RELU)
+    assert variant.startswith("conv_patch_f32_f16x3"), variant
+    G.assert_close_f32(got, ref, f"{shape} [{variant}]")
+    add = rng.uniform(-1, 1, size=ref.shape).astype(np.float32)
+    ref = oracle.conv2d_f32_add(x, wt, None, add, (st, st), (pd,) * 4, 1, act=wl.ACT_NONE)
+    for in_place in (False, True):
+        got, variant = G.gpu_conv2d_f32_chain(x, wt, None, add, desc, wl.ACT_NONE, in_place=in_place)
+        assert variant.startswith("conv_patch_f32_f16x3") and variant.endswith("_add"), variant
+        G.assert_close_f32(got, ref, f"{shape} add [{variant}]")
+    planes = torch.empty(glowmi.conv2d_filter_planes_bytes(desc), dtype=torch.uint8, device="cuda:0")
+    wd = G.dev(wt)
+    glowmi.conv2d_pack_filter(wd, desc, planes)
+    y = G.poison(ref.shape, torch.float32)
+    ws = torch.empty(glowmi.conv2d_packed_workspace_bytes(desc), dtype=torch.uint8, device="cuda:0")
+    glowmi.conv2d_packed(G.dev(x), wd, planes, None, y, desc, addend=G.dev(add), act=wl.ACT_NONE, workspace=ws)
+    torch.cuda.synchronize()
+    assert glowmi.last_variant() == variant
+    G.assert_close_f32(y.cpu().numpy(), ref, f"{shape} packed [{variant}]")
+
+
+@pytest.mark.parametrize("r,st", [(3, 1), (3, 2), (1, 1)])
+def test_conv_patch_wide_value_ranges(r, st, knobs):
+    G = _gpu()
+    knobs.set("F32_PATCH", 2)
+    knobs.set("F32_K3", 0)
+    knobs.set("F32_K3C64", 0)
+    n, h, w, c, k, pd = 2, 12, 12, 160, 40, r // 2
+    x, wt, b, rng = _inputs(37500 + r + st, n, h, w, c, k, r)
+    desc = G.make_desc(x.shape, wt.shape, (st, st), (pd,) * 4, 1)
+
+    def bound(xv, wv):
+        mag = oracle.conv2d_f32(np.abs(xv), np.abs(wv), np.abs(b), (st, st), (pd,) * 4, 1)
+        return 4 * 2.0 ** -22 * mag.astype(np.float64)
+
+    # 24 binades of magnitudes in both operands
+    xs = (x * np.exp2(rng.integers(-12, 13, size=x.shape))).astype(np.float32)
+    ws = (wt * np.exp2(rng.integers(-12, 13, size=wt.shape))).astype(np.float32)
+    for xv, wv in ((xs, wt), (x, ws), (xs, ws)):
+        ref = oracle.conv2d_f32(xv, wv, b, (st, st), (pd,) * 4, 1)
+        got, variant = G.gpu_conv2d_f32(xv, wv, b, desc, wl.ACT_NONE)
+        assert variant.startswith("conv_patch_f32_f16x3"), variant
+        assert np.all(np.abs(got.astype(np.float64) - ref) <= bound(xv, wv) + 1e-30), variant
+    # channel groups of very different magnitude, growing and shrinking: the accumulators are scaled along
+    for order in (1, -1):
+        xv = (x * np.exp2(order * 20.0 * (np.arange(c) // 32)).astype(np.float32)[None, None, None, :]).astype(np.float32)
+        ref = oracle.conv2d_f32(xv, wt, b, (st, st), (pd,) * 4, 1)
+        got, variant = G.gpu_conv2d_f32(xv, wt, b, desc, wl.ACT_NONE)
+        assert np.all(np.abs(got.astype(np.float64) - ref) <= bound(xv, wt) + 1e-30), (order, variant)
+    # zeros, and non-finite values: what they reach is not finite, nothing is finite and wrong
+    got, _ = G.gpu_conv2d_f32(np.zeros_like(x), wt, b, desc, wl.ACT_NONE)
+    assert np.array_equal(got, np.broadcast_to(b, got.shape))
+    xv = x.copy()
+    xv[1, 5, 5, 3] = np.inf
+    xv[0, 2, 2, 40] = np.nan
+    ref = oracle.conv2d_f32(xv, wt, b, (st, st), (pd,) * 4, 1)
+    got, _ = G.gpu_conv2d_f32(xv, wt, b, desc, wl.ACT_NONE)
+    reached = ~np.isfinite(ref)
+    assert reached.any() and not np.isfinite(got[reached]).any()
+    ok = np.isfinite(got)
+    assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 + 1e-4 * np.abs(ref[ok]))
