@@ -632,7 +632,8 @@ int cheapest_form(const Problem& p, double* cost) {
 // The form to run a layer in, -1: not a layer for this kernel.
 int patch_f32_form(const Problem& p) {
   const int mode = knob_or(KNOB_F32_PATCH, 1);          // 0: off, 2: any size (tests)
-  if (mode == 0 || p.b_is_kn || p.chain_n > 0 || p.groups != 1) return -1;
+  if (mode == 0 || (mode == 1 && knob_or(KNOB_F32_P3, 1) == 0)) return -1;   // either switch: such layers stay on the fp32 matrix cores
+  if (p.b_is_kn || p.chain_n > 0 || p.groups != 1) return -1;
   if (p.r != p.s || (p.r != 1 && p.r != 3) || p.stride_h != p.stride_w || (p.stride_h != 1 && p.stride_h != 2)) return -1;
   if (p.r == 1 && (p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h >= p.h || (p.ow - 1) * p.stride_w >= p.w_)) return -1;
   if (p.c % 8 != 0) return -1;

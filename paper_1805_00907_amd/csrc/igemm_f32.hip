@@ -714,6 +714,13 @@ Plan plan_f32(const Problem& p, bool allow_split) {
         pl.kernel = KERNEL_PATCH;
         pl.tile = form;
         pl.pack_bytes = patch_f32_pack_bytes(p);
+        // the workspace to ask for stays what the contraction over planes asks for where the layer could run there too: a
+        // caller's buffer of that size serves either
+        if (p3_f32_applicable(p)) {
+          const Plan p3 = plan_p3_f32(p);
+          const size_t ask = p3.pack_bytes + (p3.split_k > 1 ? (size_t)p3.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
+          if (ask > pl.pack_bytes) pl.pack_bytes = ask;
+        }
         return pl;
       }
     }
