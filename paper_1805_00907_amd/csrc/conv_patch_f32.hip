@@ -414,47 +414,63 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
   }
 }
 
-// The filter [k][r][s][c] as two planes [Kgemm / 8][k][8], each output channel by a scale of its own, in one launch: WPR
-// wavefronts take a channel, hold up to 32 of its values per lane in registers (what is beyond is read twice), find the
-// largest magnitude, leave its bits in words[channel] and cut.  The eight consecutive reduction indices of a channel are 16
-// bytes and the channels lie side by side, so the fragment of 32 channels x 16 indices that a wavefront multiplies is two
-// runs of 512 bytes; as rows of one channel it is 32 lines of which 32 bytes each are wanted, and a CU fetches it at a
-// quarter of the rate (8 KB in 0.22 instead of 0.058 us).
-template <int WPR>
-__global__ __launch_bounds__(256) void cut_filter_kernel(const float* __restrict__ w, unsigned short* __restrict__ dst, int rows,
-                                                         int row8, long long plane_elems, unsigned* __restrict__ words) {
-  constexpr int HELD = 4, STEP = 64 * WPR;
-  __shared__ unsigned red[4];
+// The filter [k][r][s][c] as two planes [Kgemm / 8][k][8], each output channel by a scale of its own, in one launch.  The
+// eight consecutive reduction indices of a channel are 16 bytes and the channels lie side by side, so the fragment of 32
+// channels x 16 indices that a wavefront multiplies is two runs of 512 bytes; as rows of one channel it is 32 lines of which
+// 32 bytes each are wanted, and a CU fetches it at a quarter of the rate (8 KB in 0.22 instead of 0.058 us).
+// A workgroup takes eight channels, so that it writes whole 128-byte lines (one channel at a time, 16 bytes of eight lines
+// here and there, 512 x 4608 took 9 us instead of 5): a wavefront finds each one's largest magnitude and its bits go into
+// words[channel]; then the workgroup cuts its part of the reduction of all eight.  Where eight channels at a time leave CUs
+// idle, `parts` workgroups share them, each measuring for itself.
+constexpr int CUT_ROWS = 8;
+__global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const float* __restrict__ w, unsigned short* __restrict__ dst, int rows,
+                                                                   int row8, int parts, long long plane_elems,
+                                                                   unsigned* __restrict__ words) {
+  __shared__ unsigned largest[CUT_ROWS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // consecutive channels on one XCD: the 16-byte pieces of a line then meet in its L2
+  // the parts of a group on one XCD, whose L2 serves the measuring of all but the first
   const int block = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  const int row = WPR == 1 ? block * 4 + wave : block;
-  if (row >= rows) return;                              // whole wavefronts; a whole workgroup where it has barriers
-  const int first = WPR == 1 ? lane : (int)threadIdx.x;
-  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(w) + (size_t)row * row8 * 2;
+  const int group = block / parts, part = block - group * parts;
+  if (group * CUT_ROWS >= rows) return;
+  const v4f* __restrict__ w4 = reinterpret_cast<const v4f*>(w);
+  // what this thread will cut, asked for first: two trips to memory become one
+  constexpr int HELD = 4, STEP = 64;
+  const int r = (int)threadIdx.x & (CUT_ROWS - 1), row = group * CUT_ROWS + r;
+  const int per = (row8 + parts - 1) / parts;
+  const int first = part * per + (int)threadIdx.x / CUT_ROWS;
+  const int end = row < rows ? ((part + 1) * per < row8 ? (part + 1) * per : row8) : 0;
+  const v4f* __restrict__ src = w4 + (size_t)row * row8 * 2;
   v4f held[HELD][2];
 #pragma unroll
   for (int q = 0; q < HELD; ++q) {
-    const int g = first + q * STEP;
     const v4f zero = {0.f, 0.f, 0.f, 0.f};
-    held[q][0] = g < row8 ? src[2 * g] : zero;
-    held[q][1] = g < row8 ? src[2 * g + 1] : zero;
+    const int g = first + q * STEP;
+    held[q][0] = g < end ? src[2 * g] : zero;
+    held[q][1] = g < end ? src[2 * g + 1] : zero;
   }
-  unsigned m = wave_max_of(held);
-  for (int g0 = HELD * STEP; g0 < row8; g0 += STEP) {
-    const int g = g0 + first < row8 ? g0 + first : row8 - 1;
-    const v4f again[1][2] = {{src[2 * g], src[2 * g + 1]}};
-    const unsigned o = wave_max_of(again);
-    m = o > m ? o : m;
-  }
-  if (WPR > 1) {
-    if (lane == 0) red[wave] = m;
-    __syncthreads();
+  {
+    const int mine = group * CUT_ROWS + wave;
+    unsigned m = 0;
+    if (mine < rows) {
+      const v4f* __restrict__ all = w4 + (size_t)mine * row8 * 2;
+      constexpr int PAIRS = 5;                          // of loads in flight
+      for (int g0 = lane; g0 < 2 * row8; g0 += 128 * PAIRS) {
+        v4f v[PAIRS][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) m = red[i] > m ? red[i] : m;
+        for (int q = 0; q < 2 * PAIRS; ++q) {
+          const int g = g0 + 64 * q;
+          v[q / 2][q % 2] = all[g < 2 * row8 ? g : 2 * row8 - 1];
+        }
+        const unsigned o = lane_max_of(v);
+        m = o > m ? o : m;
+      }
+      m = wave_max_u32(m);
+      if (part == 0 && lane == 0) words[mine] = m;
+    }
+    if (lane == 0) largest[wave] = m;
   }
-  if (first == 0) words[row] = m;
-  const int se = scale_exponent(m);
+  __syncthreads();
+  const int se = scale_exponent(largest[r]);
   auto write = [&](int g, const v4f& a, const v4f& b) {
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     v4u p1, p2;
@@ -465,8 +481,8 @@ __global__ __launch_bounds__(256) void cut_filter_kernel(const float* __restrict
   };
 #pragma unroll
   for (int q = 0; q < HELD; ++q)
-    if (first + q * STEP < row8) write(first + q * STEP, held[q][0], held[q][1]);
-  for (int g = first + HELD * STEP; g < row8; g += STEP) write(g, src[2 * g], src[2 * g + 1]);
+    if (first + q * STEP < end) write(first + q * STEP, held[q][0], held[q][1]);
+  for (int g = first + HELD * STEP; g < end; g += STEP) write(g, src[2 * g], src[2 * g + 1]);
 }
 
 int patch_pitch(int tw, int st) {
@@ -664,10 +680,13 @@ hipError_t launch_patch_f32(const Problem& p_in, int form, hipStream_t stream, c
   const float* w = static_cast<const float*>(p.w);
   unsigned short* out = reinterpret_cast<unsigned short*>(planes);
   const long long elems = (long long)(p.w_bytes >> 2);
-  if (row8 <= 128)                                      // two values of eight per lane: a wavefront per channel
-    hipLaunchKernelGGL(cut_filter_kernel<1>, dim3((unsigned)((p.k + 31) / 32 * 8)), dim3(256), 0, stream, w, out, p.k, row8, elems, words);
-  else
-    hipLaunchKernelGGL(cut_filter_kernel<4>, dim3((unsigned)((p.k + 7) / 8 * 8)), dim3(256), 0, stream, w, out, p.k, row8, elems, words);
+  const int groups = (p.k + CUT_ROWS - 1) / CUT_ROWS;
+  int parts = 256 / groups;
+  if (parts > (row8 + 15) / 16) parts = (row8 + 15) / 16;   // at least two wavefronts' work each
+  if (parts > 8) parts = 8;
+  if (parts < 1) parts = 1;
+  hipLaunchKernelGGL(cut_filter_kernel, dim3((unsigned)((groups * parts + 7) / 8 * 8)), dim3(64 * CUT_ROWS), 0, stream, w, out, p.k, row8, parts, elems,
+                     words);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   p.w_planes = planes;

@@ -62,10 +62,10 @@ __device__ __forceinline__ unsigned wave_max_words(const unsigned* __restrict__ 
   return wave_max_u32(m);
 }
 
-// Largest magnitude (bits) among 8 * N prefetched values held as N pairs of float4, over the whole wavefront.  A NaN
+// Largest magnitude (bits) among 8 * N prefetched values held as N pairs of float4: of the lane, over the wavefront.  A NaN
 // among numbers is left out of it (an infinity is not): it reaches the results it belongs to through its pieces.
 template <int N, typename V4>
-__device__ __forceinline__ unsigned wave_max_of(const V4 (&pre)[N][2]) {
+__device__ __forceinline__ unsigned lane_max_of(const V4 (&pre)[N][2]) {
   float m = 0.f;
 #pragma unroll
   for (int q = 0; q < N; ++q)
@@ -74,8 +74,10 @@ __device__ __forceinline__ unsigned wave_max_of(const V4 (&pre)[N][2]) {
 #pragma unroll
       for (int e = 0; e < 4; e += 2)                   // magnitudes are a source modifier, and no quieting in front
         asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(pre[q][h][e]), "v"(pre[q][h][e + 1]));
-  return wave_max_u32(__builtin_bit_cast(unsigned, m) & 0x7fffffffu);
+  return __builtin_bit_cast(unsigned, m) & 0x7fffffffu;
 }
+template <int N, typename V4>
+__device__ __forceinline__ unsigned wave_max_of(const V4 (&pre)[N][2]) { return wave_max_u32(lane_max_of(pre)); }
 
 // The largest of the eight words the wavefronts of a workgroup left at `words` (LDS).
 __device__ __forceinline__ unsigned max_of_eight(const unsigned* words) {

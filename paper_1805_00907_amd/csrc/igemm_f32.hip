@@ -693,36 +693,40 @@ Plan plan_f32(const Problem& p, bool allow_split) {
     // kernels of their own, no workspace
     if (dw_f32_applicable(p)) { pl.kernel = KERNEL_DW; return pl; }
     if (smallc_f32_applicable(p) && !p.addend) { pl.kernel = KERNEL_SMALLC; return pl; }
-    // 3x3 over 64 channels on many pixels, with the filter's planes given or room in the workspace for them
-    const bool filter_planes = p.w_packed != nullptr || (allow_split && p.allow_pack);   // given, or room to make them
-    if (filter_planes && k3c64_f32_applicable(p)) {
+    // 1x1 and 3x3 layers, the input cut tile by tile and the filter into the workspace; pointwise layers over few channels
+    // on many pixels are faster on the kernel that keeps the filter in registers
+    int form = -1;
+    if (allow_split && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p)))
+      form = patch_f32_form(p);
+    // the 3x3 tile kernels, which need the filter's planes given or room in the workspace for them: without a workspace, and
+    // where planes are given and the tiles fill the machine (there they save the cut of the filter, and the layer the
+    // workspace: 512 -> 512 on 28x28 at batch 16 182 us, 185 on the patch kernel; cutting the filter in the call 196 and 188)
+    const bool filter_planes = p.w_packed != nullptr || (allow_split && p.allow_pack);
+    const bool k3c64 = filter_planes && k3c64_f32_applicable(p), k3 = filter_planes && !k3c64 && k3_f32_applicable(p);
+    if (k3c64 && (form < 0 || knob_is_set(KNOB_F32_K3C64_MIN_TILES))) {
       pl.kernel = KERNEL_K3C64;
       pl.pack_bytes = k3c64_f32_pack_bytes(p);
       return pl;
     }
-    // 3x3 stride 1 with many channels on maps that tile into 16 x 16 blocks, again only the filter repacked
-    if (filter_planes && k3_f32_applicable(p)) {
+    if (k3 && (form < 0 || knob_or(KNOB_F32_K3_ANY, 0) != 0 || (p.w_packed && k3v_f32_efficiency(p) >= 0.85))) {
       pl.kernel = KERNEL_K3;
       pl.pack_bytes = k3_f32_pack_bytes(p);
       return pl;
     }
-    // 1x1 and 3x3 of ordinary size, the input cut tile by tile, the filter into the workspace; pointwise layers over few
-    // channels on many pixels are faster on the kernel that keeps the filter in registers
-    if (allow_split && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p))) {
-      const int form = patch_f32_form(p);
-      if (form >= 0) {
-        pl.kernel = KERNEL_PATCH;
-        pl.tile = form;
-        pl.pack_bytes = patch_f32_pack_bytes(p);
-        // the workspace to ask for stays what the contraction over planes asks for where the layer could run there too: a
-        // caller's buffer of that size serves either
-        if (p3_f32_applicable(p)) {
-          const Plan p3 = plan_p3_f32(p);
-          const size_t ask = p3.pack_bytes + (p3.split_k > 1 ? (size_t)p3.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
-          if (ask > pl.pack_bytes) pl.pack_bytes = ask;
-        }
-        return pl;
+    if (form >= 0) {
+      pl.kernel = KERNEL_PATCH;
+      pl.tile = form;
+      pl.pack_bytes = patch_f32_pack_bytes(p);
+      // the workspace to ask for stays what the kernel asks for that would run otherwise: a buffer of that size serves either
+      size_t ask = 0;
+      if (k3c64) ask = k3c64_f32_pack_bytes(p);
+      else if (k3) ask = k3_f32_pack_bytes(p);
+      else if (p3_f32_applicable(p)) {
+        const Plan p3 = plan_p3_f32(p);
+        ask = p3.pack_bytes + (p3.split_k > 1 ? (size_t)p3.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
       }
+      if (ask > pl.pack_bytes) pl.pack_bytes = ask;
+      return pl;
     }
     // large contractions with a workspace to repack the operands into: the kernel over fp16 planes
     if (allow_split && p.allow_pack && p3_f32_applicable(p)) return plan_p3_f32(p);
