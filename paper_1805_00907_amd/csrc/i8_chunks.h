@@ -87,6 +87,28 @@ __device__ __forceinline__ i8x16 byte_mask(int valid) {
   return m;
 }
 
+// The first n (1 .. 15) of 16 codes, to any address.
+__device__ __forceinline__ void store_front(signed char* dst, i8x16 v, int n) {
+  int lo = v[0], hi = v[1];
+  if (n & 8) {
+    __builtin_memcpy(dst, &v, 8);
+    dst += 8;
+    lo = v[2];
+    hi = v[3];
+  }
+  if (n & 4) {
+    __builtin_memcpy(dst, &lo, 4);
+    dst += 4;
+    lo = hi;
+  }
+  if (n & 2) {
+    __builtin_memcpy(dst, &lo, 2);
+    dst += 2;
+    lo = (int)((unsigned)lo >> 16);
+  }
+  if (n & 1) *dst = (signed char)lo;
+}
+
 // acc plus the signed bytes of v (ones = 0x01010101), or acc (ones = 0)
 __device__ __forceinline__ int sum_bytes(i8x16 v, int ones, int acc) {
 #pragma unroll

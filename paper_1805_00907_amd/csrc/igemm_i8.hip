@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
   constexpr int A_BYTES = BM * LDQ, B_BYTES = BN * LDQ;
   constexpr int OUT_PITCH = BN + 16;                    // output tile staged in LDS, bytes per pixel row
   constexpr int XCH = KGRP > 1 ? KGRP * BM * BN * 4 : 0;  // partial tiles of the groups
-  static_assert(2 * KGRP * (A_BYTES + B_BYTES) >= XCH + BM * OUT_PITCH + (BM + 2 * BN) * 4, "epilogue reuses the staging LDS");
+  static_assert(2 * KGRP * (A_BYTES + B_BYTES) >= XCH + BM * OUT_PITCH + (BM + 2 * BN + 256) * 4, "epilogue reuses the staging LDS");
   static_assert(KGRP == 1 || (TM == 1 && TN == 1), "the groups share the outputs of one MFMA block per wavefront");
 
   extern __shared__ __align__(16) unsigned char ldsq[];
@@ -401,8 +401,28 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
   int* xsum = reinterpret_cast<int*>(out + BM * OUT_PITCH);
   int* wsum = xsum + BM;
   int* cterm = wsum + BN;
+  int* addlut = cterm + BN;                             // [256] the addend's code (as an unsigned byte) -> its term
+  constexpr int CHUNKS = BN / 16;                       // 16-byte pieces of a pixel row of the tile
   for (int i = all_tid; i < BM + BN; i += ALL_THREADS) xsum[i] = 0;
   __syncthreads();
+  const bool adding = !CHAINV && p.addend && p.split_k == 1;   // uniform: tensor-add link of the chain
+  if (adding) {
+    // The addend's tile into `out`, whole 16-byte pieces whatever the alignment (the tensor's last ones fetched from its
+    // last 16 bytes and shifted); its codes' terms once per workgroup.  Byte by byte, each rescaled for itself, a layer
+    // with an addend took twice as long as without (3x3 16 -> 512 on 37x37 at batch 24 50 us instead of 26).
+    const unsigned y_size = (unsigned)p.M * (unsigned)p.k < 16u ? 16u : (unsigned)p.M * (unsigned)p.k;
+    const __amdgpu_buffer_rsrc_t rsrc_add = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.addend), 0, (int)y_size, 0x00020000);
+    for (int i = all_tid; i < 256; i += ALL_THREADS) addlut[i] = rescale_term((int)(signed char)i - p.r_off, p.r_mant, p.r_shift);
+    for (int u = all_tid; u < BM * CHUNKS; u += ALL_THREADS) {
+      const int lr = u / CHUNKS, ch = u % CHUNKS;
+      const int row = tm * BM + lr, col = tn * BN + ch * 16;
+      unsigned off = row < p.M && col < p.kg ? (unsigned)row * (unsigned)p.k + (unsigned)(g * p.kg + col) : OOB;
+      const unsigned over = off != OOB && off > y_size - 16u ? off - (y_size - 16u) : 0u;
+      v4i v = __builtin_amdgcn_raw_buffer_load_b128(rsrc_add, off - over, 0, 0);
+      if (over) v = shift_down(v, over);
+      *reinterpret_cast<v4i*>(out + lr * OUT_PITCH + ch * 16) = v;
+    }
+  }
   if (need_xsum) {
 #pragma unroll
     for (int q = 0; q < A_PASSES; ++q) atomicAdd(&xsum[row0 + q * ROWS_PER_PASS], asum[q]);
@@ -445,7 +465,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
     }
   }
 
-  const signed char* addend = static_cast<const signed char*>(p.addend);   // may be the output itself
   if (p.split_k == 1) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -458,6 +477,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
         for (int q4 = 0; q4 < Q4S; ++q4) {
           const int lc = wn * WTN + j * 32 + (grp * Q4S + q4) * 8 + lhalf * 4;   // first of 4 consecutive channels
           const v4i ct = *reinterpret_cast<const v4i*>(cterm + lc);
+          unsigned* four = reinterpret_cast<unsigned*>(out + lr * OUT_PITCH + lc);
+          const unsigned codes = adding ? *four : 0u;
           unsigned packed = 0;
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
@@ -465,39 +486,26 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
             if (CHAINV) {                                             // general op list
               const int col = tn * BN + lc + t;
               if (row < p.M && col < p.kg) v = apply_chain_i8(p, v, (size_t)row * p.k + g * p.kg + col);
-            } else if (addend) {                                      // uniform: tensor-add link of the chain
-              const int col = tn * BN + lc + t;
-              const int code = (row < p.M && col < p.kg) ? (int)addend[(size_t)row * p.k + g * p.kg + col] : p.r_off;
-              v += rescale_term(code - p.r_off, p.r_mant, p.r_shift);
+            } else if (adding) {
+              v += addlut[(codes >> (8 * t)) & 0xffu];
             }
             packed |= ((unsigned)requantize(v, p.mant, p.shift, p.y_off, p.lo, p.hi) & 0xffu) << (t * 8);
           }
-          *reinterpret_cast<unsigned*>(out + lr * OUT_PITCH + lc) = packed;
+          *four = packed;
         }
       }
     }
     __syncthreads();
-    // copy out: 16 bytes of one pixel row per thread and pass
+    // copy out: 16 bytes of one pixel row per thread and pass, at whatever address the row starts
     signed char* __restrict__ Y = static_cast<signed char*>(p.y);
-    constexpr int CHUNKS = BN / 16;
-    const int align = (p.kg | p.k) & 15;                             // rows start at multiples of its lowest set bit
     for (int u = all_tid; u < BM * CHUNKS; u += ALL_THREADS) {
       const int lr = u / CHUNKS, ch = u % CHUNKS;
       const int row = tm * BM + lr, col = tn * BN + ch * 16;
       if (row >= p.M || col >= p.kg) continue;
       signed char* dst = Y + (size_t)row * p.k + g * p.kg + col;
-      const unsigned char* src = out + lr * OUT_PITCH + ch * 16;
-      if (align == 0) {
-        *reinterpret_cast<v4i*>(dst) = *reinterpret_cast<const v4i*>(src);
-      } else if ((align & 7) == 0) {
-        for (int e = 0; e < 16 && col + e < p.kg; e += 8)
-          *reinterpret_cast<v2i*>(dst + e) = *reinterpret_cast<const v2i*>(src + e);
-      } else if ((align & 3) == 0) {
-        for (int e = 0; e < 16 && col + e < p.kg; e += 4)
-          *reinterpret_cast<int*>(dst + e) = *reinterpret_cast<const int*>(src + e);
-      } else {
-        for (int e = 0; e < 16 && col + e < p.kg; ++e) dst[e] = (signed char)src[e];
-      }
+      const v4i codes = *reinterpret_cast<const v4i*>(out + lr * OUT_PITCH + ch * 16);
+      if (col + 16 <= p.kg) __builtin_memcpy(dst, &codes, 16);
+      else store_front(dst, codes, p.kg - col);
     }
   } else {
     int* __restrict__ part = static_cast<int*>(p.partial);
@@ -674,8 +682,10 @@ Plan plan_i8(const Problem& p, bool allow_split) {
     // at twice that many tiles the groups only take each other's room (3x3 19->119 on 68x94 at batch 3, 600 tiles: 10.6 -> 14.2)
     if (t64 <= 320 && pl.slabs >= 2) tile = pl.slabs >= 8 ? 7 : 6;
     // many tiles: the larger ones read each operand fewer times (3x3 120->128 on 56x56 at batch 16: 33 us with 64 x 64 tiles,
-    // 26 us with 128 x 128; 1x1 344->176 stride 2 on 85x86 at batch 11, three slabs: 11.1 -> 10.1 us with 128 x 64)
-    else if (!p.b_is_kn && t128 >= 256 && p.kg > 64 && pl.slabs >= 4) tile = 2;
+    // 26 us with 128 x 128; 1x1 344->176 stride 2 on 85x86 at batch 11, three slabs: 11.1 -> 10.1 us with 128 x 64; with a
+    // slab or two the output is what counts, and there have to be four tiles per CU: 1x1 40->896 on 40x40 at batch 24
+    // 36.1 us with 128 x 64, 30.4 with 128 x 128)
+    else if (!p.b_is_kn && t128 >= (pl.slabs >= 4 ? 256 : 1000) && p.kg > 64) tile = 2;
     else if (t64 >= 900) tile = 1;
   }
   pl.tile = tile;
