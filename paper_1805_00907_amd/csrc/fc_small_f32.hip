@@ -150,6 +150,109 @@ __global__ __launch_bounds__(FSF_THREADS) void fc_small_f32_kernel(const Problem
   static_cast<float*>(p.y)[(size_t)row * N + ocol] = v;
 }
 
+// ---- one to four rows on the vector units, the whole reduction of a strip of columns in one workgroup, any K and N.
+//
+// At these sizes a call is a latency, and the kernel that streams the matrix through every CU needs a second one for its
+// partial sums.  Here a workgroup of sixteen wavefronts owns 4 LPR columns: LPR lanes of four columns, 1024 / LPR rows at a
+// time, eight of those in flight.  The row's values come through LDS; the lanes' sums meet by lane permutations and then
+// through LDS in wavefront order (deterministic).  A CU takes in 16 lines of 64 bytes as slowly as 16 whole ones, so strips
+// are as wide as eight rows in flight per lane cover the reduction, and a matrix of some megabytes is better off on every CU:
+// 1 x 512 x 1000 5.4 us streamed, 4.2 here; 1 x 2048 x 1000 7.2 both; 2 x 2048 x 1000 7.4 and 8.7.  Rows that do not start
+// on 16 bytes, which the other kernels fetch value by value: 1 x 500 x 130 11.3 -> 4.2, 3 x 1536 x 777 12.5 -> 10.2.
+constexpr int FR_THREADS = 1024;
+constexpr int FR_DEPTH = 8;                  // rows of a lane in flight
+
+template <int MR, int LPR>
+__global__ __launch_bounds__(FR_THREADS) void fc_rows_f32_kernel(const Problem p, int strips) {
+  constexpr int ROWS = FR_THREADS / LPR;           // weight rows per pass
+  constexpr int COLS = 4 * LPR;
+  __shared__ float red[16 * MR * COLS];
+  extern __shared__ float xs[];                    // [MR][passes * ROWS]
+
+  const int per_xcd = gridDim.x >> 3;              // consecutive strips share lines: one XCD
+  const int strip = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (strip >= strips) return;
+  const int tid = threadIdx.x;
+  const int quad = tid % LPR, row0 = tid / LPR;
+  const int K = p.Kgemm, N = p.k;
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, (int)p.w_bytes, 0x00020000);
+  constexpr unsigned OOB = 0xFFFFFF00u;
+  const int col = strip * COLS + 4 * quad;
+  const unsigned first = ((unsigned)row0 * (unsigned)N + (unsigned)col) * 4u;
+  const unsigned pass_step = (unsigned)ROWS * (unsigned)N * 4u;
+  const int passes = (K + ROWS - 1) / ROWS;
+  auto load = [&](int pass) {                      // rows past the last one read zeros; columns past it are not stored
+    const unsigned off = col < N && row0 + pass * ROWS < K ? first + (unsigned)pass * pass_step : OOB;
+    return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, off, 0, 0));
+  };
+  v4f w[FR_DEPTH];
+#pragma unroll
+  for (int d = 0; d < FR_DEPTH; ++d) w[d] = load(d);
+  const float* __restrict__ x = static_cast<const float*>(p.x);
+  const int kpad = passes * ROWS;
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+    for (int k = tid; k < kpad; k += FR_THREADS) xs[m * kpad + k] = m < p.M && k < K ? x[(size_t)m * K + k] : 0.f;
+  __syncthreads();
+  v4f acc[MR];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) acc[m] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int pass = 0; pass < passes; pass += FR_DEPTH) {
+#pragma unroll
+    for (int d = 0; d < FR_DEPTH; ++d) {
+      const v4f v = w[d];
+      w[d] = load(pass + d + FR_DEPTH);            // past the end: no memory traffic
+      const int k = row0 + (pass + d < passes ? pass + d : 0) * ROWS;
+#pragma unroll
+      for (int m = 0; m < MR; ++m) {
+        const float xv = xs[m * kpad + k];         // past the last pass the weights are zeros
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][j] = __builtin_fmaf(xv, v[j], acc[m][j]);
+      }
+    }
+  }
+  const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float s = acc[m][j];
+#pragma unroll
+      for (int d = 32; d >= LPR; d >>= 1) s += __shfl_xor(s, d, 64);
+      if (lane < LPR) red[(wave * MR + m) * COLS + 4 * lane + j] = s;
+    }
+  __syncthreads();
+  if (tid >= MR * COLS) return;
+  const int m = tid / COLS, ocol = strip * COLS + tid % COLS;
+  if (m >= p.M || ocol >= N) return;
+  float v = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v += red[(i * MR) * COLS + tid];
+  const float* __restrict__ bias = static_cast<const float*>(p.bias);
+  if (bias) v += bias[ocol];
+  if (p.act == 1) v = fmaxf(v, 0.f);
+  static_cast<float*>(p.y)[(size_t)m * N + ocol] = v;
+}
+
+template <int MR, int LPR>
+hipError_t launch_rows_variant(const Problem& p, hipStream_t stream) {
+  constexpr int ROWS = FR_THREADS / LPR;
+  const int strips = (p.k + 4 * LPR - 1) / (4 * LPR);
+  const size_t lds = (size_t)MR * ((p.Kgemm + ROWS - 1) / ROWS * ROWS) * sizeof(float);
+  hipLaunchKernelGGL((fc_rows_f32_kernel<MR, LPR>), dim3((unsigned)((strips + 7) / 8 * 8)), dim3(FR_THREADS), lds, stream, p, strips);
+  return hipGetLastError();
+}
+
+template <int MR>
+hipError_t launch_rows(const Problem& p, int lanes, hipStream_t stream) {
+  switch (lanes) {
+    case 4: return launch_rows_variant<MR, 4>(p, stream);
+    case 8: return launch_rows_variant<MR, 8>(p, stream);
+    default: return launch_rows_variant<MR, 16>(p, stream);
+  }
+}
+
 template <int VW>
 hipError_t launch_fsf(const Problem& p, hipStream_t stream) {
   constexpr int COLS = 16 * VW;
@@ -191,6 +294,23 @@ bool fc_small_f32_applicable(const Problem& p) {
   const long long max_kb = knob_or(KNOB_F32_FC_SMALL_MAX_KB, 8704);      // the knob: experiments and tests
   if ((long long)p.w_bytes > (max_kb << 10) || p.w_bytes > 0x7FFFFFFFu || p.x_bytes > 0x7FFFFFFFu) return false;
   return true;
+}
+
+bool fc_rows_f32_applicable(const Problem& p) {
+  if (!p.b_is_kn || p.groups != 1 || p.addend || p.chain_n > 0 || p.M > 4 || p.Kgemm > 8192) return false;
+  const int mode = knob_or(KNOB_F32_FC_ROWS, 1);         // 0: off, 2: any size (tests)
+  if (mode == 0 || knob_is_set(KNOB_F32_FC_SMALL_MIN_M)) return false;
+  if (mode == 2) return true;
+  if (p.k % 4 != 0 || p.Kgemm % 4 != 0) return p.w_bytes <= (16u << 20);
+  return p.M == 1 && p.Kgemm > 128 && p.Kgemm <= 2048 && p.w_bytes <= (4u << 20);
+}
+
+hipError_t launch_fc_rows_f32(const Problem& p, hipStream_t stream, const char** variant) {
+  const int lanes = p.Kgemm <= 512 ? 16 : p.Kgemm <= 1024 ? 8 : 4;   // eight rows in flight per lane cover the reduction
+  *variant = "fc_rows_f32";
+  if (p.M == 1) return launch_rows<1>(p, lanes, stream);
+  if (p.M == 2) return launch_rows<2>(p, lanes, stream);
+  return launch_rows<4>(p, lanes, stream);
 }
 
 hipError_t launch_fc_small_f32(const Problem& p, hipStream_t stream, const char** variant) {

@@ -732,6 +732,7 @@ Plan plan_f32(const Problem& p, bool allow_split) {
     if (allow_split && p.allow_pack && p3_f32_applicable(p)) return plan_p3_f32(p);
     if (pw_f32_applicable(p)) { pl.kernel = KERNEL_PW; return pl; }
     if (conv_small_f32_applicable(p)) { pl.kernel = KERNEL_SMALL; return pl; }
+    if (fc_rows_f32_applicable(p)) { pl.kernel = KERNEL_FC_ROWS; return pl; }
     if (fc_small_f32_applicable(p)) { pl.kernel = KERNEL_FC_SMALL; return pl; }
   }
   if (p.b_is_kn && p.M <= 16 && p.groups == 1 && p.k % 4 == 0 && p.Kgemm % 4 == 0 && !p.addend && !forced) {
@@ -871,6 +872,7 @@ hipError_t launch_f32(const Problem& p_in, const Plan& plan, hipStream_t stream,
     case KERNEL_P3: return launch_p3_f32(p_in, plan, stream, variant);
     case KERNEL_K3C64: return launch_k3c64_f32(p_in, stream, variant);
     case KERNEL_K3: return launch_k3_f32(p_in, stream, variant);
+    case KERNEL_FC_ROWS: return launch_fc_rows_f32(p_in, stream, variant);
     case KERNEL_PATCH: return launch_patch_f32(p_in, plan.tile, stream, variant);
     default: break;
   }
