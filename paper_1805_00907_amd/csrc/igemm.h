@@ -80,7 +80,7 @@ struct Problem {
   const void* planes; // fp32 on the fp16 matrix cores: workspace for the input's planes (or only its partial maxima), then the weights' planes
   const void* w_packed; // the weights' planes as the caller made them ahead of time (glowmi_*_pack_filter), or null
   const void* w_planes; // where the kernel reads the weights' planes: w_packed, or inside `planes` (set by the launcher)
-  const unsigned* x_range; // x_range_n words whose largest is the bits of the input's largest magnitude (set by the launcher)
+  const unsigned* x_range; // the bits of the input's largest magnitude, or of each of its x_range_n rows' (set by the launcher)
   const unsigned* w_range; // one word: the same for the weights (the trailer of their planes)
   int32_t x_range_n;
   const void* addend; // tensor operand of the element-wise chain [M][k] (float or int8), may be null:

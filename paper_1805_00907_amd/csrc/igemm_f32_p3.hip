@@ -198,6 +198,50 @@ __device__ __forceinline__ void pack2_transposed(const float* __restrict__ w, un
   }
 }
 
+// A FullyConnected input measured and cut in one launch, each row by a scale of its own: a workgroup per row, which it holds
+// in registers up to 8192 values (what is beyond is read twice); words[row] = the bits of its largest magnitude.  One scale
+// for the whole input takes a launch that measures it first (256 rows of 4096: 5 + 6 us, 4 here).
+__global__ __launch_bounds__(256) void cut_rows_kernel(const float* __restrict__ x, unsigned short* __restrict__ dst, int row8,
+                                                       long long plane_elems, unsigned* __restrict__ words) {
+  constexpr int HELD = 4;
+  __shared__ unsigned red[4];
+  const int tid = threadIdx.x;
+  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(x) + (size_t)blockIdx.x * row8 * 2;
+  v4f held[HELD][2];
+#pragma unroll
+  for (int q = 0; q < HELD; ++q) {
+    const int g = tid + q * 256;
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    held[q][0] = g < row8 ? src[2 * g] : zero;
+    held[q][1] = g < row8 ? src[2 * g + 1] : zero;
+  }
+  unsigned m = lane_max_of(held);
+  for (int g = tid + HELD * 256; g < row8; g += 256) {
+    const v4f again[1][2] = {{src[2 * g], src[2 * g + 1]}};
+    const unsigned o = lane_max_of(again);
+    m = o > m ? o : m;
+  }
+  m = wave_max_u32(m);
+  if ((tid & 63) == 0) red[tid >> 6] = m;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m = red[i] > m ? red[i] : m;
+  if (tid == 0) words[blockIdx.x] = m;
+  const int se = scale_exponent(m);
+  unsigned short* __restrict__ out = dst + (size_t)blockIdx.x * row8 * 8;
+  auto write = [&](int g, const v4f& a, const v4f& b) {
+    const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    v4u p1, p2;
+    cut8_in_place(v, se, p1, p2);
+    *reinterpret_cast<v4u*>(out + 8 * g) = p1;
+    *reinterpret_cast<v4u*>(out + plane_elems + 8 * g) = p2;
+  };
+#pragma unroll
+  for (int q = 0; q < HELD; ++q)
+    if (tid + q * 256 < row8) write(tid + q * 256, held[q][0], held[q][1]);
+  for (int g = tid + HELD * 256; g < row8; g += 256) write(g, src[2 * g], src[2 * g + 1]);
+}
+
 __global__ __launch_bounds__(256) void pack2_rows_kernel(const float* __restrict__ src, unsigned short* __restrict__ dst,
                                                          long long count8, long long plane_elems,
                                                          unsigned* __restrict__ trailer) {
@@ -241,6 +285,8 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   constexpr int LPI = 2 * (A_GROUPS + 1);               // loads one wavefront issues per slab
   constexpr int A_PLANE = PBM * PROW, B_PLANE = BN * PROW;
   constexpr int BUF = 2 * (A_PLANE + B_PLANE);
+  constexpr int AHEAD = NBUF >= 4 ? 1 : 0;              // the slab after the one multiplied has landed as well
+  static_assert(!AHEAD || NBUF % 2 == 0, "register sets alternate with the buffers");
   static_assert(NBUF * BUF >= WAVES * 32 * 64 * 4, "exchange of the partial tiles fits the slab buffers");
 
   extern __shared__ __align__(16) unsigned char lds[];
@@ -272,8 +318,10 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   const v4i rsrc_x = make_rsrc(p.planes, 2u * xpb);
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;   // planes are at most 512 MiB each: OOB + a plane neither wraps nor lands inside
-  // what the two accumulator sets are scaled back by: the operands' scale exponents, from their largest magnitudes
-  const ScaleBack sb = scale_back(wave_max_words(p.x_range, p.x_range_n), wave_max_words(p.w_range, 1));
+  // what the two accumulator sets are scaled back by: the operands' scale exponents, from their largest magnitudes (the
+  // input's: one word, or one per row)
+  const unsigned w_max = *p.w_range;
+  const bool row_scales = p.x_range_n > 1;              // uniform
 
   // The bias values now, not in the epilogue: a load there would make the compiler wait for all memory operations
   // in front of every store (each store is a branch of its own, and each would wait for the store before it).
@@ -384,20 +432,21 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   const int pos = ((kgrp * 2 + lhalf) ^ ((lrow >> 2) & 3)) << 4;
   const int frag_a = (wm * 64 + lrow) * PROW + pos;
   const int frag_b = 2 * A_PLANE + (wn * 64 + lrow) * PROW + pos;
-  // All fragments of a slab are read up front (8 ds_read_b128) in the order the MFMAs use them, and the
-  // refill loads are dealt out between the MFMAs.
-  auto trip = [&](int buf, int refill_buf) {
+  v8h fa[AHEAD + 1][2][2], fb[AHEAD + 1][2][2];         // [set][plane][block]
+  // fragment n of a slab, in the order the MFMAs use them: the cross terms come first, a1 with b2, then a2 with b1
+  auto read_fragment = [&](int set, int buf, int n) {    // n = 0 .. 7, compile-time
     const unsigned char* base = lds + buf * BUF;
-    v8h a[2][2], b[2][2];
+    const int o = n / 4, i = n % 2;
+    if (n % 4 < 2) fa[set][o][i] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(base + o * A_PLANE + frag_a + i * 32 * PROW));
+    else fb[set][1 - o][i] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(base + (1 - o) * B_PLANE + frag_b + i * 32 * PROW));
+  };
+  // One slab.  AHEAD: the next slab's fragments are read between this one's MFMAs (its reads take 512 cycles of LDS time,
+  // its MFMAs 768, and one after the other for every wavefront at once they took 38 us of FullyConnected 256 x 4096 x 4096
+  // on 256 workgroups); otherwise they are read up front.  The refill loads are dealt out as well.
+  auto trip = [&](int set, int buf, int next_buf, int refill_buf) {
+    if (!AHEAD) {
 #pragma unroll
-    for (int o = 0; o < 2; ++o) {
-      const int pa = o, pb = 1 - o;                       // the cross terms come first: a1 with b2, then a2 with b1
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[pa][i] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(base + pa * A_PLANE + frag_a + i * 32 * PROW));
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        b[pb][j] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(base + pb * B_PLANE + frag_b + j * 32 * PROW));
+      for (int n = 0; n < 8; ++n) read_fragment(0, buf, n);
     }
     issue_prepare(refill_buf);
     __builtin_amdgcn_sched_barrier(0);
@@ -406,9 +455,13 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
 #pragma unroll
     for (int q = 0; q < MFMAS; ++q) {
       const int t = q / 4, i = (q / 2) % 2, j = q % 2;
-      if (t == 0) acc_lo[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0][i], b[1][j], acc_lo[i][j], 0, 0, 0);
-      else if (t == 1) acc_lo[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1][i], b[0][j], acc_lo[i][j], 0, 0, 0);
-      else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0][i], b[0][j], acc[i][j], 0, 0, 0);
+      if (t == 0) acc_lo[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][0][i], fb[set][1][j], acc_lo[i][j], 0, 0, 0);
+      else if (t == 1) acc_lo[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][1][i], fb[set][0][j], acc_lo[i][j], 0, 0, 0);
+      else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][0][i], fb[set][0][j], acc[i][j], 0, 0, 0);
+      if (AHEAD && q < 8) {
+        read_fragment(set ^ 1, next_buf, q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if (q % EVERY == EVERY - 1 && q / EVERY < LPI) {
         __builtin_amdgcn_sched_barrier(0);
         issue_piece(q / EVERY);
@@ -417,21 +470,37 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
     }
   };
 
-  // ---- main loop.  Trip s: wait for slab s (the younger slabs stay in flight), barrier (everyone's part of
-  // slab s has landed and everyone is done with the buffer multiplied last trip), read slab s's fragments,
-  // refill that older buffer with slab s + NBUF - 1, multiply slab s.  Loads are issued on every trip, past the end as zero fills, so the waits are
+  // ---- main loop.  Trip s: wait for slab s, AHEAD for slab s + 1 (the younger slabs stay in flight), barrier (everyone's
+  // part of it has landed and everyone is done with the buffer multiplied last trip), refill that older buffer with slab
+  // s + NBUF - 1, multiply slab s.  Loads are issued on every trip, past the end as zero fills, so the waits are
   // compile-time constants.  Unrolled NBUF times so that buffer indices are constants.
   {
 #pragma unroll
     for (int d = 0; d < NBUF - 1; ++d) issue(d);
+    if (AHEAD) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm((NBUF - 2) * LPI));
+      __syncthreads();
+#pragma unroll
+      for (int n = 0; n < 8; ++n) read_fragment(0, 0, n);
+    }
     int since_flush = 0;
     for (int s0 = slab_begin; s0 < slab_end; s0 += NBUF) {
 #pragma unroll
       for (int u = 0; u < NBUF; ++u) {
         if (s0 + u < slab_end) {                          // uniform
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm((NBUF - 2) * LPI));
-          __syncthreads();
-          trip(u, (u + NBUF - 1) % NBUF);
+          __builtin_amdgcn_s_waitcnt(vmcnt_imm((NBUF - 2 - AHEAD) * LPI));
+          if (AHEAD) {
+            // leaves the wavefront's own reads in flight: they are of slab s, whose buffer is refilled two trips on, and
+            // every read before them was consumed by an MFMA that lies before the barrier
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+          } else {
+            __syncthreads();
+          }
+          trip(AHEAD ? u & 1 : 0, u, (u + 1) % NBUF, (u + NBUF - 1) % NBUF);
           if (LONGK && ++since_flush == P3_FLUSH) {
             since_flush = 0;
 #pragma unroll
@@ -484,13 +553,23 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
     if (kgrp) exchange_as(std::integral_constant<int, 1>{});
     else exchange_as(std::integral_constant<int, 0>{});
     __syncthreads();
+    // of the sixteen rows this lane finishes
+    unsigned x_max[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int row = tm * PBM + wm * 64 + kgrp * 32 + lhalf * 4 + (e >> 2) * 8 + (e & 3);
+      x_max[e] = p.x_range[row_scales ? (row < p.M ? row : p.M - 1) : 0];
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4) {
         const v4f got = xch[(theirs + j * 4 + e4) * 64 + lane];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) keep[j][e4 * 4 + t] = __builtin_ldexpf(keep[j][e4 * 4 + t] + got[t], sb.neg_se) + sb.poison;   // scaled back
+        for (int t = 0; t < 4; ++t) {
+          const ScaleBack sb = scale_back(x_max[e4 * 4 + t], w_max);
+          keep[j][e4 * 4 + t] = __builtin_ldexpf(keep[j][e4 * 4 + t] + got[t], sb.neg_se) + sb.poison;   // scaled back
+        }
       }
   }
 
@@ -550,11 +629,13 @@ hipError_t launch_p3_variant(const Problem& p, const Plan& plan, hipStream_t str
   return hipGetLastError();
 }
 
-template <int WN, int NBUF>
+// With 128 channels four slab buffers, the fragments read a slab ahead; a second accumulator set leaves no registers for that.
+template <int WN>
 hipError_t launch_p3_flags(const Problem& p, const Plan& plan, hipStream_t stream, bool padded, bool longk) {
-  if (padded) return longk ? launch_p3_variant<WN, true, true, NBUF>(p, plan, stream)
+  constexpr int NBUF = WN == 2 ? 4 : 2, NBUF_LONG = WN == 2 ? 3 : 2;
+  if (padded) return longk ? launch_p3_variant<WN, true, true, NBUF_LONG>(p, plan, stream)
                            : launch_p3_variant<WN, true, false, NBUF>(p, plan, stream);
-  return longk ? launch_p3_variant<WN, false, true, NBUF>(p, plan, stream)
+  return longk ? launch_p3_variant<WN, false, true, NBUF_LONG>(p, plan, stream)
                : launch_p3_variant<WN, false, false, NBUF>(p, plan, stream);
 }
 
@@ -709,8 +790,15 @@ hipError_t launch_p3_f32(const Problem& p_in, const Plan& plan, hipStream_t stre
   if (bx > 8192) bx = 8192;
   if (bx < 1) bx = 1;
   hipError_t e;
-  if (p.w_packed) {
-    // ---- the weights' planes were made ahead of time: only the input is measured and cut
+  if (p.w_packed && p.b_is_kn && p.M > 1 && p.M <= (int)(kPlaneTrailerBytes / sizeof(unsigned))) {
+    // ---- the weights' planes were made ahead of time: only the input is cut, row by row (the words fit the trailer)
+    p.w_planes = p.w_packed;
+    p.w_range = planes_trailer(p.w_packed, w_elems);
+    p.x_range_n = p.M;
+    hipLaunchKernelGGL(cut_rows_kernel, dim3((unsigned)p.M), dim3(256), 0, stream, static_cast<const float*>(p.x), xp, p.Kgemm / 8,
+                       (long long)x_elems, x_trailer);
+  } else if (p.w_packed) {
+    // ---- the same with one scale for the input
     p.w_planes = p.w_packed;
     p.w_range = planes_trailer(p.w_packed, w_elems);
     e = launch_ranges(static_cast<const float*>(p.x), (long long)x_elems, x_trailer + kRangeWords, nullptr, 0, nullptr, stream);
@@ -748,8 +836,8 @@ hipError_t launch_p3_f32(const Problem& p_in, const Plan& plan, hipStream_t stre
   static thread_local char name[64];
   snprintf(name, sizeof(name), "igemm_f32_p3_128x%d%s%s", plan.bn, padded ? "_pad" : "", longk ? "_longk" : "");
   *variant = name;
-  if (plan.bn == 128) e = launch_p3_flags<2, 3>(p, plan, stream, padded, longk);
-  else e = launch_p3_flags<1, 2>(p, plan, stream, padded, longk);
+  if (plan.bn == 128) e = launch_p3_flags<2>(p, plan, stream, padded, longk);
+  else e = launch_p3_flags<1>(p, plan, stream, padded, longk);
   if (e != hipSuccess) return e;
   if (plan.split_k > 1) e = launch_splitk_finish_f32(p, plan, stream);
   return e;
