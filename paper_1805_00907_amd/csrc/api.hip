@@ -363,6 +363,24 @@ hipError_t scratch_pointer(void** out) {
 
 namespace glowmi {
 
+size_t conv2d_cut_bytes(const glowmi_conv_desc* d) {
+  Geometry geo;
+  if (check_desc(d, &geo) != GLOWMI_OK) return 0;
+  Problem p;
+  fill_conv(p, d, geo);
+  if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;
+  return plan_f32(p, true).kernel == KERNEL_PATCH ? patch_f32_pack_bytes(p) : 0;
+}
+
+glowmi_status run_cuts(PreparedCall* const* calls, int n, hipStream_t stream) {
+  const Problem* layers[kCutJobs];
+  for (int i = 0; i < n; ++i) layers[i] = &calls[i]->p;
+  const glowmi_status st = finish(launch_cut_filters(layers, n, stream), "cut_filters");
+  if (st != GLOWMI_OK) return st;
+  for (int i = 0; i < n; ++i) calls[i]->p.filter_is_cut = 1;
+  return GLOWMI_OK;
+}
+
 glowmi_status prepare_conv2d_chain(const float* x, const float* w, const float* bias, float* y,
                                    const glowmi_conv_desc* d, const glowmi_chain* chain, void* workspace,
                                    size_t workspace_bytes, PreparedCall* out, const void* w_planes) {

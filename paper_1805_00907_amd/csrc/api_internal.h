@@ -27,6 +27,11 @@ glowmi_status prepare_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int
                                     const int32_t* bias, int8_t* y, glowmi_qparam yq, const glowmi_conv_desc* d,
                                     const glowmi_chain* chain, void* workspace, size_t workspace_bytes,
                                     PreparedCall* out);
+// Bytes for the planes of a layer's filter where the planner takes the kernel that cuts it into an order of its own
+// (conv_patch_f32), else 0.
+size_t conv2d_cut_bytes(const glowmi_conv_desc* d);
+// One launch for the filters of n (at most kCutJobs) prepared calls of that kernel, each with a place of its own (p.planes).
+glowmi_status run_cuts(PreparedCall* const* calls, int n, hipStream_t stream);
 // Launch a prepared call on `stream`.
 glowmi_status run_prepared(const PreparedCall& call, hipStream_t stream);
 

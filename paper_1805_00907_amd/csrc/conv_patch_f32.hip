@@ -422,14 +422,32 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 // here and there, 512 x 4608 took 9 us instead of 5): a wavefront finds each one's largest magnitude and its bits go into
 // words[channel]; then the workgroup cuts its part of the reduction of all eight.  Where eight channels at a time leave CUs
 // idle, `parts` workgroups share them, each measuring for itself.
+// One launch cuts the filters of several layers of a sequence (kCutJobs at most).
 constexpr int CUT_ROWS = 8;
-__global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const float* __restrict__ w, unsigned short* __restrict__ dst, int rows,
-                                                                   int row8, int parts, long long plane_elems,
-                                                                   unsigned* __restrict__ words) {
+struct CutJob {
+  const float* w;
+  unsigned short* dst;
+  unsigned* words;
+  int rows, row8, parts, first_block;
+};
+struct CutJobs {
+  int n;
+  CutJob job[kCutJobs];
+};
+__global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs jobs) {
   __shared__ unsigned largest[CUT_ROWS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first_block) ++j;   // uniform
+  const float* __restrict__ w = jobs.job[j].w;
+  unsigned short* __restrict__ dst = jobs.job[j].dst;
+  unsigned* __restrict__ words = jobs.job[j].words;
+  const int rows = jobs.job[j].rows, row8 = jobs.job[j].row8, parts = jobs.job[j].parts;
+  const size_t plane_elems = (size_t)rows * row8 * 8;
+  const int at = (int)blockIdx.x - jobs.job[j].first_block;
+  const int blocks = (j + 1 < jobs.n ? jobs.job[j + 1].first_block : (int)gridDim.x) - jobs.job[j].first_block;   // a multiple of 8
   // the parts of a group on one XCD, whose L2 serves the measuring of all but the first
-  const int block = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int block = (at & 7) * (blocks >> 3) + (at >> 3);
   const int group = block / parts, part = block - group * parts;
   if (group * CUT_ROWS >= rows) return;
   const v4f* __restrict__ w4 = reinterpret_cast<const v4f*>(w);
@@ -618,7 +636,7 @@ constexpr FormCost kForms[FORMS] = {
 // chunk of it takes 1.35 times as long).
 int cheapest_form(const Problem& p, double* cost) {
   const bool pointwise = p.r == 1;
-  const double fixed = 4.3 + 1e-6 * p.w_bytes + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1));
+  const double fixed = 4.3 + 1e-6 * p.w_bytes + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k);
   int best = -1;
   MapTile map[2] = {{0, 0, 0}, {0, 0, 0}};               // of 64 and of 128 pixels
   if (!pointwise) {
@@ -645,7 +663,8 @@ int cheapest_form(const Problem& p, double* cost) {
 
 }  // namespace
 
-// The form to run a layer in, -1: not a layer for this kernel.
+// The form to run a layer in, -1: not a layer for this kernel.  An addend does not count: the workspace queries do not know
+// of it, and a call must not plan what they did not ask room for.
 int patch_f32_form(const Problem& p) {
   const int mode = knob_or(KNOB_F32_PATCH, 1);          // 0: off, 2: any size (tests)
   if (mode == 0 || (mode == 1 && knob_or(KNOB_F32_P3, 1) == 0)) return -1;   // either switch: such layers stay on the fp32 matrix cores
@@ -663,7 +682,7 @@ int patch_f32_form(const Problem& p) {
   // estimates' errors where the kernels are close.
   const double us = 2e-6 * p.M * (double)p.k * p.Kgemm;
   const bool small = conv_small_f32_applicable(p) || conv_small_f32_splits(p) > 0;
-  const double bytes = (double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1);
+  const double bytes = (double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k;
   double other = p.r == 3 ? 8.0 + us / 75.0 : 6.0 + (us / 75.0 > bytes / 3e6 ? us / 75.0 : bytes / 3e6);
   if (small && 3.5 + us / 32.0 < other) other = 3.5 + us / 32.0;
   return cost + (p.r == 1 || small ? 1.6 : 0.5) < other ? (forced >= 0 ? forced : form) : -1;
@@ -671,26 +690,48 @@ int patch_f32_form(const Problem& p) {
 
 size_t patch_f32_pack_bytes(const Problem& p) { return (p.w_bytes + 255) / 256 * 256 + 4 * (size_t)p.k; }
 
+namespace {
+unsigned* cut_words(const Problem& p) {
+  return reinterpret_cast<unsigned*>(static_cast<unsigned char*>(const_cast<void*>(p.planes)) + (p.w_bytes + 255) / 256 * 256);
+}
+}  // namespace
+
+// Cuts the filters of n layers (at most kCutJobs), each into its own p.planes.
+hipError_t launch_cut_filters(const Problem* const* layers, int n, hipStream_t stream) {
+  if (n < 1 || n > kCutJobs) return hipErrorInvalidValue;
+  CutJobs jobs;
+  jobs.n = n;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    const Problem& p = *layers[i];
+    if (!p.planes) return hipErrorInvalidValue;         // the ABI layer never plans this kernel without a workspace
+    CutJob& j = jobs.job[i];
+    j.w = static_cast<const float*>(p.w);
+    j.dst = static_cast<unsigned short*>(const_cast<void*>(p.planes));
+    j.words = cut_words(p);
+    j.rows = p.k;
+    j.row8 = p.Kgemm / 8;
+    const int groups = (p.k + CUT_ROWS - 1) / CUT_ROWS;
+    j.parts = 256 / groups;
+    if (j.parts > (j.row8 + 15) / 16) j.parts = (j.row8 + 15) / 16;   // at least two wavefronts' work each
+    if (j.parts > 8) j.parts = 8;
+    if (j.parts < 1) j.parts = 1;
+    j.first_block = blocks;
+    blocks += (groups * j.parts + 7) / 8 * 8;
+  }
+  hipLaunchKernelGGL(cut_filter_kernel, dim3((unsigned)blocks), dim3(64 * CUT_ROWS), 0, stream, jobs);
+  return hipGetLastError();
+}
+
 hipError_t launch_patch_f32(const Problem& p_in, int form, hipStream_t stream, const char** variant) {
   Problem p = p_in;
-  if (!p.planes) return hipErrorInvalidValue;           // the ABI layer never plans this kernel without a workspace
-  unsigned char* planes = static_cast<unsigned char*>(const_cast<void*>(p.planes));
-  unsigned* words = reinterpret_cast<unsigned*>(planes + (p.w_bytes + 255) / 256 * 256);
-  const int row8 = p.Kgemm / 8;
-  const float* w = static_cast<const float*>(p.w);
-  unsigned short* out = reinterpret_cast<unsigned short*>(planes);
-  const long long elems = (long long)(p.w_bytes >> 2);
-  const int groups = (p.k + CUT_ROWS - 1) / CUT_ROWS;
-  int parts = 256 / groups;
-  if (parts > (row8 + 15) / 16) parts = (row8 + 15) / 16;   // at least two wavefronts' work each
-  if (parts > 8) parts = 8;
-  if (parts < 1) parts = 1;
-  hipLaunchKernelGGL(cut_filter_kernel, dim3((unsigned)((groups * parts + 7) / 8 * 8)), dim3(64 * CUT_ROWS), 0, stream, w, out, p.k, row8, parts, elems,
-                     words);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  p.w_planes = planes;
-  p.w_range = words;
+  if (!p.filter_is_cut) {
+    const Problem* one = &p;
+    const hipError_t e = launch_cut_filters(&one, 1, stream);
+    if (e != hipSuccess) return e;
+  }
+  p.w_planes = p.planes;
+  p.w_range = cut_words(p);
   return p.addend ? launch_patch_shape<true>(p, form, stream, variant) : launch_patch_shape<false>(p, form, stream, variant);
 }
 

@@ -99,6 +99,7 @@ struct Problem {
   int32_t act;              // 0 none, 1 the value is clamped to [act_lo, act_hi] (Relu: [0, inf])
   float act_lo, act_hi;     // -inf, inf with act == 0
   int32_t b_is_kn;          // FC weight layout
+  int32_t filter_is_cut;    // the planes of this layer's filter were cut ahead, with those of other layers (conv_patch_f32.hip)
   int32_t allow_pack;       // the caller's workspace may hold repacked operands (fp32 three-piece form)
   // quantized form only
   int32_t x_off, w_off, y_off;
@@ -207,6 +208,8 @@ hipError_t launch_k3v_f32(const Problem& p, hipStream_t stream, const char** var
 int patch_f32_form(const Problem& p);
 size_t patch_f32_pack_bytes(const Problem& p);
 hipError_t launch_patch_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
+constexpr int kCutJobs = 8;
+hipError_t launch_cut_filters(const Problem* const* layers, int n, hipStream_t stream);
 // Depthwise 3x3 convolution, stride 1 or 2, channels a multiple of four, no tensor operand behind it (conv_dw.hip).
 bool dw_f32_applicable(const Problem& p);
 hipError_t launch_dw_f32(const Problem& p, hipStream_t stream, const char** variant);

@@ -118,3 +118,35 @@ def test_conv_patch_wide_value_ranges(r, st, knobs):
     assert reached.any() and not np.isfinite(got[reached]).any()
     ok = np.isfinite(got)
     assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 + 1e-4 * np.abs(ref[ok]))
+
+
+@pytest.mark.parametrize("layers", [1, 8, 10])
+def test_sequence_cuts_filters_ahead_in_groups(layers, knobs):
+    """Layers of a sequence have their filters cut up to eight at a time: the same results as layer by layer."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    knobs.set("F32_PATCH", 2)
+    rng = np.random.default_rng(37900 + layers)
+    widths = [24, 40, 16, 72, 8, 32, 136, 24, 64, 48, 24]
+    x = rng.uniform(-1, 1, size=(2, 9, 11, widths[0])).astype(np.float32)
+    seq, keep, step = [], [], G.dev(x)
+    for i in range(layers):
+        r, c, k = 3 if i % 2 else 1, widths[i], widths[i + 1]
+        wd = G.dev((rng.standard_normal(size=(k, r, r, c)) / np.sqrt(r * r * c)).astype(np.float32))
+        bd = G.dev(rng.uniform(-0.1, 0.1, size=(k,)).astype(np.float32))
+        desc = G.make_desc(tuple(step.shape), (k, r, r, c), (1, 1), (r // 2,) * 4, 1)
+        seq.append((desc, wd, bd, wl.ACT_RELU, False))
+        y = torch.empty((2, 9, 11, k), device="cuda:0")
+        ws = torch.empty(max(glowmi.conv2d_workspace_bytes(desc), 16), dtype=torch.uint8, device="cuda:0")
+        glowmi.conv2d(step, wd, bd, y, desc, wl.ACT_RELU, ws)
+        assert glowmi.last_variant().startswith("conv_patch_f32"), glowmi.last_variant()
+        keep += [wd, bd, ws]
+        step = y
+    arr = glowmi.seq_layers(seq)
+    arena = torch.empty(glowmi.seq_arena_bytes(arr, False), dtype=torch.uint8, device="cuda:0")
+    got = G.poison(tuple(step.shape), torch.float32)
+    for _ in range(2):
+        glowmi.seq_conv2d(G.dev(x), arr, got, arena)
+    torch.cuda.synchronize()
+    assert torch.equal(got, step)
