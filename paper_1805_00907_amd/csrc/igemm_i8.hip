@@ -680,7 +680,9 @@ Plan plan_i8(const Problem& p, bool allow_split) {
     // up to about one 64 x 64 tile per CU: several wavefront groups per tile, the chain of slabs is what counts (3x3 72->120 on
     // 33x45 at batch 5, 232 tiles: 10.4 us with one group, 8.2 with two; FC 76x808x208, 8 tiles: 12.0, 9.6, 8.9 with four);
     // at twice that many tiles the groups only take each other's room (3x3 19->119 on 68x94 at batch 3, 600 tiles: 10.6 -> 14.2)
-    if (t64 <= 320 && pl.slabs >= 2) tile = pl.slabs >= 8 ? 7 : 6;
+    // (and four groups fill a CU: beyond 256 tiles they take a second round, 3x3 256->40 on 48x30 at batch 12, 270 tiles: 20.0 us,
+    // 14.5 with two)
+    if (t64 <= 320 && pl.slabs >= 2) tile = pl.slabs >= 8 && t64 <= 256 ? 7 : 6;
     // many tiles: the larger ones read each operand fewer times (3x3 120->128 on 56x56 at batch 16: 33 us with 64 x 64 tiles,
     // 26 us with 128 x 128; 1x1 344->176 stride 2 on 85x86 at batch 11, three slabs: 11.1 -> 10.1 us with 128 x 64; with a
     // slab or two the output is what counts, and there have to be four tiles per CU: 1x1 40->896 on 40x40 at batch 24
