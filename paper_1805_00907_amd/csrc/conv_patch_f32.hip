@@ -1,5 +1,5 @@
 // fp32 convolutions of ordinary size on the fp16 matrix cores: 1x1 and 3x3 filters, stride 1 or 2, any map and channel
-// counts that are multiples of eight.  The arithmetic is that of the other kernels over fp16 pieces (f16_pieces.h): three
+// counts.  The arithmetic is that of the other kernels over fp16 pieces (f16_pieces.h): three
 // exact fp16 products per fp32 product, fp32 accumulation.
 //
 // The 3x3 tile kernels (conv_k3*_f32.hip) own a CU per tile of 200 pixels x 128 channels, so they need a large map at a
@@ -121,14 +121,17 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 
   // ---- filter fragments: planes [Kgemm / 8][k][8]; lane: channel lrow of the wavefront's 32, eight indices lhalf of the
   // step's 16.  Step st of a chunk: tap st / MS, channels 16 ((st % MS) KS + kset) .. of the chunk.
-  const unsigned wpb = p.w_bytes >> 1;                  // bytes of one plane
+  // Pieces of eight channels per tap, the filter's last one filled up with zeros: they meet whatever lies behind a pixel's
+  // last channel (the next pixel; behind the tensor zeros).
+  const int c8 = (p.c + 7) >> 3;
+  const unsigned k16 = 16u * (unsigned)p.k;             // bytes of eight reduction indices
+  const unsigned wpb = (unsigned)(R * R * c8) * k16;    // bytes of one plane
   const __amdgpu_buffer_rsrc_t rsrc_w1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w_planes), 0, (int)wpb, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(static_cast<const unsigned char*>(p.w_planes)) + wpb, 0, (int)wpb, 0x00020000);
   const int ch = ct * T::BN + wn * 32 + lrow;
-  const unsigned k16 = 16u * (unsigned)p.k;             // bytes of eight reduction indices
   const unsigned b_base = ch < p.k ? (unsigned)(2 * kset + lhalf) * k16 + 16u * (unsigned)ch : OOBW;
-  const unsigned tap_step = (unsigned)(p.c >> 3) * k16, chunk_step = (unsigned)(T::CC >> 3) * k16;
+  const unsigned tap_step = (unsigned)c8 * k16, chunk_step = (unsigned)(T::CC >> 3) * k16;
   v4i fb[T::DB][2];                                     // [step in flight][plane]
   auto load_b = [&](int slot, int chunk, int st) {      // slot, st: compile-time
     const unsigned at = chunk < tl.chunks ? (unsigned)chunk * chunk_step + (unsigned)(st / T::MS) * tap_step +
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
     const int c0 = chunk * T::CC;
 #pragma unroll
     for (int q = 0; q < T::PASSES; ++q) {
-      const unsigned off = raw_off[q] != OOBX && c0 + raw_c[q] < p.c ? raw_off[q] + (unsigned)c0 * 4u : OOBX;   // p.c % 8 == 0
+      const unsigned off = raw_off[q] != OOBX && c0 + raw_c[q] < p.c ? raw_off[q] + (unsigned)c0 * 4u : OOBX;
       dst[q][0] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off, 0, 0));
       dst[q][1] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off + 16u, 0, 0));
     }
@@ -428,56 +431,74 @@ struct CutJob {
   const float* w;
   unsigned short* dst;
   unsigned* words;
-  int rows, row8, parts, first_block;
+  int rows, taps, c, parts, first_block;
+  FastDiv div_c8;
 };
+template <int N>
 struct CutJobs {
   int n;
-  CutJob job[kCutJobs];
+  CutJob job[N];
 };
-__global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs jobs) {
+template <int N>
+__global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs<N> jobs) {
   __shared__ unsigned largest[CUT_ROWS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int j = 0;
-  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first_block) ++j;   // uniform
+  while (N > 1 && j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first_block) ++j;   // uniform
   const float* __restrict__ w = jobs.job[j].w;
   unsigned short* __restrict__ dst = jobs.job[j].dst;
   unsigned* __restrict__ words = jobs.job[j].words;
-  const int rows = jobs.job[j].rows, row8 = jobs.job[j].row8, parts = jobs.job[j].parts;
+  const int rows = jobs.job[j].rows, taps = jobs.job[j].taps, c = jobs.job[j].c, parts = jobs.job[j].parts;
+  const int c8 = (c + 7) >> 3, row8 = taps * c8, depth = taps * c;   // a channel's pieces of eight; its weights
+  const bool ragged = (c & 7) != 0;                     // uniform
   const size_t plane_elems = (size_t)rows * row8 * 8;
   const int at = (int)blockIdx.x - jobs.job[j].first_block;
-  const int blocks = (j + 1 < jobs.n ? jobs.job[j + 1].first_block : (int)gridDim.x) - jobs.job[j].first_block;   // a multiple of 8
+  const int blocks = (N > 1 && j + 1 < jobs.n ? jobs.job[j + 1].first_block : (int)gridDim.x) - jobs.job[j].first_block;   // a multiple of 8
   // the parts of a group on one XCD, whose L2 serves the measuring of all but the first
   const int block = (at & 7) * (blocks >> 3) + (at >> 3);
   const int group = block / parts, part = block - group * parts;
   if (group * CUT_ROWS >= rows) return;
-  const v4f* __restrict__ w4 = reinterpret_cast<const v4f*>(w);
+  // 16 bytes from any weight on, zeros past the last one (buffer loads are checked word by word)
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w), 0, (int)(4u * (unsigned)rows * (unsigned)depth), 0x00020000);
+  auto load = [&](unsigned weight) { return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, 4u * weight, 0, 0)); };
   // what this thread will cut, asked for first: two trips to memory become one
   constexpr int HELD = 4, STEP = 64;
   const int r = (int)threadIdx.x & (CUT_ROWS - 1), row = group * CUT_ROWS + r;
   const int per = (row8 + parts - 1) / parts;
   const int first = part * per + (int)threadIdx.x / CUT_ROWS;
   const int end = row < rows ? ((part + 1) * per < row8 ? (part + 1) * per : row8) : 0;
-  const v4f* __restrict__ src = w4 + (size_t)row * row8 * 2;
+  auto piece = [&](int g, v4f (&v)[2]) {                 // eight weights of this thread's channel, a tap's last ones filled up
+    const int tap = ragged ? jobs.job[j].div_c8.div(g) : 0;
+    const int ch = (g - tap * c8) * 8;                   // (not ragged: the weights lie in the order of the pieces)
+    // (no branch around the loads: the compiler would wait for them where its paths join)
+    const unsigned from = g < end ? (unsigned)row * (unsigned)depth + (unsigned)(tap * c + ch) : 0x3fffffc0u;
+    v[0] = load(from);
+    v[1] = load(from + 4);
+    if (ragged) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e / 4][e % 4] = ch + e < c ? v[e / 4][e % 4] : 0.f;
+    }
+  };
   v4f held[HELD][2];
 #pragma unroll
-  for (int q = 0; q < HELD; ++q) {
-    const v4f zero = {0.f, 0.f, 0.f, 0.f};
-    const int g = first + q * STEP;
-    held[q][0] = g < end ? src[2 * g] : zero;
-    held[q][1] = g < end ? src[2 * g + 1] : zero;
-  }
+  for (int q = 0; q < HELD; ++q) piece(first + q * STEP, held[q]);
   {
     const int mine = group * CUT_ROWS + wave;
     unsigned m = 0;
     if (mine < rows) {
-      const v4f* __restrict__ all = w4 + (size_t)mine * row8 * 2;
+      const unsigned from = (unsigned)mine * (unsigned)depth;
+      const int quads = (depth + 3) >> 2;
       constexpr int PAIRS = 5;                          // of loads in flight
-      for (int g0 = lane; g0 < 2 * row8; g0 += 128 * PAIRS) {
+      for (int g0 = lane; g0 < quads; g0 += 128 * PAIRS) {
         v4f v[PAIRS][2];
 #pragma unroll
         for (int q = 0; q < 2 * PAIRS; ++q) {
-          const int g = g0 + 64 * q;
-          v[q / 2][q % 2] = all[g < 2 * row8 ? g : 2 * row8 - 1];
+          const int g = g0 + 64 * q < quads ? g0 + 64 * q : quads - 1;
+          v[q / 2][q % 2] = load(from + 4u * (unsigned)g);
+          if (ragged) {                                 // the next channel's first weights do not count
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[q / 2][q % 2][e] = 4 * g + e < depth ? v[q / 2][q % 2][e] : 0.f;
+          }
         }
         const unsigned o = lane_max_of(v);
         m = o > m ? o : m;
@@ -489,8 +510,8 @@ __global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs
   }
   __syncthreads();
   const int se = scale_exponent(largest[r]);
-  auto write = [&](int g, const v4f& a, const v4f& b) {
-    const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  auto write = [&](int g, const v4f (&w8)[2]) {
+    const float v[8] = {w8[0][0], w8[0][1], w8[0][2], w8[0][3], w8[1][0], w8[1][1], w8[1][2], w8[1][3]};
     v4u p1, p2;
     cut8_in_place(v, se, p1, p2);
     unsigned short* out = dst + ((size_t)g * rows + row) * 8;
@@ -499,8 +520,12 @@ __global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs
   };
 #pragma unroll
   for (int q = 0; q < HELD; ++q)
-    if (first + q * STEP < end) write(first + q * STEP, held[q][0], held[q][1]);
-  for (int g = first + HELD * STEP; g < end; g += STEP) write(g, src[2 * g], src[2 * g + 1]);
+    if (first + q * STEP < end) write(first + q * STEP, held[q]);
+  for (int g = first + HELD * STEP; g < end; g += STEP) {
+    v4f w8[2];
+    piece(g, w8);
+    write(g, w8);
+  }
 }
 
 int patch_pitch(int tw, int st) {
@@ -671,35 +696,40 @@ int patch_f32_form(const Problem& p) {
   if (p.b_is_kn || p.chain_n > 0 || p.groups != 1) return -1;
   if (p.r != p.s || (p.r != 1 && p.r != 3) || p.stride_h != p.stride_w || (p.stride_h != 1 && p.stride_h != 2)) return -1;
   if (p.r == 1 && (p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h >= p.h || (p.ow - 1) * p.stride_w >= p.w_)) return -1;
-  if (p.c % 8 != 0) return -1;
   if (p.x_bytes > 0xF0000000u || p.w_bytes > (1u << 30) || (long long)p.M * p.k * 4 > 0xF0000000LL) return -1;   // 32-bit byte offsets
   double cost = 0.0;
   const int form = cheapest_form(p, &cost);
   const int forced = knob_or(KNOB_F32_PATCH_TILE, -1);
   if (mode == 2) return forced >= 0 ? forced : form;
-  // Against what the layer would take elsewhere: on the fp32 matrix cores 8 us (6 for pointwise) and 75 TFLOP/s, or what
+  // Against what the layer would take elsewhere: on the fp32 matrix cores 8 us (6 for pointwise) and 50 or 75 TFLOP/s, or what
   // its tensors take at 3 TB/s; on the one-launch kernel for few pixels 3.5 us and 32 TFLOP/s.  The margin covers both
   // estimates' errors where the kernels are close.
   const double us = 2e-6 * p.M * (double)p.k * p.Kgemm;
+  const double rate = p.c % 4 == 0 ? 75.0 : 50.0;       // TFLOP/s; channels that do not start on 16 bytes are fetched one by one
   const bool small = conv_small_f32_applicable(p) || conv_small_f32_splits(p) > 0;
   const double bytes = (double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k;
-  double other = p.r == 3 ? 8.0 + us / 75.0 : 6.0 + (us / 75.0 > bytes / 3e6 ? us / 75.0 : bytes / 3e6);
+  double other = p.r == 3 ? 8.0 + us / rate : 6.0 + (us / rate > bytes / 3e6 ? us / rate : bytes / 3e6);
   if (small && 3.5 + us / 32.0 < other) other = 3.5 + us / 32.0;
   return cost + (p.r == 1 || small ? 1.6 : 0.5) < other ? (forced >= 0 ? forced : form) : -1;
 }
 
-size_t patch_f32_pack_bytes(const Problem& p) { return (p.w_bytes + 255) / 256 * 256 + 4 * (size_t)p.k; }
+namespace {
+// Both planes of the filter, a tap's channels filled up to whole pieces of eight.
+size_t cut_plane_bytes(const Problem& p) { return ((size_t)p.r * p.s * ((p.c + 7) / 8) * 32 * (size_t)p.k + 255) / 256 * 256; }
+}  // namespace
+
+size_t patch_f32_pack_bytes(const Problem& p) { return cut_plane_bytes(p) + 4 * (size_t)p.k; }
 
 namespace {
 unsigned* cut_words(const Problem& p) {
-  return reinterpret_cast<unsigned*>(static_cast<unsigned char*>(const_cast<void*>(p.planes)) + (p.w_bytes + 255) / 256 * 256);
+  return reinterpret_cast<unsigned*>(static_cast<unsigned char*>(const_cast<void*>(p.planes)) + cut_plane_bytes(p));
 }
 }  // namespace
 
 // Cuts the filters of n layers (at most kCutJobs), each into its own p.planes.
 hipError_t launch_cut_filters(const Problem* const* layers, int n, hipStream_t stream) {
   if (n < 1 || n > kCutJobs) return hipErrorInvalidValue;
-  CutJobs jobs;
+  CutJobs<kCutJobs> jobs;
   jobs.n = n;
   int blocks = 0;
   for (int i = 0; i < n; ++i) {
@@ -710,16 +740,26 @@ hipError_t launch_cut_filters(const Problem* const* layers, int n, hipStream_t s
     j.dst = static_cast<unsigned short*>(const_cast<void*>(p.planes));
     j.words = cut_words(p);
     j.rows = p.k;
-    j.row8 = p.Kgemm / 8;
+    j.taps = p.r * p.s;
+    j.c = p.c;
+    const int c8 = (p.c + 7) / 8, row8 = j.taps * c8;
+    j.div_c8 = make_fastdiv((uint32_t)c8);
     const int groups = (p.k + CUT_ROWS - 1) / CUT_ROWS;
     j.parts = 256 / groups;
-    if (j.parts > (j.row8 + 15) / 16) j.parts = (j.row8 + 15) / 16;   // at least two wavefronts' work each
+    if (j.parts > (row8 + 15) / 16) j.parts = (row8 + 15) / 16;   // at least two wavefronts' work each
     if (j.parts > 8) j.parts = 8;
     if (j.parts < 1) j.parts = 1;
     j.first_block = blocks;
     blocks += (groups * j.parts + 7) / 8 * 8;
   }
-  hipLaunchKernelGGL(cut_filter_kernel, dim3((unsigned)blocks), dim3(64 * CUT_ROWS), 0, stream, jobs);
+  if (n == 1) {
+    CutJobs<1> one;
+    one.n = 1;
+    one.job[0] = jobs.job[0];
+    hipLaunchKernelGGL(cut_filter_kernel<1>, dim3((unsigned)blocks), dim3(64 * CUT_ROWS), 0, stream, one);
+  } else {
+    hipLaunchKernelGGL(cut_filter_kernel<kCutJobs>, dim3((unsigned)blocks), dim3(64 * CUT_ROWS), 0, stream, jobs);
+  }
   return hipGetLastError();
 }
 

@@ -27,6 +27,10 @@ SHAPES = [
     (2, 16, 16, 64, 64, 3, 2, 1),      # stride 2
     (1, 13, 17, 72, 40, 3, 2, 1),
     (1, 9, 64, 32, 32, 3, 2, 1),
+    (2, 9, 7, 13, 20, 3, 1, 1),        # channels that end inside a piece of eight, also behind a whole chunk
+    (1, 12, 10, 65, 33, 3, 2, 1),
+    (2, 7, 11, 131, 50, 1, 1, 0),
+    (1, 5, 9, 3, 16, 1, 2, 0),
     (2, 11, 9, 64, 100, 1, 1, 0),      # pointwise: the last tile's pixels end inside it
     (1, 5, 5, 264, 40, 1, 1, 0),
     (3, 14, 11, 72, 136, 1, 2, 0),     # pointwise, stride 2
@@ -67,6 +71,8 @@ def test_conv_patch(shape, tile, knobs):
         got, variant = G.gpu_conv2d_f32_chain(x, wt, None, add, desc, wl.ACT_NONE, in_place=in_place)
         assert variant.startswith("conv_patch_f32_f16x3") and variant.endswith("_add"), variant
         G.assert_close_f32(got, ref, f"{shape} add [{variant}]")
+    if c % 8:
+        return                                          # no plane form
     planes = torch.empty(glowmi.conv2d_filter_planes_bytes(desc), dtype=torch.uint8, device="cuda:0")
     wd = G.dev(wt)
     glowmi.conv2d_pack_filter(wd, desc, planes)
