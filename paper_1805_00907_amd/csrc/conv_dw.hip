@@ -11,12 +11,15 @@
 //     buffer loads (int8: and are then replaced by the code of real zero);
 //   - a thread's channel quad never changes (the grid is a multiple of the channel quads), so its 36 filter values
 //     and its bias are fetched once and stay in registers while it walks over runs;
+//   - a channel count that is not a multiple of four anchors its last quad at the last four channels: a few outputs
+//     are then computed and stored twice with the same value, and pieces start on a channel instead of on 16 (int8:
+//     4) bytes, which the loads and stores take as they are (int8, 7 images of 63 x 63 x 279: generic kernel 877 us -> 10.0);
 //   - neighbouring runs share input rows, so every XCD works on one contiguous eighth of the runs and finds the
 //     shared rows in its own L2 (12.8 M outputs of 128 channels at 56 x 56: 32 -> 24 us);
 //   - bias, Relu (int8: the requantize of Section 4.3 with Relu as the lower clamp bound) and one 16-byte (int8:
 //     4-byte) store per output pixel, predicated on the pixel being inside the output.
-// Other filter sizes, strides above 2, channel counts that are not a multiple of four and layers with a tensor
-// operand behind them stay on the generic kernels.
+// Other filter sizes, strides above 2, ragged channel counts below eight (a third of the work and more would be
+// repeated) and layers with a tensor operand behind them stay on the generic kernels.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -28,13 +31,15 @@ namespace glowmi {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef v4f v4f_at4 __attribute__((aligned(4)));          // a quad that starts on any channel
+typedef unsigned u32_at1 __attribute__((aligned(1)));
 
 constexpr int DW_RUN = 4;                      // output pixels of one row per run
 constexpr int DW_THREADS = 256;
 constexpr unsigned DW_OOB = 0xFFFFFF00u;       // beyond any tensor these kernels accept: loads give zeros
 
 struct DwGrid {
-  int cq;                                      // channel quads
+  int cq;                                      // channel quads, the last one anchored at the last four channels
   int runs_w;                                  // runs per output row
   int strips;                                  // strips of ROWS output rows per image
   long long runs;                              // n * strips * runs_w
@@ -89,7 +94,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
   if (gid < 0 || gid >= (long long)g.cq * g.slots) return;
   const int cq = (int)((unsigned)gid % (unsigned)g.cq);
   const int slot = (int)((unsigned)gid / (unsigned)g.cq);
-  const int c0 = cq * 4;
+  const int c0 = min(cq * 4, p.c - 4);
 
   const float* __restrict__ W = static_cast<const float*>(p.w);
   const float* __restrict__ bias = static_cast<const float*>(p.bias);
@@ -101,7 +106,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
   // nine 16-byte loads, then sorted by tap
   v4f wq[9];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) wq[i] = reinterpret_cast<const v4f*>(W + (size_t)c0 * 9)[i];
+  for (int i = 0; i < 9; ++i) wq[i] = reinterpret_cast<const v4f_at4*>(W + (size_t)c0 * 9)[i];
   v4f w[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
           for (int e = 0; e < 4; ++e) acc[e] = clamp_act(acc[e], act_lo, act_hi);
         }
         if (rn.oh0 + ro < p.oh && rn.ow0 + o < p.ow)
-          *reinterpret_cast<v4f*>(yrow + ((size_t)ro * p.ow + o) * p.k) = acc;
+          *reinterpret_cast<v4f_at4*>(yrow + ((size_t)ro * p.ow + o) * p.k) = acc;
       }
     }
   }
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_i8_kernel(const Problem p,
   if (gid < 0 || gid >= (long long)g.cq * g.slots) return;
   const int cq = (int)((unsigned)gid % (unsigned)g.cq);
   const int slot = (int)((unsigned)gid / (unsigned)g.cq);
-  const int c0 = cq * 4;
+  const int c0 = min(cq * 4, p.c - 4);
 
   const signed char* __restrict__ W = static_cast<const signed char*>(p.w);
   const int* __restrict__ bias = static_cast<const int*>(p.bias);
@@ -173,7 +178,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_i8_kernel(const Problem p,
   // the quad's 36 filter codes are nine dwords; per channel and filter row one dword (w0, w1, w2, 0)
   unsigned wq[9];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) wq[i] = reinterpret_cast<const unsigned*>(W + (size_t)c0 * 9)[i];
+  for (int i = 0; i < 9; ++i) wq[i] = reinterpret_cast<const u32_at1*>(W + (size_t)c0 * 9)[i];
   int wr[3][4];
   int kb[4];
 #pragma unroll
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_i8_kernel(const Problem p,
           }
         }
         if (rn.oh0 + ro < p.oh && rn.ow0 + o < p.ow)
-          *reinterpret_cast<unsigned*>(yrow + ((size_t)ro * p.ow + o) * p.k) = pack_codes(q[0], q[1], q[2], q[3]);
+          *reinterpret_cast<u32_at1*>(yrow + ((size_t)ro * p.ow + o) * p.k) = pack_codes(q[0], q[1], q[2], q[3]);
       }
     }
   }
@@ -249,7 +254,7 @@ bool dw_shape(const Problem& p) {
   if (p.b_is_kn || p.chain_n > 0 || p.addend) return false;
   if (p.groups != p.c || p.k != p.c || p.cg != 1 || p.kg != 1) return false;
   if (p.r != 3 || p.s != 3 || p.stride_h != p.stride_w || (p.stride_h != 1 && p.stride_h != 2)) return false;
-  if (p.c % 4 != 0) return false;
+  if (p.c % 4 != 0 && p.c < 8) return false;
   if ((long long)p.n * p.oh * p.ow * p.k >= (1LL << 31)) return false;      // 32-bit run and thread indices
   return p.x_bytes < 0xF0000000u;
 }
@@ -265,7 +270,7 @@ int dw_rows(const Problem& p) {
 
 DwGrid dw_grid(const Problem& p, int rows) {
   DwGrid g;
-  g.cq = p.c / 4;
+  g.cq = (p.c + 3) / 4;
   g.runs_w = (p.ow + DW_RUN - 1) / DW_RUN;
   g.strips = (p.oh + rows - 1) / rows;
   g.runs = (long long)p.n * g.strips * g.runs_w;

@@ -249,3 +249,25 @@ def test_separable_block_int8_sequence(n, hw, c, k, stride):
                               (s.stride, s.stride), (s.pad,) * 4, s.groups, act=s.act)
     G.assert_equal_i8(y.cpu().numpy(), prev, "int8 separable block sequence")
     assert 0.02 < np.mean((prev > -128) & (prev < 127)), "almost everything saturates"
+
+
+@pytest.mark.parametrize("n,h,w,c,st", [(1, 5, 9, 9, 1), (2, 7, 6, 11, 2), (2, 9, 14, 34, 1), (1, 12, 13, 259, 2),
+                                        (3, 8, 5, 70, 1)])
+@pytest.mark.parametrize("w_off", [0, -7])
+def test_depthwise_ragged_channels(n, h, w, c, st, w_off):
+    """One, two and three channels beyond whole quads: the last quad is anchored at the last four channels."""
+    G = _gpu()
+    layer = wl.ConvLayer("dwr", n, h, w, c, c, 3, 3, st, 1, c)
+    pd = (1, 1, 1, 1)
+    x, wt, b = wl.conv_inputs_f32(layer, 38400)
+    desc = G.make_desc(x.shape, wt.shape, (st, st), pd, c)
+    ref = oracle.conv2d_f32(x, wt, b, (st, st), pd, c, act=wl.ACT_RELU)
+    got, variant = G.gpu_conv2d_f32(x, wt, b, desc, wl.ACT_RELU)
+    assert variant == f"conv_dw_f32_3x3s{st}", variant
+    G.assert_close_f32(got, ref, f"depthwise fp32 c {c}")
+    xq, wq, bq, qp = wl.conv_inputs_q(layer, 38401, dist="uniform", w_off=w_off)
+    ref = oracle.qconv2d(xq, qp.x_scale, qp.x_off, wq, qp.w_scale, qp.w_off, bq, qp.y_scale, qp.y_off,
+                         (st, st), pd, c, act=wl.ACT_NONE)
+    got, variant = G.gpu_qconv2d(xq, wq, bq, qp, desc, wl.ACT_NONE)
+    assert variant == f"conv_dw_i8_3x3s{st}", variant
+    G.assert_equal_i8(got, ref, f"depthwise int8 c {c}")
