@@ -1,5 +1,5 @@
-// fp32 Convolution for layers with very few input channels (a network's first layer: 7x7 stride 2 on
-// 3 channels).  The paper's CPU backend singles out "convolutions with a small number of channels"
+// fp32 Convolution for layers with very few input channels (a network's first layer: 7x7 stride 2 or 3x3 stride 1
+// or 2 on 3 channels).  The paper's CPU backend singles out "convolutions with a small number of channels"
 // as one of three kinds that get their own strategy (Section 5.3); this is that kind on gfx950.
 //
 // With 3 channels the generic implicit-GEMM gather degenerates into scalar loads with per-element
@@ -14,6 +14,8 @@
 //   - the filter fragment of the wavefront's 32 output channels (ceil(R*S*C/2) registers per lane)
 //     is loaded once and stays in registers while the persistent workgroup walks over its tiles.
 // Epilogue as everywhere: bias + Relu on the accumulators, one store.
+// Where the last 64 channels would be half empty the tile is twice as tall and 32 channels wide: the four wavefronts
+// share the rows.  (3x3 on 281 x 281, 72 channels, batch 9: generic kernel 129 us -> 74.)
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
@@ -33,8 +35,22 @@ constexpr int TW = 16;                  // output tile width (pixels); 4 wavefro
 // fifth of the chip to the uneven last round (3136 tiles on 768 workgroups: 5 rounds for 4.08).
 constexpr int SC_THREADS = 256;
 
-template <int R, int S, int C, int STRIDE, int TH>
+// The workgroups that share a tile's pixels and differ in their channels are dealt to the same XCD (workgroups go to
+// the eight in turn): where a pixel's channels do not end on a cache line, the line's parts meet in one L2
+// (3x3 on 281 x 281, 72 channels in three slices, batch 9: 105 -> 74 us).
+struct SmallcSlot {
+  int first, step, n_tile;                 // first tile, tiles between two of the workgroup's, its channels
+  __device__ __forceinline__ explicit SmallcSlot(int n_tiles) {
+    const unsigned j = blockIdx.x >> 3;
+    n_tile = (int)(j % (unsigned)n_tiles);
+    first = (int)(j / (unsigned)n_tiles * 8u + (blockIdx.x & 7u));
+    step = (int)(gridDim.x / (unsigned)n_tiles);
+  }
+};
+
+template <int R, int S, int C, int STRIDE, int NB, int CW>
 struct SmallC {
+  static constexpr int TH = 2 * NB * (4 / CW);           // output rows per tile
   static constexpr int K = R * S * C;                    // reduction length
   static constexpr int STEPS = (K + 1) / 2;              // MFMA steps (two k each)
   static constexpr int RUN = S * C;                      // contiguous (s, c) run per filter row
@@ -50,20 +66,20 @@ struct SmallC {
   static constexpr int off(int v) { return (v / RUN) * PITCH + (v % RUN); }
 };
 
-template <int R, int S, int C, int STRIDE, int TH>
+template <int R, int S, int C, int STRIDE, int NB, int CW>
 __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Problem p, int tiles_y, int tiles_x,
-                                                                    int total_tiles) {
-  using G = SmallC<R, S, C, STRIDE, TH>;
-  static_assert(TH == 4 || TH == 8, "tile height");
-  constexpr int NB = TH / 4;             // 32-pixel blocks (2 rows x 16) per wavefront
+                                                                    int total_tiles, int n_tiles) {
+  using G = SmallC<R, S, C, STRIDE, NB, CW>;
+  constexpr int TH = G::TH;
   extern __shared__ __align__(16) float patch[];          // [2][PH + 1][PITCH]
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int lrow = lane & 31, lhalf = lane >> 5;
-  const int wpix = wave >> 1;            // which half of the tile's pixels (rows 2*NB*wpix .. + 2*NB - 1)
-  const int wch = wave & 1;              // which 32 of the 64 output channels
-  const int n_tile = blockIdx.y;
+  const int wpix = wave / CW;            // which part of the tile's pixels (rows 2*NB*wpix .. + 2*NB - 1)
+  const int wch = wave % CW;             // which 32 of the 32 * CW output channels
+  const SmallcSlot slot(n_tiles);
+  const int n_tile = slot.n_tile;
 
   const float* __restrict__ X = static_cast<const float*>(p.x);
   const float* __restrict__ Wt = static_cast<const float*>(p.w);
@@ -71,7 +87,7 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
   const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(
       p.y, 0, (int)((unsigned)p.M * (unsigned)p.k * 4u), 0x00020000);
 
-  const int ch = n_tile * 64 + wch * 32 + lrow;
+  const int ch = n_tile * (32 * CW) + wch * 32 + lrow;
   const bool ch_ok = ch < p.k;
   const float bv = (ch_ok && bias) ? bias[ch] : 0.f;
 
@@ -112,8 +128,8 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
     }
   };
 
-  // persistent walk over tiles: blockIdx.x, + gridDim.x, ...
-  int tile = blockIdx.x;
+  // persistent walk over tiles
+  int tile = slot.first;
   if (tile >= total_tiles) return;
   load_patch(tile);                        // in flight while the filter is fetched
 
@@ -131,8 +147,8 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
     constexpr int HALF_FLOATS = 32 * G::K;
     constexpr int W_LOADS = (HALF_FLOATS + SC_THREADS - 1) / SC_THREADS;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const unsigned base = (unsigned)((n_tile * 64 + half * 32) * G::K) * 4u;
+    for (int half = 0; half < CW; ++half) {
+      const unsigned base = (unsigned)((n_tile * (32 * CW) + half * 32) * G::K) * 4u;
       float wst[W_LOADS];
 #pragma unroll
       for (int i = 0; i < W_LOADS; ++i) {
@@ -165,7 +181,7 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
   __syncthreads();
   int buf = 0;
   for (;;) {
-    const int next = tile + gridDim.x;
+    const int next = tile + slot.step;
     const bool has_next = next < total_tiles;
     if (has_next) load_patch(next);
 
@@ -184,8 +200,11 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
       const float* b = cross ? pc_ : pn;
       const int o = G::off(2 * t);
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[o + i * blk], wfrag[t], acc[i], 0, 0, 0);
+      for (int i = 0; i < NB; ++i) {
+        float av = b[o + i * blk];
+        if (2 * t + 1 == G::K) av = lhalf ? 0.f : av;                // past the reduction: an Inf there must not meet a zero
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, wfrag[t], acc[i], 0, 0, 0);
+      }
     }
 
     if (has_next) store_patch(buf ^ 1);
@@ -243,8 +262,9 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
 // replace 74 fp32 MFMAs of 64 per 32 x 32 block (the first form of this kernel took 11 x 6 bf16 MFMAs over
 // three bf16 pieces per operand: batch 32 62 -> 52 us).
 // ---------------------------------------------------------------------------------------------------
-template <int R, int S, int C, int STRIDE, int TH>
+template <int R, int S, int C, int STRIDE, int NB, int CW>
 struct SmallCB {
+  static constexpr int TH = 2 * NB * (4 / CW);           // output rows per tile
   static constexpr int K = R * S * C;
   static constexpr int RUN = S * C;                      // contiguous (s, c) run per filter row
   static constexpr int RUN8 = (RUN + 7) / 8;             // groups of 8 per filter row
@@ -262,13 +282,12 @@ struct SmallCB {
   static constexpr int off(int g) { return (g / RUN8) * PITCH + (g % RUN8) * 8; }
 };
 
-template <int R, int S, int C, int STRIDE, int TH>
+template <int R, int S, int C, int STRIDE, int NB, int CW>
 __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(const Problem p, int tiles_y, int tiles_x,
-                                                                            int total_tiles) {
-  using G = SmallCB<R, S, C, STRIDE, TH>;
-  static_assert(TH == 4, "tile height: one 32-pixel block per wavefront");
+                                                                            int total_tiles, int n_tiles) {
+  using G = SmallCB<R, S, C, STRIDE, NB, CW>;
+  constexpr int TH = G::TH;
   static_assert((STRIDE * C) % 2 == 0 && G::PITCH % 2 == 0, "a pixel's run starts on a 4-byte boundary");
-  constexpr int NB = TH / 4;
   extern __shared__ __align__(16) unsigned short patchb[];   // [2][2][PH + 2][PITCH]; first the filter halves as fp32
   float* wstage = reinterpret_cast<float*>(patchb);
   unsigned* maxw = reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(patchb) + G::stage_bytes);
@@ -277,9 +296,10 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int lrow = lane & 31, lhalf = lane >> 5;
-  const int wpix = wave >> 1;
-  const int wch = wave & 1;
-  const int n_tile = blockIdx.y;
+  const int wpix = wave / CW;
+  const int wch = wave % CW;
+  const SmallcSlot slot(n_tiles);
+  const int n_tile = slot.n_tile;
 
   const float* __restrict__ X = static_cast<const float*>(p.x);
   const float* __restrict__ Wt = static_cast<const float*>(p.w);
@@ -287,7 +307,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(
       p.y, 0, (int)((unsigned)p.M * (unsigned)p.k * 4u), 0x00020000);
 
-  const int ch = n_tile * 64 + wch * 32 + lrow;
+  const int ch = n_tile * (32 * CW) + wch * 32 + lrow;
   const bool ch_ok = ch < p.k;
   const float bv = (ch_ok && bias) ? bias[ch] : 0.f;
 
@@ -346,7 +366,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     return m;
   };
 
-  int tile = blockIdx.x;
+  int tile = slot.first;
   if (tile >= total_tiles) return;
   if (tid >= 4 && tid < 8) maxw[tid] = 0u;  // never written again; visible after the first barrier
   load_patch(tile);                        // in flight while the filter is fetched
@@ -364,11 +384,11 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wt), 0, (int)p.w_bytes, 0x00020000);
     constexpr int HALF_FLOATS = 32 * G::K;
     constexpr int W_LOADS = (HALF_FLOATS + SC_THREADS - 1) / SC_THREADS;
-    float wst[2][W_LOADS];
+    float wst[CW][W_LOADS];
     unsigned wm = 0;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const unsigned base = (unsigned)((n_tile * 64 + half * 32) * G::K) * 4u;
+    for (int half = 0; half < CW; ++half) {
+      const unsigned base = (unsigned)((n_tile * (32 * CW) + half * 32) * G::K) * 4u;
 #pragma unroll
       for (int i = 0; i < W_LOADS; ++i) {
         const int e = tid + i * SC_THREADS;
@@ -377,7 +397,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
       }
     }
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+    for (int half = 0; half < CW; ++half)
 #pragma unroll
       for (int i = 0; i < W_LOADS; ++i) {
         const unsigned b = __builtin_bit_cast(unsigned, wst[half][i]) & 0x7fffffffu;
@@ -394,7 +414,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     se_w = scale_exponent(w_max_bits);
     finite = w_max_bits < 0x7f800000u;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < CW; ++half) {
 #pragma unroll
       for (int i = 0; i < W_LOADS; ++i) {
         const int e = tid + i * SC_THREADS;
@@ -443,7 +463,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   __syncthreads();
   int buf = 0;
   for (;;) {
-    const int next = tile + gridDim.x;
+    const int next = tile + slot.step;
     const bool has_next = next < total_tiles;
     if (has_next) load_patch(next);
 
@@ -523,12 +543,12 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   }
 }
 
-template <int R, int S, int C, int STRIDE, int TH, bool BF16>
+template <int R, int STRIDE, int NB, int CW, bool BF16>
 hipError_t launch_smallc(const Problem& p, hipStream_t stream) {
-  using G = std::conditional_t<BF16, SmallCB<R, S, C, STRIDE, TH>, SmallC<R, S, C, STRIDE, TH>>;
+  using G = std::conditional_t<BF16, SmallCB<R, R, 3, STRIDE, NB, CW>, SmallC<R, R, 3, STRIDE, NB, CW>>;
   auto kern = [] {
-    if constexpr (BF16) return conv_smallc_f32_f16_kernel<R, S, C, STRIDE, TH>;
-    else return conv_smallc_f32_kernel<R, S, C, STRIDE, TH>;
+    if constexpr (BF16) return conv_smallc_f32_f16_kernel<R, R, 3, STRIDE, NB, CW>;
+    else return conv_smallc_f32_kernel<R, R, 3, STRIDE, NB, CW>;
   }();
   // once per instantiation; initialisation of a function-local static is thread-safe
   struct Setup { hipError_t status; int wg_per_cu; };
@@ -547,42 +567,57 @@ hipError_t launch_smallc(const Problem& p, hipStream_t stream) {
   const int wg_per_cu = setup.wg_per_cu;
   const int num_cu = num_compute_units();
   if (num_cu < 1) return hipErrorInvalidDevice;
+  constexpr int TH = G::TH;
   const int tiles_y = (p.oh + TH - 1) / TH, tiles_x = (p.ow + TW - 1) / TW;
   const long long total = (long long)p.n * tiles_y * tiles_x;
-  const int n_tiles = (p.k + 63) / 64;
+  const int n_tiles = (p.k + 32 * CW - 1) / (32 * CW);
   long long gx = (long long)num_cu * wg_per_cu / n_tiles;
-  if (gx < 1) gx = 1;
-  if (gx > total) gx = total;
-  dim3 grid((unsigned)gx, n_tiles, 1), block(SC_THREADS, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, G::lds_bytes, stream, p, tiles_y, tiles_x, (int)total);
+  gx = gx < 8 ? 8 : gx / 8 * 8;            // whole rounds over the XCDs
+  if (gx > total) gx = (total + 7) / 8 * 8;
+  dim3 grid((unsigned)(gx * n_tiles), 1, 1), block(SC_THREADS, 1, 1);
+  hipLaunchKernelGGL(kern, grid, block, G::lds_bytes, stream, p, tiles_y, tiles_x, (int)total, n_tiles);
   return hipGetLastError();
 }
 
 }  // namespace
 
 bool smallc_f32_applicable(const Problem& p) {
-  return !p.b_is_kn && p.groups == 1 && p.r == 7 && p.s == 7 && p.c == 3 && p.stride_h == 2 && p.stride_w == 2 &&
+  return !p.b_is_kn && p.groups == 1 && p.r == p.s && p.c == 3 && p.stride_h == p.stride_w &&
+         ((p.r == 7 && p.stride_h == 2) || (p.r == 3 && (p.stride_h == 1 || p.stride_h == 2))) &&
          (long long)p.M * p.k * 4 < (1LL << 31) && p.w_bytes <= 0x7FFFFFFFu &&
          (long long)p.n * ((p.oh + 3) / 4) * ((p.ow + TW - 1) / TW) < (1LL << 31);
 }
 
 hipError_t launch_smallc_f32(const Problem& p, hipStream_t stream, const char** variant) {
+  // The last 64 channels no more than half full: tiles of twice the rows and 32 channels.
+  const bool half = (p.k - 1) % 64 < 32;
+  // the taller tile is the faster one per tile (two independent MFMA chains per wavefront); the
+  // shorter one doubles the number of tiles, which pays while there are fewer than about two per
+  // resident workgroup (batch 1: 13.8 -> 11.1 us; batch 32: 97.8 vs 100.5 us)
+  const long long tiles8 = (long long)p.n * ((p.oh + 7) / 8) * ((p.ow + TW - 1) / TW);
+  bool two = tiles8 >= 1536;
+  if (knob_is_set(KNOB_SMALLC_TH)) two = knob(KNOB_SMALLC_TH) == 8;   // experiments
+  if (p.r == 3) {
+    // nine multiply-adds per input value: bound by the output on the fp32 cores already
+    *variant = p.stride_h == 1 ? "conv_smallc_f32_3x3s1c3" : "conv_smallc_f32_3x3s2c3";
+    if (p.stride_h == 1) {
+      if (half) return two ? launch_smallc<3, 1, 2, 1, false>(p, stream) : launch_smallc<3, 1, 1, 1, false>(p, stream);
+      return two ? launch_smallc<3, 1, 2, 2, false>(p, stream) : launch_smallc<3, 1, 1, 2, false>(p, stream);
+    }
+    if (half) return two ? launch_smallc<3, 2, 2, 1, false>(p, stream) : launch_smallc<3, 2, 1, 1, false>(p, stream);
+    return two ? launch_smallc<3, 2, 2, 2, false>(p, stream) : launch_smallc<3, 2, 1, 2, false>(p, stream);
+  }
   // The fp16-piece form pays a longer prologue (the filter fragments are cut per workgroup): batch 32 90 -> 52 us,
   // batch 8 27 -> 22 us, but batch 1 (196 tiles, launch-bound) 8.2 -> 11.7 us, which therefore keeps the fp32 form.
   // The knob forces one.
   const long long tiles4 = (long long)p.n * ((p.oh + 3) / 4) * ((p.ow + TW - 1) / TW);
   const bool bf16 = knob_or(KNOB_F32_SMALLC_BF16, tiles4 >= 1536 ? 1 : 0) != 0;
   *variant = bf16 ? "conv_smallc_f32_7x7s2c3_f16x3" : "conv_smallc_f32_7x7s2c3";
-  // the taller tile is the faster one per tile (two independent MFMA chains per wavefront); the
-  // shorter one doubles the number of tiles, which pays while there are fewer than about two per
-  // resident workgroup (batch 1: 13.8 -> 11.1 us; batch 32: 97.8 vs 100.5 us)
-  const long long tiles8 = (long long)p.n * ((p.oh + 7) / 8) * ((p.ow + TW - 1) / TW);
-  int th = tiles8 < 1536 ? 4 : 8;
-  if (knob_is_set(KNOB_SMALLC_TH)) th = knob(KNOB_SMALLC_TH) == 8 ? 8 : 4;   // experiments
   // (the fp16-piece form keeps 88 registers of filter fragments per lane and two accumulator sets: with two pixel
-  // blocks per wavefront it would spill, so it always takes the four-row tile)
-  if (bf16) return launch_smallc<7, 7, 3, 2, 4, true>(p, stream);
-  return th == 8 ? launch_smallc<7, 7, 3, 2, 8, false>(p, stream) : launch_smallc<7, 7, 3, 2, 4, false>(p, stream);
+  // blocks per wavefront it would spill, so it always takes the shorter tile)
+  if (bf16) return half ? launch_smallc<7, 2, 1, 1, true>(p, stream) : launch_smallc<7, 2, 1, 2, true>(p, stream);
+  if (half) return two ? launch_smallc<7, 2, 2, 1, false>(p, stream) : launch_smallc<7, 2, 1, 1, false>(p, stream);
+  return two ? launch_smallc<7, 2, 2, 2, false>(p, stream) : launch_smallc<7, 2, 1, 2, false>(p, stream);
 }
 
 }  // namespace glowmi

@@ -146,3 +146,35 @@ def test_first_layer_int8_multipliers(mr_exp):
     assert variant.startswith("conv_smallc_i8"), variant
     assert len(np.unique(ref)) > 8
     G.assert_equal_i8(got, ref, f"first layer int8 multiplier {0.8 * 2.0 ** mr_exp / 8}")
+
+
+# n  h  w  k  pads(t,l,b,r): 32- and 64-channel forms, their last channels ragged, maps around one tile, the tail pixel
+FIRST_3X3 = [
+    (1, 3, 3, 8, (0, 0, 0, 0)),
+    (2, 5, 1, 33, (1, 1, 1, 1)),
+    (2, 17, 35, 64, (1, 1, 1, 1)),
+    (1, 34, 31, 72, (0, 1, 1, 0)),
+    (3, 9, 70, 47, (1, 1, 1, 1)),
+    (70, 40, 33, 40, (1, 1, 1, 1)),       # more tiles than persistent workgroups
+]
+
+
+@pytest.mark.parametrize("i", range(len(FIRST_3X3)))
+@pytest.mark.parametrize("st", [1, 2])
+def test_first_layer_3x3(i, st):
+    G = _gpu()
+    n, h, w, k, pd = FIRST_3X3[i]
+    layer = wl.ConvLayer(f"first3{i}", n, h, w, 3, k, 3, 3, st, 1, 1)
+    x, wt, b = wl.conv_inputs_f32(layer, 9960 + i)
+    desc = G.make_desc(x.shape, wt.shape, (st, st), pd, 1)
+    ref = oracle.conv2d_f32(x, wt, b, (st, st), pd, 1, act=wl.ACT_RELU)
+    got, variant = G.gpu_conv2d_f32(x, wt, b, desc, wl.ACT_RELU)
+    assert variant == f"conv_smallc_f32_3x3s{st}c3", variant
+    G.assert_close_f32(got, ref, f"first layer fp32 3x3 {FIRST_3X3[i]}")
+    xq, wq, bq, qp = wl.conv_inputs_q(layer, 9970 + i, dist="uniform", w_off=0)
+    for act, bias in ((wl.ACT_RELU, bq), (wl.ACT_NONE, None)):
+        ref = oracle.qconv2d(xq, qp.x_scale, qp.x_off, wq, qp.w_scale, qp.w_off, bias, qp.y_scale, qp.y_off,
+                             (st, st), pd, 1, act=act)
+        got, variant = G.gpu_qconv2d(xq, wq, bias, qp, desc, act)
+        assert variant == f"conv_smallc_i8_3x3s{st}c3", variant
+        G.assert_equal_i8(got, ref, f"first layer int8 3x3 {FIRST_3X3[i]} act {act}")
