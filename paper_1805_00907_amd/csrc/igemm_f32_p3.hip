@@ -274,8 +274,13 @@ __global__ __launch_bounds__(256) void pack2_pair_kernel(const float* __restrict
 // ------------------------------------------------------------------------------------------------
 // WN: 64-channel columns of wavefronts (2: 128 channels, 512 threads; 1: 64 channels, 256 threads).
 // PADDED: some filter tap of some pixel may fall on padding.  LONGK: reductions longer than P3_FLUSH slabs
-// keep a second accumulator set.  NBUF: slab buffers in the LDS ring.
-template <int WN, bool PADDED, bool LONGK, int NBUF>
+// keep a second accumulator set.  RING: buffers of the LDS ring for the slab multiplied and those in flight.
+// With 128 channels the fragments are read a slab ahead, out of one buffer more; a second accumulator set leaves no
+// registers for that.
+template <int WN, bool LONGK>
+constexpr int kFragmentsAhead = WN == 2 && !LONGK ? 1 : 0;
+
+template <int WN, bool PADDED, bool LONGK, int RING>
 __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem p, int tiles_m, int tiles_n,
                                                                    int band_n, int total_work) {
   constexpr int BN = 64 * WN;
@@ -285,7 +290,8 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   constexpr int LPI = 2 * (A_GROUPS + 1);               // loads one wavefront issues per slab
   constexpr int A_PLANE = PBM * PROW, B_PLANE = BN * PROW;
   constexpr int BUF = 2 * (A_PLANE + B_PLANE);
-  constexpr int AHEAD = NBUF >= 4 ? 1 : 0;              // the slab after the one multiplied has landed as well
+  constexpr int AHEAD = kFragmentsAhead<WN, LONGK>;     // the slab after the one multiplied has landed as well
+  constexpr int NBUF = RING + AHEAD;
   static_assert(!AHEAD || NBUF % 2 == 0, "register sets alternate with the buffers");
   static_assert(NBUF * BUF >= WAVES * 32 * 64 * 4, "exchange of the partial tiles fits the slab buffers");
 
@@ -612,10 +618,11 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   }
 }
 
-template <int WN, bool PADDED, bool LONGK, int NBUF>
+template <int WN, bool PADDED, bool LONGK>
 hipError_t launch_p3_variant(const Problem& p, const Plan& plan, hipStream_t stream) {
-  auto kern = igemm_f32_p3_kernel<WN, PADDED, LONGK, NBUF>;
-  constexpr int lds_bytes = NBUF * 2 * (PBM + 64 * WN) * PROW;
+  constexpr int RING = WN == 2 ? 3 : 2;
+  auto kern = igemm_f32_p3_kernel<WN, PADDED, LONGK, RING>;
+  constexpr int lds_bytes = (RING + kFragmentsAhead<WN, LONGK>) * 2 * (PBM + 64 * WN) * PROW;
   static const hipError_t attr_status = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
   if (attr_status != hipSuccess) return attr_status;
@@ -629,14 +636,10 @@ hipError_t launch_p3_variant(const Problem& p, const Plan& plan, hipStream_t str
   return hipGetLastError();
 }
 
-// With 128 channels four slab buffers, the fragments read a slab ahead; a second accumulator set leaves no registers for that.
 template <int WN>
 hipError_t launch_p3_flags(const Problem& p, const Plan& plan, hipStream_t stream, bool padded, bool longk) {
-  constexpr int NBUF = WN == 2 ? 4 : 2, NBUF_LONG = WN == 2 ? 3 : 2;
-  if (padded) return longk ? launch_p3_variant<WN, true, true, NBUF_LONG>(p, plan, stream)
-                           : launch_p3_variant<WN, true, false, NBUF>(p, plan, stream);
-  return longk ? launch_p3_variant<WN, false, true, NBUF_LONG>(p, plan, stream)
-               : launch_p3_variant<WN, false, false, NBUF>(p, plan, stream);
+  if (padded) return longk ? launch_p3_variant<WN, true, true>(p, plan, stream) : launch_p3_variant<WN, true, false>(p, plan, stream);
+  return longk ? launch_p3_variant<WN, false, true>(p, plan, stream) : launch_p3_variant<WN, false, false>(p, plan, stream);
 }
 
 size_t align_up(size_t v) { return (v + kPlaneAlign - 1) / kPlaneAlign * kPlaneAlign; }
