@@ -21,6 +21,7 @@ enum Knob {
   KNOB_F32_SMALL_SPLIT_MAX_TILES, KNOB_F32_SMALL_MIN_WGS, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW, KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_SMALLC_TH, KNOB_F32_SMALLC_BF16,
   KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_SMALLC_I8_WGS, KNOB_I8_PW_MIN_ITEMS,
   KNOB_I8_FC_SMALL_MAX_M, KNOB_I8_K3_MIN_BLOCKS, KNOB_I8_K3_WAVES, KNOB_I8_K3_GATHER, KNOB_DW, KNOB_F32_PATCH, KNOB_F32_PATCH_TILE, KNOB_F32_FC_ROWS,
+  KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT,
   KNOB_COUNT
 };
 constexpr int kKnobUnset = INT_MIN;
@@ -135,6 +136,7 @@ enum KernelKind {
   KERNEL_P3,            // fp32 large contractions on the fp16 matrix cores, operands cut into two pieces (igemm_f32_p3.hip)
   KERNEL_DW,            // depthwise 3x3 convolution, fp32 and int8 (conv_dw.hip)
   KERNEL_FC_ROWS,       // fp32 FullyConnected with one to four rows in one launch (fc_small_f32.hip)
+  KERNEL_FC_TILES,      // fp32 FullyConnected, both operands cut on the way to the fp16 matrix cores (fc_tiles_f32.hip)
   KERNEL_PATCH          // fp32 1x1 and 3x3 convolution, fp16 matrix cores, one input patch per tile (conv_patch_f32.hip)
 };
 struct Plan {
@@ -166,6 +168,9 @@ hipError_t launch_pw_f32(const Problem& p, hipStream_t stream, const char** vari
 bool conv_small_f32_applicable(const Problem& p);
 hipError_t launch_conv_small_f32(const Problem& p, hipStream_t stream, const char** variant);
 int conv_small_f32_splits(const Problem& p);   // > 1: the split form of that kernel applies, with this many reduction slices
+// fp32 FullyConnected with dozens to hundreds of rows (fc_tiles_f32.hip).
+bool plan_fc_tiles_f32(const Problem& p, bool allow_split, Plan* plan, double* us);
+hipError_t launch_fc_tiles_f32(const Problem& p, const Plan& plan, hipStream_t stream, const char** variant);
 // fp32 FullyConnected with few rows and a small weight matrix, in one launch (fc_small_f32.hip).
 bool fc_small_f32_applicable(const Problem& p);
 hipError_t launch_fc_small_f32(const Problem& p, hipStream_t stream, const char** variant);

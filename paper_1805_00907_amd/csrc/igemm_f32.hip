@@ -677,7 +677,44 @@ constexpr TileF32 kTilesF32[] = {
 };
 constexpr int kNumTilesF32 = sizeof(kTilesF32) / sizeof(kTilesF32[0]);
 
+namespace {
+Plan plan_f32_rest(const Problem& p, bool allow_split);
+size_t wanted_bytes(const Problem& p, const Plan& pl) {
+  return pl.pack_bytes + (pl.split_k > 1 ? (size_t)pl.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
+}
+}  // namespace
+
 Plan plan_f32(const Problem& p, bool allow_split) {
+  const Plan rest = plan_f32_rest(p, allow_split);
+  const int mode = knob_or(KNOB_F32_FC_TILES, 1);
+  if (!p.b_is_kn || mode == 0) return rest;
+  Plan pl = rest;
+  double us;
+  if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? pl : rest;
+  // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 30 -> 17.7 us), and of the
+  // contraction over planes where that would have to cut the weights as well and takes longer by its own measured times
+  // (256x4096x4096 84 -> 47 us; 1024x4096x4096 stays: 158 against 186).
+  if (p.M < 65 || (rest.kernel != KERNEL_TILED && rest.kernel != KERNEL_P3) || knob_is_set(KNOB_F32_TILE) ||
+      knob_is_set(KNOB_F32_P3_MIN_M) || knob_is_set(KNOB_F32_SPLIT) || (rest.kernel == KERNEL_P3 && p.w_packed))
+    return rest;
+  if (!plan_fc_tiles_f32(p, allow_split, &pl, &us)) return rest;
+  const size_t ask = wanted_bytes(p, rest);
+  if (wanted_bytes(p, pl) > ask) {                       // no more workspace than before
+    pl = rest;
+    if (!plan_fc_tiles_f32(p, false, &pl, &us)) return rest;
+  }
+  if (rest.kernel == KERNEL_P3) {
+    const double padded = 2e-9 * ((p.M + 127) / 128 * 128) * ((p.k + 127) / 128 * 128) * (double)p.Kgemm;
+    if (us > 22.0 + 3.3 * padded + 0.45e-6 * (double)p.w_bytes) return rest;
+  }
+  // the workspace to ask for stays what the other kernel asks for
+  const size_t mine = wanted_bytes(p, pl);
+  if (mine < ask) pl.pack_bytes = (ask - mine) / 256 * 256;
+  return pl;
+}
+
+namespace {
+Plan plan_f32_rest(const Problem& p, bool allow_split) {
   Plan pl;
   pl.kernel = KERNEL_TILED;
   pl.tile = 0;
@@ -833,6 +870,7 @@ Plan plan_f32(const Problem& p, bool allow_split) {
   }
   return pl;
 }
+}  // namespace
 
 namespace {
 template <int BM, int BN, int WM, int WN, bool LONGK>
@@ -887,6 +925,8 @@ hipError_t launch_f32(const Problem& p_in, const Plan& plan, hipStream_t stream,
   hipError_t e;
   if (plan.kernel == KERNEL_SMALL_SPLIT) {
     e = launch_conv_small_f32(p, stream, variant);
+  } else if (plan.kernel == KERNEL_FC_TILES) {
+    e = launch_fc_tiles_f32(p, plan, stream, variant);
   } else if (plan.kernel == KERNEL_SKINNY16) {
     *variant = "fc_skinny16_f32";
     dim3 grid(plan.tiles_n, plan.split_k, 1), block(64 * SK_WAVES, 1, 1);

@@ -1,0 +1,31 @@
+"""fp32 FullyConnected cut on the way to the matrix cores (fc_tiles_f32) against the CPU oracle: ragged rows, columns and
+reductions, fewer chunks than wavefronts, split reductions, values that outgrow a wavefront's scale."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import oracle
+from paper_1805_00907_amd import workloads as wl
+
+
+SHAPES = [(1, 1, 1), (17, 16, 64), (33, 130, 65), (64, 1000, 96), (65, 259, 33), (138, 783, 223), (100, 513, 130), (130, 2048, 192)]
+
+
+@pytest.mark.parametrize("rows", [32, 64])
+@pytest.mark.parametrize("shape,split", [(s, 1) for s in SHAPES] + [(SHAPES[3], 3), (SHAPES[5], 3), (SHAPES[7], 2), (SHAPES[7], 8)], ids=str)
+def test_fc_tiles_f32(shape, split, rows, knobs):
+    import gpu_util as G
+    m, k, n = shape
+    knobs.set("F32_FC_TILES", 3 if rows == 32 else 4)
+    knobs.set("F32_FC_TILES_SPLIT", split)
+    rng = np.random.default_rng(39000 + m + k + n)
+    a = rng.uniform(-1, 1, size=(m, k)).astype(np.float32)
+    w = (rng.uniform(-1, 1, size=(k, n)) / np.sqrt(k)).astype(np.float32)
+    a[:, :k // 2] /= 37.0                                # later chunks outgrow the first one's scale
+    w[:k // 3] /= 5.0
+    b = rng.uniform(-0.1, 0.1, size=(n,)).astype(np.float32)
+    for bias, act in ((b, wl.ACT_RELU), (None, wl.ACT_NONE)):
+        got, variant = G.gpu_fc_f32(a, w, bias, act)
+        assert variant.startswith("fc_tiles_f32_%dx" % rows), variant
+        G.assert_close_f32(got, oracle.fc_f32(a, w, bias, act=act), f"{shape} [{variant}]")
