@@ -13,7 +13,11 @@
 //   - a wavefront multiplies 64 pixels x 32 channels: every filter fragment meets two pixel fragments.  The eight
 //     or four wavefronts of a workgroup cover the tile, and where it has fewer such blocks, KS wavefronts share one: each
 //     takes every KS-th run of 16 channels, and they add up through LDS at the end;
-//   - the filter's fragments go from memory into registers, DB steps ahead: no LDS traffic and no barrier for them.
+//   - the filter's fragments go from memory into registers, DB steps ahead: no LDS traffic and no barrier for them;
+//   - the accumulators of the h1 h1' products are folded into a second set after every eight or nine steps.  One chain of
+//     rounded additions per output was less exact than the contraction over planes that some of these layers came from (3x3
+//     392 -> 200 on 92x75 2.7e-7 of the result's norm against 1.1e-7, 512 -> 512 on 28x28 4.3e-7); so it is no further from
+//     64-bit sums than that kernel (1.1e-7 and 1.6e-7), for 2 % of the time.
 // What bounds it: LDS and vector memory bandwidth next to the matrix cores, and what a workgroup does before its first and
 // behind its last chunk.  A form with 32 x 32 blocks per wavefront and the filter in an LDS ring read 32 KB of fragments per
 // 32 reduction indices of a 64 x 64 tile, 256 cycles against 192 of matrix work, and did not get past a third of the matrix
@@ -65,6 +69,7 @@ struct Patch {
   static constexpr int ROWS = 4 * PASSES * THREADS * 16 <= (W == 8 ? 150 : 75) * 1024 ? PASSES * THREADS / PIECES : MAXP;
   static constexpr int ITEMS = ROWS * PIECES;
   static constexpr int APLANE = ROWS * ROW, PAIR = 2 * APLANE;
+  static constexpr int FOLD = R == 3 ? 1 : 8 / NS;          // chunks between folds of the accumulators (18 steps: one in the middle, too)
   static constexpr int CUT_FROM = NS > 2 ? 1 : 0;            // the steps beside which the next chunk is cut
   static constexpr int CUT_STEPS = PASSES < NS - CUT_FROM ? PASSES : NS - CUT_FROM;
   static constexpr int XCH = KS > 1 ? W * 8 * 64 * 16 : 0;   // exchange of partial tiles, in place of the planes
@@ -258,12 +263,14 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
   }
 
   v16f acc[2], acc_lo[2];                               // the h1 h1' products; the cross terms (weight 2^-11)
+  v16f total[2];                                        // what acc is folded into
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       acc[b][e] = 0.f;
       acc_lo[b][e] = 0.f;
+      total[b][e] = 0.f;
     }
 
   leave_max(pre0, 0);
@@ -297,6 +304,16 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
         fa[st & 1][b][1] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(at + T::APLANE));
       }
     };
+    auto fold = [&] {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          total[b][e] += acc[b][e];
+          acc[b][e] = 0.f;
+        }
+    };
+    if (U % T::FOLD == 0 && chunk % T::FOLD == 0) fold();   // uniform
     __syncthreads();                                    // this chunk's planes and the next one's magnitudes are there
     read_a(0);
     if (se_x < se_acc) {                                // uniform: larger values than any chunk before
@@ -306,6 +323,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
         for (int e = 0; e < 16; ++e) {
           acc[b][e] = __builtin_ldexpf(acc[b][e], se_x - se_acc);
           acc_lo[b][e] = __builtin_ldexpf(acc_lo[b][e], se_x - se_acc);
+          total[b][e] = __builtin_ldexpf(total[b][e], se_x - se_acc);
         }
       se_acc = se_x;
     }
@@ -313,6 +331,11 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 #pragma unroll
     for (int st = 0; st < T::NS; ++st) {
       const int cur = st & 1, slot = (U * T::NS + st) % T::DB;
+      if (T::NS > 9 && st == T::NS / 2) {
+        int always = 1;                                 // opaque: without the branch the registers run out (14 to 25 spills a chunk)
+        asm volatile("" : "+s"(always));
+        if (always) fold();
+      }
       __builtin_amdgcn_sched_barrier(0);
       if (st + 1 < T::NS) read_a(st + 1);
       const v8h b1 = __builtin_bit_cast(v8h, fb[slot][0]), b2 = __builtin_bit_cast(v8h, fb[slot][1]);
@@ -356,7 +379,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) joined[b * 16 + e] = __builtin_fmaf(acc_lo[b][e], kLowPieceWeight, acc[b][e]);
+    for (int e = 0; e < 16; ++e) joined[b * 16 + e] = __builtin_fmaf(acc_lo[b][e], kLowPieceWeight, acc[b][e]) + total[b][e];
   if (T::KS > 1) {
     v4f* xch = reinterpret_cast<v4f*>(lds);
     const int pair = wave % (PXB * CHB);

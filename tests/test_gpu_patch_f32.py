@@ -126,6 +126,29 @@ def test_conv_patch_wide_value_ranges(r, st, knobs):
     assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 + 1e-4 * np.abs(ref[ok]))
 
 
+@pytest.mark.parametrize("r,st,tile", [(r, st, t) for r, st in ((3, 1), (3, 2), (1, 1)) for t in range(7)
+                                       if not (t == 1 and r == 1) and not (t != 1 and (r, st) == (3, 2))])
+def test_long_reductions_are_summed_in_short_runs(r, st, tile, knobs):
+    """Error against 64-bit sums of a reduction of 256 to 288 steps of 16.  Cutting the operands: a quarter of the values
+    lose their last bit, 2^-24 rms of the value, twice.  An addition to an accumulator rounds by 0.29 of 2^-23 rms; n of them
+    to a growing sum count as n / 2: runs of nine, then 32 runs.  (One run of 288 would give 4.2e-7.)"""
+    G = _gpu()
+    knobs.set("F32_PATCH", 2)
+    knobs.set("F32_PATCH_TILE", tile)
+    knobs.set("F32_K3", 0)
+    knobs.set("F32_K3C64", 0)
+    c = 512 if r == 3 else 4096
+    rng = np.random.default_rng(37700)
+    x = rng.standard_normal(size=(1, 16, 8, c)).astype(np.float32)
+    wt = (rng.standard_normal(size=(64, r, r, c)) / np.sqrt(r * r * c)).astype(np.float32)
+    desc = G.make_desc(x.shape, wt.shape, (st, st), (r // 2,) * 4, 1)
+    ref = oracle.conv2d_f32(x, wt, None, (st, st), (r // 2,) * 4, 1, act=wl.ACT_NONE).astype(np.float64)
+    got, variant = G.gpu_conv2d_f32(x, wt, None, desc, wl.ACT_NONE)
+    assert variant.startswith("conv_patch_f32_f16x3"), variant
+    bound = 1.15 * np.sqrt(2 * 2.0 ** -48 + (0.29 * 2.0 ** -23) ** 2 * (9 / 2 + 32 / 2))
+    assert np.linalg.norm(got - ref) <= bound * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("layers", [1, 8, 10])
 def test_sequence_cuts_filters_ahead_in_groups(layers, knobs):
     """Layers of a sequence have their filters cut up to eight at a time: the same results as layer by layer."""
