@@ -11,6 +11,9 @@
 //   - x arrives as 64 bytes of 16 rows per load and goes, cut, through 4 KB of LDS of the wavefront's own (fetched in the
 //     operand's own layout, 32 bytes of 32 rows at a time, it comes at a quarter of the rate);
 //   - a wavefront scales either operand by the largest magnitude it has seen; values that outgrow it scale the sums down;
+//   - every eight chunks the accumulators of the h1 h1' products are folded into sums in LDS.  One chain of rounded additions
+//     per output and wavefront was less exact than the contraction over planes at deep reductions (256x9216x4096 2.4e-7 of
+//     the result's norm against 1.7e-7, now 1.4e-7);
 //   - at the end the wavefronts exchange their sums through LDS and finish an eighth of the tile each.
 // Bound by the vector unit (the cuts: 32 values a lane and chunk) and the 64 bytes a clock of a CU's memory path, closely
 // followed by the matrix cores.  Measured: 256x4096x4096 47 us, 1000x1024x512 12.6, 150x301x77 6.5 (84, 22, 13 on the kernels
@@ -29,7 +32,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-constexpr int FT_WAVES = 8, FT_COLS = 64, FT_CHUNK = 16;
+constexpr int FT_WAVES = 8, FT_COLS = 64, FT_CHUNK = 16, FT_FOLD = 8;   // FT_FOLD: chunks of a wavefront between folds, even
 constexpr unsigned FT_OOB = 0x80000000u;                 // operands are smaller: whatever is added or set below, past the end
 
 __device__ __forceinline__ void cut4_in_place(const v4f& x, int se, v2u& p1, v2u& p2) {
@@ -192,11 +195,39 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
     }
   };
 
+  // Sums of short runs round less: every FT_FOLD chunks acc goes into LDS of the wavefront's own, at the scale of that moment.
+  constexpr int NQ = MB * 8;                             // quads of registers of the tile
+  v4f* const kept = reinterpret_cast<v4f*>(lds + FT_WAVES * 2 * PLANE) + wave * NQ * 64 + lane;
+  int kept_se = 0, since_fold = 0;
+  bool any_kept = false;                                 // uniform, as the two above
+  auto kept_quad = [&](int q) {                          // at the present scale
+    v4f v = kept[q * 64];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __builtin_ldexpf(v[e], sx.se + sw.se - kept_se);
+    return v;
+  };
+
   int chunk = first + wave;
   load(0, chunk);
   load(1, chunk + FT_WAVES);
   // in pairs; the one after the last is all zeros
   do {
+    if (since_fold == FT_FOLD) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        v4f v = any_kept ? kept_quad(q) : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] += acc[q / 8][q / 4 % 2][q % 4 * 4 + e];
+          acc[q / 8][q / 4 % 2][q % 4 * 4 + e] = 0.f;
+        }
+        kept[q * 64] = v;
+      }
+      kept_se = sx.se + sw.se;
+      since_fold = 0;
+      any_kept = true;
+    }
+    since_fold += 2;
     multiply(0, chunk);
     multiply(1, chunk + FT_WAVES);
     chunk += 2 * FT_WAVES;
@@ -204,7 +235,15 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
 
   // ---- the wavefronts swap their sums: each finishes OQ of the tile's NQ quads of registers.  Register e of a block is row
   // (e/4)*8 + 4*lhalf + e%4 of its 32, column lane % 32.
-  constexpr int NQ = MB * 8, OQ = NQ / FT_WAVES;
+  constexpr int OQ = NQ / FT_WAVES;
+  if (any_kept) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const v4f v = kept_quad(q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[q / 8][q / 4 % 2][q % 4 * 4 + e] += v[e];
+    }
+  }
   const ScaleBack sb = scale_back_of(sx.se, sw.se, finite);
   v4f* xch = reinterpret_cast<v4f*>(lds);
   float res[OQ][4];
@@ -255,7 +294,7 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
 
 template <int MB>
 hipError_t launch_ft(const Problem& p, const Plan& plan, hipStream_t stream) {
-  constexpr int lds_bytes = FT_WAVES * MB * 8 * 64 * 16;   // the exchange; the planes are smaller
+  constexpr int lds_bytes = FT_WAVES * MB * (2 * 32 * 32 + 8 * 64 * 16);   // the planes of x, the folded sums (then the exchange)
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(fc_tiles_f32_kernel<MB>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
   if (attr != hipSuccess) return attr;

@@ -29,3 +29,22 @@ def test_fc_tiles_f32(shape, split, rows, knobs):
         got, variant = G.gpu_fc_f32(a, w, bias, act)
         assert variant.startswith("fc_tiles_f32_%dx" % rows), variant
         G.assert_close_f32(got, oracle.fc_f32(a, w, bias, act=act), f"{shape} [{variant}]")
+
+
+@pytest.mark.parametrize("rows", [32, 64])
+def test_long_reductions_are_summed_in_short_runs(rows, knobs):
+    """Error against 64-bit sums, a reduction of 576 steps of 16, 72 per wavefront.  Cutting the operands: a quarter of the
+    values lose their last bit, 2^-24 rms of the value, twice.  An addition to an accumulator rounds by 0.29 of 2^-23 rms; n
+    of them to a growing sum count as n / 2: runs of eight, nine runs, eight wavefronts.  (A run of 72 would give 2.4e-7.)"""
+    import gpu_util as G
+    knobs.set("F32_FC_TILES", 3 if rows == 32 else 4)
+    knobs.set("F32_FC_TILES_SPLIT", 1)
+    m, k, n = 64, 9216, 192
+    rng = np.random.default_rng(39500)
+    a = rng.standard_normal(size=(m, k)).astype(np.float32)
+    w = (rng.standard_normal(size=(k, n)) / np.sqrt(k)).astype(np.float32)
+    got, variant = G.gpu_fc_f32(a, w, None, wl.ACT_NONE)
+    assert variant.startswith("fc_tiles_f32_%dx" % rows), variant
+    ref = a.astype(np.float64) @ w.astype(np.float64)
+    bound = 1.15 * np.sqrt(2 * 2.0 ** -48 + (0.29 * 2.0 ** -23) ** 2 * (8 / 2 + 9 / 2 + 8 / 2))
+    assert np.linalg.norm(got - ref) <= bound * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
