@@ -682,15 +682,21 @@ Plan plan_f32_rest(const Problem& p, bool allow_split);
 size_t wanted_bytes(const Problem& p, const Plan& pl) {
   return pl.pack_bytes + (pl.split_k > 1 ? (size_t)pl.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
 }
+// A plan that needs no scratch asks for a little all the same: without a workspace the call stays on the fp32 matrix cores.
+Plan asking(const Problem& p, Plan pl) {
+  if (wanted_bytes(p, pl) == 0) pl.pack_bytes = 256;
+  return pl;
+}
 }  // namespace
 
 Plan plan_f32(const Problem& p, bool allow_split) {
   const Plan rest = plan_f32_rest(p, allow_split);
   const int mode = knob_or(KNOB_F32_FC_TILES, 1);
-  if (!p.b_is_kn || mode == 0) return rest;
+  // only for calls that have the workspace they asked for (or the static buffer in its place)
+  if (!p.b_is_kn || mode == 0 || !allow_split) return rest;
   Plan pl = rest;
   double us;
-  if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? pl : rest;
+  if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? asking(p, pl) : rest;
   // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 30 -> 17.7 us), and of the
   // contraction over planes where that would have to cut the weights as well and takes longer by its own measured times
   // (256x4096x4096 84 -> 47 us; 1024x4096x4096 stays: 158 against 186).
@@ -710,7 +716,7 @@ Plan plan_f32(const Problem& p, bool allow_split) {
   // the workspace to ask for stays what the other kernel asks for
   const size_t mine = wanted_bytes(p, pl);
   if (mine < ask) pl.pack_bytes = (ask - mine) / 256 * 256;
-  return pl;
+  return asking(p, pl);
 }
 
 namespace {

@@ -48,3 +48,35 @@ def test_long_reductions_are_summed_in_short_runs(rows, knobs):
     ref = a.astype(np.float64) @ w.astype(np.float64)
     bound = 1.15 * np.sqrt(2 * 2.0 ** -48 + (0.29 * 2.0 ** -23) ** 2 * (8 / 2 + 9 / 2 + 8 / 2))
     assert np.linalg.norm(got - ref) <= bound * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("shape,taken", [((64, 512, 256), False), ((65, 256, 64), True), ((1000, 1024, 512), True),
+                                         ((256, 4096, 4096), True), ((150, 301, 77), True), ((1024, 4096, 4096), False)], ids=str)
+def test_which_calls_take_the_kernel(shape, taken):
+    """From 65 rows, up to where the contraction over planes is faster; only with the workspace the query names.  The call
+    that works in the static buffer runs what the call with a workspace runs."""
+    import torch
+    import gpu_util as G
+    import paper_1805_00907_amd as glowmi
+    m, k, n = shape
+    a, w = torch.randn((m, k), device="cuda:0"), torch.randn((k, n), device="cuda:0")
+    y = G.poison((m, n), torch.float32)
+    need = glowmi.fc_workspace_bytes(m, k, n)
+    assert need > 0 or not taken
+
+    def variant(workspace_bytes):
+        ws = torch.empty(workspace_bytes, dtype=torch.uint8, device="cuda:0") if workspace_bytes else None
+        glowmi.fc(a, w, None, y, m, k, n, wl.ACT_NONE, ws)
+        return glowmi.last_variant()
+
+    full = variant(need)
+    assert full.startswith("fc_tiles_f32") == taken, full
+    for too_small in (0, max(need - 1, 0)):
+        assert not variant(too_small).startswith(("fc_tiles_f32", "igemm_f32_p3")), too_small
+    if taken:
+        try:
+            glowmi.fc_noalloc(a, w, None, y, m, k, n)
+            assert glowmi.last_variant() == full
+        except glowmi.GlowmiError as e:
+            assert e.status == 3 and need > glowmi.fc_noalloc_max_scratch_bytes()
+    torch.cuda.synchronize()
