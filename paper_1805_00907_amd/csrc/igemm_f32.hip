@@ -693,7 +693,7 @@ Plan plan_f32(const Problem& p, bool allow_split) {
   const Plan rest = plan_f32_rest(p, allow_split);
   const int mode = knob_or(KNOB_F32_FC_TILES, 1);
   // only for calls that have the workspace they asked for (or the static buffer in its place)
-  if (!p.b_is_kn || mode == 0 || !allow_split) return rest;
+  if (!p.b_is_kn || mode == 0 || !allow_split || (mode == 1 && knob_or(KNOB_F32_P3, 1) == 0)) return rest;   // either switch
   Plan pl = rest;
   double us;
   if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? asking(p, pl) : rest;

@@ -80,3 +80,20 @@ def test_which_calls_take_the_kernel(shape, taken):
         except glowmi.GlowmiError as e:
             assert e.status == 3 and need > glowmi.fc_noalloc_max_scratch_bytes()
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("shape", [(150, 301, 77), (256, 4096, 4096)], ids=str)
+def test_switching_piece_contractions_off_covers_the_kernel(shape, knobs):
+    import torch
+    import gpu_util as G
+    import paper_1805_00907_amd as glowmi
+    m, k, n = shape
+    knobs.set("F32_P3", 0)
+    a, w = torch.randn((m, k), device="cuda:0"), torch.randn((k, n), device="cuda:0")
+    y = G.poison((m, n), torch.float32)
+    glowmi.fc(a, w, None, y, m, k, n, wl.ACT_NONE, G.workspace(glowmi.fc_workspace_bytes(m, k, n)))
+    assert glowmi.last_variant().startswith("igemm_f32_") and "p3" not in glowmi.last_variant(), glowmi.last_variant()
+    if glowmi.fc_workspace_bytes(m, k, n) <= glowmi.fc_noalloc_max_scratch_bytes():
+        glowmi.fc_noalloc(a, w, None, y, m, k, n)
+        assert glowmi.last_variant().startswith("igemm_f32_") and "p3" not in glowmi.last_variant(), glowmi.last_variant()
+    torch.cuda.synchronize()
