@@ -43,8 +43,10 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr unsigned OOBX = 0xFFFFFF00u;           // beyond any fp32 tensor this kernel accepts
-constexpr unsigned OOBW = 0x80000000u;           // beyond a filter plane (at most 2^29 bytes), also after adding an offset
+constexpr unsigned OOBW = 0x80000000u;           // beyond a filter plane (kPlaneReach), also after adding an offset
 constexpr unsigned PASTW = 0x40000000u;          // inside one or PASTW, which itself takes any offset past the plane
+constexpr long long kPlaneReach = 1LL << 30;     // a filter plane and what a chunk's steps may address behind its end
+constexpr int kChunkPieces = 32;                 // of eight channels: the widest chunk
 
 // R: filter extent, ST: stride, PXB: 64-pixel blocks, CHB: 32-channel blocks of a tile, W: wavefronts (8: a workgroup
 // owns a CU, 4: two share it).
@@ -76,6 +78,7 @@ struct Patch {
   static constexpr int WORDS_AT = 2 * PAIR > XCH ? 2 * PAIR : XCH;
   static constexpr int LDS = WORDS_AT + 64 + PX * 4;         // + the wavefronts' largest magnitudes, the pixels' output positions
   static_assert(KS >= 1 && PXB * CHB * KS == W && (NS * UNROLL) % DB == 0, "work of a wavefront");
+  static_assert(PIECES <= kChunkPieces, "kPlaneReach");
   static_assert(LDS <= (W == 8 ? 160 : 80) * 1024, "LDS of one CU");
   // A pixel's 16-byte pieces sit at piece ^ swizzle(key), key = the pixel's position at the tile's own pitch: 16
   // consecutive lanes have 16 consecutive keys, and (position, piece) then names 16 different bank groups (the host
@@ -720,6 +723,7 @@ int patch_f32_form(const Problem& p) {
   if (p.r != p.s || (p.r != 1 && p.r != 3) || p.stride_h != p.stride_w || (p.stride_h != 1 && p.stride_h != 2)) return -1;
   if (p.r == 1 && (p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h >= p.h || (p.ow - 1) * p.stride_w >= p.w_)) return -1;
   if (p.x_bytes > 0xF0000000u || p.w_bytes > (1u << 30) || (long long)p.M * p.k * 4 > 0xF0000000LL) return -1;   // 32-bit byte offsets
+  if (((long long)p.r * p.s * ((p.c + 7) / 8) + kChunkPieces) * 16 * p.k > kPlaneReach) return -1;   // a tap's channels are filled up to eight
   double cost = 0.0;
   const int form = cheapest_form(p, &cost);
   const int forced = knob_or(KNOB_F32_PATCH_TILE, -1);

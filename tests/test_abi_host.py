@@ -155,6 +155,20 @@ def test_tuning_knobs():
     assert glowmi.fc_workspace_bytes(64, 4096, 4096) == base
 
 
+def test_patch_kernel_plane_limit_counts_the_filled_channels():
+    """The patch kernel addresses a filter plane, its channels filled up to eight, with 30 bits.  A filter of 2^26 outputs over
+    one channel is 256 MB and its plane 1 GB: not a layer for it even when it is asked for; 2^20 outputs are."""
+    glowmi.tuning_reset()
+    glowmi.tuning_set("F32_PATCH", 2)
+    try:
+        for c, k, taken in ((1, 1 << 26, False), (8, 1 << 25, False), (1, 1 << 20, True), (8, 1 << 20, True)):
+            d = _desc(h=1, w=1, c=c, k=k, r=1, s=1, pad_t=0, pad_l=0, pad_b=0, pad_r=0)
+            planes = 2 * 16 * k + 4 * k                  # bytes the kernel asks for
+            assert (glowmi.conv2d_workspace_bytes(d) >= planes) == taken, (c, k)
+    finally:
+        glowmi.tuning_reset()
+
+
 def test_fc_noalloc_rejects_what_its_scratch_cannot_hold():
     cap = glowmi.fc_noalloc_max_scratch_bytes()
     assert cap == 8 << 20
