@@ -94,9 +94,8 @@ __global__ __launch_bounds__(CQ_THREADS, STEPS <= 4 ? 4 : 2) void conv_small_i8_
   Chunk at = gr.chunk.at(chunk, p);
 
   const bool ragged = p.cg % 16 != 0;
-  // chunks that would run past the end of a tensor are fetched from its last 16 bytes and shifted (only tiles that see
-  // the last pixel or the last filter)
-  const bool at_end = ragged && (tm * 32 + 32 > p.M - (p.r * p.ow + p.s) || tn * 32 + 32 >= p.kg);
+  // chunks that would run past the end of a tensor are fetched from its last 16 bytes and shifted (only tiles that see them)
+  const bool at_end = ragged && (tm * 32 + 32 > p.M - gr.chunk.end_pixels || tn * 32 + 32 > p.kg - gr.chunk.end_filters);
 
   v4i a[STEPS], b[STEPS];
   unsigned inside = 0, brief = 0;

@@ -74,10 +74,10 @@ __global__ __launch_bounds__(FS_THREADS, STEPS <= 4 ? 4 : 2) void fc_small_i8_ke
   for (int e = 0; e < 16; ++e) acc[e] = 0;
   int wacc = 0, xacc = 0;
   const bool need_xsum = p.w_off != 0;
-  // K % 16 != 0: a row's last run of activations is short (the weights past K are zeros), the tensor's last one is
-  // fetched from its last 16 bytes and shifted
+  // K % 16 != 0: a row's last run of activations is short (the weights past K are zeros), one that would
+  // run past the tensor's end is fetched from its last 16 bytes and shifted
   const bool ragged = K % 16 != 0;
-  const bool at_end = ragged && m0 + 32 >= M;
+  const bool at_end = ragged && (unsigned)(m0 + 32) * (unsigned)K + 15u > a_size;   // a run of this block starts in the last 15 bytes
 
   // Weight staging: load i of a lane covers row 32i + lane/2 of the slice, 16 columns at 16*(lane%2).
   // Fragment reads (per 16-lane group: columns 16*cb .. +15 of the strip, reduction half lhalf): lane i16

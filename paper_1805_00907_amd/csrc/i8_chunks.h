@@ -19,6 +19,7 @@ struct ChunkWalk {
   FastDiv div_cpt;
   int cpt, chunks;                       // chunks per tap, chunks of the reduction
   int dr, ds, dc;                        // one step = (dr * S + ds) taps and dc channels
+  int end_pixels, end_filters;           // the last output pixels, filters of a group, whose chunks may run past the end of a tensor
 #if defined(__HIPCC__)
   __device__ __forceinline__ Chunk at(int chunk, const Problem& p) const {
     Chunk k;
@@ -46,6 +47,22 @@ struct ChunkWalk {
 #endif
 };
 
+// A 16-byte load that starts in the last 15 bytes of a tensor runs past its end, and a dword of it that straddles the end is
+// lost with whatever codes lie in front of it.  The output pixels with taps in those bytes: all from the first output row that
+// reaches the input's last rows (of its last image, or the last images where one is smaller than that).
+inline int pixels_at_end(const Problem& p) {
+  const long long image = (long long)p.h * p.w_, near = (15 + (long long)p.c - 1) / p.c;   // input pixels in the last bytes
+  if (near > image) {
+    const long long images = (near + image - 1) / image;
+    return images < p.n ? (int)(images * p.oh * p.ow) : p.M;
+  }
+  const int first_row = p.h - (int)((near + p.w_ - 1) / p.w_);
+  const long long reach = (long long)first_row + p.pad_t - (p.r - 1);                      // oy * stride from which it is read
+  const long long oy = reach <= 0 ? 0 : (reach + p.stride_h - 1) / p.stride_h;
+  return oy < p.oh ? (int)(p.oh - oy) * p.ow : 0;
+}
+inline int filters_at_end(const Problem& p) { return (15 + p.Kgemm - 1) / p.Kgemm; }
+
 inline ChunkWalk make_chunk_walk(const Problem& p, int step) {
   ChunkWalk w;
   w.cpt = (p.cg + 15) / 16;
@@ -55,6 +72,8 @@ inline ChunkWalk make_chunk_walk(const Problem& p, int step) {
   w.dc = (step - taps * w.cpt) * 16;
   w.dr = taps / p.s;
   w.ds = taps - w.dr * p.s;
+  w.end_pixels = pixels_at_end(p);
+  w.end_filters = filters_at_end(p);
   return w;
 }
 

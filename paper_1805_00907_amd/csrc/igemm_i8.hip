@@ -158,9 +158,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M *
   const bool padded = walk.padded != 0;                 // some tap of some pixel falls on padding (or a row lies past M)
   const bool ragged = p.cg % 16 != 0;                   // a tap's last chunk has cg % 16 codes: the bytes of those
   const v4i short_mask = byte_mask(p.cg % 16);
-  // Chunks that run past the end of a tensor (its last pixel's, or last filter's, short chunk) are fetched from its last
-  // 16 bytes and shifted: only tiles that see that pixel or filter look for them.
-  const bool at_end = p.cg % 16 != 0 && (tm * BM + BM > p.M - (p.r * p.ow + p.s) || tn * BN + BN >= p.kg);
+  // Chunks that run past the end of a tensor (its last pixels', or last filters', short chunks) are fetched from its last
+  // 16 bytes and shifted: only tiles that see such pixels or filters look for them.
+  const bool at_end = p.cg % 16 != 0 && (tm * BM + BM > p.M - walk.chunk.end_pixels || tn * BN + BN > p.kg - walk.chunk.end_filters);
 
   struct Stage {                                        // one slab on its way to LDS
     v4i a[A_PASSES], b[B_KN ? B_UPT : B_PASSES];
