@@ -137,6 +137,7 @@ def library() -> ctypes.CDLL:
     L.glowmi_last_error.restype = ctypes.c_char_p
     L.glowmi_last_variant.restype = ctypes.c_char_p
     from . import _native as native      # linked against the library just loaded
+    native.structure_types(ConvDesc, QParam, SeqLayer)
     _native = native
     _lib = L
     return L

@@ -7,8 +7,8 @@
 //
 // For a tensor, the facts the C side cannot see are checked here, because a mismatch would become an out-of-bounds
 // access on the device: it must live on a GPU, be contiguous, have the element type the call reads and hold at least
-// as many elements as the descriptor asks for (ValueError).  An integer is taken as a raw device address, None as
-// NULL.  The functions return the glowmi_status; binding.py turns it into an exception.
+// as many elements as the descriptor asks for (ValueError); a structure must be of its own ctypes class (TypeError).  An
+// integer is taken as a raw device address, None as NULL.  The functions return the glowmi_status; binding.py turns it into an exception.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -36,6 +36,13 @@ long long integer(PyObject* o) {
 }
 
 int32_t int32_of(PyObject* o) { return (int32_t)integer(o); }
+
+// An extent that tensors are measured against: cut to 32 bits it would let a tensor pass that is too small.
+int32_t extent(PyObject* o, const char* what) {
+  const long long v = integer(o);
+  if (v != (int32_t)v) refuse(PyExc_ValueError, std::string(what) + ": " + std::to_string(v) + " is not a 32-bit integer");
+  return (int32_t)v;
+}
 
 float number(PyObject* o) {
   const double v = PyFloat_AsDouble(o);
@@ -103,7 +110,16 @@ hipStream_t stream_of(PyObject* o) {
   return static_cast<hipStream_t>(p);
 }
 
-// A ctypes structure (or array of them) as the C type it mirrors.
+// binding.py's ctypes classes, handed over when it loads this module (structure_types below).
+PyObject *g_conv_desc = nullptr, *g_qparam = nullptr, *g_seq_layer = nullptr;
+
+void check_type(PyObject* o, PyObject* type, const char* name) {
+  if (!type) refuse(PyExc_RuntimeError, "structure types not set");
+  if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type)))
+    refuse(PyExc_TypeError, std::string("expected a ") + name + ", got " + Py_TYPE(o)->tp_name);
+}
+
+// The memory of a ctypes structure (or array of them), as the C type it mirrors.
 template <typename T>
 struct View {
   Py_buffer buf;
@@ -121,7 +137,23 @@ struct View {
   const T* get() const { return static_cast<const T*>(buf.buf); }
 };
 
+PyObject* checked_desc(PyObject* o) {
+  check_type(o, g_conv_desc, "ConvDesc");
+  return o;
+}
+
+PyObject* checked_layers(PyObject* o) {              // a ctypes array of SeqLayer
+  PyObject* item = PyObject_GetAttrString(o, "_type_");
+  if (!item) PyErr_Clear();
+  const int ok = item && g_seq_layer && PyType_Check(item) ? PyObject_IsSubclass(item, g_seq_layer) : 0;
+  Py_XDECREF(item);
+  if (ok < 0) throw Refused{};
+  if (!ok) refuse(PyExc_TypeError, std::string("expected an array of SeqLayer (seq_layers), got ") + Py_TYPE(o)->tp_name);
+  return o;
+}
+
 glowmi_qparam qparam_of(PyObject* o) {
+  check_type(o, g_qparam, "QParam");
   View<glowmi_qparam> v(o);
   return *v.get();
 }
@@ -217,7 +249,7 @@ struct Ops {
 // planes are the general ones with None in their place --------------------------------------
 int conv2d_packed(PyObject* const* a) {     // x, w, w_planes, bias, y, desc, addend, act, workspace, stream
   const Bytes ws = bytes_of(a[8], "workspace");
-  View<glowmi_conv_desc> d(a[5]);
+  View<glowmi_conv_desc> d(checked_desc(a[5]));
   const Counts c(*d.get());
   const Bytes planes = bytes_of(a[2], "planes", a[2] == Py_None ? 0 : glowmi_conv2d_filter_planes_bytes(d.get()));
   const glowmi_chain chain = {in_f32(a[6], c.y, "addend"), {1.0f, 0}, (glowmi_act)int32_of(a[7])};
@@ -228,7 +260,7 @@ int conv2d_packed(PyObject* const* a) {     // x, w, w_planes, bias, y, desc, ad
 }
 
 int conv2d_pack_filter(PyObject* const* a) {   // w, desc, planes, stream
-  View<glowmi_conv_desc> d(a[1]);
+  View<glowmi_conv_desc> d(checked_desc(a[1]));
   const Counts c(*d.get());
   const Bytes planes = bytes_of(a[2], "planes");
   const float* w = in_f32(a[0], c.w, "w");
@@ -238,7 +270,7 @@ int conv2d_pack_filter(PyObject* const* a) {   // w, desc, planes, stream
 
 int conv2d_chainv(PyObject* const* a) {     // x, w, bias, y, desc, ops, workspace, stream
   const Bytes ws = bytes_of(a[6], "workspace");
-  View<glowmi_conv_desc> d(a[4]);
+  View<glowmi_conv_desc> d(checked_desc(a[4]));
   const Counts c(*d.get());
   const Ops ops(a[5], F32, c.y);
   const float *x = in_f32(a[0], c.x, "x"), *w = in_f32(a[1], c.w, "w"), *b = in_f32(a[2], d.get()->k, "bias");
@@ -249,7 +281,7 @@ int conv2d_chainv(PyObject* const* a) {     // x, w, bias, y, desc, ops, workspa
 
 int qconv2d_chain(PyObject* const* a) {     // x, xq, w, wq, bias, y, yq, desc, addend, addend_q, act, workspace, stream
   const Bytes ws = bytes_of(a[11], "workspace");
-  View<glowmi_conv_desc> d(a[7]);
+  View<glowmi_conv_desc> d(checked_desc(a[7]));
   const Counts c(*d.get());
   glowmi_chain chain = {in_i8(a[8], c.y, "addend"), {1.0f, 0}, (glowmi_act)int32_of(a[10])};
   if (a[9] != Py_None) chain.addend_q = qparam_of(a[9]);
@@ -263,7 +295,7 @@ int qconv2d_chain(PyObject* const* a) {     // x, xq, w, wq, bias, y, yq, desc, 
 
 int qconv2d_chainv(PyObject* const* a) {    // x, xq, w, wq, bias, y, yq, desc, ops, workspace, stream
   const Bytes ws = bytes_of(a[9], "workspace");
-  View<glowmi_conv_desc> d(a[7]);
+  View<glowmi_conv_desc> d(checked_desc(a[7]));
   const Counts c(*d.get());
   const Ops ops(a[8], I8, c.y);
   const int8_t *x = in_i8(a[0], c.x, "x"), *w = in_i8(a[2], c.w, "w");
@@ -276,7 +308,7 @@ int qconv2d_chainv(PyObject* const* a) {    // x, xq, w, wq, bias, y, yq, desc, 
 
 int fc_packed(PyObject* const* a) {         // a, w, w_planes, bias, y, M, K, N, act, workspace, stream
   const Bytes ws = bytes_of(a[9], "workspace");
-  const int32_t M = int32_of(a[5]), K = int32_of(a[6]), N = int32_of(a[7]);
+  const int32_t M = extent(a[5], "M"), K = extent(a[6], "K"), N = extent(a[7], "N");
   const Bytes planes = bytes_of(a[2], "planes", a[2] == Py_None ? 0 : glowmi_fc_filter_planes_bytes(K, N));
   const float *x = in_f32(a[0], (long long)M * K, "a"), *w = in_f32(a[1], (long long)K * N, "w"), *b = in_f32(a[3], N, "bias");
   float* y = out_f32(a[4], (long long)M * N, "y");
@@ -286,7 +318,7 @@ int fc_packed(PyObject* const* a) {         // a, w, w_planes, bias, y, M, K, N,
 }
 
 int fc_noalloc(PyObject* const* a) {        // a, w, bias, y, M, K, N, act, stream
-  const int32_t M = int32_of(a[4]), K = int32_of(a[5]), N = int32_of(a[6]);
+  const int32_t M = extent(a[4], "M"), K = extent(a[5], "K"), N = extent(a[6], "N");
   const float *x = in_f32(a[0], (long long)M * K, "a"), *w = in_f32(a[1], (long long)K * N, "w"), *b = in_f32(a[2], N, "bias");
   float* y = out_f32(a[3], (long long)M * N, "y");
   const glowmi_act act = (glowmi_act)int32_of(a[7]);
@@ -295,7 +327,7 @@ int fc_noalloc(PyObject* const* a) {        // a, w, bias, y, M, K, N, act, stre
 }
 
 int fc_pack_filter(PyObject* const* a) {    // w, K, N, planes, stream
-  const int32_t K = int32_of(a[1]), N = int32_of(a[2]);
+  const int32_t K = extent(a[1], "K"), N = extent(a[2], "N");
   const Bytes planes = bytes_of(a[3], "planes");
   const float* w = in_f32(a[0], (long long)K * N, "w");
   const hipStream_t s = stream_of(a[4]);
@@ -304,7 +336,7 @@ int fc_pack_filter(PyObject* const* a) {    // w, K, N, planes, stream
 
 int qfc(PyObject* const* a) {               // a, aq, w, wq, bias, y, yq, M, K, N, act, workspace, stream
   const Bytes ws = bytes_of(a[11], "workspace");
-  const int32_t M = int32_of(a[7]), K = int32_of(a[8]), N = int32_of(a[9]);
+  const int32_t M = extent(a[7], "M"), K = extent(a[8], "K"), N = extent(a[9], "N");
   const int8_t *x = in_i8(a[0], (long long)M * K, "a"), *w = in_i8(a[2], (long long)K * N, "w");
   const int32_t* b = in_i32(a[4], N, "bias");
   int8_t* y = out_i8(a[5], (long long)M * N, "y");
@@ -343,7 +375,7 @@ int rescale(PyObject* const* a) {           // q_in, from_q, q_out, to_q, count,
 
 int seq_conv2d(PyObject* const* a) {        // x, layers, y, arena, stream
   const Bytes arena = bytes_of(a[3], "workspace");
-  View<glowmi_seq_layer> l(a[1]);
+  View<glowmi_seq_layer> l(checked_layers(a[1]));
   const Counts first(l.get()[0].desc), last(l.get()[l.count - 1].desc);
   const float* x = in_f32(a[0], first.x, "x");
   float* y = out_f32(a[2], last.y, "y");
@@ -353,7 +385,7 @@ int seq_conv2d(PyObject* const* a) {        // x, layers, y, arena, stream
 
 int seq_qconv2d(PyObject* const* a) {       // x, xq, layers, y, arena, stream
   const Bytes arena = bytes_of(a[4], "workspace");
-  View<glowmi_seq_layer> l(a[2]);
+  View<glowmi_seq_layer> l(checked_layers(a[2]));
   const Counts first(l.get()[0].desc), last(l.get()[l.count - 1].desc);
   const int8_t* x = in_i8(a[0], first.x, "x");
   int8_t* y = out_i8(a[3], last.y, "y");
@@ -382,6 +414,20 @@ PyObject* tensor_address(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
 }
 
+// Called once by binding.py: ConvDesc, QParam, SeqLayer.
+PyObject* structure_types(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 3 || !PyType_Check(a[0]) || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
+    PyErr_SetString(PyExc_TypeError, "structure_types takes three classes");
+    return nullptr;
+  }
+  PyObject** const held[3] = {&g_conv_desc, &g_qparam, &g_seq_layer};
+  for (int i = 0; i < 3; ++i) {
+    Py_INCREF(a[i]);
+    Py_XSETREF(*held[i], a[i]);
+  }
+  Py_RETURN_NONE;
+}
+
 template <int (*F)(PyObject* const*), int N>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
   try {
@@ -400,6 +446,7 @@ PyMethodDef methods[] = {
     ENTRY(conv2d_packed, 10), ENTRY(conv2d_pack_filter, 4), ENTRY(conv2d_chainv, 8),
     ENTRY(qconv2d_chain, 13), ENTRY(qconv2d_chainv, 11), ENTRY(fc_packed, 11), ENTRY(fc_noalloc, 9), ENTRY(fc_pack_filter, 5),
     ENTRY(qfc, 13), ENTRY(quantize, 5), ENTRY(dequantize, 5), ENTRY(rescale, 6), ENTRY(seq_conv2d, 5), ENTRY(seq_qconv2d, 6),
+    {"structure_types", (PyCFunction)(void (*)(void))structure_types, METH_FASTCALL, nullptr},
     {"address", (PyCFunction)(void (*)(void))tensor_address, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 

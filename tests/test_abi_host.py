@@ -191,6 +191,31 @@ def test_binding_checks_tensors_before_the_call():
         glowmi.conv2d(x, FAKE, None, FAKE, d, stream=0)
 
 
+def test_binding_takes_each_structure_only_as_what_it_is():
+    """A structure of another type is refused, also where its size would fit, and so is an extent of more than 32 bits."""
+    d, q = _desc(), glowmi.QParam(0.1, 0)
+    layers = glowmi.seq_layers([(d, FAKE, None, 0, False)])
+    for bad in (d, layers, b"12345678", (0.1, 0), None):
+        with pytest.raises(TypeError):
+            glowmi.qconv2d(FAKE, bad, FAKE, q, None, FAKE, q, d, stream=0)
+        with pytest.raises(TypeError):
+            glowmi.quantize(FAKE, FAKE, bad, 16, stream=0)
+    for bad in (q, layers, bytes(56), bytearray(56 * 2), None):
+        with pytest.raises(TypeError):
+            glowmi.conv2d(FAKE, FAKE, None, FAKE, bad, stream=0)
+    for bad in (d, (glowmi.QParam * 16)(), bytes(ctypes.sizeof(glowmi.binding.SeqLayer)), None):
+        with pytest.raises(TypeError):
+            glowmi.seq_conv2d(FAKE, bad, FAKE, None, stream=0)
+    with pytest.raises((ValueError, OverflowError)):
+        glowmi.fc(FAKE, FAKE, None, FAKE, (1 << 32) + 4, 4, 4, stream=0)
+
+    class Desc(glowmi.ConvDesc):                     # what derives from a structure is one
+        pass
+    with pytest.raises(glowmi.GlowmiError) as e:
+        glowmi.conv2d(None, FAKE, None, FAKE, Desc(*(getattr(d, f) for f, _ in d._fields_)), stream=0)
+    assert e.value.status == 1
+
+
 def test_requant_params_match_oracle():
     rng = np.random.default_rng(6)
     for _ in range(2000):
