@@ -21,9 +21,9 @@
  *    call still computes the same result to the same accuracy; with at least
  *    glowmi_*_workspace_bytes() bytes the library may split the reduction dimension over more
  *    workgroups (small-M layers) and, for large fp32 contractions, repack both operands there (two
- *    fp16 pieces per value, 4 bytes per element: see "Results" below), which is faster.  A workspace
- *    smaller than that figure is not used at all.  The contents on entry do not matter and are
- *    undefined on return.  Two calls that share a workspace must be ordered on one stream.
+ *    fp16 pieces per value, 4 bytes per element: see "Results" below), which is faster.  That
+ *    figure is always enough; some convolutions use less of it than it names, and a workspace that holds less
+ *    than a call uses is not touched.  The contents on entry do not matter and are undefined on return.  Two calls that share a workspace must be ordered on one stream.
  *  - Arguments are validated on the host before anything is launched.  On any error nothing is
  *    launched, y is untouched, the status says why and glowmi_last_error() gives a sentence.
  *  - Every tensor must hold fewer than 2^31 elements (GLOWMI_ERR_UNSUPPORTED otherwise).
@@ -127,8 +127,8 @@ size_t glowmi_fc_workspace_bytes(int32_t M, int32_t K, int32_t N);
  * sums go to a buffer that is part of the library image (a static array in device memory of
  * glowmi_fc_noalloc_max_scratch_bytes() = 8 MiB, one copy per GPU the library is used on, held until
  * the process ends).  The call allocates nothing and calls no allocating routine.
- *   - A shape whose partial sums need more than that is rejected with GLOWMI_ERR_UNSUPPORTED and a message;
- *     nothing is launched.
+ *   - A shape whose partial sums need more than that (as the fp32 matrix-core kernel splits it) is rejected with
+ *     GLOWMI_ERR_UNSUPPORTED and a message; nothing is launched.
  *   - Every call on one GPU shares that GPU's buffer: calls must be ordered on one stream (or otherwise
  *     serialised); calls that overlap on one GPU race.  Nothing in the buffer needs to start at zero
  *     (every partial sum is written before it is read), so its stale contents are harmless.

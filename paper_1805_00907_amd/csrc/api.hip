@@ -262,6 +262,13 @@ size_t split_bytes(const glowmi::Plan& pl, const glowmi::Problem& p) {
   return pl.pack_bytes + (pl.split_k > 1 ? (size_t)pl.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
 }
 
+// What the convolution queries name: room for the kernel planned or the one it stands in for.  A call is content with what its
+// kernel uses.
+size_t query_bytes(const glowmi::Plan& pl, const glowmi::Problem& p) {
+  const size_t need = split_bytes(pl, p);
+  return need > pl.ask ? need : pl.ask;
+}
+
 // Plan once per call: with what the planner wants from a workspace (repacked operands, a split reduction)
 // when the caller's workspace can hold it, without either otherwise.  Sets p.planes and p.partial accordingly.
 template <typename PlanFn>
@@ -468,7 +475,7 @@ size_t glowmi_conv2d_workspace_bytes(const glowmi_conv_desc* d) {
   glowmi::Problem p;
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;   // the planner sees what the call sees
-  return split_bytes(glowmi::plan_f32(p, true), p);
+  return query_bytes(glowmi::plan_f32(p, true), p);
 }
 
 glowmi_status glowmi_conv2d(const float* x, const float* w, const float* bias, float* y,
@@ -531,7 +538,7 @@ size_t glowmi_conv2d_packed_workspace_bytes(const glowmi_conv_desc* d) {
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;
   if (conv_planes_bytes(d, geo) > 0) p.w_packed = &kPlanesGiven;
-  return split_bytes(glowmi::plan_f32(p, true), p);
+  return query_bytes(glowmi::plan_f32(p, true), p);
 }
 
 glowmi_status glowmi_conv2d_packed(const float* x, const float* w, const void* w_planes, const float* bias,
@@ -588,7 +595,7 @@ glowmi_status glowmi_fc_noalloc(const float* a, const float* w, const float* bia
   if (st != GLOWMI_OK) return st;
   p.allow_pack = 0;     // the static buffer is for partial sums only: operands are never repacked into it
   const glowmi::Plan plan = glowmi::plan_f32(p, true);      // otherwise the plan glowmi_fc takes with a full workspace
-  const size_t need = split_bytes(plan, p);
+  const size_t need = query_bytes(plan, p);                 // the limit is that of the kernel that keeps fp32 operands
   if (need > kScratchBytes)
     return fail(GLOWMI_ERR_UNSUPPORTED,
                 "FullyConnected %d x %d x %d needs %zu bytes of split-reduction scratch, more than the %zu the "
@@ -905,7 +912,7 @@ size_t glowmi_conv2d_chainv_workspace_bytes(const glowmi_conv_desc* d, const glo
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;
   describe_chain(p, ops, n_ops, false);
-  return split_bytes(glowmi::plan_f32(p, true), p);
+  return query_bytes(glowmi::plan_f32(p, true), p);
 }
 
 glowmi_status glowmi_conv2d_chainv(const float* x, const float* w, const float* bias, float* y,

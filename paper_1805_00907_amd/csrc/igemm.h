@@ -148,6 +148,7 @@ struct Plan {
   int split_k;
   int slabs_per_split;
   size_t pack_bytes = 0;  // workspace bytes for repacked operands, ahead of the partial sums (KERNEL_P3)
+  size_t ask = 0;       // what a kernel of the layer's that this one stands in for would want, where that is more
 };
 Plan plan_f32(const Problem& p, bool allow_split);
 Plan plan_i8(const Problem& p, bool allow_split);

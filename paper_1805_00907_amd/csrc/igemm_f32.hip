@@ -713,9 +713,7 @@ Plan plan_f32(const Problem& p, bool allow_split) {
     const double padded = 2e-9 * ((p.M + 127) / 128 * 128) * ((p.k + 127) / 128 * 128) * (double)p.Kgemm;
     if (us > 22.0 + 3.3 * padded + 0.45e-6 * (double)p.w_bytes) return rest;
   }
-  // the workspace to ask for stays what the other kernel asks for
-  const size_t mine = wanted_bytes(p, pl);
-  if (mine < ask) pl.pack_bytes = (ask - mine) / 256 * 256;
+  pl.ask = ask;
   return asking(p, pl);
 }
 
@@ -760,15 +758,10 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
       pl.kernel = KERNEL_PATCH;
       pl.tile = form;
       pl.pack_bytes = patch_f32_pack_bytes(p);
-      // the workspace to ask for stays what the kernel asks for that would run otherwise: a buffer of that size serves either
-      size_t ask = 0;
-      if (k3c64) ask = k3c64_f32_pack_bytes(p);
-      else if (k3) ask = k3_f32_pack_bytes(p);
-      else if (p3_f32_applicable(p)) {
-        const Plan p3 = plan_p3_f32(p);
-        ask = p3.pack_bytes + (p3.split_k > 1 ? (size_t)p3.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
-      }
-      if (ask > pl.pack_bytes) pl.pack_bytes = ask;
+      // the workspace queries name what the kernel wants that would run otherwise: a buffer of that size serves either
+      if (k3c64) pl.ask = k3c64_f32_pack_bytes(p);
+      else if (k3) pl.ask = k3_f32_pack_bytes(p);
+      else if (p3_f32_applicable(p)) pl.ask = wanted_bytes(p, plan_p3_f32(p));
       return pl;
     }
     // large contractions with a workspace to repack the operands into: the kernel over fp16 planes

@@ -66,10 +66,11 @@ glowmi_status plan_sequence(const glowmi_seq_layer* layers, int32_t n, size_t el
       if (first.n != d.n || first.h != oh || first.w != ow || first.c != d.k)
         return fail(GLOWMI_ERR_SHAPE, "layer %d adds the sequence input, whose shape differs from the layer's output", i);
     }
-    const size_t ws = quantized ? glowmi_qconv2d_workspace_bytes(&d) : glowmi_conv2d_workspace_bytes(&d);
-    plan->workspace = std::max(plan->workspace, round_up(ws));
     const size_t cut = quantized ? 0 : round_up(glowmi::conv2d_cut_bytes(&d));
-    if (cut > 0) {
+    if (cut == 0) {
+      const size_t ws = quantized ? glowmi_qconv2d_workspace_bytes(&d) : glowmi_conv2d_workspace_bytes(&d);
+      plan->workspace = std::max(plan->workspace, round_up(ws));
+    } else {                        // its place in the region of cut filters is all the workspace it uses
       if (group < 0 || jobs == glowmi::kCutJobs || used + cut > kCutGroupBytes) {
         group = i;
         jobs = 0;
@@ -101,6 +102,7 @@ glowmi_status run_sequence(const void* x, glowmi_qparam xq, const glowmi_seq_lay
   char* base = static_cast<char*>(arena);
   char* region[2] = {base, base + plan.region[0]};
   void* ws = plan.workspace ? base + plan.region[0] + plan.region[1] : nullptr;
+  char* cuts = base + plan.region[0] + plan.region[1] + plan.workspace;
   std::vector<glowmi::PreparedCall> calls((size_t)n);
   const void* in = x;
   glowmi_qparam in_q = xq;
@@ -115,15 +117,17 @@ glowmi_status run_sequence(const void* x, glowmi_qparam xq, const glowmi_seq_lay
                                          layers[i].wq, static_cast<const int32_t*>(layers[i].bias),
                                          static_cast<int8_t*>(out), layers[i].yq, &layers[i].desc, &chain, ws,
                                          plan.workspace, &calls[(size_t)i]);
-    else
+    else {
+      const size_t cut = plan.cut_bytes[(size_t)i];
       st = glowmi::prepare_conv2d_chain(static_cast<const float*>(in), static_cast<const float*>(layers[i].w),
                                         static_cast<const float*>(layers[i].bias), static_cast<float*>(out),
-                                        &layers[i].desc, &chain, ws, plan.workspace, &calls[(size_t)i]);
+                                        &layers[i].desc, &chain, cut ? cuts + plan.cut_at[(size_t)i] : ws,
+                                        cut ? cut : plan.workspace, &calls[(size_t)i]);
+    }
     if (st != GLOWMI_OK) return st;          // nothing has been launched
     in = out;
     in_q = layers[i].yq;
   }
-  char* cuts = base + plan.region[0] + plan.region[1] + plan.workspace;
   for (int32_t i = 0; i < n; ++i) {
     if (plan.cut_before[(size_t)i] == i) {              // a group of filters starts here
       glowmi::PreparedCall* group[glowmi::kCutJobs];
@@ -132,7 +136,6 @@ glowmi_status run_sequence(const void* x, glowmi_qparam xq, const glowmi_seq_lay
         if (plan.cut_bytes[(size_t)l] == 0) continue;
         if (plan.cut_before[(size_t)l] != i) break;
         if (calls[(size_t)l].plan.kernel != glowmi::KERNEL_PATCH) continue;
-        calls[(size_t)l].p.planes = cuts + plan.cut_at[(size_t)l];
         group[jobs++] = &calls[(size_t)l];
       }
       if (jobs > 0 && (st = glowmi::run_cuts(group, jobs, stream)) != GLOWMI_OK) return st;

@@ -394,6 +394,15 @@ def test_workspace_queries_are_pure():
     assert glowmi.fc_workspace_bytes(128, 4096, 4096) < 4 * (128 * 4096 + 4096 * 4096)
 
 
+def test_sequence_arena_holds_nothing_twice():
+    """Two 3x3 layers on the patch kernel: the activation between them and each filter's planes (4 bytes a weight, and a word
+    per channel), nothing for a kernel that neither of them runs on."""
+    up = lambda v: (v + 255) // 256 * 256
+    conv = lambda hw, st: glowmi.ConvDesc(16, hw, hw, 128, 128, 3, 3, st, st, 1, 1, 1, 1, 1)
+    arr = glowmi.seq_layers([(conv(56, 2), FAKE, None, 0, False), (conv(28, 1), FAKE, None, 0, False)])
+    assert glowmi.seq_arena_bytes(arr, False) == 16 * 28 * 28 * 128 * 4 + 2 * up(4 * 128 * 9 * 128 + 4 * 128)
+
+
 def test_packed_filter_queries_and_errors():
     """Filters transformed ahead of time: sizes, and every refusal happens before a launch."""
     up = lambda v: (v + 255) // 256 * 256

@@ -149,6 +149,30 @@ def test_long_reductions_are_summed_in_short_runs(r, st, tile, knobs):
     assert np.linalg.norm(got - ref) <= bound * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("n,hw,c,k,st", [(16, 56, 128, 128, 2), (32, 7, 512, 512, 1), (8, 28, 128, 128, 1)])
+def test_a_workspace_that_holds_the_cut_filter_is_enough(n, hw, c, k, st):
+    """The query names more where the contraction over planes would run otherwise; a byte less than the cut filter and the
+    workspace is left alone."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    desc = glowmi.ConvDesc(n, hw, hw, c, k, 3, 3, st, st, 1, 1, 1, 1, 1)
+    x, w = torch.randn((n, hw, hw, c), device="cuda:0"), torch.randn((k, 3, 3, c), device="cuda:0")
+    oh, ow = glowmi.conv_out_shape(desc)
+    need = 4 * k * 9 * c + 4 * k                         # (a multiple of 256 here)
+    assert glowmi.conv2d_workspace_bytes(desc) >= need
+    out = []
+    for given in (glowmi.conv2d_workspace_bytes(desc), need, need - 1):
+        y = G.poison((n, oh, ow, k), torch.float32)
+        ws = torch.full((given,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        glowmi.conv2d(x, w, None, y, desc, wl.ACT_NONE, ws)
+        torch.cuda.synchronize()
+        out.append((glowmi.last_variant(), y, bool((ws == 0x5A).all())))
+    assert out[0][0].startswith("conv_patch_f32") and out[1][0] == out[0][0], (out[0][0], out[1][0])
+    assert torch.equal(out[0][1], out[1][1])
+    assert not out[2][0].startswith("conv_patch_f32") and out[2][2]
+
+
 @pytest.mark.parametrize("layers", [1, 8, 10])
 def test_sequence_cuts_filters_ahead_in_groups(layers, knobs):
     """Layers of a sequence have their filters cut up to eight at a time: the same results as layer by layer."""
