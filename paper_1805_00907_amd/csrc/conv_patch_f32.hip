@@ -141,10 +141,9 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
   const unsigned b_base = ch < p.k ? (unsigned)(2 * kset + lhalf) * k16 + 16u * (unsigned)ch : OOBW;
   const unsigned tap_step = (unsigned)c8 * k16, chunk_step = (unsigned)(T::CC >> 3) * k16;
   v4i fb[T::DB][2];                                     // [step in flight][plane]
-  auto load_b = [&](int slot, int chunk, int st) {      // slot, st: compile-time
-    const unsigned at = chunk < tl.chunks ? (unsigned)chunk * chunk_step + (unsigned)(st / T::MS) * tap_step +
-                                                (unsigned)(st % T::MS * 2 * T::KS) * k16
-                                          : PASTW;
+  auto chunk_at = [&](int chunk) { return chunk < tl.chunks ? (unsigned)chunk * chunk_step : PASTW; };
+  auto load_b = [&](int slot, unsigned from, int st) {  // slot, st: compile-time; from: chunk_at of the chunk
+    const unsigned at = from + (unsigned)(st / T::MS) * tap_step + (unsigned)(st % T::MS * 2 * T::KS) * k16;
     fb[slot][0] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w1, b_base + at, 0, 0));
     fb[slot][1] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w2, b_base + at, 0, 0));
   };
@@ -229,7 +228,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 #pragma unroll
   for (int j = 1; j <= T::SETS; ++j) load_raw(pre[j % T::SETS], j);
 #pragma unroll
-  for (int d = 0; d < T::DB; ++d) load_b(d, d / T::NS, d % T::NS);
+  for (int d = 0; d < T::DB; ++d) load_b(d, chunk_at(d / T::NS), d % T::NS);
 
   // ---- what the epilogue needs, fetched now: the channel's bias, the filter's scale, where the pixels lie in the output
   const float* __restrict__ bias = static_cast<const float*>(p.bias);
@@ -317,6 +316,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
         }
     };
     if (U % T::FOLD == 0 && chunk % T::FOLD == 0) fold();   // uniform
+    const unsigned from[3] = {(unsigned)chunk * chunk_step, chunk_at(chunk + 1), chunk_at(chunk + 2)};   // (DB <= 2 NS)
     __syncthreads();                                    // this chunk's planes and the next one's magnitudes are there
     read_a(0);
     if (se_x < se_acc) {                                // uniform: larger values than any chunk before
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
 #pragma unroll
       for (int b = 0; b < 2; ++b) acc_lo[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[cur][b][1], b1, acc_lo[b], 0, 0, 0);
       const int ahead = st + T::DB;                     // DB <= 2 NS
-      load_b(slot, chunk + ahead / T::NS, ahead % T::NS);
+      load_b(slot, from[ahead / T::NS], ahead % T::NS);
       constexpr int LAST_CUT = T::CUT_FROM + T::CUT_STEPS - 1;
       const bool cutting = st >= T::CUT_FROM && st <= LAST_CUT;
       if (T::CUT_FROM == 1 && st == 0) take_scale(parity ^ 1);
@@ -640,7 +640,7 @@ hipError_t launch_patch(const Problem& p, hipStream_t stream, const char** varia
 
 // ---- forms: pixels x channels of a tile, wavefronts.  Eight wavefronts per tile where the tiles do not fill the machine
 // twice, four (and two workgroups per CU, one's start and end behind the other's middle) where they do.
-constexpr int FORMS = 7;
+constexpr int FORMS = 6;
 
 template <int R, int ST, bool ADD>
 hipError_t launch_patch_form(const Problem& p, int form, hipStream_t stream, const char** variant) {
@@ -652,9 +652,8 @@ hipError_t launch_patch_form(const Problem& p, int form, hipStream_t stream, con
       case 0: return launch_patch<R, ST, 1, 2, 8, ADD>(p, stream, variant);
       case 2: return launch_patch<R, ST, 1, 1, 8, ADD>(p, stream, variant);
       case 3: return launch_patch<R, ST, 1, 2, 4, ADD>(p, stream, variant);
-      case 4: return launch_patch<R, ST, 2, 2, 4, ADD>(p, stream, variant);
-      case 5: return launch_patch<R, ST, 1, 4, 4, ADD>(p, stream, variant);
-      case 6: return launch_patch<R, ST, 2, 1, 4, ADD>(p, stream, variant);
+      case 4: return launch_patch<R, ST, 1, 4, 4, ADD>(p, stream, variant);
+      case 5: return launch_patch<R, ST, 2, 1, 4, ADD>(p, stream, variant);
     }
   }
   return hipErrorInvalidValue;
@@ -668,19 +667,21 @@ hipError_t launch_patch_shape(const Problem& p, int form, hipStream_t stream, co
                          : launch_patch_form<3, 2, ADD>(p, form, stream, variant);
 }
 
-// What a form costs, in microseconds, fitted to 61 layers of 0.05 to 20 GFLOP in all forms (median error 4 %; choosing by
-// it costs 0.6 % over the best form of each layer): 4.3 for the two launches, 1 per megabyte of filter to cut, 0.1 per
-// megabyte of input and output, and per round of workgroups a start and end and so much per chunk of channels.  A
-// four-wavefront workgroup that has a CU to itself takes 0.7 of what two take that share it.
+// What a form costs, in microseconds, fitted to 78 layers of 0.05 to 59 GFLOP in all forms (median error 4 %; choosing by it
+// costs 0.15 % over the best form of each layer, 5 % at most): 4.3 for the two launches, 1 per megabyte of filter to cut, 0.1
+// per megabyte of input and output, and per round of workgroups a start and end and so much per chunk of channels.  A
+// four-wavefront workgroup that has a CU to itself takes 0.7 of what two take that share it.  Above 20 GFLOP the estimates are
+// low, up to 25 % (512 -> 512 on 28x28 at batch 16: 142, measured 188), for all forms alike: nothing but the choice among forms
+// goes by them there.  (A tile of 128 pixels x 64 channels lost its place to 64 x 64 with the second accumulator set, for which
+// it has no registers: 64 -> 64 on 112x112 at batch 16 60 -> 71 us, 64 x 64 63.)
 struct FormCost { int px, bn, waves, cc1, cc3; float round1, chunk1, round3, chunk3; };
 constexpr FormCost kForms[FORMS] = {
-    {64, 64, 8, 128, 64, 3.1f, 0.84f, 2.7f, 2.55f},
-    {64, 128, 8, 0, 32, 0.f, 0.f, 3.0f, 1.94f},
-    {64, 32, 8, 256, 128, 3.8f, 1.49f, 3.3f, 3.25f},
-    {64, 64, 4, 64, 32, 2.4f, 0.89f, 2.9f, 2.18f},
-    {128, 64, 4, 64, 32, 3.2f, 1.70f, 4.6f, 3.83f},
-    {64, 128, 4, 64, 32, 2.5f, 1.21f, 4.1f, 3.33f},
-    {128, 32, 4, 64, 32, 3.0f, 1.41f, 4.1f, 2.44f},
+    {64, 64, 8, 128, 64, 3.48f, 0.97f, 3.23f, 2.51f},
+    {64, 128, 8, 0, 32, 0.f, 0.f, 3.51f, 2.02f},
+    {64, 32, 8, 256, 128, 4.02f, 1.64f, 3.97f, 2.95f},
+    {64, 64, 4, 64, 32, 2.57f, 1.09f, 3.79f, 2.21f},
+    {64, 128, 4, 64, 32, 2.95f, 1.36f, 4.82f, 3.54f},
+    {128, 32, 4, 64, 32, 3.10f, 1.62f, 4.87f, 2.53f},
 };
 
 // The cheapest form for the layer and its cost; a 3x3 stride-2 layer has one form (two of its patches do not fit a CU; a
@@ -726,7 +727,7 @@ int patch_f32_form(const Problem& p) {
   if (((long long)p.r * p.s * ((p.c + 7) / 8) + kChunkPieces) * 16 * p.k > kPlaneReach) return -1;   // a tap's channels are filled up to eight
   double cost = 0.0;
   const int form = cheapest_form(p, &cost);
-  const int forced = knob_or(KNOB_F32_PATCH_TILE, -1);
+  const int knob_form = knob_or(KNOB_F32_PATCH_TILE, -1), forced = knob_form < FORMS ? knob_form : -1;   // (no such form: the rule's)
   if (mode == 2) return forced >= 0 ? forced : form;
   // Against what the layer would take elsewhere: on the fp32 matrix cores 8 us (6 for pointwise) and 50 or 75 TFLOP/s, or what
   // its tensors take at 3 TB/s; on the one-launch kernel for few pixels 3.5 us and 32 TFLOP/s.  The margin covers both
