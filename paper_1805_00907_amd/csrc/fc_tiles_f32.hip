@@ -13,10 +13,10 @@
 //   - a wavefront scales either operand by the largest magnitude it has seen; values that outgrow it scale the sums down;
 //   - every eight chunks the accumulators of the h1 h1' products are folded into sums in LDS.  One chain of rounded additions
 //     per output and wavefront was less exact than the contraction over planes at deep reductions (256x9216x4096 2.4e-7 of
-//     the result's norm against 1.7e-7, now 1.4e-7);
+//     the result's norm against 1.7e-7, now 1.4e-7); it costs 4 to 7 % from 2000 indices on, most of it LDS traffic;
 //   - at the end the wavefronts exchange their sums through LDS and finish an eighth of the tile each.
 // Bound by the vector unit (the cuts: 32 values a lane and chunk) and the 64 bytes a clock of a CU's memory path, closely
-// followed by the matrix cores.  Measured: 256x4096x4096 47 us, 1000x1024x512 12.6, 150x301x77 6.5 (84, 22, 13 on the kernels
+// followed by the matrix cores.  Measured: 256x4096x4096 52 us, 1000x1024x512 12.3, 150x301x77 6.5 (82, 21, 13 on the kernels
 // over planes and on the fp32 matrix cores).
 // Few tiles: the reduction is also split over the grid, and the partial sums go through the workspace.
 #include <hip/hip_runtime.h>
@@ -198,13 +198,24 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
   // Sums of short runs round less: every FT_FOLD chunks acc goes into LDS of the wavefront's own, at the scale of that moment.
   constexpr int NQ = MB * 8;                             // quads of registers of the tile
   v4f* const kept = reinterpret_cast<v4f*>(lds + FT_WAVES * 2 * PLANE) + wave * NQ * 64 + lane;
+  // (Every sixteen: 3 % faster, but 6 to 9 % further from 64-bit sums than the contraction over planes at 1500 to 2200
+  // indices.  Left to the LDS to add, ds_add_f32: three times the time of the call.)
   int kept_se = 0, since_fold = 0;
   bool any_kept = false;                                 // uniform, as the two above
-  auto kept_quad = [&](int q) {                          // at the present scale
-    v4f v = kept[q * 64];
+  auto add_kept = [&] {                                  // brought to the present scale
+    const int by = sx.se + sw.se - kept_se;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = __builtin_ldexpf(v[e], sx.se + sw.se - kept_se);
-    return v;
+    for (int q = 0; q < NQ; q += 4) {                    // four reads in flight
+      v4f v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = kept[(q + i) * 64];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[(q + i) / 8][(q + i) / 4 % 2][(q + i) % 4 * 4 + e] += __builtin_ldexpf(v[i][e], by);
+    }
   };
 
   int chunk = first + wave;
@@ -213,12 +224,13 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
   // in pairs; the one after the last is all zeros
   do {
     if (since_fold == FT_FOLD) {
+      if (any_kept) add_kept();
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        v4f v = any_kept ? kept_quad(q) : v4f{0.f, 0.f, 0.f, 0.f};
+        v4f v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          v[e] += acc[q / 8][q / 4 % 2][q % 4 * 4 + e];
+          v[e] = acc[q / 8][q / 4 % 2][q % 4 * 4 + e];
           acc[q / 8][q / 4 % 2][q % 4 * 4 + e] = 0.f;
         }
         kept[q * 64] = v;
@@ -236,14 +248,7 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
   // ---- the wavefronts swap their sums: each finishes OQ of the tile's NQ quads of registers.  Register e of a block is row
   // (e/4)*8 + 4*lhalf + e%4 of its 32, column lane % 32.
   constexpr int OQ = NQ / FT_WAVES;
-  if (any_kept) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const v4f v = kept_quad(q);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[q / 8][q / 4 % 2][q % 4 * 4 + e] += v[e];
-    }
-  }
+  if (any_kept) add_kept();
   const ScaleBack sb = scale_back_of(sx.se, sw.se, finite);
   v4f* xch = reinterpret_cast<v4f*>(lds);
   float res[OQ][4];
