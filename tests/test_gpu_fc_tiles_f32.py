@@ -1,5 +1,6 @@
 """fp32 FullyConnected cut on the way to the matrix cores (fc_tiles_f32) against the CPU oracle: ragged rows, columns and
-reductions, fewer chunks than wavefronts, split reductions, values that outgrow a wavefront's scale."""
+reductions, fewer chunks than wavefronts, split reductions, values that outgrow a wavefront's scale (before and after sums have
+been put aside), and what the kernels over fp16 pieces promise about accuracy, scales, zeros and non-finite values."""
 import numpy as np
 import pytest
 
@@ -97,3 +98,116 @@ def test_switching_piece_contractions_off_covers_the_kernel(shape, knobs):
         glowmi.fc_noalloc(a, w, None, y, m, k, n)
         assert glowmi.last_variant().startswith("igemm_f32_") and "p3" not in glowmi.last_variant(), glowmi.last_variant()
     torch.cuda.synchronize()
+
+
+# rows of a tile; sizes: one pass of the wavefronts, and deep enough that each puts its sums aside twice and more
+FORMS = [(rows, m, k, n) for rows in (32, 64) for m, k, n in ((70, 133, 97), (33, 2500, 70))]
+
+
+def _operands(seed, m, k, n):
+    rng = np.random.default_rng(seed)
+    a = rng.uniform(-1, 1, size=(m, k)).astype(np.float32)
+    w = (rng.standard_normal(size=(k, n)) / np.sqrt(k)).astype(np.float32)
+    return a, w, rng.uniform(-0.1, 0.1, size=(n,)).astype(np.float32), rng
+
+
+def _run(rows, a, w, b, knobs):
+    import gpu_util as G
+    knobs.set("F32_FC_TILES", 3 if rows == 32 else 4)
+    knobs.set("F32_FC_TILES_SPLIT", 1)
+    got, variant = G.gpu_fc_f32(a, w, b, wl.ACT_NONE)
+    assert variant.startswith("fc_tiles_f32_%dx" % rows), variant
+    return got
+
+
+def _exact_and_scale(a, w, b):
+    a, w, b = (v.astype(np.float64) for v in (a, w, b))
+    return a @ w + b, np.abs(a) @ np.abs(w) + np.abs(b)
+
+
+@pytest.mark.parametrize("form", FORMS, ids=str)
+@pytest.mark.parametrize("ex,ew", [(80, -90), (-100, 40), (100, -90), (-50, -50), (13, 0)])
+def test_power_of_two_scaling_changes_only_the_scale(form, ex, ew, knobs):
+    rows, m, k, n = form
+    a, w, b, _ = _operands(39600, m, k, n)
+    a[:, k // 2:] *= 64.0                                # the scale grows on the way
+    base = _run(rows, a, w, b, knobs)
+    got = _run(rows, np.ldexp(a, ex).astype(np.float32), np.ldexp(w, ew).astype(np.float32), np.ldexp(b, ex + ew).astype(np.float32),
+               knobs)
+    assert np.array_equal(np.ldexp(got.astype(np.float64), -(ex + ew)), base.astype(np.float64))
+
+
+@pytest.mark.parametrize("form", FORMS, ids=str)
+def test_wide_value_ranges_are_held_to_fp32_accuracy(form, knobs):
+    """|gpu - exact| <= 4 * 2^-22 * (|A||W| + |b|): 24 binades of magnitudes in either operand and in both, and runs of the
+    reduction of very different magnitude, growing and shrinking."""
+    rows, m, k, n = form
+    a, w, b, rng = _operands(39610, m, k, n)
+    spread = lambda v: (v * np.exp2(rng.integers(-12, 13, size=v.shape))).astype(np.float32)
+    steps = np.exp2(6.0 * (np.arange(k) * 5 // k)).astype(np.float32)      # within 2^28 of the largest
+    cases = [(spread(a), w), (a, spread(w)), (spread(a), spread(w))]
+    for order in (steps, steps[::-1], steps[rng.permutation(k)]):
+        cases += [(a * order, w), (a, w * order[:, None]), (a * order, w * order[::-1][:, None])]
+    for av, wv in cases:
+        av[::7, ::5] = 0.0
+        got = _run(rows, av, wv, b, knobs)
+        exact, scale = _exact_and_scale(av, wv, b)
+        assert np.all(np.isfinite(got))
+        worst = float((np.abs(got - exact) / scale).max())
+        assert worst <= 4 * 2.0 ** -22, worst
+
+
+@pytest.mark.parametrize("form", FORMS, ids=str)
+@pytest.mark.parametrize("where", ["input", "weight", "both"])
+@pytest.mark.parametrize("last", [False, True])
+def test_elements_far_below_the_largest(form, where, last, knobs):
+    """One huge element, first or last in the reduction: the others are cut with what is left of them, an absolute error below
+    2^-39 of the largest magnitude they are scaled by, and the product of two of them may be dropped."""
+    rows, m, k, n = form
+    a, w, b, _ = _operands(39620, m, k, n)
+    at = k - 1 if last else 0
+    if where in ("input", "both"):
+        a[3, at] = np.float32(2.0 ** 33)
+    if where in ("weight", "both"):
+        w[at, 5] = np.float32(2.0 ** 31)
+    got = _run(rows, a, w, b, knobs)
+    exact, scale = _exact_and_scale(a, w, b)
+    bound = 4 * 2.0 ** -22 * scale + 2.0 ** -38 * float(np.abs(a).max()) * float(np.abs(w).max()) * k
+    assert np.all(np.isfinite(got)) and np.all(np.abs(got - exact) <= bound)
+    if where != "both":
+        assert float((np.abs(got - exact) / scale).max()) <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("form", FORMS, ids=str)
+def test_zero_and_subnormal_operands(form, knobs):
+    import gpu_util as G
+    rows, m, k, n = form
+    a, w, b, _ = _operands(39630, m, k, n)
+    for az, wz in ((np.zeros_like(a), w), (a, np.zeros_like(w))):
+        got = _run(rows, az, wz, b, knobs)
+        assert np.array_equal(got, np.broadcast_to(b, got.shape))
+    tiny = (a * np.float32(2.0 ** -140)).astype(np.float32)          # fp32 subnormals and zeros
+    G.assert_close_f32(_run(rows, tiny, w, b, knobs), oracle.fc_f32(tiny, w, b, act=wl.ACT_NONE), "subnormal input")
+
+
+@pytest.mark.parametrize("form", FORMS, ids=str)
+@pytest.mark.parametrize("what", ["inf_in_input", "nan_in_input", "inf_in_weight", "nan_in_weight"])
+@pytest.mark.parametrize("at", [0, -1])
+def test_non_finite_operands_never_give_wrong_finite_values(form, what, at, knobs):
+    """What a non-finite element reaches is not finite; other outputs are right or NaN; other rows' tiles are right.  (A tile of
+    columns that ends inside the matrix also fetches columns of the next row.)"""
+    rows, m, k, n = form
+    a, w, b, _ = _operands(39640, m, k, n)
+    value = np.inf if what.startswith("inf") else np.nan
+    if what.endswith("input"):
+        a[2, at] = value
+    else:
+        w[at, 3] = value
+    got = _run(rows, a, w, b, knobs)
+    ref = oracle.fc_f32(a, w, b, act=wl.ACT_NONE)
+    reached = ~np.isfinite(ref)
+    assert reached.any() and not np.isfinite(got[reached]).any()
+    rest = ~reached & ~np.isnan(got)
+    assert np.all(np.abs(got[rest] - ref[rest]) <= 1e-5 + 1e-4 * np.abs(ref[rest]))
+    if what.endswith("input"):
+        assert np.all(np.isfinite(got[rows:]))

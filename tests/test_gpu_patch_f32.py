@@ -126,6 +126,26 @@ def test_conv_patch_wide_value_ranges(r, st, knobs):
     assert np.all(np.abs(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 + 1e-4 * np.abs(ref[ok]))
 
 
+@pytest.mark.parametrize("c", [13, 67])
+@pytest.mark.parametrize("r,st", [(3, 1), (3, 2), (1, 1), (1, 2)])
+def test_non_finite_values_with_channels_that_end_inside_a_piece(c, r, st, knobs):
+    """A pixel's last piece of eight channels ends in the next pixel, whose values meet zeros of the filter: outputs that a
+    non-finite one does not reach are right or NaN, never finite and wrong."""
+    G = _gpu()
+    knobs.set("F32_PATCH", 2)
+    n, h, w, k = 2, 9, 11, 24
+    x, wt, b, _ = _inputs(37600 + c, n, h, w, c, k, r)
+    x[0, 4, 4, 0], x[0, 8, 2, 1], x[1, 2, 6, 0] = np.nan, -np.inf, np.inf
+    desc = G.make_desc(x.shape, wt.shape, (st, st), (r // 2,) * 4, 1)
+    ref = oracle.conv2d_f32(x, wt, b, (st, st), (r // 2,) * 4, 1, act=wl.ACT_NONE)
+    got, variant = G.gpu_conv2d_f32(x, wt, b, desc, wl.ACT_NONE)
+    assert variant.startswith("conv_patch_f32_f16x3"), variant
+    reached = ~np.isfinite(ref)
+    assert reached.any() and not np.isfinite(got[reached]).any()
+    rest = ~reached & ~np.isnan(got)
+    assert np.all(np.abs(got[rest] - ref[rest]) <= 1e-5 + 1e-4 * np.abs(ref[rest]))
+
+
 @pytest.mark.parametrize("r,st,tile", [(r, st, t) for r, st in ((3, 1), (3, 2), (1, 1)) for t in range(7)
                                        if not (t == 1 and r == 1) and not (t != 1 and (r, st) == (3, 2))])
 def test_long_reductions_are_summed_in_short_runs(r, st, tile, knobs):
