@@ -17,33 +17,42 @@
  *  - x, w, y (and a, the FC input) must be 16-byte aligned, bias 4-byte aligned (any 4-byte
  *    boundary will do), else GLOWMI_ERR_ALIGN.  bias may be NULL (treated as zeros).
  *  - Calls are asynchronous on `stream`, never synchronise the device and never allocate.
- *  - `workspace` is optional scratch in device memory (16-byte aligned).  With NULL / 0 bytes the
- *    call still computes the same result to the same accuracy; with at least
- *    glowmi_*_workspace_bytes() bytes the library may split the reduction dimension over more
- *    workgroups (small-M layers) and, for large fp32 contractions, repack both operands there (two
- *    fp16 pieces per value, 4 bytes per element: see "Results" below), which is faster.  That
- *    figure is always enough; some convolutions use less of it than it names, and a workspace that holds less
- *    than a call uses is not touched.  The contents on entry do not matter and are undefined on return.  Two calls that share a workspace must be ordered on one stream.
+ *  - `workspace` is optional scratch in device memory (16-byte aligned).  With NULL / 0 bytes the call computes the
+ *    same result on kernels that need none; with glowmi_*_workspace_bytes() bytes the library may also split the
+ *    reduction dimension over more workgroups (few rows or pixels) and, in fp32, cut operands into two fp16 pieces
+ *    per value (see "Results" below), which is faster.  That figure is always enough; some convolutions use less of
+ *    it than it names, and a workspace that holds less than a call uses is not touched.  The contents on entry do not
+ *    matter and are undefined on return.  Two calls that share a workspace must be ordered on one stream.
  *  - Arguments are validated on the host before anything is launched.  On any error nothing is
  *    launched, y is untouched, the status says why and glowmi_last_error() gives a sentence.
  *  - Every tensor must hold fewer than 2^31 elements (GLOWMI_ERR_UNSUPPORTED otherwise).
- *  - Results: fp32 entry points accumulate in fp32 (order unspecified).  Products are fp32 products:
- *    either the fp32 matrix cores' own, or -- large contractions with a workspace -- formed on the
- *    fp16 matrix cores from operands cut into two fp16 pieces each: a tensor (in the convolution tile kernels:
- *    each patch of the input a workgroup stages, and of a filter cut in the call each output channel) is scaled by
- *    the power of two that brings its largest magnitude
- *    under 2^15 (exact), a scaled value v becomes h1 = fp16(v) and
+ *  - Results: fp32 entry points accumulate in fp32 (order unspecified).  Products are fp32 products, formed in one of
+ *    two ways.
+ *      On the fp32 matrix cores: small layers; grouped (not depthwise) ones; calls without a workspace but for two
+ *    kernels that hold the filter in registers as pieces and need none: pointwise layers over 64, 128 or 256 channels
+ *    on many pixels (three bf16 pieces per value, all 24 bits, six products) and 7x7 first layers on many pixels (two
+ *    fp16 pieces).
+ *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the filter's
+ *    planes given and none): 1x1 and 3x3 convolutions of ordinary size and
+ *    more, large convolutions of other shapes, FullyConnected layers from 65 rows.  Operands are scaled by a power of
+ *    two that brings the largest magnitude of what is scaled together under 2^15 (exact): a whole tensor, or the patch
+ *    of the input a workgroup stages, a row of a FullyConnected input, a filter's output channel, or what one
+ *    wavefront has fetched so far of either operand.  A scaled value v becomes h1 = fp16(v) and
  *    H2 = fp16((v - h1) * 2^11), 22 significant bits together, and a product is the three piece products
- *    h1 h1' + 2^-11 (h1 H2' + H2 h1'), multiplied exactly and accumulated in fp32; a product is then
- *    within 3 * 2^-22 of |x*y|, a few fp32 roundings.  Either way |result - exact| stays within a few
- *    2^-22 * (|A||W| + |bias|) componentwise for tensors whose elements lie within 2^28 of the largest
- *    magnitude they are scaled by; smaller elements keep 11 significant bits and the product of two such elements,
- *    one from each operand, is dropped, which adds at most 2^-38 * max|A| * max|W| * (reduction length).
- *    Scaling an operand by a power of two scales the result by it and changes nothing else.  With
- *    non-finite inputs the outputs they reach are non-finite (an infinity may come out as NaN); on the
- *    fp16 matrix cores outputs they do not reach may turn into NaN as well, up to every output of the
- *    call (no scale fits a tensor or patch that holds one), but never into wrong finite values.  The int8
- *    entry points are exact integer arithmetic and reproducible bit for bit.
+ *    h1 h1' + 2^-11 (h1 H2' + H2 h1'), multiplied exactly and accumulated in fp32; a product is then within
+ *    3 * 2^-22 of |x*y|.  Sums are kept in short runs on the kernels for FullyConnected layers and for convolutions
+ *    of ordinary size, and sixteen products are rounded once: measured against 64-bit sums over reductions of 64 to
+ *    9216, results lie at 0.3 to 0.8 of the distance that the fp32 matrix cores' have.
+ *      Either way |result - exact| stays within a few 2^-22 * (|A||W| + |bias|) componentwise for tensors whose
+ *    elements lie within 2^28 of the largest magnitude they are scaled by; smaller elements keep 11 significant bits
+ *    and the product of two such elements, one from each operand, is dropped, which adds at most
+ *    2^-38 * max|A| * max|W| * (reduction length).  Scaling an operand by a power of two scales the result by it and
+ *    changes nothing else.
+ *      With non-finite inputs the outputs they reach are non-finite (an infinity may come out as NaN); on the fp16
+ *    matrix cores outputs they do not reach may turn into NaN as well, up to every output of the call (no scale fits
+ *    what holds an infinity; where channels are no multiple of eight a pixel also meets its neighbour's values), but
+ *    never into wrong finite values.  A caller that needs them apart passes no workspace.
+ *      The int8 entry points are exact integer arithmetic and reproducible bit for bit.
  */
 #ifndef GLOWMI_H
 #define GLOWMI_H
@@ -122,9 +131,9 @@ size_t glowmi_fc_workspace_bytes(int32_t M, int32_t K, int32_t N);
 /*
  * glowmi_fc for callers that cannot allocate and have no workspace to hand over: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and checks as glowmi_fc,
- * and the kernels and results glowmi_fc gives with a workspace that holds its split-reduction partial sums
- * (operands are never repacked here: the fp32 matrix-core kernels are used whatever the size); the partial
- * sums go to a buffer that is part of the library image (a static array in device memory of
+ * and the kernels and results glowmi_fc gives with a workspace that holds its split-reduction partial sums,
+ * except that operands are never repacked in memory (a layer that glowmi_fc runs over packed planes takes the
+ * kernel that cuts them on the way, or the fp32 matrix cores); the partial sums go to a buffer that is part of the library image (a static array in device memory of
  * glowmi_fc_noalloc_max_scratch_bytes() = 8 MiB, one copy per GPU the library is used on, held until
  * the process ends).  The call allocates nothing and calls no allocating routine.
  *   - A shape whose partial sums need more than that (as the fp32 matrix-core kernel splits it) is rejected with
@@ -392,8 +401,10 @@ glowmi_status glowmi_rescale_params(float r_scale, float x_scale, float w_scale,
  * (e.g. "F32_TILE", "I8_K3_MIN_BLOCKS"); the same knobs are seeded ONCE, at the library's first use,
  * from environment variables GLOWMI_<name>.  Every setting computes the same result (int8: bit for
  * bit; fp32: within the accuracy stated at the top of this file, the kernels differ in rounding order and
- * in which matrix cores form the products: "F32_P3", "F32_K3", "F32_K3C64", "F32_PW_BF16",
- * "F32_SMALLC_BF16" (the first-layer kernel's piece-product form, whatever the pieces' type) = 0 keep a layer on the
+ * in which matrix cores form the products: "F32_P3" = 0 keeps every layer that needs a workspace for its pieces off the
+ * fp16 matrix cores (the 3x3 tile kernels apart), "F32_PATCH", "F32_FC_TILES", "F32_K3", "F32_K3C64" each a kernel of
+ * them, "F32_PW_BF16" and "F32_SMALLC_BF16" = 0 (the first-layer kernel's piece-product form, whatever the pieces'
+ * type) the two that need no workspace; with all of them a layer stays on the
  * fp32 matrix cores; "F32_K3V" = 0 keeps the 3x3 kernel on its
  * fixed 16 x 16 pixel tile and "F32_K3_TH" / "F32_K3_TW" force a tile of that many rows / columns, at most 256
  * pixels, 64 columns and (rows + 2) x (columns + 4) <= 360, else ignored; "DW" = 0 keeps depthwise 3x3 layers,
