@@ -28,13 +28,13 @@
  *  - Every tensor must hold fewer than 2^31 elements (GLOWMI_ERR_UNSUPPORTED otherwise).
  *  - Results: fp32 entry points accumulate in fp32 (order unspecified).  Products are fp32 products, formed in one of
  *    two ways.
- *      On the fp32 matrix cores: small layers; grouped (not depthwise) ones; calls without a workspace but for two
- *    kernels that hold the filter in registers as pieces and need none: pointwise layers over 64, 128 or 256 channels
+ *      In fp32 arithmetic (matrix cores; vector units for depthwise layers and a few FullyConnected rows): small
+ *    layers, depthwise ones, and calls without a workspace but for two kernels that hold the filter in registers as pieces and need none: pointwise layers over 64, 128 or 256 channels
  *    on many pixels (three bf16 pieces per value, all 24 bits, six products) and 7x7 first layers on many pixels (two
  *    fp16 pieces).
  *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the filter's
- *    planes given and none): 1x1 and 3x3 convolutions of ordinary size and
- *    more, large convolutions of other shapes, FullyConnected layers from 65 rows.  Operands are scaled by a power of
+  *    planes given and none): 1x1 and 3x3 convolutions of ordinary size and more, large convolutions of other shapes,
+ *    FullyConnected layers from 65 rows.  Operands are scaled by a power of
  *    two that brings the largest magnitude of what is scaled together under 2^15 (exact): a whole tensor, or the patch
  *    of the input a workgroup stages, a row of a FullyConnected input, a filter's output channel, or what one
  *    wavefront has fetched so far of either operand.  A scaled value v becomes h1 = fp16(v) and
