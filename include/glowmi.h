@@ -29,20 +29,20 @@
  *  - Results: fp32 entry points accumulate in fp32 (order unspecified).  Products are fp32 products, formed in one of
  *    two ways.
  *      In fp32 arithmetic (matrix cores; vector units for depthwise layers and a few FullyConnected rows): small
- *    layers, depthwise ones, and calls without a workspace but for two kernels that hold the filter in registers as pieces and need none: pointwise layers over 64, 128 or 256 channels
- *    on many pixels (three bf16 pieces per value, all 24 bits, six products) and 7x7 first layers on many pixels (two
- *    fp16 pieces).
- *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the filter's
-  *    planes given and none): 1x1 and 3x3 convolutions of ordinary size and more, large convolutions of other shapes,
- *    FullyConnected layers from 65 rows.  Operands are scaled by a power of
- *    two that brings the largest magnitude of what is scaled together under 2^15 (exact): a whole tensor, or the patch
- *    of the input a workgroup stages, a row of a FullyConnected input, a filter's output channel, or what one
- *    wavefront has fetched so far of either operand.  A scaled value v becomes h1 = fp16(v) and
- *    H2 = fp16((v - h1) * 2^11), 22 significant bits together, and a product is the three piece products
- *    h1 h1' + 2^-11 (h1 H2' + H2 h1'), multiplied exactly and accumulated in fp32; a product is then within
- *    3 * 2^-22 of |x*y|.  Sums are kept in short runs on the kernels for FullyConnected layers and for convolutions
- *    of ordinary size, and sixteen products are rounded once: measured against 64-bit sums over reductions of 64 to
- *    9216, results lie at 0.3 to 0.8 of the distance that the fp32 matrix cores' have.
+ *    layers, depthwise ones, and calls without a workspace but for two kernels that hold the filter in registers as
+ *    pieces and need none: pointwise layers over 64, 128 or 256 channels on many pixels (three bf16 pieces per
+ *    value, all 24 bits, six products) and 7x7 first layers on many pixels (two fp16 pieces).
+ *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the
+ *    filter's planes given and none): 1x1 and 3x3 convolutions of ordinary size and more, large convolutions of
+ *    other shapes, FullyConnected layers from 65 rows.  Operands are scaled by a power of two that brings the
+ *    largest magnitude of what is scaled together under 2^15 (exact): a whole tensor, or the patch of the input a
+ *    workgroup stages, a row of a FullyConnected input, a filter's output channel, or what one wavefront has
+ *    fetched so far of either operand.  A scaled value v becomes h1 = fp16(v) and H2 = fp16((v - h1) * 2^11), 22
+ *    significant bits together, and a product is the three piece products h1 h1' + 2^-11 (h1 H2' + H2 h1'),
+ *    multiplied exactly and accumulated in fp32; a product is then within 3 * 2^-22 of |x*y|.  Sums are kept in
+ *    short runs on the kernels for FullyConnected layers and for convolutions of ordinary size, and sixteen
+ *    products are rounded once: measured against 64-bit sums over reductions of 64 to 9216, results lie at 0.3 to
+ *    0.8 of the distance that the fp32 matrix cores' have.
  *      Either way |result - exact| stays within a few 2^-22 * (|A||W| + |bias|) componentwise for tensors whose
  *    elements lie within 2^28 of the largest magnitude they are scaled by; smaller elements keep 11 significant bits
  *    and the product of two such elements, one from each operand, is dropped, which adds at most
