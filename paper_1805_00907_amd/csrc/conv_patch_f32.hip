@@ -23,8 +23,8 @@
 // 32 reduction indices of a 64 x 64 tile, 256 cycles against 192 of matrix work, and did not get past a third of the matrix
 // rate; here it is 16 KB from LDS and 8 KB from memory.  The instructions that are neither go between the matrix ones.
 // Measured, microseconds with the filter cut in the call, before (igemm_f32, igemm_f32_p3) -> here: 3x3 stride 2 128 -> 128
-// on 56x56 at batch 16 48.9 -> 23.4, 3x3 128 -> 128 on 28x28 at batch 8 31 -> 14, 3x3 152 -> 152 on 57x57 at batch 13
-// 137 -> 82, 3x3 32 -> 344 on 102x102 at batch 4 103 -> 43, 1x1 608 -> 152 on 57x57 at batch 13 96 -> 61.
+// on 56x56 at batch 16 49 -> 23, 3x3 128 -> 128 on 28x28 at batch 8 30 -> 14.8, 3x3 152 -> 152 on 57x57 at batch 13
+// 133 -> 87, 3x3 32 -> 344 on 102x102 at batch 4 93 -> 41, 1x1 608 -> 152 on 57x57 at batch 13 92 -> 60.
 // The input's scale is per patch (within a tile the exponent only goes down, the accumulators are scaled along), the
 // filter's per output channel.  Planes of the filter made ahead of time are rows of channels, which do not help here.
 #include <hip/hip_runtime.h>

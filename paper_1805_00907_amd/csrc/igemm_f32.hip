@@ -697,9 +697,10 @@ Plan plan_f32(const Problem& p, bool allow_split) {
   Plan pl = rest;
   double us;
   if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? asking(p, pl) : rest;
-  // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 30 -> 17.7 us), and of the
+  // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 29 -> 18.6 us), and of the
   // contraction over planes where that would have to cut the weights as well and takes longer by its own measured times
-  // (256x4096x4096 84 -> 47 us; 1024x4096x4096 stays: 158 against 186).
+  // (256x4096x4096 82 -> 52 us; 1024x4096x4096 stays: 162 against 195; near the line it is still the faster one by up to 10 %,
+  // 600x3000x4000 107 against 119, 700x9216x1000 93 against 100).
   if (p.M < 65 || (rest.kernel != KERNEL_TILED && rest.kernel != KERNEL_P3) || knob_is_set(KNOB_F32_TILE) ||
       knob_is_set(KNOB_F32_P3_MIN_M) || knob_is_set(KNOB_F32_SPLIT) || (rest.kernel == KERNEL_P3 && p.w_packed))
     return rest;
@@ -741,7 +742,8 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
       form = patch_f32_form(p);
     // the 3x3 tile kernels, which need the filter's planes given or room in the workspace for them: without a workspace, and
     // where planes are given and the tiles fill the machine (there they save the cut of the filter, and the layer the
-    // workspace: 512 -> 512 on 28x28 at batch 16 182 us, 185 on the patch kernel; cutting the filter in the call 196 and 188)
+    // workspace: 512 -> 512 on 28x28 at batch 16 177 us, 188 on the patch kernel, which cuts the filter in the call; cutting it
+    // there too they take 189, 64 -> 64 on 112x112 73 against 63, 128 -> 128 on 56x56 at batch 32 110 against 95)
     const bool filter_planes = p.w_packed != nullptr || (allow_split && p.allow_pack);
     const bool k3c64 = filter_planes && k3c64_f32_applicable(p), k3 = filter_planes && !k3c64 && k3_f32_applicable(p);
     if (k3c64 && (form < 0 || knob_is_set(KNOB_F32_K3C64_MIN_TILES))) {
