@@ -53,7 +53,7 @@ def _mfma_peak(dtype, variant=""):
     pointwise and first-layer ones on the bf16 cores with six."""
     if dtype != "f32":
         return PEAK_INT8_MFMA, 1
-    if "igemm_f32_p3" in variant or "f16x3" in variant:
+    if "igemm_f32_p3" in variant or "f16x3" in variant or "fc_tiles_f32" in variant:
         return PEAK_F16_MFMA, F16_PRODUCTS
     if "bf16x6" in variant:
         return PEAK_F16_MFMA, BF16_PRODUCTS
@@ -548,9 +548,10 @@ def run_workload(name, args, torch, glowmi, cpu_budget_s):
                          "pipe_frac": round(products * achieved / peak, 4),
                          "fp32_mfma_peak": PEAK_FP32_MFMA / 1e12,
                          "frac_of_fp32_mfma_peak": round(achieved * 1e12 / PEAK_FP32_MFMA, 4)})
-    if "igemm_f32_p3" in dominant:
-        # one call of this kernel's layer = the range pass and the packing kernel (operands cut into fp16 planes) + the contraction;
-        # the event pair brackets the call, so the packing is inside avg_launch_us (profiles/ has the kernels apart)
+    if "igemm_f32_p3" in dominant or "conv_patch_f32" in dominant:
+        # one call of this kernel's layer = the range pass and the packing kernel (operands cut into fp16 planes) + the contraction,
+        # or the kernel that cuts the filter + the convolution; the event pair brackets the call, so the cutting is inside
+        # avg_launch_us (profiles/ has the kernels apart)
         roofline["launch_includes_packing"] = True
 
     layer_rows = []
