@@ -53,6 +53,8 @@ def _mfma_peak(dtype, variant=""):
     pointwise and first-layer ones on the bf16 cores with six."""
     if dtype != "f32":
         return PEAK_INT8_MFMA, 1
+    if variant.startswith("sequence"):      # its launches cut operands into fp16 (three products) or bf16 pieces (six)
+        return PEAK_F16_MFMA, 1
     if "igemm_f32_p3" in variant or "f16x3" in variant or "fc_tiles_f32" in variant:
         return PEAK_F16_MFMA, F16_PRODUCTS
     if "bf16x6" in variant:
@@ -250,7 +252,7 @@ class Sequence:
         first, last = layers[0].spec, layers[-1].spec
         self.bytes = (first.n * first.h * first.w * first.c + last.n * last.oh * last.ow * last.k) * elem + \
             sum(l.spec.k * l.spec.r * l.spec.s * (l.spec.c // l.spec.groups) * elem + 4 * l.spec.k for l in layers)
-        peak = PEAK_FP32_MFMA if dtype == "f32" else PEAK_INT8_MFMA
+        peak = _mfma_peak(dtype, "sequence")[0]
         t_mfma, t_hbm = self.ops / peak, self.bytes / PEAK_HBM
         self.bound = "mfma" if t_mfma >= t_hbm else "hbm"
         self.t_roof = max(t_mfma, t_hbm)
