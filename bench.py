@@ -49,8 +49,8 @@ BF16_PRODUCTS = 6              # bf16 piece products per fp32 multiply-add (thre
 
 def _mfma_peak(dtype, variant=""):
     """(published peak of the matrix-core dtype the kernel multiplies in, matrix-core products per algorithmic
-    multiply-add).  The large fp32 kernels run on the fp16 cores with three piece products per fp32 product, the
-    pointwise and first-layer ones on the bf16 cores with six."""
+    multiply-add).  Most fp32 kernels run on the fp16 cores with three piece products per fp32 product, the
+    pointwise ones over 64 to 256 channels on the bf16 cores with six."""
     if dtype != "f32":
         return PEAK_INT8_MFMA, 1
     if variant.startswith("sequence"):      # its launches cut operands into fp16 (three products) or bf16 pieces (six)

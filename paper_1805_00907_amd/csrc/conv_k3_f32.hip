@@ -10,8 +10,8 @@
 //     chunks of 32.  The chunk's 18 x 18 x 32 input patch is read from the fp32 input ONCE (coalesced 32-byte
 //     pieces, zeros outside the image from the range-checked loads), cut into pieces in registers and kept in
 //     LDS as two fp16 planes (45 KB); all nine taps read their MFMA fragments from it at shifted addresses.
-//     No packing pass over the input (only the pass that finds its largest magnitude), and a ninth of the
-//     input traffic;
+//     No pass over the input ahead of the kernel (the scale is the patch's own), and a ninth of the input
+//     traffic;
 //   - the filter is cut once per call by the packing kernel into two planes in the workspace and streamed
 //     slab by slab (one tap x 32 channels x 128 output channels, 16 KB) straight into a ring of two LDS
 //     buffers;

@@ -10,8 +10,8 @@
 //     read from global memory ONCE (fp32, coalesced 32-byte pieces, zeros outside the image from the
 //     range-checked loads), cut into pieces in registers and kept in LDS as two fp16 planes (83 KB); all
 //     nine taps read their MFMA fragments from it at shifted addresses.  Per tile 83 KB of input are fetched
-//     instead of nine times its planes, and no packing pass over the input is needed (only the pass that finds
-//     its largest magnitude);
+//     instead of nine times its planes, and no pass over the input is needed ahead of the kernel (the scale is
+//     the patch's own);
 //   - the filter (64 x 576) is cut once per call by the packing kernel into two planes in the workspace
 //     (147 KB, L2-resident) and streamed slab by slab (one tap x 32 channels, 8 KB) straight into a ring of
 //     two LDS buffers;

@@ -3,7 +3,7 @@
 // operand cut into two fp16 pieces first (f16_pieces.h).
 //
 //   A tensor is scaled by a power of two taken from its largest magnitude (found by a pass over the tensor,
-//   range_kernel) and every scaled value v is cut into h1 = fp16(v) and H2 = fp16((v - h1) * 2^11); a product
+//   range_kernel; a FullyConnected input beside packed weights row by row, cut_rows_kernel) and every scaled value v is cut into h1 = fp16(v) and H2 = fp16((v - h1) * 2^11); a product
 //   is taken as h1 h1' + 2^-11 (h1 H2' + H2 h1'): three v_mfma_f32_32x32x16_f16, which multiply fp16 exactly
 //   and accumulate in fp32, the cross terms in an accumulator set of their own.  What is lost against an fp32
 //   multiply-add chain is 2^-22 H2 H2' and the cuts' own rounding, each at most 2^-22 of |v v'|.  Three MFMAs
