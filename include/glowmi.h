@@ -408,9 +408,9 @@ glowmi_status glowmi_rescale_params(float r_scale, float x_scale, float w_scale,
  * bit; fp32: within the accuracy stated at the top of this file, the kernels differ in rounding order and
  * in which matrix cores form the products: "F32_P3" = 0 keeps every layer that needs a workspace for its pieces off the
  * fp16 matrix cores (the 3x3 tile kernels apart), "F32_PATCH", "F32_FC_TILES", "F32_K3", "F32_K3C64" each a kernel of
- * them, "F32_PW_BF16" and "F32_SMALLC_BF16" = 0 (the first-layer kernel's piece-product form, whatever the pieces'
- * type) the two that need no workspace; with all of them a layer stays on the
- * fp32 matrix cores; "F32_K3V" = 0 keeps the 3x3 kernel on its
+ * them; of the kernels that need no workspace "F32_PW_BF16" = 0 keeps pointwise layers off bf16 pieces ("F32_SHORT" = 0
+ * only off the kernel for any channels in fours), "F32_SMALLC_BF16" = 0 first layers off fp16 pieces; with all of
+ * these but "F32_SHORT", which the others include, a layer stays on the fp32 matrix cores; "F32_K3V" = 0 keeps the 3x3 kernel on its
  * fixed 16 x 16 pixel tile and "F32_K3_TH" / "F32_K3_TW" force a tile of that many rows / columns, at most 256
  * pixels, 64 columns and (rows + 2) x (columns + 4) <= 360, else ignored; "DW" = 0 keeps depthwise 3x3 layers,
  * groups == c == k, off their own kernel, 2 / 3 make its threads walk one / two output rows at a time); only the

@@ -296,6 +296,7 @@ int short_f32_form(const Problem& p, double* us) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode == 0 || p.b_is_kn || p.groups != 1 || p.chain_n > 0 || p.r != 1 || p.s != 1 || p.pad_t || p.pad_l || p.c % 4 != 0) return -1;
   if (mode == 1 && (p.M < 1000 || p.c > 320)) return -1;   // (the range of the fit)
+  if (mode == 1 && knob_or(KNOB_F32_PW_BF16, 1) == 0) return -1;   // either switch: such layers stay on the fp32 matrix cores
   // bottom/right padding would make output pixels read outside the image
   if ((long long)(p.oh - 1) * p.stride_h >= p.h || (long long)(p.ow - 1) * p.stride_w >= p.w_) return -1;
   // 32-bit offsets of the rows past M too, below the offset that stands for none

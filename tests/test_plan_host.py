@@ -1,0 +1,37 @@
+"""What the planner chooses, on the host (no GPU): the promises of the header about which kernels a call may take."""
+import random
+
+import pytest
+
+import paper_1805_00907_amd as glowmi
+from plan_probe import Probe
+
+
+@pytest.fixture(scope="module")
+def probe():
+    return Probe()
+
+
+def _desc(n, h, w, c, k, r, st=1):
+    return glowmi.ConvDesc(n, h, w, c, k, r, r, st, st, r // 2, r // 2, r // 2, r // 2, 1)
+
+
+# the switches that together keep a layer on the fp32 matrix cores (glowmi.h, tuning knobs)
+PIECE_SWITCHES = ("F32_P3", "F32_PATCH", "F32_FC_TILES", "F32_K3", "F32_K3C64", "F32_PW_BF16", "F32_SMALLC_BF16")
+PIECE_KERNELS = {"patch", "p3", "k3", "k3c64", "short", "fc_tiles"}      # (pw and smallc have an fp32 form each)
+
+
+@pytest.mark.parametrize("workspace", [0, 1 << 36], ids=["no_workspace", "workspace"])
+def test_the_documented_switches_keep_every_layer_on_the_fp32_matrix_cores(probe, knobs, workspace):
+    for name in PIECE_SWITCHES:
+        knobs.set(name, 0)
+    rng = random.Random(1)
+    cases = [_desc(3, 60, 60, c, 64, 1) for c in (24, 56, 96, 160, 224)]
+    for _ in range(600):
+        r = rng.choice([1, 1, 3])
+        cases.append(_desc(rng.choice([1, 2, 5, 16]), rng.randint(7, 80), rng.randint(7, 80), 4 * rng.randint(4, 90),
+                           4 * rng.randint(4, 120), r, rng.choice([1, 1, 2])))
+    for d in cases:
+        for packed in (False, d.c % 8 == 0):
+            plan = probe.conv(d, packed=packed, workspace=workspace)
+            assert plan.kernel not in PIECE_KERNELS, ((d.n, d.h, d.w, d.c, d.k, d.r), packed, plan)
