@@ -35,3 +35,23 @@ def test_the_documented_switches_keep_every_layer_on_the_fp32_matrix_cores(probe
         for packed in (False, d.c % 8 == 0):
             plan = probe.conv(d, packed=packed, workspace=workspace)
             assert plan.kernel not in PIECE_KERNELS, ((d.n, d.h, d.w, d.c, d.k, d.r), packed, plan)
+
+
+# with an offset in the filter's codes another kernel may run than without, and the query does not know which
+QUERY_FC = [(627, 8004, 3204), (1024, 9216, 4096), (600, 4100, 2052), (65, 4100, 1000), (16, 2052, 1000)]
+
+
+@pytest.mark.parametrize("w_offset", [0, 7, -128])
+def test_the_int8_queries_cover_a_filter_with_an_offset(probe, w_offset):
+    rng = random.Random(2)
+    shapes = QUERY_FC + [(rng.randint(1, 1100), 4 * rng.randint(60, 2300), 4 * rng.randint(16, 1150)) for _ in range(1500)]
+    for m, k, n in shapes:
+        plan = probe.qfc(m, k, n, w_offset)
+        assert plan.workspace <= glowmi.qfc_workspace_bytes(m, k, n), ((m, k, n), plan)
+    for _ in range(1500):
+        r = rng.choice([1, 3])
+        d = _desc(rng.choice([1, 2, 5, 16]), rng.randint(7, 60), rng.randint(7, 60), rng.choice([4, 8, 8, 3]) * rng.randint(4, 90),
+                  rng.choice([4, 8, 1]) * rng.randint(16, 120), r, rng.choice([1, 1, 2]))
+        for addend in (False, True):
+            plan = probe.conv(d, quantized=True, addend=addend, w_offset=w_offset)
+            assert plan.workspace <= glowmi.qconv2d_workspace_bytes(d), ((d.n, d.h, d.w, d.c, d.k, d.r), plan)
