@@ -224,13 +224,14 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  * compile time, into the form the selected convolution reads.  The form here is the one the fp32 kernels on the
  * fp16 matrix cores read: the weights scaled by a power of two that follows from the largest magnitude and cut
  * into two fp16 pieces each (see "Results" above), kept as two planes of fp16, followed by a trailer that holds
- * the largest magnitude.  The order within a plane is that of the kernel the library selects for the descriptor:
- *   - a convolution filter in its own [k][r][s][c/groups] order, a FullyConnected weight transposed to [N][K], one
- *     scale for the tensor;
- *   - for the 1x1 and 3x3 layers of ordinary size that run on one input patch per tile (up to 1024 output channels):
- *     [r][s][c/8][k][8], a scale per output channel, whose largest magnitudes are the trailer.
- * So planes belong to the descriptor they were made for (batch and map included) and to the library, and the tuning
- * settings, that made them.  glowmi_conv2d / glowmi_fc make these planes inside every call
+ * the largest magnitude.  A convolution filter is kept in its own [k][r][s][c/groups] order, a FullyConnected weight
+ * transposed to [N][K], with one scale for the tensor; filters of 1x1 and 3x3 layers (one group, up to 1024 output
+ * channels) in [r][s][c/8][k][8] with a scale per output channel, whose largest magnitudes are the trailer, where c is a
+ * multiple of 16 or the descriptor's kernel is the one that reads one input patch per tile.  The trailer says which, and
+ * every kernel reads either order: planes belong to the filter, and serve calls at any batch and map, with any strides
+ * and padding and under any tuning settings.  (Where c is no multiple of 16 they are fastest for descriptors like the one
+ * they were made with: that kernel takes up to 1.7 times as long over planes in the filter's own order.)  They belong to
+ * the library that made them.  glowmi_conv2d / glowmi_fc make these planes inside every call
  * (in the workspace); a caller that keeps the weights fixed makes them once and hands them to the *_packed
  * entry points, which are otherwise the same calls: bit for bit the same results where the same kernel serves
  * both, and within the accuracy stated at the top where a layer takes the fp16 kernels only once its weights
@@ -243,8 +244,9 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  *       GLOWMI_ERR_UNSUPPORTED when that figure is 0, GLOWMI_ERR_SHAPE when planes_bytes is too small).
  *       Asynchronous on `stream`; `w` is not written.
  *   glowmi_conv2d_packed / glowmi_fc_packed
- *       glowmi_conv2d_chain / glowmi_fc with `w_planes` = the planes made from this very `w` for this very
- *       descriptor (or K, N); the library cannot check that and results are undefined otherwise.  `w` itself
+ *       glowmi_conv2d_chain / glowmi_fc with `w_planes` = the planes made from this very `w` for a descriptor of the
+ *       same filter: k, r, s, c and groups (or K, N); the library cannot check that and results are undefined otherwise.
+ *       `w` itself
  *       is still required: layers that take a kernel which does not read planes use it, and ignore w_planes.
  *       w_planes = NULL makes the call the plain one.  chain of glowmi_conv2d_packed must not be NULL.
  *       GLOWMI_ERR_ALIGN for w_planes not 16-byte aligned, GLOWMI_ERR_UNSUPPORTED for w_planes != NULL on a

@@ -290,7 +290,8 @@ size_t fc_query_bytes(const glowmi::Problem& p) {
 // Plan once per call: with what the planner wants from a workspace (repacked operands, a split reduction)
 // when the caller's workspace can hold it, without either otherwise.  Sets p.planes and p.partial accordingly.
 template <typename PlanFn>
-glowmi::Plan settle_workspace(glowmi::Problem& p, glowmi::Plan plan, PlanFn plan_fn, void* workspace, size_t workspace_bytes) {
+glowmi::Plan plan_with_workspace(glowmi::Problem& p, PlanFn plan_fn, void* workspace, size_t workspace_bytes) {
+  glowmi::Plan plan = plan_fn(p, true);
   const size_t need = split_bytes(plan, p);
   p.partial = nullptr;
   p.planes = nullptr;
@@ -303,10 +304,6 @@ glowmi::Plan settle_workspace(glowmi::Problem& p, glowmi::Plan plan, PlanFn plan
     }
   }
   return plan;
-}
-template <typename PlanFn>
-glowmi::Plan plan_with_workspace(glowmi::Problem& p, PlanFn plan_fn, void* workspace, size_t workspace_bytes) {
-  return settle_workspace(p, plan_fn(p, true), plan_fn, workspace, workspace_bytes);
 }
 
 // Bytes of the bf16 planes of a layer's weights, 0 when the shape has no plane form: the kernels that read
@@ -321,16 +318,13 @@ size_t fc_planes_bytes(int32_t K, int32_t N) {
   return glowmi::filter_planes_bytes((size_t)K * (size_t)N);
 }
 
-// Plans a convolution whose filter's planes are given.  They are kept in the order of conv_patch_f32, which then runs the packed
-// calls and needs no workspace, where it is the planner's choice for the descriptor with its filter cut (p.packed_is_cut on
-// return).  The tensor-add link does not count for that, since one form has to serve a layer with and without it: `p` comes as
-// fill_conv and set_operand_bytes leave it.  A layer that is not for that kernel with its filter cut is not with a filter to cut.
+// A convolution whose filter's planes are given, or will be.  Planes say themselves which of the two orders they are in and every
+// kernel over planes reads either (f16_pieces.h), so that planes serve their filter at any batch and map and under any tuning;
+// conv_patch_f32 needs none cut in the call where they can be in its order.
 const unsigned char kPlanesGiven = 0;                  // the planner only asks whether planes were given
-glowmi::Plan plan_packed(glowmi::Problem& p) {
-  p.packed_is_cut = glowmi::patch_f32_order_fits(p) ? 1 : 0;
-  const glowmi::Plan plan = glowmi::plan_f32(p, true);
-  if (plan.kernel != glowmi::KERNEL_PATCH) p.packed_is_cut = 0;
-  return plan;
+void set_packed(glowmi::Problem& p, const void* w_planes) {
+  p.w_packed = w_planes;
+  p.packed_is_cut = w_planes && glowmi::patch_f32_order_fits(p) ? 1 : 0;
 }
 
 // The planes argument of the *_packed entry points: NULL, or aligned planes of a shape that has a plane form.
@@ -438,11 +432,9 @@ glowmi_status prepare_conv2d_chain(const float* x, const float* w, const float* 
   fill_conv(p, d, geo);
   if ((st = set_operand_bytes(p, geo.x_elems, geo.w_elems, 4)) != GLOWMI_OK) return st;
   p.x = x; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
-  p.w_packed = w_planes;
-  Plan plan = w_planes ? plan_packed(p) : Plan();
+  set_packed(p, w_planes);
   p.addend = chain->addend;
-  if (!w_planes || (p.addend && !p.packed_is_cut)) plan = plan_f32(p, true);
-  out->plan = settle_workspace(p, plan, plan_f32, workspace, workspace_bytes);
+  out->plan = plan_with_workspace(p, plan_f32, workspace, workspace_bytes);
   out->quantized = false;
   return GLOWMI_OK;
 }
@@ -562,9 +554,13 @@ glowmi_status glowmi_conv2d_pack_filter(const float* w, const glowmi_conv_desc* 
   if ((st = check_pack_args(w, planes, planes_bytes, conv_planes_bytes(d, geo))) != GLOWMI_OK) return st;
   glowmi::Problem p;
   fill_conv(p, d, geo);
-  p.w_packed = planes;
-  if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) == GLOWMI_OK) plan_packed(p);
-  if (p.packed_is_cut) {
+  set_packed(p, planes);
+  // By channel where conv_patch_f32 takes whole steps of sixteen channels, whatever kernel this descriptor takes: over rows that
+  // kernel takes 1.2 to 1.7 times as long (3x3 128->128 on 28x28 at batch 16 15.9 -> 24.2 us), the others over channels 0.97 to
+  // 1.03 times (contraction over planes 34.0 and 34.4, 79.7 and 77.4, 39.0 and 40.3; 3x3 tiles 179.9 and 178.9).  Else where it is
+  // the kernel of this descriptor.
+  if (p.packed_is_cut && set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) == GLOWMI_OK &&
+      (p.c % 16 == 0 || glowmi::plan_f32(p, true).kernel == glowmi::KERNEL_PATCH)) {
     p.w = w;
     p.planes = planes;
     const glowmi::Problem* one = &p;
@@ -580,8 +576,8 @@ size_t glowmi_conv2d_packed_workspace_bytes(const glowmi_conv_desc* d) {
   fill_conv(p, d, geo);
   if (set_operand_bytes(p, geo.x_elems, geo.w_elems, 4) != GLOWMI_OK) return 0;
   if (conv_planes_bytes(d, geo) == 0) return query_bytes(glowmi::plan_f32(p, true), p);
-  p.w_packed = &kPlanesGiven;
-  return query_bytes(plan_packed(p), p);
+  set_packed(p, &kPlanesGiven);
+  return query_bytes(glowmi::plan_f32(p, true), p);
 }
 
 glowmi_status glowmi_conv2d_packed(const float* x, const float* w, const void* w_planes, const float* bias,

@@ -90,12 +90,11 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
   const unsigned wpb = p.w_bytes >> 1;                  // bytes of one filter plane
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;
-  // The filter's scale exponent follows from its largest magnitude (the trailer of its planes).  The input is scaled
+  // The filter's scale exponent follows from its largest magnitude, or its channel's (f16_pieces.h).  The input is scaled
   // patch by patch: the workgroup takes the largest magnitude of the patch chunk it is about to write (from the
   // prefetch registers), which costs no pass over the input; within a tile the exponent only ever goes down, and
   // when it does the accumulators are scaled along (exact: a power of two).
-  const unsigned w_max_bits = wave_max_words(p.w_range, 1);
-  const int se_w = scale_exponent(w_max_bits);
+  const PlaneOrder order(p.w_range, p.k, p.Kgemm >> 3);
   constexpr unsigned OOBX = 0xFFFFFF00u;                // beyond any fp32 tensor this library accepts
 
   const int chunks = p.c / G_CH;                        // p.c % 32 == 0 on this kernel
@@ -155,7 +154,7 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
   auto issue_b = [&](int ct, int slab, int buf) {
     const int chunk = slab / 9, tap = slab - chunk * 9;
     const unsigned lbase = __builtin_amdgcn_readfirstlane(lds_offset_of(bring) + buf * G_BBUF);
-    const unsigned k_off = (unsigned)(tap * p.c + chunk * G_CH + bch * 8);
+    const unsigned k_off = (order.piece >> 3) * (unsigned)(tap * p.c + chunk * G_CH + bch * 8);
 #pragma unroll
     for (int u = 0; u < T::LPW; ++u) {
       const int j = wave + 8 * u;                        // load number: plane j / (BN / 16), row group j % (BN / 16)
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
       const int n = ct * G_BN + rg * 16 + (lane >> 2);
       const bool real = j < T::WLOADS;
       const bool ok = real && slab < slabs && n < p.k;   // past the last slab: zero fills, no memory traffic
-      const unsigned off = ok ? 2u * ((unsigned)n * (unsigned)p.Kgemm + k_off) + (unsigned)plane * wpb : OOB;
+      const unsigned off = ok ? (unsigned)n * order.row + k_off + (unsigned)plane * wpb : OOB;
       const unsigned dst = real ? lbase + plane * G_BPLANE + rg * 16 * G_BROW
                                 : __builtin_amdgcn_readfirstlane(lds_offset_of(bring) + G_NBUF * G_BBUF);
       load16_to_lds(rsrc_w, dst, off);
@@ -208,10 +207,12 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
     // The tile's bias values now, not in the epilogue: there every store sits in a branch of its own, and the compiler
     // would wait for all memory operations in front of each store's bias add, i.e. for the store before it.
     float bias_v[2];
+    unsigned w_max_bits[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int ch = ct * G_BN + wn * 64 + j * 32 + lrow;
       bias_v[j] = (ch < p.k && bias) ? bias[ch] : 0.f;
+      w_max_bits[j] = order.max_bits(p.w_range, ch < p.k ? ch : 0);
     }
 
     v16f acc[2][2], acc_lo[2][2];                       // the h1 h1' products; the cross terms (weight 2^-11)
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
 
     int s = 0;
     int se_x = 0;
-    bool finite = w_max_bits < 0x7f800000u;
+    bool finite = true;
     for (int chunk = 0; chunk < chunks; ++chunk) {
       // ---- the chunk's patch: its largest magnitude (every wavefront leaves that of its share), everyone is done
       // with the previous patch, scale, write it, publish it (the barrier of the first trip below), and start
@@ -308,12 +309,12 @@ __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem
     // ---- epilogue.  Register e of a lane is pixel (e/4)*8 + 4*lhalf + e%4 of the 32-pixel block, i.e. tile pixel
     // 64wm + 32i + that; channel wn * 64 + j * 32 + lrow.
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));           // nothing is in flight any more; the compiler cannot see it
-    const ScaleBack sb = scale_back_of(se_x, se_w, finite);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int ch = ct * G_BN + wn * 64 + j * 32 + lrow;
       const bool cok = ch < p.k;
       const float bv = bias_v[j];
+      const ScaleBack sb = scale_back_of(se_x, scale_exponent(w_max_bits[j]), finite && w_max_bits[j] < 0x7f800000u);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
 #pragma unroll

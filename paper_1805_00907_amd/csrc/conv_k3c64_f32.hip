@@ -77,10 +77,10 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
   const unsigned wpb = p.w_bytes >> 1;                  // bytes of one filter plane
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;
-  // The filter's scale exponent follows from its largest magnitude (the trailer of its planes).  The input is scaled
+  // The filter's scale exponent follows from its largest magnitude, or its channel's (f16_pieces.h).  The input is scaled
   // patch by patch: the workgroup takes the largest magnitude of the patch it is about to write (from the prefetch
   // registers), which costs no pass over the input.
-  const unsigned w_max_bits = wave_max_words(p.w_range, 1);
+  const PlaneOrder order(p.w_range, p.k, 72);
   constexpr unsigned OOBX = 0xFFFFFF00u;                // beyond any fp32 tensor this library accepts
 
   // ---- tile decode: channel tile fastest (workgroups that share a patch run side by side), then x, y, image
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
       const int plane = wave >> 2, rg = wave & 3;
       const int n = ct * 64 + rg * 16 + (lane >> 2);
       const bool ok = slab < K_SLABS && n < p.k;         // past the last slab: a zero fill, no memory traffic
-      const unsigned off = ok ? 2u * ((unsigned)n * 576u + (unsigned)(tap * 64 + half * 32 + bch * 8)) + (unsigned)plane * wpb : OOB;
+      const unsigned off = ok ? (unsigned)n * order.row + (unsigned)(tap * 8 + half * 4 + bch) * order.piece + (unsigned)plane * wpb : OOB;
       load16_to_lds(rsrc_w, lbase + plane * K_BPLANE + rg * 16 * K_BROW, off);
     }
   };
@@ -194,7 +194,6 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
     __syncthreads();                                    // the previous tile's exchange has been read: the patch area is free
     const unsigned x_max_bits = max_of_eight(maxw);
     const int se_x = scale_exponent(x_max_bits);
-    const ScaleBack sb = scale_back(x_max_bits, w_max_bits);
     commit_patch(se_x);
     const int t_next = t + gridDim.x;
     const bool prefetching = t_next < total;            // uniform
@@ -211,10 +210,12 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
     // the tile's bias values now: a load in the epilogue would make the compiler wait there for everything issued
     // before it, the next tile's slabs included
     float bias_v[2];
+    unsigned w_max_bits[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int ch = ct * 64 + j * 32 + lrow;
       bias_v[j] = (ch < p.k && bias) ? bias[ch] : 0.f;
+      w_max_bits[j] = order.max_bits(p.w_range, ch < p.k ? ch : 0);
     }
 
     v16f acc[2][2], acc_lo[2][2];                       // the h1 h1' products; the cross terms (weight 2^-11)
@@ -315,13 +316,15 @@ __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Prob
       else exchange_as(std::integral_constant<int, 0>{});
       __syncthreads();
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j) {
+        const ScaleBack sb = scale_back(x_max_bits, w_max_bits[j]);
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           const v4f got = xch[(theirs + j * 4 + e4) * 64 + lane];
 #pragma unroll
           for (int tq = 0; tq < 4; ++tq) keep[j][e4 * 4 + tq] = __builtin_ldexpf(keep[j][e4 * 4 + tq] + got[tq], sb.neg_se) + sb.poison;   // scaled back
         }
+      }
     }
 
     // ---- epilogue.  Register e of a lane is pixel (e/4)*8 + 4*lhalf + e%4 of the 32-pixel block, i.e. tile row

@@ -76,12 +76,11 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
   const unsigned wpb = p.w_bytes >> 1;                  // bytes of one filter plane
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;
-  // The filter's scale exponent follows from its largest magnitude (the trailer of its planes).  The input is scaled
+  // The filter's scale exponent follows from its largest magnitude, or its channel's (f16_pieces.h).  The input is scaled
   // patch by patch: the workgroup takes the largest magnitude of the patch chunk it is about to write (from the
   // prefetch registers), which costs no pass over the input; within a tile the exponent only ever goes down, and
   // when it does the accumulators are scaled along (exact: a power of two).
-  const unsigned w_max_bits = wave_max_words(p.w_range, 1);
-  const int se_w = scale_exponent(w_max_bits);
+  const PlaneOrder order(p.w_range, p.k, p.Kgemm >> 3);
   constexpr unsigned OOBX = 0xFFFFFF00u;                // beyond any fp32 tensor this library accepts
 
   // Patch rows have a pitch of tw + 4 pixels (tw + 2 used), and a pixel's four 16-byte chunks are stored at
@@ -161,9 +160,9 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
   auto issue_b = [&](int ct, int slab, int buf) {
     const int chunk = slab / 9, tap = slab - chunk * 9;
     const unsigned lbase = __builtin_amdgcn_readfirstlane(lds_offset_of(bring) + buf * V_BBUF + wave * 16 * V_BROW);
-    const unsigned k_off = (unsigned)(tap * p.c + chunk * V_CH + bch * 8);
+    const unsigned k_off = (order.piece >> 3) * (unsigned)(tap * p.c + chunk * V_CH + bch * 8);
     const int n = ct * V_BN + wave * 16 + (lane >> 2);
-    const unsigned row_off = n < p.k ? 2u * ((unsigned)n * (unsigned)p.Kgemm + k_off) : OOB;
+    const unsigned row_off = n < p.k ? (unsigned)n * order.row + k_off : OOB;
 #pragma unroll
     for (int plane = 0; plane < V_LPW; ++plane)
       load16_to_lds(rsrc_w, lbase + plane * V_BPLANE, row_off == OOB ? OOB : row_off + (unsigned)plane * wpb);
@@ -209,10 +208,12 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
       // cannot carry "already waited for" across them and waits for ALL memory operations in front of each store's
       // bias add, i.e. for the store before it.
       float bias_v[CH];
+      unsigned w_max_bits[CH];
 #pragma unroll
       for (int j = 0; j < CH; ++j) {
         const int ch = ct * V_BN + (ch_first + j) * 32 + lrow;
         bias_v[j] = (ch < p.k && bias) ? bias[ch] : 0.f;
+        w_max_bits[j] = order.max_bits(p.w_range, ch < p.k ? ch : 0);
       }
 
       v16f acc[PX][CH], acc_lo[PX][CH];                 // the h1 h1' products; the cross terms (weight 2^-11)
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
 
       int s = 0;
       int se_x = 0;
-      bool finite = w_max_bits < 0x7f800000u;
+      bool finite = true;
       for (int chunk = 0; chunk < chunks; ++chunk) {
         // ---- the chunk's patch: its largest magnitude (every wavefront leaves that of its share), everyone is done
         // with the previous patch, scale, write it, publish it (the barrier of the first trip below), and start
@@ -319,7 +320,6 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
       // see that through the loops: told so, it stops putting a wait for all memory operations in front of every
       // store's bias add, which made each store wait for the one before it.
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-      const ScaleBack sb = scale_back_of(se_x, se_w, finite);
       int lh4 = lhalf * 4;
       asm volatile("" : "+v"(lh4));      // keeps the pixel arithmetic below inside the tile loop (hoisted, it is spilled)
 #pragma unroll
@@ -327,6 +327,7 @@ __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Proble
         const int ch = ct * V_BN + (ch_first + j) * 32 + lrow;
         const bool cok = ch < p.k;
         const float bv = bias_v[j];
+        const ScaleBack sb = scale_back_of(se_x, scale_exponent(w_max_bits[j]), finite && w_max_bits[j] < 0x7f800000u);
         if (ADD) {
           // The add link: eight addend values at a time, all in flight together, then one wait the compiler can see
           // and eight range-checked stores at the same offsets.  Loaded one by one in front of their stores, each

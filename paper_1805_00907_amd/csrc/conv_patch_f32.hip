@@ -26,8 +26,8 @@
 // on 56x56 at batch 16 49 -> 23, 3x3 128 -> 128 on 28x28 at batch 8 30 -> 14.8, 3x3 152 -> 152 on 57x57 at batch 13
 // 133 -> 87, 3x3 32 -> 344 on 102x102 at batch 4 93 -> 41, 1x1 608 -> 152 on 57x57 at batch 13 92 -> 60.
 // The input's scale is per patch (within a tile the exponent only goes down, the accumulators are scaled along), the
-// filter's per output channel.  A filter made ahead of time (glowmi_conv2d_pack_filter) is kept in this kernel's order where
-// the planner takes it for the layer (plan_packed in api.hip): the packed call is then one launch and needs no workspace, 3x3
+// filter's per output channel.  Planes made ahead of time (glowmi_conv2d_pack_filter) are in this kernel's order where the
+// channels come in sixteens or the planner takes it for the descriptor they were made with: the packed call is then one launch, 3x3
 // stride 2 128 -> 128 on 56x56 at batch 16 24.4 -> 20.8 us, 3x3 128 -> 64 on 85x85 13.4 -> 9.8, 1x1 248 -> 952 on 20x20 at batch 3
 // 13.6 -> 9.3.
 #include <hip/hip_runtime.h>
@@ -130,23 +130,25 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
     ty = t2 - img * tl.tiles_y;
   }
 
-  // ---- filter fragments: planes [Kgemm / 8][k][8]; lane: channel lrow of the wavefront's 32, eight indices lhalf of the
-  // step's 16.  Step st of a chunk: tap st / MS, channels 16 ((st % MS) KS + kset) .. of the chunk.
+  // ---- filter fragments: planes of pieces in either order (by channel unless the caller had them made for another kernel, and
+  // then slower: a load's lanes are a filter apart); lane: channel lrow of the wavefront's 32, eight indices lhalf of the step's
+  // 16.  Step st of a chunk: tap st / MS, channels 16 ((st % MS) KS + kset) .. of the chunk.
   // Pieces of eight channels per tap, the filter's last one filled up with zeros: they meet whatever lies behind a pixel's
   // last channel (the next pixel; behind the tensor zeros).
   const int c8 = (p.c + 7) >> 3;
-  const unsigned k16 = 16u * (unsigned)p.k;             // bytes of eight reduction indices
-  const unsigned wpb = (unsigned)(R * R * c8) * k16;    // bytes of one plane
+  const unsigned wpb = 16u * (unsigned)(R * R * c8) * (unsigned)p.k;   // bytes of one plane
   const __amdgpu_buffer_rsrc_t rsrc_w1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w_planes), 0, (int)wpb, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(static_cast<const unsigned char*>(p.w_planes)) + wpb, 0, (int)wpb, 0x00020000);
   const int ch = ct * T::BN + wn * 32 + lrow;
-  const unsigned b_base = ch < p.k ? (unsigned)(2 * kset + lhalf) * k16 + 16u * (unsigned)ch : OOBW;
-  const unsigned tap_step = (unsigned)c8 * k16, chunk_step = (unsigned)(T::CC >> 3) * k16;
+  const PlaneOrder order(p.w_range, p.k, R * R * c8, p.packed_is_cut == 0);
+  const unsigned b_base = ch < p.k ? (unsigned)(2 * kset + lhalf) * order.piece + (unsigned)ch * order.row : OOBW;
+  const unsigned tap_step = (unsigned)c8 * order.piece, chunk_step = (unsigned)(T::CC >> 3) * order.piece;
   v4i fb[T::DB][2];                                     // [step in flight][plane]
   auto chunk_at = [&](int chunk) { return chunk < tl.chunks ? (unsigned)chunk * chunk_step : PASTW; };
   auto load_b = [&](int slot, unsigned from, int st) {  // slot, st: compile-time; from: chunk_at of the chunk
-    const unsigned at = from + (unsigned)(st / T::MS) * tap_step + (unsigned)(st % T::MS * 2 * T::KS) * k16;
+    unsigned at = from + (unsigned)(st / T::MS) * tap_step + (unsigned)(st % T::MS * 2 * T::KS) * order.piece;
+    asm("" : "+s"(at));                                   // one sum, added to the lane's base: split up it costs eight to twenty registers
     fb[slot][0] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w1, b_base + at, 0, 0));
     fb[slot][1] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w2, b_base + at, 0, 0));
   };
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem
   // ---- what the epilogue needs, fetched now: the channel's bias, the filter's scale, where the pixels lie in the output
   const float* __restrict__ bias = static_cast<const float*>(p.bias);
   const float bv = ch < p.k && bias ? bias[ch] : 0.f;
-  const unsigned w_max_bits = p.w_range[ch < p.k ? ch : 0];
+  const unsigned w_max_bits = order.max_bits(p.w_range, ch < p.k ? ch : 0);
   if (tid < T::PX) {
     int pix = -1;
     if (R == 1) {
@@ -533,7 +535,7 @@ __global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs
         m = o > m ? o : m;
       }
       m = wave_max_u32(m);
-      if (part == 0 && lane == 0) words[mine] = m;
+      if (part == 0 && lane == 0) words[mine] = mine == 0 ? m | kByChannel : m;
     }
     if (lane == 0) largest[wave] = m;
   }
@@ -768,7 +770,9 @@ size_t cut_plane_bytes(const Problem& p) { return ((size_t)p.r * p.s * ((p.c + 7
 
 size_t patch_f32_pack_bytes(const Problem& p) { return cut_plane_bytes(p) + 4 * (size_t)p.k; }
 // (Whole pieces of eight channels take the same bytes in either order; the channels' words then lie in the trailer's place.)
-bool patch_f32_order_fits(const Problem& p) { return p.c % 8 == 0 && 4 * (size_t)p.k <= kPlaneTrailerBytes; }
+bool patch_f32_order_fits(const Problem& p) {
+  return p.groups == 1 && p.r == p.s && (p.r == 1 || p.r == 3) && p.c % 8 == 0 && 4 * (size_t)p.k <= kPlaneTrailerBytes;
+}
 
 namespace {
 unsigned* cut_words(const Problem& p, const void* planes) {

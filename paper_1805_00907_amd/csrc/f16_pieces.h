@@ -130,6 +130,28 @@ __device__ __forceinline__ Cut2 cut2(float x, int se) {
   return c;
 }
 
+// A filter's planes in memory hold pieces of eight reduction indices, 16 bytes each, in one of two orders, and the first word
+// behind them says which:
+//   rows        [output channel][reduction / 8], one scale: word 0 is the bits of the tensor's largest magnitude;
+//   by channel  [reduction / 8][output channel], the order conv_patch_f32 reads best, a scale per output channel: word i is the
+//               bits of channel i's largest magnitude, word 0 with kByChannel.
+// Every kernel over planes reads either, so planes made once serve the filter whichever kernel a call takes.
+constexpr unsigned kByChannel = 0x80000000u;
+struct PlaneOrder {
+  unsigned row, piece;                                   // bytes from a channel's piece to the next channel's, to its next piece
+  bool by_channel;
+  // words: behind the planes; pieces: of a channel; known: made in this call by conv_patch_f32, whose order needs no asking (a
+  // trip to memory ahead of the first fragments: 0.4 us of a residual block)
+  __device__ __forceinline__ PlaneOrder(const unsigned* words, int channels, int pieces, bool known = false) {
+    by_channel = true;
+    if (!known) by_channel = (__builtin_amdgcn_readfirstlane((int)words[0]) & (int)kByChannel) != 0;   // uniform
+    row = by_channel ? 16u : 16u * (unsigned)pieces;
+    piece = by_channel ? 16u * (unsigned)channels : 16u;
+  }
+  // the bits of the largest magnitude that channel ch was scaled by
+  __device__ __forceinline__ unsigned max_bits(const unsigned* words, int ch) const { return words[by_channel ? (unsigned)ch : 0u] & ~kByChannel; }
+};
+
 // The two operands' largest magnitudes (bits) -> what the accumulators are scaled back by, and what is added to
 // every result: 0, or NaN when an operand holds an infinity or a NaN (its largest "magnitude" is then not finite and
 // no scale fits: the whole call's results are NaN rather than finite numbers that are wrong).

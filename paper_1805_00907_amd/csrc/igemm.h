@@ -83,7 +83,7 @@ struct Problem {
   const void* w_packed; // the weights' planes as the caller made them ahead of time (glowmi_*_pack_filter), or null
   const void* w_planes; // where the kernel reads the weights' planes: w_packed, or inside `planes` (set by the launcher)
   const unsigned* x_range; // the bits of the input's largest magnitude, or of each of its x_range_n rows' (set by the launcher)
-  const unsigned* w_range; // one word: the same for the weights (the trailer of their planes)
+  const unsigned* w_range; // the words behind the weights' planes: the same for the weights, whole or by channel (f16_pieces.h)
   int32_t x_range_n;
   const void* addend; // tensor operand of the element-wise chain [M][k] (float or int8), may be null:
                       // added to the accumulator after the bias and before the activation
@@ -102,7 +102,7 @@ struct Problem {
   float act_lo, act_hi;     // -inf, inf with act == 0
   int32_t b_is_kn;          // FC weight layout
   int32_t filter_is_cut;    // the planes of this layer's filter were cut ahead, with those of other layers (conv_patch_f32.hip)
-  int32_t packed_is_cut;    // w_packed holds the filter in that kernel's order (patch_f32_takes_packed), which then runs
+  int32_t packed_is_cut;    // w_packed is given and can be in that kernel's order (patch_f32_order_fits): it cuts no filter then
   int32_t allow_pack;       // the caller's workspace may hold repacked operands (fp32 three-piece form)
   // quantized form only
   int32_t x_off, w_off, y_off;
@@ -208,7 +208,7 @@ constexpr int kRangeWords = 512;
 constexpr size_t kRangeBytes = 4 * (size_t)kRangeWords;
 constexpr size_t kPlaneTrailerBytes = 2 * kRangeBytes;
 // The weights' planes, the form every fp16 three-product kernel reads them in: convolution filters in their own
-// [k][r][s][cg] order, FullyConnected weights transposed to [N][K].
+// [k][r][s][cg] order or by channel (conv_patch_f32.hip), FullyConnected weights transposed to [N][K].
 // filter_planes_bytes: bytes of that form (a multiple of 256).  launch_pack_filter: measures and writes it
 // (b_is_kn: transposed).  stage_filter_planes, for the kernels that cut the input themselves: takes the planes the
 // caller made ahead of time (p.w_packed) or measures and cuts the filter into `dst` now; sets p.w_planes / p.w_range.
@@ -232,7 +232,7 @@ hipError_t launch_k3v_f32(const Problem& p, hipStream_t stream, const char** var
 // patch_f32_form: the tile form to run a layer in and its expected microseconds, -1 where another kernel is the better one.
 int patch_f32_form(const Problem& p, double* us);
 size_t patch_f32_pack_bytes(const Problem& p);
-bool patch_f32_order_fits(const Problem& p);   // whether the filter in that kernel's order fits the buffer of filter_planes_bytes
+bool patch_f32_order_fits(const Problem& p);   // whether planes of the filter in that kernel's order fit the buffer of filter_planes_bytes
 hipError_t launch_patch_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 constexpr int kCutJobs = 8;
 hipError_t launch_cut_filters(const Problem* const* layers, int n, hipStream_t stream);

@@ -325,16 +325,18 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;   // planes are at most 512 MiB each: OOB + a plane neither wraps nor lands inside
   // what the two accumulator sets are scaled back by: the operands' scale exponents, from their largest magnitudes (the
-  // input's: one word, or one per row)
-  const unsigned w_max = *p.w_range;
+  // input's: one word, or one per row; the weights' per channel in planes ordered by it)
+  const PlaneOrder order(p.w_range, p.k, p.Kgemm >> 3);
   const bool row_scales = p.x_range_n > 1;              // uniform
 
   // The bias values now, not in the epilogue: a load there would make the compiler wait for all memory operations
   // in front of every store (each store is a branch of its own, and each would wait for the store before it).
   float bias_v[2];
+  unsigned w_max[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int col = tn * BN + wn * 64 + j * 32 + lrow;
+    w_max[j] = order.max_bits(p.w_range, col < p.kg ? g * p.kg + col : 0);
     const float* __restrict__ bias_p = static_cast<const float*>(p.bias);
     bias_v[j] = (col < p.kg && p.split_k == 1 && bias_p) ? bias_p[g * p.kg + col] : 0.f;
   }
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   unsigned b_base;                                      // byte offset of the filter row's chunk in plane 0
   {
     const int n = tn * BN + 16 * wave + (lane >> 2);
-    b_base = n < p.kg ? 2u * ((unsigned)(g * p.kg + n) * (unsigned)p.Kgemm + (unsigned)(cch * 8)) : OOB;
+    b_base = n < p.kg ? (unsigned)(g * p.kg + n) * order.row + (unsigned)cch * order.piece : OOB;
   }
   // scalar walk over (tap, channel block): the next slab to issue
   int tap_r, tap_s, tap_c0, next_slab = slab_begin;
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
     const bool live = next_slab < slab_end;             // ring positions past the end: zeros, no memory traffic
     const bool cok = live && tap_c0 + cch * 8 < p.cg;   // channel tail of a tap
     const unsigned tap_off = 2u * (unsigned)((tap_r * p.w_ + tap_s) * p.c + tap_c0);
-    const unsigned k_off = 2u * (unsigned)((tap_r * p.s + tap_s) * p.cg + tap_c0);
+    const unsigned k_off = (order.piece >> 3) * (unsigned)((tap_r * p.s + tap_s) * p.cg + tap_c0);
 #pragma unroll
     for (int t = 0; t < A_GROUPS; ++t) {
       bool ok = cok && a_base[t] != OOB;
@@ -573,7 +575,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
         const v4f got = xch[(theirs + j * 4 + e4) * 64 + lane];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const ScaleBack sb = scale_back(x_max[e4 * 4 + t], w_max);
+          const ScaleBack sb = scale_back(x_max[e4 * 4 + t], w_max[j]);
           keep[j][e4 * 4 + t] = __builtin_ldexpf(keep[j][e4 * 4 + t] + got[t], sb.neg_se) + sb.poison;   // scaled back
         }
       }

@@ -380,3 +380,109 @@ def test_conv_packed_in_the_order_of_the_patch_kernel(shape, knobs):
             ref = ref + add.cpu().numpy()
             mag = mag + np.abs(add.cpu().numpy())
         assert np.all(np.abs(packed.cpu().numpy() - np.maximum(ref, 0)) <= 4 * 2.0 ** -22 * mag)
+
+
+# how planes of channels that come in eights but not in sixteens get their order: conv_patch_f32 takes every layer, or none
+ORDERS = {"by_channel": {"F32_PATCH": 2}, "rows": {"F32_PATCH": 0}}
+READERS = {       # knobs that bring a layer to the kernel, its name, layers: n h w c k r stride
+    "patch": ({"F32_PATCH": 2}, "conv_patch_f32", [(2, 21, 17, 136, 128, 3, 1), (2, 13, 15, 72, 200, 3, 2), (3, 9, 11, 88, 1024, 1, 1),
+                                                   (1, 16, 24, 8, 40, 3, 1), (2, 12, 12, 296, 24, 1, 2), (2, 9, 9, 64, 96, 3, 1)]),
+    "p3": ({"F32_P3_MIN_M": 1, "F32_P3_RATIO": 0, "F32_K3": 0, "F32_K3C64": 0}, "igemm_f32_p3",
+           [(2, 14, 14, 64, 128, 3, 1), (3, 9, 11, 136, 72, 1, 1), (2, 13, 15, 72, 200, 3, 2), (1, 10, 9, 40, 1000, 3, 1)]),
+    "k3v": ({"F32_PATCH": 0, "F32_K3_ANY": 1, "F32_K3C64": 0}, "conv_k3_f32", [(2, 20, 37, 96, 200, 3, 1), (1, 28, 28, 128, 136, 3, 1)]),
+    "k3": ({"F32_PATCH": 0, "F32_K3_ANY": 1, "F32_K3C64": 0, "F32_K3V": 0}, "conv_k3_f32", [(2, 21, 45, 96, 64, 3, 1), (1, 18, 18, 128, 200, 3, 1)]),
+    "k3c64": ({"F32_PATCH": 0, "F32_K3C64_MIN_TILES": 1}, "conv_k3c64_f32", [(2, 40, 40, 64, 64, 3, 1), (1, 33, 50, 64, 200, 3, 1)]),
+}
+
+
+@pytest.mark.parametrize("reader", READERS)
+def test_every_kernel_over_planes_reads_either_order(reader, knobs):
+    """The same pieces at other places, scaled by other powers of two: the results of the plain call bit for bit, whose planes the
+    patch kernel makes by channel and the others as rows."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    forced, name, shapes = READERS[reader]
+
+    def tune(settings):
+        glowmi.tuning_reset()
+        for key, value in settings.items():
+            knobs.set(key, value)
+    for i, (n, h, w, c, k, r, st) in enumerate(shapes):
+        x, wt, b = _conv_inputs(37000 + 10 * i + c, n, h, w, c, k, r, r)
+        wt *= np.exp2(np.arange(k) % 11 - 5).astype(np.float32)[:, None, None, None]     # each channel a scale of its own
+        pads = (r // 2,) * 4
+        desc = G.make_desc(x.shape, wt.shape, (st, st), pads, 1)
+        oh, ow = glowmi.conv_out_shape(desc)
+        xd, wd, bd = G.dev(x), G.dev(wt), G.dev(b)
+        add = torch.randn((n, oh, ow, k), device="cuda:0") if i % 2 else None
+        ref = oracle.conv2d_f32(x, wt, b, (st, st), pads, 1, act=wl.ACT_NONE).astype(np.float64)
+        mag = oracle.conv2d_f32(np.abs(x), np.abs(wt), np.abs(b), (st, st), pads, 1).astype(np.float64)
+        if add is not None:
+            ref, mag = ref + add.cpu().numpy(), mag + np.abs(add.cpu().numpy())
+        tune(forced)
+        plain = G.poison((n, oh, ow, k), torch.float32)
+        glowmi.conv2d_chain(xd, wd, bd, plain, desc, addend=add, act=wl.ACT_RELU, workspace=G.workspace(glowmi.conv2d_workspace_bytes(desc)))
+        torch.cuda.synchronize()
+        variant = glowmi.last_variant()
+        assert variant.startswith(name), variant
+        # products within 3 * 2^-22 of |x w|, sums in runs of fp32: 8 * 2^-22 of the sum of magnitudes
+        assert np.all(np.abs(plain.cpu().numpy() - np.maximum(ref, 0)) <= 8 * 2.0 ** -22 * mag), (reader, i)
+        for order, settings in ORDERS.items():
+            tune(settings)
+            planes = torch.empty(glowmi.conv2d_filter_planes_bytes(desc), dtype=torch.uint8, device="cuda:0")
+            glowmi.conv2d_pack_filter(wd, desc, planes)
+            torch.cuda.synchronize()
+            first = int(planes[-4096:-4092].cpu().numpy().view(np.uint32)[0])
+            assert first >> 31 == (1 if order == "by_channel" or c % 16 == 0 else 0)
+            tune(forced)
+            y = G.poison((n, oh, ow, k), torch.float32)
+            ws = G.workspace(glowmi.conv2d_packed_workspace_bytes(desc))
+            glowmi.conv2d_packed(xd, wd, planes, bd, y, desc, addend=add, act=wl.ACT_RELU, workspace=ws)
+            torch.cuda.synchronize()
+            assert glowmi.last_variant() == variant, (glowmi.last_variant(), variant)
+            assert torch.equal(y, plain), (reader, i, order)
+
+
+# k c r, and the batches and maps (with strides) that a program may move between without packing again
+MOVES = [((128, 128, 3), [(1, 14, 14, 1), (16, 28, 28, 1), (3, 33, 30, 2)]), ((120, 72, 3), [(1, 9, 9, 1), (9, 33, 45, 1), (2, 30, 30, 2)]), ((256, 64, 1), [(1, 7, 7, 1), (9, 20, 20, 2), (16, 40, 40, 1)]),
+         ((512, 512, 3), [(1, 7, 7, 1), (8, 14, 14, 1), (16, 28, 28, 1)])]
+
+
+@pytest.mark.parametrize("i", range(len(MOVES)))
+def test_planes_serve_their_filter_at_every_batch_and_map(i, knobs):
+    """Packed once with any of the descriptors, called with all of them, and under other tuning: always the filter's results."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    (k, c, r), places = MOVES[i]
+    gen = torch.Generator(device="cuda:0").manual_seed(37100 + i)
+    wd = torch.randn((k, r, r, c), generator=gen, device="cuda:0") / (r * r * c) ** 0.5
+    descs = [glowmi.ConvDesc(n, h, w, c, k, r, r, st, st, r // 2, r // 2, r // 2, r // 2, 1) for n, h, w, st in places]
+    inputs = [torch.randn((d.n, d.h, d.w, d.c), generator=gen, device="cuda:0") for d in descs]
+
+    def call(d, x, planes):
+        oh, ow = glowmi.conv_out_shape(d)
+        y = G.poison((d.n, oh, ow, d.k), torch.float32)
+        ws = G.workspace(glowmi.conv2d_packed_workspace_bytes(d) if planes is not None else glowmi.conv2d_workspace_bytes(d))
+        if planes is not None:
+            glowmi.conv2d_packed(x, wd, planes, None, y, d, act=wl.ACT_NONE, workspace=ws)
+        else:
+            glowmi.conv2d(x, wd, None, y, d, wl.ACT_NONE, ws)
+        torch.cuda.synchronize()
+        return y
+    knobs.set("F32_P3", 0)                                # the fp32 matrix cores, or their equal
+    knobs.set("F32_PATCH", 0)
+    refs = [call(d, x, None) for d, x in zip(descs, inputs)]
+    for packed_for in descs:
+        for pack_few in (1, 0):
+            glowmi.tuning_reset()
+            knobs.set("F32_FEW", pack_few)
+            knobs.set("F32_SHORT", pack_few)
+            planes = torch.empty(glowmi.conv2d_filter_planes_bytes(packed_for), dtype=torch.uint8, device="cuda:0")
+            glowmi.conv2d_pack_filter(wd, packed_for, planes)
+            glowmi.tuning_reset()
+            for d, x, ref in zip(descs, inputs, refs):
+                y = call(d, x, planes)
+                # two ways of adding 64 to 4608 products, each within about 2e-6 of the result's norm
+                assert float((y - ref).norm() / ref.norm()) < 4e-6, (i, glowmi.last_variant())
