@@ -868,17 +868,18 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
     // kernels of their own, no workspace
     if (dw_f32_applicable(p)) { pl.kernel = KERNEL_DW; return pl; }
     if (smallc_f32_applicable(p) && !p.addend) { pl.kernel = KERNEL_SMALLC; return pl; }
-    // 1x1 and 3x3 layers, the input cut tile by tile and the filter into the workspace; pointwise layers over few channels
-    // on many pixels are faster on the kernel that keeps the filter in registers
-    int form = -1;
-    double patch_us = 0.0;
-    if (allow_split && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p)))
-      form = patch_f32_form(p, &patch_us);
-    // the 3x3 tile kernels, which need the filter's planes given or room in the workspace for them: without a workspace, and
-    // where the patch kernel has no form or cannot read what was packed ahead (more than 1024 output channels) and the tiles
-    // fill the machine
+    // the 3x3 tile kernels, which need the filter's planes given or room in the workspace for them: where the patch kernel has
+    // no form or cannot read what was packed ahead (more than 1024 output channels) and the tiles fill the machine
     const bool filter_planes = p.w_packed != nullptr || (allow_split && p.allow_pack);
     const bool k3c64 = filter_planes && k3c64_f32_applicable(p), k3 = filter_planes && !k3c64 && k3_f32_applicable(p);
+    // 1x1 and 3x3 layers, the input cut tile by tile and the filter into the workspace; pointwise layers over few channels
+    // on many pixels are faster on the kernel that keeps the filter in registers.  Over planes given it uses no workspace, but
+    // a call that has none stays in fp32 arithmetic where it would without planes, the layers of the 3x3 tile kernels apart
+    const bool without = p.packed_is_cut && (k3c64 || k3 || knob_or(KNOB_F32_PATCH, 1) == 2);
+    int form = -1;
+    double patch_us = 0.0;
+    if ((allow_split || without) && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p)))
+      form = patch_f32_form(p, &patch_us);
     if (k3c64 && (form < 0 || knob_is_set(KNOB_F32_K3C64_MIN_TILES))) {
       pl.kernel = KERNEL_K3C64;
       pl.pack_bytes = k3c64_f32_pack_bytes(p);
@@ -893,7 +894,7 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
       pl.kernel = KERNEL_PATCH;
       pl.tile = form;
       pl.us = (float)patch_us;
-      pl.pack_bytes = p.packed_is_cut ? 0 : patch_f32_pack_bytes(p);
+      pl.pack_bytes = without ? 0 : p.packed_is_cut ? 256 : patch_f32_pack_bytes(p);
       // the workspace queries name what the kernel wants that would run otherwise: a buffer of that size serves either
       if (k3c64) pl.ask = k3c64_f32_pack_bytes(p);
       else if (k3) pl.ask = k3_f32_pack_bytes(p);

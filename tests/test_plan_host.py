@@ -37,6 +37,29 @@ def test_the_documented_switches_keep_every_layer_on_the_fp32_matrix_cores(probe
             assert plan.kernel not in PIECE_KERNELS, ((d.n, d.h, d.w, d.c, d.k, d.r), packed, plan)
 
 
+def test_planes_given_without_a_workspace_leave_a_layer_in_fp32_arithmetic(probe):
+    """The header: a caller that needs non-finite values kept apart passes no workspace; of layers with their filter's planes
+    given only 3x3 ones on large maps, which the 3x3 tile kernels take, run on the fp16 matrix cores then."""
+    rng = random.Random(3)
+    seen = set()
+    for _ in range(1500):
+        r = rng.choice([1, 3])
+        d = _desc(rng.choice([1, 2, 5, 16]), rng.randint(7, 100), rng.randint(7, 100), 8 * rng.randint(2, 80), 8 * rng.randint(2, 140), r,
+                  rng.choice([1, 1, 2]))
+        with_room = probe.conv(d, packed=True, workspace=glowmi.conv2d_packed_workspace_bytes(d))
+        assert with_room == probe.conv(d, packed=True), "the query covers the plan"
+        plan = probe.conv(d, packed=True, workspace=0)
+        assert plan.workspace == 0
+        if plan.kernel in ("patch", "k3", "k3c64"):
+            assert probe.conv(d, packed=True).kernel in ("patch", "k3", "k3c64")
+            # (a tile of theirs, 160 pixels x 128 channels, for six in ten CUs at least)
+            assert r == 3 and d.stride_h == 1 and d.n * d.h * d.w * d.k >= 3000000, ((d.n, d.h, d.w, d.c, d.k, d.r, d.stride_h), plan)
+        else:
+            assert plan.kernel not in ("p3", "fc_tiles"), plan
+        seen.add((with_room.kernel, plan.kernel))
+    assert ("patch", "tiled") in seen and ("patch", "patch") in seen
+
+
 # with an offset in the filter's codes another kernel may run than without, and the query does not know which
 QUERY_FC = [(627, 8004, 3204), (1024, 9216, 4096), (600, 4100, 2052), (65, 4100, 1000), (16, 2052, 1000)]
 
