@@ -31,8 +31,8 @@
  *      In fp32 arithmetic (matrix cores; vector units for depthwise layers and a few FullyConnected rows): small
  *    layers, depthwise ones, and calls without a workspace but for those that hold the filter on the chip as
  *    pieces and need none: pointwise layers on many pixels over 64, 128 or 256 channels or any multiple of four up to
- *    320 (three bf16 pieces per value, all 24 bits, six products) and 7x7 first layers on many pixels (two fp16
- *    pieces).
+ *    320 (three bf16 pieces per value, all 24 bits, six products) and 7x7 stride 2 first layers of 300 tiles of 4 x 16
+ *    pixels or more (two fp16 pieces, scaled by tile; a tile that no scale fits in fp32 arithmetic).
  *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the
  *    filter's planes given and none): 1x1 and 3x3 convolutions of ordinary size and more, large convolutions of
  *    other shapes, FullyConnected layers from 65 rows.  Operands are scaled by a power of two that brings the
@@ -50,9 +50,10 @@
  *    2^-38 * max|A| * max|W| * (reduction length).  Scaling an operand by a power of two scales the result by it and
  *    changes nothing else.
  *      With non-finite inputs the outputs they reach are non-finite (an infinity may come out as NaN); on the fp16
- *    matrix cores outputs they do not reach may turn into NaN as well, up to every output of the call (no scale fits
- *    what holds an infinity; where channels are no multiple of eight a pixel also meets its neighbour's values), but
- *    never into wrong finite values.  A caller that needs them apart passes no workspace.
+ *    matrix cores, first layers apart, outputs they do not reach may turn into NaN as well, up to every output of the
+ *    call (no scale fits what holds an infinity; where channels are no multiple of eight a pixel also meets its
+ *    neighbour's values), but never into wrong finite values.  A caller that needs them apart passes no workspace (and
+ *    for 3x3 layers no planes).
  *      The int8 entry points are exact integer arithmetic and reproducible bit for bit.
  */
 #ifndef GLOWMI_H
@@ -246,8 +247,7 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  *   glowmi_conv2d_packed / glowmi_fc_packed
  *       glowmi_conv2d_chain / glowmi_fc with `w_planes` = the planes made from this very `w` for a descriptor of the
  *       same filter: k, r, s, c and groups (or K, N); the library cannot check that and results are undefined otherwise.
- *       `w` itself
- *       is still required: layers that take a kernel which does not read planes use it, and ignore w_planes.
+ *       `w` itself is still required: layers that take a kernel which does not read planes use it, and ignore w_planes.
  *       w_planes = NULL makes the call the plain one.  chain of glowmi_conv2d_packed must not be NULL.
  *       GLOWMI_ERR_ALIGN for w_planes not 16-byte aligned, GLOWMI_ERR_UNSUPPORTED for w_planes != NULL on a
  *       shape without a plane form.

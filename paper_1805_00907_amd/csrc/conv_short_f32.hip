@@ -17,7 +17,8 @@
 // add at 59643 15.8 -> 8.9, 32->488 at 24336 20.0 -> 14.6 (from the patch kernel with a pass that cuts the filter).  Errors against
 // 64-bit sums are 0.36 to 0.99 of those kernels'.  What bounds it: with few channels the bytes, at two thirds of a large
 // copy's rate; from a hundred channels on the cut (6.5 instructions a value and slice) and the six MFMAs about equally.
-// Two tiles without an addend take 160 registers, so three wavefronts to a SIMD in one workgroup of twelve (224->56 26.4 us with
+// Results that infinities made NaN are formed again in fp32 arithmetic; looking for them costs 1 % (24->184 at 47524 pixels, whose
+// blocks are over soonest, 10.5 -> 11.0 us).  Two tiles without an addend take 160 registers, so three wavefronts to a SIMD in one workgroup of twelve (224->56 26.4 us with
 // two workgroups of eight that spill, 19.9 so); the forms with more tiles were slower that way.
 #include <hip/hip_runtime.h>
 
@@ -80,8 +81,7 @@ __global__ __launch_bounds__(64 * waves_of(NT, ADD), waves_per_simd(NT, ADD)) vo
 
   // ---- this lane's pixel of a block, and its loads of a trip
   const int ohow = p.oh * p.ow;
-  auto locate = [&](int b, bool live) {
-    int m = b * 32 + l32;
+  auto pixel_at = [&](int m) {
     if (m >= p.M) m = p.M - 1;                          // (results of such rows are never stored)
     int pix = m;
     if (p.stride_h != 1 || p.stride_w != 1) {           // uniform
@@ -90,8 +90,9 @@ __global__ __launch_bounds__(64 * waves_of(NT, ADD), waves_per_simd(NT, ADD)) vo
       const int oh = p.div_ow.div(rem);
       pix = (img * p.h + oh * p.stride_h) * p.w_ + (rem - oh * p.ow) * p.stride_w;
     }
-    return live ? (unsigned)pix * (unsigned)p.c * 4u : OOB;
+    return (unsigned)pix * (unsigned)p.c * 4u;
   };
+  auto locate = [&](int b, bool live) { return live ? pixel_at(b * 32 + l32) : OOB; };
   const int swapped = LINES ? l32 & 1 : 0;
   static_assert(T == 2, "the steps of a trip are the halves of a line");
   typedef v4f Raw[T][2];
@@ -156,7 +157,9 @@ __global__ __launch_bounds__(64 * waves_of(NT, ADD), waves_per_simd(NT, ADD)) vo
 
   const unsigned char* w_lane = wlds + l32 * pitch + 16 * lh;
   const unsigned row_bytes = (unsigned)p.k * 4u;
-  const float act_lo = p.act_lo, act_hi = p.act_hi;
+  // (without an activation the bounds are NaNs, between which every value is the median and a NaN stays one: [-inf, inf] would
+  // make it -inf)
+  const float act_lo = p.act == 1 ? p.act_lo : __builtin_nanf(""), act_hi = p.act == 1 ? p.act_hi : __builtin_nanf("");
   v16f acc[NT];
   auto multiply = [&](Raw& r, int trip) {
     if (LINES) unswap(r);
@@ -226,17 +229,59 @@ __global__ __launch_bounds__(64 * waves_of(NT, ADD), waves_per_simd(NT, ADD)) vo
     multiply(a, walk.trips - 1);
 
     // rows past M and channels past k fall outside the output's range and the checked stores drop them (no branch around a
-    // store: the wait for the loads ahead of it would become one for the stores)
+    // store: the wait for the loads ahead of it would become one for the stores).  Results that `redo` names are not stored.
+    unsigned redo[(NT + 1) / 2];                        // bit e + 16 (t % 2) of word t / 2: this lane's result e of tile t
+    auto store_block = [&](auto checked) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float bv = blds[32 * t + l32];
-      unsigned lane_off = at[t];
-      asm volatile("" : "+v"(lane_off));                // keep the per-register row offsets scalar
+      for (int t = 0; t < NT; ++t) {
+        const float bv = blds[32 * t + l32];
+        unsigned lane_off = at[t];
+        asm volatile("" : "+v"(lane_off));              // keep the per-register row offsets scalar
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float v = acc[t][e] + bv + (ADD ? add[t][e] : 0.f);
-        const float out = clamp_act(v, act_lo, act_hi);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, out), rsrc_y, lane_off + (unsigned)((e >> 2) * 8 + (e & 3)) * row_bytes, 0, 0);
+        for (int e = 0; e < 16; ++e) {
+          const float v = acc[t][e] + bv + (ADD ? add[t][e] : 0.f);
+          const float out = clamp_act(v, act_lo, act_hi);
+          const unsigned off = lane_off + (unsigned)((e >> 2) * 8 + (e & 3)) * row_bytes;
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, out), rsrc_y, checked && (redo[t / 2] >> (16 * (t % 2) + e) & 1) ? OOB : off, 0, 0);
+        }
+      }
+    };
+    // An infinity's lower pieces are NaN, and so is what it reaches: such results once more, in fp32 arithmetic.
+    bool nans = false;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) nans |= __builtin_isunordered(acc[t][e], acc[t][e + 1]);   // either is one
+    if (__builtin_expect(!__any(nans), 1)) {
+      store_block(std::false_type{});
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (t % 2 == 0) redo[t / 2] = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          redo[t / 2] |= acc[t][e] != acc[t][e] ? 1u << (16 * (t % 2) + e) : 0u;
+          asm volatile("" : "+v"(redo[t / 2]));         // one comparison after the other: kept for the stores they take 100 registers
+        }
+      }
+      store_block(std::true_type{});
+      int who = tid;
+      asm volatile("" : "+v"(who));                     // nothing of this is kept in registers meanwhile
+#pragma unroll 1
+      for (int i = 0; i < 16 * NT; ++i) {
+        const bool mine = (NT > 2 && i >= 32 ? redo[(NT - 1) / 2] : redo[0]) >> (i & 31) & 1;
+        if (!__any(mine)) continue;
+        const int e = i & 15, col = 32 * (i >> 4) + (who & 31), ch = slice * BN + col, m = blk * 32 + (e >> 2) * 8 + (who >> 5 & 1) * 4 + (e & 3);
+        const unsigned x_at = pixel_at(m), w_at = (unsigned)ch * (unsigned)p.c * 4u;
+        const unsigned y_at = mine && m < p.M && ch < p.k ? (unsigned)m * row_bytes + (unsigned)ch * 4u : OOB;
+        float v = 0.f;
+#pragma unroll 1
+        for (int c = 0; c < p.c; ++c)
+          v = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_x, x_at + 4u * (unsigned)c, 0, 0)),
+                             __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_w, w_at + 4u * (unsigned)c, 0, 0)), v);
+        v += blds[col];
+        if (ADD) v += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_add, y_at, 0, 0));
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, clamp_act(v, act_lo, act_hi)), rsrc_y, y_at, 0, 0);
       }
     }
 #pragma unroll

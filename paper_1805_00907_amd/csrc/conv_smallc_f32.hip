@@ -441,7 +441,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   // reads of four bytes and cut everything twice: 5 us of batch 8's 20.)
   v8h wfrag[G::STEPS][2];
   int se_w;
-  bool finite;
+  bool w_finite;
   {
     const __amdgpu_buffer_rsrc_t rsrc_w =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, (int)p.w_bytes, 0x00020000);
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     __syncthreads();
     const unsigned w_max_bits = max_of_eight(maxw);
     se_w = scale_exponent(w_max_bits);
-    finite = w_max_bits < 0x7f800000u;
+    w_finite = w_max_bits < 0x7f800000u;
 #pragma unroll
     for (int i = 0; i < G::W_LOADS; ++i) {
       const int idx = tid + i * SC_THREADS;
@@ -499,9 +499,10 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   }
   __syncthreads();
   int se_x;                                              // scale exponent of the patch in `buf`
+  bool finite;                                           // whether it and the filter hold neither infinities nor NaNs
   {
     const unsigned m = max_of_eight(maxw);
-    finite = finite && m < 0x7f800000u;
+    finite = w_finite && m < 0x7f800000u;
     se_x = scale_exponent(m);
   }
   store_patch(here, 0, se_x);
@@ -548,18 +549,47 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
 
     // ---- the next tile's patch: its largest magnitude, then (everyone is done with the other buffer since the
     // barrier that ended the last tile) scaled, cut and written while this tile's results are stored
-    const ScaleBack sb = scale_back_of(se_x, se_w, finite);
+    const ScaleBack sb = scale_back_of(se_x, se_w, true);
+    const bool pieces_hold = finite;
     if (has_next) {
       clear_neighbours(in, next);
       const unsigned share = stage_max(in);
       if (lane == 0) maxw[wave] = share;
       __syncthreads();
       const unsigned m = max_of_eight(maxw);
-      finite = finite && m < 0x7f800000u;
+      finite = w_finite && m < 0x7f800000u;
       se_x = scale_exponent(m);
       store_patch(in, buf ^ 1, se_x);
     }
 
+    // ---- a tile that no scale fits: in fp32 arithmetic, an output at a time, so that each has what its own inputs give (that
+    // this is here costs the others 1 to 2 %, batch 8 15.7 -> 16.0 us)
+    if (__builtin_expect(!pieces_hold, 0)) {             // uniform
+      int at = tile;
+      asm volatile("" : "+s"(at));                       // nothing of this is kept in registers meanwhile
+      const int tx = at % tiles_x, t2 = at / tiles_x, ty = t2 % tiles_y, img = t2 / tiles_y;
+#pragma unroll 1
+      for (int o = 0; o < 16 * NB; ++o) {
+        const int oh = ty * TH + wpix * 2 * NB + (o >> 4) * 2 + (o >> 3 & 1), ow = tx * TW + 4 * lhalf + (o & 3) + 8 * (o >> 2 & 1);
+        float v = 0.f;
+#pragma unroll 1
+        for (int r = 0; r < R; ++r)
+#pragma unroll 1
+          for (int q = 0; q < G::RUN; ++q) {
+            const int ih = oh * STRIDE - p.pad_t + r, fx = (ow * STRIDE - p.pad_l) * C + q;
+            const bool inside = (unsigned)ih < (unsigned)p.h && (unsigned)fx < (unsigned)row_floats;
+            const unsigned x_at = inside ? 4u * (unsigned)((img * p.h + ih) * row_floats + fx) : OOB;
+            const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_x, x_at, 0, 0));
+            const float w = ch_ok ? static_cast<const float*>(p.w)[ch * G::K + r * G::RUN + q] : 0.f;
+            v = inside ? __builtin_fmaf(x, w, v) : v;    // (padding meets no filter value: an infinity there is not multiplied)
+          }
+        v += bv;
+        if (p.act == 1) v = clamp_act(v, p.act_lo, p.act_hi);
+        const bool ok = ch_ok && oh < p.oh && ow < p.ow;
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), rsrc_y,
+                                              ok ? (unsigned)(((img * p.oh + oh) * p.ow + ow) * p.k + ch) * 4u : OOB, 0, 0);
+      }
+    } else
     // ---- epilogue of this tile: as in the kernel above
     {
       const int tx = tile % tiles_x;

@@ -89,3 +89,41 @@ def test_conv_short_f32_non_finite(value, knobs):
     assert not np.isfinite(got[0, 3, 4]).any()
     got[0, 3, 4] = clean[0, 3, 4]
     assert np.array_equal(got, clean)
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4])
+@pytest.mark.parametrize("add", [False, True])
+def test_conv_short_f32_non_finite_results_are_those_of_fp32_arithmetic(tiles, add, knobs):
+    """Infinities keep their sign, inf - inf and 0 * inf are NaN, values that bf16 would round to infinity stay finite; in the
+    input, in the filter, at the ends of blocks and tiles, with the add link in place."""
+    G = _gpu()
+    knobs.set("F32_SHORT", 2)
+    knobs.set("F32_SHORT_FORM", tiles)
+    rng = np.random.default_rng(42700 + tiles)
+    c, k = 72, 130
+    x = rng.uniform(-1, 1, size=(1, 9, 15, c)).astype(np.float32)
+    wt = (rng.uniform(0.1, 1, size=(k, 1, 1, c)) * rng.choice([-1, 1], size=(k, 1, 1, c))).astype(np.float32)
+    x[0, 0, 0, 0] = np.inf
+    x[0, 2, 1, 71] = -np.inf
+    x[0, 2, 2, [3, 40]] = np.inf, -np.inf                # inf of either sign, or NaN
+    x[0, 5, 7, 33] = np.nan
+    x[0, 8, 14, 5] = np.finfo(np.float32).max            # one step below 2^128: bf16 rounds it up
+    wt[77, 0, 0, 12] = -np.inf
+    wt[129, 0, 0, 0] = 0.0                               # 0 * inf
+    wt[3, 0, 0, 0] = 0.5                                 # pieces that are zero
+    extra = rng.uniform(-1, 1, size=(1, 9, 15, k)).astype(np.float32)
+    desc = G.make_desc(x.shape, wt.shape, (1, 1), (0, 0, 0, 0), 1)
+    with np.errstate(all="ignore"):
+        ref = (x.astype(np.float64)[0, :, :, None, :] * wt[None, None, :, 0, 0, :]).sum(axis=-1)[None] + (extra if add else 0)
+    import torch
+    import paper_1805_00907_amd as glowmi
+    y = torch.from_numpy(extra).to("cuda:0") if add else G.poison(ref.shape, torch.float32)
+    glowmi.conv2d_chain(G.dev(x), G.dev(wt), None, y, desc, addend=y if add else None, act=wl.ACT_NONE, workspace=None)
+    torch.cuda.synchronize()
+    assert glowmi.last_variant().startswith("conv_short_f32"), glowmi.last_variant()
+    got = y.cpu().numpy()
+    finite = np.isfinite(ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~finite & ~np.isnan(ref)], ref[~finite & ~np.isnan(ref)])
+    mag = np.abs(np.where(np.isfinite(x), x, 0)).astype(np.float64)[0, :, :, None, :] * np.abs(np.where(np.isfinite(wt), wt, 0))[None, None, :, 0, 0, :]
+    # 72 products of 24 bits: 73 roundings at most
+    assert np.all(np.abs(got[finite] - ref[finite]) <= 73 * 2.0 ** -24 * (mag.sum(axis=-1)[None] + np.abs(extra))[finite])

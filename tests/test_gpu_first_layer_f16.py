@@ -43,3 +43,27 @@ def test_first_layer_f16_many_tiles(knobs):
 def test_first_layer_f16_is_planned(n, taken):
     """A map of 50 tiles of 4 x 16 pixels."""
     assert _check(_gpu(), n, 80, 160, 64, (3, 3, 3, 3)).endswith("f16x3") == taken
+
+
+@pytest.mark.parametrize("place", ["input", "filter"])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_first_layer_f16_non_finite(place, value, knobs):
+    """A value that no scale fits: the outputs it reaches are what fp32 arithmetic gives, all others as close as ever, those of its
+    tile and of the tiles that its workgroup takes later among them."""
+    G = _gpu()
+    knobs.set("F32_SMALLC_BF16", 1)
+    rng = np.random.default_rng(41500)
+    x = rng.uniform(-1, 1, size=(31, 46, 101, 3)).astype(np.float32)
+    wt = (rng.uniform(0.1, 1, size=(40, 7, 7, 3)) / 12).astype(np.float32)
+    b = rng.uniform(-0.1, 0.1, size=(40,)).astype(np.float32)
+    if place == "input":
+        x[0, 0, 0, 1] = x[2, 20, 50, 2] = x[30, 45, 100, 0] = value
+    else:
+        wt[17, 3, 2, 1] = value
+    ref = oracle.conv2d_f32(x, wt, b, (2, 2), (3, 3, 3, 3), 1, act=wl.ACT_NONE)
+    got, variant = G.gpu_conv2d_f32(x, wt, b, G.make_desc(x.shape, wt.shape, (2, 2), (3, 3, 3, 3), 1), wl.ACT_NONE)
+    assert variant.endswith("f16x3")
+    finite = np.isfinite(ref)
+    assert 0 < (~finite).sum() < ref.size // 30
+    assert np.array_equal(got[~finite], ref[~finite], equal_nan=True)
+    G.assert_close_f32(np.where(finite, got, 0), np.where(finite, ref, 0), f"{place} {value}")
