@@ -154,7 +154,7 @@ struct Plan {
   int slabs_per_split;
   size_t pack_bytes = 0;  // workspace bytes for repacked operands, ahead of the partial sums (KERNEL_P3)
   float us = 0;         // KERNEL_PATCH, KERNEL_FEW, KERNEL_SHORT: the microseconds it is expected to take
-  bool as_small = false; // KERNEL_FEW: as a form of conv_small_f32, whose layer it is
+  bool was_small = false; // KERNEL_FEW: in place of conv_small_f32 (fp32)
   size_t stood_in_for = 0; // KERNEL_FEW, KERNEL_FC_FEW, KERNEL_SHORT, which use none: the workspace of the kernel that would have run
   size_t ask = 0;       // what a kernel of the layer's that this one stands in for would want, where that is more
 };
@@ -180,7 +180,7 @@ int conv_small_f32_splits(const Problem& p);   // > 1: the split form of that ke
 // fp32 convolution on few pixels in one launch, any reduction (conv_few_f32.hip): the tile form to run it in and the
 // microseconds it is expected to take, -1: not a layer for it.
 int few_f32_form(const Problem& p, double* us);
-hipError_t launch_few_f32(const Problem& p, int form, bool as_small, hipStream_t stream, const char** variant);
+hipError_t launch_few_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // fp32 pointwise convolution of any channel counts in fours on many pixels (conv_short_f32.hip): form and expected microseconds.
 int short_f32_form(const Problem& p, double* us);
 hipError_t launch_short_f32(const Problem& p, int form, hipStream_t stream, const char** variant);

@@ -712,7 +712,7 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
 // Convolutions on few pixels: conv_few_f32 in place of the tiled kernel, the sliced form of conv_small_f32 or the patch kernel
 // where its estimate is lower than theirs, fitted like its own to 840 layers (tiled: median error 4 %; sliced: 5 %).  Choosing
 // so costs 1.5 % over the best of both for each layer; the margin covers what the estimates miss.
-// Of conv_small_f32 in one launch it is a form: 124 of 170 such layers move and take 0.83 of the time (1x1 512->128 at 128 pixels
+// Of the layers of conv_small_f32 in one launch 124 of 170 move and take 0.83 of the time (1x1 512->128 at 128 pixels
 // 7.6 -> 4.8 us, 3x3 64->64 at 972 8.1 -> 5.3, 48->48 at 1125 7.1 -> 4.8; the worst 1.06), those with many tiles for their
 // reduction stay (1x1 192->48 at 4080 5.3, 6.0 here; 3x3 24->384 at 450 5.4 and 5.7).
 Plan few_or(const Problem& p, const Plan& rest) {
@@ -744,7 +744,7 @@ Plan few_or(const Problem& p, const Plan& rest) {
   }
   Plan pl = instead_of(p, rest, KERNEL_FEW, form);
   pl.us = (float)us;
-  pl.as_small = mode != 2 && rest.kernel == KERNEL_SMALL;
+  pl.was_small = mode != 2 && rest.kernel == KERNEL_SMALL;
   return pl;
 }
 // Pointwise convolutions on many pixels: conv_short_f32 in place of the tiled kernel, the patch kernel or conv_few_f32 where its
@@ -755,7 +755,7 @@ Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode != 2) {
     const bool patch = rest.kernel == KERNEL_PATCH && knob_or(KNOB_F32_PATCH, 1) != 2;
-    if (!(rest.kernel == KERNEL_TILED || patch || (rest.kernel == KERNEL_FEW && !rest.as_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= 128))) return rest;
+    if (!(rest.kernel == KERNEL_TILED || patch || (rest.kernel == KERNEL_FEW && !rest.was_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= 128))) return rest;
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_PATCH_TILE, KNOB_F32_FEW_TILE})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
   }
@@ -804,8 +804,8 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
 
 // FullyConnected with few rows or a small matrix: fc_few_f32 in place of the weight stream, the one-launch kernel of up to 64
 // rows, the tiled kernel and fc_tiles_f32 where its estimate is lower than theirs (200 calls: choosing so costs 1.4 % over the
-// best for each).  One row on few columns stays with fc_rows_f32, as fast.  Matrices under 96 KB stay where they were: callers
-// (the tests among them) rely on which kernel those run.
+// best for each).  One row on few columns stays with fc_rows_f32, as fast, and so do up to sixteen rows of fewer than 256
+// columns of input with the weight stream, which is one launch there (42 calls of up to 96 KB of weights 3.7 and 3.7 us).
 Plan fc_few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FC_FEW, 1);         // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
@@ -815,9 +815,9 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW,
                          KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_F32_FC_ROWS, KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    if (p.w_bytes < (96u << 10)) return rest;
     const double depth = 1e-3 * p.Kgemm;
     if (rest.kernel == KERNEL_SKINNY16) {
+      if (p.Kgemm < 256) return rest;
       // a large matrix is a stream that wants every CU and whole lines: with the weights beyond the last-level cache 16x4096x4096 17.7
       // us there, 25.1 here, 8x9216x4096 30 and 46, 16x25088x4096 75 and 141
       if (p.w_bytes > (24u << 20)) return rest;
@@ -1048,7 +1048,7 @@ hipError_t launch_f32(const Problem& p_in, const Plan& plan, hipStream_t stream,
     case KERNEL_K3: return launch_k3_f32(p_in, stream, variant);
     case KERNEL_FC_ROWS: return launch_fc_rows_f32(p_in, stream, variant);
     case KERNEL_SHORT: return launch_short_f32(p_in, plan.tile, stream, variant);
-    case KERNEL_FEW: return launch_few_f32(p_in, plan.tile, plan.as_small, stream, variant);
+    case KERNEL_FEW: return launch_few_f32(p_in, plan.tile, stream, variant);
     case KERNEL_FC_FEW: return launch_fc_few_f32(p_in, plan.tile, stream, variant);
     case KERNEL_PATCH: return launch_patch_f32(p_in, plan.tile, stream, variant);
     default: break;

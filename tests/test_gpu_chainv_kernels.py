@@ -42,7 +42,13 @@ F32 = {
     "patch_3x3": ({"F32_PATCH": 2, **NO_K3}, (2, 9, 13, 40, 24, 3, 1, 1, 1), "conv_patch_f32", True),
     "patch_3x3s2": ({"F32_PATCH": 2, **NO_K3}, (2, 9, 13, 40, 24, 3, 2, 1, 1), "conv_patch_f32", True),
     "patch_1x1": ({"F32_PATCH": 2}, (2, 11, 9, 72, 100, 1, 1, 0, 1), "conv_patch_f32", True),
-    "small": ({"F32_PATCH": 0}, (1, 7, 7, 48, 48, 3, 1, 1, 1), "conv_small_f32", False),
+    "small": ({"F32_PATCH": 0, "F32_FEW": 0}, (1, 7, 7, 48, 48, 3, 1, 1, 1), "conv_small_f32", False),
+    "few0": ({"F32_FEW": 2, "F32_FEW_TILE": 0}, (1, 7, 7, 48, 50, 3, 1, 1, 1), "conv_few_f32_16x16w4", True),
+    "few1": ({"F32_FEW": 2, "F32_FEW_TILE": 1}, (1, 9, 8, 64, 36, 3, 2, 1, 1), "conv_few_f32_16x16w8", True),
+    "few2": ({"F32_FEW": 2, "F32_FEW_TILE": 2}, (2, 7, 8, 21, 40, 3, 1, 1, 1), "conv_few_f32_16x32w4", True),
+    "short1": ({"F32_SHORT": 2, "F32_SHORT_FORM": 1}, (2, 9, 13, 72, 50, 1, 1, 0, 1), "conv_short_f32_32x32", True),
+    "short2": ({"F32_SHORT": 2, "F32_SHORT_FORM": 2}, (2, 9, 13, 96, 70, 1, 2, 0, 1), "conv_short_f32_32x64", True),
+    "short4": ({"F32_SHORT": 2, "F32_SHORT_FORM": 4}, (1, 11, 13, 20, 130, 1, 1, 0, 1), "conv_short_f32_32x128", True),
     "small_split": ({"F32_PATCH": 0, "F32_SMALL_MIN_WGS": 1}, (1, 7, 7, 512, 96, 3, 1, 1, 1), "conv_small_f32", True),
     "tile0_long": ({"F32_TILE": 0, "F32_SPLIT": 1}, (1, 6, 6, 2080, 33, 1, 1, 0, 1), "igemm_f32_64x64w4", True),
     "tile0_split": ({"F32_TILE": 0, "F32_SPLIT": 4}, (1, 6, 6, 480, 33, 3, 1, 1, 1), "igemm_f32_64x64w4", True),
@@ -104,7 +110,7 @@ def test_folded_lists_f32(name, knobs):
             G.assert_close_f32(y.cpu().numpy(), ref, what)
 
 
-@pytest.mark.parametrize("name", ["dw_s1", "first_fp32", "pw64", "small", "tile1"])
+@pytest.mark.parametrize("name", ["dw_s1", "first_fp32", "pw64", "small", "few0", "few2", "tile1"])
 def test_folded_clamp_takes_nan_and_infinities_as_the_ops_in_turn(name, knobs):
     """On kernels that multiply in fp32: a NaN becomes the lower bound (the result of max, then min), an infinity the bound
     on its side, as where the ops run one by one."""
@@ -148,7 +154,13 @@ I8 = {
     "wide64": ({"I8_TILE": 5}, (1, 15, 15, 80, 140, 3, 1, 1, 1), 3, "igemm_i8_wide", True),
     "wide_split": ({"I8_TILE": 4, "I8_WIDE_SPLIT": 3}, (1, 15, 15, 160, 140, 3, 1, 1, 1), 0, "igemm_i8_wide", True),
     "small": ({"I8_SMALL_MAX_TILES": 100000}, (1, 13, 9, 40, 50, 3, 1, 1, 1), -5, "conv_small_i8", True),
-    "small_split": ({}, (1, 7, 7, 512, 96, 3, 1, 1, 1), 0, "conv_small_i8", True),
+    "small_split": ({"I8_FEW": 0}, (1, 7, 7, 512, 96, 3, 1, 1, 1), 0, "conv_small_i8", True),
+    "few0": ({"I8_FEW": 2, "I8_FEW_TILE": 0}, (1, 7, 7, 128, 50, 3, 1, 1, 1), 0, "conv_few_i8_16x16w4", True),
+    "few1": ({"I8_FEW": 2, "I8_FEW_TILE": 1}, (1, 9, 8, 100, 36, 3, 2, 1, 1), 5, "conv_few_i8_16x16w8", True),
+    "few2": ({"I8_FEW": 2, "I8_FEW_TILE": 2}, (2, 7, 5, 21, 40, 3, 1, 1, 1), 0, "conv_few_i8_16x32w4", True),
+    "short1": ({"I8_SHORT": 2, "I8_SHORT_FORM": 1}, (2, 9, 13, 72, 52, 3, 1, 1, 1), 0, "conv_short_i8_32x32", True),
+    "short2": ({"I8_SHORT": 2, "I8_SHORT_FORM": 2}, (2, 9, 13, 128, 72, 1, 2, 0, 1), 0, "conv_short_i8_32x64", True),
+    "short_odd": ({"I8_SHORT": 2, "I8_SHORT_FORM": 2}, (2, 9, 13, 23, 70, 1, 1, 0, 1), 0, "conv_short_i8_32x64", False),
     "tile0": ({"I8_TILE": 0}, (1, 13, 9, 40, 50, 3, 1, 1, 1), 4, "igemm_i8_64x64w4", True),
     "tile0_split": ({"I8_TILE": 0, "I8_SPLIT": 3}, (1, 6, 6, 480, 33, 3, 1, 1, 1), 0, "igemm_i8_64x64w4", True),
     "tile1": ({"I8_TILE": 1}, (1, 13, 13, 40, 70, 3, 1, 1, 1), 0, "igemm_i8_128x64w8", True),

@@ -49,11 +49,11 @@ def test_conv_few_i8(shape, tile, knobs):
         args = (x, xs, -9, wt, ws, w_off, b)
         ref = oracle.qconv2d(*args, ys, 3, st, pd, 1, act=act)
         got, variant = G.gpu_qconv2d(x, wt, b, qp, desc, act)
-        assert variant.startswith("conv_small_i8_16x"), variant
+        assert variant.startswith("conv_few_i8_16x"), variant
         G.assert_equal_i8(got, ref, f"{shape} w_off {w_off} [{variant}]")
         add = rng.integers(-128, 128, size=ref.shape, dtype=np.int8)
         ref = oracle.qconv2d_add(*args, add, 0.05, 11, ys, 3, st, pd, 1, act=act)
         for in_place in (False, True):
             got, variant = G.gpu_qconv2d_chain(x, wt, b, qp, add, 0.05, 11, desc, act, in_place=in_place)
-            assert variant.startswith("conv_small_i8_16x"), variant
+            assert variant.startswith("conv_few_i8_16x"), variant
             G.assert_equal_i8(got, ref, f"{shape} add w_off {w_off} in place {in_place} [{variant}]")

@@ -35,8 +35,9 @@ TAKEN = [True, True, True, True, False, True, True, False, True, True]
 
 
 @pytest.mark.parametrize("i", range(len(SMALL_CONV)))
-def test_conv2d_small_f32(i):
+def test_conv2d_small_f32(i, knobs):
     G = _gpu()
+    knobs.set("F32_FEW", 0)                 # which takes most of these layers
     n, h, w, c, k, r, s, st, pd = SMALL_CONV[i]
     rng = np.random.default_rng(9700 + i)
     x = rng.uniform(-1, 1, size=(n, h, w, c)).astype(np.float32)
@@ -53,8 +54,9 @@ def test_conv2d_small_f32(i):
     G.assert_close_f32(got, oracle.conv2d_f32(x, wt, None, st, pd, 1, act=wl.ACT_NONE), f"small conv {i} without bias")
 
 
-def test_conv2d_small_f32_not_taken_with_many_tiles_or_odd_channels():
+def test_conv2d_small_f32_not_taken_with_many_tiles_or_odd_channels(knobs):
     G = _gpu()
+    knobs.set("F32_FEW", 0)
     rng = np.random.default_rng(9790)
     for shape in [(8, 56, 56, 64, 64, 1, 1), (1, 20, 20, 20, 16, 3, 3), (1, 20, 20, 16, 18, 3, 3)]:
         n, h, w, c, k, r, s = shape

@@ -137,7 +137,7 @@ def test_launch_on_a_caller_stream_and_back_to_back():
 
 
 @pytest.mark.parametrize("case", ["fc_skinny16", "conv_small", "conv_tiled_split", "fc_tiled"])
-def test_bias_at_a_four_byte_address(case):
+def test_bias_at_a_four_byte_address(case, knobs):
     """The ABI asks only 4-byte alignment of the bias: every kernel family reads it correctly from an
     address 4 bytes past a 16-byte boundary."""
     import torch
@@ -152,6 +152,9 @@ def test_bias_at_a_four_byte_address(case):
         assert view.data_ptr() % 16 == 4
         return view
 
+    for name, value in {"fc_skinny16": {"F32_FC_FEW": 0}, "conv_small": {"F32_FEW": 0, "F32_PATCH": 0},
+                        "conv_tiled_split": {"F32_TILE": 0, "F32_SPLIT": 8}, "fc_tiled": {"F32_TILE": 0}}[case].items():
+        knobs.set(name, value)                           # the kernel that the case names
     if case in ("fc_skinny16", "fc_tiled"):
         M, K, N = (8, 512, 264) if case == "fc_skinny16" else (70, 4096, 96)
         a = rng.uniform(-1, 1, size=(M, K)).astype(np.float32)
@@ -161,7 +164,7 @@ def test_bias_at_a_four_byte_address(case):
         glowmi.fc(G.dev(a), G.dev(w), shifted(b), y, M, K, N, wl.ACT_RELU, G.workspace(glowmi.fc_workspace_bytes(M, K, N)))
         torch.cuda.synchronize()
         variant = glowmi.last_variant()
-        assert ("skinny16" in variant) == (case == "fc_skinny16"), variant
+        assert variant.startswith("fc_skinny16_f32" if case == "fc_skinny16" else "igemm_f32"), variant
         G.assert_close_f32(y.cpu().numpy(), oracle.fc_f32(a, w, b, act=wl.ACT_RELU), f"{case} [{variant}]")
         return
     if case == "conv_small":
@@ -177,4 +180,5 @@ def test_bias_at_a_four_byte_address(case):
     glowmi.conv2d(G.dev(x), G.dev(wt), shifted(b), y, desc, wl.ACT_RELU, G.workspace(glowmi.conv2d_workspace_bytes(desc)))
     torch.cuda.synchronize()
     variant = glowmi.last_variant()
+    assert variant.startswith("conv_small_f32" if case == "conv_small" else "igemm_f32"), variant
     G.assert_close_f32(y.cpu().numpy(), oracle.conv2d_f32(x, wt, b, (1, 1), pd, 1, act=wl.ACT_RELU), f"{case} [{variant}]")

@@ -68,6 +68,7 @@ def test_fc_small_f32_bias_at_a_four_byte_address_and_output_guards():
 
 def test_fc_small_f32_is_the_planners_choice_from_17_rows_and_can_be_switched_off(knobs):
     G = _gpu()
+    knobs.set("F32_FC_FEW", 0)                # which takes small matrices and few rows
     layer = wl.FcLayer("fs", 40, 256, 64)
     a, w, b = wl.fc_inputs_f32(layer, 12200)
     got, variant = G.gpu_fc_f32(a, w, b, wl.ACT_RELU)

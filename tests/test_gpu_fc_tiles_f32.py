@@ -53,13 +53,14 @@ def test_long_reductions_are_summed_in_short_runs(rows, knobs):
 
 @pytest.mark.parametrize("shape,taken", [((64, 512, 256), False), ((65, 256, 64), True), ((1000, 1024, 512), True),
                                          ((256, 4096, 4096), True), ((150, 301, 77), True), ((1024, 4096, 4096), False)], ids=str)
-def test_which_calls_take_the_kernel(shape, taken):
+def test_which_calls_take_the_kernel(shape, taken, knobs):
     """From 65 rows, up to where the contraction over planes is faster; only with the workspace the query names.  The call
     that works in the static buffer runs what the call with a workspace runs."""
     import torch
     import gpu_util as G
     import paper_1805_00907_amd as glowmi
     m, k, n = shape
+    knobs.set("F32_FC_FEW", 0)               # which takes small matrices and few rows
     a, w = torch.randn((m, k), device="cuda:0"), torch.randn((k, n), device="cuda:0")
     y = G.poison((m, n), torch.float32)
     need = glowmi.fc_workspace_bytes(m, k, n)
@@ -90,6 +91,7 @@ def test_switching_piece_contractions_off_covers_the_kernel(shape, knobs):
     import paper_1805_00907_amd as glowmi
     m, k, n = shape
     knobs.set("F32_P3", 0)
+    knobs.set("F32_FC_FEW", 0)
     a, w = torch.randn((m, k), device="cuda:0"), torch.randn((k, n), device="cuda:0")
     y = G.poison((m, n), torch.float32)
     glowmi.fc(a, w, None, y, m, k, n, wl.ACT_NONE, G.workspace(glowmi.fc_workspace_bytes(m, k, n)))
