@@ -744,13 +744,8 @@ int patch_f32_form(const Problem& p, double* us_out) {
   const double bytes = (double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k;
   double other = p.r == 3 ? 8.0 + us / rate : 6.0 + (us / rate > bytes / 3e6 ? us / rate : bytes / 3e6);
   if (small && 3.5 + us / 32.0 < other) other = 3.5 + us / 32.0;
-  // with planes given the contraction over them, where deep reductions meet few pixels and many channels (fitted to 37 layers;
-  // 3x3 stride 2 416 -> 1000 on 24x38 at batch 2 33 us there, 40 here)
-  if (p.packed_is_cut && p3_f32_applicable(p)) {
-    const double padded = 2e-9 * ((p.M + 127) / 128 * 128) * ((p.k + 127) / 128 * 128) * (double)p.Kgemm;
-    const double planes = 14.0 + 4.2 * padded + 0.4e-6 * p.x_bytes;
-    if (planes < other) other = planes;
-  }
+  // (The contraction over planes does not come into it: of 60 deep 3x3 stride 2 layers with planes given it takes 0.69 to 1.42,
+  // at the mean 1.03 of the time, and lies up to 1.32 times as far from 64-bit sums, 1.12 at the median.)
   // (With the filter cut ahead many a small pointwise layer is as fast on either, 5 to 6 us: those stay.)
   // (a pointwise layer of few channels, which fill a quarter of a chunk, longer: 16->824 stride 2 at 2312 pixels 6.5 us with tiles, 7.6)
   const double margin = p.packed_is_cut && p.r == 1 ? (p.c < 32 ? 4.5 : 3.2) : p.r == 1 || small ? 1.6 : 0.5;

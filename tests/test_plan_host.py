@@ -78,3 +78,14 @@ def test_the_int8_queries_cover_a_filter_with_an_offset(probe, w_offset):
         for addend in (False, True):
             plan = probe.conv(d, quantized=True, addend=addend, w_offset=w_offset)
             assert plan.workspace <= glowmi.qconv2d_workspace_bytes(d), ((d.n, d.h, d.w, d.c, d.k, d.r), plan)
+
+
+def test_planes_given_do_not_move_a_layer_of_the_patch_kernel_to_the_contraction_over_planes(probe):
+    """That one lies up to 1.3 times as far from 64-bit sums."""
+    rng = random.Random(4)
+    for _ in range(1500):
+        r = rng.choice([1, 3, 3])
+        d = _desc(rng.randint(1, 24), rng.randint(7, 60), rng.randint(7, 60), 8 * rng.randint(2, 90), 8 * rng.randint(2, 128), r,
+                  rng.choice([1, 2]))
+        if probe.conv(d).kernel == "patch":
+            assert probe.conv(d, packed=True).kernel != "p3", ((d.n, d.h, d.w, d.c, d.k, d.r, d.stride_h),)
