@@ -23,6 +23,10 @@
 //   - patch rows are kept TW + 4 pixels apart and a pixel's four 16-byte chunks are stored at
 //     chunk ^ ((key / 4) % 4), key = TW * patch row + patch column, which spreads the tile rows a fragment read
 //     touches over all bank groups whatever the tap.
+// What is left to this kernel: the patch kernel (conv_patch_f32.hip) is as fast or faster and two to three times closer to 64-bit sums
+// wherever it reads or cuts the filter itself, so the planner comes here only for planes made ahead of filters with more than
+// 1024 output channels, whose scales do not fit behind the planes in that kernel's order: calls without a workspace, and ones with it on
+// maps that fill the tiles to 85 % (conv_k3v_f32.hip).
 #include <hip/hip_runtime.h>
 
 #include <cstdio>

@@ -24,6 +24,9 @@
 //     them (loads and stores complete in order under one counter);
 //   - a pixel's eight 16-byte chunks are stored at chunk ^ ((key / 2) % 8), key = 16 * patch row + patch column,
 //     which spreads the two tile rows a fragment read touches over all bank groups whatever the tap.
+// What is left to this kernel: the patch kernel (conv_patch_f32.hip) is as fast or faster and two to three times closer to 64-bit sums
+// wherever it reads or cuts the filter itself, so the planner comes here only for planes made ahead of filters with more than
+// 1024 output channels, whose scales do not fit behind the planes in that kernel's order: calls without a workspace.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>

@@ -1,4 +1,4 @@
-// int8 Convolution with a short reduction on many pixels, any filter of up to 31 taps, for gfx950 (MI355X): the quantized
+// int8 Convolution with a short reduction on many pixels, any filter of up to 30 taps, for gfx950 (MI355X): the quantized
 // form of Section 4 of the paper, one more of the kinds of convolution that get a strategy of their own (Section 5.3).
 //
 // With a reduction of one to a dozen steps a workgroup that makes one tile and ends is a chain of waits: pixel indexes, loads,

@@ -836,8 +836,9 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
     }
     // what the estimates miss: most on fc_tiles_f32, and where this kernel's fetches crowd every CU
     // (and, from beyond the last-level cache, 64 bytes of a row at a time: 16x2048x1000 9.9 us on the skinny kernel, 9.8 here, then
-    // 9.7 and 12.3; 8x1736x2960 11.3 and 8.1, 11.5 and 9.6; with up to four rows it gains more than that loses: 4x2048x1000 10.0 and
-    // 8.5, 8.8 and 10.2; 1x2048x1000 8.4 and 6.4, 8.6 and 9.2)
+    // 9.7 and 12.3; 8x1736x2960 11.3 and 8.1, 11.5 and 9.6; with up to four rows it gains on weights in the caches what it loses on
+    // ones that are not: 4x2048x1000 10.0 and 8.5, then 8.8 and 10.2; 1x2048x1000 8.4 and 6.4, then 8.6 and 9.2, but a program's first
+    // call on new weights 18.7 and 18.3)
     if ((rest.kernel == KERNEL_FC_TILES || (rest.kernel == KERNEL_SKINNY16 && p.M > 4) ? 1.15 : us > 25.0 ? 1.25 : 1.05) * us > other) return rest;
   }
   return instead_of(p, rest, KERNEL_FC_FEW, form);
@@ -869,7 +870,9 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
     if (dw_f32_applicable(p)) { pl.kernel = KERNEL_DW; return pl; }
     if (smallc_f32_applicable(p) && !p.addend) { pl.kernel = KERNEL_SMALLC; return pl; }
     // the 3x3 tile kernels, which need the filter's planes given or room in the workspace for them: where the patch kernel has
-    // no form or cannot read what was packed ahead (more than 1024 output channels) and the tiles fill the machine
+    // no form or cannot read what was packed ahead (more than 1024 output channels) and the tiles fill the machine.  Nowhere
+    // else: 512->512 on 28x28 at batch 16 with planes given takes 180 to 185 us there and 183 to 190 on the patch kernel, 32 images 351
+    // and 339, 256->256 on 56x56 185 and 167, and lies 4.3e-7 of the result's norm from 64-bit sums, 1.5e-7 there
     const bool filter_planes = p.w_packed != nullptr || (allow_split && p.allow_pack);
     const bool k3c64 = filter_planes && k3c64_f32_applicable(p), k3 = filter_planes && !k3c64 && k3_f32_applicable(p);
     // 1x1 and 3x3 layers, the input cut tile by tile and the filter into the workspace; pointwise layers over few channels
