@@ -824,9 +824,11 @@ Plan short_or(const Problem& p, const Plan& rest) {
   const int form = short_i8_form(p, &us);
   if (form < 0) return rest;
   if (knob_or(KNOB_I8_SHORT, 1) != 2) {
-    // (filters so deep that a slice holds one tile, against 128 x 128 tiles: 3x3 176->408 on 45x45 at batch 16 49.8 us, 64.3 here,
-    // 144->840 at 13456 pixels 40.0 and 47.8, 216->416 at 16731 51.0 and 49.1)
-    if (form == 1 && rest.kernel == KERNEL_WIDE && rest.bn == 128) return rest;
+    // Filters so deep that a slice holds one tile, against the wide kernel.  128 x 128 tiles: 3x3 176->408 on 45x45 at batch 16 49.8 us,
+    // 64.3 here, 144->840 at 13456 pixels 40.0 and 47.8, 216->416 at 16731 51.0 and 49.1.  128 x 64 tiles from eleven slabs on, where
+    // each lane's chain of loads takes longer than its estimate: 40 layers at the median 1.10 of the time there (232->256 on 87x87 14.2
+    // us, 17.7 here), of 47 with fewer slabs 0.83
+    if (form == 1 && rest.kernel == KERNEL_WIDE && (rest.bn == 128 || rest.slabs > 10)) return rest;
     // (nor, against the generic ones, 3x3 185->344 stride 2 at 20172 pixels 41 us, 67 here)
     if (form == 1 && rest.kernel == KERNEL_TILED && rest.bm == 128 && rest.slabs > 8) return rest;
     for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_I8_FEW})

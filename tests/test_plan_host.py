@@ -89,3 +89,9 @@ def test_planes_given_do_not_move_a_layer_of_the_patch_kernel_to_the_contraction
                   rng.choice([1, 2]))
         if probe.conv(d).kernel == "patch":
             assert probe.conv(d, packed=True).kernel != "p3", ((d.n, d.h, d.w, d.c, d.k, d.r, d.stride_h),)
+
+
+@pytest.mark.parametrize("layer,kernel", [((1, 87, 87, 232, 256, 3), "wide"), ((18, 18, 18, 216, 640, 3), "wide"),
+                                          ((9, 34, 34, 240, 288, 3), "wide"), ((5, 33, 45, 72, 120, 3), "short")], ids=str)
+def test_deep_int8_filters_stay_with_the_wide_kernel(probe, layer, kernel):
+    assert probe.conv(_desc(*layer), quantized=True).kernel == kernel
