@@ -680,8 +680,7 @@ Plan plan_i8_rest(const Problem& p, bool allow_split) {
   // Large contractions (deep reduction, enough pixels and channels for 128-wide tiles) take the
   // kernel built for them.
   if (wide_i8_applicable(p)) {
-    if ((forced == 4 || forced == 5) && (!p.b_is_kn || p.k % 16 == 0))
-      return plan_wide_i8(p, (forced == 4 || p.b_is_kn) ? 128 : 64, allow_split);
+    if (forced == 4 || forced == 5) return plan_wide_i8(p, (forced == 4 || p.b_is_kn) ? 128 : 64, allow_split);
     if (forced < 0 && p.Kgemm >= 256 && p.M >= 96 && p.kg >= 128 && !pw_i8_applicable(p)) {
       // convolutions with at most one 128 x 128 tile per CU take 128 x 64 tiles: twice the workgroups
       // for the same bytes per workgroup (measured: 3x3 512->512 on 7x7 at batch 32 21.8 -> 19.6 us,

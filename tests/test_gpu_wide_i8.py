@@ -55,8 +55,7 @@ def test_qconv2d_wide(i, tile, dist, w_off, knobs):
     G.assert_equal_i8(got, ref, f"wide conv {i} without bias")
 
 
-# (M, K, N); the kernel stages 16-byte chunks of weight rows, so N must be a multiple of 16 (other
-# widths fall back to the generic kernel and are checked all the same)
+# (M, K, N): every K a multiple of 16, so the filter may have an offset; N any multiple of four
 WIDE_FC = [(130, 272, 144), (5, 64, 16), (256, 1040, 528), (33, 4096, 64), (300, 2048, 1008), (128, 128, 128),
            (1, 2048, 1024), (97, 6400, 272), (130, 272, 132), (300, 2048, 1000)]
 
@@ -73,7 +72,7 @@ def test_qfc_wide(shape, dist, w_off, knobs):
         ref = oracle.qfc(aq, qp.x_scale, qp.x_off, wq, qp.w_scale, qp.w_off, bq, qp.y_scale, qp.y_off, act=act)
         for use_ws in (True, False):
             got, variant = G.gpu_qfc(aq, wq, bq, qp, act, use_workspace=use_ws)
-            assert variant.startswith("igemm_i8_wide") == (N % 16 == 0), variant
+            assert variant.startswith("igemm_i8_wide"), variant
             G.assert_equal_i8(got, ref, f"wide qfc {shape} {dist} act {act} ws {use_ws} [{variant}]")
 
 
@@ -153,7 +152,7 @@ def test_qconv2d_wide_two_buffers(i, tile, dist, w_off, knobs):
         G.assert_equal_i8(got, ref, f"wide conv {i} tile {tile} {dist} w_off {w_off} ws {use_ws} [{variant}]")
 
 
-@pytest.mark.parametrize("shape", [(130, 272, 144), (256, 1040, 528), (300, 2048, 1008)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(130, 272, 144), (256, 1040, 528), (300, 2048, 1008), (130, 272, 132), (300, 2048, 1000), (97, 1040, 20)], ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("dist,w_off", [("normal", 0), ("uniform", 3)])
 def test_qfc_wide_two_buffers(shape, dist, w_off, knobs):
     G = _gpu()
@@ -219,13 +218,16 @@ def test_qconv2d_wide_ragged_channels(i, tile, nbuf, w_off, knobs):
 
 
 @pytest.mark.parametrize("shape,w_off", [((200, 1544, 392), 0), ((130, 268, 260), 0), ((97, 1036, 1000), 0), ((200, 1544, 392), 3)], ids=str)
-def test_qfc_wide_ragged_rows_and_columns(shape, w_off, knobs):
+@pytest.mark.parametrize("nbuf", [0, 2])
+def test_qfc_wide_ragged_rows_and_columns(shape, w_off, nbuf, knobs):
     """Rows of input and weights at multiples of four bytes; a filter offset needs code sums and stays elsewhere."""
     G = _gpu()
     knobs.set("I8_FC_SMALL_MAX_M", 0)
+    if nbuf:
+        knobs.set("I8_WIDE_NBUF", nbuf)
     M, K, N = shape
     aq, wq, bq, qp = wl.fc_inputs_q(wl.FcLayer("ragged", M, K, N), 8900 + M + K + N, dist="uniform", w_off=w_off)
     ref = oracle.qfc(aq, qp.x_scale, qp.x_off, wq, qp.w_scale, qp.w_off, bq, qp.y_scale, qp.y_off, act=wl.ACT_NONE)
     got, variant = G.gpu_qfc(aq, wq, bq, qp, wl.ACT_NONE)
-    assert variant.startswith("igemm_i8_wide") == (w_off == 0), variant
+    assert variant.startswith("igemm_i8_wide") == (w_off == 0) and (w_off or not nbuf or "r2_" in variant), variant
     G.assert_equal_i8(got, ref, f"ragged qfc {shape} [{variant}]")
