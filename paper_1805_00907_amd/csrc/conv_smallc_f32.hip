@@ -308,7 +308,7 @@ struct SmallCB {
   static constexpr int W_LOADS = (CW * 32 * WGROUPS + SC_THREADS - 1) / SC_THREADS;
   static constexpr int patch_bytes = (LEAD + 2 * PATCH) * 2, filter_bytes = 2 * CW * 32 * WPITCH * 2;
   static constexpr int stage_bytes = (patch_bytes > filter_bytes ? patch_bytes + 15 : filter_bytes) / 16 * 16;
-  static constexpr int lds_bytes = stage_bytes + 32;     // + the eight wavefronts' largest magnitudes
+  static constexpr int lds_bytes = stage_bytes + 32;     // + the wavefronts' largest magnitudes, room for eight
   // patch offset (elements) of group g relative to a pixel's patch origin
   static constexpr int off(int g) { return (g / RUN8) * PITCH + (g % RUN8) * 8; }
 };
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     }
   };
   // Largest magnitude (bits) of a patch in registers, over the wavefront; the workgroup's follows from the
-  // eight words the wavefronts leave in maxw.
+  // words that the four wavefronts leave in maxw.
   auto bits_of = [](float v) { return __builtin_bit_cast(unsigned, v) & 0x7fffffffu; };
   auto stage_max = [&](const Stage& stage) {
     unsigned m = 0;

@@ -171,7 +171,9 @@ __global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_
         b_off[t] = n < p.kg ? (unsigned)((g * p.kg + n) * p.Kgemm + (RAGGED ? 0 : cch * 16)) : OOB;
       }
     } else {
-      const int col = tn * BN + cch * 16;               // k % 16 == 0 on this path: a chunk is whole or absent
+      // k % 4 == 0 on this path: a row's last chunk may run into the next row, or past the tensor into zeros.  What it brings
+      // belongs to columns from k on, whose sums are never stored
+      const int col = tn * BN + cch * 16;
       b_off[0] = col < p.k ? (unsigned)col : OOB;
     }
   }
