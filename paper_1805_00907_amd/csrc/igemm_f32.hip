@@ -835,11 +835,11 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
       other = tiled_us(p, rest);
     }
     // what the estimates miss: most on fc_tiles_f32, and where this kernel's fetches crowd every CU
-    // (and, from beyond the last-level cache, 64 bytes of a row at a time: 16x2048x1000 9.9 us on the skinny kernel, 9.8 here, then
-    // 9.7 and 12.3; 8x1736x2960 11.3 and 8.1, 11.5 and 9.6; with up to four rows it gains on weights in the caches what it loses on
-    // ones that are not: 4x2048x1000 10.0 and 8.5, then 8.8 and 10.2; 1x2048x1000 8.4 and 6.4, then 8.6 and 9.2, but a program's first
-    // call on new weights 18.7 and 18.3)
-    if ((rest.kernel == KERNEL_FC_TILES || (rest.kernel == KERNEL_SKINNY16 && p.M > 4) ? 1.15 : us > 25.0 ? 1.25 : 1.05) * us > other) return rest;
+    // (and, from three rows on or beyond 2048 inputs, with weights beyond the last-level cache, of which it takes 64 bytes of a row at a time: 4x2048x1000
+    // 7.4 us on the skinny kernel, 6.7 here, then 8.7 and 9.6, 16x2048x1000 8.0 and 7.8, 9.3 and 11.9; one and two rows are as fast
+    // there then: 1x2048x1000 8.2 and 6.2, 8.7 and 8.6, 2x2048x1000 7.9 and 6.5, 8.7 and 8.9; 8x1736x2960 9.1 and 7.3,
+    // 11.1 and 9.5; 1x3072x1000 7.9 and 7.1, 9.9 and 11.2)
+    if ((rest.kernel == KERNEL_FC_TILES || (rest.kernel == KERNEL_SKINNY16 && (p.M > 2 || p.Kgemm > 2048)) ? 1.15 : us > 25.0 ? 1.25 : 1.05) * us > other) return rest;
   }
   return instead_of(p, rest, KERNEL_FC_FEW, form);
 }
