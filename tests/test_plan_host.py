@@ -95,3 +95,9 @@ def test_planes_given_do_not_move_a_layer_of_the_patch_kernel_to_the_contraction
                                           ((9, 34, 34, 240, 288, 3), "wide"), ((5, 33, 45, 72, 120, 3), "short")], ids=str)
 def test_deep_int8_filters_stay_with_the_wide_kernel(probe, layer, kernel):
     assert probe.conv(_desc(*layer), quantized=True).kernel == kernel
+
+
+@pytest.mark.parametrize("call,kernel", [((196, 2360, 344), "fc_small"), ((128, 1548, 132), "fc_small"), ((900, 2356, 396), "wide"),
+                                         ((196, 2368, 352), "wide"), ((359, 3160, 3760), "wide")], ids=str)
+def test_int8_rows_in_fours_stay_on_the_strip_kernel_within_its_traffic(probe, call, kernel):
+    assert probe.qfc(*call).kernel == kernel
