@@ -803,9 +803,11 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
 }
 
 // FullyConnected with few rows or a small matrix: fc_few_f32 in place of the weight stream, the one-launch kernel of up to 64
-// rows, the tiled kernel and fc_tiles_f32 where its estimate is lower than theirs (200 calls: choosing so costs 1.4 % over the
-// best for each).  One row on few columns stays with fc_rows_f32, as fast, and so do up to sixteen rows of fewer than 256
-// columns of input with the weight stream, which is one launch there (42 calls of up to 96 KB of weights 3.7 and 3.7 us).
+// rows, the tiled kernel and fc_tiles_f32 where its estimate is lower than theirs by a tenth.  Of the time of those, over calls
+// drawn from their ranges, weights in the caches and from memory: 0.77 and 0.82 of the weight stream's (1154 calls), 0.72 and 0.68
+// (845), 0.52 and 0.55 (652), 0.82 and 0.80 (833), within 2 to 3 % of the best choice for each.  What errs takes up to 1.1 times as
+// long, the two times together; 4x2048x1000 stays (7.4 us, 6.7 here, but 8.7 and 9.9 from memory).  One row on few columns
+// stays with fc_rows_f32, and so do up to sixteen rows of fewer than 256 inputs with the weight stream, which is one launch there.
 Plan fc_few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FC_FEW, 1);         // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
@@ -815,31 +817,26 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW,
                          KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_F32_FC_ROWS, KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    const double depth = 1e-3 * p.Kgemm;
+    // (the weight stream, fc_rows_f32 and fc_small_f32: fitted to 2400 calls as fc_few_f32 itself, median errors 3, 5 and 7 %)
+    const double depth = 1e-3 * p.Kgemm, mb = 1e-6 * p.w_bytes;
     if (rest.kernel == KERNEL_SKINNY16) {
       if (p.Kgemm < 256) return rest;
       // a large matrix is a stream that wants every CU and whole lines: with the weights beyond the last-level cache 16x4096x4096 17.7
       // us there, 25.1 here, 8x9216x4096 30 and 46, 16x25088x4096 75 and 141
       if (p.w_bytes > (24u << 20)) return rest;
-      other = 5.6 + 0.19e-6 * p.w_bytes + 0.35 * depth;
-      if (other < 6.9) other = 6.9;
+      other = 7.0 + 0.246 * depth + 0.131 * mb;
     } else if (rest.kernel == KERNEL_FC_ROWS) {
-      if (p.M > 1 && p.k % 4 == 0) other = 5.8 + 1.8 * depth;
+      if (p.M > 1 && p.k % 4 == 0) other = 3.57 + (0.785 + 0.17 * p.M) * depth + 0.304 * mb + 0.72 * p.M;
     } else if (rest.kernel == KERNEL_FC_SMALL) {
       const int width = fc_small_f32_width(p);
       const double workgroups = (double)((p.k + 16 * width - 1) / (16 * width)) * ((p.M + 15) / 16);
-      other = 5.6 + depth * (3.7 * width - 1.35 + 8.1 * ((int)((workgroups + 255) / 256) - 1));
+      other = 5.74 + depth * (3.96 - 2.09 * width + 1.21 * width * workgroups / 256 + 7.73 * (int)(workgroups / 256)) + 0.125 * mb;
     } else if (rest.kernel == KERNEL_FC_TILES) {
       other = rest.us;
     } else if (rest.kernel == KERNEL_TILED) {
       other = tiled_us(p, rest);
     }
-    // what the estimates miss: most on fc_tiles_f32, and where this kernel's fetches crowd every CU
-    // (and, from three rows on or beyond 2048 inputs, with weights beyond the last-level cache, of which it takes 64 bytes of a row at a time: 4x2048x1000
-    // 7.4 us on the skinny kernel, 6.7 here, then 8.7 and 9.6, 16x2048x1000 8.0 and 7.8, 9.3 and 11.9; one and two rows are as fast
-    // there then: 1x2048x1000 8.2 and 6.2, 8.7 and 8.6, 2x2048x1000 7.9 and 6.5, 8.7 and 8.9; 8x1736x2960 9.1 and 7.3,
-    // 11.1 and 9.5; 1x3072x1000 7.9 and 7.1, 9.9 and 11.2)
-    if ((rest.kernel == KERNEL_FC_TILES || (rest.kernel == KERNEL_SKINNY16 && (p.M > 2 || p.Kgemm > 2048)) ? 1.15 : us > 25.0 ? 1.25 : 1.05) * us > other) return rest;
+    if (1.1 * us > other) return rest;
   }
   return instead_of(p, rest, KERNEL_FC_FEW, form);
 }
