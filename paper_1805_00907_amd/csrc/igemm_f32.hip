@@ -688,15 +688,21 @@ Plan asking(const Problem& p, Plan pl) {
   return pl;
 }
 
-// What the generic 64 x 64 and 32 x 128 tiles cost in microseconds (fitted to 390 convolutions, median error 4 %).
+// What the generic 64 x 64 and 32 x 128 tiles cost in microseconds: so much to begin with, per slab of a CU's workgroups in turn,
+// for a split and per million of its parts, per megabyte, for an addend.  Fitted to 1030 and 210 convolutions, operands in fours or
+// value by value, and to 120 and 750 FullyConnected calls, to the geometric mean of the times with operands in the caches and from
+// memory (median error 3 %).
+struct TiledCost { double fixed, slab, split, part, mb, add; };
 double tiled_us(const Problem& p, const Plan& pl) {
+  static constexpr TiledCost kConv = {4.81, 0.653, 3.34, 0.69, 0.085, 0.54}, kFc = {4.35, 0.452, 4.35, 1.66, 0.064, 0.0},
+                             kByValue = {5.58, 0.990, 3.62, 0.96, 0.079, 0.0};
   const bool vec = p.b_is_kn ? p.Kgemm % 4 == 0 && p.k % 4 == 0 : p.cg % 4 == 0;
+  const TiledCost& c = !vec ? kByValue : p.b_is_kn ? kFc : kConv;
   const double mb = 1e-6 * ((double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1));
   const double workgroups = (double)pl.tiles_m * pl.tiles_n * pl.split_k;
   const double per_cu = workgroups < 1024 ? (double)(int)((workgroups + 255) / 256) : workgroups / 256;
-  const double parts = pl.split_k > 1 ? 3.05 + 0.8e-6 * pl.split_k * (double)p.M * p.k : 0.0;
-  return (vec ? 4.38 : 4.64) + (vec ? 0.578 : 1.05) * pl.slabs_per_split * (per_cu > 1.0 ? per_cu : 1.0) + parts +
-         (vec ? 0.135 : 0.083) * mb + (p.addend ? 0.35 : 0.0);
+  const double parts = pl.split_k > 1 ? c.split + c.part * 1e-6 * pl.split_k * (double)p.M * p.k : 0.0;
+  return c.fixed + c.slab * pl.slabs_per_split * (per_cu > 1.0 ? per_cu : 1.0) + parts + c.mb * mb + (p.addend ? c.add : 0.0);
 }
 // A kernel that needs no workspace in place of `rest`; the queries name what they named before.
 Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
@@ -709,12 +715,12 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
   pl.ask = pl.stood_in_for > rest.ask ? pl.stood_in_for : rest.ask;
   return pl;
 }
-// Convolutions on few pixels: conv_few_f32 in place of the tiled kernel, the sliced form of conv_small_f32 or the patch kernel
-// where its estimate is lower than theirs, fitted like its own to 840 layers (tiled: median error 4 %; sliced: 5 %).  Choosing
-// so costs 1.5 % over the best of both for each layer; the margin covers what the estimates miss.
-// Of the layers of conv_small_f32 in one launch 124 of 170 move and take 0.83 of the time (1x1 512->128 at 128 pixels
-// 7.6 -> 4.8 us, 3x3 64->64 at 972 8.1 -> 5.3, 48->48 at 1125 7.1 -> 4.8; the worst 1.06), those with many tiles for their
-// reduction stay (1x1 192->48 at 4080 5.3, 6.0 here; 3x3 24->384 at 450 5.4 and 5.7).
+constexpr int kShortExactChannels = 128;   // up to which conv_short_f32's sums are as close as conv_few_f32's (short_or)
+// Convolutions on few pixels: conv_few_f32 in place of the tiled kernel, of conv_small_f32 in one launch and sliced over the grid,
+// and of the patch kernel, where its estimate is lower than theirs.  Of the time of those, over layers drawn from its range, operands
+// in the caches and from memory: tiles 0.67 and 0.69 (970 layers, 755 move), sliced 0.80 and 0.80 (1228, 820 move), one launch 0.92
+// and 0.89 (236, 114 move), within 1, 1 and 5 % of the best choice for each.  What errs takes up to 1.2 times as long as tiles and 1.1
+// times as the others.  Deep 3x3 layers stay with slices: 512->512 on 7x7 10.8 us there and 14.0 here, 12.4 and 17.8 from memory.
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FEW, 1);            // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
@@ -728,8 +734,11 @@ Plan few_or(const Problem& p, const Plan& rest) {
     const double workgroups = (double)rest.tiles_m * rest.tiles_n * rest.split_k;
     if (rest.kernel == KERNEL_TILED) {
       other = tiled_us(p, rest);
+      // (pointwise layers that short_or leaves here once they are: only what gains over tiles by more than the estimates miss)
+      double short_us = 0.0;
+      if (p.c > kShortExactChannels && short_f32_form(p, &short_us) >= 0 && short_us < us) other *= 0.9;
     } else if (rest.kernel == KERNEL_SMALL_SPLIT) {
-      other = -0.7 + 8.9 * (workgroups > 256 ? workgroups / 256 : 1.0) + 256e-6 * 0.075 * rest.tiles_m * rest.tiles_n * p.Kgemm + 0.31 * parts;
+      other = 5.17 + 4.18 * (workgroups > 256 ? workgroups / 256 : 1.0) + 256e-6 * 0.0525 * rest.tiles_m * rest.tiles_n * p.Kgemm + 0.507 * parts;
     } else if (rest.kernel == KERNEL_SMALL) {
       const double rounds = (double)(((long long)((p.M + 31) / 32) * ((p.k + 31) / 32) + 255) / 256);
       other = 2.65 + rounds * (1.16 + 0.00636 * p.Kgemm) + (p.c % 32 == 0 ? 0.0018 * p.Kgemm : 0.0);
@@ -755,7 +764,7 @@ Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode != 2) {
     const bool patch = rest.kernel == KERNEL_PATCH && knob_or(KNOB_F32_PATCH, 1) != 2;
-    if (!(rest.kernel == KERNEL_TILED || patch || (rest.kernel == KERNEL_FEW && !rest.was_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= 128))) return rest;
+    if (!(rest.kernel == KERNEL_TILED || patch || (rest.kernel == KERNEL_FEW && !rest.was_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= kShortExactChannels))) return rest;
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_PATCH_TILE, KNOB_F32_FEW_TILE})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
   }
