@@ -715,7 +715,7 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
   pl.ask = pl.stood_in_for > rest.ask ? pl.stood_in_for : rest.ask;
   return pl;
 }
-constexpr int kShortExactChannels = 128;   // up to which conv_short_f32's sums are as close as conv_few_f32's (short_or)
+constexpr int kShortExactChannels = 224;   // up to which conv_short_f32's sums are as close as conv_few_f32's (short_or)
 // Convolutions on few pixels: conv_few_f32 in place of the tiled kernel, of conv_small_f32 in one launch and sliced over the grid,
 // and of the patch kernel, where its estimate is lower than theirs.  Of the time of those, over layers drawn from its range, operands
 // in the caches and from memory: tiles 0.67 and 0.69 (970 layers, 755 move), sliced 0.80 and 0.80 (1228, 820 move), one launch 0.92
@@ -758,8 +758,9 @@ Plan few_or(const Problem& p, const Plan& rest) {
 }
 // Pointwise convolutions on many pixels: conv_short_f32 in place of the tiled kernel, the patch kernel or conv_few_f32 where its
 // estimate is lower than theirs (150 layers: 0.77 of the tiled kernel's time over 47, 0.62 to 1.59 of the patch kernel's over 53).
-// Its sums are closer to 64-bit ones than the first two's at any depth; conv_few_f32's are closer still from about 150
-// channels on (up to 1.12 at 296), so what that has there stays.  The kernel for 64, 128 and 256 channels on many pixels stays too.
+// Its sums are closer to 64-bit ones than the first two's at any depth, and than conv_few_f32's up to 224 channels (0.91 to 1.00 of
+// their distance, 1.00 to 1.04 at 232 to 320): what that has beyond stays.  The kernel for 64, 128 and 256 channels on many pixels
+// stays too.
 Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode != 2) {

@@ -109,3 +109,9 @@ def test_int8_rows_in_fours_stay_on_the_strip_kernel_within_its_traffic(probe, c
 def test_deep_layers_stay_in_slices_where_those_are_the_faster_ones(probe, layer, st, kernel):
     d = _desc(*layer, st)
     assert probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
+
+
+@pytest.mark.parametrize("layer,kernel", [((2, 32, 25, 160, 824, 1), "short"), ((4, 37, 37, 176, 200, 1), "short"), ((4, 32, 40, 240, 176, 1), "few")], ids=str)
+def test_pointwise_layers_of_up_to_224_channels_take_the_faster_kernel(probe, layer, kernel):
+    d = _desc(*layer)
+    assert probe.conv(d, addend=True, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
