@@ -105,7 +105,7 @@ def test_int8_rows_in_fours_stay_on_the_strip_kernel_within_its_traffic(probe, c
 
 @pytest.mark.parametrize("layer,st,kernel", [((1, 11, 9, 352, 616, 3), 1, "small_split"), ((2, 38, 38, 368, 84, 3), 2, "small_split"),
                                              ((1, 7, 7, 512, 512, 3), 1, "small_split"), ((1, 14, 14, 256, 256, 3), 1, "few"),
-                                             ((1, 8, 8, 352, 896, 3), 1, "few"), ((1, 17, 17, 512, 128, 1), 1, "few")], ids=str)
+                                             ((2, 11, 11, 136, 496, 3), 1, "few"), ((1, 17, 17, 512, 128, 1), 1, "few")], ids=str)
 def test_deep_layers_stay_in_slices_where_those_are_the_faster_ones(probe, layer, st, kernel):
     d = _desc(*layer, st)
     assert probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
