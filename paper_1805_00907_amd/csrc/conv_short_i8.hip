@@ -385,9 +385,14 @@ hipError_t launch_nt(const Problem& p, hipStream_t stream) {
 }  // namespace
 
 // The form (tiles of 32 channels to a slice) and what it is expected to take, -1: not a layer for this kernel.  Whether it is the
-// best kernel is the planner's question.  The estimate was fitted to 772 runs of 230 layers (median error 6 %): a start, the
-// filter's way into LDS for each workgroup of a CU, the blocks a wavefront goes through and the steps of each (its chain), the
-// tiles and loads of a SIMD's wavefronts (what they share), the bytes of the layer.
+// best kernel is the planner's question.  The estimate: a start, what a CU's workgroups take in turn, the filter's way into LDS for
+// each, the blocks a wavefront goes through (tiles, steps, an addend) as the workgroups of a CU share its pipes and as one
+// wavefront's chain, the bytes of the tensors and of the filter.  Fitted to 5600 and 990 runs of 2100 and 300 layers, with channels in
+// fours and others (five dwords to a chunk, and shifts, or codes stored one by one), to the geometric mean of the times with operands
+// in the caches and from memory (median errors 4 and 5 %; rows whole cache lines apart lie where the others do).
+struct ShortCost { double fixed, per_cu, fill, tile, step, mfma, add, block, chain, mb, filter; };
+constexpr ShortCost kShort[2] = {{3.36, 0.211, 0.0167, 0.268, 0.0214, 0.0091, 0.340, 0.168, 0.0887, 0.126, 0.449},
+                                 {3.76, 0.0, 0.0313, 0.284, 0.0924, 0.0, 0.195, 0.017, 0.0790, 0.188, 0.698}};
 int short_i8_form(const Problem& p, double* us) {
   const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
   if (mode == 0 || p.b_is_kn || p.groups != 1 || p.chain_n > 0 || p.w_off != 0 || (p.addend && p.k % 4 != 0)) return -1;
@@ -397,7 +402,7 @@ int short_i8_form(const Problem& p, double* us) {
   // (padding at the far sides only: a single tap past the image has no bit to say so)
   if (!taps && ((long long)(p.oh - 1) * p.stride_h >= p.h || (long long)(p.ow - 1) * p.stride_w >= p.w_)) return -1;
   const int chunks = p.r * p.s * ((p.c + 15) / 16), blocks = (p.M + 31) / 32, forced = knob_or(KNOB_I8_SHORT_FORM, -1);
-  const bool odd = p.c % 4 != 0 || p.k % 4 != 0;
+  const ShortCost& cost = kShort[p.c % 4 != 0 || p.k % 4 != 0];
   const double mb = 1e-6 * ((double)p.x_bytes + (p.addend ? 2.0 : 1.0) * p.M * p.k);
   int best = -1;
   for (int nt = 1; nt <= 4; ++nt) {
@@ -405,13 +410,9 @@ int short_i8_form(const Problem& p, double* us) {
     if (short_lds(nt, steps * 32 + 16) > SH_LDS || (forced > 0 && nt != forced)) continue;
     const int slices = (p.k + 32 * nt - 1) / (32 * nt), wgs = workgroups(blocks, slices, 256);
     const double per_cu = (wgs * slices + 255) / 256, deep = (blocks + wgs * SH_WAVES - 1) / (wgs * SH_WAVES);
-    double t = 3.18 + per_cu * (0.0406 * 0.016 * 32 * nt * chunks + deep * (0.398 * nt + (odd ? 0.12 : 0.078) * steps)) +
-                     deep * (0.283 + 0.0225 * steps) + 0.0784 * mb;
-    // rows whole cache lines apart, without the other order of their halves
-    if (p.c % 128 == 0) t *= by_lines(p, nt) ? 1.1 : 1.4;
-    // five dwords to a chunk, and shifts; most where a block is a long walk for one tile of channels (3x3 230->488 at 5832 pixels 32 us
-    // with tiles, 42 here)
-    if (odd) t *= nt == 1 && chunks > 48 ? 1.3 : 1.1;
+    const double t = cost.fixed + per_cu * (cost.per_cu + cost.fill * nt * chunks +
+                                            deep * (nt * (cost.tile + cost.mfma * chunks + (p.addend ? cost.add : 0.0)) + cost.step * steps)) +
+                     deep * (cost.block + cost.chain * steps) + cost.mb * mb + cost.filter * 1e-6 * p.w_bytes;
     if (best < 0 || t < *us) {
       best = nt;
       *us = t;

@@ -640,12 +640,41 @@ double groups_us(const Problem& p, long long tiles, int split, int slabs, int kg
   return rounds * (4.6 + slab * slabs) + (split > 1 ? 4.0 + 0.6e-6 * 4.0 * split * (double)p.M * p.k : 0.0);
 }
 
-// What unsplit 64 x 64 tiles of one or two wavefront groups take.
-double tiled_us(const Problem& p, const Plan& pl, int kgrp) {
-  const long long t = (long long)pl.tiles_m * pl.tiles_n;
-  return (kgrp == 2 ? 4.0 : 4.9) + (kgrp == 2 ? 0.69 : 0.44) * pl.slabs * (t > 256 ? t / 256.0 : 1.0) +
-         0.15e-6 * ((double)p.x_bytes + p.w_bytes + (double)p.M * p.k);
+// What a convolution takes in microseconds on the kernel `pl` has it on, 0: not known.  Fitted to 2400 layers of 16 to 768 channels and
+// 49 to 400000 pixels, to the geometric mean of the times with operands in the caches and from memory (median errors: conv_small_i8 and
+// its sliced form 4 %, tiles 3 to 5 %, the wide kernel 4 and 6 %).  Tiles: to begin with, per workgroup of a CU in turn, per slab of
+// those, more per slab where channels end inside sixteen and inside four, per megabyte of the tensors, for a split, per megabyte of its parts.
+struct TileCost { double fixed, per_cu, slab, ragged, by_value, mb, split, part; };
+constexpr TileCost kTileCost[kNumTilesI8] = {
+    {5.01, 0.0, 0.350, 0.119, 0.055, 0.072, 5.47, 0.0}, {2.50, 1.586, 0.478, 0.152, 0.083, 0.114, 0.0, 0.0},
+    {4.91, 1.363, 0.578, 0.250, 0.097, 0.235, 0.0, 0.0}, {}, {}, {}, {5.81, 0.0, 0.258, 0.146, 0.058, 0.076, 0.0, 0.0},
+    {0.0, 6.055, 0.287, 0.126, 0.060, 0.081, 1.94, 1.141},
+};
+double planned_us(const Problem& p, const Plan& pl) {
+  const double out = 1e-6 * (double)p.M * p.k, mb = 1e-6 * ((double)p.x_bytes + p.w_bytes) + (p.addend ? 2.0 : 1.0) * out;
+  const double parts = pl.split_k > 1 ? 4.0 * pl.split_k * out : 0.0;
+  if (pl.kernel == KERNEL_SMALL || pl.kernel == KERNEL_SMALL_SPLIT) {
+    const long long t32 = (long long)((p.M + 31) / 32) * ((p.k + 31) / 32) * pl.split_k;
+    const double rounds = (double)((t32 + 255) / 256), chunks = p.r * p.s * ((p.cg + 15) / 16);
+    if (pl.kernel == KERNEL_SMALL_SPLIT) return 5.83 + 1.78 * rounds + 0.353 * parts + 0.345 * mb;
+    return 3.90 + rounds * (0.107 + (p.cg % 4 != 0 ? 0.0366 : 0.0161) * chunks) + (p.cg % 16 != 0 ? 0.0203 : 0.0071) * chunks +
+           1.25 * out + 0.067 * mb;
+  }
+  const double t = (double)pl.tiles_m * pl.tiles_n * pl.split_k;
+  double per_cu = t < 1024 ? (double)(int)((t + 255) / 256) : t / 256;
+  if (per_cu < 1.0) per_cu = 1.0;
+  const double slabs = per_cu * pl.slabs_per_split;
+  if (pl.kernel == KERNEL_WIDE) {
+    const double fetch = (t > 256 ? t / 256 : 1.0) * pl.slabs_per_split;
+    return pl.bn == 128 ? 4.70 + 0.587 * slabs + 0.049 * fetch + 0.765 * out + 0.100 * mb
+                        : 5.83 + 0.231 * slabs + 0.244 * fetch + 0.369 * out + 0.106 * mb + (pl.split_k > 1 ? 1.81 : 0.0) + 0.489 * parts;
+  }
+  if (pl.kernel != KERNEL_TILED) return 0.0;
+  const TileCost& c = kTileCost[pl.tile];
+  return c.fixed + c.per_cu * per_cu + slabs * (c.slab + (p.cg % 16 != 0 ? c.ragged : 0.0) + (p.cg % 4 != 0 ? c.by_value : 0.0)) + c.mb * mb +
+         (pl.split_k > 1 ? c.split : 0.0) + c.part * parts;
 }
+constexpr double kMargin = 1.02;                        // what a kernel's estimate has to be below the planned one's by
 
 Plan plan_i8_rest(const Problem& p, bool allow_split) {
   Plan pl;
@@ -762,97 +791,10 @@ Plan plan_i8_rest(const Problem& p, bool allow_split) {
   return pl;
 }
 
-// Convolutions on few pixels: conv_few_i8 in place of the tiled kernel and of both forms of conv_small_i8 where its estimate is
-// lower than theirs (fitted to 420 layers of up to 8 GOP).
-Plan few_or(const Problem& p, const Plan& rest) {
-  const int mode = knob_or(KNOB_I8_FEW, 1);             // 0: off, 2: any size (tests)
-  // (the smallest calls are as long as their way through here)
-  if (mode == 1 && rest.kernel == KERNEL_SMALL &&
-      !((long long)((p.M + 31) / 32) * ((p.k + 31) / 32) <= 64 && p.r * p.s * ((p.cg + 15) / 16) >= 32)) return rest;
-  double us = 0.0, other = 0.0;
-  const int form = few_i8_form(p, &us);
-  if (form < 0) return rest;
-  if (mode != 2) {
-    for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES})
-      if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    const long long t32 = (long long)((p.M + 31) / 32) * ((p.k + 31) / 32);
-    const int chunks = p.r * p.s * ((p.cg + 15) / 16);
-    if (rest.kernel == KERNEL_SMALL) {
-      other = 4.3 + 0.03 * chunks;
-    } else if (rest.kernel == KERNEL_SMALL_SPLIT) {
-      const double workgroups = (double)t32 * rest.split_k;
-      other = 0.5 + 7.2 * (workgroups > 256 ? workgroups / 256 : 1.0) + 1.2e-6 * rest.split_k * (double)p.M * p.k;
-    } else if (rest.kernel == KERNEL_TILED) {
-      const long long t = (long long)rest.tiles_m * rest.tiles_n;
-      const int kgrp = kTilesI8[rest.tile].kgrp;
-      if (kgrp == 4) other = groups_us(p, t, rest.split_k, rest.slabs_per_split, kgrp);
-      else if (rest.tile == 0 || kgrp == 2)
-        other = tiled_us(p, rest, kgrp);
-    }
-    if (1.08 * us > other) return rest;
-  }
+// A kernel that needs no workspace in place of `rest`; the queries name what they named before.
+Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form, double us) {
   Plan pl;
-  pl.kernel = KERNEL_FEW;
-  pl.tile = form;
-  pl.bm = pl.bn = pl.bk = 0;
-  pl.tiles_m = pl.tiles_n = pl.slabs = pl.split_k = pl.slabs_per_split = 1;
-  pl.us = (float)us;
-  pl.stood_in_for = rest.split_k > 1 ? (size_t)rest.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u;
-  return pl;
-}
-
-// Convolutions whose filters fit the LDS of a CU in slices: conv_short_i8 where its estimate is lower than that of the kernel that
-// would run (230 layers of 1000 to 270000 pixels: 145 move, and take 0.74 of the time; 3x3 24->208 on 100x100 at batch 27
-// 84.7 -> 33 us with tiles of 128 x 128, 1x1 72->472 on 43x46 at batch 16 20.2 -> 10.0 with 128 x 64, 3x3 72->120 on 33x45 at
-// batch 5 8.1 -> 6.9 with two wavefront groups, 3x3 72->152 at 18564 pixels 16.5 -> 8.9 with the wide kernel).  The formulas are
-// fitted to the same layers (median errors 4 to 6 %); tiles of 128 rows were never the better ones (0.38 to 0.84).  The kernels
-// for one kind of layer stay (1x1 256->64 on 56x56 at batch 32 8.6 us, 10.4 here).
-Plan short_or(const Problem& p, const Plan& rest) {
-  const long long t32 = (long long)((p.M + 31) / 32) * ((p.k + 31) / 32);
-  if (knob_or(KNOB_I8_SHORT, 1) != 2) {
-    switch (rest.kernel) {
-      // (128 x 128 tiles of several taps over whole cache lines of channels: equal, 3x3 128->256 on 56x56 at batch 6 17.7 us, 18.1
-      // here, at batch 12 28.6 and 26.0)
-      case KERNEL_WIDE: if (p.c % 128 != 0 || p.r * p.s == 1 || rest.bn == 64) break; return rest;
-      case KERNEL_TILED: case KERNEL_FEW: break;
-      case KERNEL_SMALL: if (t32 > 256) break; return rest;   // one tile to a CU: 4.2 to 5.6 us, and not slower than here
-      default: return rest;
-    }
-  }
-  double us = 0.0;
-  const int form = short_i8_form(p, &us);
-  if (form < 0) return rest;
-  if (knob_or(KNOB_I8_SHORT, 1) != 2) {
-    // Filters so deep that a slice holds one tile, against the wide kernel.  128 x 128 tiles: 3x3 176->408 on 45x45 at batch 16 49.8 us,
-    // 64.3 here, 144->840 at 13456 pixels 40.0 and 47.8, 216->416 at 16731 51.0 and 49.1.  128 x 64 tiles from eleven slabs on, where
-    // each lane's chain of loads takes longer than its estimate: 40 layers at the median 1.10 of the time there (232->256 on 87x87 14.2
-    // us, 17.7 here), of 47 with fewer slabs 0.83
-    if (form == 1 && rest.kernel == KERNEL_WIDE && (rest.bn == 128 || rest.slabs > 10)) return rest;
-    // (nor, against the generic ones, 3x3 185->344 stride 2 at 20172 pixels 41 us, 67 here)
-    if (form == 1 && rest.kernel == KERNEL_TILED && rest.bm == 128 && rest.slabs > 8) return rest;
-    for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_I8_FEW})
-      if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    const double chunks = p.r * p.s * ((p.cg + 15) / 16), out = (double)p.M * p.k;
-    double other = 0.0;
-    if (rest.kernel == KERNEL_FEW) other = rest.us;
-    else if (rest.kernel == KERNEL_SMALL) {
-      const double rounds = (double)((t32 + 255) / 256);
-      other = 3.74 + rounds * (0.287 + 0.0183 * chunks) + (p.cg % 16 != 0 ? 0.014 * chunks : 0.0) + 0.64e-6 * out;
-    } else if (rest.kernel == KERNEL_WIDE) {
-      const double t = (double)rest.tiles_m * rest.tiles_n * rest.split_k, slabs = rest.slabs_per_split;
-      other = 5.15 + slabs * (0.24 * (double)(long long)((t + 255) / 256) + 0.58 / 256 * t * rest.bn / 128) + 0.9e-6 * out +
-              (rest.split_k > 1 ? 3.5 : 0.0);
-    } else if (rest.kernel == KERNEL_TILED) {
-      const long long t = (long long)rest.tiles_m * rest.tiles_n;
-      const int kgrp = kTilesI8[rest.tile].kgrp;
-      if (kgrp == 4) other = groups_us(p, t, rest.split_k, rest.slabs_per_split, kgrp);
-      else if (rest.bm == 64) other = tiled_us(p, rest, kgrp);
-      else other = 2.0 * us;
-    }
-    if (us > 0.95 * other) return rest;
-  }
-  Plan pl;
-  pl.kernel = KERNEL_SHORT;
+  pl.kernel = kernel;
   pl.tile = form;
   pl.bm = pl.bn = pl.bk = 0;
   pl.tiles_m = pl.tiles_n = pl.slabs = pl.split_k = pl.slabs_per_split = 1;
@@ -860,6 +802,48 @@ Plan short_or(const Problem& p, const Plan& rest) {
   pl.stood_in_for = rest.kernel == KERNEL_FEW ? rest.stood_in_for
                                               : rest.split_k > 1 ? (size_t)rest.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u;
   return pl;
+}
+
+// Convolutions on few pixels: conv_few_i8 in place of the tiled kernel and of both forms of conv_small_i8 where its estimate is
+// lower than theirs by two in a hundred.  Of the time of those, over 1200 layers drawn after the fit, operands in the caches and from
+// memory: one launch of conv_small_i8 0.84 and 0.92 (278 layers move), its slices 0.81 and 0.85 (30), tiles 0.75 and 0.81 (38); the
+// worst layer 1.10.
+Plan few_or(const Problem& p, const Plan& rest) {
+  const int mode = knob_or(KNOB_I8_FEW, 1);             // 0: off, 2: any size (tests)
+  // (a reduction of a few chunks is over before either kernel differs)
+  if (mode == 1 && rest.kernel == KERNEL_SMALL && p.r * p.s * ((p.cg + 15) / 16) < 8) return rest;
+  double us = 0.0;
+  const int form = few_i8_form(p, &us);
+  if (form < 0) return rest;
+  if (mode != 2) {
+    for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES})
+      if (knob_is_set(k)) return rest;                   // another kernel is asked for
+    if (kMargin * us > planned_us(p, rest)) return rest;
+  }
+  return instead_of(p, rest, KERNEL_FEW, form, us);
+}
+
+// Convolutions whose filters fit the LDS of a CU in slices: conv_short_i8 where its estimate is lower than that of the kernel that
+// would run by two in a hundred.  Of the time of those, over the same layers: tiles 0.70 and 0.77 (370 move), the wide kernel 0.74 and
+// 0.79 (103), conv_small_i8 0.87 and 1.01 (46); the worst layer 1.09.  All choices together lie 0.9 % above the best one for each layer.
+// The kernels for one kind of layer stay (1x1 256->64 on 56x56 at batch 32 8.6 us, 10.4 here).
+Plan short_or(const Problem& p, const Plan& rest) {
+  const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
+  if (mode != 2 && rest.kernel != KERNEL_WIDE && rest.kernel != KERNEL_TILED && rest.kernel != KERNEL_FEW && rest.kernel != KERNEL_SMALL) return rest;
+  // (128 x 128 tiles of several taps over whole cache lines of channels: equal, 3x3 128->256 on 56x56 at batch 6 17.7 us, 18.1
+  // here, at batch 12 28.6 and 26.0)
+  if (mode != 2 && rest.kernel == KERNEL_WIDE && p.c % 128 == 0 && p.r * p.s > 1 && rest.bn == 128) return rest;
+  double us = 0.0;
+  const int form = short_i8_form(p, &us);
+  if (form < 0) return rest;
+  if (mode != 2) {
+    for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_I8_FEW})
+      if (knob_is_set(k)) return rest;                   // another kernel is asked for
+    // (where a slice holds one tile of a long reduction, the estimate is anywhere from 0.66 to 1.12 of the time)
+    const double margin = form == 1 && p.r * p.s * ((p.cg + 15) / 16) >= 72 ? 1.3 : kMargin;
+    if (margin * us > (rest.kernel == KERNEL_FEW ? (double)rest.us : planned_us(p, rest))) return rest;
+  }
+  return instead_of(p, rest, KERNEL_SHORT, form, us);
 }
 }  // namespace
 

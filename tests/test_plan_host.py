@@ -115,3 +115,11 @@ def test_deep_layers_stay_in_slices_where_those_are_the_faster_ones(probe, layer
 def test_pointwise_layers_of_up_to_224_channels_take_the_faster_kernel(probe, layer, kernel):
     d = _desc(*layer)
     assert probe.conv(d, addend=True, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
+
+
+# layers that single-layer thresholds had on the slower kernel: 28.2 us on conv_short_i8 and 20.2 on tiles, 7.1 and 5.9 (conv_small_i8), 5.0
+# on conv_small_i8 and 3.7 on conv_few_i8, 53 on tiles of 128 x 64 and 29 on conv_short_i8
+@pytest.mark.parametrize("layer,st,kernel", [((26, 82, 82, 112, 87, 3), 2, "tiled"), ((5, 36, 36, 48, 376, 3), 2, "small"),
+                                             ((3, 25, 32, 144, 16, 3), 1, "few"), ((13, 112, 112, 168, 32, 3), 1, "short")], ids=str)
+def test_int8_layers_take_the_kernel_of_the_lowest_estimate(probe, layer, st, kernel):
+    assert probe.conv(_desc(*layer, st), quantized=True).kernel == kernel
