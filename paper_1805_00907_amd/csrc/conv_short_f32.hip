@@ -334,9 +334,10 @@ hipError_t launch_nt(const Problem& p, hipStream_t stream) {
 }  // namespace
 
 // The form (tiles of 32 channels to a slice) and what it is expected to take, -1: not a layer for this kernel.  Whether it is the
-// best kernel is the planner's question.  The estimate was fitted to 557 runs of 150 layers of 16 to 320 channels (median error
-// 6 %): a start, the slice's way into LDS, the blocks a wavefront goes through and their trips, what a SIMD's wavefronts share of
-// MFMAs, cuts and stores, the bytes of the layer.
+// best kernel is the planner's question.  The estimate: a start, the slice's way into LDS, the trips of the blocks that a wavefront
+// goes through, what a SIMD's wavefronts share of MFMAs, stores, cuts and addends, the bytes of the tensors and of the filter.  Fitted
+// to 4500 runs of 1100 layers of 16 to 320 channels, to the geometric mean of the times with operands in the caches and from memory
+// (median error 3 %).
 int short_f32_form(const Problem& p, double* us) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode == 0 || p.b_is_kn || p.groups != 1 || p.chain_n > 0 || p.r != 1 || p.s != 1 || p.pad_t || p.pad_l || p.c % 4 != 0) return -1;
@@ -358,8 +359,8 @@ int short_f32_form(const Problem& p, double* us) {
     const int slices = (p.k + 32 * nt - 1) / (32 * nt), wgs = workgroups(blocks, slices, 256 * workgroups_of_cu(nt, lds), waves);
     const double per_cu = (wgs * slices + 255) / 256, deep = (blocks + wgs * waves - 1) / (wgs * waves);
     const double simd = deep * waves * per_cu / 4;      // blocks of a SIMD
-    const double t = 2.0 + 0.07 * per_cu * nt * trips + deep * (1.91 + 0.02 * trips) +
-                     simd * (0.148 * nt * trips + (add ? 0.156 : 0.103) * nt + 0.105 * trips) + 0.079 * mb;
+    const double t = 3.58 + 0.0871 * per_cu * nt * trips + 0.0925 * deep * trips +
+                     simd * (nt * (0.1422 * trips + (add ? 0.2378 : 0.1519)) + 0.1407 * trips) + 0.1097 * mb + 1.48e-6 * p.w_bytes;
     if (best < 0 || t < *us) {
       best = nt;
       *us = t;

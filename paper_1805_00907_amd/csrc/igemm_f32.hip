@@ -689,21 +689,24 @@ Plan asking(const Problem& p, Plan pl) {
 }
 
 // What the generic 64 x 64 and 32 x 128 tiles cost in microseconds: so much to begin with, per slab of a CU's workgroups in turn,
-// for a split and per million of its parts, per megabyte, for an addend.  Fitted to 1030 and 210 convolutions, operands in fours or
-// value by value, and to 120 and 750 FullyConnected calls, to the geometric mean of the times with operands in the caches and from
-// memory (median error 3 %).
-struct TiledCost { double fixed, slab, split, part, mb, add; };
+// for a split and per million of its parts, per megabyte of the tensors and once more of the output, for an addend.  Fitted to 1460
+// convolutions with operands in fours (pointwise ones of up to 320 channels and any on up to 2500 pixels), 210 value by value, and to
+// 120 and 750 FullyConnected calls, to the geometric mean of the times with operands in the caches and from memory (median error 2 to 3 %).
+struct TiledCost { double fixed, slab, split, part, mb, out, add; };
 double tiled_us(const Problem& p, const Plan& pl) {
-  static constexpr TiledCost kConv = {4.81, 0.653, 3.34, 0.69, 0.085, 0.54}, kFc = {4.35, 0.452, 4.35, 1.66, 0.064, 0.0},
-                             kByValue = {5.58, 0.990, 3.62, 0.96, 0.079, 0.0};
+  static constexpr TiledCost kConv = {4.25, 0.740, 3.13, 0.13, 0.044, 0.123, 0.85}, kFc = {4.35, 0.452, 4.35, 1.66, 0.064, 0.0, 0.0},
+                             kByValue = {5.58, 0.990, 3.62, 0.96, 0.079, 0.0, 0.0};
   const bool vec = p.b_is_kn ? p.Kgemm % 4 == 0 && p.k % 4 == 0 : p.cg % 4 == 0;
   const TiledCost& c = !vec ? kByValue : p.b_is_kn ? kFc : kConv;
   const double mb = 1e-6 * ((double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1));
   const double workgroups = (double)pl.tiles_m * pl.tiles_n * pl.split_k;
   const double per_cu = workgroups < 1024 ? (double)(int)((workgroups + 255) / 256) : workgroups / 256;
   const double parts = pl.split_k > 1 ? c.split + c.part * 1e-6 * pl.split_k * (double)p.M * p.k : 0.0;
-  return c.fixed + c.slab * pl.slabs_per_split * (per_cu > 1.0 ? per_cu : 1.0) + parts + c.mb * mb + (p.addend ? c.add : 0.0);
+  return c.fixed + c.slab * pl.slabs_per_split * (per_cu > 1.0 ? per_cu : 1.0) + parts + c.mb * mb + c.out * 4e-6 * p.M * p.k +
+         (p.addend ? c.add : 0.0);
 }
+// What the patch kernel takes by its own estimate, which leaves out what operands from memory cost (290 pointwise layers, median error 5 %).
+double patch_us(const Plan& pl) { return 2.60 + 0.943 * pl.us; }
 // A kernel that needs no workspace in place of `rest`; the queries name what they named before.
 Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
   Plan pl;
@@ -717,10 +720,11 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form) {
 }
 constexpr int kShortExactChannels = 224;   // up to which conv_short_f32's sums are as close as conv_few_f32's (short_or)
 // Convolutions on few pixels: conv_few_f32 in place of the tiled kernel, of conv_small_f32 in one launch and sliced over the grid,
-// and of the patch kernel, where its estimate is lower than theirs.  Of the time of those, over layers drawn from its range, operands
-// in the caches and from memory: tiles 0.67 and 0.69 (970 layers, 755 move), sliced 0.80 and 0.80 (1228, 820 move), one launch 0.92
-// and 0.89 (236, 114 move), within 1, 1 and 5 % of the best choice for each.  What errs takes up to 1.2 times as long as tiles and 1.1
-// times as the others.  Deep 3x3 layers stay with slices: 512->512 on 7x7 10.8 us there and 14.0 here, 12.4 and 17.8 from memory.
+// and of the patch kernel, where its estimate is lower than theirs by two in a hundred.  Of the time of those, over 1800 layers drawn
+// after the fit (pointwise ones, ones of up to 2500 and of more pixels), operands in the caches and from memory: tiles 0.63 and 0.70
+// (600 move), one launch 0.74 and 0.80 (179), sliced 0.76 and 0.80 (49), the patch kernel 0.82 and 0.85 (64); six layers take more than
+// 1.08 of the time, the worst 1.18.  All choices together, short_or's among them, lie 0.9 % above the best one for each layer.  Deep 3x3
+// layers stay with slices: 512->512 on 7x7 9.8 us there and 13.6 here, 14.1 and 20.0 from memory.
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FEW, 1);            // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
@@ -731,6 +735,7 @@ Plan few_or(const Problem& p, const Plan& rest) {
                          KNOB_F32_SMALL_SPLIT_MAX_TILES, KNOB_F32_SMALL_MIN_WGS})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
     const double parts = rest.split_k > 1 ? 8e-6 * rest.split_k * (double)p.M * p.k : 0.0;
+    const double mb = 1e-6 * ((double)p.x_bytes + p.w_bytes + 4.0 * p.M * p.k * (p.addend ? 2 : 1));
     const double workgroups = (double)rest.tiles_m * rest.tiles_n * rest.split_k;
     if (rest.kernel == KERNEL_TILED) {
       other = tiled_us(p, rest);
@@ -738,18 +743,17 @@ Plan few_or(const Problem& p, const Plan& rest) {
       double short_us = 0.0;
       if (p.c > kShortExactChannels && short_f32_form(p, &short_us) >= 0 && short_us < us) other *= 0.9;
     } else if (rest.kernel == KERNEL_SMALL_SPLIT) {
-      other = 5.17 + 4.18 * (workgroups > 256 ? workgroups / 256 : 1.0) + 256e-6 * 0.0525 * rest.tiles_m * rest.tiles_n * p.Kgemm + 0.507 * parts;
+      other = 4.61 + 4.64 * (workgroups > 256 ? workgroups / 256 : 1.0) + 256e-6 * 0.0657 * rest.tiles_m * rest.tiles_n * p.Kgemm + 0.296 * parts;
     } else if (rest.kernel == KERNEL_SMALL) {
       const double rounds = (double)(((long long)((p.M + 31) / 32) * ((p.k + 31) / 32) + 255) / 256);
-      other = 2.65 + rounds * (1.16 + 0.00636 * p.Kgemm) + (p.c % 32 == 0 ? 0.0018 * p.Kgemm : 0.0);
+      other = 2.60 + rounds * (1.04 + 0.00763 * p.Kgemm) + (p.c % 32 == 0 ? 0.00113 * p.Kgemm : 0.0) + 0.072 * mb;
     } else if (rest.kernel == KERNEL_PATCH && knob_or(KNOB_F32_PATCH, 1) != 2) {
-      other = rest.us;
+      other = patch_us(rest);
     }
-    // (more beyond the pixels of the fit, where it takes up to 1.35 times its estimate, 1x1 576->32 on 95x128 at batch 3, and is
-    // then slower than tiles, 328->48 on 61x61 at batch 10 26.5 us there, 29.7 here, with rows whole lines apart from 8192 pixels on, 192->72 + add on 25x25 at
-    // batch 23 13.1 and 17.4; against the patch kernel; and against conv_small_f32 with more than a tile to a CU: 1x1 288->80 on 28x28 at batch 5 9.6 us there, 10.5 here)
+    // (more beyond the pixels of the fit, where it takes up to 1.35 times its estimate, 1x1 576->32 on 95x128 at batch 3, and against
+    // conv_small_f32 with more than a tile to a CU: 1x1 224->120 on 21x21 at batch 7 8.8 us there, 11.5 here)
     const bool many = rest.kernel == KERNEL_SMALL && (long long)((p.M + 31) / 32) * ((p.k + 31) / 32) > 256;
-    if ((p.M > 16384 || (p.M > 8192 && p.c % 32 == 0) ? 1.3 : many ? 1.25 : rest.kernel == KERNEL_PATCH ? 1.15 : 1.05) * us + 0.3 > other) return rest;
+    if ((p.M > 16384 ? 1.3 : many ? 1.25 : 1.02) * us > other) return rest;
   }
   Plan pl = instead_of(p, rest, KERNEL_FEW, form);
   pl.us = (float)us;
@@ -757,7 +761,8 @@ Plan few_or(const Problem& p, const Plan& rest) {
   return pl;
 }
 // Pointwise convolutions on many pixels: conv_short_f32 in place of the tiled kernel, the patch kernel or conv_few_f32 where its
-// estimate is lower than theirs (150 layers: 0.77 of the tiled kernel's time over 47, 0.62 to 1.59 of the patch kernel's over 53).
+// estimate is lower than theirs by two in a hundred (over the same layers 0.73 and 0.80 of the tiled kernel's time, 383 move, 0.78 and
+// 0.85 of the patch kernel's, 125 move; the worst 1.05).
 // Its sums are closer to 64-bit ones than the first two's at any depth, and than conv_few_f32's up to 224 channels (0.91 to 1.00 of
 // their distance, 1.00 to 1.04 at 232 to 320): what that has beyond stays.  The kernel for 64, 128 and 256 channels on many pixels
 // stays too.
@@ -773,12 +778,10 @@ Plan short_or(const Problem& p, const Plan& rest) {
   const int form = short_f32_form(p, &us);
   if (form < 0) return rest;
   if (mode != 2) {
-    double other = rest.kernel == KERNEL_TILED ? tiled_us(p, rest) : (double)rest.us;
-    // of the patch kernel's 4.3 us and more for cutting the filter half may fall to the other layers of a sequence; with the
-    // filter cut ahead its smallest layers take 6 to 7 us whatever their estimate
-    if (rest.kernel == KERNEL_PATCH) other = !p.packed_is_cut ? other - 2.0 : other > 5.8 ? other : 5.8;
-    // (its largest layers take up to 1.3 times their estimate: 216->344 at 52488 pixels 62.8 us on the patch kernel, 68.0 here)
-    if ((us > 35.0 ? 1.25 : 1.08) * us > other) return rest;
+    // (the layers of a sequence share the launch that cuts their filters: 2 of its 4.3 us and more may fall to the others)
+    const double other = rest.kernel == KERNEL_TILED ? tiled_us(p, rest)
+                         : rest.kernel == KERNEL_PATCH ? patch_us(rest) - (p.packed_is_cut ? 0.0 : 2.0) : (double)rest.us;
+    if (1.02 * us > other) return rest;
   }
   return instead_of(p, rest, KERNEL_SHORT, form);
 }

@@ -111,7 +111,7 @@ def test_deep_layers_stay_in_slices_where_those_are_the_faster_ones(probe, layer
     assert probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
 
 
-@pytest.mark.parametrize("layer,kernel", [((2, 32, 25, 160, 824, 1), "short"), ((4, 37, 37, 176, 200, 1), "short"), ((4, 32, 40, 240, 176, 1), "few")], ids=str)
+@pytest.mark.parametrize("layer,kernel", [((2, 32, 25, 160, 824, 1), "short"), ((4, 37, 37, 176, 200, 1), "short"), ((5, 39, 39, 288, 80, 1), "few")], ids=str)
 def test_pointwise_layers_of_up_to_224_channels_take_the_faster_kernel(probe, layer, kernel):
     d = _desc(*layer)
     assert probe.conv(d, addend=True, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
@@ -123,3 +123,12 @@ def test_pointwise_layers_of_up_to_224_channels_take_the_faster_kernel(probe, la
                                              ((3, 25, 32, 144, 16, 3), 1, "few"), ((13, 112, 112, 168, 32, 3), 1, "short")], ids=str)
 def test_int8_layers_take_the_kernel_of_the_lowest_estimate(probe, layer, st, kernel):
     assert probe.conv(_desc(*layer, st), quantized=True).kernel == kernel
+
+
+# the same in fp32: 72 us on tiles and 43 on conv_short_f32, 12.7 on the patch kernel and 9.2 on conv_short_f32, 5.3 on conv_small_f32
+# and 4.1 on conv_few_f32
+@pytest.mark.parametrize("layer,st,kernel", [((30, 51, 72, 32, 400, 1), 1, "short"), ((17, 39, 39, 160, 192, 1), 2, "short"),
+                                             ((1, 55, 55, 144, 32, 1), 1, "few")], ids=str)
+def test_fp32_layers_take_the_kernel_of_the_lowest_estimate(probe, layer, st, kernel):
+    d = _desc(*layer, st)
+    assert probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
