@@ -751,9 +751,11 @@ Plan few_or(const Problem& p, const Plan& rest) {
       other = patch_us(rest);
     }
     // (more beyond the pixels of the fit, where it takes up to 1.35 times its estimate, 1x1 576->32 on 95x128 at batch 3, and against
-    // conv_small_f32 with more than a tile to a CU: 1x1 224->120 on 21x21 at batch 7 8.8 us there, 11.5 here)
+    // conv_small_f32 with more than a tile to a CU: 1x1 224->120 on 21x21 at batch 7 8.8 us there, 11.5 here;
+    // and against the patch kernel, whose estimate is no closer than a twelfth beyond pointwise layers of 320 channels: 1x1 680->56 stride 2 on
+    // 40x44 at batch 22 16.4 us there, 17.8 here)
     const bool many = rest.kernel == KERNEL_SMALL && (long long)((p.M + 31) / 32) * ((p.k + 31) / 32) > 256;
-    if ((p.M > 16384 ? 1.3 : many ? 1.25 : 1.02) * us > other) return rest;
+    if ((p.M > 16384 ? 1.3 : many ? 1.25 : rest.kernel == KERNEL_PATCH ? 1.08 : 1.02) * us > other) return rest;
   }
   Plan pl = instead_of(p, rest, KERNEL_FEW, form);
   pl.us = (float)us;
