@@ -821,7 +821,8 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
 // rows, the tiled kernel and fc_tiles_f32 where its estimate is lower than theirs by a tenth.  Of the time of those, over calls
 // drawn from their ranges, weights in the caches and from memory: 0.77 and 0.82 of the weight stream's (1154 calls), 0.72 and 0.68
 // (845), 0.52 and 0.55 (652), 0.82 and 0.80 (833), within 2 to 3 % of the best choice for each.  What errs takes up to 1.1 times as
-// long, the two times together; 4x2048x1000 stays (7.4 us, 6.7 here, but 8.7 and 9.9 from memory).  One row on few columns
+// long, the two times together; 4x2048x1000 stays (7.4 us, 6.7 here, but 8.7 and 9.9 from memory).  1x2048x1000 moves: launched one by one
+// 6.4 us and 8.1 on the weight stream, two kernels, in a graph 5.8 both, but from memory 10.8 and 9.4.  One row on few columns
 // stays with fc_rows_f32, and so do up to sixteen rows of fewer than 256 inputs with the weight stream, which is one launch there.
 Plan fc_few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FC_FEW, 1);         // 0: off, 2: any size (tests)
