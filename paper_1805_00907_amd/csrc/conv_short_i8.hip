@@ -385,7 +385,7 @@ hipError_t launch_nt(const Problem& p, hipStream_t stream) {
 }  // namespace
 
 // The form (tiles of 32 channels to a slice) and what it is expected to take, -1: not a layer for this kernel.  Whether it is the
-// best kernel is the planner's question.  The estimate: a start, what a CU's workgroups take in turn, the filter's way into LDS for
+// best kernel is the planner's question, which gives what it has to be below.  The estimate: a start, what a CU's workgroups take in turn, the filter's way into LDS for
 // each, the blocks a wavefront goes through (tiles, steps, an addend) as the workgroups of a CU share its pipes and as one
 // wavefront's chain, the bytes of the tensors and of the filter.  Fitted to 5600 and 990 runs of 2100 and 300 layers, with channels in
 // fours and others (five dwords to a chunk, and shifts, or codes stored one by one), to the geometric mean of the times with operands
@@ -393,7 +393,7 @@ hipError_t launch_nt(const Problem& p, hipStream_t stream) {
 struct ShortCost { double fixed, per_cu, fill, tile, step, mfma, add, block, chain, mb, filter; };
 constexpr ShortCost kShort[2] = {{3.36, 0.211, 0.0167, 0.268, 0.0214, 0.0091, 0.340, 0.168, 0.0887, 0.126, 0.449},
                                  {3.76, 0.0, 0.0313, 0.284, 0.0924, 0.0, 0.195, 0.017, 0.0790, 0.188, 0.698}};
-int short_i8_form(const Problem& p, double* us) {
+int short_i8_form(const Problem& p, double below, double* us) {
   const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
   if (mode == 0 || p.b_is_kn || p.groups != 1 || p.chain_n > 0 || p.w_off != 0 || (p.addend && p.k % 4 != 0)) return -1;
   if (p.r * p.s >= NO_TAP || p.x_bytes > 0x7FFFFFFFu || p.w_bytes > 0x7FFFFFFFu) return -1;
@@ -404,6 +404,10 @@ int short_i8_form(const Problem& p, double* us) {
   const int chunks = p.r * p.s * ((p.c + 15) / 16), blocks = (p.M + 31) / 32, forced = knob_or(KNOB_I8_SHORT_FORM, -1);
   const ShortCost& cost = kShort[p.c % 4 != 0 || p.k % 4 != 0];
   const double mb = 1e-6 * ((double)p.x_bytes + (p.addend ? 2.0 : 1.0) * p.M * p.k);
+  // one tile to a wavefront, with nothing to wait for but its own chain: most small layers are decided by this
+  const double chain = 0.5 * chunks;                    // at least this many steps
+  if (mode == 1 && cost.fixed + cost.per_cu + cost.fill * chunks + cost.tile + cost.mfma * chunks + cost.block + (cost.step + cost.chain) * chain +
+                       cost.mb * mb >= below) return -1;
   int best = -1;
   for (int nt = 1; nt <= 4; ++nt) {
     const int T = by_lines(p, nt) ? 4 : steps_of(nt, taps, p.addend != nullptr), steps = (chunks + 2 * T - 1) / (2 * T) * T;

@@ -252,7 +252,7 @@ hipError_t launch_conv_small_i8(const Problem& p, hipStream_t stream, const char
 int few_i8_form(const Problem& p, double* us);
 hipError_t launch_few_i8(const Problem& p, int form, hipStream_t stream, const char** variant);
 // int8 convolution with a short reduction on many pixels (conv_short_i8.hip): form and expected microseconds, -1: not one.
-int short_i8_form(const Problem& p, double* us);
+int short_i8_form(const Problem& p, double below, double* us);
 hipError_t launch_short_i8(const Problem& p, int form, hipStream_t stream, const char** variant);
 bool pw_i8_applicable(const Problem& p);
 hipError_t launch_pw_i8(const Problem& p, hipStream_t stream, const char** variant);

@@ -810,15 +810,15 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form, double
 // worst layer 1.10.
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_I8_FEW, 1);             // 0: off, 2: any size (tests)
-  // (a reduction of a few chunks is over before either kernel differs)
-  if (mode == 1 && rest.kernel == KERNEL_SMALL && p.r * p.s * ((p.cg + 15) / 16) < 8) return rest;
+  // (with fewer chunks conv_small_i8 is as fast, and such calls are as long as their way through here, 0.1 us of 4.3)
+  if (mode == 1 && rest.kernel == KERNEL_SMALL && p.r * p.s * ((p.cg + 15) / 16) < 16) return rest;
   double us = 0.0;
   const int form = few_i8_form(p, &us);
   if (form < 0) return rest;
   if (mode != 2) {
+    if (kMargin * us > planned_us(p, rest)) return rest;
     for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    if (kMargin * us > planned_us(p, rest)) return rest;
   }
   return instead_of(p, rest, KERNEL_FEW, form, us);
 }
@@ -833,16 +833,15 @@ Plan short_or(const Problem& p, const Plan& rest) {
   // (128 x 128 tiles of several taps over whole cache lines of channels: equal, 3x3 128->256 on 56x56 at batch 6 17.7 us, 18.1
   // here, at batch 12 28.6 and 26.0)
   if (mode != 2 && rest.kernel == KERNEL_WIDE && p.c % 128 == 0 && p.r * p.s > 1 && rest.bn == 128) return rest;
+  const double other = mode == 2 ? 0.0 : rest.kernel == KERNEL_FEW ? (double)rest.us : planned_us(p, rest);
   double us = 0.0;
-  const int form = short_i8_form(p, &us);
+  const int form = short_i8_form(p, other / kMargin, &us);
   if (form < 0) return rest;
-  if (mode != 2) {
+  // (where a slice holds one tile of a long reduction, the estimate is anywhere from 0.66 to 1.12 of the time)
+  if (mode != 2 && (form == 1 && p.r * p.s * ((p.cg + 15) / 16) >= 72 ? 1.3 : kMargin) * us > other) return rest;
+  if (mode != 2)
     for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_I8_FEW})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
-    // (where a slice holds one tile of a long reduction, the estimate is anywhere from 0.66 to 1.12 of the time)
-    const double margin = form == 1 && p.r * p.s * ((p.cg + 15) / 16) >= 72 ? 1.3 : kMargin;
-    if (margin * us > (rest.kernel == KERNEL_FEW ? (double)rest.us : planned_us(p, rest))) return rest;
-  }
   return instead_of(p, rest, KERNEL_SHORT, form, us);
 }
 }  // namespace
