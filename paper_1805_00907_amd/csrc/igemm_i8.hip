@@ -806,8 +806,8 @@ Plan instead_of(const Problem& p, const Plan& rest, int kernel, int form, double
 
 // Convolutions on few pixels: conv_few_i8 in place of the tiled kernel and of both forms of conv_small_i8 where its estimate is
 // lower than theirs by two in a hundred.  Of the time of those, over 1200 layers drawn after the fit, operands in the caches and from
-// memory: one launch of conv_small_i8 0.84 and 0.92 (278 layers move), its slices 0.81 and 0.85 (30), tiles 0.75 and 0.81 (38); the
-// worst layer 1.10.
+// memory: one launch of conv_small_i8 0.83 and 0.92 (250 layers move), its slices 0.82 and 0.86 (36), tiles 0.75 and 0.81 (41); the
+// worst layer 1.09.
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_I8_FEW, 1);             // 0: off, 2: any size (tests)
   // (with fewer chunks conv_small_i8 is as fast, and such calls are as long as their way through here, 0.1 us of 4.3)
@@ -824,8 +824,9 @@ Plan few_or(const Problem& p, const Plan& rest) {
 }
 
 // Convolutions whose filters fit the LDS of a CU in slices: conv_short_i8 where its estimate is lower than that of the kernel that
-// would run by two in a hundred.  Of the time of those, over the same layers: tiles 0.70 and 0.77 (370 move), the wide kernel 0.74 and
-// 0.79 (103), conv_small_i8 0.87 and 1.01 (46); the worst layer 1.09.  All choices together lie 0.9 % above the best one for each layer.
+// would run by two in a hundred.  Of the time of those, over the same layers: tiles 0.70 and 0.78 (382 move), the wide kernel 0.73 and
+// 0.79 (101), conv_small_i8 0.88 and 1.02 (44); six take more than 1.08 of it, the worst 1.31 (3x3 64->435
+// stride 2 on 56x56 at batch 17 13.7 us on tiles, 19.0 here).  All choices together lie 0.9 % above the best one for each layer.
 // The kernels for one kind of layer stay (1x1 256->64 on 56x56 at batch 32 8.6 us, 10.4 here).
 Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
