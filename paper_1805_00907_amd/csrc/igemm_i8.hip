@@ -825,7 +825,7 @@ Plan few_or(const Problem& p, const Plan& rest) {
 
 // Convolutions whose filters fit the LDS of a CU in slices: conv_short_i8 where its estimate is lower than that of the kernel that
 // would run by two in a hundred.  Of the time of those, over the same layers: tiles 0.70 and 0.78 (382 move), the wide kernel 0.73 and
-// 0.79 (101), conv_small_i8 0.88 and 1.02 (44); six take more than 1.08 of it, the worst 1.31 (3x3 64->435
+// 0.79 (101), conv_small_i8 0.88 and 1.02 (44); five take more than 1.08 of it, the worst 1.31 (3x3 64->435
 // stride 2 on 56x56 at batch 17 13.7 us on tiles, 19.0 here).  All choices together lie 0.9 % above the best one for each layer.
 // The kernels for one kind of layer stay (1x1 256->64 on 56x56 at batch 32 8.6 us, 10.4 here).
 Plan short_or(const Problem& p, const Plan& rest) {
