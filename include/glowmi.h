@@ -341,8 +341,9 @@ size_t glowmi_qconv2d_chainv_workspace_bytes(const glowmi_conv_desc* d, const gl
  * The arena also carries the split-reduction workspace.  Layer i reads layer i-1's output (layer 0
  * reads x); the last layer writes y.  add_input != 0 adds the sequence input x (an identity shortcut;
  * shapes must match) in that layer's chain before its activation: 1x1 -> 3x3 -> 1x1 with add_input on
- * the last layer is a residual bottleneck block in three launches.  Nothing is synchronised or
- * allocated, so the whole sequence can be captured in a HIP graph (fewer launches is the other gain
+ * the last layer is a residual bottleneck block, which int8 runs as one launch where the tensors between
+ * its layers fit the chip and y lies apart from what the block reads (what the arena holds after a call is
+ * undefined either way).  Nothing is synchronised or allocated, so the whole sequence can be captured in a HIP graph (fewer launches is the other gain
  * the paper names for stacking on GPUs, Section 5.2).
  *   w, bias: device pointers, float / float for glowmi_seq_conv2d, int8 / int32 for glowmi_seq_qconv2d.
  *   wq, yq:  quantized form only: the filter's and the layer output's scale/offset; a layer's input

@@ -38,7 +38,7 @@ const char* const kKnobNames[KNOB_COUNT] = {
     "F32_SMALL_SPLIT_MAX_TILES", "F32_SMALL_MIN_WGS", "F32_FC_SMALL_OFF", "F32_FC_SMALL_VW", "F32_FC_SMALL_MAX_KB", "F32_FC_SMALL_MIN_M", "SMALLC_TH", "F32_SMALLC_BF16",
     "I8_TILE", "I8_SPLIT", "I8_SMALL_MAX_TILES", "I8_WIDE_SPLIT", "I8_WIDE_NBUF", "SMALLC_I8_WGS", "I8_PW_MIN_ITEMS",
     "I8_FC_SMALL_MAX_M", "I8_K3_MIN_BLOCKS", "I8_K3_WAVES", "I8_K3_GATHER", "DW", "F32_PATCH", "F32_PATCH_TILE", "F32_FC_ROWS",
-    "F32_FC_TILES", "F32_FC_TILES_SPLIT", "F32_FEW", "F32_FEW_TILE", "F32_FC_FEW", "F32_FC_FEW_TILE", "I8_FEW", "I8_FEW_TILE", "I8_SHORT", "I8_SHORT_FORM", "F32_SHORT", "F32_SHORT_FORM",
+    "F32_FC_TILES", "F32_FC_TILES_SPLIT", "F32_FEW", "F32_FEW_TILE", "F32_FC_FEW", "F32_FC_FEW_TILE", "I8_FEW", "I8_FEW_TILE", "I8_SHORT", "I8_SHORT_FORM", "F32_SHORT", "F32_SHORT_FORM", "I8_BLOCK", "I8_BLOCK_TH", "I8_BLOCK_TW",
 };
 std::atomic<int> g_knobs[KNOB_COUNT];
 std::once_flag g_knobs_once;
@@ -481,6 +481,14 @@ glowmi_status run_prepared(const PreparedCall& call, hipStream_t stream) {
   const hipError_t e = call.quantized ? launch_i8(call.p, call.plan, stream, &variant)
                                       : launch_f32(call.p, call.plan, stream, &variant);
   return finish(e, variant);
+}
+
+bool run_in_one_launch(const PreparedCall* calls, hipStream_t stream, glowmi_status* st) {
+  const char* variant = "";
+  hipError_t e = hipSuccess;
+  if (!calls[0].quantized || !launch_block_i8(calls[0].p, calls[1].p, calls[2].p, stream, &e, &variant)) return false;
+  *st = finish(e, variant);
+  return true;
 }
 
 }  // namespace glowmi

@@ -34,5 +34,8 @@ size_t conv2d_cut_bytes(const glowmi_conv_desc* d);
 glowmi_status run_cuts(PreparedCall* const* calls, int n, hipStream_t stream);
 // Launch a prepared call on `stream`.
 glowmi_status run_prepared(const PreparedCall& call, hipStream_t stream);
+// Launches three prepared calls that follow each other in a sequence as one kernel that writes the third's output alone, where there
+// is one for them; false, and nothing is launched, where there is none.
+bool run_in_one_launch(const PreparedCall* calls, hipStream_t stream, glowmi_status* st);
 
 }  // namespace glowmi

@@ -1,0 +1,587 @@
+// int8 residual block in one launch for gfx950 (MI355X): three layers of a sequence that follow each other, a 1x1, a 3x3 with
+// padding of one and a 1x1 with or without the shortcut (Section 4 of the paper: int8 codes, int32 sums, the rescale folded into
+// the producer; Section 5.2: operators stacked so that what lies between them stays on the chip).
+//
+// As three launches the block pays each start and end (4 to 5 us next to a few of work) and sends what lies between the layers
+// through the caches.  Here a workgroup of eight wavefronts owns a tile of the output's pixels and everything in front of it:
+//   - the filters of all three layers stay in registers, in operand layout: fetched once per workgroup, straight into LDS in whole
+//     cache lines and from there into the registers of the wavefront that multiplies with them.  Nothing but pixels passes through
+//     LDS afterwards, and a workgroup with several tiles fetches no filter twice;
+//   - the tile's input patch, a ring of one pixel wider, goes from memory straight into LDS, the next tile's while this one's second
+//     layer runs;
+//   - the first layer's codes of the whole patch and the second layer's of the tile stay in LDS.  What lies outside the image takes
+//     the code of real zero there, so the 3x3 needs no tests;
+//   - in the first two layers a wavefront has one block of 32 channels with its whole reduction and a share of the pixels, in the
+//     last layer one or two blocks of channels;
+//   - the filter is the row operand with its channels permuted so that a lane ends up with 16 consecutive channels of one pixel.
+// A tap's channels are filled up to 32 CB codes in LDS with zeros on the pixels' side: what the last chunk of a filter's tap reads
+// of the next one meets them.
+// Measured (the three launches -> here): 256/64 on 56x56 at batch 32 34.4 -> 27.3 us, 256/64 on 28x28 at batch 2 15.3 -> 7.9, 128/32 on
+// 7x10 at batch 6 15.2 -> 6.7, 320/80 on 42x40 at batch 3 16.0 -> 11.4; 0.61 of their time over 300 blocks of 32 to 96 channels in the
+// middle.  What bounds it: small blocks the start, 3 to 7 thousand cycles of the filters' way at some 40 bytes a cycle, and code that
+// waits for its instructions the first time through (12 KB of it unrolled cost 1 us more than 9 KB rolled up); large ones the last
+// layer, whose requantize steps and table reads each take what it takes.  Tried: slabs of filters through a ring in LDS with a barrier
+// each (a slab is 0.9 us whatever its products: 256/64 on 28x28 13 us, 1024/256 on 14x14 60 against 18 in three launches); the
+// reduction split over the wavefronts and summed in LDS (1.1 to 1.4 of the time on any block); 128 channels, whose filters leave no
+// registers unsplit (0.9 to 1.1 of the three launches' time).
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <type_traits>
+
+#include "igemm.h"
+#include "lds_direct.h"
+#include "pw_common.h"
+#include "quant_epilogue.h"
+
+namespace glowmi {
+namespace {
+
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+constexpr int BL_THREADS = 512;
+constexpr int BL_WAVES = BL_THREADS / 64;
+constexpr int MOST_PIXELS = 256;                        // of a tile's patch
+constexpr int BL_PANEL = 4096;                          // bytes of 32 filters x 8 chunks of 16 codes
+constexpr unsigned OOB = 0x80000000u;                   // beyond any tensor the kernel accepts: loads give zeros, stores are dropped
+
+struct BlockLayer {
+  const void* w;
+  const int* bias;
+  unsigned w_bytes;
+  int k, kg, tap_len;            // channels, codes of a filter, codes of one of its taps
+  int x_off, mant, shift, y_off, lo, hi;
+};
+
+struct Block {
+  const void* x;
+  const void* addend;
+  void* y;
+  unsigned x_bytes, y_bytes;
+  BlockLayer l[3];
+  int h, w, c;
+  int th, tw, pw;                // tile, width of its patch
+  int np, nt, pbp, pbt;          // pixels of patch and tile, blocks of 32 of them
+  int tiles_x, tiles_per_image;
+  FastDiv div_tx, div_tpi, div_tw, div_pw, div_n16;   // n16: 16-code chunks of an input pixel
+  int x_shift, x_mask, x_loads;  // the patch's swizzle, its loads per thread
+  int x_early;                   // the first patch has room beside the filters on their way
+  int at_x, at_mid1, at_mid2;    // in LDS
+  PwRange range;                 // a workgroup's tiles
+  int r_off, r_mant, r_shift;
+};
+
+// Channel of a block of 32 that lies in row `r` of its panel: result register e of a lane with half h is MFMA row
+// (e / 4) * 8 + 4 h + e % 4, and this makes it channel 16 h + e.
+__device__ __forceinline__ int channel_of_row(int r) { return ((r >> 2) & 1) * 16 + (r >> 3) * 4 + (r & 3); }
+// Row r of a panel holds its chunk c at place c ^ panel_swizzle(r): the rows of a fragment read are then in different banks.
+__device__ __forceinline__ int panel_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 3); }
+
+// The term of the addend's code in byte B of `codes`, from the table at the start of LDS (the kernel's only LDS is what the launch
+// gives it, so `smem` is address 0): shifting the byte out and scaling it is one instruction.
+template <int B>
+__device__ __forceinline__ int addend_term(int codes) {
+  typedef const int __attribute__((address_space(3))) * Table;
+  Table at;
+  const int two = 2;
+  if (B == 0) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(at) : "v"(two), "v"(codes));
+  if (B == 1) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(at) : "v"(two), "v"(codes));
+  if (B == 2) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(at) : "v"(two), "v"(codes));
+  if (B == 3) asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(at) : "v"(two), "v"(codes));
+  return *at;
+}
+
+// The shape of a kernel for blocks with up to 32 CB channels in the middle and 128 CB at the ends.
+template <int CB>
+struct Shape {
+  static constexpr int COLUMNS = CB == 3 ? 4 : CB;                   // wavefronts side by side over the channels of the first two layers
+  static constexpr int PIXELS = BL_WAVES / COLUMNS;                  // wavefronts that share the pixels
+  static constexpr int S0 = 4 * CB, S1 = 9 * CB;                     // steps of 32 codes
+  static constexpr int LAST = CB <= 2 ? 1 : 2;                       // blocks of channels of a wavefront in the last layer
+  static constexpr int LAST_COLUMNS = CB == 1 ? 4 : 8;
+  static constexpr int LAST_PIXELS = BL_WAVES / LAST_COLUMNS;
+  static constexpr int P0 = CB, P1 = (18 * CB + 7) / 8;              // panels of a block of channels
+  static constexpr int SHARED = CB == 1 ? 4 : CB == 2 ? 2 : 1;       // blocks of channels of a panel of the last layer
+  static constexpr int PANELS0 = CB * P0, PANELS1 = CB * P1, PANELS2 = 4 * CB / SHARED;
+  static constexpr int EVEN0 = (PANELS0 + 1) & ~1, EVEN1 = (PANELS1 + 1) & ~1, EVEN2 = (PANELS2 + 1) & ~1;   // loaded two at a time
+  static constexpr bool TWO_ROUNDS = CB >= 3;                        // the second layer's filters after the others'
+  static constexpr int ROUND1 = EVEN0 + EVEN2 + (TWO_ROUNDS ? 0 : EVEN1);
+  static constexpr int STAGED = (TWO_ROUNDS && EVEN1 > ROUND1 ? EVEN1 : ROUND1) * BL_PANEL;
+  static constexpr int PER_CU = CB == 1 ? 2 : 1;                     // workgroups
+  static constexpr int LDS = 160 * 1024 / PER_CU;
+  static constexpr int PITCH = 32 * CB + 16;                         // of a pixel between the layers
+  static constexpr int TERMS = 32 * CB * 2 + 128 * CB;
+  static constexpr int BASE = 1024 + (TERMS * 4 + 255) / 256 * 256;  // behind the tables: the filters on their way
+};
+
+template <int CB, bool ADD>
+__global__ __launch_bounds__(BL_THREADS, 2 * Shape<CB>::PER_CU) void block_i8_kernel(const Block p) {
+  using G = Shape<CB>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lh = lane >> 5;
+  int* addlut = reinterpret_cast<int*>(smem);               // [256] the addend's code (as an unsigned byte) -> its term
+  int* terms = addlut + 256;                                // of the channels of the three layers
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_offset_of(smem)) + (unsigned)wave * 1024u;
+  const v4i rsrc_x = make_rsrc(p.x, p.x_bytes);
+  int img, y0, x0;
+  auto locate = [&](int t) {
+    img = p.div_tpi.div(t);
+    const int r = t - img * p.tiles_per_image, ty = p.div_tx.div(r);
+    y0 = ty * p.th;
+    x0 = (r - ty * p.tiles_x) * p.tw;
+  };
+  auto load_patch = [&]() {                             // of the tile located
+    const int n16 = p.c >> 4;
+#pragma unroll 1
+    for (int q = 0; q < p.x_loads; ++q) {
+      const int i = q * BL_THREADS + tid;
+      const int px = p.div_n16.div(i), at = i - px * n16;
+      const int chunk = at ^ ((px >> p.x_shift) & p.x_mask);
+      const int py = p.div_pw.div(px);
+      const int iy = y0 - 1 + py, ix = x0 - 1 + px - py * p.pw;
+      const bool in = px < p.np && (unsigned)iy < (unsigned)p.h && (unsigned)ix < (unsigned)p.w;
+      load16_to_lds(rsrc_x, lds0 + (unsigned)(p.at_x + q * (BL_THREADS * 16)),
+                    in ? (unsigned)(((img * p.h + iy) * p.w + ix) * p.c + chunk * 16) : OOB);
+    }
+  };
+  // Panels of a layer to LDS, two at a time, a quarter of one per wavefront: block of channels major, then its runs of eight chunks;
+  // a tap has FILL chunks, its last ones may lie past its codes.  SHARED > 1: a panel holds the 8 / SHARED chunks of as many blocks.
+  const int p_row = (wave & 3) * 8 + (lane >> 3), p_place = (lane & 7) ^ panel_swizzle(p_row), p_channel = channel_of_row(p_row);
+  auto load_panels = [&](const BlockLayer& l, auto panels_tag, auto per_block_tag, auto fill_tag, auto shared_tag, int first) {
+    constexpr int PANELS = decltype(panels_tag)::value, PER = decltype(per_block_tag)::value, FILL = decltype(fill_tag)::value;
+    constexpr int SHARED = decltype(shared_tag)::value, EACH = 8 / SHARED;
+    const v4i rsrc = make_rsrc(l.w, l.w_bytes);
+    const unsigned row_at = (unsigned)(p_channel * l.kg);
+    constexpr int UNROLL = PANELS > 12 ? 1 : PANELS;     // (long code waits for its instructions)
+#pragma unroll UNROLL
+    for (int i = 0; i < PANELS; i += 2) {
+      const int panel = i + (wave >> 2), row_of_blocks = panel / PER, run = panel - row_of_blocks * PER;
+      const int block = row_of_blocks * SHARED + p_place / EACH;
+      const int chunk = run * 8 + p_place % EACH, tap = chunk / FILL, c0 = (chunk - tap * FILL) * 16;
+      const bool live = panel < PANELS && block * 32 + p_channel < l.k && tap * l.tap_len < l.kg && c0 < l.tap_len;
+      load16_to_lds(rsrc, lds0 + (unsigned)(G::BASE + (first + i) * BL_PANEL),
+                    live ? row_at + (unsigned)(block * 32 * l.kg) + (unsigned)(tap * l.tap_len + c0) : OOB);
+    }
+  };
+
+  // ---- the filters
+  const int group = wave / G::COLUMNS, column = wave % G::COLUMNS;
+  const bool has_column = column < CB;
+  load_panels(p.l[0], Int<G::PANELS0>{}, Int<G::P0>{}, Int<8 * G::P0>{}, Int<1>{}, 0);
+  if (!G::TWO_ROUNDS) load_panels(p.l[1], Int<G::PANELS1>{}, Int<G::P1>{}, Int<2 * CB>{}, Int<1>{}, G::EVEN0 + G::EVEN2);
+  load_panels(p.l[2], Int<G::PANELS2>{}, Int<1>{}, Int<8>{}, Int<G::SHARED>{}, G::EVEN0);
+  // consecutive workgroups go round the eight XCDs: each XCD gets a run of tiles
+  const int wg = gridDim.x % 8 == 0 ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  int tile, tile_end;
+  deal_range(wg, (int)gridDim.x, p.range.items_div, p.range.items_rem, tile, tile_end);
+  locate(tile);
+  if (p.x_early) load_patch();
+  for (int i = tid; i < G::TERMS; i += BL_THREADS) terms[i] = 0;
+  if (ADD)
+    for (int i = tid; i < 256; i += BL_THREADS) addlut[i] = rescale_term((int)(signed char)i - p.r_off, p.r_mant, p.r_shift);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __syncthreads();
+  v4i w0[G::S0], w1[G::S1], w2[G::LAST][CB];
+  const int w_lane = l32 * 128, w_swz = (panel_swizzle(l32) ^ lh) << 4;
+  auto fragment = [&](int panel, int step) {            // step: of the panel's four
+    return *reinterpret_cast<const v4i*>(smem + G::BASE + panel * BL_PANEL + w_lane + ((step * 32) ^ w_swz));
+  };
+  // The channels' code sums, which remove the input's offset: the lanes that hold a row add up what they have of it.  The last chunks
+  // of a tap may hold codes of the next one: theirs do not count.
+  auto ones_of = [&](int len) {
+    v4i ones;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ones[e] = len - (CB * 32 - 32 + lh * 16) > 4 * e ? 0x01010101 : 0;
+    return ones;
+  };
+  const v4i all_ones = v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101};
+  auto code_sum = [&](v4i v, v4i ones, int sum) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_sdot4(v[e], ones[e], sum, false);
+    return sum;
+  };
+  const int my_channel = channel_of_row(l32);
+  const int col = G::COLUMNS == CB || column < CB ? column : 0;
+  int sum = 0;
+#pragma unroll
+  for (int s = 0; s < G::S0; ++s) {
+    w0[s] = fragment(col * G::P0 + s / 4, s % 4);
+    sum = code_sum(w0[s], all_ones, sum);
+  }
+  if (has_column && group == 0) atomicAdd(terms + column * 32 + my_channel, sum);
+  {
+    const v4i tail = ones_of(p.l[2].tap_len);
+#pragma unroll
+    for (int b = 0; b < G::LAST; ++b) {
+      const int block = wave % G::LAST_COLUMNS + b * G::LAST_COLUMNS;
+      sum = 0;
+#pragma unroll
+      for (int s = 0; s < CB; ++s) {
+        const int at = block < 4 * CB ? block : 0;
+        w2[b][s] = fragment(G::EVEN0 + at / G::SHARED, at % G::SHARED * CB + s);
+        sum = code_sum(w2[b][s], s == CB - 1 ? tail : all_ones, sum);
+      }
+      if (block < 4 * CB && wave / G::LAST_COLUMNS == 0) atomicAdd(terms + 64 * CB + block * 32 + my_channel, sum);
+    }
+  }
+  if (G::TWO_ROUNDS) {
+    __syncthreads();
+    load_panels(p.l[1], Int<G::PANELS1>{}, Int<G::P1>{}, Int<2 * CB>{}, Int<1>{}, 0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();
+  }
+  int tap_at[G::S1];                                    // where the step's tap and codes lie from a pixel of the tile in the patch
+  {
+    const v4i tail = ones_of(p.l[1].tap_len);
+    constexpr int FIRST = G::TWO_ROUNDS ? 0 : G::EVEN0 + G::EVEN2;
+    sum = 0;
+#pragma unroll
+    for (int s = 0; s < G::S1; ++s) {
+      constexpr int W = 3 * CB;                         // steps of a row of the filter
+      tap_at[s] = (s / W * p.pw + s % W / CB) * G::PITCH + s % CB * 32;
+      w1[s] = fragment(FIRST + col * G::P1 + s / 4, s % 4);
+      sum = code_sum(w1[s], s % CB == CB - 1 ? tail : all_ones, sum);
+    }
+    if (has_column && group == 0) atomicAdd(terms + 32 * CB + column * 32 + my_channel, sum);
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int i = tid; i < G::TERMS; i += BL_THREADS) {
+    const int L = i < 32 * CB ? 0 : i < 64 * CB ? 1 : 2;
+    const int ch = i - L * 32 * CB;
+    const int* bias = L == 0 ? p.l[0].bias : L == 1 ? p.l[1].bias : p.l[2].bias;
+    const int k = L == 2 ? p.l[2].k : p.l[0].k, off = L == 0 ? p.l[0].x_off : L == 1 ? p.l[1].x_off : p.l[2].x_off;
+    // combined modulo 2^32: the true accumulator fits int32 by contract
+    unsigned t = 0u - (unsigned)off * (unsigned)terms[i];
+    if (bias && ch < k) t += (unsigned)bias[ch];
+    terms[i] = (int)t;
+  }
+  if (!p.x_early) {
+    load_patch();
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  }
+  __syncthreads();
+
+  // The sums of sixteen channels start at their terms ...
+  auto start_at = [&](v16i& acc, const int* term) {
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      const v4i t = *reinterpret_cast<const v4i*>(term + 4 * e4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[4 * e4 + e] = t[e];
+    }
+  };
+  // ... and end as sixteen codes of a pixel.
+  auto requantize = [&](const v16i& acc, int mant, int shift, int y_off, int lo, int hi) {
+    const FoldedRequant fold = make_folded_requant(shift, y_off);
+    v4i codes;
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      int q[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] = requantize_folded(acc[4 * e4 + e], mant, fold, lo, hi);
+      codes[e4] = (int)pack_codes(q[0], q[1], q[2], q[3]);
+    }
+    return codes;
+  };
+  // One of the first two layers.
+  auto first_layers = [&](auto layer_tag) {
+    constexpr int L = decltype(layer_tag)::value;
+    const int blocks = L == 0 ? p.pbp : p.pbt, fill = L == 0 ? (p.l[1].x_off & 0xff) * 0x01010101 : 0;
+    const int mant = L == 0 ? p.l[0].mant : p.l[1].mant, shift = L == 0 ? p.l[0].shift : p.l[1].shift;
+    const int y_off = L == 0 ? p.l[0].y_off : p.l[1].y_off, lo = L == 0 ? p.l[0].lo : p.l[1].lo, hi = L == 0 ? p.l[0].hi : p.l[1].hi;
+    const int* layer_terms = terms + L * CB * 32 + 16 * lh;
+    v16i acc;
+    auto multiply = [&](int block) {
+      const int px = block * 32 + l32;
+      start_at(acc, layer_terms + column * 32);
+      if constexpr (L == 0) {
+        const int q = px < p.np ? px : p.np - 1;
+        const unsigned char* src = smem + p.at_x + q * p.c;
+        const int swz = (((q >> p.x_shift) & p.x_mask) << 4) ^ (lh << 4);
+#pragma unroll
+        for (int s = 0; s < G::S0; ++s) {
+          // (steps past the channels meet zeros on the filters' side)
+          const v4i a = *reinterpret_cast<const v4i*>(src + ((s * 32 < p.c ? s * 32 : 0) ^ swz));
+          acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w0[s], a, acc, 0, 0, 0);
+        }
+      } else {
+        const int q = px < p.nt ? px : p.nt - 1, ty = p.div_tw.div(q), tx = q - ty * p.tw;
+        const unsigned char* src = smem + p.at_mid1 + (ty * p.pw + tx) * G::PITCH + 16 * lh;
+#pragma unroll
+        for (int s = 0; s < G::S1; ++s) {
+          const v4i a = *reinterpret_cast<const v4i*>(src + tap_at[s]);
+          acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[s], a, acc, 0, 0, 0);
+        }
+      }
+    };
+    auto keep = [&](int block, int c) {                 // the codes to their place between the layers
+      v4i codes = requantize(acc, mant, shift, y_off, lo, hi);
+      const int px = block * 32 + l32, valid = p.l[0].k - (c * 32 + 16 * lh);
+      bool inside = true;
+      if (L == 0) {
+        const int py = p.div_pw.div(px), iy = y0 - 1 + py, ix = x0 - 1 + px - py * p.pw;
+        inside = (unsigned)iy < (unsigned)p.h && (unsigned)ix < (unsigned)p.w;
+      }
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        codes[e4] = inside ? codes[e4] : fill;
+        codes[e4] = valid > 4 * e4 ? codes[e4] : 0;     // the fill of a tap: zeros
+      }
+      *reinterpret_cast<v4i*>(smem + (L == 0 ? p.at_mid1 : p.at_mid2) + px * G::PITCH + c * 32 + 16 * lh) = codes;
+    };
+    if (has_column)
+      for (int b = group; b < blocks; b += G::PIXELS) {
+        multiply(b);
+        keep(b, column);
+      }
+  };
+
+  const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)p.y_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_add =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ADD ? p.addend : p.y), 0, (int)p.y_bytes, 0x00020000);
+  const int last_column = wave % G::LAST_COLUMNS, last_group = wave / G::LAST_COLUMNS;
+  for (;;) {
+    const int o_img = img, o_y = y0, o_x = x0;
+    const bool more = tile + 1 < tile_end;
+    first_layers(Int<0>{});
+    __syncthreads();
+    if (more) {                                         // the patch is through: the next tile's
+      locate(tile + 1);
+      load_patch();
+    }
+    first_layers(Int<1>{});
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();
+
+    // The last layer.  The sums start at the channels' terms and the addend's: a block's are made while the one before is
+    // requantized, its addend is on its way for two blocks.
+    auto place = [&](int b) {                           // where the lane's pixel of a block of the tile goes
+      const int px = b * 32 + l32, ty = p.div_tw.div(px), oy = o_y + ty, ox = o_x + px - ty * p.tw;
+      return px < p.nt && oy < p.h && ox < p.w ? (unsigned)(((o_img * p.h + oy) * p.w + ox) * p.l[2].k) + 16u * lh : OOB;
+    };
+    v4i add[G::LAST];
+    unsigned to = OOB, next_to = place(last_group);
+    auto load_addend = [&](unsigned from) {
+#pragma unroll
+      for (int c = 0; c < G::LAST; ++c)
+        add[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_add, from + (unsigned)((last_column + c * G::LAST_COLUMNS) * 32), 0, 0);
+    };
+    if (ADD) {
+      load_addend(next_to);
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    }
+    for (int b = last_group; b < p.pbt; b += G::LAST_PIXELS) {
+      const unsigned char* src = smem + p.at_mid2 + (b * 32 + l32) * G::PITCH + 16 * lh;
+      v4i a[CB];
+#pragma unroll
+      for (int s = 0; s < CB; ++s) a[s] = *reinterpret_cast<const v4i*>(src + 32 * s);
+      to = next_to;
+      next_to = b + G::LAST_PIXELS < p.pbt ? place(b + G::LAST_PIXELS) : OOB;
+#pragma unroll
+      for (int c = 0; c < G::LAST; ++c) {
+        const int block = last_column + c * G::LAST_COLUMNS;
+        v16i acc;
+        start_at(acc, terms + 64 * CB + (block < 4 * CB ? block : 0) * 32 + 16 * lh);
+        if (ADD) {
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) {              // (sums modulo 2^32: the true accumulator fits int32 by contract)
+            const int four[4] = {addend_term<0>(add[c][e4]), addend_term<1>(add[c][e4]), addend_term<2>(add[c][e4]), addend_term<3>(add[c][e4])};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * e4 + e] = (int)((unsigned)acc[4 * e4 + e] + (unsigned)four[e]);
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < CB; ++s) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w2[c][s], a[s], acc, 0, 0, 0);
+        if (ADD && c == G::LAST - 1) load_addend(next_to);
+        const v4i codes = requantize(acc, p.l[2].mant, p.l[2].shift, p.l[2].y_off, p.l[2].lo, p.l[2].hi);
+        __builtin_amdgcn_raw_buffer_store_b128(codes, rsrc_y, block * 32 + 16 * lh < p.l[2].k ? to + (unsigned)(block * 32) : OOB, 0, 0);
+      }
+      // the next block's addend but not the stores behind it: with every lane storing, out of range where it has nothing to store,
+      // their number is known
+      if (ADD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(G::LAST == 1 ? 1 : 0));
+    }
+    if (!more) break;
+    ++tile;
+  }
+}
+
+// Where a chunk of a row of n chunks is stored so that the same chunk of sixteen rows in turn lies in different banks: the rows'
+// starts repeat every 16 / (largest power of two in n) rows.
+void swizzle_of(int n, int* shift, int* mask) {
+  int g = n & -n;
+  if (g > 16) g = 16;
+  *mask = g - 1;
+  *shift = 0;
+  while ((g << *shift) < 16) ++*shift;
+}
+
+void fill_layer(BlockLayer& l, const Problem& p) {
+  l.w = p.w;
+  l.bias = static_cast<const int*>(p.bias);
+  l.w_bytes = p.w_bytes;
+  l.k = p.k;
+  l.kg = p.Kgemm;
+  l.tap_len = p.c;
+  l.x_off = p.x_off; l.mant = p.mant; l.shift = p.shift; l.y_off = p.y_off; l.lo = p.lo; l.hi = p.hi;
+}
+
+bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
+
+bool plain_layer(const Problem& p, int r) {
+  return !p.b_is_kn && p.groups == 1 && p.r == r && p.s == r && p.stride_h == 1 && p.stride_w == 1 && p.pad_t == r / 2 &&
+         p.pad_l == r / 2 && p.oh == p.h && p.ow == p.w_ && p.chain_n == 0 && p.w_off == 0 && p.shift >= 33 && p.shift <= 54 &&
+         p.w_bytes <= 0x7FFFFFFFu;
+}
+
+// A tile's shape and its place in LDS; the bytes it takes there.
+template <int CB>
+int place_tile(Block& b, int th, int tw) {
+  using G = Shape<CB>;
+  b.th = th;
+  b.tw = tw;
+  b.pw = tw + 2;
+  b.np = (th + 2) * (tw + 2);
+  b.nt = th * tw;
+  b.pbp = (b.np + 31) / 32;
+  b.pbt = (b.nt + 31) / 32;
+  b.tiles_x = (b.w + tw - 1) / tw;
+  b.tiles_per_image = b.tiles_x * ((b.h + th - 1) / th);
+  b.x_loads = (b.np * (b.c / 16) + BL_THREADS - 1) / BL_THREADS;
+  const int patch = b.x_loads * BL_THREADS * 16;
+  b.at_mid1 = G::BASE;
+  b.at_mid2 = b.at_mid1 + b.pbp * 32 * G::PITCH;
+  const int work = b.at_mid2 + b.pbt * 32 * G::PITCH, staged = G::BASE + G::STAGED;
+  // the filters pass through where the layers' codes lie later, the patch beside them if there is room
+  b.x_early = (work > staged ? work : staged) + patch <= G::LDS;
+  b.at_x = b.x_early && staged > work ? staged : work;
+  return b.at_x + patch > staged ? b.at_x + patch : staged;
+}
+
+// What a launch is expected to take, in microseconds: a start with the filters' way, what a tile costs by the turns of a wavefront in
+// each layer and the loads of its patch, the bytes of input and output (mb, in millions).  Fitted to 1700 runs of 300 blocks of 32 to 96
+// channels in the middle on 7x7 to 100x100, batch 1 to 96, in tiles of all shapes (median errors 5, 2.5 and 1.3 %; the tile chosen lies
+// 4.7, 1.7 and 0.6 % above the best tried).
+struct BlockCost {
+  double start, tile, turn0, turn1, turn2, load, mb;
+};
+constexpr BlockCost kBlock[3] = {{4.71, 0.0, 0.0, 1.22, 0.34, 0.085, 0.24}, {5.29, 0.60, 0.04, 0.38, 0.79, 0.12, 0.13}, {7.11, 0.80, 0.15, 0.57, 1.59, 0.25, 0.11}};
+// The three launches: theirs, the bytes, the products, the pixels (median error 4 %).
+double three_launches_us(const Problem& a, const Problem& c) {
+  const double px = a.M, macs = px * a.k * ((double)a.c + 9.0 * a.k + c.k);
+  return 13.8 + 0.238e-6 * px * a.c + 2.61e-9 * macs + 0.254e-4 * px;
+}
+// One launch where it is expected to take less than nine tenths of three: over the 300 blocks 0.61 of their time, none slower (all of
+// them in one launch: 0.61, two slower by half a percent).  With fewer channels in the middle more of each product is fill than the
+// estimate was fitted to, and a block's three launches take as long as one of these.
+constexpr double kBlockGain = 0.9;
+constexpr int kBlockMinMid = 24;
+
+// The lengths of equal parts of n, from `most` down to two (or n).
+struct Parts {
+  int n = 0, length[MOST_PIXELS / 3], count[MOST_PIXELS / 3];
+  Parts(int whole, int most, int forced) {
+    for (int l = whole < most ? whole : most; l >= (whole < 2 ? whole : 2); --l) {
+      const int c = (whole + l - 1) / l;
+      if ((whole + c - 1) / c != l || (forced && l != (whole + (whole + forced - 1) / forced - 1) / ((whole + forced - 1) / forced))) continue;
+      length[n] = l;
+      count[n++] = c;
+    }
+  }
+};
+
+// Chooses the tile: equal parts of the map.
+template <int CB>
+bool plan_tile(Block& b, int images, int slots, double below, int* grid, int* lds) {
+  using G = Shape<CB>;
+  const BlockCost& cost = kBlock[CB - 1];
+  const Parts cols(b.w, MOST_PIXELS / 3 - 2, knob_or(KNOB_I8_BLOCK_TW, 0)), rows(b.h, MOST_PIXELS / 3 - 2, knob_or(KNOB_I8_BLOCK_TH, 0));
+  const double fixed = cost.start + cost.mb * 1e-6 * ((double)b.x_bytes + b.y_bytes);
+  double best = -1.0;
+  int best_th = 0, best_tw = 0;
+  for (int i = 0; i < cols.n; ++i)
+    for (int j = 0; j < rows.n; ++j) {
+      const int tw = cols.length[i], th = rows.length[j], np = (th + 2) * (tw + 2);
+      const long long tiles = (long long)cols.count[i] * rows.count[j] * images;
+      if (np > MOST_PIXELS || tiles > 0x7FFFFFFF) continue;
+      const int pbp = (np + 31) / 32, pbt = (th * tw + 31) / 32, loads = (np * (b.c / 16) + BL_THREADS - 1) / BL_THREADS;
+      const double each = cost.tile + cost.turn0 * ((pbp + G::PIXELS - 1) / G::PIXELS) + cost.turn1 * ((pbt + G::PIXELS - 1) / G::PIXELS) +
+                          cost.turn2 * ((pbt + G::LAST_PIXELS - 1) / G::LAST_PIXELS) + cost.load * loads;
+      const double us = fixed + each * (double)((tiles + slots - 1) / slots);
+      if ((best >= 0.0 && us >= best) || place_tile<CB>(b, th, tw) > G::LDS) continue;
+      best = us;
+      best_th = th;
+      best_tw = tw;
+    }
+  if (best < 0.0 || best >= below) return false;
+  *lds = place_tile<CB>(b, best_th, best_tw);
+  const long long tiles = (long long)b.tiles_per_image * images;
+  *grid = tiles < slots ? (int)tiles : slots;
+  b.range = make_pw_range((int)tiles, 1, *grid);
+  b.div_tx = make_fastdiv((uint32_t)b.tiles_x);
+  b.div_tpi = make_fastdiv((uint32_t)b.tiles_per_image);
+  b.div_tw = make_fastdiv((uint32_t)b.tw);
+  b.div_pw = make_fastdiv((uint32_t)b.pw);
+  b.div_n16 = make_fastdiv((uint32_t)(b.c / 16));
+  return true;
+}
+
+template <int CB>
+bool launch_shape(Block& b, int images, double below, hipStream_t stream, hipError_t* status) {
+  const int slots = Shape<CB>::PER_CU * (num_compute_units() > 0 ? num_compute_units() : 256);
+  int grid = 0, lds = 0;
+  if (!plan_tile<CB>(b, images, slots, below, &grid, &lds)) return false;
+  auto launch = [&](auto kern) {
+    // once per instantiation; initialisation of a function-local static is thread-safe
+    static const hipError_t attr_status =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<CB>::LDS);
+    if (attr_status != hipSuccess) return attr_status;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BL_THREADS), lds, stream, b);
+    return hipGetLastError();
+  };
+  *status = b.addend ? launch(&block_i8_kernel<CB, true>) : launch(&block_i8_kernel<CB, false>);
+  return true;
+}
+
+}  // namespace
+
+bool launch_block_i8(const Problem& a, const Problem& b, const Problem& c, hipStream_t stream, hipError_t* status, const char** variant) {
+  const int mode = knob_or(KNOB_I8_BLOCK, 1);           // 0: off, 2: any block that fits (tests)
+  if (mode == 0 || !plain_layer(a, 1) || !plain_layer(b, 3) || !plain_layer(c, 1) || a.addend || b.addend) return false;
+  if (a.c % 32 != 0 || a.k % 4 != 0 || b.k != a.k || c.k % 16 != 0) return false;
+  const int cb = (a.k + 31) / 32;
+  if (cb > 3 || a.c > 128 * cb || c.k > 128 * cb) return false;
+  if (a.x_bytes > 0x7FFFFFFFu || (unsigned long long)c.M * c.k > 0x7FFFFFFFull) return false;
+  const size_t y_bytes = (size_t)c.M * c.k;
+  // a tile's neighbours read the input after its output is written
+  if (overlaps(c.y, y_bytes, a.x, a.x_bytes)) return false;
+  const Problem* all[3] = {&a, &b, &c};
+  for (const Problem* p : all)
+    if (overlaps(c.y, y_bytes, p->w, p->w_bytes) || overlaps(c.y, y_bytes, p->bias, (size_t)p->k * 4)) return false;
+  Block t;
+  t.x = a.x; t.x_bytes = a.x_bytes;
+  t.addend = c.addend; t.y = c.y; t.y_bytes = (unsigned)y_bytes;
+  t.h = a.h; t.w = a.w_; t.c = a.c;
+  t.r_off = c.r_off; t.r_mant = c.r_mant; t.r_shift = c.r_shift;
+  for (int i = 0; i < 3; ++i) fill_layer(t.l[i], *all[i]);
+  swizzle_of(t.c / 16, &t.x_shift, &t.x_mask);
+  const double below = mode == 2 ? 1e30 : a.k < kBlockMinMid ? 0.0 : kBlockGain * three_launches_us(a, c);
+  if (!(cb == 1   ? launch_shape<1>(t, a.n, below, stream, status)
+        : cb == 2 ? launch_shape<2>(t, a.n, below, stream, status)
+                  : launch_shape<3>(t, a.n, below, stream, status)))
+    return false;
+  static thread_local char name[48];
+  snprintf(name, sizeof(name), "block_i8_%dx%d%s", t.th, t.tw, t.addend ? "_add" : "");
+  *variant = name;
+  return true;
+}
+
+}  // namespace glowmi

@@ -22,7 +22,7 @@ enum Knob {
   KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_SMALLC_I8_WGS, KNOB_I8_PW_MIN_ITEMS,
   KNOB_I8_FC_SMALL_MAX_M, KNOB_I8_K3_MIN_BLOCKS, KNOB_I8_K3_WAVES, KNOB_I8_K3_GATHER, KNOB_DW, KNOB_F32_PATCH, KNOB_F32_PATCH_TILE, KNOB_F32_FC_ROWS,
   KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT, KNOB_F32_FEW, KNOB_F32_FEW_TILE, KNOB_F32_FC_FEW, KNOB_F32_FC_FEW_TILE, KNOB_I8_FEW, KNOB_I8_FEW_TILE,
-  KNOB_I8_SHORT, KNOB_I8_SHORT_FORM, KNOB_F32_SHORT, KNOB_F32_SHORT_FORM,
+  KNOB_I8_SHORT, KNOB_I8_SHORT_FORM, KNOB_F32_SHORT, KNOB_F32_SHORT_FORM, KNOB_I8_BLOCK, KNOB_I8_BLOCK_TH, KNOB_I8_BLOCK_TW,
   KNOB_COUNT
 };
 constexpr int kKnobUnset = INT_MIN;
@@ -259,6 +259,9 @@ hipError_t launch_pw_i8(const Problem& p, hipStream_t stream, const char** varia
 // int8 3x3 convolution over 64 input channels on many pixels (conv_k3c64_i8.hip).
 bool k3c64_i8_applicable(const Problem& p);
 hipError_t launch_k3c64_i8(const Problem& p, hipStream_t stream, const char** variant);
+// Three int8 layers of a sequence in one launch: 1x1, 3x3, 1x1 with or without an addend (block_i8.hip).
+// False: not a run for it, nothing is launched.
+bool launch_block_i8(const Problem& a, const Problem& b, const Problem& c, hipStream_t stream, hipError_t* status, const char** variant);
 bool smallc_i8_applicable(const Problem& p);
 // int8 FullyConnected with at most 64 rows in one launch (fc_small_i8.hip).
 bool fc_small_i8_applicable(const Problem& p);

@@ -129,6 +129,11 @@ glowmi_status run_sequence(const void* x, glowmi_qparam xq, const glowmi_seq_lay
     in_q = layers[i].yq;
   }
   for (int32_t i = 0; i < n; ++i) {
+    if (i + 2 < n && glowmi::run_in_one_launch(&calls[(size_t)i], stream, &st)) {
+      if (st != GLOWMI_OK) return st;
+      i += 2;
+      continue;
+    }
     if (plan.cut_before[(size_t)i] == i) {              // a group of filters starts here
       glowmi::PreparedCall* group[glowmi::kCutJobs];
       int jobs = 0;
