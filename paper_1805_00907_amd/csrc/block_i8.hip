@@ -29,6 +29,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "igemm.h"
 #include "lds_direct.h"
 #include "pw_common.h"
@@ -119,6 +120,7 @@ struct Shape {
 
 template <int CB, bool ADD>
 __global__ __launch_bounds__(BL_THREADS, 2 * Shape<CB>::PER_CU) void block_i8_kernel(const Block p) {
+  fetch_arguments(p);
   using G = Shape<CB>;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;

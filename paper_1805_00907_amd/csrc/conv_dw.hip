@@ -24,6 +24,7 @@
 
 #include <cstdio>
 
+#include "arguments.h"
 #include "igemm.h"
 #include "quant_epilogue.h"
 
@@ -89,6 +90,7 @@ struct DwWindow {
 
 template <int STRIDE, int ROWS>
 __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p, const DwGrid g) {
+  fetch_arguments(p, g);
   constexpr int COLS = (DW_RUN - 1) * STRIDE + 3, XROWS = (ROWS - 1) * STRIDE + 3;
   const long long gid = dw_thread(g);
   if (gid < 0 || gid >= (long long)g.cq * g.slots) return;
@@ -162,6 +164,7 @@ __global__ __launch_bounds__(DW_THREADS) void conv_dw_f32_kernel(const Problem p
 // folded into one addend), Relu as the lower clamp bound, four codes per store.
 template <int STRIDE, int ROWS, bool PLAIN>
 __global__ __launch_bounds__(DW_THREADS) void conv_dw_i8_kernel(const Problem p, const DwGrid g) {
+  fetch_arguments(p, g);
   constexpr int COLS = (DW_RUN - 1) * STRIDE + 3, XROWS = (ROWS - 1) * STRIDE + 3;
   const long long gid = dw_thread(g);
   if (gid < 0 || gid >= (long long)g.cq * g.slots) return;

@@ -32,6 +32,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -74,6 +75,7 @@ struct K3 {
 template <bool ADD, int TW, int BN>
 __global__ __launch_bounds__(G_THREADS, 2) void conv_k3_f32_kernel(const Problem p, int tiles_y, int tiles_x,
                                                                   int tiles_c, int total) {
+  fetch_arguments(p, tiles_y, tiles_x, tiles_c, total);
   using T = K3<TW, BN>;
   constexpr int GP = T::PW, G_APLANE = T::APLANE, G_BPLANE = T::BPLANE, G_BBUF = T::BBUF, G_BN = BN;
   constexpr int G_ITEMS = T::ITEMS, G_PASSES = T::PASSES, G_PREF = T::PREF;

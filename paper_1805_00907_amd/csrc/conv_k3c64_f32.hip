@@ -32,6 +32,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -63,6 +64,7 @@ static_assert(2 * K_APLANE >= 8 * 32 * 64 * 4, "exchange of the partial tiles fi
 template <bool ADD>
 __global__ __launch_bounds__(K_THREADS, 2) void conv_k3c64_f32_kernel(const Problem p, int tiles_y, int tiles_x,
                                                                      int tiles_c, int total) {
+  fetch_arguments(p, tiles_y, tiles_x, tiles_c, total);
   extern __shared__ __align__(16) unsigned char lds[];
   unsigned char* bring = lds + 2 * K_APLANE;
   unsigned* maxw = reinterpret_cast<unsigned*>(lds + K_STAGE);

@@ -23,6 +23,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "arguments.h"
 #include "igemm.h"
 #include "pw_common.h"
 #include "quant_epilogue.h"
@@ -58,6 +59,7 @@ __host__ __device__ constexpr int k3_staged_row(int c) {
 template <int WAVES, bool ADD>
 __global__ __launch_bounds__(WAVES * 64, 1) void conv_k3c64_i8_kernel(const Problem p, int blocks_div,
                                                                       int blocks_rem) {
+  fetch_arguments(p, blocks_div, blocks_rem);
   extern __shared__ __align__(16) unsigned char smem[];   // filter slice, chunk regions, channel terms
   unsigned char* wlds = smem;
   int* cterm = reinterpret_cast<int*>(smem + K3_BN * K3_WPITCH + WAVES * K3_AREGION);
@@ -291,6 +293,7 @@ constexpr int t2_lds_bytes() { return K3_BN * K3_WPITCH + WAVES * T2_REGION + K3
 template <int WAVES, bool ADD>
 __global__ __launch_bounds__(WAVES * 64, 1) void conv_k3c64_i8_tile_kernel(const Problem p, int blocks_y, int blocks_x,
                                                                            int items_div, int items_rem) {
+  fetch_arguments(p, blocks_y, blocks_x, items_div, items_rem);
   extern __shared__ __align__(16) unsigned char smem[];   // filter slice, patch regions, channel terms
   unsigned char* wlds = smem;
   int* cterm = reinterpret_cast<int*>(smem + K3_BN * K3_WPITCH + WAVES * T2_REGION);

@@ -33,6 +33,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -65,6 +66,7 @@ static_assert(V_LDS <= 160 * 1024, "LDS of one CU");
 template <bool ADD, int NB>
 __global__ __launch_bounds__(V_THREADS, 2) void conv_k3v_f32_kernel(const Problem p, int th, int tw, int tiles_y,
                                                                    int tiles_x, int tiles_c, int total) {
+  fetch_arguments(p, th, tw, tiles_y, tiles_x, tiles_c, total);
   extern __shared__ __align__(16) unsigned char lds[];
   unsigned char* bring = lds + 2 * V_APLANE;
   unsigned* maxw = reinterpret_cast<unsigned*>(lds + V_STAGE);

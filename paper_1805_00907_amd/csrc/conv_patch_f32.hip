@@ -35,6 +35,7 @@
 #include <cstdio>
 #include <cstdlib>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -101,6 +102,7 @@ template <int V> struct Const { static constexpr int value = V; };
 
 template <int R, int ST, int PXB, int CHB, int W, bool ADD>
 __global__ __launch_bounds__(64 * W, 2) void conv_patch_f32_kernel(const Problem p, const Tiles tl) {
+  fetch_arguments(p, tl);
   using T = Patch<R, ST, PXB, CHB, W>;
   extern __shared__ __align__(16) unsigned char lds[];
   unsigned* maxw = reinterpret_cast<unsigned*>(lds + T::WORDS_AT);
@@ -472,6 +474,7 @@ struct CutJobs {
 };
 template <int N>
 __global__ __launch_bounds__(64 * CUT_ROWS) void cut_filter_kernel(const CutJobs<N> jobs) {
+  fetch_arguments(jobs);
   __shared__ unsigned largest[CUT_ROWS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int j = 0;

@@ -22,6 +22,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "arguments.h"
 #include "igemm.h"
 #include "pw_common.h"
 #include "quant_epilogue.h"
@@ -64,6 +65,7 @@ template <int K, bool CONTIGUOUS, bool ADD>
 __global__ __launch_bounds__(PWQ_THREADS, PwQ<K>::WG_PER_CU) void conv_pw_i8_kernel(const Problem p,
                                                                                   const PwRange full,
                                                                                   const PwRange last) {
+  fetch_arguments(p, full, last);
   using G = PwQ<K>;
   extern __shared__ __align__(16) unsigned char smem[];   // filter slice, A regions, channel terms
   unsigned char* wlds = smem;

@@ -25,6 +25,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "bf16_pieces.h"
 #include "igemm.h"
 #include "pw_common.h"
@@ -56,6 +57,7 @@ constexpr int short_f32_lds(int nt, int pitch) { return nt * 32 * (3 * pitch + 4
 // 40000 24.0 -> 22.5).
 template <int NT, bool ADD, bool LINES>
 __global__ __launch_bounds__(64 * waves_of(NT, ADD), waves_per_simd(NT, ADD)) void conv_short_f32_kernel(const Problem p, const ShortF32Walk walk) {
+  fetch_arguments(p, walk);
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int BN = 32 * NT, T = SF_T, SF_WAVES = waves_of(NT, ADD), SF_THREADS = 64 * SF_WAVES;
   const int pitch = walk.pitch, plane = BN * pitch;

@@ -24,6 +24,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "i8_chunks.h"
 #include "igemm.h"
 #include "pw_common.h"
@@ -72,6 +73,7 @@ constexpr int short_lds(int nt, int pitch) { return nt * 32 * pitch + nt * 32 * 
 // 11.3, 1x1 30->144 at 27540 9.4 -> 5.2; 64 of 90 layers move and take 0.79 of the time; 1x1 24->183 at 72090 21.2 -> 10.0).
 template <int NT, int T, bool TAPS, bool ADD, bool ODD>
 __global__ __launch_bounds__(SH_THREADS, 4) void conv_short_i8_kernel(const Problem p, const ShortWalk walk) {
+  fetch_arguments(p, walk);
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int BN = 32 * NT;
   constexpr bool LINES = T == 4;

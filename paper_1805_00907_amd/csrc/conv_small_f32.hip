@@ -23,6 +23,7 @@
 
 #include <cstdlib>
 
+#include "arguments.h"
 #include "igemm.h"
 
 namespace glowmi {
@@ -38,6 +39,7 @@ constexpr int CS_MAXG = 10;                     // groups of 8 reduction indices
 template <int G>
 __global__ __launch_bounds__(CS_THREADS, 1) void conv_small_f32_kernel(const Problem p, int groups_total,
                                                                        int groups_per_split) {
+  fetch_arguments(p, groups_total, groups_per_split);
   __shared__ float part[CS_WAVES * 16 * 64];    // partial accumulators [wave][register][lane]
 
   const int tid = threadIdx.x;

@@ -18,6 +18,7 @@
 // sums them), or stay on the tiled kernels.
 #include <hip/hip_runtime.h>
 
+#include "arguments.h"
 #include "i8_chunks.h"
 #include "igemm.h"
 #include "quant_epilogue.h"
@@ -43,6 +44,7 @@ struct Grid {
 
 template <int STEPS>
 __global__ __launch_bounds__(CQ_THREADS, STEPS <= 4 ? 4 : 2) void conv_small_i8_kernel(const Problem p, const Grid gr) {
+  fetch_arguments(p, gr);
   __shared__ __align__(16) int part[CQ_WAVES * 32 * CQ_PITCH];
   __shared__ int sums[64];                       // filter code sums per channel, input code sums per pixel
   int* wsum = sums;

@@ -23,6 +23,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 
@@ -73,6 +74,7 @@ struct SmallC {
 template <int R, int S, int C, int STRIDE, int NB, int CW>
 __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Problem p, int tiles_y, int tiles_x,
                                                                     int total_tiles, int n_tiles) {
+  fetch_arguments(p, tiles_y, tiles_x, total_tiles, n_tiles);
   using G = SmallC<R, S, C, STRIDE, NB, CW>;
   constexpr int TH = G::TH;
   extern __shared__ __align__(16) float patch[];          // [2][PH + 1][PITCH]
@@ -316,6 +318,7 @@ struct SmallCB {
 template <int R, int S, int C, int STRIDE, int NB, int CW>
 __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(const Problem p, int tiles_y, int tiles_x,
                                                                             int total_tiles, int n_tiles) {
+  fetch_arguments(p, tiles_y, tiles_x, total_tiles, n_tiles);
   using G = SmallCB<R, S, C, STRIDE, NB, CW>;
   constexpr int TH = G::TH;
   static_assert((STRIDE * C) % 2 == 0 && G::PITCH % 2 == 0, "a pixel's run starts on a 4-byte boundary");

@@ -25,6 +25,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "arguments.h"
 #include "i8_chunks.h"
 #include "igemm.h"
 #include "pw_common.h"
@@ -86,6 +87,7 @@ __device__ __forceinline__ unsigned load4_shift(unsigned d, unsigned over) {
 template <int R, int STRIDE, int NBC>
 __global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Problem p, int blocks_y, int blocks_x,
                                                                       int items_div, int items_rem, int n_tiles) {
+  fetch_arguments(p, blocks_y, blocks_x, items_div, items_rem, n_tiles);
   using G = SmallI8<R, STRIDE, NBC>;
   constexpr int PH = G::PH, PW = G::PW, PITCH = G::PITCH, STEPS = G::STEPS;
   __shared__ __align__(16) int lds[G::LDS_DWORDS];

@@ -23,6 +23,7 @@
 //     bias + activation, one store.
 #include <hip/hip_runtime.h>
 
+#include "arguments.h"
 #include "igemm.h"
 
 namespace glowmi {
@@ -55,6 +56,7 @@ __device__ __forceinline__ float elem(const typename VecOf<VW>::type& v, int j) 
 
 template <int VW>
 __global__ __launch_bounds__(FSF_THREADS) void fc_small_f32_kernel(const Problem p, int strips, int steps_per_wave) {
+  fetch_arguments(p, strips, steps_per_wave);
   constexpr int U = 4 / VW < 1 ? 1 : 4 / VW;       // steps per chunk: 16 weight registers per set
   constexpr int COLS = 16 * VW;
   typedef typename VecOf<VW>::type wvec;
@@ -164,6 +166,7 @@ constexpr int FR_DEPTH = 8;                  // rows of a lane in flight
 
 template <int MR, int LPR>
 __global__ __launch_bounds__(FR_THREADS) void fc_rows_f32_kernel(const Problem p, int strips) {
+  fetch_arguments(p, strips);
   constexpr int ROWS = FR_THREADS / LPR;           // weight rows per pass
   constexpr int COLS = 4 * LPR;
   __shared__ float red[16 * MR * COLS];

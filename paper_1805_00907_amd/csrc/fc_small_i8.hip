@@ -23,6 +23,7 @@
 
 #include <cstdlib>
 
+#include "arguments.h"
 #include "i8_chunks.h"
 #include "igemm.h"
 #include "quant_epilogue.h"
@@ -44,6 +45,7 @@ constexpr int FS_PITCH = FS_COLS;                // bytes per staged weight row
 // short reduction is spread over all eight wavefronts too (FC 18x552x4072: two steps instead of three wavefronts with eight).
 template <int STEPS>
 __global__ __launch_bounds__(FS_THREADS, STEPS <= 4 ? 4 : 2) void fc_small_i8_kernel(const Problem p) {
+  fetch_arguments(p);
   constexpr int KW = 32 * STEPS;                           // weight rows per wavefront and pass
   constexpr int WLOADS = STEPS;                            // 16-byte weight loads per lane and pass
   constexpr int REGION = KW * FS_PITCH > 4096 ? KW * FS_PITCH : 4096;   // bytes per wavefront: its weight slice, later its 4 KB of partial sums

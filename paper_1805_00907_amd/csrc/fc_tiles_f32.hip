@@ -21,6 +21,7 @@
 // Few tiles: the reduction is also split over the grid, and the partial sums go through the workspace.
 #include <hip/hip_runtime.h>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -62,6 +63,7 @@ struct RunningScale {
 template <int MB>
 __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Problem p, int tiles_m, int tiles_n, int total, int chunks,
                                                                         int chunks_per_split) {
+  fetch_arguments(p, tiles_m, tiles_n, total, chunks, chunks_per_split);
   constexpr int ROWS = 32 * MB, LOADS = ROWS / 16;
   constexpr int PLANE = ROWS * 32;                       // bytes of a plane of a wavefront's chunk of x
   extern __shared__ __align__(16) unsigned char lds[];

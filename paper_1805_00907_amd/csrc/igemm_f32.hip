@@ -21,6 +21,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "arguments.h"
 #include "igemm.h"
 
 namespace glowmi {
@@ -98,6 +99,7 @@ struct Item {
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool VEC, bool B_KN, bool LONGK, bool CHAINV = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_f32_kernel(const Problem p, int tiles_m,
                                                                           int tiles_n, int total_work) {
+  fetch_arguments(p, tiles_m, tiles_n, total_work);
   constexpr int NTHREADS = 64 * WAVES_M * WAVES_N;
   constexpr int ROWS_PER_PASS = NTHREADS / KV;            // tile rows staged per pass over the threads
   static_assert(NTHREADS == 256 || NTHREADS == 512, "four or eight wavefronts per workgroup");
@@ -470,6 +472,7 @@ __global__ __launch_bounds__(256) void splitk_finish_f32(const float* __restrict
                                                          const float* __restrict__ bias,
                                                          const float* addend, float* y, int total, int k,
                                                          int split_k, int act, float lo, float hi) {
+  fetch_arguments(partial, bias, addend, y, total, k, split_k, act, lo, hi);
   typedef float vec __attribute__((ext_vector_type(W)));
   const int groups = total / W;                      // W divides total (the launcher checks)
   for (int gi = blockIdx.x * blockDim.x + threadIdx.x; gi < groups; gi += gridDim.x * blockDim.x) {
@@ -499,6 +502,7 @@ __global__ __launch_bounds__(256) void splitk_finish_f32(const float* __restrict
 // Finish of a split reduction whose element-wise chain is a general op list: partial sums in split
 // order, bias, then the ops in order, one store.
 __global__ __launch_bounds__(256) void splitk_finish_chain_f32(const Problem p, int total) {
+  fetch_arguments(p, total);
   const float* __restrict__ partial = static_cast<const float*>(p.partial);
   const float* __restrict__ bias = static_cast<const float*>(p.bias);
   float* y = static_cast<float*>(p.y);
@@ -543,6 +547,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void fc_skinny16_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ Wt, const float* __restrict__ bias,
     float* __restrict__ Y, float* __restrict__ partial, int M, int K, int N, int act, int split_k,
     int steps_per_split) {
+  fetch_arguments(A, Wt, bias, Y, partial, M, K, N, act, split_k, steps_per_split);
   __shared__ float red[(SK_WAVES - 1) * 16 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c16 = lane & 15, q = lane >> 4;

@@ -33,6 +33,7 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "arguments.h"
 #include "f16_pieces.h"
 #include "igemm.h"
 #include "lds_direct.h"
@@ -262,6 +263,7 @@ __global__ __launch_bounds__(256) void pack2_pair_kernel(const float* __restrict
                                                          const float* __restrict__ w, unsigned short* __restrict__ wp,
                                                          long long w_count8, long long w_elems, int transposed, int K,
                                                          int N, int tiles_n, unsigned* __restrict__ w_trailer) {
+  fetch_arguments(x, xp, x_count8, x_elems, blocks_x, x_trailer, w, wp, w_count8, w_elems, transposed, K, N, tiles_n, w_trailer);
   __shared__ float tile[kPackTile][kPackTile + 1];
   const int b = (int)blockIdx.x;
   if (b < blocks_x) pack2_rows(x, xp, x_count8, x_elems, b, blocks_x, x_trailer);
@@ -283,6 +285,7 @@ constexpr int kFragmentsAhead = WN == 2 && !LONGK ? 1 : 0;
 template <int WN, bool PADDED, bool LONGK, int RING>
 __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem p, int tiles_m, int tiles_n,
                                                                    int band_n, int total_work) {
+  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work);
   constexpr int BN = 64 * WN;
   constexpr int WAVES = 4 * WN;
   constexpr int A_GROUPS = (PBM / 16) / WAVES;          // 16-row groups of the pixel tile one wavefront loads per plane

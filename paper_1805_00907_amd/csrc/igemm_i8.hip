@@ -25,6 +25,7 @@
 #include <cstdio>
 #include <cstdlib>
 
+#include "arguments.h"
 #include "i8_chunks.h"
 #include "igemm.h"
 #include "quant_epilogue.h"
@@ -77,6 +78,7 @@ __device__ __forceinline__ int apply_chain_i8(const Problem& p, int v, size_t of
 // six slabs: 10.6 us with one group).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int KGRP, bool B_KN, bool CHAINV = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KGRP, BM * BN / (WAVES_M * WAVES_N) <= (B_KN ? 1024 : 2048) ? 4 : 2) void igemm_i8_kernel(const Problem p, const Walk walk) {
+  fetch_arguments(p, walk);
   constexpr int NTHREADS = 64 * WAVES_M * WAVES_N;      // of one group
   constexpr int ALL_THREADS = NTHREADS * KGRP;
   constexpr int ROWS_PER_PASS = NTHREADS / KV;
@@ -539,6 +541,7 @@ __global__ __launch_bounds__(256) void splitk_finish_i8(const int* __restrict__ 
                                                         int r_shift, signed char* y, int total, int k,
                                                         int split_k, int mant, int shift, int y_off,
                                                         int lo, int hi) {
+  fetch_arguments(partial, bias, addend, r_off, r_mant, r_shift, y, total, k, split_k, mant, shift, y_off, lo, hi);
   typedef unsigned vec __attribute__((ext_vector_type(W)));
   const int groups = total / W;                      // W divides total (the launcher checks)
   for (int gi = blockIdx.x * blockDim.x + threadIdx.x; gi < groups; gi += gridDim.x * blockDim.x) {
@@ -574,6 +577,7 @@ __global__ __launch_bounds__(256) void splitk_finish_i8(const int* __restrict__ 
 
 // Finish of a split reduction whose element-wise chain is a general op list.
 __global__ __launch_bounds__(256) void splitk_finish_chain_i8(const Problem p, int total) {
+  fetch_arguments(p, total);
   const int* __restrict__ partial = static_cast<const int*>(p.partial);
   const int* __restrict__ bias = static_cast<const int*>(p.bias);
   signed char* y = static_cast<signed char*>(p.y);

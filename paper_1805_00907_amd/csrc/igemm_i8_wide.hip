@@ -33,6 +33,7 @@
 #include <cstdio>
 #include <cstdlib>
 
+#include "arguments.h"
 #include "igemm.h"
 #include "lds_direct.h"
 #include "quant_epilogue.h"
@@ -69,6 +70,7 @@ template <int BN, bool B_KN, bool PADDED, bool XSUM, int NBUF, bool RAGGED = fal
 __global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_i8_wide_kernel(const Problem p, int tiles_m,
                                                                                    int tiles_n, int band_n,
                                                                                    int total_work, const FastDiv div_tap) {
+  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work, div_tap);
   static_assert(BN == 64 || BN == 128, "channel tile");
   static_assert(!B_KN || BN == 128, "the [K][N] weight path stages 128 columns");
   constexpr int TN = BN / 64;                           // MFMA tiles along the channels per wavefront
