@@ -145,6 +145,14 @@ struct PlaneOrder {
   __device__ __forceinline__ PlaneOrder(const unsigned* words, int channels, int pieces, bool known = false) {
     by_channel = true;
     if (!known) by_channel = (__builtin_amdgcn_readfirstlane((int)words[0]) & (int)kByChannel) != 0;   // uniform
+    set(channels, pieces);
+  }
+  // the same from the first word itself
+  __device__ __forceinline__ PlaneOrder(unsigned first_word, int channels, int pieces) {
+    by_channel = (__builtin_amdgcn_readfirstlane((int)first_word) & (int)kByChannel) != 0;
+    set(channels, pieces);
+  }
+  __device__ __forceinline__ void set(int channels, int pieces) {
     row = by_channel ? 16u : 16u * (unsigned)pieces;
     piece = by_channel ? 16u * (unsigned)channels : 16u;
   }

@@ -1,0 +1,348 @@
+// fp32 FullyConnected over planes of fp16 pieces (Section 3.4 of the paper: MatMul + broadcast add): the contraction of large calls,
+// whose input this call has cut into planes and whose weights were cut ahead of time or in this call (igemm_f32_p3.hip).  A product
+// of two cut values is three v_mfma_f32_32x32x16_f16 (f16_pieces.h).
+//
+// 128 rows x 128 columns per workgroup, eight wavefronts: four of 32 rows by all columns, twice, once for each half of every slab
+// of 64 reduction indices; the halves' sums meet in LDS at the end.
+//   - The weights' slab, 128 columns of 128 bytes in each plane, goes straight into a ring of three LDS buffers; the 16-byte chunk c
+//     of column n lies at c ^ (n / 2) % 8, so that the sixteen columns of a phase of a fragment read fall on different banks.
+//   - The input needs no LDS: a wavefront is the only one of its half that reads its 32 rows.  Its planes are ordered by piece
+//     ([K / 8][M][8], the order cut_rows_kernel and pack2_pieces write), in which a fragment is two runs of 512 bytes, and are read
+//     into registers a slab and a half ahead.
+//   - The weights take the matrix instruction's first operand, so that a lane ends up with one row and four columns in a row of
+//     registers: 16-byte stores, one scale of the input's per lane.
+// What bounds it: power.  A slab is 1536 cycles of matrix work on every SIMD and takes 1830, next to 1024 cycles of LDS reads, 256 of
+// LDS writes and 1024 of the vector memory path; in calls back to back the clock falls to 1.63 GHz (2.35 alone).  256 x 4096 x 4096
+// on 256 workgroups of 16 slabs: 4800 cycles until the first slab is there, 29300 for the slabs, 7200 for sums and stores, 28.6 us
+// where both operands went through LDS, 64-byte pieces of rows at a time, and results left a dword per row: 33.4; the whole call 45.2 ->
+// 40.9 us, 1024 rows 110 -> 104.  Sums as far from 64-bit ones as there (1.26e-7 of the result's norm).
+#include <hip/hip_runtime.h>
+
+#include "arguments.h"
+#include "f16_pieces.h"
+#include "igemm.h"
+#include "lds_direct.h"
+
+namespace glowmi {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+constexpr int FP_ROWS = 128, FP_COLS = 128;
+constexpr int FP_SLAB = 64;                             // reduction indices per slab: one 128-byte line of a column's plane
+constexpr int FP_RING = 3;
+constexpr int FP_PLANE = FP_COLS * 2 * FP_SLAB, FP_BUF = 2 * FP_PLANE;
+constexpr int FP_TOTALS = FP_ROWS * FP_COLS * 4;        // LONGK: the sums folded so far, behind the ring
+constexpr int FP_FLUSH = 16;                            // slabs: a chain of 512 reduction indices per wavefront
+
+// A fragment of the input, 16 bytes per lane (zeros where the offset is out of range).  Inline assembly like load16_to_lds, and for
+// its sake: the compiler counts only the loads it knows of.  The kernel waits, then passes the registers through arrived().
+__device__ __forceinline__ v4i load16(v4i rsrc, unsigned voffset) {
+  v4i r;
+  asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(r) : "v"(voffset), "s"(rsrc) : "memory");
+  return r;
+}
+__device__ __forceinline__ void arrived(v4i& a, v4i& b, v4i& c, v4i& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+
+// LONGK: more than FP_FLUSH slabs per workgroup; the sums so far are folded into totals in LDS, by the two halves in turn.
+template <bool LONGK>
+__global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p, int tiles_m, int tiles_n, int band_n, int total_work) {
+  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work);
+  __builtin_amdgcn_sched_barrier(0);                     // none is read, and waited for, ahead of it
+  extern __shared__ __align__(16) unsigned char lds[];
+
+  // ---- which tile: id % 8 picks the XCD, which walks a contiguous run of tiles in bands of band_n tile columns
+  const int per_xcd = gridDim.x >> 3;
+  const int wk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (wk >= total_work) return;
+  const int plane_tiles = tiles_m * tiles_n;
+  const int split = wk / plane_tiles, wi = wk - split * plane_tiles;
+  const int band = wi / (tiles_m * band_n);
+  const int in_band = wi - band * tiles_m * band_n;
+  const int band_w = tiles_n - band * band_n < band_n ? tiles_n - band * band_n : band_n;
+  const int tm = in_band / band_w;
+  const int tn = band * band_n + (in_band - tm * band_w);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kgrp = wave >> 2, wm = wave & 3;
+  const int lrow = lane & 31, lhalf = lane >> 5;
+
+  const unsigned xpb = p.x_bytes >> 1, wpb = p.w_bytes >> 1;   // bytes of a plane
+  const v4i rsrc_x1 = make_rsrc(p.planes, xpb), rsrc_x2 = make_rsrc(static_cast<const unsigned char*>(p.planes) + xpb, xpb);
+  const v4i rsrc_w1 = make_rsrc(p.w_planes, wpb), rsrc_w2 = make_rsrc(static_cast<const unsigned char*>(p.w_planes) + wpb, wpb);
+  const unsigned first_word = *(const unsigned __attribute__((address_space(4)))*)p.w_range;   // a scalar load
+  constexpr unsigned OOB = 0x80000000u;                  // beyond any plane (at most 512 MiB)
+
+  const int total_slabs = (p.Kgemm + FP_SLAB - 1) / FP_SLAB;
+  const int slab_begin = split * p.slabs_per_split;
+  int slab_end = slab_begin + p.slabs_per_split;
+  if (slab_end > total_slabs) slab_end = total_slabs;
+  int chunk_end = slab_end * (FP_SLAB / 8);             // loads from here on are zeros and move nothing
+  if (chunk_end > (p.Kgemm >> 3)) chunk_end = p.Kgemm >> 3;
+
+  // ---- the input: chunk (of eight indices) and byte offset of this lane's next fragment; rows past the last have no chunk
+  const int m = tm * FP_ROWS + wm * 32 + lrow;
+  const unsigned x_piece = 16u * (unsigned)p.M;
+  int x_chunk = slab_begin * 8 + kgrp * 4 + lhalf;
+  unsigned x_at = (unsigned)x_chunk * x_piece + 16u * (unsigned)m;
+  if (m >= p.M) x_chunk = 1 << 28;
+  v4i xs[FP_RING][2][2] = {};                            // [slab % 3][step of 16 indices][plane]
+  auto x_offset = [&](int st) { return x_chunk + 2 * st < chunk_end ? x_at + 2u * st * x_piece : OOB; };
+  auto issue_x = [&](int set, int st, int pl) { xs[set][st][pl] = load16(pl ? rsrc_x2 : rsrc_x1, x_offset(st)); };
+  auto next_x = [&]() { x_chunk += 8; x_at += 8u * x_piece; };
+
+  // ---- the weights: a load covers eight columns, lane l the column l / 8 and the chunk that belongs at position l % 8
+  int w_chunk[2];
+  unsigned w_at[2], w_step;
+  auto place_w = [&](unsigned row, unsigned piece) {     // bytes from a column's piece to the next column's, to its next piece
+    const int c = slab_begin * 8 + ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7));
+    w_step = 8u * piece;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int n = tn * FP_COLS + 8 * (wave + 8 * t) + (lane >> 3);
+      w_chunk[t] = n < p.k ? c : 1 << 28;
+      w_at[t] = (unsigned)n * row + (unsigned)c * piece;
+    }
+  };
+  const unsigned lds_base = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + wave * 1024);
+  auto issue_w = [&](int buf, int t, int pl) {
+    load16_to_lds(pl ? rsrc_w2 : rsrc_w1, lds_base + buf * FP_BUF + pl * FP_PLANE + t * 8192, w_chunk[t] < chunk_end ? w_at[t] : OOB);
+  };
+  auto next_w = [&]() {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      w_chunk[t] += 8;
+      w_at[t] += w_step;
+    }
+  };
+  auto issue_slab_x = [&](int set) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) issue_x(set, q >> 1, q & 1);
+    next_x();
+  };
+  auto issue_slab_w = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) issue_w(buf, q >> 1, q & 1);
+    next_w();
+  };
+
+  // hi the h1 h1' products, lo the cross terms (weight 2^-11), of 32 columns each
+  v16f hi[4], lo[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) hi[j][e] = lo[j][e] = 0.f;
+  v4f* const totals = reinterpret_cast<v4f*>(lds + FP_RING * FP_BUF) + wm * 16 * 64 + lane;
+  if (LONGK) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) totals[(kgrp * 8 + q) * 64] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+
+  v8h f[4][2];                                           // the step's weights: [32 columns][plane]
+  const int swz = (lrow >> 1) & 7;
+  const int frag[2] = {lrow * 128 + (((kgrp * 4 + lhalf) ^ swz) << 4), lrow * 128 + (((kgrp * 4 + 2 + lhalf) ^ swz) << 4)};
+  auto read_fragments = [&](int buf, int st, int j) {
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+      f[j][pl] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(lds + buf * FP_BUF + pl * FP_PLANE + frag[st] + j * 4096));
+  };
+  auto multiply = [&](int set, int st, int j, int which) {
+    const v8h x1 = __builtin_bit_cast(v8h, xs[set][st][0]), x2 = __builtin_bit_cast(v8h, xs[set][st][1]);
+    if (which == 0) lo[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[j][1], x1, lo[j], 0, 0, 0);
+    else if (which == 1) hi[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[j][0], x1, hi[j], 0, 0, 0);
+    else lo[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[j][0], x2, lo[j], 0, 0, 0);
+  };
+  auto barrier = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+
+  // ---- main loop.  In flight, oldest first, when slab s is begun: x(s), w(s + 1), x(s + 1), w(s + 2), four loads each; issued after the
+  // barrier in its middle, x(s + 2) and w(s + 3).  The barrier says that w(s + 1) has landed and that every wavefront has read all of
+  // w(s), whose buffer w(s + 3) takes.  A fragment's registers are refilled as soon as their three products are issued.
+  // (The first loads go out before the word is there that says in which order the weights' planes are: FullyConnected planes are
+  // rows.  The other order starts over.)
+  place_w(2u * (unsigned)p.Kgemm, 16u);
+  issue_slab_w(0);
+  issue_slab_x(0);
+  issue_slab_w(1);
+  const PlaneOrder order(first_word, p.k, p.Kgemm >> 3);
+  if (order.by_channel) {                                 // uniform
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    place_w(order.row, order.piece);
+    issue_slab_w(0);
+    issue_slab_w(1);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+  barrier();
+  issue_slab_x(1);
+  issue_slab_w(2);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) read_fragments(0, 0, j);
+  int done = 0;
+  for (int s0 = slab_begin; s0 < slab_end; s0 += FP_RING) {
+#pragma unroll
+    for (int u = 0; u < FP_RING; ++u) {
+      if (s0 + u < slab_end) {                            // uniform
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(12));
+        arrived(xs[u][0][0], xs[u][0][1], xs[u][1][0], xs[u][1][1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+          for (int which = 0; which < 3; ++which) multiply(u, 0, j, which);
+          read_fragments(u, 1, j);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int which = 0; which < 3; ++which) multiply(u, 1, 0, which);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(8 | (7 << 4));         // w(s + 1) has landed: vmcnt(8); and lgkmcnt(0)
+        barrier();
+        read_fragments((u + 1) % FP_RING, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 1; j < 4; ++j) {
+#pragma unroll
+          for (int which = 0; which < 3; ++which) {
+            multiply(u, 1, j, which);
+            const int q = (j - 1) * 3 + which;
+            __builtin_amdgcn_sched_barrier(0);
+            if (q < 4) issue_x((u + 2) % FP_RING, q >> 1, q & 1);
+            else if (q < 8) issue_w(u, (q - 4) >> 1, q & 1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          read_fragments((u + 1) % FP_RING, 0, j);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        next_x();
+        next_w();
+        // the halves fold in turn, eight slabs and their barriers apart
+        if (LONGK && (++done & (FP_FLUSH - 1)) == kgrp * (FP_FLUSH / 2)) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+              v4f t = totals[(j * 4 + e4) * 64];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                t[e] += __builtin_fmaf(lo[j][e4 * 4 + e], kLowPieceWeight, hi[j][e4 * 4 + e]);
+                hi[j][e4 * 4 + e] = lo[j][e4 * 4 + e] = 0.f;
+              }
+              totals[(j * 4 + e4) * 64] = t;
+            }
+        }
+      }
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));               // the zeros past the end have landed too: no register is used again before
+#pragma unroll
+  for (int u = 0; u < FP_RING; ++u) arrived(xs[u][0][0], xs[u][0][1], xs[u][1][0], xs[u][1][1]);
+  __syncthreads();                                        // every wavefront is done with the ring
+
+  // ---- the halves' sums meet in LDS, [row][column], the 16-byte unit u of a row at u ^ row % 32: the second half writes (LONGK:
+  // adds to) them, the first adds its own.
+  v4f* const sums = reinterpret_cast<v4f*>(lds) + (wm * 32 + lrow) * 32;
+  auto add_half = [&](bool add) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        v4f& at = sums[(j * 8 + e4 * 2 + lhalf) ^ lrow];
+        v4f v = {0.f, 0.f, 0.f, 0.f};
+        if (add) v = at;
+        if (LONGK && !add) v = totals[(j * 4 + e4) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += __builtin_fmaf(lo[j][e4 * 4 + e], kLowPieceWeight, hi[j][e4 * 4 + e]);
+        at = v;
+      }
+  };
+  if (kgrp) add_half(false);
+  __syncthreads();
+  if (!kgrp) add_half(true);
+
+  // ---- scaled back, bias and activation (or the partial sums); a wavefront writes two rows at a time, 16 bytes to a lane where
+  // the rows allow it
+  const bool finish = p.split_k == 1;
+  const bool relu = finish && p.act == 1;
+  const bool wide = (p.k & 3) == 0;                      // uniform; y and the partial sums are 16-byte aligned
+  const float* __restrict__ bias = finish ? static_cast<const float*>(p.bias) : nullptr;
+  float* const dst = finish ? static_cast<float*>(p.y) : static_cast<float*>(p.partial) + (size_t)split * p.M * p.k;
+  const int n0 = tn * FP_COLS + lrow * 4, row0 = wave * 16 + lhalf;
+  // what a column and a row are scaled back by, and what is added to them: the bias, and a NaN where they hold no finite numbers
+  float col_add[4], row_add[8];
+  int col_exp[4], row_exp[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int n = n0 + e < p.k ? n0 + e : p.k - 1;
+    const ScaleBack sb = scale_back(0, order.max_bits(p.w_range, n));
+    col_exp[e] = sb.neg_se;
+    col_add[e] = sb.poison + (bias ? bias[n] : 0.f);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = tm * FP_ROWS + row0 + 2 * i;
+    const ScaleBack sb = scale_back(p.x_range[p.x_range_n > 1 ? (row < p.M ? row : p.M - 1) : 0], 0);
+    row_exp[i] = sb.neg_se - scale_back(0, 0).neg_se;
+    row_add[i] = sb.poison;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = row0 + 2 * i, row = tm * FP_ROWS + r;
+    v4f v = reinterpret_cast<const v4f*>(lds)[r * 32 + (lrow ^ (r & 31))];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = __builtin_ldexpf(v[e], row_exp[i] + col_exp[e]) + row_add[i] + col_add[e];
+      if (relu) v[e] = clamp_act(v[e], p.act_lo, p.act_hi);
+    }
+    if (row < p.M) {
+      float* const at = dst + (size_t)row * p.k + n0;
+      if (wide) {
+        if (n0 < p.k) *reinterpret_cast<v4f*>(at) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n0 + e < p.k) at[e] = v[e];
+      }
+    }
+  }
+}
+
+template <bool LONGK>
+hipError_t launch(const Problem& p, const Plan& plan, hipStream_t stream) {
+  auto kern = igemm_f32_p3_fc_kernel<LONGK>;
+  constexpr int lds_bytes = FP_RING * FP_BUF + (LONGK ? FP_TOTALS : 0);
+  static const hipError_t attr_status =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  if (attr_status != hipSuccess) return attr_status;
+  const long long total_work = (long long)plan.tiles_m * plan.tiles_n * plan.split_k;
+  const long long per_xcd = (total_work + 7) / 8;
+  int band_n = 1;
+  while ((long long)band_n * band_n * 2 < per_xcd && band_n < plan.tiles_n) ++band_n;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(512), lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, band_n,
+                     (int)total_work);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// The contraction over planes that p names (input by piece, weights in either order); the caller finishes a split reduction.
+hipError_t launch_fc_planes_f32(const Problem& p, const Plan& plan, hipStream_t stream, const char** variant) {
+  const bool longk = plan.slabs_per_split > FP_FLUSH;
+  *variant = longk ? "igemm_f32_p3_fc_128x128_longk" : "igemm_f32_p3_fc_128x128";
+  return longk ? launch<true>(p, plan, stream) : launch<false>(p, plan, stream);
+}
+
+int fc_planes_f32_slab() { return FP_SLAB; }
+
+}  // namespace glowmi

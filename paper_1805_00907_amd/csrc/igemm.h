@@ -200,6 +200,8 @@ hipError_t launch_fc_rows_f32(const Problem& p, hipStream_t stream, const char**
 // fp32 large contractions as three fp16 MFMAs per product over operands cut into two fp16 planes (igemm_f32_p3.hip).
 bool p3_f32_applicable(const Problem& p);
 Plan plan_p3_f32(const Problem& p);
+hipError_t launch_fc_planes_f32(const Problem& p, const Plan& plan, hipStream_t stream, const char** variant);   // fc_planes_f32.hip
+int fc_planes_f32_slab();
 hipError_t launch_p3_f32(const Problem& p, const Plan& plan, hipStream_t stream, const char** variant);
 // A tensor's largest magnitude is found as kRangeWords partial maxima (a pass over the tensor), reduced by whoever
 // needs it.  A tensor's planes: two fp16 planes of `elems` each, padded to 256 bytes, then a trailer of

@@ -14,7 +14,8 @@
 // element, again for every tile that stages it (a 3 x 3 layer stages each input element 9 x N/128
 // times), and measured that eats most of the gain.  So the pieces are made ONCE per call by a packing
 // pass into two fp16 planes per operand (workspace), FullyConnected weights ([K][N]) transposed to
-// K-contiguous on the way, and the contraction kernel has no vector ALU work in its loop at all:
+// K-contiguous on the way, and the contraction kernel has no vector ALU work in its loop at all
+// (FullyConnected has one of its own, fc_planes_f32.hip, over an input that is cut here too):
 //   - 128 pixels x 64*WN channels per workgroup; 2 x WN wavefronts tile the output (64 x 64 each) and two such
 //     sets split every slab's 32 reduction indices between them (16 each); the two partial tiles are
 //     exchanged through LDS at the end and each wavefront finishes half of them;
@@ -199,15 +200,42 @@ __device__ __forceinline__ void pack2_transposed(const float* __restrict__ w, un
   }
 }
 
-// A FullyConnected input measured and cut in one launch, each row by a scale of its own: a workgroup per row, which it holds
-// in registers up to 8192 values (what is beyond is read twice); words[row] = the bits of its largest magnitude.  One scale
-// for the whole input takes a launch that measures it first (256 rows of 4096: 5 + 6 us, 4 here).
-__global__ __launch_bounds__(256) void cut_rows_kernel(const float* __restrict__ x, unsigned short* __restrict__ dst, int row8,
-                                                       long long plane_elems, unsigned* __restrict__ words) {
+// A FullyConnected input [M][K] -> two planes ordered by piece, [K / 8][M][8], with one scale.  A wavefront cuts eight rows by eight
+// pieces at a time: it reads 256 bytes of each row and writes eight runs of 128.
+__device__ __forceinline__ void pack2_pieces(const float* __restrict__ src, unsigned short* __restrict__ dst, int rows, int row8, int block,
+                                             int blocks, unsigned* __restrict__ trailer) {
+  const int se = take_scale(trailer, block == 0);
+  const int lane = threadIdx.x & 63, across = (row8 + 7) / 8;
+  const long long tiles = (long long)((rows + 7) / 8) * across;
+  const size_t plane = (size_t)rows * row8 * 8;
+  for (long long t = (long long)block * 4 + (threadIdx.x >> 6); t < tiles; t += (long long)blocks * 4) {
+    const int tr = (int)(t / across);
+    const int row = tr * 8 + (lane >> 3), piece = (int)(t - (long long)tr * across) * 8 + (lane & 7);
+    if (row >= rows || piece >= row8) continue;
+    const float* from = src + ((size_t)row * row8 + piece) * 8;
+    const v4f a = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(from));
+    const v4f b = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(from + 4));
+    const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    v4u p1, p2;
+    cut8(v, se, p1, p2);
+    unsigned short* to = dst + ((size_t)piece * rows + row) * 8;
+    *reinterpret_cast<v4u*>(to) = p1;
+    *reinterpret_cast<v4u*>(to + plane) = p2;
+  }
+}
+
+// The same measured and cut in one launch, each row by a scale of its own: a workgroup per row, which it holds in registers up
+// to 8192 values (what is beyond is read twice); words[row] = the bits of its largest magnitude.  One scale for the whole input
+// takes a launch that measures it first (256 rows of 4096: 5 + 6 us, 4 here).  Rows that lie side by side are cut on one XCD (its
+// share of consecutive workgroup ids is every eighth), whose L2 joins their pieces of 16 bytes to whole lines.
+__global__ __launch_bounds__(256) void cut_rows_kernel(const float* __restrict__ x, unsigned short* __restrict__ dst, int rows, int row8,
+                                                       unsigned* __restrict__ words) {
   constexpr int HELD = 4;
   __shared__ unsigned red[4];
   const int tid = threadIdx.x;
-  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(x) + (size_t)blockIdx.x * row8 * 2;
+  const int row = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+  if (row >= rows) return;
+  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(x) + (size_t)row * row8 * 2;
   v4f held[HELD][2];
 #pragma unroll
   for (int q = 0; q < HELD; ++q) {
@@ -227,15 +255,16 @@ __global__ __launch_bounds__(256) void cut_rows_kernel(const float* __restrict__
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 4; ++i) m = red[i] > m ? red[i] : m;
-  if (tid == 0) words[blockIdx.x] = m;
+  if (tid == 0) words[row] = m;
   const int se = scale_exponent(m);
-  unsigned short* __restrict__ out = dst + (size_t)blockIdx.x * row8 * 8;
+  unsigned short* __restrict__ out = dst + (size_t)row * 8;
+  const size_t plane = (size_t)rows * row8 * 8, piece = (size_t)rows * 8;
   auto write = [&](int g, const v4f& a, const v4f& b) {
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     v4u p1, p2;
     cut8_in_place(v, se, p1, p2);
-    *reinterpret_cast<v4u*>(out + 8 * g) = p1;
-    *reinterpret_cast<v4u*>(out + plane_elems + 8 * g) = p2;
+    *reinterpret_cast<v4u*>(out + piece * g) = p1;
+    *reinterpret_cast<v4u*>(out + plane + piece * g) = p2;
   };
 #pragma unroll
   for (int q = 0; q < HELD; ++q)
@@ -249,14 +278,20 @@ __global__ __launch_bounds__(256) void pack2_rows_kernel(const float* __restrict
   pack2_rows(src, dst, count8, plane_elems, (int)blockIdx.x, (int)gridDim.x, trailer);
 }
 
+__global__ __launch_bounds__(256) void pack2_pieces_kernel(const float* __restrict__ src, unsigned short* __restrict__ dst, int rows,
+                                                           int row8, unsigned* __restrict__ trailer) {
+  pack2_pieces(src, dst, rows, row8, (int)blockIdx.x, (int)gridDim.x, trailer);
+}
+
 __global__ __launch_bounds__(256) void pack2_transposed_kernel(const float* __restrict__ w, unsigned short* __restrict__ dst,
                                                                int K, int N, int tiles_n, unsigned* __restrict__ trailer) {
   __shared__ float tile[kPackTile][kPackTile + 1];
   pack2_transposed(w, dst, K, N, tiles_n, (int)blockIdx.x, tile, trailer);
 }
 
-// Both operands of one contraction in one launch: the first blocks_x workgroups cut the input, the rest the
-// weights, either in their own order or (FullyConnected, transposed != 0) one 64 x 64 tile per workgroup.
+// Both operands of one contraction in one launch: the first blocks_x workgroups cut the input, the rest the weights, either in
+// their own order or (FullyConnected, transposed != 0, N = the weights' columns) the input by piece and the weights one 64 x 64
+// tile per workgroup.
 __global__ __launch_bounds__(256) void pack2_pair_kernel(const float* __restrict__ x, unsigned short* __restrict__ xp,
                                                          long long x_count8, long long x_elems, int blocks_x,
                                                          unsigned* __restrict__ x_trailer,
@@ -266,7 +301,8 @@ __global__ __launch_bounds__(256) void pack2_pair_kernel(const float* __restrict
   fetch_arguments(x, xp, x_count8, x_elems, blocks_x, x_trailer, w, wp, w_count8, w_elems, transposed, K, N, tiles_n, w_trailer);
   __shared__ float tile[kPackTile][kPackTile + 1];
   const int b = (int)blockIdx.x;
-  if (b < blocks_x) pack2_rows(x, xp, x_count8, x_elems, b, blocks_x, x_trailer);
+  if (b < blocks_x && transposed) pack2_pieces(x, xp, (int)(x_elems / K), K / 8, b, blocks_x, x_trailer);
+  else if (b < blocks_x) pack2_rows(x, xp, x_count8, x_elems, b, blocks_x, x_trailer);
   else if (transposed) pack2_transposed(w, wp, K, N, tiles_n, b - blocks_x, tile, w_trailer);
   else pack2_rows(w, wp, w_count8, w_elems, b - blocks_x, (int)gridDim.x - blocks_x, w_trailer);
 }
@@ -328,9 +364,8 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   const v4i rsrc_w = make_rsrc(p.w_planes, 2u * wpb);
   constexpr unsigned OOB = 0x80000000u;   // planes are at most 512 MiB each: OOB + a plane neither wraps nor lands inside
   // what the two accumulator sets are scaled back by: the operands' scale exponents, from their largest magnitudes (the
-  // input's: one word, or one per row; the weights' per channel in planes ordered by it)
+  // weights' per channel in planes ordered by it)
   const PlaneOrder order(p.w_range, p.k, p.Kgemm >> 3);
-  const bool row_scales = p.x_range_n > 1;              // uniform
 
   // The bias values now, not in the epilogue: a load there would make the compiler wait for all memory operations
   // in front of every store (each store is a branch of its own, and each would wait for the store before it).
@@ -564,13 +599,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
     if (kgrp) exchange_as(std::integral_constant<int, 1>{});
     else exchange_as(std::integral_constant<int, 0>{});
     __syncthreads();
-    // of the sixteen rows this lane finishes
-    unsigned x_max[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int row = tm * PBM + wm * 64 + kgrp * 32 + lhalf * 4 + (e >> 2) * 8 + (e & 3);
-      x_max[e] = p.x_range[row_scales ? (row < p.M ? row : p.M - 1) : 0];
-    }
+    const unsigned x_max = p.x_range[0];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -578,7 +607,7 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
         const v4f got = xch[(theirs + j * 4 + e4) * 64 + lane];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const ScaleBack sb = scale_back(x_max[e4 * 4 + t], w_max[j]);
+          const ScaleBack sb = scale_back(x_max, w_max[j]);
           keep[j][e4 * 4 + t] = __builtin_ldexpf(keep[j][e4 * 4 + t] + got[t], sb.neg_se) + sb.poison;   // scaled back
         }
       }
@@ -744,9 +773,11 @@ Plan plan_p3_f32(const Problem& p) {
   if (knob_is_set(KNOB_F32_P3_BN)) pl.bn = knob(KNOB_F32_P3_BN) == 64 ? 64 : 128;
   pl.tile = pl.bn == 128 ? 0 : 1;
   pl.bk = PBK;
+  const int deep = p.b_is_kn ? fc_planes_f32_slab() / PBK : 1;   // its slabs are that many of these
+  if (p.b_is_kn) { pl.bn = 128; pl.tile = 0; pl.bk = fc_planes_f32_slab(); }
   pl.tiles_m = (p.M + PBM - 1) / PBM;
   pl.tiles_n = (p.kg + pl.bn - 1) / pl.bn;
-  pl.slabs = p.r * p.s * ((p.cg + PBK - 1) / PBK);
+  pl.slabs = p.r * p.s * ((p.cg + pl.bk - 1) / pl.bk);
   pl.split_k = 1;
   pl.slabs_per_split = pl.slabs;
   pl.pack_bytes = p3_pack_bytes(p);
@@ -755,8 +786,8 @@ Plan plan_p3_f32(const Problem& p) {
   // fills 90 % of its last round, else the one that fills it best.
   const long long t = (long long)pl.tiles_m * pl.tiles_n * p.groups;
   const long long slots = pl.bn == 128 ? 256 : 512;
-  if (t < slots && pl.slabs >= 16) {
-    const int max_split = pl.slabs / 8 < 32 ? pl.slabs / 8 : 32;
+  if (t < slots && pl.slabs * deep >= 16) {
+    const int max_split = pl.slabs * deep / 8 < 32 ? pl.slabs * deep / 8 : 32;
     int best = 1;
     double best_u = 0.0;
     for (int sk = 1; sk <= max_split; ++sk) {
@@ -799,20 +830,24 @@ hipError_t launch_p3_f32(const Problem& p_in, const Plan& plan, hipStream_t stre
   if (bx < 1) bx = 1;
   hipError_t e;
   if (p.w_packed && p.b_is_kn && p.M > 1 && p.M <= (int)(kPlaneTrailerBytes / sizeof(unsigned))) {
-    // ---- the weights' planes were made ahead of time: only the input is cut, row by row (the words fit the trailer)
+    // ---- FullyConnected, the weights' planes made ahead of time: only the input is cut, row by row (the words fit the trailer)
     p.w_planes = p.w_packed;
     p.w_range = planes_trailer(p.w_packed, w_elems);
     p.x_range_n = p.M;
-    hipLaunchKernelGGL(cut_rows_kernel, dim3((unsigned)p.M), dim3(256), 0, stream, static_cast<const float*>(p.x), xp, p.Kgemm / 8,
-                       (long long)x_elems, x_trailer);
+    hipLaunchKernelGGL(cut_rows_kernel, dim3((unsigned)((p.M + 7) / 8 * 8)), dim3(256), 0, stream, static_cast<const float*>(p.x), xp,
+                       p.M, p.Kgemm / 8, x_trailer);
   } else if (p.w_packed) {
     // ---- the same with one scale for the input
     p.w_planes = p.w_packed;
     p.w_range = planes_trailer(p.w_packed, w_elems);
     e = launch_ranges(static_cast<const float*>(p.x), (long long)x_elems, x_trailer + kRangeWords, nullptr, 0, nullptr, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pack2_rows_kernel, dim3((unsigned)bx), dim3(256), 0, stream, static_cast<const float*>(p.x), xp, xc8,
-                       (long long)x_elems, x_trailer);
+    if (p.b_is_kn)
+      hipLaunchKernelGGL(pack2_pieces_kernel, dim3((unsigned)bx), dim3(256), 0, stream, static_cast<const float*>(p.x), xp, p.M,
+                         p.Kgemm / 8, x_trailer);
+    else
+      hipLaunchKernelGGL(pack2_rows_kernel, dim3((unsigned)bx), dim3(256), 0, stream, static_cast<const float*>(p.x), xp, xc8,
+                         (long long)x_elems, x_trailer);
   } else {
     // ---- both operands: one launch for their largest magnitudes, one that cuts them into planes
     p.w_planes = wp;
@@ -838,6 +873,11 @@ hipError_t launch_p3_f32(const Problem& p_in, const Plan& plan, hipStream_t stre
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // ---- the contraction
+  if (p.b_is_kn) {
+    e = launch_fc_planes_f32(p, plan, stream, variant);
+    if (e == hipSuccess && plan.split_k > 1) e = launch_splitk_finish_f32(p, plan, stream);
+    return e;
+  }
   const bool padded = p.pad_t != 0 || p.pad_l != 0 || (p.oh - 1) * p.stride_h - p.pad_t + p.r > p.h ||
                       (p.ow - 1) * p.stride_w - p.pad_l + p.s > p.w_;
   const bool longk = plan.slabs_per_split > P3_FLUSH;
