@@ -46,6 +46,17 @@ struct FastDiv {
 #endif
 };
 
+// n / d where n d < 2^30: one multiply-high whatever d is, no branch for d = 1.
+struct QuickDiv {
+  uint32_t mul;
+#if defined(__HIPCC__)
+  __device__ __forceinline__ int div(int n) const { return (int)__umulhi(2u * (unsigned)n + 1u, mul); }
+#endif
+};
+// With mul = (2^31 + e) / d, 0 <= e < d: (2 n + 1) mul / 2^32 = (n + 1/2) / d + (2 n + 1) e / (2^32 d), and n + 1/2 lies half a unit
+// below the next multiple of d at least, which the second term reaches only where (2 n + 1) e >= 2^31.
+inline QuickDiv make_quickdiv(uint32_t d) { return {(uint32_t)((0x80000000ull + d - 1) / d)}; }
+
 inline FastDiv make_fastdiv(uint32_t d) {
   FastDiv f;
   f.d = d;
@@ -179,7 +190,7 @@ hipError_t launch_conv_small_f32(const Problem& p, hipStream_t stream, const cha
 int conv_small_f32_splits(const Problem& p);   // > 1: the split form of that kernel applies, with this many reduction slices
 // fp32 convolution on few pixels in one launch, any reduction (conv_few_f32.hip): the tile form to run it in and the
 // microseconds it is expected to take, -1: not a layer for it.
-int few_f32_form(const Problem& p, double* us);
+int few_f32_form(const Problem& p, double* us, bool taps);   // taps: its form with the input patch in LDS may be taken
 hipError_t launch_few_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // fp32 pointwise convolution of any channel counts in fours on many pixels (conv_short_f32.hip): form and expected microseconds.
 int short_f32_form(const Problem& p, double* us);

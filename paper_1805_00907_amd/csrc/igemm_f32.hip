@@ -733,7 +733,9 @@ constexpr int kShortExactChannels = 224;   // up to which conv_short_f32's sums 
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FEW, 1);            // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
-  const int form = few_f32_form(p, &us);
+  // (slices of 4608 indices and more stay where nothing but the patch in LDS is faster: with operands in the caches 512->512 on 7x7 takes
+  // 10.6 us there and 10.4 here, in a graph 10.9 and 9.9, 512->64 on 10x10 10.2 and 10.3, 9.1 and 9.8; of 400 channels 10.5 and 8.7)
+  const int form = few_f32_form(p, &us, rest.kernel != KERNEL_SMALL_SPLIT || p.Kgemm < 4608);
   if (form < 0) return rest;
   if (mode != 2) {
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_SMALL_MAX_TILES, KNOB_F32_SMALL_NO_SPLIT,

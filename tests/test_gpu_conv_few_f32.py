@@ -1,5 +1,5 @@
-"""The fp32 kernel for convolutions on few pixels with any reduction (conv_few_f32: four or eight wavefronts share the reduction
-of a tile of 16 pixels x 16 or 32 channels, one launch, no workspace) through the C ABI against the CPU oracle, element by element,
+"""The fp32 kernel for convolutions on few pixels with any reduction (conv_few_f32: four to sixteen wavefronts share the reduction
+of a tile of 16 pixels x 16 or 32 channels, one launch, no workspace; in one form the tile's input patch lies in LDS) through the C ABI against the CPU oracle, element by element,
 |gpu - oracle| <= 1e-5 + 1e-4 |oracle|: every tile form, ragged pixels, channels and reductions, one and several passes over
 the reduction, taps on padding, with and without the add link, in place too."""
 import numpy as np
@@ -27,13 +27,15 @@ SHAPES = [
     (1, 6, 6, 1032, 24, 1, 1, (1, 1), (0, 0, 0, 0)),
     (1, 3, 5, 520, 20, 3, 3, (1, 1), (1, 1, 1, 1)),        # 4680: several passes in every form
     (1, 9, 13, 64, 31, 1, 1, (2, 2), (0, 0, 0, 0)),
+    (2, 17, 5, 68, 47, 3, 3, (1, 2), (1, 1, 1, 1)),        # a chunk of four channels behind two whole ones, a wavefront with two chunks
+    (1, 2, 33, 192, 18, 1, 3, (1, 1), (0, 1, 0, 1)),       # one row of taps
     (2, 5, 7, 3, 21, 3, 3, (1, 1), (1, 1, 1, 1)),          # channels that are no multiple of four: value by value
     (1, 6, 5, 43, 18, 1, 1, (1, 1), (0, 0, 0, 0)),
     (1, 4, 6, 131, 35, 3, 3, (2, 2), (1, 1, 1, 1)),        # 1179 indices, several passes
 ]
 
 
-@pytest.mark.parametrize("tile", range(3))
+@pytest.mark.parametrize("tile", range(4))
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s[:7])))
 def test_conv_few(shape, tile, knobs):
     G = _gpu()
@@ -49,6 +51,8 @@ def test_conv_few(shape, tile, knobs):
         ref = oracle.conv2d_f32(x, wt, bias, st, pd, 1, act=act)
         got, variant = G.gpu_conv2d_f32(x, wt, bias, desc, act)
         assert variant.startswith("conv_few_f32"), variant
+        if tile == 3 and r * s > 1 and c % 4 == 0:             # the patch in LDS
+            assert variant == "conv_few_f32_taps", variant
         G.assert_close_f32(got, ref, f"{shape} act {act} [{variant}]")
         add = rng.uniform(-1, 1, size=ref.shape).astype(np.float32)
         ref = oracle.conv2d_f32_add(x, wt, bias, add, st, pd, 1, act=act)
