@@ -44,11 +44,11 @@ constexpr int SC_THREADS = 256;
 // (3x3 on 281 x 281, 72 channels in three slices, batch 9: 105 -> 74 us).
 struct SmallcSlot {
   int first, step, n_tile;                 // first tile, tiles between two of the workgroup's, its channels
-  __device__ __forceinline__ explicit SmallcSlot(int n_tiles) {
-    const unsigned j = blockIdx.x >> 3;
-    n_tile = (int)(j % (unsigned)n_tiles);
-    first = (int)(j / (unsigned)n_tiles * 8u + (blockIdx.x & 7u));
-    step = (int)(gridDim.x / (unsigned)n_tiles);
+  __device__ __forceinline__ explicit SmallcSlot(const FastDiv& n_tiles) {
+    const int j = (int)(blockIdx.x >> 3), t = n_tiles.div(j);
+    n_tile = j - t * (int)n_tiles.d;
+    first = t * 8 + (int)(blockIdx.x & 7u);
+    step = n_tiles.div((int)gridDim.x);
   }
 };
 
@@ -72,8 +72,8 @@ struct SmallC {
 };
 
 template <int R, int S, int C, int STRIDE, int NB, int CW>
-__global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Problem p, int tiles_y, int tiles_x,
-                                                                    int total_tiles, int n_tiles) {
+__global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Problem p, const FastDiv tiles_y, const FastDiv tiles_x,
+                                                                    int total_tiles, const FastDiv n_tiles) {
   fetch_arguments(p, tiles_y, tiles_x, total_tiles, n_tiles);
   using G = SmallC<R, S, C, STRIDE, NB, CW>;
   constexpr int TH = G::TH;
@@ -114,10 +114,8 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
   const int row_floats = p.w_ * C;
   using Stage = v4f[G::LOADS];
   auto load_patch = [&](Stage& stage, int tile) {                    // (past the last tile: nothing is read)
-    const int tx = tile % tiles_x;
-    const int t2 = tile / tiles_x;
-    const int ty = t2 % tiles_y;
-    const int img = t2 / tiles_y;
+    const int t2 = tiles_x.div(tile), img = tiles_y.div(t2);
+    const int tx = tile - t2 * (int)tiles_x.d, ty = t2 - img * (int)tiles_y.d;
     const int ih0 = ty * TH * STRIDE - p.pad_t;
     const int fx0 = (tx * TW * STRIDE - p.pad_l) * C - early;        // float offset inside an image row, a multiple of four
 #pragma unroll
@@ -132,7 +130,7 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
   };
   auto store_patch = [&](const Stage& stage, int buf, int tile) {
     float* dst = patch + buf * G::PATCH;
-    const int fx0 = (tile % tiles_x * TW * STRIDE - p.pad_l) * C - early;
+    const int fx0 = ((tile - tiles_x.div(tile) * (int)tiles_x.d) * TW * STRIDE - p.pad_l) * C - early;
 #pragma unroll
     for (int i = 0; i < G::LOADS; ++i) {
       const int idx = tid + i * SC_THREADS;
@@ -238,10 +236,8 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
     // below 2 GiB here, so 2^31 plus any pixel step is past the end without wrapping) and is dropped by
     // the hardware.
     {
-      const int tx = tile % tiles_x;
-      const int t2 = tile / tiles_x;
-      const int ty = t2 % tiles_y;
-      const int img = t2 / tiles_y;
+      const int t2 = tiles_x.div(tile), img = tiles_y.div(t2);
+      const int tx = tile - t2 * (int)tiles_x.d, ty = t2 - img * (int)tiles_y.d;
       const int ow0 = tx * TW + 4 * lhalf;
       const int cols_left = ch_ok ? p.ow - ow0 : 0;                  // dcol is stored iff dcol < cols_left
 #pragma unroll
@@ -316,8 +312,8 @@ struct SmallCB {
 };
 
 template <int R, int S, int C, int STRIDE, int NB, int CW>
-__global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(const Problem p, int tiles_y, int tiles_x,
-                                                                            int total_tiles, int n_tiles) {
+__global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(const Problem p, const FastDiv tiles_y, const FastDiv tiles_x,
+                                                                            int total_tiles, const FastDiv n_tiles) {
   fetch_arguments(p, tiles_y, tiles_x, total_tiles, n_tiles);
   using G = SmallCB<R, S, C, STRIDE, NB, CW>;
   constexpr int TH = G::TH;
@@ -359,10 +355,8 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   const int row_floats = p.w_ * C;
   using Stage = v4f[G::LOADS];
   auto load_patch = [&](Stage& stage, int tile) {       // (past the last tile: nothing is read)
-    const int tx = tile % tiles_x;
-    const int t2 = tile / tiles_x;
-    const int ty = t2 % tiles_y;
-    const int img = t2 / tiles_y;
+    const int t2 = tiles_x.div(tile), img = tiles_y.div(t2);
+    const int tx = tile - t2 * (int)tiles_x.d, ty = t2 - img * (int)tiles_y.d;
     const int ih0 = ty * TH * STRIDE - p.pad_t;
     const int fx0 = (tx * TW * STRIDE - p.pad_l) * C - early;
 #pragma unroll
@@ -377,7 +371,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   };
   // What belongs to the row's neighbours (behind the image's row, ahead of and behind the patch's) becomes zero.
   auto clear_neighbours = [&](Stage& stage, int tile) {
-    const int fx0 = (tile % tiles_x * TW * STRIDE - p.pad_l) * C - early;
+    const int fx0 = ((tile - tiles_x.div(tile) * (int)tiles_x.d) * TW * STRIDE - p.pad_l) * C - early;
 #pragma unroll
     for (int i = 0; i < G::LOADS; ++i) {
       const int four = (tid + i * SC_THREADS) % G::FOURS;
@@ -570,7 +564,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     if (__builtin_expect(!pieces_hold, 0)) {             // uniform
       int at = tile;
       asm volatile("" : "+s"(at));                       // nothing of this is kept in registers meanwhile
-      const int tx = at % tiles_x, t2 = at / tiles_x, ty = t2 % tiles_y, img = t2 / tiles_y;
+      const int t2 = tiles_x.div(at), img = tiles_y.div(t2), tx = at - t2 * (int)tiles_x.d, ty = t2 - img * (int)tiles_y.d;
 #pragma unroll 1
       for (int o = 0; o < 16 * NB; ++o) {
         const int oh = ty * TH + wpix * 2 * NB + (o >> 4) * 2 + (o >> 3 & 1), ow = tx * TW + 4 * lhalf + (o & 3) + 8 * (o >> 2 & 1);
@@ -595,10 +589,8 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
     } else
     // ---- epilogue of this tile: as in the kernel above
     {
-      const int tx = tile % tiles_x;
-      const int t2 = tile / tiles_x;
-      const int ty = t2 % tiles_y;
-      const int img = t2 / tiles_y;
+      const int t2 = tiles_x.div(tile), img = tiles_y.div(t2);
+      const int tx = tile - t2 * (int)tiles_x.d, ty = t2 - img * (int)tiles_y.d;
       const int ow0 = tx * TW + 4 * lhalf;
       const int cols_left = ch_ok ? p.ow - ow0 : 0;                  // dcol is stored iff dcol < cols_left
 #pragma unroll
@@ -658,7 +650,8 @@ hipError_t launch_smallc(const Problem& p, hipStream_t stream) {
   gx = gx < 8 ? 8 : gx / 8 * 8;            // whole rounds over the XCDs
   if (gx > total) gx = (total + 7) / 8 * 8;
   dim3 grid((unsigned)(gx * n_tiles), 1, 1), block(SC_THREADS, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, G::lds_bytes, stream, p, tiles_y, tiles_x, (int)total, n_tiles);
+  hipLaunchKernelGGL(kern, grid, block, G::lds_bytes, stream, p, make_fastdiv((uint32_t)tiles_y), make_fastdiv((uint32_t)tiles_x),
+                     (int)total, make_fastdiv((uint32_t)n_tiles));
   return hipGetLastError();
 }
 

@@ -85,8 +85,8 @@ __device__ __forceinline__ unsigned load4_shift(unsigned d, unsigned over) {
 }
 
 template <int R, int STRIDE, int NBC>
-__global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Problem p, int blocks_y, int blocks_x,
-                                                                      int items_div, int items_rem, int n_tiles) {
+__global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Problem p, const FastDiv blocks_y, const FastDiv blocks_x,
+                                                                      int items_div, int items_rem, const FastDiv n_tiles) {
   fetch_arguments(p, blocks_y, blocks_x, items_div, items_rem, n_tiles);
   using G = SmallI8<R, STRIDE, NBC>;
   constexpr int PH = G::PH, PW = G::PW, PITCH = G::PITCH, STEPS = G::STEPS;
@@ -100,9 +100,9 @@ __global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Pro
   const int lrow = lane & 31, lhalf = lane >> 5;
   // the workgroups that share pixels and differ in their channels are dealt to the same XCD (workgroups go to the eight in
   // turn): the parts of a cache line that two of them write meet in one L2 (88 channels in three slices, 7x7 on 224 x 224 at batch 8: 13.9 -> 11.1 us)
-  const unsigned slot = blockIdx.x >> 3;
-  const int n_tile = (int)(slot % (unsigned)n_tiles);
-  const int group = (int)(slot / (unsigned)n_tiles * 8u + (blockIdx.x & 7u));
+  const int slot = (int)(blockIdx.x >> 3), slots = n_tiles.div(slot);
+  const int n_tile = slot - slots * (int)n_tiles.d;
+  const int group = slots * 8 + (int)(blockIdx.x & 7u);
   int* patch = lds + wave * G::PATCH;                      // [PH][PITCH] dwords, one pixel each
 
   const int* __restrict__ bias = static_cast<const int*>(p.bias);
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Pro
   // ---- this wavefront's contiguous range of pixel blocks (image major, then block row, then column)
   const int wv = group * QS_WAVES + wave;
   int it, it_end_;
-  deal_range(wv, (int)(gridDim.x / (unsigned)n_tiles) * QS_WAVES, items_div, items_rem, it, it_end_);
+  deal_range(wv, n_tiles.div((int)gridDim.x) * QS_WAVES, items_div, items_rem, it, it_end_);
   const int it_end = it_end_;
 
   // ---- input patch: lane l < PW fetches column l of each of the PH patch rows, one pixel (3 codes)
@@ -140,18 +140,18 @@ __global__ __launch_bounds__(QS_THREADS, 4) void conv_smallc_i8_kernel(const Pro
   };
   auto pos_of = [&](int item) {
     Pos q;
-    q.bx = item % blocks_x;
-    const int t2 = item / blocks_x;
-    q.by = t2 % blocks_y;
-    q.img = t2 / blocks_y;
+    const int t2 = blocks_x.div(item);
+    q.bx = item - t2 * (int)blocks_x.d;
+    q.img = blocks_y.div(t2);
+    q.by = t2 - q.img * (int)blocks_y.d;
     return q;
   };
   auto advance = [&](Pos& q) {
     q.bx += 1;
-    const bool wx = q.bx == blocks_x;
+    const bool wx = q.bx == (int)blocks_x.d;
     q.bx = wx ? 0 : q.bx;
     q.by += wx ? 1 : 0;
-    const bool wy = q.by == blocks_y;
+    const bool wy = q.by == (int)blocks_y.d;
     q.by = wy ? 0 : q.by;
     q.img += wy ? 1 : 0;
   };
@@ -360,7 +360,8 @@ hipError_t launch_form(const Problem& p, hipStream_t stream) {
   const long long waves = gx * QS_WAVES;
   dim3 grid((unsigned)(gx * n_tiles), 1, 1), block(QS_THREADS, 1, 1);
   auto kern = conv_smallc_i8_kernel<R, STRIDE, NBC>;
-  hipLaunchKernelGGL(kern, grid, block, 0, stream, p, blocks_y, blocks_x, (int)(items / waves), (int)(items % waves), n_tiles);
+  hipLaunchKernelGGL(kern, grid, block, 0, stream, p, make_fastdiv((uint32_t)blocks_y), make_fastdiv((uint32_t)blocks_x), (int)(items / waves), (int)(items % waves),
+                     make_fastdiv((uint32_t)n_tiles));
   return hipGetLastError();
 }
 }  // namespace

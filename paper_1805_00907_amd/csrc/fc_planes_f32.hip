@@ -47,8 +47,8 @@ __device__ __forceinline__ void arrived(v4i& a, v4i& b, v4i& c, v4i& d) { asm vo
 
 // LONGK: more than FP_FLUSH slabs per workgroup; the sums so far are folded into totals in LDS, by the two halves in turn.
 template <bool LONGK>
-__global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p, int tiles_m, int tiles_n, int band_n, int total_work) {
-  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work);
+__global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p, const TileBands bands, int total_work) {
+  fetch_arguments(p, bands, total_work);
   __builtin_amdgcn_sched_barrier(0);                     // none is read, and waited for, ahead of it
   extern __shared__ __align__(16) unsigned char lds[];
 
@@ -56,13 +56,8 @@ __global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p
   const int per_xcd = gridDim.x >> 3;
   const int wk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (wk >= total_work) return;
-  const int plane_tiles = tiles_m * tiles_n;
-  const int split = wk / plane_tiles, wi = wk - split * plane_tiles;
-  const int band = wi / (tiles_m * band_n);
-  const int in_band = wi - band * tiles_m * band_n;
-  const int band_w = tiles_n - band * band_n < band_n ? tiles_n - band * band_n : band_n;
-  const int tm = in_band / band_w;
-  const int tn = band * band_n + (in_band - tm * band_w);
+  int group, split, tm, tn;                             // (one group)
+  bands.place(wk, &group, &split, &tm, &tn);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -329,8 +324,8 @@ hipError_t launch(const Problem& p, const Plan& plan, hipStream_t stream) {
   const long long per_xcd = (total_work + 7) / 8;
   int band_n = 1;
   while ((long long)band_n * band_n * 2 < per_xcd && band_n < plan.tiles_n) ++band_n;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(512), lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, band_n,
-                     (int)total_work);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(512), lds_bytes, stream, p,
+                     make_tile_bands(plan.tiles_m, plan.tiles_n, 1, band_n), (int)total_work);
   return hipGetLastError();
 }
 

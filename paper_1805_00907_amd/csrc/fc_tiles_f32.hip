@@ -61,7 +61,7 @@ struct RunningScale {
 };
 
 template <int MB>
-__global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Problem p, int tiles_m, int tiles_n, int total, int chunks,
+__global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Problem p, const FastDiv tiles_m, const FastDiv tiles_n, int total, int chunks,
                                                                         int chunks_per_split) {
   fetch_arguments(p, tiles_m, tiles_n, total, chunks, chunks_per_split);
   constexpr int ROWS = 32 * MB, LOADS = ROWS / 16;
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(64 * FT_WAVES, 2) void fc_tiles_f32_kernel(const Pr
   const int per_xcd = (int)(gridDim.x >> 3);
   int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
   if (tile >= total) return;
-  const int strips = tile / tiles_m, tm = tile - strips * tiles_m;
-  const int split = strips / tiles_n, tn = strips - split * tiles_n;
+  const int strips = tiles_m.div(tile), tm = tile - strips * (int)tiles_m.d;
+  const int split = tiles_n.div(strips), tn = strips - split * (int)tiles_n.d;
   const int tid = threadIdx.x, lane = tid & 63, lrow = lane & 31, lhalf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = p.Kgemm, N = p.k;
@@ -307,7 +307,7 @@ hipError_t launch_ft(const Problem& p, const Plan& plan, hipStream_t stream) {
   if (attr != hipSuccess) return attr;
   const int total = plan.tiles_m * plan.tiles_n * plan.split_k;
   hipLaunchKernelGGL(fc_tiles_f32_kernel<MB>, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * FT_WAVES), lds_bytes, stream, p,
-                     plan.tiles_m, plan.tiles_n, total, plan.slabs, plan.slabs_per_split);
+                     make_fastdiv((uint32_t)plan.tiles_m), make_fastdiv((uint32_t)plan.tiles_n), total, plan.slabs, plan.slabs_per_split);
   return hipGetLastError();
 }
 

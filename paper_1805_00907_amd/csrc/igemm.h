@@ -70,6 +70,30 @@ inline FastDiv make_fastdiv(uint32_t d) {
   return f;
 }
 
+// The tiles of a contraction in the order of the workgroups: the planes of its groups and splits one behind the other, each walked in
+// bands of some tile columns.  (A workgroup that divides by arguments for its place spends some forty instructions on each, one
+// behind the other, before its first load.)
+struct TileBands {
+  FastDiv plane, groups, band, width, last_width;      // tiles of a plane; groups; tiles of a band; columns of a band, of the last one
+  int32_t tiles_n;
+#if defined(__HIPCC__)
+  __device__ __forceinline__ void place(int work, int* group, int* split, int* tm, int* tn) const {
+    const int pl = plane.div(work), in_plane = work - pl * (int)plane.d;
+    *split = groups.div(pl);
+    *group = pl - *split * (int)groups.d;
+    const int b = band.div(in_plane), in_band = in_plane - b * (int)band.d, first = b * (int)width.d;
+    const bool whole = first + (int)width.d <= tiles_n;   // uniform
+    *tm = whole ? width.div(in_band) : last_width.div(in_band);
+    *tn = first + in_band - *tm * (int)(whole ? width.d : last_width.d);
+  }
+#endif
+};
+inline TileBands make_tile_bands(int tiles_m, int tiles_n, int groups, int columns) {
+  const int last = tiles_n % columns;
+  return {make_fastdiv((uint32_t)tiles_m * (uint32_t)tiles_n), make_fastdiv((uint32_t)groups), make_fastdiv((uint32_t)tiles_m * (uint32_t)columns),
+          make_fastdiv((uint32_t)columns), make_fastdiv((uint32_t)(last ? last : columns)), tiles_n};
+}
+
 // One link of a general element-wise chain behind the contraction (Section 5.2 of the paper: any run
 // of data-parallel operators is stacked onto the producer).  fp32 uses a/b; the quantized form uses
 // the integer bounds ia/ib on the int32 accumulator and, for an added tensor, its offset and the

@@ -97,9 +97,9 @@ struct Item {
 };
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool VEC, bool B_KN, bool LONGK, bool CHAINV = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_f32_kernel(const Problem p, int tiles_m,
-                                                                          int tiles_n, int total_work) {
-  fetch_arguments(p, tiles_m, tiles_n, total_work);
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_f32_kernel(const Problem p, const FastDiv tiles_m, const FastDiv tiles_n,
+                                                                          const FastDiv groups, int total_work) {
+  fetch_arguments(p, tiles_m, tiles_n, groups, total_work);
   constexpr int NTHREADS = 64 * WAVES_M * WAVES_N;
   constexpr int ROWS_PER_PASS = NTHREADS / KV;            // tile rows staged per pass over the threads
   static_assert(NTHREADS == 256 || NTHREADS == 512, "four or eight wavefronts per workgroup");
@@ -124,12 +124,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void igemm_f32_kernel(const
   const int total_slabs = (p.Kgemm + BK - 1) / BK;
   Item cur;
   {
-    cur.tn = w % tiles_n;
-    int t = w / tiles_n;
-    cur.tm = t % tiles_m;
-    t /= tiles_m;
-    cur.g = t % p.groups;
-    cur.split = t / p.groups;
+    const int t = tiles_n.div(w), plane = tiles_m.div(t);
+    cur.tn = w - t * (int)tiles_n.d;
+    cur.tm = t - plane * (int)tiles_m.d;
+    cur.split = groups.div(plane);
+    cur.g = plane - cur.split * (int)groups.d;
     cur.slab_begin = cur.split * p.slabs_per_split;
     cur.slab_end = cur.slab_begin + p.slabs_per_split < total_slabs ? cur.slab_begin + p.slabs_per_split : total_slabs;
   }
@@ -664,7 +663,8 @@ hipError_t launch_variant(const Problem& p, const Plan& plan, hipStream_t stream
   const long long total_work = (long long)plan.tiles_m * plan.tiles_n * p.groups * plan.split_k;
   const long long grid_x = ((total_work + 7) / 8) * 8;
   dim3 grid((unsigned)grid_x, 1, 1), block(nthreads, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, (int)total_work);
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, make_fastdiv((uint32_t)plan.tiles_m), make_fastdiv((uint32_t)plan.tiles_n),
+                     make_fastdiv((uint32_t)p.groups), (int)total_work);
   return hipGetLastError();
 }
 

@@ -319,9 +319,8 @@ template <int WN, bool LONGK>
 constexpr int kFragmentsAhead = WN == 2 && !LONGK ? 1 : 0;
 
 template <int WN, bool PADDED, bool LONGK, int RING>
-__global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem p, int tiles_m, int tiles_n,
-                                                                   int band_n, int total_work) {
-  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work);
+__global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem p, const TileBands bands, int total_work) {
+  fetch_arguments(p, bands, total_work);
   constexpr int BN = 64 * WN;
   constexpr int WAVES = 4 * WN;
   constexpr int A_GROUPS = (PBM / 16) / WAVES;          // 16-row groups of the pixel tile one wavefront loads per plane
@@ -342,15 +341,8 @@ __global__ __launch_bounds__(256 * WN, 2) void igemm_f32_p3_kernel(const Problem
   const int per_xcd = gridDim.x >> 3;
   const int wk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (wk >= total_work) return;
-  const int plane = tiles_m * tiles_n;
-  const int pl_i = wk / plane, wi = wk - pl_i * plane;
-  const int g = pl_i % p.groups;
-  const int split = pl_i / p.groups;
-  const int band = wi / (tiles_m * band_n);
-  const int in_band = wi - band * tiles_m * band_n;
-  const int band_w = tiles_n - band * band_n < band_n ? tiles_n - band * band_n : band_n;
-  const int tm = in_band / band_w;
-  const int tn = band * band_n + (in_band - tm * band_w);
+  int g, split, tm, tn;
+  bands.place(wk, &g, &split, &tm, &tn);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -666,7 +658,7 @@ hipError_t launch_p3_variant(const Problem& p, const Plan& plan, hipStream_t str
   int band_n = 1;
   while ((long long)band_n * band_n * 2 < per_xcd && band_n < plan.tiles_n) ++band_n;
   dim3 grid((unsigned)grid_x, 1, 1), block(256 * WN, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, band_n, (int)total_work);
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, make_tile_bands(plan.tiles_m, plan.tiles_n, p.groups, band_n), (int)total_work);
   return hipGetLastError();
 }
 

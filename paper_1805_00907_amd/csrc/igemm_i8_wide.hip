@@ -67,10 +67,9 @@ template <int BN, bool B_KN, bool PADDED, bool XSUM, int NBUF, bool RAGGED = fal
 // (second launch bound = wavefronts per SIMD: two workgroups of eight per CU need four, i.e. at most 128
 // registers -- with a bound of two the padded 128-channel form took 130 and ran one workgroup per CU;
 // the forms that also take input code sums do not fit 128 without spilling and stay at one per CU)
-__global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_i8_wide_kernel(const Problem p, int tiles_m,
-                                                                                   int tiles_n, int band_n,
+__global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_i8_wide_kernel(const Problem p, const TileBands bands,
                                                                                    int total_work, const FastDiv div_tap) {
-  fetch_arguments(p, tiles_m, tiles_n, band_n, total_work, div_tap);
+  fetch_arguments(p, bands, total_work, div_tap);
   static_assert(BN == 64 || BN == 128, "channel tile");
   static_assert(!B_KN || BN == 128, "the [K][N] weight path stages 128 columns");
   constexpr int TN = BN / 64;                           // MFMA tiles along the channels per wavefront
@@ -93,15 +92,8 @@ __global__ __launch_bounds__(WTHREADS, (NBUF <= 2 && !XSUM) ? 4 : 2) void igemm_
   const int per_xcd = gridDim.x >> 3;
   const int wk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (wk >= total_work) return;
-  const int plane = tiles_m * tiles_n;
-  const int pl = wk / plane, wi = wk - pl * plane;
-  const int g = pl % p.groups;
-  const int split = pl / p.groups;
-  const int band = wi / (tiles_m * band_n);
-  const int in_band = wi - band * tiles_m * band_n;
-  const int band_w = tiles_n - band * band_n < band_n ? tiles_n - band * band_n : band_n;
-  const int tm = in_band / band_w;
-  const int tn = band * band_n + (in_band - tm * band_w);
+  int g, split, tm, tn;
+  bands.place(wk, &g, &split, &tm, &tn);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -509,7 +501,7 @@ hipError_t launch_wide_variant(const Problem& p, const Plan& plan, hipStream_t s
   int band_n = 1;
   while ((long long)band_n * band_n * 2 < per_xcd && band_n < plan.tiles_n) ++band_n;
   dim3 grid((unsigned)grid_x, 1, 1), block(WTHREADS, 1, 1);
-  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, plan.tiles_m, plan.tiles_n, band_n, (int)total_work,
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, p, make_tile_bands(plan.tiles_m, plan.tiles_n, p.groups, band_n), (int)total_work,
                      make_fastdiv((uint32_t)((p.cg + 15) / 16 * 16)));
   return hipGetLastError();
 }
