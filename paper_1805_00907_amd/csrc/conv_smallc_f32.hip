@@ -305,8 +305,9 @@ struct SmallCB {
   static_assert((WPITCH / 8) % 2 == 1, "fragment reads spread over the banks");
   static constexpr int W_LOADS = (CW * 32 * WGROUPS + SC_THREADS - 1) / SC_THREADS;
   static constexpr int patch_bytes = (LEAD + 2 * PATCH) * 2, filter_bytes = 2 * CW * 32 * WPITCH * 2;
-  static constexpr int stage_bytes = (patch_bytes > filter_bytes ? patch_bytes + 15 : filter_bytes) / 16 * 16;
-  static constexpr int lds_bytes = stage_bytes + 32;     // + the wavefronts' largest magnitudes, room for eight
+  static constexpr int stage_bytes = (filter_bytes + patch_bytes + 15) / 16 * 16;
+  static constexpr int lds_bytes = stage_bytes + 64;     // + the wavefronts' largest magnitudes, patches and filters, room for eight each
+  static_assert(filter_bytes % 16 == 0 && 2 * lds_bytes <= 160 * 1024, "two workgroups to a CU");
   // patch offset (elements) of group g relative to a pixel's patch origin
   static constexpr int off(int g) { return (g / RUN8) * PITCH + (g % RUN8) * 8; }
 };
@@ -319,10 +320,11 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
   constexpr int TH = G::TH;
   static_assert((STRIDE * C) % 2 == 0 && G::PITCH % 2 == 0, "a pixel's run starts on a 4-byte boundary");
   static_assert((TW * STRIDE * C) % 4 == 0, "all tiles' patches start at the same place of an aligned group of four");
-  extern __shared__ __align__(16) unsigned short smallc_lds[];   // first the filters' pieces, then [2][2][PH + 2][PITCH]
-  unsigned short* patchb = smallc_lds + G::LEAD;
+  extern __shared__ __align__(16) unsigned short smallc_lds[];   // the filters' pieces, [2][2][PH + 2][PITCH]
+  unsigned short* const patches = smallc_lds + G::filter_bytes / 2;
+  unsigned short* patchb = patches + G::LEAD;
   unsigned* maxw = reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(smallc_lds) + G::stage_bytes);
-  static_assert(SC_THREADS == 256, "four wavefronts leave their largest magnitudes in words 0-3; words 4-7 stay zero");
+  static_assert(SC_THREADS == 256, "four wavefronts leave their largest magnitudes in words 0-3; words 4-7 stay zero (8-11, 12-15: the filters')");
   constexpr unsigned OOB = 0x80000000u;                  // beyond every tensor the kernel takes: loads give zeros, stores are dropped
 
   const int tid = threadIdx.x;
@@ -427,23 +429,24 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
 
   int tile = slot.first;
   if (tile >= total_tiles) return;
-  if (tid >= 4 && tid < 8) maxw[tid] = 0u;  // never written again; visible after the first barrier
+  if (tid < 16 && (tid & 4)) maxw[tid] = 0u;  // never written again; visible after the first barrier
   Stage here, ahead;                       // two patches on their way to LDS
   load_patch(here, tile);                  // in flight while the filter is fetched
 
   // ---- filter fragments: lane (channel, half) keeps, for every step t and piece, the eight values of group
   // 2t + half.  The workgroup's threads fetch the groups, each one's largest magnitude gives the scale, each cuts its own
-  // into LDS (in the space of the patch buffers) and the lanes pick from there; rows past the last output channel lie past
+  // into LDS and the lanes pick from there; rows past the last output channel lie past
   // the end of the tensor and the range-checked loads return zeros.  (Every lane cutting its own fragments took 176 LDS
   // reads of four bytes and cut everything twice: 5 us of batch 8's 20.)
+  // The first patch goes the same way beside them, with a place in LDS of its own: the two wait for memory and meet at two
+  // barriers together (one behind the other, in the same space, five).
   v8h wfrag[G::STEPS][2];
-  int se_w;
-  bool w_finite;
+  int se_w, se_x;                                        // scale exponents, se_x: of the patch in `buf`
+  bool w_finite, finite;                                 // whether patch and filters hold neither infinities nor NaNs
   {
     const __amdgpu_buffer_rsrc_t rsrc_w =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.w), 0, (int)p.w_bytes, 0x00020000);
-    float v[G::W_LOADS][8];
-    unsigned wm = 0;
+    v4f raw[G::W_LOADS][2];
 #pragma unroll
     for (int i = 0; i < G::W_LOADS; ++i) {
       const int idx = tid + i * SC_THREADS;
@@ -451,21 +454,41 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
       const int r = g / G::RUN8, q0 = (g % G::RUN8) * 8;
       const bool ok = chn < CW * 32 && r < R;
       const unsigned at = ok ? 4u * (unsigned)((n_tile * (32 * CW) + chn) * G::K + r * G::RUN + q0) : OOB;
-      const v4f a = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, at, 0, 0));
-      const v4f b = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, ok ? at + 16u : OOB, 0, 0));
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[i][e] = q0 + e < G::RUN ? (e < 4 ? a[e] : b[e - 4]) : 0.f;
+      raw[i][0] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, at, 0, 0));
+      raw[i][1] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, ok ? at + 16u : OOB, 0, 0));
     }
+    load_patch(ahead, tile + slot.step);
+    // zero both buffers once: the spare rows and the row tails are never overwritten by patch stores and must
+    // hold finite values (they meet zero filter pieces)
+    static_assert(G::patch_bytes % 16 == 0, "zeroed sixteen bytes at a time");
 #pragma unroll
-    for (int i = 0; i < G::W_LOADS; ++i)
+    for (int i = 0; i < (G::patch_bytes / 16 + SC_THREADS - 1) / SC_THREADS; ++i)
+      if ((i + 1) * SC_THREADS <= G::patch_bytes / 16 || tid + i * SC_THREADS < G::patch_bytes / 16)
+        reinterpret_cast<v4u*>(patches)[tid + i * SC_THREADS] = v4u{0u, 0u, 0u, 0u};
+    clear_neighbours(here, tile);
+    const unsigned share = stage_max(here);
+    float v[G::W_LOADS][8];
+    unsigned wm = 0;
+#pragma unroll
+    for (int i = 0; i < G::W_LOADS; ++i) {
+      const int q0 = (tid + i * SC_THREADS) % G::WGROUPS % G::RUN8 * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[i][e] = q0 + e < G::RUN ? raw[i][e / 4][e % 4] : 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) wm = bits_of(v[i][e]) > wm ? bits_of(v[i][e]) : wm;
+    }
     wm = wave_max_u32(wm);
-    if (lane == 0) maxw[wave] = wm;
+    if (lane == 0) {
+      maxw[wave] = share;
+      maxw[8 + wave] = wm;
+    }
     __syncthreads();
-    const unsigned w_max_bits = max_of_eight(maxw);
+    const unsigned w_max_bits = max_of_eight(maxw + 8), x_max_bits = max_of_eight(maxw);
     se_w = scale_exponent(w_max_bits);
     w_finite = w_max_bits < 0x7f800000u;
+    se_x = scale_exponent(x_max_bits);
+    finite = w_finite && x_max_bits < 0x7f800000u;
+    store_patch(here, 0, se_x);
 #pragma unroll
     for (int i = 0; i < G::W_LOADS; ++i) {
       const int idx = tid + i * SC_THREADS;
@@ -483,27 +506,7 @@ __global__ __launch_bounds__(SC_THREADS, 2) void conv_smallc_f32_f16_kernel(cons
 #pragma unroll
       for (int pc = 0; pc < 2; ++pc)
         wfrag[t][pc] = *reinterpret_cast<const v8h*>(smallc_lds + (pc * CW * 32 + wch * 32 + lrow) * G::WPITCH + (2 * t + lhalf) * 8);
-    __syncthreads();
   }
-  // zero both buffers once: the spare rows and the row tails are never overwritten by patch stores and must
-  // hold finite values (they meet zero filter pieces)
-  for (int i = tid; i < (G::LEAD + 2 * G::PATCH) / 2; i += SC_THREADS) reinterpret_cast<unsigned*>(smallc_lds)[i] = 0u;
-  load_patch(ahead, tile + slot.step);
-  clear_neighbours(here, tile);
-  {
-    const unsigned share = stage_max(here);
-    if (lane == 0) maxw[wave] = share;                   // (the filter's words were read before the last barrier)
-  }
-  __syncthreads();
-  int se_x;                                              // scale exponent of the patch in `buf`
-  bool finite;                                           // whether it and the filter hold neither infinities nor NaNs
-  {
-    const unsigned m = max_of_eight(maxw);
-    finite = w_finite && m < 0x7f800000u;
-    se_x = scale_exponent(m);
-  }
-  store_patch(here, 0, se_x);
-  __syncthreads();
   int buf = 0;
   // One tile from LDS: `in` holds the next one's patch, asked for a tile ago (a load takes two or three times as long as the
   // MFMAs of a tile), `out` takes the one after that.
