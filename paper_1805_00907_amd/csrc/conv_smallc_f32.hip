@@ -280,7 +280,7 @@ __global__ __launch_bounds__(SC_THREADS) void conv_smallc_f32_kernel(const Probl
 // 64 per 32 x 32 block.
 // What bounds it (224 x 224, 64 channels): with many tiles the MFMAs and the output, 24 us each at batch 32 at the
 // rates of a large product and a large copy and only partly over each other with two wavefronts to a SIMD (47 us);
-// at batch 8 (18.0 us) the start, 8 us with the first tile, and 3.06 tiles to a workgroup, which take four rounds.
+// at batch 8 (14.7 us) the start, 9500 cycles to the first tile, and 3.06 tiles to a workgroup, which take four rounds.
 // ---------------------------------------------------------------------------------------------------
 template <int R, int S, int C, int STRIDE, int NB, int CW>
 struct SmallCB {
@@ -687,7 +687,7 @@ hipError_t launch_smallc_f32(const Problem& p, hipStream_t stream, const char** 
     return two ? launch_smallc<3, 2, 2, 2, false>(p, stream) : launch_smallc<3, 2, 1, 2, false>(p, stream);
   }
   // The fp16-piece form pays a longer prologue (the filters are cut per workgroup): 224 x 224 at batch 32 90 -> 47 us, batch 8
-  // 27 -> 18.0, batch 3 13.0 -> 10.8, batch 2 (392 tiles) 10.3 -> 9.6, but batch 1 (196 tiles, launch-bound) 7.7 -> 8.3, which
+  // 27 -> 14.7, batch 3 13.0 -> 10.8, batch 2 (392 tiles) 10.3 -> 9.6, but batch 1 (196 tiles, launch-bound) 7.7 -> 8.3, which
   // therefore keeps the fp32 form.  Errors against 64 bits are 0.36 to 0.56 of the fp32 form's.  The knob forces one.
   const long long tiles4 = (long long)p.n * ((p.oh + 3) / 4) * ((p.ow + TW - 1) / TW);
   const bool bf16 = knob_or(KNOB_F32_SMALLC_BF16, tiles4 >= 300 ? 1 : 0) != 0;

@@ -14,8 +14,8 @@
 // What bounds it: power.  A slab is 1536 cycles of matrix work on every SIMD and takes 1830, next to 1024 cycles of LDS reads, 256 of
 // LDS writes and 1024 of the vector memory path; in calls back to back the clock falls to 1.63 GHz (2.35 alone).  256 x 4096 x 4096
 // on 256 workgroups of 16 slabs: 4800 cycles until the first slab is there, 29300 for the slabs, 7200 for sums and stores, 28.6 us
-// where both operands went through LDS, 64-byte pieces of rows at a time, and results left a dword per row: 33.4; the whole call 45.2 ->
-// 40.9 us, 1024 rows 110 -> 104.  Sums as far from 64-bit ones as there (1.26e-7 of the result's norm).
+// where both operands went through LDS, 64-byte pieces of rows at a time, and results left a dword per row: 33.4; the whole call 44.2 ->
+// 38.7 us, 1024 rows 110 -> 104.  Sums as far from 64-bit ones as there (1.26e-7 of the result's norm).
 #include <hip/hip_runtime.h>
 
 #include "arguments.h"
