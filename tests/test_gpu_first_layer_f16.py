@@ -45,6 +45,12 @@ def test_first_layer_f16_is_planned(n, taken):
     assert _check(_gpu(), n, 80, 160, 64, (3, 3, 3, 3)).endswith("f16x3") == taken
 
 
+@pytest.mark.parametrize("n,k,taken", [(2, 128, False), (3, 128, True), (2, 192, True), (2, 160, False), (3, 160, True), (3, 96, False), (4, 96, True), (1, 300, False), (1, 330, True)])
+def test_first_layer_f16_is_planned_by_slices(n, k, taken):
+    """The same map: taken where some workgroup has a second tile, of a slice of 64 channels (one workgroup to a CU) or of 32 (two)."""
+    assert _check(_gpu(), n, 80, 160, k, (3, 3, 3, 3)).endswith("f16x3") == taken
+
+
 @pytest.mark.parametrize("place", ["input", "filter"])
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
 def test_first_layer_f16_non_finite(place, value, knobs):
