@@ -690,7 +690,7 @@ hipError_t launch_smallc_f32(const Problem& p, hipStream_t stream, const char** 
   // wants a second tile for some of them: 160 channels at batch 1 11.53 -> 8.82 us, 128 9.58 -> 7.90, 96 8.81 -> 7.28, 64 at 288 tiles
   // 9.31 -> 7.54.  With a tile each it takes 0.96 of the time with 64 channels to a workgroup and 1.01 to 1.02 with 32, two of which a CU
   // holds.  From 300 tiles on it is taken with few channels too: 1.01 of the time there, but errors against 64 bits are 0.36 to 0.56 of the fp32
-  // form's.  The knob forces one.
+  // form's (0.55 and 0.56 for 64 to 192 channels on maps below 300 tiles).  The knob forces one.
   const long long tiles4 = (long long)p.n * ((p.oh + 3) / 4) * ((p.ow + TW - 1) / TW);
   const long long cus = num_compute_units() > 0 ? num_compute_units() : 256;
   const bool second = half ? tiles4 * ((p.k + 31) / 32) > 2 * cus : tiles4 * ((p.k + 63) / 64) > cus;
