@@ -769,24 +769,34 @@ Plan few_or(const Problem& p, const Plan& rest) {
   pl.was_small = mode != 2 && rest.kernel == KERNEL_SMALL;
   return pl;
 }
+// Pointwise layers of up to 32 output channels over 64 or 128: conv_pw_f32 multiplies groups of 64.  Over 258 layers of 32768 to
+// 131072 pixels conv_short_f32 takes 0.783 of its time, 0.66 to 0.94 (64->32 at 33124 pixels 8.22 -> 5.43 us, 128->32 at 37636 10.86 -> 7.75, 64->16 at 524288 42.7 -> 37.9, 64->32 + add at 1048576 119 -> 113);
+// sums at 0.48 to 0.71 of its distance from 64-bit ones.  Not with a second round of the wavefronts less than half full (1.00 to 1.06 with operands
+// from memory), nor channels out of fours with an addend (64->31 + add at 262144 29.0 -> 30.5).
+bool narrow_layer(const Problem& p) {
+  const long long blocks = ((long long)p.M + 31) / 32, wavefronts = 8LL * (num_compute_units() > 0 ? num_compute_units() : 256);
+  return p.k <= 32 && p.c <= 128 && p.stride_h == 1 && p.stride_w == 1 && (p.k % 4 == 0 || !p.addend) &&
+         (blocks <= wavefronts || 2 * blocks >= 3 * wavefronts) && !knob_is_set(KNOB_F32_PW_MIN_ITEMS) && !knob_is_set(KNOB_F32_PW_BF16);
+}
 // Pointwise convolutions on many pixels: conv_short_f32 in place of the tiled kernel, the patch kernel or conv_few_f32 where its
 // estimate is lower than theirs by two in a hundred (over the same layers 0.73 and 0.80 of the tiled kernel's time, 383 move, 0.78 and
 // 0.85 of the patch kernel's, 125 move; the worst 1.05).
 // Its sums are closer to 64-bit ones than the first two's at any depth, and than conv_few_f32's up to 224 channels (0.91 to 1.00 of
 // their distance, 1.00 to 1.04 at 232 to 320): what that has beyond stays.  The kernel for 64, 128 and 256 channels on many pixels
-// stays too.
+// stays too but where narrow_layer moves it.
 Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_SHORT, 1);          // 0: off, 2: any layer that fits (tests)
   if (mode != 2) {
     const bool patch = rest.kernel == KERNEL_PATCH && knob_or(KNOB_F32_PATCH, 1) != 2;
-    if (!(rest.kernel == KERNEL_TILED || patch || (rest.kernel == KERNEL_FEW && !rest.was_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= kShortExactChannels))) return rest;
+    const bool narrow = rest.kernel == KERNEL_PW && narrow_layer(p);
+    if (!(rest.kernel == KERNEL_TILED || patch || narrow || (rest.kernel == KERNEL_FEW && !rest.was_small && knob_or(KNOB_F32_FEW, 1) != 2 && p.c <= kShortExactChannels))) return rest;
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_PATCH_TILE, KNOB_F32_FEW_TILE})
       if (knob_is_set(k)) return rest;                   // another kernel is asked for
   }
   double us = 0.0;
   const int form = short_f32_form(p, &us);
   if (form < 0) return rest;
-  if (mode != 2) {
+  if (mode != 2 && rest.kernel != KERNEL_PW) {
     // (the layers of a sequence share the launch that cuts their filters: 2 of its 4.3 us and more may fall to the others)
     const double other = rest.kernel == KERNEL_TILED ? tiled_us(p, rest)
                          : rest.kernel == KERNEL_PATCH ? patch_us(rest) - (p.packed_is_cut ? 0.0 : 2.0) : (double)rest.us;

@@ -54,6 +54,26 @@ def test_conv_short_f32(shape, tiles, knobs):
             G.assert_close_f32(got, ref, f"{shape} add act {act} [{variant}]")
 
 
+@pytest.mark.parametrize("c,k,n,h,add,taken", [(64, 32, 2, 128, False, True), (128, 31, 1, 182, False, True), (64, 3, 1, 256, True, False), (128, 20, 1, 256, True, True),
+                                               (64, 33, 2, 128, False, False), (64, 32, 1, 257, False, False), (128, 8, 2, 222, False, True)])
+def test_narrow_layers_are_planned(c, k, n, h, add, taken):
+    """Up to 32 channels over 64 or 128: at most 2048 blocks of 32 pixels or 3072 and more, fours with an addend."""
+    G = _gpu()
+    rng = np.random.default_rng(42700 + c + k + h)
+    x = rng.uniform(-1, 1, size=(n, h, h, c)).astype(np.float32)
+    wt = (rng.uniform(-1, 1, size=(k, 1, 1, c)) / np.sqrt(c)).astype(np.float32)
+    desc = G.make_desc(x.shape, wt.shape, (1, 1), (0, 0, 0, 0), 1)
+    if add:
+        extra = rng.uniform(-1, 1, size=(n, h, h, k)).astype(np.float32)
+        ref = oracle.conv2d_f32_add(x, wt, None, extra, (1, 1), (0, 0, 0, 0), 1, act=wl.ACT_RELU)
+        got, variant = G.gpu_conv2d_f32_chain(x, wt, None, extra, desc, wl.ACT_RELU)
+    else:
+        ref = oracle.conv2d_f32(x, wt, None, (1, 1), (0, 0, 0, 0), 1, act=wl.ACT_RELU)
+        got, variant = G.gpu_conv2d_f32(x, wt, None, desc, wl.ACT_RELU)
+    assert variant.startswith("conv_short_f32" if taken else "conv_pw_f32"), variant
+    G.assert_close_f32(got, ref, f"{c} {k} [{variant}]")
+
+
 @pytest.mark.parametrize("c,k,h,add", [(24, 184, 60, False), (56, 224, 60, True), (224, 56, 75, False), (16, 40, 110, True)])
 def test_conv_short_f32_is_planned(c, k, h, add):
     """Several blocks to a wavefront, with and without a workspace."""
