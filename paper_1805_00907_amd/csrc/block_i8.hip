@@ -536,20 +536,23 @@ bool plan_tile(Block& b, int images, int slots, double below, int* grid, int* ld
   return true;
 }
 
+template <int CB, bool ADD>
+hipError_t launch_kernel(const Block& b, int grid, int lds, hipStream_t stream) {
+  auto kern = block_i8_kernel<CB, ADD>;
+  // once for each kernel; initialisation of a function-local static is thread-safe
+  static const hipError_t attr_status =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<CB>::LDS);
+  if (attr_status != hipSuccess) return attr_status;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BL_THREADS), lds, stream, b);
+  return hipGetLastError();
+}
+
 template <int CB>
 bool launch_shape(Block& b, int images, double below, hipStream_t stream, hipError_t* status) {
   const int slots = Shape<CB>::PER_CU * (num_compute_units() > 0 ? num_compute_units() : 256);
   int grid = 0, lds = 0;
   if (!plan_tile<CB>(b, images, slots, below, &grid, &lds)) return false;
-  auto launch = [&](auto kern) {
-    // once per instantiation; initialisation of a function-local static is thread-safe
-    static const hipError_t attr_status =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<CB>::LDS);
-    if (attr_status != hipSuccess) return attr_status;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BL_THREADS), lds, stream, b);
-    return hipGetLastError();
-  };
-  *status = b.addend ? launch(&block_i8_kernel<CB, true>) : launch(&block_i8_kernel<CB, false>);
+  *status = b.addend ? launch_kernel<CB, true>(b, grid, lds, stream) : launch_kernel<CB, false>(b, grid, lds, stream);
   return true;
 }
 

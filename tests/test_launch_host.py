@@ -1,0 +1,24 @@
+"""What calls hand to the runtime (no GPU): kernels, their dynamic LDS and the limit that was set for it."""
+import pytest
+
+from launch_probe import LaunchProbe
+
+
+def _block(mid, c=None):
+    return [(mid, 1), (mid, 3), (c or 4 * mid, 1)]
+
+
+@pytest.mark.parametrize("first", [True, False], ids=["addend_first", "addend_second"])
+def test_every_block_kernel_has_its_own_lds_limit(first):
+    """More dynamic LDS than 64 KB is given to a kernel only once its limit was raised: the kernel with and the one without an addend
+    have the same type, and each needs it, whichever runs first."""
+    with LaunchProbe() as probe:
+        probe.knob("I8_BLOCK", 2)
+        kernels = set()
+        for add in (first, not first):
+            for mid in (32, 64, 96):
+                launches = probe.sequence((1, 14, 14, 4 * mid), _block(mid), add=[2] if add else [])
+                assert len(launches) == 1 and "block_i8_kernel" in launches[0].kernel, launches
+                kernels.add(launches[0].kernel)
+                assert launches[0].limit >= launches[0].lds, launches
+        assert len(kernels) == 6
