@@ -32,8 +32,7 @@
  *    layers, depthwise ones, and calls without a workspace but for those that hold the filter on the chip as
  *    pieces and need none: pointwise layers on many pixels over 64, 128 or 256 channels or any multiple of four up to
  *    320 (three bf16 pieces per value, all 24 bits, six products) and 7x7 stride 2 first layers of 300 tiles of 4 x 16
- *    pixels or more, or of more tiles times groups of 64 channels than there are CUs (32 and twice as many where the last group
- *    has 32 or fewer) (two fp16 pieces, scaled by tile; a tile that no scale fits in fp32 arithmetic).
+ *    pixels or more (two fp16 pieces, scaled by tile; a tile that no scale fits in fp32 arithmetic).
  *      On the fp16 matrix cores, with the workspace the query names (3x3 layers on large maps also with the
  *    filter's planes given and none): 1x1 and 3x3 convolutions of ordinary size and more, large convolutions of
  *    other shapes, FullyConnected layers from 65 rows.  Operands are scaled by a power of two that brings the

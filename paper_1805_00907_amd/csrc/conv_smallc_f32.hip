@@ -686,15 +686,11 @@ hipError_t launch_smallc_f32(const Problem& p, hipStream_t stream, const char** 
     if (half) return two ? launch_smallc<3, 2, 2, 1, false>(p, stream) : launch_smallc<3, 2, 1, 1, false>(p, stream);
     return two ? launch_smallc<3, 2, 2, 2, false>(p, stream) : launch_smallc<3, 2, 1, 2, false>(p, stream);
   }
-  // The fp16-piece form cuts the filters of each workgroup first (224 x 224, 64 channels: batch 32 90 -> 47 us, batch 8 27 -> 14.7), so it
-  // wants a second tile for some of them: 160 channels at batch 1 11.53 -> 8.82 us, 128 9.58 -> 7.90, 96 8.81 -> 7.28, 64 at 288 tiles
-  // 9.31 -> 7.54.  With a tile each it takes 0.96 of the time with 64 channels to a workgroup and 1.01 to 1.02 with 32, two of which a CU
-  // holds.  From 300 tiles on it is taken with few channels too: 1.01 of the time there, but errors against 64 bits are 0.36 to 0.56 of the fp32
-  // form's (0.55 and 0.56 for 64 to 192 channels on maps below 300 tiles).  The knob forces one.
+  // The fp16-piece form pays a longer prologue (the filters are cut per workgroup): 224 x 224 at batch 32 90 -> 47 us, batch 8
+  // 27 -> 14.7, batch 3 13.0 -> 10.8, batch 2 (392 tiles) 10.3 -> 9.6, but batch 1 (196 tiles, launch-bound) 7.7 -> 8.3, which
+  // therefore keeps the fp32 form.  Errors against 64 bits are 0.36 to 0.56 of the fp32 form's.  The knob forces one.
   const long long tiles4 = (long long)p.n * ((p.oh + 3) / 4) * ((p.ow + TW - 1) / TW);
-  const long long cus = num_compute_units() > 0 ? num_compute_units() : 256;
-  const bool second = half ? tiles4 * ((p.k + 31) / 32) > 2 * cus : tiles4 * ((p.k + 63) / 64) > cus;
-  const bool bf16 = knob_or(KNOB_F32_SMALLC_BF16, second || tiles4 >= 300 ? 1 : 0) != 0;
+  const bool bf16 = knob_or(KNOB_F32_SMALLC_BF16, tiles4 >= 300 ? 1 : 0) != 0;
   *variant = bf16 ? "conv_smallc_f32_7x7s2c3_f16x3" : "conv_smallc_f32_7x7s2c3";
   // (the fp16-piece form keeps 88 registers of filter fragments per lane and two accumulator sets: with two pixel
   // blocks per wavefront it would spill, so it always takes the shorter tile)

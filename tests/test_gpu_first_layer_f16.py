@@ -45,10 +45,21 @@ def test_first_layer_f16_is_planned(n, taken):
     assert _check(_gpu(), n, 80, 160, 64, (3, 3, 3, 3)).endswith("f16x3") == taken
 
 
-@pytest.mark.parametrize("n,k,taken", [(2, 128, False), (3, 128, True), (2, 192, True), (2, 160, False), (3, 160, True), (3, 96, False), (4, 96, True), (1, 300, False), (1, 330, True)])
-def test_first_layer_f16_is_planned_by_slices(n, k, taken):
-    """The same map: taken where some workgroup has a second tile, of a slice of 64 channels (one workgroup to a CU) or of 32 (two)."""
-    assert _check(_gpu(), n, 80, 160, k, (3, 3, 3, 3)).endswith("f16x3") == taken
+@pytest.mark.parametrize("n,k", [(1, 64), (5, 64), (3, 128), (2, 192), (4, 96), (1, 330)])
+def test_first_layer_below_300_tiles_keeps_every_bit(n, k):
+    """The same map, filters of one tap: below 300 tiles the product is one of fp32 operands and gives the input back bit for bit, whatever
+    the number of channels (two fp16 pieces hold 22 of the 24 bits)."""
+    G = _gpu()
+    rng = np.random.default_rng(41300 + n + k)
+    x = rng.uniform(-1, 1, size=(n, 80, 160, 3)).astype(np.float32)
+    taps = rng.integers(0, [7, 7, 3], size=(k, 3))
+    wt = np.zeros((k, 7, 7, 3), np.float32)
+    wt[np.arange(k), taps[:, 0], taps[:, 1], taps[:, 2]] = 1
+    got, variant = G.gpu_conv2d_f32(x, wt, None, G.make_desc(x.shape, wt.shape, (2, 2), (3, 3, 3, 3), 1), wl.ACT_NONE)
+    assert variant.startswith("conv_smallc_f32"), variant
+    padded = np.pad(x, ((0, 0), (3, 3), (3, 3), (0, 0)))
+    for i, (r, s, c) in enumerate(taps):
+        assert np.array_equal(got[..., i], padded[:, r:r + 80:2, s:s + 160:2, c]), (i, variant)
 
 
 @pytest.mark.parametrize("place", ["input", "filter"])
