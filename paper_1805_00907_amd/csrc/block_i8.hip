@@ -560,6 +560,10 @@ bool launch_shape(Block& b, int images, double below, hipStream_t stream, hipErr
 
 bool launch_block_i8(const Problem& a, const Problem& b, const Problem& c, hipStream_t stream, hipError_t* status, const char** variant) {
   const int mode = knob_or(KNOB_I8_BLOCK, 1);           // 0: off, 2: any block that fits (tests)
+  if (mode != 2)
+    for (const Knob k : {KNOB_I8_TILE, KNOB_I8_SPLIT, KNOB_I8_SMALL_MAX_TILES, KNOB_I8_WIDE_SPLIT, KNOB_I8_WIDE_NBUF, KNOB_I8_PW_MIN_ITEMS,
+                         KNOB_I8_K3_MIN_BLOCKS, KNOB_I8_K3_WAVES, KNOB_I8_K3_GATHER, KNOB_I8_FEW, KNOB_I8_FEW_TILE, KNOB_I8_SHORT, KNOB_I8_SHORT_FORM})
+      if (knob_is_set(k)) return false;                 // a kernel for single layers is asked for
   if (mode == 0 || !plain_layer(a, 1) || !plain_layer(b, 3) || !plain_layer(c, 1) || a.addend || b.addend) return false;
   if (a.c % 32 != 0 || a.k % 4 != 0 || b.k != a.k || c.k % 16 != 0) return false;
   const int cb = (a.k + 31) / 32;

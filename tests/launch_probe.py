@@ -1,6 +1,8 @@
 """What a call hands to the runtime, without a GPU: builds launch_probe.cpp, whose own launch functions stand in for the runtime's, and
 drives it over a pipe."""
+import atexit
 import collections
+import functools
 import os
 import subprocess
 import tempfile
@@ -13,17 +15,23 @@ PKG = os.path.dirname(os.path.abspath(glowmi.__file__))
 Launch = collections.namedtuple("Launch", "kernel lds limit")
 
 
+@functools.lru_cache(maxsize=None)
+def _built(library):
+    tmp = tempfile.TemporaryDirectory()
+    atexit.register(tmp.cleanup)
+    exe = os.path.join(tmp.name, "launch_probe")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-D__HIP_PLATFORM_AMD__=1", "-isystem", "/opt/rocm/include", "-o", exe,
+                    os.path.join(HERE, "launch_probe.cpp"), library, f"-Wl,-rpath,{os.path.dirname(library)}", "-L/opt/rocm/lib",
+                    "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True, capture_output=True)
+    return exe
+
+
 class LaunchProbe:
     """A process of its own: nothing has been launched in it yet."""
 
     def __init__(self, library=None):
-        library = library or os.path.join(PKG, "libglowmi.so")
-        self.tmp = tempfile.TemporaryDirectory()
-        exe = os.path.join(self.tmp.name, "launch_probe")
-        subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-D__HIP_PLATFORM_AMD__=1", "-isystem", "/opt/rocm/include", "-o", exe,
-                        os.path.join(HERE, "launch_probe.cpp"), library, f"-Wl,-rpath,{os.path.dirname(library)}", "-L/opt/rocm/lib",
-                        "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True, capture_output=True)
-        self.process = subprocess.Popen([exe], stdin=subprocess.PIPE, stdout=subprocess.PIPE, text=True)
+        self.process = subprocess.Popen([_built(library or os.path.join(PKG, "libglowmi.so"))], stdin=subprocess.PIPE,
+                                        stdout=subprocess.PIPE, text=True)
 
     def _ask(self, line):
         self.process.stdin.write(line + "\n")
@@ -53,7 +61,6 @@ class LaunchProbe:
     def close(self):
         self.process.stdin.close()
         self.process.wait(timeout=30)
-        self.tmp.cleanup()
 
     def __enter__(self):
         return self

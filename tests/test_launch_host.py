@@ -22,3 +22,17 @@ def test_every_block_kernel_has_its_own_lds_limit(first):
                 kernels.add(launches[0].kernel)
                 assert launches[0].limit >= launches[0].lds, launches
         assert len(kernels) == 6
+
+
+@pytest.mark.parametrize("name,value", [("I8_TILE", 0), ("I8_SPLIT", 1), ("I8_SMALL_MAX_TILES", 0), ("I8_WIDE_SPLIT", 1), ("I8_WIDE_NBUF", 2),
+                                        ("I8_PW_MIN_ITEMS", 1), ("I8_K3_MIN_BLOCKS", 1), ("I8_K3_WAVES", 8), ("I8_K3_GATHER", 1), ("I8_FEW", 0),
+                                        ("I8_FEW_TILE", 0), ("I8_SHORT", 0), ("I8_SHORT_FORM", 0), ("I8_BLOCK", 0)])
+def test_a_switch_for_single_int8_layers_keeps_them_single(name, value):
+    """A sequence that runs as one launch by itself, and under a switch that asks for another kernel as three layers."""
+    with LaunchProbe() as probe:
+        assert len(probe.sequence((4, 28, 28, 256), _block(64), add=[2])) == 1
+        probe.knob(name, value)
+        launches = probe.sequence((4, 28, 28, 256), _block(64), add=[2])
+        assert len(launches) >= 3 and "block_i8" not in str(launches), launches
+        probe.knob("I8_BLOCK", 2)                        # asked for itself
+        assert len(probe.sequence((4, 28, 28, 256), _block(64), add=[2])) == 1
