@@ -132,3 +132,10 @@ def test_int8_layers_take_the_kernel_of_the_lowest_estimate(probe, layer, st, ke
 def test_fp32_layers_take_the_kernel_of_the_lowest_estimate(probe, layer, st, kernel):
     d = _desc(*layer, st)
     assert probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d)).kernel == kernel
+
+
+@pytest.mark.parametrize("m,k,n,bytes_of_slabs_of_32", [(330, 3568, 2293, 31954824), (314, 4088, 2219, 30222264), (570, 6296, 280, 24573440)])
+def test_deeper_slabs_of_fully_connected_layers_ask_for_no_more_workspace(m, k, n, bytes_of_slabs_of_32):
+    """A program that keeps a buffer of the size its calls once asked for keeps its kernel: the slices of the reduction are no more than
+    slabs of 32 give."""
+    assert 0 < glowmi.fc_packed_workspace_bytes(m, k, n) <= bytes_of_slabs_of_32
