@@ -444,10 +444,22 @@ bool plain_layer(const Problem& p, int r) {
          p.w_bytes <= 0x7FFFFFFFu;
 }
 
+// What a tile takes in LDS, by the blocks of 32 pixels of its patch and of itself and its patch's loads per thread.
+template <int CB>
+struct TileLds {
+  using G = Shape<CB>;
+  int work, staged, patch;
+  bool early;                    // the filters pass through where the layers' codes lie later, the patch beside them if there is room
+  int at_x, bytes;
+  TileLds(int pbp, int pbt, int loads)
+      : work(G::BASE + (pbp + pbt) * 32 * G::PITCH), staged(G::BASE + G::STAGED), patch(loads * BL_THREADS * 16),
+        early((work > staged ? work : staged) + patch <= G::LDS), at_x(early && staged > work ? staged : work),
+        bytes(at_x + patch > staged ? at_x + patch : staged) {}
+};
+
 // A tile's shape and its place in LDS; the bytes it takes there.
 template <int CB>
 int place_tile(Block& b, int th, int tw) {
-  using G = Shape<CB>;
   b.th = th;
   b.tw = tw;
   b.pw = tw + 2;
@@ -458,14 +470,12 @@ int place_tile(Block& b, int th, int tw) {
   b.tiles_x = (b.w + tw - 1) / tw;
   b.tiles_per_image = b.tiles_x * ((b.h + th - 1) / th);
   b.x_loads = (b.np * (b.c / 16) + BL_THREADS - 1) / BL_THREADS;
-  const int patch = b.x_loads * BL_THREADS * 16;
-  b.at_mid1 = G::BASE;
-  b.at_mid2 = b.at_mid1 + b.pbp * 32 * G::PITCH;
-  const int work = b.at_mid2 + b.pbt * 32 * G::PITCH, staged = G::BASE + G::STAGED;
-  // the filters pass through where the layers' codes lie later, the patch beside them if there is room
-  b.x_early = (work > staged ? work : staged) + patch <= G::LDS;
-  b.at_x = b.x_early && staged > work ? staged : work;
-  return b.at_x + patch > staged ? b.at_x + patch : staged;
+  const TileLds<CB> lds(b.pbp, b.pbt, b.x_loads);
+  b.x_early = lds.early;
+  b.at_mid1 = Shape<CB>::BASE;
+  b.at_mid2 = b.at_mid1 + b.pbp * 32 * Shape<CB>::PITCH;
+  b.at_x = lds.at_x;
+  return lds.bytes;
 }
 
 // What a launch is expected to take, in microseconds: a start with the filters' way, what a tile costs by the turns of a wavefront in
@@ -487,16 +497,24 @@ double three_launches_us(const Problem& a, const Problem& c) {
 constexpr double kBlockGain = 0.9;
 constexpr int kBlockMinMid = 24;
 
-// The lengths of equal parts of n, from `most` down to two (or n).
+// The lengths of equal parts of `whole`, from `most` down to two (or `whole`); `forced`: the one that this length gives.  Two divisions
+// for each: the next shorter length asks for this many parts, and that many parts have this length.
 struct Parts {
   int n = 0, length[MOST_PIXELS / 3], count[MOST_PIXELS / 3];
   Parts(int whole, int most, int forced) {
-    for (int l = whole < most ? whole : most; l >= (whole < 2 ? whole : 2); --l) {
-      const int c = (whole + l - 1) / l;
-      if ((whole + c - 1) / c != l || (forced && l != (whole + (whole + forced - 1) / forced - 1) / ((whole + forced - 1) / forced))) continue;
+    const int least = whole < 2 ? whole : 2, only = forced > 0 ? equal(whole, forced) : 0;
+    for (int l = whole < most ? whole : most; l >= least; --l) {
+      const int parts = (whole + l - 1) / l;
+      l = (whole + parts - 1) / parts;
+      if (l < least) break;
+      if (only && l != only) continue;
       length[n] = l;
-      count[n++] = c;
+      count[n++] = parts;
     }
+  }
+  static int equal(int whole, int l) {
+    const int parts = (whole + l - 1) / l;
+    return (whole + parts - 1) / parts;
   }
 };
 
@@ -509,20 +527,23 @@ bool plan_tile(Block& b, int images, int slots, double below, int* grid, int* ld
   const double fixed = cost.start + cost.mb * 1e-6 * ((double)b.x_bytes + b.y_bytes);
   double best = -1.0;
   int best_th = 0, best_tw = 0;
-  for (int i = 0; i < cols.n; ++i)
-    for (int j = 0; j < rows.n; ++j) {
+  for (int i = 0; i < cols.n; ++i) {
+    int j = 0;                                          // the first row of tiles whose patch is small enough
+    while (j < rows.n && (rows.length[j] + 2) * (cols.length[i] + 2) > MOST_PIXELS) ++j;
+    for (; j < rows.n; ++j) {
       const int tw = cols.length[i], th = rows.length[j], np = (th + 2) * (tw + 2);
       const long long tiles = (long long)cols.count[i] * rows.count[j] * images;
-      if (np > MOST_PIXELS || tiles > 0x7FFFFFFF) continue;
+      if (tiles > 0x7FFFFFFF) continue;
       const int pbp = (np + 31) / 32, pbt = (th * tw + 31) / 32, loads = (np * (b.c / 16) + BL_THREADS - 1) / BL_THREADS;
       const double each = cost.tile + cost.turn0 * ((pbp + G::PIXELS - 1) / G::PIXELS) + cost.turn1 * ((pbt + G::PIXELS - 1) / G::PIXELS) +
                           cost.turn2 * ((pbt + G::LAST_PIXELS - 1) / G::LAST_PIXELS) + cost.load * loads;
-      const double us = fixed + each * (double)((tiles + slots - 1) / slots);
-      if ((best >= 0.0 && us >= best) || place_tile<CB>(b, th, tw) > G::LDS) continue;
+      const double us = fixed + each * (double)(((unsigned)tiles + (unsigned)slots - 1) / (unsigned)slots);
+      if ((best >= 0.0 && us >= best) || TileLds<CB>(pbp, pbt, loads).bytes > G::LDS) continue;
       best = us;
       best_th = th;
       best_tw = tw;
     }
+  }
   if (best < 0.0 || best >= below) return false;
   *lds = place_tile<CB>(b, best_th, best_tw);
   const long long tiles = (long long)b.tiles_per_image * images;
@@ -567,6 +588,7 @@ bool launch_block_i8(const Problem& a, const Problem& b, const Problem& c, hipSt
   if (mode == 0 || !plain_layer(a, 1) || !plain_layer(b, 3) || !plain_layer(c, 1) || a.addend || b.addend) return false;
   if (a.c % 32 != 0 || a.k % 4 != 0 || b.k != a.k || c.k % 16 != 0) return false;
   const int cb = (a.k + 31) / 32;
+  if (mode != 2 && a.k < kBlockMinMid) return false;
   if (cb > 3 || a.c > 128 * cb || c.k > 128 * cb) return false;
   if (a.x_bytes > 0x7FFFFFFFu || (unsigned long long)c.M * c.k > 0x7FFFFFFFull) return false;
   const size_t y_bytes = (size_t)c.M * c.k;
@@ -582,7 +604,7 @@ bool launch_block_i8(const Problem& a, const Problem& b, const Problem& c, hipSt
   t.r_off = c.r_off; t.r_mant = c.r_mant; t.r_shift = c.r_shift;
   for (int i = 0; i < 3; ++i) fill_layer(t.l[i], *all[i]);
   swizzle_of(t.c / 16, &t.x_shift, &t.x_mask);
-  const double below = mode == 2 ? 1e30 : a.k < kBlockMinMid ? 0.0 : kBlockGain * three_launches_us(a, c);
+  const double below = mode == 2 ? 1e30 : kBlockGain * three_launches_us(a, c);
   if (!(cb == 1   ? launch_shape<1>(t, a.n, below, stream, status)
         : cb == 2 ? launch_shape<2>(t, a.n, below, stream, status)
                   : launch_shape<3>(t, a.n, below, stream, status)))
