@@ -6,7 +6,7 @@
 //   reset                              -> ok
 //   seq QUANTIZED LAYERS ADD n h w c   -> status, the variant's name, then for every launch  name|dynamic LDS bytes|limit set for that kernel
 //       followed by LAYERS times  k r  (stride 1, padding r / 2); ADD: bit i adds the sequence input in layer i
-//   times REPEATS                      -> shortest time of the last seq command's call, in nanoseconds
+//   versus NAME VALUE REPEATS          -> median times of the last seq command's call, in nanoseconds: with that knob set, with none set
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -118,19 +118,22 @@ int main() {
       std::cout << call() << ' ' << glowmi_last_variant();
       for (const Launch& l : launches) std::cout << ' ' << l.name << '|' << l.lds << '|' << l.limit;
       std::cout << std::endl;
-    } else if (what == "times") {
-      int repeats;
-      in >> repeats;
+    } else if (what == "versus") {
+      std::string name;
+      int value, repeats;
+      in >> name >> value >> repeats;
       note = false;
-      long long best = -1;
-      for (int i = 0; i < repeats; ++i) {
+      std::vector<long long> ns[2];
+      for (int i = 0; i < 2 * repeats; ++i) {            // in turn, call by call
+        glowmi_tuning_reset();
+        if (i % 2 == 0) glowmi_tuning_set(name.c_str(), value);
         const auto a = std::chrono::steady_clock::now();
         call();
-        const long long ns = std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - a).count();
-        best = best < 0 ? ns : std::min(best, ns);
+        ns[i % 2].push_back(std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - a).count());
       }
       note = true;
-      std::cout << best << std::endl;
+      for (auto& v : ns) std::nth_element(v.begin(), v.begin() + repeats / 2, v.end());
+      std::cout << ns[0][repeats / 2] << ' ' << ns[1][repeats / 2] << std::endl;
     } else {
       std::cout << "?" << std::endl;
     }

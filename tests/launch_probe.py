@@ -54,9 +54,9 @@ class LaunchProbe:
         self.variant = said[1]
         return [Launch(k, int(lds), int(limit)) for k, lds, limit in (s.rsplit("|", 2) for s in said[2:])]
 
-    def nanoseconds(self, repeats=2000):
-        """The shortest of so many calls like the last one."""
-        return int(self._ask(f"times {repeats}"))
+    def versus(self, name, value, repeats=3000):
+        """Median nanoseconds of a call like the last one: with that switch, with none."""
+        return tuple(map(int, self._ask(f"versus {name} {value} {repeats}").split()))
 
     def close(self):
         self.process.stdin.close()
