@@ -82,7 +82,7 @@ __device__ __forceinline__ int channel_of_row(int r) { return ((r >> 2) & 1) * 1
 __device__ __forceinline__ int panel_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 3); }
 
 // The term of the addend's code in byte B of `codes`, from the table at the start of LDS (the kernel's only LDS is what the launch
-// gives it, so `smem` is address 0): shifting the byte out and scaling it is one instruction.
+// gives it, so `smem` is address 0, which tests/test_kernel_invariants.py holds the compiler to): shifting the byte out and scaling it is one instruction.
 template <int B>
 __device__ __forceinline__ int addend_term(int codes) {
   typedef const int __attribute__((address_space(3))) * Table;

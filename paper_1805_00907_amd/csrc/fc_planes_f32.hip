@@ -37,7 +37,9 @@ constexpr int FP_TOTALS = FP_ROWS * FP_COLS * 4;        // LONGK: the sums folde
 constexpr int FP_FLUSH = 16;                            // slabs: a chain of 512 reduction indices per wavefront
 
 // A fragment of the input, 16 bytes per lane (zeros where the offset is out of range).  Inline assembly like load16_to_lds, and for
-// its sake: the compiler counts only the loads it knows of.  The kernel waits, then passes the registers through arrived().
+// its sake: the compiler counts only the loads it knows of.  The kernel waits, then passes the registers through arrived().  Between the
+// two nothing may copy or spill them, which the compiler cannot know: tests/test_kernel_invariants.py follows every path of the kernels as
+// compiled (with one way out of the main loop, in place of its three tests, the compiler spills 500 registers, some of them on their way).
 __device__ __forceinline__ v4i load16(v4i rsrc, unsigned voffset) {
   v4i r;
   asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(r) : "v"(voffset), "s"(rsrc) : "memory");

@@ -13,6 +13,9 @@ to drop loads; this test fails the build of the library's sources if it ever doe
 in a branch of its own; with a load still pending when such a branch is entered (a bias or addend value loaded inside
 the epilogue) the compiler puts `s_waitcnt vmcnt(0)` in front of every store, and every store then waits for the one
 before it to be written.  The kernels load those values ahead and state the wait once; this checks that it stays so.
+
+3. Registers whose loads the compiler does not count are left alone until a wait has covered them, and the LDS that a kernel
+addresses from zero starts there (what each is about stands with its test).
 """
 import os
 import re
@@ -99,3 +102,82 @@ def test_no_epilogue_store_waits_for_the_one_before_it(tmp_path, source, kernel,
     stores, waiting = _stores_that_wait(body)
     assert stores == n_stores, stores
     assert waiting <= 2, waiting        # (the contraction over planes waits once per 32-channel column, by design)
+
+
+def _registers(text):
+    regs = set()
+    for m in re.finditer(r"\bv(?:\[(\d+):(\d+)\]|(\d+))", text):
+        regs.update(range(int(m.group(1)), int(m.group(2)) + 1) if m.group(1) else [int(m.group(3))])
+    return frozenset(regs)
+
+
+def _touched_in_flight(body, step):
+    """Instructions that read or write a register whose load a wait has not yet covered, over every path through a kernel: (loads that
+    were followed, such instructions).  Vector-memory operations finish in order; s_waitcnt vmcnt(n) leaves the last n.
+    A step of the kernel's loop begins with the line `step`; a path on which a condition has left one out takes no further one (the
+    conditions of the unrolled steps are those of a count that goes up)."""
+    labels = {ln[:-1]: i for i, ln in enumerate(body) if ln.endswith(":")}
+    todo, seen, loads, bad = [(0, (), False)], set(), set(), set()
+    while todo:
+        at, flying, left_out = todo.pop()
+        while at < len(body):
+            ln = body[at]
+            if (at, flying, left_out) in seen or (left_out and ln == step):
+                break
+            seen.add((at, flying, left_out))
+            op, _, rest = ln.partition(" ")
+            if op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+                to_register = "_load_" in op and not rest.split()[-1] == "lds"
+                target = _registers(rest.split(",")[0]) if to_register else frozenset()
+                if (_registers(rest) - target | target) & frozenset().union(*flying):
+                    bad.add((at, ln))
+                if target:
+                    loads.add(at)
+                flying = (flying + (target,))[-63:]
+            elif op == "s_waitcnt":
+                m = re.search(r"vmcnt\((\d+)\)", rest)
+                assert m or "lgkmcnt" in rest, ln
+                if m:
+                    flying = flying[len(flying) - min(len(flying), int(m.group(1))):]
+            elif _registers(rest) & frozenset().union(*flying):
+                bad.add((at, ln))
+            if op == "s_endpgm":
+                break
+            m = re.match(r"s_(c?)branch\S* (\S+)$", ln)
+            if m:
+                if m.group(1):
+                    to = labels[m.group(2)]
+                    todo.append((to, flying, left_out or step in body[at:to]))
+                    left_out = left_out or step in body[to:to + 4]
+                else:
+                    at = labels[m.group(2)]
+                    continue
+            at += 1
+    return loads, sorted(bad)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_registers_of_loads_in_assembly_are_left_alone_until_they_are_there(tmp_path):
+    """fc_planes_f32.hip asks for the input's fragments in inline assembly, which the compiler does not count: a copy or spill of such a
+    register between the load and the wait would take what was in it before.  Every path of both kernels is followed."""
+    asm = _compile(tmp_path, "fc_planes_f32")
+    for longk in (0, 1):
+        body = _kernel_body(asm, f"igemm_f32_p3_fc_kernelILb{longk}E")
+        loads, bad = _touched_in_flight(body, "s_waitcnt vmcnt(12)")
+        assert not bad, bad[:5]
+        assert loads == {i for i, ln in enumerate(body) if re.match(r"(buffer|global)_load", ln) and ln.split()[-1] != "lds"}, "every load is on some path"
+        # what the check is worth: with the wait ahead of a slab's products gone (in the text alone), their operands are in flight
+        waits = [i for i, ln in enumerate(body) if ln == "s_waitcnt vmcnt(12)"]
+        assert len(waits) == 3, waits
+        for w in waits:
+            assert _touched_in_flight(body[:w] + ["s_nop 0"] + body[w + 1:], "s_waitcnt vmcnt(12)")[1]
+    assert re.findall(r"\.(?:vgpr_spill_count|private_segment_fixed_size): +(\d+)", asm) == ["0"] * 4
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_the_block_kernels_dynamic_lds_starts_at_address_zero(tmp_path):
+    """block_i8.hip's table of the addend's terms is addressed by the code alone: no LDS of a size known to the compiler may lie ahead of
+    what the launch gives the kernel."""
+    asm = _compile(tmp_path, "block_i8")
+    sizes = re.findall(r"\.group_segment_fixed_size: +(\d+)", asm)
+    assert sizes == ["0"] * 6, sizes
