@@ -1,5 +1,6 @@
 """1x1, 3x3, 1x1 of an int8 sequence in one launch (block_i8.hip) against the oracle's chain, code for code: channel counts that fill
-no chunk, tap or block of channels, maps smaller than a tile and ones that cut it, several tiles to a workgroup, and what stays three launches."""
+no chunk, tap or block of channels, maps smaller than a tile and ones that cut it, several tiles to a workgroup, and what stays three launches; runs
+anywhere in a longer sequence."""
 import numpy as np
 import pytest
 
@@ -104,6 +105,58 @@ def test_graph_replays_give_what_the_eager_call_gives(knobs):
         torch.cuda.synchronize()
         G.assert_equal_i8(y.cpu().numpy(), b.ref, "graph replay")
         float(torch.empty(1 << 16, device="cuda:0").normal_().sum())
+
+
+# layers as (output channels, filter size), which of them add the sequence's input, x's channels
+LONGER = {
+    "block, layer": ([(32, 1), (32, 3), (128, 1), (128, 3)], (2, 3), 128),
+    "layer, block": ([(128, 3), (32, 1), (32, 3), (128, 1)], (3,), 128),
+    "layer, block, layer": ([(96, 1), (28, 1), (28, 3), (112, 1), (64, 1)], (), 64),
+    "block, block": ([(64, 1), (64, 3), (256, 1), (56, 1), (56, 3), (256, 1)], (2, 5), 256),
+    "layer, block, block": ([(128, 1), (32, 1), (32, 3), (128, 1), (24, 1), (24, 3), (96, 1)], (6,), 96),
+}
+
+
+@pytest.mark.parametrize("layers,add,c", LONGER.values(), ids=LONGER)
+@pytest.mark.parametrize("in_place", [False, True], ids=["", "over_its_input"])
+@pytest.mark.parametrize("mode", [2, 0], ids=["blocks", "layers"])
+def test_longer_sequences(layers, add, c, in_place, mode, knobs):
+    """Runs that begin behind a layer (their input is a region of the arena, the addend the sequence's x), stand in front of one or of each
+    other, and write over x, which the last one's addend still is."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    knobs.set("I8_BLOCK", mode)
+    n, h, w = 2, 9, 11
+    specs, ci = [], c
+    for i, (k, r) in enumerate(layers):
+        specs.append(wl.ConvLayer(f"s{i}", n, h, w, ci, k, r, r, 1, r // 2, act=True, add=i in add))
+        ci = k
+    data = [wl.conv_inputs_q(s, 9700 + 10 * len(layers) + i) for i, s in enumerate(specs)]
+    qps = [d[3] for d in data]
+    in_q = [(qps[0].x_scale, qps[0].x_off)] + [(q.y_scale, q.y_off) for q in qps[:-1]]
+    x = ref = data[0][0]
+    tuples, keep = [], []
+    for i, s in enumerate(specs):
+        _, wt, b, qp = data[i]
+        wd, bd = G.dev(wt), G.dev(b)
+        keep += [wd, bd]
+        tuples.append((G.desc_of(s), wd, bd, s.act, s.add, glowmi.QParam(qp.w_scale, qp.w_off), glowmi.QParam(qp.y_scale, qp.y_off)))
+        ref = oracle.qconv2d_add(ref, in_q[i][0], in_q[i][1], wt, qp.w_scale, qp.w_off, b, x if s.add else None, in_q[0][0], in_q[0][1],
+                                 qp.y_scale, qp.y_off, (1, 1), (s.pad,) * 4, 1, act=s.act)
+    arr = glowmi.seq_layers(tuples)
+    arena, arena_guard = torch.full((glowmi.seq_arena_bytes(arr, True) + 4096,), 0x5a, dtype=torch.uint8, device="cuda:0"), 4096
+    xd = G.dev(x)
+    whole, y = (None, xd) if in_place else G.guarded((n, h, w, layers[-1][0]), torch.int8)
+    glowmi.seq_qconv2d(xd, glowmi.QParam(*in_q[0]), arr, y, arena[:-arena_guard])
+    torch.cuda.synchronize()
+    variant = glowmi.last_variant()
+    if layers[-2][1] == 3:                                    # a run is the last launch
+        assert variant.startswith("block_i8") == (mode == 2), variant
+    assert whole is None or G.guards_intact(whole, torch.int8), "write outside the output tensor"
+    assert bool((arena[-arena_guard:] == 0x5a).all()), "write behind the arena"
+    G.assert_equal_i8(y.cpu().numpy(), ref, variant)
+    assert 0.02 < np.mean((ref > -128) & (ref < 127)), "almost everything saturates"
 
 
 def test_what_stays_three_launches(knobs):

@@ -197,11 +197,14 @@ def test_resnet50_block_fp32_sequence_batch32():
     assert 0.2 < np.mean(prev > 0) < 0.98
 
 
-def test_resnet50_block_int8_sequence_batch32():
-    """Integer arithmetic end to end: the block's output must match the oracle's chain bit for bit."""
+@pytest.mark.parametrize("launches", [1, 3])
+def test_resnet50_block_int8_sequence_batch32(launches, knobs):
+    """Integer arithmetic end to end: the block's output must match the oracle's chain bit for bit, in one launch and in three."""
     import torch
     import paper_1805_00907_amd as glowmi
     G = _gpu()
+    if launches == 3:
+        knobs.set("I8_BLOCK", 0)
     specs = wl.resnet50_bottleneck(32)
     data = [wl.conv_inputs_q(s, wl.layer_seed(6, i)) for i, s in enumerate(specs)]
     xq = data[0][0]
@@ -229,5 +232,6 @@ def test_resnet50_block_int8_sequence_batch32():
         glowmi.seq_qconv2d(xd, glowmi.QParam(*in_q[0]), arr, y, arena)
         torch.cuda.synchronize()
         assert G.guards_intact(whole, torch.int8, fill=fill), "write outside the output tensor"
+        assert glowmi.last_variant().startswith("block_i8") == (launches == 1), glowmi.last_variant()
         G.assert_equal_i8(y.cpu().numpy(), prev, f"int8 block sequence, pre-fill {fill}")
     assert 0.02 < np.mean((prev > -128) & (prev < 127)), "almost everything saturates"

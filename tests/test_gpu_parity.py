@@ -535,6 +535,7 @@ def test_sequence_int8_bottleneck(n, hw, c, mid, knobs):
     y = G.poison((n, last.oh, last.ow, last.k), torch.int8)
     glowmi.seq_qconv2d(xd, glowmi.QParam(*in_q[0]), arr, y, arena)
     torch.cuda.synchronize()
+    assert not glowmi.last_variant().startswith("block_i8"), "the layers one by one"
     prev = xq
     for i, s in enumerate(specs):
         _, w, b, qp = data[i]

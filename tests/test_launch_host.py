@@ -45,3 +45,16 @@ def test_a_block_that_cannot_run_as_one_launch_is_not_searched_for_its_tile():
         assert len(probe.sequence((32, 56, 56, 64), _block(16), add=[2])) >= 3
         off, on = probe.versus("I8_BLOCK", 0)
         assert on < 1.15 * off, (off, on)
+
+
+@pytest.mark.parametrize("layers,runs,launches", [
+    ([(32, 1), (32, 3), (128, 1), (128, 3)], 1, 2), ([(128, 3), (32, 1), (32, 3), (128, 1)], 1, 2),
+    ([(96, 1), (28, 1), (28, 3), (112, 1), (64, 1)], 1, 3), ([(64, 1), (64, 3), (256, 1), (56, 1), (56, 3), (256, 1)], 2, 2),
+    ([(128, 1), (32, 1), (32, 3), (128, 1), (24, 1), (24, 3), (96, 1)], 2, 3), ([(32, 1), (32, 3)], 0, 2),
+], ids=["block_layer", "layer_block", "layer_block_layer", "block_block", "layer_block_block", "two_layers"])
+def test_runs_in_longer_sequences_are_found(layers, runs, launches):
+    """1x1, 3x3, 1x1 anywhere in a sequence is one launch, and every other layer is launched once."""
+    with LaunchProbe() as probe:
+        probe.knob("I8_BLOCK", 2)
+        got = probe.sequence((2, 9, 11, 64), layers)
+        assert sum("block_i8" in l.kernel for l in got) == runs and len(got) == launches, got
