@@ -471,7 +471,6 @@ __global__ __launch_bounds__(256) void splitk_finish_f32(const float* __restrict
                                                          const float* __restrict__ bias,
                                                          const float* addend, float* y, int total, int k,
                                                          int split_k, int act, float lo, float hi) {
-  fetch_arguments(partial, bias, addend, y, total, k, split_k, act, lo, hi);
   typedef float vec __attribute__((ext_vector_type(W)));
   const int groups = total / W;                      // W divides total (the launcher checks)
   for (int gi = blockIdx.x * blockDim.x + threadIdx.x; gi < groups; gi += gridDim.x * blockDim.x) {
@@ -546,7 +545,6 @@ __global__ __launch_bounds__(64 * SK_WAVES) void fc_skinny16_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ Wt, const float* __restrict__ bias,
     float* __restrict__ Y, float* __restrict__ partial, int M, int K, int N, int act, int split_k,
     int steps_per_split) {
-  fetch_arguments(A, Wt, bias, Y, partial, M, K, N, act, split_k, steps_per_split);
   __shared__ float red[(SK_WAVES - 1) * 16 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c16 = lane & 15, q = lane >> 4;

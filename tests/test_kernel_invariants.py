@@ -181,3 +181,20 @@ def test_the_block_kernels_dynamic_lds_starts_at_address_zero(tmp_path):
     asm = _compile(tmp_path, "block_i8")
     sizes = re.findall(r"\.group_segment_fixed_size: +(\d+)", asm)
     assert sizes == ["0"] * 6, sizes
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+@pytest.mark.parametrize("source,kernels", [("block_i8", 6), ("conv_dw", 12)])
+def test_every_line_of_a_kernels_arguments_is_asked_for_at_its_start(tmp_path, source, kernels):
+    """arguments.h: one load of each 64 bytes that the parameters lie in, whatever their number, ahead of the first wait."""
+    asm = _compile(tmp_path, source)
+    seen = 0
+    for m in re.finditer(r"^  - \.agpr_count.*?\.name: +(\S+)$", asm, re.S | re.M):
+        seen += 1
+        ends = [int(o) + int(n) for o, n in re.findall(r"\.offset: +(\d+)\s+\.size: +(\d+)\s+\.value_kind: +(?:by_value|global_buffer)", m.group(0))]
+        body = _kernel_body(asm, re.escape(m.group(1)[3:]))
+        first = body[:next(i for i, ln in enumerate(body) if ln.startswith("s_waitcnt"))]
+        got = {int(ln.rsplit(",", 1)[1], 16) for ln in first if ln.startswith("s_load_dword s")}
+        assert got >= set(range(0, max(ends), 64)), (m.group(1), max(ends), sorted(got))
+        assert max(got) < max(ends)
+    assert seen == kernels, seen
