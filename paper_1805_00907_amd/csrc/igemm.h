@@ -214,7 +214,8 @@ hipError_t launch_conv_small_f32(const Problem& p, hipStream_t stream, const cha
 int conv_small_f32_splits(const Problem& p);   // > 1: the split form of that kernel applies, with this many reduction slices
 // fp32 convolution on few pixels in one launch, any reduction (conv_few_f32.hip): the tile form to run it in and the
 // microseconds it is expected to take, -1: not a layer for it.
-int few_f32_form(const Problem& p, double* us, bool taps);   // taps: its form with the input patch in LDS may be taken
+int few_f32_form(const Problem& p, double* us);
+bool few_f32_in_lds(int form);   // the form whose tile's input patch lies in LDS
 hipError_t launch_few_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // fp32 pointwise convolution of any channel counts in fours on many pixels (conv_short_f32.hip): form and expected microseconds.
 int short_f32_form(const Problem& p, double* us);

@@ -727,13 +727,11 @@ constexpr int kShortExactChannels = 224;   // up to which conv_short_f32's sums 
 // after the fit (pointwise ones, ones of up to 2500 and of more pixels), operands in the caches and from memory: tiles 0.63 and 0.70
 // (600 move), one launch 0.74 and 0.80 (179), sliced 0.76 and 0.80 (49), the patch kernel 0.82 and 0.85 (64); six layers take more than
 // 1.08 of the time, the worst 1.18.  All choices together, short_or's among them, lie 0.9 % above the best one for each layer.  Deep 3x3
-// layers stay with slices: 512->512 on 7x7 9.8 us there and 13.6 here, 14.1 and 20.0 from memory.
+// layers stay with slices: 512->512 on 7x7 10.2 us there and 10.6 here with the patch in LDS, 13.6 without (from memory 13.6, 11.6 and 20.0).
 Plan few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FEW, 1);            // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
-  // (slices of 4608 indices and more stay where nothing but the patch in LDS is faster: with operands in the caches 512->512 on 7x7 takes
-  // 10.6 us there and 10.4 here, in a graph 10.9 and 9.9, 512->64 on 10x10 10.2 and 10.3, 9.1 and 9.8; of 400 channels 10.5 and 8.7)
-  const int form = few_f32_form(p, &us, rest.kernel != KERNEL_SMALL_SPLIT || p.Kgemm < 4608);
+  const int form = few_f32_form(p, &us);
   if (form < 0) return rest;
   if (mode != 2) {
     for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_SMALL_MAX_TILES, KNOB_F32_SMALL_NO_SPLIT,
@@ -760,7 +758,10 @@ Plan few_or(const Problem& p, const Plan& rest) {
     // and against the patch kernel, whose estimate is no closer than a twelfth beyond pointwise layers of 320 channels: 1x1 680->56 stride 2 on
     // 40x44 at batch 22 16.4 us there, 17.8 here)
     const bool many = rest.kernel == KERNEL_SMALL && (long long)((p.M + 31) / 32) * ((p.k + 31) / 32) > 256;
-    if ((p.M > 16384 ? 1.3 : many ? 1.25 : rest.kernel == KERNEL_PATCH ? 1.08 : 1.02) * us > other) return rest;
+    // the form with the patch in LDS against slices by an eighth: 63 layers whose estimates lie that far apart take 0.86 of the time in slices,
+    // 0.72 from memory, the slowest 1.10 and 0.89; the 26 that lie nearer 1.01, up to 1.18, and 0.84
+    const bool sliced = rest.kernel == KERNEL_SMALL_SPLIT && few_f32_in_lds(form);
+    if ((p.M > 16384 ? 1.3 : many ? 1.25 : sliced ? 1.12 : rest.kernel == KERNEL_PATCH ? 1.08 : 1.02) * us > other) return rest;
   }
   Plan pl = instead_of(p, rest, KERNEL_FEW, form);
   pl.us = (float)us;

@@ -139,3 +139,14 @@ def test_deeper_slabs_of_fully_connected_layers_ask_for_no_more_workspace(m, k, 
     """A program that keeps a buffer of the size its calls once asked for keeps its kernel: the slices of the reduction are no more than
     slabs of 32 give."""
     assert 0 < glowmi.fc_packed_workspace_bytes(m, k, n) <= bytes_of_slabs_of_32
+
+
+@pytest.mark.parametrize("n,h,c,k,form", [(1, 14, 256, 256, ("few", 3)), (1, 10, 400, 64, ("few", 3)), (3, 8, 608, 136, ("few", 3)),
+                                          (1, 20, 312, 48, ("few", 3)), (1, 28, 128, 128, ("few", 1)), (1, 7, 512, 512, ("small_split", 0)),
+                                          (5, 19, 512, 16, ("small_split", 0)), (1, 16, 504, 56, ("small_split", 0))])
+def test_estimates_alone_say_which_few_pixel_layers_keep_their_patch_in_lds(probe, n, h, c, k, form):
+    """3x3 layers whose tiles make one round of the compute units, however deep (608 channels 15.1 us in slices, 11.7 here); against slices
+    only what lies an eighth below them (504 channels 8.9 us in slices, 10.4 here)."""
+    d = _desc(n, h, h, c, k, 3, 2 if h == 19 else 1)
+    plan = probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d))
+    assert (plan.kernel, plan.tile if plan.kernel == "few" else 0) == form, plan
