@@ -757,22 +757,6 @@ bool p3_f32_applicable(const Problem& p) {
   return flops >= (double)knob_or(KNOB_F32_P3_RATIO, 400) * elems;
 }
 
-// Into how many slices a reduction is split where the tiles alone leave CUs idle: of the factors up to `most` the smallest that fills
-// 90 % of its last round over the slots, else the one that fills it best.
-int p3_slices(long long tiles, long long slots, int slabs, int most) {
-  int best = 1;
-  double best_u = 0.0;
-  for (int sk = 1; sk <= most; ++sk) {
-    const int sps = (slabs + sk - 1) / sk;
-    if ((slabs + sps - 1) / sps != sk) continue;
-    const long long blocks = tiles * sk;
-    const double u = (double)blocks / (double)(((blocks + slots - 1) / slots) * slots);
-    if (u > best_u + 1e-9) { best_u = u; best = sk; }
-    if (u >= 0.9) return sk;
-  }
-  return best;
-}
-
 Plan plan_p3_f32(const Problem& p) {
   Plan pl;
   pl.kernel = KERNEL_P3;
@@ -787,26 +771,23 @@ Plan plan_p3_f32(const Problem& p) {
   pl.split_k = 1;
   pl.slabs_per_split = pl.slabs;
   pl.pack_bytes = p3_pack_bytes(p);
-  // One workgroup per CU for the 128-channel tile, two for the 64-channel one; at least eight slabs per workgroup.
-  long long t = (long long)pl.tiles_m * pl.tiles_n * p.groups, slots = pl.bn == 128 ? 256 : 512;
-  const bool split = t < slots && pl.slabs >= 16;
-  int most = pl.slabs / 8 < 32 ? pl.slabs / 8 : 32;
-  if (p.b_is_kn) {
-    // a kernel of its own, 128 columns and slabs of twice the depth: no more slices than slabs of this depth give, as no call's query
-    // grows with the slabs, and 14 slices of 4 are slower than 4 of 14 besides (330x3568x2293 47.1 MB and 59.0 us without this bound, 16.8 and
-    // 38.2 with it; 671x3552x1143 61.9 and 39.4, 50.0 on slabs of 32; 25 calls of 20000 drawn ones differ)
-    if (split) most = p3_slices(t, slots, pl.slabs, most);
-    pl.bn = 128;
-    pl.tile = 0;
-    pl.bk = fc_planes_f32_slab();
-    pl.tiles_n = (p.kg + pl.bn - 1) / pl.bn;
-    pl.slabs = (p.cg + pl.bk - 1) / pl.bk;
-    pl.slabs_per_split = pl.slabs;
-    t = (long long)pl.tiles_m * pl.tiles_n;
-    slots = 256;
-  }
-  if (split) {
-    int best = p3_slices(t, slots, pl.slabs, most);
+  // Split the reduction when the tiles alone leave CUs idle: one workgroup per CU for the 128-channel tile, two
+  // for the 64-channel one; among the factors that keep at least eight slabs per workgroup take the smallest that
+  // fills 90 % of its last round, else the one that fills it best.
+  const long long t = (long long)pl.tiles_m * pl.tiles_n * p.groups;
+  const long long slots = pl.bn == 128 ? 256 : 512;
+  if (t < slots && pl.slabs >= 16) {
+    const int max_split = pl.slabs / 8 < 32 ? pl.slabs / 8 : 32;
+    int best = 1;
+    double best_u = 0.0;
+    for (int sk = 1; sk <= max_split; ++sk) {
+      const int sps = (pl.slabs + sk - 1) / sk;
+      if ((pl.slabs + sps - 1) / sps != sk) continue;
+      const long long blocks = t * sk;
+      const double u = (double)blocks / (double)(((blocks + slots - 1) / slots) * slots);
+      if (u > best_u + 1e-9) { best_u = u; best = sk; }
+      if (u >= 0.9) { best = sk; break; }
+    }
     if (knob_is_set(KNOB_F32_SPLIT)) {
       best = knob(KNOB_F32_SPLIT);
       if (best < 1) best = 1;
@@ -817,6 +798,18 @@ Plan plan_p3_f32(const Problem& p) {
       pl.slabs_per_split = (pl.slabs + best - 1) / best;
       pl.split_k = (pl.slabs + pl.slabs_per_split - 1) / pl.slabs_per_split;
     }
+  }
+  if (p.b_is_kn) {
+    // A kernel of its own, 128 columns and slabs of twice the depth: the same slices, filled up to whole slabs.  Fewer and longer ones, which a
+    // search over slabs of that depth finds, lie up to 1.28 times as far from 64-bit sums (819x1912x3872: 57 us in place of 103); more and
+    // shorter ones ask for more workspace and are slower (330x3568x2293: 47 MB in place of 28, 62 us in place of 48).
+    const int deep = fc_planes_f32_slab() / PBK;
+    pl.bn = 128;
+    pl.tile = 0;
+    pl.bk = fc_planes_f32_slab();
+    pl.slabs = (p.cg + pl.bk - 1) / pl.bk;
+    pl.slabs_per_split = (pl.slabs_per_split + deep - 1) / deep;
+    pl.split_k = (pl.slabs + pl.slabs_per_split - 1) / pl.slabs_per_split;
   }
   return pl;
 }
