@@ -222,7 +222,10 @@ __global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p
         }
         next_x();
         next_w();
-        // the halves fold in turn, eight slabs and their barriers apart
+        // The halves fold in turn, eight slabs and their barriers apart, into one set of totals: twice as many additions as each would
+        // make by itself, so what one loses goes on with the sums (1024x9216x4096 1.03 of the generic kernel's distance from 64-bit sums
+        // without that, 0.95 with it, 0.95 to 1.00 over 49 calls; 0.9 % of the time).  An infinity's loss is a NaN, which the outputs of
+        // such an operand are anyway.
         if (LONGK && (++done & (FP_FLUSH - 1)) == kgrp * (FP_FLUSH / 2)) {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
@@ -231,8 +234,10 @@ __global__ __launch_bounds__(512, 2) void igemm_f32_p3_fc_kernel(const Problem p
               v4f t = totals[(j * 4 + e4) * 64];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                t[e] += __builtin_fmaf(lo[j][e4 * 4 + e], kLowPieceWeight, hi[j][e4 * 4 + e]);
-                hi[j][e4 * 4 + e] = lo[j][e4 * 4 + e] = 0.f;
+                const float v = __builtin_fmaf(lo[j][e4 * 4 + e], kLowPieceWeight, hi[j][e4 * 4 + e]), sum = t[e] + v;
+                hi[j][e4 * 4 + e] = v - (sum - t[e]);     // what the addition lost
+                lo[j][e4 * 4 + e] = 0.f;
+                t[e] = sum;
               }
               totals[(j * 4 + e4) * 64] = t;
             }

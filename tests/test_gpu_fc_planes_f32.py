@@ -51,3 +51,35 @@ def test_fc_over_planes(case, order, knobs):
     assert G.guards_intact(whole, torch.float32), "write outside the output"
     scale = np.where(np.arange(M) % 3 == 0, np.float32(2.0 ** 20), np.float32(1.0))[:, None]   # a row's results scale with it
     G.assert_close_f32(y.cpu().numpy() / scale, ref / scale, f"fc over planes {case} {order}")
+
+
+@pytest.mark.parametrize("M,K,N", [(1152, 9216, 128), (1152, 4608, 256)])
+def test_sums_folded_in_turn_lie_no_farther_from_64_bit_ones(M, K, N, knobs):
+    """Long reductions fold the sums of a workgroup's two halves into one set of totals.  The same product as a pointwise convolution over the
+    same planes (igemm_f32_p3: as many products to a chain, totals of each half's own) says how far sums of this kind lie from 64-bit ones; a
+    hundredth is what the order alone changes."""
+    import gpu_util as G
+    import torch
+    import paper_1805_00907_amd as glowmi
+    for name, value in (("F32_P3_MIN_M", 1), ("F32_P3_RATIO", 0), ("F32_SPLIT", 1)):
+        knobs.set(name, value)
+    rng = np.random.default_rng(47500 + K)
+    a = rng.standard_normal((M, K)).astype(np.float32)
+    w = (rng.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32)
+    exact = a.astype(np.float64) @ w.astype(np.float64)
+    ad, wd, y = G.dev(a), G.dev(w), G.poison((M, N), torch.float32)
+    planes = torch.empty(glowmi.fc_filter_planes_bytes(K, N), dtype=torch.uint8, device="cuda:0")
+    glowmi.fc_pack_filter(wd, K, N, planes)
+    glowmi.fc_packed(ad, wd, planes, None, y, M, K, N, wl.ACT_NONE, G.workspace(glowmi.fc_packed_workspace_bytes(M, K, N)))
+    torch.cuda.synchronize()
+    assert glowmi.last_variant() == "igemm_f32_p3_fc_128x128_longk"
+    got = np.linalg.norm(y.cpu().numpy() - exact)
+    knobs.set("F32_PATCH", 0)
+    desc = glowmi.ConvDesc(1, M, 1, K, N, 1, 1, 1, 1, 0, 0, 0, 0, 1)
+    z = G.poison((1, M, 1, N), torch.float32)
+    glowmi.conv2d(ad, G.dev(np.ascontiguousarray(w.T)), None, z, desc, wl.ACT_NONE, G.workspace(glowmi.conv2d_workspace_bytes(desc)))
+    torch.cuda.synchronize()
+    assert glowmi.last_variant().startswith("igemm_f32_p3_128x128") and glowmi.last_variant().endswith("longk"), glowmi.last_variant()
+    reference = np.linalg.norm(z.cpu().numpy().reshape(M, N) - exact)
+    print(f"distances {got / np.linalg.norm(exact):.3e} and {reference / np.linalg.norm(exact):.3e}")
+    assert got <= 1.01 * reference, (got, reference)

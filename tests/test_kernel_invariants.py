@@ -147,7 +147,7 @@ def _touched_in_flight(body, step):
             if m:
                 if m.group(1):
                     to = labels[m.group(2)]
-                    todo.append((to, flying, left_out or step in body[at:to]))
+                    todo.append((to, flying, left_out or step in body[at:to] + body[at + 1:at + 4]))
                     left_out = left_out or step in body[to:to + 4]
                 else:
                     at = labels[m.group(2)]
