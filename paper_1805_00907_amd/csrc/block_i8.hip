@@ -17,8 +17,8 @@
 // A tap's channels are filled up to 32 CB codes in LDS with zeros on the pixels' side: what the last chunk of a filter's tap reads
 // of the next one meets them.
 // Measured (the three launches -> here): 256/64 on 56x56 at batch 32 34.4 -> 27.3 us, 256/64 on 28x28 at batch 2 15.3 -> 7.9, 128/32 on
-// 7x10 at batch 6 15.2 -> 6.7, 320/80 on 42x40 at batch 3 16.0 -> 11.4; 0.61 of their time over 300 blocks of 32 to 96 channels in the
-// middle.  What bounds it: small blocks the start, 3 to 7 thousand cycles of the filters' way at some 40 bytes a cycle, and code that
+// 7x10 at batch 6 15.2 -> 6.7, 320/80 on 42x40 at batch 3 16.0 -> 11.4; over 287 drawn blocks of 24 to 96 channels in the middle that
+// run here 0.65 of their time, 0.62 with operands from memory (0.54, 0.61 and 0.82 with up to 32, 64 and 96 channels).  What bounds it: small blocks the start, 3 to 7 thousand cycles of the filters' way at some 40 bytes a cycle, and code that
 // waits for its instructions the first time through (12 KB of it unrolled cost 1 us more than 9 KB rolled up); large ones the last
 // layer, whose requantize steps and table reads each take what it takes.  Tried: slabs of filters through a ring in LDS with a barrier
 // each (a slab is 0.9 us whatever its products: 256/64 on 28x28 13 us, 1024/256 on 14x14 60 against 18 in three launches); the
@@ -361,8 +361,9 @@ __global__ __launch_bounds__(BL_THREADS, 2 * Shape<CB>::PER_CU) void block_i8_ke
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
 
-    // The last layer.  The sums start at the channels' terms and the addend's: a block's are made while the one before is
-    // requantized, its addend is on its way for two blocks.
+    // The last layer.  The sums start at the channels' terms and the addend's.  The addend of the first block of a wavefront's pixels is
+    // waited for with nothing beside it; a later one's is asked for once the products of the block before are issued and waited for behind
+    // its requantize steps.
     auto place = [&](int b) {                           // where the lane's pixel of a block of the tile goes
       const int px = b * 32 + l32, ty = p.div_tw.div(px), oy = o_y + ty, ox = o_x + px - ty * p.tw;
       return px < p.nt && oy < p.h && ox < p.w ? (unsigned)(((o_img * p.h + oy) * p.w + ox) * p.l[2].k) + 16u * lh : OOB;
@@ -491,8 +492,8 @@ double three_launches_us(const Problem& a, const Problem& c) {
   const double px = a.M, macs = px * a.k * ((double)a.c + 9.0 * a.k + c.k);
   return 13.8 + 0.238e-6 * px * a.c + 2.61e-9 * macs + 0.254e-4 * px;
 }
-// One launch where it is expected to take less than nine tenths of three: over the 300 blocks 0.61 of their time, none slower (all of
-// them in one launch: 0.61, two slower by half a percent).  With fewer channels in the middle more of each product is fill than the
+// One launch where it is expected to take less than nine tenths of three: 287 of 300 blocks drawn after the fit, 0.65 and 0.62 of their time,
+// the slowest 0.99 and 0.91 (all 300 in one launch: 0.67 and 0.63, the slowest 1.12 and 0.99).  With fewer channels in the middle more of each product is fill than the
 // estimate was fitted to, and a block's three launches take as long as one of these.
 constexpr double kBlockGain = 0.9;
 constexpr int kBlockMinMid = 24;

@@ -811,10 +811,14 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
   Plan pl = rest;
   double us;
   if (mode >= 2) return plan_fc_tiles_f32(p, allow_split, &pl, &us) ? asking(p, pl) : rest;
-  // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 29 -> 18.6 us), and of the
-  // contraction over planes where that would have to cut the weights as well and takes longer by its own measured times
-  // (256x4096x4096 82 -> 52 us; 1024x4096x4096 stays: 162 against 195; near the line it is still the faster one by up to 10 %,
-  // 600x3000x4000 107 against 119, 700x9216x1000 93 against 100).
+  // From 65 rows, in place of the fp32 matrix cores (half its time at most sizes: 200x2048x2048 29 -> 18.6 us), and of the contraction over
+  // planes where that would have to cut the weights as well (256x4096x4096 82 -> 52 us) and either of two estimates says that it takes
+  // longer.  One goes by its operations and the weights: what it gives to this kernel asks for next to no workspace, and stays (838x712x4008
+  // would be 41 us over planes, 51 here).  The other is that of the contraction as it is: so much to begin with, per round of the CUs and slab
+  // of 64 in it, per megabyte of a split's parts and of what is cut (fitted to 220 calls of 256 to 1600 rows, operands in the caches and from
+  // memory, median error 3 %; fc_tiles_f32's own estimate lies at 0.87 of such times).  Over 440 calls, half of them drawn after the fit, it
+  // moves 42 more, 0.91 of their time (770x2224x4000 140 -> 113 us), one slower by more than 2 % (1442x4112x472 58 -> 73); the choices lie 0.5 %
+  // above the best one for each, 1.4 % without it.  What moves lies at 0.76 to 1.00 of the distance from 64-bit sums.
   if (p.M < 65 || (rest.kernel != KERNEL_TILED && rest.kernel != KERNEL_P3) || knob_is_set(KNOB_F32_TILE) ||
       knob_is_set(KNOB_F32_P3_MIN_M) || knob_is_set(KNOB_F32_SPLIT) || (rest.kernel == KERNEL_P3 && p.w_packed))
     return rest;
@@ -826,7 +830,11 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
   }
   if (rest.kernel == KERNEL_P3) {
     const double padded = 2e-9 * ((p.M + 127) / 128 * 128) * ((p.k + 127) / 128 * 128) * (double)p.Kgemm;
-    if (us > 22.0 + 3.3 * padded + 0.45e-6 * (double)p.w_bytes) return rest;
+    const double by_work = 22.0 + 3.3 * padded + 0.45e-6 * (double)p.w_bytes;
+    const double rounds = (double)(((long long)rest.tiles_m * rest.tiles_n * rest.split_k + 255) / 256);
+    const double parts = rest.split_k > 1 ? 4e-6 * rest.split_k * (double)p.M * p.k : 0.0;
+    const double as_it_is = 13.85 + rounds * (1.272 * rest.slabs_per_split + 2.754) + 0.424 * parts + 0.723e-6 * ((double)p.x_bytes + p.w_bytes);
+    if (us > by_work && us > 0.84 * as_it_is) return rest;
   }
   pl.ask = ask;
   pl.us = (float)us;

@@ -47,9 +47,8 @@ void probe_conv(const glowmi_conv_desc* d, int32_t mode, int32_t addend, int32_t
   out->workspace = used(call.p, call.plan);
 }
 
-// The int8 FullyConnected call of those extents with a workspace as large as it likes.
-void probe_qfc(int32_t M, int32_t K, int32_t N, int32_t w_offset, ProbePlan* out) {
-  Problem p;
+// The FullyConnected calls of those extents with a workspace as large as they like.
+static void fill(Problem& p, int32_t M, int32_t K, int32_t N) {
   std::memset(&p, 0, sizeof(p));
   p.allow_pack = 1;
   p.n = M; p.h = p.w_ = 1; p.c = p.cg = K; p.k = p.kg = N; p.r = p.s = 1; p.oh = p.ow = 1;
@@ -57,6 +56,23 @@ void probe_qfc(int32_t M, int32_t K, int32_t N, int32_t w_offset, ProbePlan* out
   p.div_ohow = p.div_ow = p.div_s = make_fastdiv(1);
   p.div_cg = make_fastdiv((uint32_t)K);
   p.x = fake(1); p.w = fake(2); p.y = fake(4);
+}
+
+void probe_fc(int32_t M, int32_t K, int32_t N, ProbePlan* out) {
+  Problem p;
+  fill(p, M, K, N);
+  p.x_bytes = 4u * (uint32_t)M * (uint32_t)K; p.w_bytes = 4u * (uint32_t)K * (uint32_t)N;
+  const Plan pl = plan_f32(p, true);
+  out->status = GLOWMI_OK;
+  out->kernel = pl.kernel;
+  out->tile = pl.tile;
+  out->split_k = pl.split_k;
+  out->workspace = used(p, pl);
+}
+
+void probe_qfc(int32_t M, int32_t K, int32_t N, int32_t w_offset, ProbePlan* out) {
+  Problem p;
+  fill(p, M, K, N);
   p.x_bytes = (uint32_t)M * (uint32_t)K; p.w_bytes = (uint32_t)K * (uint32_t)N;
   p.w_off = w_offset; p.mant = 1 << 30; p.shift = 31; p.lo = -128; p.hi = 127;
   const Plan pl = plan_i8(p, true);

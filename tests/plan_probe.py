@@ -40,6 +40,11 @@ class Probe:
                             ctypes.byref(raw))
         return self._plan(raw)
 
+    def fc(self, m, k, n):
+        raw = _Raw()
+        self.lib.probe_fc(m, k, n, ctypes.byref(raw))
+        return self._plan(raw)
+
     def qfc(self, m, k, n, w_offset=0):
         raw = _Raw()
         self.lib.probe_qfc(m, k, n, w_offset, ctypes.byref(raw))

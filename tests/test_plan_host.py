@@ -151,3 +151,16 @@ def test_estimates_alone_say_which_few_pixel_layers_keep_their_patch_in_lds(prob
     d = _desc(n, h, h, c, k, 3, 2 if h == 19 else 1)
     plan = probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d))
     assert (plan.kernel, plan.tile if plan.kernel == "few" else 0) == form, plan
+
+
+@pytest.mark.parametrize("m,k,n,kernel", [(770, 2224, 4000, "fc_tiles"), (256, 4096, 4096, "fc_tiles"), (1024, 4096, 4096, "p3"),
+                                          (1455, 2424, 1072, "fc_tiles")])
+def test_fully_connected_calls_that_cut_their_weights_take_the_faster_kernel(probe, m, k, n, kernel):
+    """Against the contraction over planes as it is: its rounds of the compute units and its slices count."""
+    assert probe.fc(m, k, n).kernel == kernel
+
+
+def test_fully_connected_calls_that_ask_for_next_to_no_workspace_go_on_doing_so(probe):
+    """What fc_tiles_f32 takes in place of the contraction over planes by its operations alone has no scratch to ask for."""
+    for m, k, n in [(838, 712, 4008), (609, 536, 4264), (881, 3200, 2264), (948, 912, 3944)]:
+        assert probe.fc(m, k, n).kernel == "fc_tiles" and glowmi.fc_workspace_bytes(m, k, n) <= 256
