@@ -18,9 +18,10 @@
 // of the next one meets them.
 // Measured (the three launches -> here): 256/64 on 56x56 at batch 32 34.4 -> 27.3 us, 256/64 on 28x28 at batch 2 15.3 -> 7.9, 128/32 on
 // 7x10 at batch 6 15.2 -> 6.7, 320/80 on 42x40 at batch 3 16.0 -> 11.4; over 287 drawn blocks of 24 to 96 channels in the middle that
-// run here 0.65 of their time, 0.62 with operands from memory (0.54, 0.61 and 0.82 with up to 32, 64 and 96 channels).  What bounds it: small blocks the start, 3 to 7 thousand cycles of the filters' way at some 40 bytes a cycle, and code that
-// waits for its instructions the first time through (12 KB of it unrolled cost 1 us more than 9 KB rolled up); large ones the last
-// layer, whose requantize steps and table reads each take what it takes.  Tried: slabs of filters through a ring in LDS with a barrier
+// run here 0.65 of their time, 0.62 with operands from memory (0.54, 0.61 and 0.82 with up to 32, 64 and 96 channels).  What bounds it:
+// small blocks the start, 3 to 7 thousand cycles of the filters' way at some 40 bytes a cycle, and code that waits for its instructions the
+// first time through (12 KB of it unrolled cost 1 us more than 9 KB rolled up); large ones the last layer, whose requantize steps and table
+// reads each take what it takes.  Tried: slabs of filters through a ring in LDS with a barrier
 // each (a slab is 0.9 us whatever its products: 256/64 on 28x28 13 us, 1024/256 on 14x14 60 against 18 in three launches); the
 // reduction split over the wavefronts and summed in LDS (1.1 to 1.4 of the time on any block); 128 channels, whose filters leave no
 // registers unsplit (0.9 to 1.1 of the three launches' time).
@@ -82,7 +83,8 @@ __device__ __forceinline__ int channel_of_row(int r) { return ((r >> 2) & 1) * 1
 __device__ __forceinline__ int panel_swizzle(int r) { return (r & 7) ^ ((r >> 3) & 3); }
 
 // The term of the addend's code in byte B of `codes`, from the table at the start of LDS (the kernel's only LDS is what the launch
-// gives it, so `smem` is address 0, which tests/test_kernel_invariants.py holds the compiler to): shifting the byte out and scaling it is one instruction.
+// gives it, so `smem` is address 0, which tests/test_kernel_invariants.py holds the compiler to): shifting the byte out and scaling it is
+// one instruction.
 template <int B>
 __device__ __forceinline__ int addend_term(int codes) {
   typedef const int __attribute__((address_space(3))) * Table;
@@ -493,8 +495,8 @@ double three_launches_us(const Problem& a, const Problem& c) {
   return 13.8 + 0.238e-6 * px * a.c + 2.61e-9 * macs + 0.254e-4 * px;
 }
 // One launch where it is expected to take less than nine tenths of three: 287 of 300 blocks drawn after the fit, 0.65 and 0.62 of their time,
-// the slowest 0.99 and 0.91 (all 300 in one launch: 0.67 and 0.63, the slowest 1.12 and 0.99).  With fewer channels in the middle more of each product is fill than the
-// estimate was fitted to, and a block's three launches take as long as one of these.
+// the slowest 0.99 and 0.91 (all 300 in one launch: 0.67 and 0.63, the slowest 1.12 and 0.99).  With fewer channels in the middle more of
+// each product is fill than the estimate was fitted to, and a block's three launches take as long as one of these.
 constexpr double kBlockGain = 0.9;
 constexpr int kBlockMinMid = 24;
 

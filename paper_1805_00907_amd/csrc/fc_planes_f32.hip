@@ -11,11 +11,12 @@
 //     into registers a slab and a half ahead.
 //   - The weights take the matrix instruction's first operand, so that a lane ends up with one row and four columns in a row of
 //     registers: 16-byte stores, one scale of the input's per lane.
-// What bounds it: power.  A slab is 1536 cycles of matrix work on every SIMD and takes 1830, next to 1024 cycles of LDS reads, 256 of
-// LDS writes and 1024 of the vector memory path; in calls back to back the clock falls to 1.63 GHz (2.35 alone).  256 x 4096 x 4096
-// on 256 workgroups of 16 slabs: 4800 cycles until the first slab is there, 29300 for the slabs, 7200 for sums and stores, 28.6 us
-// where both operands went through LDS, 64-byte pieces of rows at a time, and results left a dword per row: 33.4; the whole call 44.2 ->
-// 38.7 us, 1024 rows 110 -> 104.  Sums as far from 64-bit ones as there (1.26e-7 of the result's norm).
+// What bounds it: power.  A slab is 1536 cycles of matrix work on every SIMD and takes 1810, next to 1024 cycles of LDS reads, 256 of
+// LDS writes and 1024 of the vector memory path; the clock, 2.2 to 2.4 GHz ahead of the loop and behind it, is 1.56 GHz in it in calls back to
+// back and 1.41 in one alone.  256 x 4096 x 4096 on 256 workgroups of 16 slabs: 4200 cycles until the first slab is there, 28900 for the slabs,
+// 7800 for sums and stores, 23.6 us between a workgroup's first and last, 29 us by the trace; where both operands went through LDS, 64-byte
+// pieces of rows at a time, and results left a dword per row: 33.4; the whole call 44.2 -> 38.7 us, 1024 rows 110 -> 104, 0.91 of the time over 200
+// calls, 0.88 with operands from memory.  Sums as far from 64-bit ones as there (0.91 to 1.03 of their distance, median 1.00).
 #include <hip/hip_runtime.h>
 
 #include "arguments.h"

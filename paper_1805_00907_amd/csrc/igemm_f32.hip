@@ -768,10 +768,11 @@ Plan few_or(const Problem& p, const Plan& rest) {
   pl.was_small = mode != 2 && rest.kernel == KERNEL_SMALL;
   return pl;
 }
-// Pointwise layers of up to 32 output channels over 64 or 128: conv_pw_f32 multiplies groups of 64.  Over 258 layers of 32768 to
-// 131072 pixels conv_short_f32 takes 0.783 of its time, 0.66 to 0.94 (64->32 at 33124 pixels 8.22 -> 5.43 us, 128->32 at 37636 10.86 -> 7.75, 64->16 at 524288 42.7 -> 37.9, 64->32 + add at 1048576 119 -> 113);
-// sums at 0.48 to 0.71 of its distance from 64-bit ones.  Not with a second round of the wavefronts less than half full (1.00 to 1.06 with operands
-// from memory), nor channels out of fours with an addend (64->31 + add at 262144 29.0 -> 30.5).
+// Pointwise layers of up to 32 output channels over 64 or 128: conv_pw_f32 multiplies groups of 64.  Over 157 of 260 drawn layers of 32768 to
+// 131072 pixels that move conv_short_f32 takes 0.71 of its time, 0.84 with operands from memory, the slowest 0.88 and 1.01 (64->32 at 33124
+// pixels 8.22 -> 5.43 us, 128->32 at 37636 10.86 -> 7.75, 64->16 at 524288 42.7 -> 37.9, 64->32 + add at 1048576 119 -> 113); sums at 0.49 to
+// 0.70 of its distance from 64-bit ones.  Not with a second round of the wavefronts less than half full (1.00 to 1.06 with operands from memory),
+// nor channels out of fours with an addend (64->31 + add at 262144 29.0 -> 30.5).
 bool narrow_layer(const Problem& p) {
   const long long blocks = ((long long)p.M + 31) / 32, wavefronts = 8LL * (num_compute_units() > 0 ? num_compute_units() : 256);
   return p.k <= 32 && p.c <= 128 && p.stride_h == 1 && p.stride_w == 1 && (p.k % 4 == 0 || !p.addend) &&
