@@ -728,8 +728,9 @@ double fixed_cost(const Problem& p) {
 }
 
 // The cheapest form for the layer and its cost; a 3x3 stride-2 layer has one form (two of its patches do not fit a CU; a
-// chunk of it takes 1.35 times as long).
-int cheapest_form(const Problem& p, int forced, int forced_parts, bool may_split, double* cost, int* parts) {
+// chunk of it takes 1.35 times as long).  split: the cheapest form in parts, with forced_parts of them or, where that is below one, as many
+// as are fastest; one where it takes longer than the form for the whole.
+int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, PatchParts* split, double* split_us) {
   const bool pointwise = p.r == 1;
   const double fixed = fixed_cost(p);
   int best = -1;
@@ -739,34 +740,40 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, bool may_split
     if (p.stride_h == 1) map[1] = pick_map_tile(p, 128, 208);
   }
   // (a filter of more than 16 MB: 624->816 on 17x17 at batch 2 31 -> 42 us in parts)
-  const int most = may_split && !pointwise && p.w_bytes <= (16u << 20) ? kMostParts : 1;
-  *parts = 1;
+  const int most = split && !pointwise && p.w_bytes <= (16u << 20) ? kMostParts : 1;
+  PatchParts in_parts = {0, 1};
   for (int f = 0; f < FORMS; ++f) {
     const FormCost& c = kForms[f];
     if (pointwise ? c.cc1 == 0 : p.stride_h == 2 && f != 1) continue;
     if (forced >= 0 && f != forced) continue;
     const double px_tiles = pointwise ? (double)((p.M + c.px - 1) / c.px) : (double)p.n * map[c.px == 128].tiles;
-    const double tiles = px_tiles * ((p.k + c.bn - 1) / c.bn);
+    const double tiles = px_tiles * ((p.k + c.bn - 1) / c.bn), slots = c.waves == 8 ? 256 : 512;
+    auto in_rounds = [&](double rounds) {
+      return c.waves == 4 && rounds <= 0.5 ? 0.7 : rounds <= 3.0 ? (double)(int)(rounds + 0.999999) : rounds + 0.5;
+    };
     const int cc = pointwise ? c.cc1 : c.cc3;
     const int chunks = (p.c + cc - 1) / cc;
     const double chunk = pointwise ? c.chunk1 : p.stride_h == 2 ? 1.35 * c.chunk3 : c.chunk3;
-    for (int s = 1; s <= most; ++s) {
+    const double round = pointwise ? c.round1 : c.round3;
+    const double t = fixed + in_rounds(tiles / slots) * (round + chunks * chunk);
+    if (best < 0 || t < *cost) {
+      best = f;
+      *cost = t;
+    }
+    for (int s = 2; s <= most; ++s) {
       const int each = (chunks + s - 1) / s;
       if ((chunks + each - 1) / each != s || (forced_parts > 0 && s != forced_parts)) continue;
       // (a part's tiles are dealt to the eight XCDs: three times 84 tiles are 33 workgroups to an XCD of 32 CUs)
-      const double rounds = (s == 1 ? tiles : 8.0 * (((long long)tiles + 7) / 8)) * s / (c.waves == 8 ? 256 : 512);
-      const double r = c.waves == 4 && rounds <= 0.5 ? 0.7 : rounds <= 3.0 ? (double)(int)(rounds + 0.999999) : rounds + 0.5;
-      const double round = pointwise ? c.round1 : c.round3;
-      double t = fixed + r * (round + each * chunk);
-      if (s > 1) t = kPartsMargin * (3.0 + 1.03 * fixed + 0.83 * r * round + 0.94 * r * each * chunk + 1.02 * (rounds < 1.0 ? rounds : 1.0) +
-                                     1.34e-6 * s * (double)p.M * p.k + 0.067e-6 * p.w_bytes);
-      if (best < 0 || t < *cost) {
-        best = f;
-        *cost = t;
-        *parts = s;
+      const double rounds = 8.0 * (((long long)tiles + 7) / 8) * s / slots, r = in_rounds(rounds);
+      const double u = kPartsMargin * (3.0 + 1.03 * fixed + 0.83 * r * round + 0.94 * r * each * chunk + 1.02 * (rounds < 1.0 ? rounds : 1.0) +
+                                       1.34e-6 * s * (double)p.M * p.k + 0.067e-6 * p.w_bytes);
+      if (in_parts.parts == 1 || u < *split_us) {
+        in_parts = {f, s};
+        *split_us = u;
       }
     }
   }
+  if (split) *split = in_parts.parts > 1 && (forced_parts > 1 || *split_us < *cost) ? in_parts : PatchParts{0, 1};
   return best;
 }
 
@@ -774,7 +781,8 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, bool may_split
 
 // The form to run a layer in, -1: not a layer for this kernel.  An addend does not count: the workspace queries do not know
 // of it, and a call must not plan what they did not ask room for.
-int patch_f32_form(const Problem& p, bool may_split, double* us_out, int* parts) {
+int patch_f32_form(const Problem& p, double* us_out, PatchParts* split) {
+  if (split) *split = {0, 1};
   const int mode = knob_or(KNOB_F32_PATCH, 1);          // 0: off, 2: any size (tests)
   if (mode == 0 || (mode == 1 && knob_or(KNOB_F32_P3, 1) == 0)) return -1;   // either switch: such layers stay on the fp32 matrix cores
   if (p.b_is_kn || p.chain_n > 0 || p.groups != 1) return -1;
@@ -799,10 +807,13 @@ int patch_f32_form(const Problem& p, bool may_split, double* us_out, int* parts)
   const double margin = p.packed_is_cut && p.r == 1 ? (p.c < 32 ? 4.5 : 3.2) : p.r == 1 || small ? 1.6 : 0.5;
   // no form takes less than a start, an end and a chunk of the cheapest: most small layers are decided without a search for tiles
   if (mode == 1 && fixed_cost(p) + (p.r == 1 ? 2.4 : 4.1) + margin >= other) return -1;
-  double cost = 0.0;
-  const int form = cheapest_form(p, forced, knob_or(KNOB_F32_PATCH_PARTS, mode == 2 ? 1 : -1), may_split, &cost, parts);
+  const int parts = knob_or(KNOB_F32_PATCH_PARTS, mode == 2 ? 1 : -1);
+  double cost = 0.0, split_us = 0.0;
+  const int form = cheapest_form(p, forced, parts, &cost, parts == 1 ? nullptr : split, &split_us);
   *us_out = cost;
-  return mode == 2 || cost + margin < other ? form : -1;
+  if (mode == 2 || cost + margin < other) return form;
+  if (split && split->parts > 1 && split_us + margin >= other) split->parts = 1;
+  return -1;
 }
 
 namespace {

@@ -193,6 +193,7 @@ struct Plan {
   bool was_small = false; // KERNEL_FEW: in place of conv_small_f32 (fp32)
   size_t stood_in_for = 0; // KERNEL_FEW, KERNEL_FC_FEW, KERNEL_SHORT, which use none: the workspace of the kernel that would have run
   size_t ask = 0;       // what a kernel of the layer's that this one stands in for would want, where that is more
+  int parts = 1, parts_tile = 0;   // KERNEL_PATCH, KERNEL_P3: conv_patch_f32's parts of the reduction and the form with them, where they are faster
 };
 Plan plan_f32(const Problem& p, bool allow_split);
 Plan plan_i8(const Problem& p, bool allow_split);
@@ -269,8 +270,10 @@ double k3v_f32_efficiency(const Problem& p);
 bool k3v_f32_prefers_fixed_tile(const Problem& p);
 hipError_t launch_k3v_f32(const Problem& p, hipStream_t stream, const char** variant);
 // fp32 1x1 and 3x3 convolution, stride 1 or 2, of ordinary size on the fp16 matrix cores (conv_patch_f32.hip).
-// patch_f32_form: the tile form to run a layer in and its expected microseconds, -1 where another kernel is the better one.
-int patch_f32_form(const Problem& p, bool may_split, double* us, int* parts);   // parts: of its reduction
+// patch_f32_form: the tile form to run a layer in and its expected microseconds, -1 where another kernel is the better one.  split, where
+// asked for: the form with the reduction in parts and their number, one where that is not faster (than the other kernel, with -1).
+struct PatchParts { int form, parts; };
+int patch_f32_form(const Problem& p, double* us, PatchParts* split);
 size_t patch_f32_pack_bytes(const Problem& p);
 bool patch_f32_order_fits(const Problem& p);   // whether planes of the filter in that kernel's order fit the buffer of filter_planes_bytes
 hipError_t launch_patch_f32(const Problem& p, int form, int parts, hipStream_t stream, const char** variant);

@@ -893,21 +893,24 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
   }
   return instead_of(p, rest, KERNEL_FC_FEW, form);
 }
+// conv_patch_f32 with the reduction in parts in place of itself and of the contraction over planes, which multiply the same two fp16 pieces of
+// an operand.  What runs on fp32 operands (tiles, slices, conv_few_f32) stays there: 24 bits of each, and an infinity reaches no other outputs
+// than its own.
+Plan in_parts(const Problem& p, const Plan& whole) {
+  Plan pl = instead_of(p, whole, KERNEL_PATCH, whole.parts_tile);
+  pl.stood_in_for = 0;
+  pl.split_k = whole.parts;
+  pl.pack_bytes = p.packed_is_cut ? 256 : (patch_f32_pack_bytes(p) + 255) / 256 * 256;   // the parts behind the planes
+  return pl;
+}
 }  // namespace
 
 Plan plan_f32(const Problem& p, bool allow_split) {
   const Plan rest = plan_f32_rest(p, allow_split);
   if (p.b_is_kn) return fc_few_or(p, tiles_or(p, rest, allow_split));
-  if (rest.kernel == KERNEL_PATCH && rest.split_k > 1) {
-    // parts of the reduction take the place of what runs without them, but for the kernels of shorter reductions: conv_few_f32's results lie
-    // 0.82 to 0.88 as far from 64-bit sums
-    Problem whole = p;
-    whole.allow_pack = kPackWhole;
-    const Plan before = plan_f32(whole, allow_split);
-    return before.kernel == KERNEL_FEW || before.kernel == KERNEL_SHORT ? before : rest;
-  }
   const bool may_move = rest.kernel == KERNEL_TILED || rest.kernel == KERNEL_SMALL || rest.kernel == KERNEL_SMALL_SPLIT || rest.kernel == KERNEL_PATCH;
-  return short_or(p, may_move || knob_or(KNOB_F32_FEW, 1) == 2 ? few_or(p, rest) : rest);
+  const Plan whole = short_or(p, may_move || knob_or(KNOB_F32_FEW, 1) == 2 ? few_or(p, rest) : rest);
+  return whole.parts > 1 ? in_parts(p, whole) : whole;
 }
 
 namespace {
@@ -937,10 +940,11 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
     // on many pixels are faster on the kernel that keeps the filter in registers.  Over planes given it uses no workspace, but
     // a call that has none stays in fp32 arithmetic where it would without planes, the layers of the 3x3 tile kernels apart
     const bool without = p.packed_is_cut && (k3c64 || k3 || knob_or(KNOB_F32_PATCH, 1) == 2);
-    int form = -1, parts = 1;
+    int form = -1;
+    PatchParts split = {0, 1};
     double patch_us = 0.0;
     if ((allow_split || without) && p.allow_pack && !knob_is_set(KNOB_F32_P3_MIN_M) && (knob_or(KNOB_F32_PATCH, 1) == 2 || !pw_f32_applicable(p)))
-      form = patch_f32_form(p, allow_split && p.allow_pack != kPackWhole, &patch_us, &parts);
+      form = patch_f32_form(p, &patch_us, allow_split && p.allow_pack != kPackWhole ? &split : nullptr);
     if (k3c64 && (form < 0 || knob_is_set(KNOB_F32_K3C64_MIN_TILES))) {
       pl.kernel = KERNEL_K3C64;
       pl.pack_bytes = k3c64_f32_pack_bytes(p);
@@ -955,11 +959,9 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
       pl.kernel = KERNEL_PATCH;
       pl.tile = form;
       pl.us = (float)patch_us;
-      pl.pack_bytes = without && parts == 1 ? 0 : p.packed_is_cut ? 256 : patch_f32_pack_bytes(p);
-      if (parts > 1) {
-        pl.split_k = parts;
-        pl.pack_bytes = (pl.pack_bytes + 255) / 256 * 256;   // the parts behind the planes
-      }
+      pl.parts = split.parts;
+      pl.parts_tile = split.form;
+      pl.pack_bytes = without ? 0 : p.packed_is_cut ? 256 : patch_f32_pack_bytes(p);
       // the workspace queries name what the kernel wants that would run otherwise: a buffer of that size serves either
       if (k3c64) pl.ask = k3c64_f32_pack_bytes(p);
       else if (k3) pl.ask = k3_f32_pack_bytes(p);
@@ -967,7 +969,12 @@ Plan plan_f32_rest(const Problem& p, bool allow_split) {
       return pl;
     }
     // large contractions with a workspace to repack the operands into: the kernel over fp16 planes
-    if (allow_split && p.allow_pack && p3_f32_applicable(p)) return plan_p3_f32(p);
+    if (allow_split && p.allow_pack && p3_f32_applicable(p)) {
+      pl = plan_p3_f32(p);
+      pl.parts = split.parts;
+      pl.parts_tile = split.form;
+      return pl;
+    }
     if (pw_f32_applicable(p)) { pl.kernel = KERNEL_PW; return pl; }
     if (conv_small_f32_applicable(p)) { pl.kernel = KERNEL_SMALL; return pl; }
     if (fc_rows_f32_applicable(p)) { pl.kernel = KERNEL_FC_ROWS; return pl; }

@@ -164,3 +164,34 @@ def test_fully_connected_calls_that_ask_for_next_to_no_workspace_go_on_doing_so(
     """What fc_tiles_f32 takes in place of the contraction over planes by its operations alone has no scratch to ask for."""
     for m, k, n in [(838, 712, 4008), (609, 536, 4264), (881, 3200, 2264), (948, 912, 3944)]:
         assert probe.fc(m, k, n).kernel == "fc_tiles" and glowmi.fc_workspace_bytes(m, k, n) <= 256
+
+
+def _drawn_3x3(seed, count):
+    """3x3 layers of 48 to 1024 channels on small and middling maps, one in six with channels out of eights."""
+    rng = random.Random(seed)
+    for _ in range(count):
+        step = rng.choice([8, 8, 8, 8, 8, 1])
+        h = rng.randint(5, 60)
+        yield _desc(rng.choice([1, 2, 4, 9, 20]), h, h if rng.random() < 0.6 else rng.randint(5, 60), step * rng.randint(48 // step, 1024 // step),
+                    step * rng.randint(16 // step, 1024 // step), 3, rng.choice([1, 2]))
+
+
+def _is(d):
+    return (d.n, d.h, d.w, d.c, d.k, d.stride_h)
+
+
+def test_reductions_in_parts_only_replace_kernels_of_the_same_arithmetic(probe, knobs):
+    """Layers that run on fp32 operands keep them, and infinities to the outputs they reach: tiles, slices and conv_few_f32 stay."""
+    layers = list(_drawn_3x3(5, 1200)) + [_desc(8, 28, 28, 256, 256, 3, 2), _desc(4, 14, 14, 512, 512, 3, 2), _desc(7, 10, 10, 632, 56, 3)]
+    calls = [(d, packed, add) for d in layers for packed in (False, True) if not packed or d.c % 8 == 0 for add in (False, True)]
+    plans = [probe.conv(d, packed=packed, addend=add) for d, packed, add in calls]
+    knobs.set("F32_PATCH_PARTS", 1)
+    whole = [probe.conv(d, packed=packed, addend=add) for d, packed, add in calls]
+    taken = set()
+    for (d, packed, add), plan, before in zip(calls, plans, whole):
+        if plan.kernel == "patch" and plan.split_k > 1:
+            taken.add(before.kernel)
+            assert before.kernel in ("patch", "p3"), (_is(d), packed, add, before, plan)
+        else:
+            assert plan == before, (_is(d), packed, add)
+    assert taken == {"patch", "p3"}
