@@ -723,8 +723,8 @@ constexpr FormCost kForms[FORMS] = {
 constexpr int kMostParts = 8;
 constexpr double kPartsMargin = 1.10;
 
-double fixed_cost(const Problem& p) {
-  return (p.packed_is_cut ? 1.0 : 4.3 + 1e-6 * p.w_bytes) + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k);
+double fixed_cost(const Problem& p, bool cut_ahead) {
+  return (cut_ahead ? 1.0 : 4.3 + 1e-6 * p.w_bytes) + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k);
 }
 
 // The cheapest form for the layer and its cost; a 3x3 stride-2 layer has one form (two of its patches do not fit a CU; a
@@ -732,7 +732,7 @@ double fixed_cost(const Problem& p) {
 // as are fastest; one where it takes longer than the form for the whole.
 int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, PatchParts* split, double* split_us) {
   const bool pointwise = p.r == 1;
-  const double fixed = fixed_cost(p);
+  double steps = 0.0, split_steps = 0.0;                 // of the forms chosen, beside what is fixed
   int best = -1;
   MapTile map[2] = {{0, 0, 0}, {0, 0, 0}};               // of 64 and of 128 pixels
   if (!pointwise) {
@@ -755,25 +755,28 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, 
     const int chunks = (p.c + cc - 1) / cc;
     const double chunk = pointwise ? c.chunk1 : p.stride_h == 2 ? 1.35 * c.chunk3 : c.chunk3;
     const double round = pointwise ? c.round1 : c.round3;
-    const double t = fixed + in_rounds(tiles / slots) * (round + chunks * chunk);
-    if (best < 0 || t < *cost) {
+    const double t = in_rounds(tiles / slots) * (round + chunks * chunk);
+    if (best < 0 || t < steps) {
       best = f;
-      *cost = t;
+      steps = t;
     }
     for (int s = 2; s <= most; ++s) {
       const int each = (chunks + s - 1) / s;
       if ((chunks + each - 1) / each != s || (forced_parts > 0 && s != forced_parts)) continue;
       // (a part's tiles are dealt to the eight XCDs: three times 84 tiles are 33 workgroups to an XCD of 32 CUs)
       const double rounds = 8.0 * (((long long)tiles + 7) / 8) * s / slots, r = in_rounds(rounds);
-      const double u = kPartsMargin * (3.0 + 1.03 * fixed + 0.83 * r * round + 0.94 * r * each * chunk + 1.02 * (rounds < 1.0 ? rounds : 1.0) +
-                                       1.34e-6 * s * (double)p.M * p.k + 0.067e-6 * p.w_bytes);
-      if (in_parts.parts == 1 || u < *split_us) {
+      const double u = 0.83 * r * round + 0.94 * r * each * chunk + 1.02 * (rounds < 1.0 ? rounds : 1.0) + 1.34e-6 * s * (double)p.M * p.k;
+      if (in_parts.parts == 1 || u < split_steps) {
         in_parts = {f, s};
-        *split_us = u;
+        split_steps = u;
       }
     }
   }
-  if (split) *split = in_parts.parts > 1 && (forced_parts > 1 || *split_us < *cost) ? in_parts : PatchParts{0, 1};
+  auto split_cost = [&](double fixed) { return kPartsMargin * (3.0 + 1.03 * fixed + split_steps + 0.067e-6 * p.w_bytes); };
+  const double fixed = fixed_cost(p, p.packed_is_cut != 0), over_planes = fixed_cost(p, true);
+  *cost = fixed + steps;
+  *split_us = split_cost(fixed);
+  if (split) *split = in_parts.parts > 1 && (forced_parts > 1 || split_cost(over_planes) < over_planes + steps) ? in_parts : PatchParts{0, 1};
   return best;
 }
 
@@ -806,7 +809,7 @@ int patch_f32_form(const Problem& p, double* us_out, PatchParts* split) {
   // (a pointwise layer of few channels, which fill a quarter of a chunk, longer: 16->824 stride 2 at 2312 pixels 6.5 us with tiles, 7.6)
   const double margin = p.packed_is_cut && p.r == 1 ? (p.c < 32 ? 4.5 : 3.2) : p.r == 1 || small ? 1.6 : 0.5;
   // no form takes less than a start, an end and a chunk of the cheapest: most small layers are decided without a search for tiles
-  if (mode == 1 && fixed_cost(p) + (p.r == 1 ? 2.4 : 4.1) + margin >= other) return -1;
+  if (mode == 1 && fixed_cost(p, p.packed_is_cut != 0) + (p.r == 1 ? 2.4 : 4.1) + margin >= other) return -1;
   const int parts = knob_or(KNOB_F32_PATCH_PARTS, mode == 2 ? 1 : -1);
   double cost = 0.0, split_us = 0.0;
   const int form = cheapest_form(p, forced, parts, &cost, parts == 1 ? nullptr : split, &split_us);

@@ -380,6 +380,36 @@ def test_conv_packed_in_the_order_of_the_patch_kernel(shape, knobs):
         assert np.all(np.abs(packed.cpu().numpy() - np.maximum(ref, 0)) <= 4 * 2.0 ** -22 * mag)
 
 
+# n  h   w   c    k    st     reductions in parts, by the planner's own choice
+PARTS_SHAPES = [(9, 41, 41, 200, 232, 2), (1, 50, 50, 600, 224, 1), (16, 14, 14, 512, 512, 2)]
+
+
+@pytest.mark.parametrize("shape", PARTS_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv_packed_in_parts(shape):
+    """A layer whose reduction is taken in parts: as many of the same tiles with planes and without, bit for bit the same results."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    G = _gpu()
+    n, h, w, c, k, st = shape
+    desc = glowmi.ConvDesc(n, h, w, c, k, 3, 3, st, st, 1, 1, 1, 1, 1)
+    oh, ow = glowmi.conv_out_shape(desc)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(37900 + c)
+    x = torch.randn((n, h, w, c), generator=gen, device="cuda:0")
+    wt = torch.randn((k, 3, 3, c), generator=gen, device="cuda:0") / (9 * c) ** 0.5
+    b, add = torch.randn((k,), generator=gen, device="cuda:0"), torch.randn((n, oh, ow, k), generator=gen, device="cuda:0")
+    planes = G.workspace(glowmi.conv2d_filter_planes_bytes(desc))
+    glowmi.conv2d_pack_filter(wt, desc, planes)
+    for addend in (None, add):
+        plain, packed = G.poison((n, oh, ow, k), torch.float32), G.poison((n, oh, ow, k), torch.float32)
+        glowmi.conv2d_chain(x, wt, b, plain, desc, addend=addend, act=wl.ACT_RELU, workspace=G.workspace(glowmi.conv2d_workspace_bytes(desc)))
+        variant = glowmi.last_variant()
+        glowmi.conv2d_packed(x, wt, planes, b, packed, desc, addend=addend, act=wl.ACT_RELU, workspace=G.workspace(glowmi.conv2d_packed_workspace_bytes(desc)))
+        torch.cuda.synchronize()
+        assert variant.startswith("conv_patch_f32") and variant.endswith("_parts") and glowmi.last_variant() == variant, (variant, glowmi.last_variant())
+        assert torch.equal(plain, packed)
+
+
 # how planes of channels that come in eights but not in sixteens get their order: conv_patch_f32 takes every layer, or none
 ORDERS = {"by_channel": {"F32_PATCH": 2}, "rows": {"F32_PATCH": 0}}
 READERS = {       # knobs that bring a layer to the kernel, its name, layers: n h w c k r stride

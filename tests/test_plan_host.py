@@ -195,3 +195,18 @@ def test_reductions_in_parts_only_replace_kernels_of_the_same_arithmetic(probe, 
         else:
             assert plan == before, (_is(d), packed, add)
     assert taken == {"patch", "p3"}
+
+
+def test_planes_given_do_not_change_how_the_patch_kernel_sums(probe):
+    """Bit for bit the same results where that kernel serves a layer both ways: the same form and the same parts of its reduction."""
+    both = in_parts = 0
+    for d in list(_drawn_3x3(6, 3000)) + [_desc(9, 41, 41, 200, 232, 3, 2), _desc(1, 50, 50, 600, 224, 3)]:
+        if d.c % 8:
+            continue
+        plain = probe.conv(d, workspace=glowmi.conv2d_workspace_bytes(d))
+        packed = probe.conv(d, packed=True, workspace=glowmi.conv2d_packed_workspace_bytes(d))
+        if plain.kernel == packed.kernel == "patch":
+            both += 1
+            in_parts += plain.split_k > 1
+            assert (plain.tile, plain.split_k) == (packed.tile, packed.split_k), (_is(d), plain, packed)
+    assert both > 500 and in_parts > 50
