@@ -433,7 +433,7 @@ glowmi_status run_cuts(PreparedCall* const* calls, int n, hipStream_t stream) {
 
 glowmi_status prepare_conv2d_chain(const float* x, const float* w, const float* bias, float* y,
                                    const glowmi_conv_desc* d, const glowmi_chain* chain, void* workspace,
-                                   size_t workspace_bytes, PreparedCall* out, const void* w_planes) {
+                                   size_t workspace_bytes, PreparedCall* out, const void* w_planes, bool parts) {
   if (!chain) return fail(GLOWMI_ERR_NULL, "chain must not be NULL");
   const glowmi_act act = chain->act;
   Geometry geo;
@@ -449,6 +449,7 @@ glowmi_status prepare_conv2d_chain(const float* x, const float* w, const float* 
   p.x = x; p.w = w; p.bias = bias; p.y = y; set_act(p, act);
   set_packed(p, w_planes);
   p.addend = chain->addend;
+  if (!parts) p.allow_pack = kPackWhole;
   out->plan = plan_with_workspace(p, plan_f32, workspace, workspace_bytes);
   out->quantized = false;
   return GLOWMI_OK;

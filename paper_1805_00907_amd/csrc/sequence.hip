@@ -122,7 +122,7 @@ glowmi_status run_sequence(const void* x, glowmi_qparam xq, const glowmi_seq_lay
       st = glowmi::prepare_conv2d_chain(static_cast<const float*>(in), static_cast<const float*>(layers[i].w),
                                         static_cast<const float*>(layers[i].bias), static_cast<float*>(out),
                                         &layers[i].desc, &chain, cut ? cuts + plan.cut_at[(size_t)i] : ws,
-                                        cut ? cut : plan.workspace, &calls[(size_t)i]);
+                                        cut ? cut : plan.workspace, &calls[(size_t)i], nullptr, false);
     }
     if (st != GLOWMI_OK) return st;          // nothing has been launched
     in = out;

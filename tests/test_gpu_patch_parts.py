@@ -84,3 +84,35 @@ def test_planned(n, h, c, k, stride, parts, knobs):
     # ways to sum 4608 products of unit variance in short runs of 32 bits: each within some 2e-7 of the sums' norm
     for other in outs[1:]:
         assert float((outs[0] - other).norm() / outs[0].norm()) < 1e-6, names
+
+
+def test_layers_of_a_sequence_run_whole(knobs):
+    """A layer that runs in parts by itself, and next to one that wants more scratch than its parts: in a sequence it is what the same calls
+    without parts give, bit for bit."""
+    import torch
+    import paper_1805_00907_amd as glowmi
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(9)
+    x = torch.randn((16, 5, 7, 840), generator=gen, device="cuda:0")
+    descs = [glowmi.ConvDesc(16, 5, 7, c, k, 3, 3, 1, 1, 1, 1, 1, 1, 1) for c, k in ((840, 248), (248, 1024))]
+    ws = [torch.randn((d.k, 3, 3, d.c), generator=gen, device="cuda:0") / (9 * d.c) ** 0.5 for d in descs]
+    bs = [torch.randn((d.k,), generator=gen, device="cuda:0") for d in descs]
+
+    def one_by_one():
+        at, names = x, []
+        for d, w, b in zip(descs, ws, bs):
+            y = torch.full((16, 5, 7, d.k), float("nan"), device="cuda:0")
+            nbytes = glowmi.conv2d_workspace_bytes(d)
+            glowmi.conv2d(at, w, b, y, d, glowmi.ACT_RELU, torch.empty(nbytes, dtype=torch.uint8, device="cuda:0") if nbytes else None)
+            names.append(glowmi.last_variant())
+            at = y
+        return at, names
+
+    assert one_by_one()[1][0].endswith("_parts")
+    layers = glowmi.seq_layers([(d, w, b, glowmi.ACT_RELU, False) for d, w, b in zip(descs, ws, bs)])
+    y = torch.full((16, 5, 7, 1024), float("nan"), device="cuda:0")
+    glowmi.seq_conv2d(x, layers, y, torch.empty(glowmi.seq_arena_bytes(layers, False), dtype=torch.uint8, device="cuda:0"))
+    knobs.set("F32_PATCH_PARTS", 1)
+    want, names = one_by_one()
+    torch.cuda.synchronize()
+    assert not names[0].endswith("_parts") and torch.equal(y, want), names

@@ -58,3 +58,13 @@ def test_runs_in_longer_sequences_are_found(layers, runs, launches):
         probe.knob("I8_BLOCK", 2)
         got = probe.sequence((2, 9, 11, 64), layers)
         assert sum("block_i8" in l.kernel for l in got) == runs and len(got) == launches, got
+
+
+@pytest.mark.parametrize("neighbours", [[], [(512, 1)], [(1024, 3)]], ids=["alone", "small", "large"])
+@pytest.mark.parametrize("x,layer", [((16, 5, 7, 840), (248, 3)), ((5, 17, 17, 472), (64, 3)), ((1, 50, 50, 600), (224, 3))], ids=str)
+def test_a_layer_of_a_sequence_is_launched_as_its_arena_was_sized(x, layer, neighbours):
+    """Arenas name no room for reductions in parts, and whatever a layer finds free in one, its reduction is in one part."""
+    with LaunchProbe() as probe:
+        got = probe.sequence(x, [layer] + neighbours, quantized=False)
+        probe.knob("F32_PATCH_PARTS", 1)
+        assert got == probe.sequence(x, [layer] + neighbours, quantized=False)
