@@ -69,6 +69,30 @@ def test_conv_short_i8(shape, tiles, knobs):
            ((0, wl.ACT_RELU), (0.7, wl.ACT_NONE), (2.0 ** -26, wl.ACT_NONE)))
 
 
+# long reductions: the filter reaches LDS in passes of 64 chunks of 16 codes, each lane with one to four of them
+# n  h  w  c  k  r  s  stride  pads, the slices (in tiles of 32 channels) whose filters LDS holds
+LONG = [
+    ((1, 7, 6, 92, 68, 3, 3, (1, 1), (1, 1, 1, 1)), (1, 2)),      # 54 chunks: one pass of four to a lane
+    ((1, 4, 9, 796, 36, 1, 1, (1, 1), (0, 0, 0, 0)), (1, 2)),     # 50, a single tap
+    ((2, 6, 7, 100, 40, 3, 3, (1, 1), (1, 1, 1, 1)), (1, 2)),     # 63 and zeros up to 66: a second pass of zeros but one
+    ((1, 5, 4, 1021, 36, 1, 1, (1, 1), (0, 0, 0, 0)), (1, 2)),    # 64, the last one cut, channels at every byte of a dword
+    ((2, 5, 6, 128, 72, 3, 3, (2, 1), (1, 1, 1, 1)), (1, 2)),     # 72, rows whole cache lines apart, a stride
+    ((1, 5, 7, 125, 44, 3, 3, (1, 1), (1, 0, 2, 1)), (1, 2)),     # 72, channels at every byte, one-sided padding
+    ((1, 4, 5, 1100, 36, 1, 1, (1, 1), (0, 0, 0, 0)), (1, 2)),    # 69 and zeros up to 72, a single tap
+    ((2, 5, 6, 136, 40, 3, 3, (1, 1), (1, 1, 1, 1)), (1,)),       # 81 and zeros up to 84
+    ((1, 4, 5, 228, 68, 3, 3, (1, 2), (1, 1, 1, 1)), (1,)),       # 135 and zeros up to 138: a third pass
+    ((1, 4, 5, 231, 36, 3, 3, (1, 1), (1, 1, 1, 1)), (1,)),       # the same, channels at every byte
+]
+
+
+@pytest.mark.parametrize("shape,tiles", [(shape, t) for shape, forms in LONG for t in forms], ids=lambda v: "x".join(map(str, v[:7])) if isinstance(v, tuple) else str(v))
+def test_conv_short_i8_long_reductions(shape, tiles, knobs):
+    """Code sums, places in the image and zeros behind the reduction that go on from one pass of the filter's staging to the next."""
+    knobs.set("I8_SHORT", 2)
+    knobs.set("I8_SHORT_FORM", tiles)
+    _check(_gpu(), shape, np.random.default_rng(40900 + shape[3] + shape[4]), f"{shape} tiles {tiles}", ((0, wl.ACT_RELU), (0.7, wl.ACT_NONE)))
+
+
 @pytest.mark.parametrize("shape", [(3, 61, 77, 24, 40, 1, 1, (1, 1), (0, 0, 0, 0)), (2, 70, 53, 12, 136, 3, 3, (1, 1), (1, 1, 1, 1))],
                          ids=lambda s: "x".join(map(str, s[:7])))
 def test_conv_short_i8_several_blocks(shape, knobs):
