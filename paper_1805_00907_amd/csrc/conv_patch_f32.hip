@@ -722,6 +722,11 @@ constexpr FormCost kForms[FORMS] = {
 // fitted to 3551 runs of 260 3x3 layers of 96 to 768 channels on up to 9000 pixels (median error 4 %); the margin is that of both estimates.
 constexpr int kMostParts = 8;
 constexpr double kPartsMargin = 1.10;
+// Layers that parts are measured on: 410 drawn ones that the estimates give to them, 0.84 of the time in one part with operands in the caches
+// and 0.80 from memory, the slowest 1.04 by both.  Beyond: 91592 pixels 1.06, 1896 channels on 12264 1.06; and in place of the contraction over
+// planes 44 layers 0.69 and 0.72, but one of 2000 channels 1.23.
+bool parts_measured(const Problem& p) { return p.c >= 96 && p.c <= 2048 && p.M <= 40000 && p.w_bytes <= (16u << 20); }
+constexpr int kMostOverPlanes = 1400;
 
 double fixed_cost(const Problem& p, bool cut_ahead) {
   return (cut_ahead ? 1.0 : 4.3 + 1e-6 * p.w_bytes) + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k);
@@ -729,43 +734,55 @@ double fixed_cost(const Problem& p, bool cut_ahead) {
 
 // The cheapest form for the layer and its cost; a 3x3 stride-2 layer has one form (two of its patches do not fit a CU; a
 // chunk of it takes 1.35 times as long).  split: the cheapest form in parts, with forced_parts of them or, where that is below one, as many
-// as are fastest; one where it takes longer than the form for the whole.
+// as are fastest; one where it takes longer than the form for the whole.  Whether the filter was cut ahead counts in the costs and in neither
+// choice (both go by a call over planes): calls with and without them sum in the same order.
 int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, PatchParts* split, double* split_us) {
   const bool pointwise = p.r == 1;
-  double steps = 0.0, split_steps = 0.0;                 // of the forms chosen, beside what is fixed
-  int best = -1;
   MapTile map[2] = {{0, 0, 0}, {0, 0, 0}};               // of 64 and of 128 pixels
   if (!pointwise) {
     map[0] = pick_map_tile(p, 64, p.stride_h == 1 ? 120 : 320);
     if (p.stride_h == 1) map[1] = pick_map_tile(p, 128, 208);
   }
-  // (a filter of more than 16 MB: 624->816 on 17x17 at batch 2 31 -> 42 us in parts)
-  const int most = split && !pointwise && p.w_bytes <= (16u << 20) ? kMostParts : 1;
-  PatchParts in_parts = {0, 1};
-  for (int f = 0; f < FORMS; ++f) {
-    const FormCost& c = kForms[f];
-    if (pointwise ? c.cc1 == 0 : p.stride_h == 2 && f != 1) continue;
-    if (forced >= 0 && f != forced) continue;
+  auto takes = [&](int f) {
+    return !(pointwise ? kForms[f].cc1 == 0 : p.stride_h == 2 && f != 1) && (forced < 0 || f == forced);
+  };
+  auto tiles_of = [&](const FormCost& c) {
     const double px_tiles = pointwise ? (double)((p.M + c.px - 1) / c.px) : (double)p.n * map[c.px == 128].tiles;
-    const double tiles = px_tiles * ((p.k + c.bn - 1) / c.bn), slots = c.waves == 8 ? 256 : 512;
-    auto in_rounds = [&](double rounds) {
-      return c.waves == 4 && rounds <= 0.5 ? 0.7 : rounds <= 3.0 ? (double)(int)(rounds + 0.999999) : rounds + 0.5;
-    };
-    const int cc = pointwise ? c.cc1 : c.cc3;
-    const int chunks = (p.c + cc - 1) / cc;
-    const double chunk = pointwise ? c.chunk1 : p.stride_h == 2 ? 1.35 * c.chunk3 : c.chunk3;
-    const double round = pointwise ? c.round1 : c.round3;
-    const double t = in_rounds(tiles / slots) * (round + chunks * chunk);
+    return px_tiles * ((p.k + c.bn - 1) / c.bn);
+  };
+  auto chunks_of = [&](const FormCost& c) { return (p.c + (pointwise ? c.cc1 : c.cc3) - 1) / (pointwise ? c.cc1 : c.cc3); };
+  auto chunk_us = [&](const FormCost& c) { return pointwise ? (double)c.chunk1 : p.stride_h == 2 ? 1.35 * c.chunk3 : (double)c.chunk3; };
+  auto rounds_of = [](const FormCost& c, double workgroups) {
+    const double rounds = workgroups / (c.waves == 8 ? 256 : 512);
+    return c.waves == 4 && rounds <= 0.5 ? 0.7 : rounds <= 3.0 ? (double)(int)(rounds + 0.999999) : rounds + 0.5;
+  };
+  double steps = 0.0, split_steps = 0.0;                 // of the forms chosen, beside what is fixed
+  int best = -1;
+  for (int f = 0; f < FORMS; ++f) {
+    if (!takes(f)) continue;
+    const FormCost& c = kForms[f];
+    const double t = rounds_of(c, tiles_of(c)) * ((pointwise ? c.round1 : c.round3) + chunks_of(c) * chunk_us(c));
     if (best < 0 || t < steps) {
       best = f;
       steps = t;
     }
-    for (int s = 2; s <= most; ++s) {
+  }
+  const double fixed = fixed_cost(p, p.packed_is_cut != 0), over_planes = fixed_cost(p, true);
+  *cost = fixed + steps;
+  if (!split || pointwise || best < 0 || !(forced_parts > 1 || parts_measured(p))) return best;
+  PatchParts in_parts = {0, 1};
+  for (int f = 0; f < FORMS; ++f) {
+    if (!takes(f)) continue;
+    const FormCost& c = kForms[f];
+    const int chunks = chunks_of(c);
+    const double tiles = tiles_of(c), chunk = chunk_us(c);
+    for (int s = 2; s <= kMostParts; ++s) {
       const int each = (chunks + s - 1) / s;
       if ((chunks + each - 1) / each != s || (forced_parts > 0 && s != forced_parts)) continue;
       // (a part's tiles are dealt to the eight XCDs: three times 84 tiles are 33 workgroups to an XCD of 32 CUs)
-      const double rounds = 8.0 * (((long long)tiles + 7) / 8) * s / slots, r = in_rounds(rounds);
-      const double u = 0.83 * r * round + 0.94 * r * each * chunk + 1.02 * (rounds < 1.0 ? rounds : 1.0) + 1.34e-6 * s * (double)p.M * p.k;
+      const double workgroups = 8.0 * (((long long)tiles + 7) / 8) * s, full = workgroups / (c.waves == 8 ? 256 : 512);
+      const double r = rounds_of(c, workgroups);
+      const double u = 0.83 * r * c.round3 + 0.94 * r * each * chunk + 1.02 * (full < 1.0 ? full : 1.0) + 1.34e-6 * s * (double)p.M * p.k;
       if (in_parts.parts == 1 || u < split_steps) {
         in_parts = {f, s};
         split_steps = u;
@@ -773,10 +790,8 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, 
     }
   }
   auto split_cost = [&](double fixed) { return kPartsMargin * (3.0 + 1.03 * fixed + split_steps + 0.067e-6 * p.w_bytes); };
-  const double fixed = fixed_cost(p, p.packed_is_cut != 0), over_planes = fixed_cost(p, true);
-  *cost = fixed + steps;
   *split_us = split_cost(fixed);
-  if (split) *split = in_parts.parts > 1 && (forced_parts > 1 || split_cost(over_planes) < over_planes + steps) ? in_parts : PatchParts{0, 1};
+  if (in_parts.parts > 1 && (forced_parts > 1 || split_cost(over_planes) < over_planes + steps)) *split = in_parts;
   return best;
 }
 
@@ -815,7 +830,7 @@ int patch_f32_form(const Problem& p, double* us_out, PatchParts* split) {
   const int form = cheapest_form(p, forced, parts, &cost, parts == 1 ? nullptr : split, &split_us);
   *us_out = cost;
   if (mode == 2 || cost + margin < other) return form;
-  if (split && split->parts > 1 && split_us + margin >= other) split->parts = 1;
+  if (split && split->parts > 1 && (split_us + margin >= other || p.c > kMostOverPlanes)) split->parts = 1;
   return -1;
 }
 

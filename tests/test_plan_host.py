@@ -210,3 +210,24 @@ def test_planes_given_do_not_change_how_the_patch_kernel_sums(probe):
             in_parts += plain.split_k > 1
             assert (plain.tile, plain.split_k) == (packed.tile, packed.split_k), (_is(d), plain, packed)
     assert both > 500 and in_parts > 50
+
+
+@pytest.mark.parametrize("layer,st", [((14, 100, 100, 624, 16, 3), 1), ((25, 9, 7, 2000, 232, 3), 2), ((16, 66, 66, 544, 32, 3), 1)], ids=str)
+def test_layers_beyond_those_measured_run_whole(probe, layer, st):
+    """140000 and 69696 pixels; 2000 channels, 42 us on the contraction over planes and 52 in parts."""
+    d = _desc(*layer, st)
+    for packed in (False, True):
+        plan = probe.conv(d, packed=packed)
+        assert plan.kernel != "patch" or plan.split_k == 1, (packed, plan)
+
+
+def test_reductions_in_parts_stay_within_the_layers_measured(probe):
+    rng, taken = random.Random(8), 0
+    for _ in range(4000):
+        h, c, k = rng.randint(5, 110), 8 * rng.randint(4, 300), 8 * rng.randint(2, 60)
+        d = _desc(rng.choice([1, 3, 10, 30]), h, h, c, k, 3, rng.choice([1, 2]))
+        plan = probe.conv(d, packed=rng.random() < 0.5)
+        if plan.kernel == "patch" and plan.split_k > 1:
+            taken += 1
+            assert 96 <= c <= 2048 and d.n * ((h - 1) // d.stride_h + 1) ** 2 <= 40000 and 36 * c * k <= 16 << 20, (_is(d), plan)
+    assert taken > 100
