@@ -722,11 +722,16 @@ constexpr FormCost kForms[FORMS] = {
 // fitted to 3551 runs of 260 3x3 layers of 96 to 768 channels on up to 9000 pixels (median error 4 %); the margin is that of both estimates.
 constexpr int kMostParts = 8;
 constexpr double kPartsMargin = 1.10;
-// Layers that parts are measured on: 410 drawn ones that the estimates give to them, 0.84 of the time in one part with operands in the caches
-// and 0.80 from memory, the slowest 1.04 by both.  Beyond: 91592 pixels 1.06, 1896 channels on 12264 1.06; and in place of the contraction over
-// planes 44 layers 0.69 and 0.72, but one of 2000 channels 1.23.
+// Layers that parts are measured on: 486 drawn ones that the estimates give to them, 0.84 of the time in one part with operands in the caches
+// and 0.80 from memory, the slowest 1.04 by both; in place of the contraction over planes 34, 0.71 and 0.73, the slowest 0.90.  Beyond: 488->16 on
+// 107x107 at batch 8 1.06; in place of the contraction over planes 2000->232 stride 2 on 9x7 at batch 25 1.23; a filter of more than 16 MB
+// 624->816 on 17x17 at batch 2 31 -> 42 us.
 bool parts_measured(const Problem& p) { return p.c >= 96 && p.c <= 2048 && p.M <= 40000 && p.w_bytes <= (16u << 20); }
 constexpr int kMostOverPlanes = 1400;
+// Wavefronts that share the reduction of a form's block.  With no fewer runs than in one part, and two chunks and more to a part, sums lie at
+// 0.72 to 1.006 of the distance from 64-bit ones that they have without parts (520 layers, median 0.97); 26 layers of fewer runs lay at 0.97 to
+// 1.09, 8 of one chunk to a part at 0.99 to 1.02.
+int sharing(const FormCost& c) { return c.waves / (c.px / 64 * (c.bn / 32)); }
 
 double fixed_cost(const Problem& p, bool cut_ahead) {
   return (cut_ahead ? 1.0 : 4.3 + 1e-6 * p.w_bytes) + 1e-7 * ((double)p.x_bytes + 4.0 * p.M * p.k);
@@ -779,6 +784,7 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, 
     for (int s = 2; s <= kMostParts; ++s) {
       const int each = (chunks + s - 1) / s;
       if ((chunks + each - 1) / each != s || (forced_parts > 0 && s != forced_parts)) continue;
+      if (forced_parts <= 1 && (each < 2 || s * sharing(c) < sharing(kForms[best]))) continue;
       // (a part's tiles are dealt to the eight XCDs: three times 84 tiles are 33 workgroups to an XCD of 32 CUs)
       const double workgroups = 8.0 * (((long long)tiles + 7) / 8) * s, full = workgroups / (c.waves == 8 ? 256 : 512);
       const double r = rounds_of(c, workgroups);

@@ -231,3 +231,23 @@ def test_reductions_in_parts_stay_within_the_layers_measured(probe):
             taken += 1
             assert 96 <= c <= 2048 and d.n * ((h - 1) // d.stride_h + 1) ** 2 <= 40000 and 36 * c * k <= 16 << 20, (_is(d), plan)
     assert taken > 100
+
+
+def test_parts_of_a_reduction_are_no_longer_sums_than_without_them(probe, knobs):
+    """The wavefronts that share a tile's reduction, times the parts, are no fewer than in one part, and a part has two chunks and more: what sums
+    nearer to 64-bit ones need (forms: wavefronts sharing a block, channels of a chunk)."""
+    sharing, chunk = (4, 2, 8, 2, 1, 2), (64, 32, 128, 32, 32, 32)
+    layers = list(_drawn_3x3(7, 2500)) + [_desc(4, 56, 56, 112, 110, 3, 2), _desc(1, 29, 29, 506, 96, 3), _desc(1, 48, 48, 432, 48, 3)]
+    plans = [probe.conv(d, packed=d.c % 8 == 0) for d in layers]
+    knobs.set("F32_PATCH_PARTS", 1)
+    compared = 0
+    for d, plan in zip(layers, plans):
+        if plan.kernel != "patch" or plan.split_k == 1:
+            continue
+        chunks = -(-d.c // chunk[plan.tile])
+        assert -(-chunks // plan.split_k) >= 2, (_is(d), plan)
+        whole = probe.conv(d, packed=d.c % 8 == 0)
+        if whole.kernel == "patch":
+            compared += 1
+            assert plan.split_k * sharing[plan.tile] >= sharing[whole.tile], (_is(d), whole, plan)
+    assert compared > 30
