@@ -776,15 +776,20 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, 
   *cost = fixed + steps;
   if (!split || pointwise || best < 0 || !(forced_parts > 1 || parts_measured(p))) return best;
   PatchParts in_parts = {0, 1};
+  const int runs = sharing(kForms[best]);
+  auto split_cost = [&](double fixed) { return kPartsMargin * (3.0 + 1.03 * fixed + split_steps + 0.067e-6 * p.w_bytes); };
+  const double below = (over_planes + steps) / kPartsMargin - (3.0 + 1.03 * over_planes + 0.067e-6 * p.w_bytes) + 1e-6;   // of split_steps
   for (int f = 0; f < FORMS; ++f) {
     if (!takes(f)) continue;
     const FormCost& c = kForms[f];
     const int chunks = chunks_of(c);
     const double tiles = tiles_of(c), chunk = chunk_us(c);
+    // no number of parts takes less than the products in full rounds: most layers that stay whole are decided by this
+    if (forced_parts <= 1 && 0.94 * tiles * chunks * chunk / (c.waves == 8 ? 256 : 512) + 0.83 * 0.7 * c.round3 >= below) continue;
     for (int s = 2; s <= kMostParts; ++s) {
       const int each = (chunks + s - 1) / s;
       if ((chunks + each - 1) / each != s || (forced_parts > 0 && s != forced_parts)) continue;
-      if (forced_parts <= 1 && (each < 2 || s * sharing(c) < sharing(kForms[best]))) continue;
+      if (forced_parts <= 1 && (each < 2 || s * sharing(c) < runs)) continue;
       // (a part's tiles are dealt to the eight XCDs: three times 84 tiles are 33 workgroups to an XCD of 32 CUs)
       const double workgroups = 8.0 * (((long long)tiles + 7) / 8) * s, full = workgroups / (c.waves == 8 ? 256 : 512);
       const double r = rounds_of(c, workgroups);
@@ -795,7 +800,6 @@ int cheapest_form(const Problem& p, int forced, int forced_parts, double* cost, 
       }
     }
   }
-  auto split_cost = [&](double fixed) { return kPartsMargin * (3.0 + 1.03 * fixed + split_steps + 0.067e-6 * p.w_bytes); };
   *split_us = split_cost(fixed);
   if (in_parts.parts > 1 && (forced_parts > 1 || split_cost(over_planes) < over_planes + steps)) *split = in_parts;
   return best;

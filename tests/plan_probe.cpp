@@ -1,7 +1,10 @@
 // What the planner chooses for a call, without launching it: the prepare half of the convolution entry points and the
 // planners behind the FullyConnected ones, for tests that need no GPU (plan_probe.py builds and loads this).
+#include <algorithm>
+#include <chrono>
 #include <cstdint>
 #include <cstring>
+#include <vector>
 
 #include "../paper_1805_00907_amd/csrc/api_internal.h"
 
@@ -45,6 +48,24 @@ void probe_conv(const glowmi_conv_desc* d, int32_t mode, int32_t addend, int32_t
   out->tile = call.plan.tile;
   out->split_k = call.plan.split_k;
   out->workspace = used(call.p, call.plan);
+}
+
+// Median nanoseconds of planning an fp32 layer with room for whatever it likes, in turn: with that switch, with none.
+void probe_conv_versus(const glowmi_conv_desc* d, int32_t packed, const char* knob, int32_t value, int32_t repeats, int64_t* out) {
+  std::vector<int64_t> ns[2];
+  ProbePlan plan;
+  for (int32_t i = 0; i < 2 * repeats; ++i) {
+    glowmi_tuning_reset();
+    if (i % 2 == 0) glowmi_tuning_set(knob, value);
+    const auto a = std::chrono::steady_clock::now();
+    probe_conv(d, 0, 0, packed, 0, (uint64_t)1 << 36, &plan);
+    ns[i % 2].push_back(std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - a).count());
+  }
+  glowmi_tuning_reset();
+  for (int t = 0; t < 2; ++t) {
+    std::nth_element(ns[t].begin(), ns[t].begin() + repeats / 2, ns[t].end());
+    out[t] = ns[t][repeats / 2];
+  }
 }
 
 // The FullyConnected calls of those extents with a workspace as large as they like.

@@ -40,6 +40,12 @@ class Probe:
                             ctypes.byref(raw))
         return self._plan(raw)
 
+    def conv_versus(self, desc, name, value, packed=False, repeats=400):
+        """Median nanoseconds of planning the layer: with that switch, with none."""
+        ns = (ctypes.c_int64 * 2)()
+        self.lib.probe_conv_versus(ctypes.byref(desc), int(packed), name.encode(), value, repeats, ns)
+        return tuple(ns)
+
     def fc(self, m, k, n):
         raw = _Raw()
         self.lib.probe_fc(m, k, n, ctypes.byref(raw))

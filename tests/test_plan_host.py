@@ -251,3 +251,12 @@ def test_parts_of_a_reduction_are_no_longer_sums_than_without_them(probe, knobs)
             compared += 1
             assert plan.split_k * sharing[plan.tile] >= sharing[whole.tile], (_is(d), whole, plan)
     assert compared > 30
+
+
+def test_layers_that_stay_whole_are_not_searched_for_parts(probe):
+    """Planning a layer of conv_patch_f32 in one part costs the host what it costs with parts switched off (a search over the parts of every form
+    was 1.2 times that)."""
+    whole = [d for d in _drawn_3x3(9, 400) if d.c % 8 == 0 and probe.conv(d, packed=True)[:3:2] == ("patch", 1)][:60]
+    assert len(whole) == 60
+    off, on = (sum(ns) for ns in zip(*(probe.conv_versus(d, "F32_PATCH_PARTS", 1, packed=True) for d in whole)))
+    assert on < 1.12 * off, (off, on)
