@@ -224,7 +224,6 @@ int short_f32_form(const Problem& p, double* us);
 hipError_t launch_short_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // The same for fp32 FullyConnected (fc_few_f32.hip): wavefronts of a workgroup as a form.
 int fc_few_f32_form(const Problem& p, bool whole, double* us);   // whole: tiles of 16 x 16 only
-constexpr int kFcNarrow = 16;                  // added to a form: smaller tiles in place of a kernel that 16 x 16 ones do not replace
 hipError_t launch_fc_few_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // fp32 FullyConnected with dozens to hundreds of rows (fc_tiles_f32.hip).
 bool plan_fc_tiles_f32(const Problem& p, bool allow_split, Plan* plan, double* us);

@@ -852,9 +852,10 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
 // rows, the tiled kernel and fc_tiles_f32 where its estimate is lower than theirs by a tenth.  Of the time of those, over calls
 // drawn from their ranges, weights in the caches and from memory: 0.77 and 0.82 of the weight stream's (1154 calls), 0.72 and 0.68
 // (845), 0.52 and 0.55 (652), 0.82 and 0.80 (833), within 2 to 3 % of the best choice for each.  What errs takes up to 1.1 times as
-// long, the two times together; 4x2048x1000 stays (7.4 us, 6.7 here, but 8.7 and 9.9 from memory).  1x2048x1000 moves: launched one by one
-// 6.4 us and 8.1 on the weight stream, two kernels, in a graph 5.8 both, but from memory 10.8 and 9.4.  One row on few columns
-// stays with fc_rows_f32, and so do up to sixteen rows of fewer than 256 inputs with the weight stream, which is one launch there.
+// long, the two times together.  On tiles of 16 x 16 4x2048x1000 would stay (7.4 us on the weight stream, 6.7 there, but 8.7 and 9.9 from memory);
+// on 8 x 8 ones it moves, 6.3 -> 4.9 and 9.8 -> 8.9, and so does 1x2048x1000 on 4 x 4 ones (4.1 us in a graph, 5.8 on the weight stream; from memory
+// 8.3 and 9.4).  One row stays with fc_rows_f32 up to 512 inputs or where its inputs or columns are no multiple of four, and up to sixteen rows of
+// fewer than 256 inputs with the weight stream, which is one launch there.
 Plan fc_few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FC_FEW, 1);         // 0: off, 2: any size (tests)
   double us = 0.0, other = 0.0;
@@ -876,7 +877,7 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
       other = 7.0 + 0.246 * depth + 0.131 * mb;
     } else if (rest.kernel == KERNEL_FC_ROWS) {
       // one row of more than 512 aligned inputs: 0.69 of its time over 112 calls, all of them faster (1x1696x544 4.6 -> 3.7 us, 8.9 -> 6.4)
-      if (p.M == 1 && p.k % 4 == 0 && p.Kgemm % 4 == 0 && p.Kgemm > 512 && form != whole) return instead_of(p, rest, KERNEL_FC_FEW, kFcNarrow + form);
+      if (p.M == 1 && p.k % 4 == 0 && p.Kgemm % 4 == 0 && p.Kgemm > 512 && form != whole) return instead_of(p, rest, KERNEL_FC_FEW, form);
       if (p.M > 1 && p.k % 4 == 0) other = 3.57 + (0.785 + 0.17 * p.M) * depth + 0.304 * mb + 0.72 * p.M;
     } else if (rest.kernel == KERNEL_FC_SMALL) {
       const int width = fc_small_f32_width(p);
@@ -889,7 +890,7 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
     }
     // Smaller tiles where those of 16 x 16 do not pay: 727 calls of the weight stream's 0.90 of their time with the weights in the caches and
     // from memory together, the slowest 1.03.
-    if (1.1 * us > other) return 1.1 * narrow_us <= other ? instead_of(p, rest, KERNEL_FC_FEW, kFcNarrow + form) : rest;
+    if (1.1 * us > other) return 1.1 * narrow_us <= other ? instead_of(p, rest, KERNEL_FC_FEW, form) : rest;
   }
   return instead_of(p, rest, KERNEL_FC_FEW, form);
 }

@@ -48,7 +48,8 @@ def test_non_finite_rows_stay_to_themselves(k, knobs):
 
 @pytest.mark.parametrize("shape,taken", [((2, 480, 208), True), ((1, 2048, 1000), True), ((21, 920, 2224), True), ((125, 784, 320), True),
                                          ((2, 2048, 1000), True), ((4, 1600, 744), True),
-                                         ((4, 2048, 1000), False), ((1, 3072, 1000), False), ((44, 456, 4280), False), ((16, 248, 64), False), ((16, 256, 64), True), ((40, 256, 64), True), ((256, 4096, 4096), False), ((9, 5088, 112), False)], ids=str)
+                                         ((4, 2048, 1000), True), ((1, 3072, 1000), True),      # on tiles of 8 x 8 and 4 x 4; 16 x 16 left them
+                                         ((44, 456, 4280), False), ((16, 248, 64), False), ((16, 256, 64), True), ((40, 256, 64), True), ((256, 4096, 4096), False), ((9, 5088, 112), False)], ids=str)
 def test_which_calls_take_it(shape, taken, knobs):
     import torch
     import gpu_util as G
@@ -95,7 +96,7 @@ def test_smaller_tiles(shape, tile, knobs):
         assert not np.isfinite(got[[1, m - 1]]).any()
 
 
-@pytest.mark.parametrize("shape,variant", [((4, 2048, 1000), "fc_narrow_f32"), ((1, 2048, 1000), "fc_few_f32_w"), ((1, 1696, 544), "fc_narrow_f32"),
+@pytest.mark.parametrize("shape,variant", [((4, 2048, 1000), "fc_few_f32_w16c8"), ((1, 2048, 1000), "fc_few_f32_w8c4"), ((1, 1696, 544), "fc_few_f32_w8c4"),
                                            ((1, 512, 1000), "fc_rows_f32"), ((16, 4096, 4096), "fc_skinny16_f32")], ids=str)
 def test_which_calls_take_smaller_tiles(shape, variant):
     """The answer of the query stays that of the kernel they stand in for."""
