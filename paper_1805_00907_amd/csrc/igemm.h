@@ -222,8 +222,9 @@ hipError_t launch_few_f32(const Problem& p, int form, hipStream_t stream, const 
 // fp32 pointwise convolution of any channel counts in fours on many pixels (conv_short_f32.hip): form and expected microseconds.
 int short_f32_form(const Problem& p, double* us);
 hipError_t launch_short_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
-// The same for fp32 FullyConnected (fc_few_f32.hip): wavefronts of a workgroup as a form.
-int fc_few_f32_form(const Problem& p, bool whole, double* us);   // whole: tiles of 16 x 16 only
+// The same for fp32 FullyConnected (fc_few_f32.hip): wavefronts of a workgroup and tiles as a form; false: not a call for it.
+struct FcFewForms { int whole, any; double whole_us, any_us; };   // the best on tiles of 16 x 16, the best of all
+bool fc_few_f32_forms(const Problem& p, FcFewForms* forms);
 hipError_t launch_fc_few_f32(const Problem& p, int form, hipStream_t stream, const char** variant);
 // fp32 FullyConnected with dozens to hundreds of rows (fc_tiles_f32.hip).
 bool plan_fc_tiles_f32(const Problem& p, bool allow_split, Plan* plan, double* us);

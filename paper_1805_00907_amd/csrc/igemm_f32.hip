@@ -858,15 +858,10 @@ Plan tiles_or(const Problem& p, const Plan& rest, bool allow_split) {
 // fewer than 256 inputs with the weight stream, which is one launch there.
 Plan fc_few_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_F32_FC_FEW, 1);         // 0: off, 2: any size (tests)
-  double us = 0.0, other = 0.0;
-  const int whole = fc_few_f32_form(p, true, &us);
-  if (whole < 0) return rest;
-  double narrow_us = 0.0;
-  const int form = fc_few_f32_form(p, false, &narrow_us);
+  if (mode == 0) return rest;
+  double other = 0.0;
+  bool one_row = false;
   if (mode != 2) {
-    for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW,
-                         KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_F32_FC_ROWS, KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT})
-      if (knob_is_set(k)) return rest;                   // another kernel is asked for
     // (the weight stream, fc_rows_f32 and fc_small_f32: fitted to 2400 calls as fc_few_f32 itself, median errors 3, 5 and 7 %)
     const double depth = 1e-3 * p.Kgemm, mb = 1e-6 * p.w_bytes;
     if (rest.kernel == KERNEL_SKINNY16) {
@@ -877,7 +872,7 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
       other = 7.0 + 0.246 * depth + 0.131 * mb;
     } else if (rest.kernel == KERNEL_FC_ROWS) {
       // one row of more than 512 aligned inputs: 0.69 of its time over 112 calls, all of them faster (1x1696x544 4.6 -> 3.7 us, 8.9 -> 6.4)
-      if (p.M == 1 && p.k % 4 == 0 && p.Kgemm % 4 == 0 && p.Kgemm > 512 && form != whole) return instead_of(p, rest, KERNEL_FC_FEW, form);
+      one_row = p.M == 1 && p.k % 4 == 0 && p.Kgemm % 4 == 0 && p.Kgemm > 512;
       if (p.M > 1 && p.k % 4 == 0) other = 3.57 + (0.785 + 0.17 * p.M) * depth + 0.304 * mb + 0.72 * p.M;
     } else if (rest.kernel == KERNEL_FC_SMALL) {
       const int width = fc_small_f32_width(p);
@@ -888,11 +883,17 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
     } else if (rest.kernel == KERNEL_TILED) {
       other = tiled_us(p, rest);
     }
-    // Smaller tiles where those of 16 x 16 do not pay: 727 calls of the weight stream's 0.90 of their time with the weights in the caches and
-    // from memory together, the slowest 1.03.
-    if (1.1 * us > other) return 1.1 * narrow_us <= other ? instead_of(p, rest, KERNEL_FC_FEW, form) : rest;
+    if (!one_row && other == 0.0) return rest;           // a kernel that it does not replace
+    for (const Knob k : {KNOB_F32_TILE, KNOB_F32_SPLIT, KNOB_F32_P3_MIN_M, KNOB_F32_FC_SMALL_OFF, KNOB_F32_FC_SMALL_VW,
+                         KNOB_F32_FC_SMALL_MAX_KB, KNOB_F32_FC_SMALL_MIN_M, KNOB_F32_FC_ROWS, KNOB_F32_FC_TILES, KNOB_F32_FC_TILES_SPLIT})
+      if (knob_is_set(k)) return rest;                   // another kernel is asked for
   }
-  return instead_of(p, rest, KERNEL_FC_FEW, form);
+  FcFewForms few;
+  if (!fc_few_f32_forms(p, &few)) return rest;
+  // Smaller tiles where those of 16 x 16 do not pay: 727 calls of the weight stream's 0.90 of their time with the weights in the caches and
+  // from memory together, the slowest 1.03.
+  if (mode != 2 && (one_row ? few.any == few.whole : 1.1 * few.whole_us > other && 1.1 * few.any_us > other)) return rest;
+  return instead_of(p, rest, KERNEL_FC_FEW, few.any);
 }
 // conv_patch_f32 with the reduction in parts in place of itself and of the contraction over planes, which multiply the same two fp16 pieces of
 // an operand.  What runs on fp32 operands (tiles, slices, conv_few_f32) stays there: 24 bits of each, and an infinity reaches no other outputs

@@ -16,6 +16,24 @@ void* fake(uintptr_t at) { return reinterpret_cast<void*>(at << 36); }   // alig
 size_t used(const Problem& p, const Plan& pl) {
   return pl.pack_bytes + (pl.split_k > 1 ? (size_t)pl.split_k * (size_t)p.M * (size_t)p.k * 4u : 0u);
 }
+
+// Median nanoseconds of planning an fp32 call with room for whatever it likes, in turn: with that switch, with none.
+template <typename PlanFn>
+void versus(const char* knob, int32_t value, int32_t repeats, int64_t* out, PlanFn plan) {
+  std::vector<int64_t> ns[2];
+  for (int32_t i = 0; i < 2 * repeats; ++i) {
+    glowmi_tuning_reset();
+    if (i % 2 == 0) glowmi_tuning_set(knob, value);
+    const auto a = std::chrono::steady_clock::now();
+    plan();
+    ns[i % 2].push_back(std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - a).count());
+  }
+  glowmi_tuning_reset();
+  for (int t = 0; t < 2; ++t) {
+    std::nth_element(ns[t].begin(), ns[t].begin() + repeats / 2, ns[t].end());
+    out[t] = ns[t][repeats / 2];
+  }
+}
 }  // namespace
 
 extern "C" {
@@ -50,24 +68,6 @@ void probe_conv(const glowmi_conv_desc* d, int32_t mode, int32_t addend, int32_t
   out->workspace = used(call.p, call.plan);
 }
 
-// Median nanoseconds of planning an fp32 layer with room for whatever it likes, in turn: with that switch, with none.
-void probe_conv_versus(const glowmi_conv_desc* d, int32_t packed, const char* knob, int32_t value, int32_t repeats, int64_t* out) {
-  std::vector<int64_t> ns[2];
-  ProbePlan plan;
-  for (int32_t i = 0; i < 2 * repeats; ++i) {
-    glowmi_tuning_reset();
-    if (i % 2 == 0) glowmi_tuning_set(knob, value);
-    const auto a = std::chrono::steady_clock::now();
-    probe_conv(d, 0, 0, packed, 0, (uint64_t)1 << 36, &plan);
-    ns[i % 2].push_back(std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - a).count());
-  }
-  glowmi_tuning_reset();
-  for (int t = 0; t < 2; ++t) {
-    std::nth_element(ns[t].begin(), ns[t].begin() + repeats / 2, ns[t].end());
-    out[t] = ns[t][repeats / 2];
-  }
-}
-
 // The FullyConnected calls of those extents with a workspace as large as they like.
 static void fill(Problem& p, int32_t M, int32_t K, int32_t N) {
   std::memset(&p, 0, sizeof(p));
@@ -89,6 +89,15 @@ void probe_fc(int32_t M, int32_t K, int32_t N, ProbePlan* out) {
   out->tile = pl.tile;
   out->split_k = pl.split_k;
   out->workspace = used(p, pl);
+}
+
+void probe_conv_versus(const glowmi_conv_desc* d, int32_t packed, const char* knob, int32_t value, int32_t repeats, int64_t* out) {
+  ProbePlan plan;
+  versus(knob, value, repeats, out, [&]() { probe_conv(d, 0, 0, packed, 0, (uint64_t)1 << 36, &plan); });
+}
+void probe_fc_versus(int32_t M, int32_t K, int32_t N, const char* knob, int32_t value, int32_t repeats, int64_t* out) {
+  ProbePlan plan;
+  versus(knob, value, repeats, out, [&]() { probe_fc(M, K, N, &plan); });
 }
 
 void probe_qfc(int32_t M, int32_t K, int32_t N, int32_t w_offset, ProbePlan* out) {

@@ -51,6 +51,11 @@ class Probe:
         self.lib.probe_fc(m, k, n, ctypes.byref(raw))
         return self._plan(raw)
 
+    def fc_versus(self, m, k, n, name, value, repeats=400):
+        ns = (ctypes.c_int64 * 2)()
+        self.lib.probe_fc_versus(m, k, n, name.encode(), value, repeats, ns)
+        return tuple(ns)
+
     def qfc(self, m, k, n, w_offset=0):
         raw = _Raw()
         self.lib.probe_qfc(m, k, n, w_offset, ctypes.byref(raw))

@@ -260,3 +260,12 @@ def test_layers_that_stay_whole_are_not_searched_for_parts(probe):
     assert len(whole) == 60
     off, on = (sum(ns) for ns in zip(*(probe.conv_versus(d, "F32_PATCH_PARTS", 1, packed=True) for d in whole)))
     assert on < 1.12 * off, (off, on)
+
+
+def test_fully_connected_calls_that_stay_elsewhere_are_not_estimated(probe):
+    """Planning a call over planes costs the host what it costs with fc_few_f32 switched off (its estimates, twice, were 1.3 times that)."""
+    rng = random.Random(6)
+    calls = [c for c in ((rng.randint(600, 1600), 8 * rng.randint(300, 1000), 8 * rng.randint(200, 500)) for _ in range(200)) if probe.fc(*c).kernel == "p3"][:50]
+    assert len(calls) == 50
+    off, on = (sum(ns) for ns in zip(*(probe.fc_versus(*c, "F32_FC_FEW", 0) for c in calls)))
+    assert on < 1.12 * off, (off, on)
