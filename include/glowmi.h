@@ -235,8 +235,8 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  * the library that made them.  glowmi_conv2d / glowmi_fc make these planes inside every call
  * (in the workspace); a caller that keeps the weights fixed makes them once and hands them to the *_packed
  * entry points, which are otherwise the same calls: bit for bit the same results where the same kernel serves
- * both, and within the accuracy stated at the top where a layer takes the fp16 kernels only once its weights
- * need no cutting.
+ * both (in the same parts of a reduction, which they are with the workspaces that the queries name), and within the
+ * accuracy stated at the top where a layer takes the fp16 kernels only once its weights need no cutting.
  *   glowmi_conv2d_filter_planes_bytes / glowmi_fc_filter_planes_bytes
  *       bytes of the planes (4 per weight, rounded up to 256, plus 4096 of trailer), or 0 when the shape has no plane form
  *       (c/groups, or K of a FullyConnected layer, not a multiple of 8; more than 2^28 weights; bad descriptor).
@@ -254,10 +254,12 @@ glowmi_status glowmi_qconv2d_chain(const int8_t* x, glowmi_qparam xq, const int8
  *   glowmi_conv2d_packed_workspace_bytes / glowmi_fc_packed_workspace_bytes
  *       the workspace of a *_packed call with w_planes != NULL.  On the same kernel it is the plain call's
  *       minus the weights' planes.  What is left of it for a 1x1 or 3x3 layer that reads one patch per tile is 256 bytes that
- *       stay untouched and the sums of the parts of its reduction where it has any, or none for a large map: without them the layer stays in fp32 arithmetic, as the plain call does
- *       without a workspace; with room for the 256 bytes alone it runs in one part.  A layer that only pays for the fp16 kernels once its weights need no cutting (a
- *       FullyConnected of a few hundred rows) takes them here and not in the plain call, and then asks for room for the
- *       input's planes.
+ *       stay untouched, or none for a large map, and behind them the sums of the parts of its reduction where it has any.
+ *       Without the 256 bytes the layer stays in fp32 arithmetic, as the plain call does without a workspace; with room for
+ *       them and not for the parts it runs what it would if it had none, mostly the same kernel in one part (where that is
+ *       one that wants more room still, fp32 arithmetic).  A layer that only pays for the fp16 kernels once its weights
+ *       need no cutting (a FullyConnected of a few hundred rows) takes them here and not in the plain call, and then asks
+ *       for room for the input's planes.
  */
 size_t glowmi_conv2d_filter_planes_bytes(const glowmi_conv_desc* d);
 glowmi_status glowmi_conv2d_pack_filter(const float* w, const glowmi_conv_desc* d, void* planes,

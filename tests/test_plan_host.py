@@ -269,3 +269,26 @@ def test_fully_connected_calls_that_stay_elsewhere_are_not_estimated(probe):
     assert len(calls) == 50
     off, on = (sum(ns) for ns in zip(*(probe.fc_versus(*c, "F32_FC_FEW", 0) for c in calls)))
     assert on < 1.12 * off, (off, on)
+
+
+def test_less_room_than_the_parts_take_is_no_room_for_them(probe, knobs):
+    """Whatever a call hands over below its query: what it would run if there were no parts.  Over planes that is, in 256 bytes, the same kernel in
+    one part, but for the layers that parts take from the contraction over planes."""
+    layers, seen = [], set()
+    for d in _drawn_3x3(10, 2500):
+        for packed in (False, d.c % 8 == 0):
+            query = (glowmi.conv2d_packed_workspace_bytes if packed else glowmi.conv2d_workspace_bytes)(d)
+            plan = probe.conv(d, packed=packed, workspace=query)
+            if plan.kernel == "patch" and plan.split_k > 1:
+                assert plan.workspace <= query
+                rooms = (0, 16, 256, plan.workspace - 4 * plan.split_k * d.n * d.k, plan.workspace // 2, plan.workspace - 1)
+                layers.append((d, packed, rooms, [probe.conv(d, packed=packed, workspace=room) for room in rooms]))
+    knobs.set("F32_PATCH_PARTS", 1)
+    for d, packed, rooms, plans in layers:
+        whole = probe.conv(d, packed=packed).kernel
+        for room, plan in zip(rooms, plans):
+            assert plan == probe.conv(d, packed=packed, workspace=room), (_is(d), packed, room)
+        if packed:
+            assert plans[2].kernel == "patch" if whole == "patch" else plans[2].kernel not in PIECE_KERNELS, (_is(d), whole, plans[2])
+        seen.add((packed, whole))
+    assert seen == {(False, "patch"), (False, "p3"), (True, "patch"), (True, "p3")} and len(layers) > 60
