@@ -418,14 +418,14 @@ hipError_t launch_nt(const Problem& p, hipStream_t stream) {
 }  // namespace
 
 // The form (tiles of 32 channels to a slice) and what it is expected to take, -1: not a layer for this kernel.  Whether it is the
-// best kernel is the planner's question, which gives what it has to be below.  The estimate: a start, what a CU's workgroups take in turn, the filter's way into LDS for
-// each, the blocks a wavefront goes through (tiles, steps, an addend) as the workgroups of a CU share its pipes and as one
-// wavefront's chain, the bytes of the tensors and of the filter.  Fitted to 5600 and 990 runs of 2100 and 300 layers, with channels in
-// fours and others (five dwords to a chunk, and shifts, or codes stored one by one), to the geometric mean of the times with operands
-// in the caches and from memory (median errors 4 and 5 %; rows whole cache lines apart lie where the others do).
-struct ShortCost { double fixed, per_cu, fill, tile, step, mfma, add, block, chain, mb, filter; };
-constexpr ShortCost kShort[2] = {{3.604, 0.0, 0.01838, 0.3973, 0.06682, 0.0, 0.2133, 0.0, 0.04485, 0.09156, 0.3565},
-                                 {3.588, 0.0, 0.02711, 0.4203, 0.1295, 0.0, 0.07967, 0.0, 0.02581, 0.1254, 1.957}};
+// best kernel is the planner's question, which gives what it has to be below.  The estimate: a start, the filter's way into LDS for each of a
+// CU's workgroups in turn, the blocks a wavefront goes through (tiles, steps, an addend) as the workgroups of a CU share its pipes and the
+// steps as one wavefront's chain, the bytes of the tensors and of the filter.  Fitted apart for channels in fours and others (five dwords to a
+// chunk, and shifts, or codes stored one by one), to the geometric mean of the times with operands in the caches and from memory: over 2361
+// and 432 runs of 900 layers drawn after the fit, in every form, median errors of 4 and 5 %, nine in ten within 11 and 14 %.
+struct ShortCost { double fixed, fill, tile, step, add, chain, mb, filter; };
+constexpr ShortCost kShort[2] = {{3.604, 0.01838, 0.3973, 0.06682, 0.2133, 0.04485, 0.09156, 0.3565},
+                                 {3.588, 0.02711, 0.4203, 0.1295, 0.07967, 0.02581, 0.1254, 1.957}};
 int short_i8_form(const Problem& p, double below, double* us) {
   const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
   if (mode == 0 || p.b_is_kn || p.groups != 1 || p.chain_n > 0 || p.w_off != 0 || (p.addend && p.k % 4 != 0)) return -1;
@@ -439,17 +439,15 @@ int short_i8_form(const Problem& p, double below, double* us) {
   const double mb = 1e-6 * ((double)p.x_bytes + (p.addend ? 2.0 : 1.0) * p.M * p.k);
   // one tile to a wavefront, with nothing to wait for but its own chain: most small layers are decided by this
   const double chain = 0.5 * chunks;                    // at least this many steps
-  if (mode == 1 && cost.fixed + cost.per_cu + cost.fill * chunks + cost.tile + cost.mfma * chunks + cost.block + (cost.step + cost.chain) * chain +
-                       cost.mb * mb >= below) return -1;
+  if (mode == 1 && cost.fixed + cost.fill * chunks + cost.tile + (cost.step + cost.chain) * chain + cost.mb * mb >= below) return -1;
   int best = -1;
   for (int nt = 1; nt <= 4; ++nt) {
     const int T = by_lines(p, nt) ? 4 : steps_of(nt, taps, p.addend != nullptr), steps = (chunks + 2 * T - 1) / (2 * T) * T;
     if (short_lds(nt, steps * 32 + 16) > SH_LDS || (forced > 0 && nt != forced)) continue;
     const int slices = (p.k + 32 * nt - 1) / (32 * nt), wgs = workgroups(blocks, slices, 256);
     const double per_cu = (wgs * slices + 255) / 256, deep = (blocks + wgs * SH_WAVES - 1) / (wgs * SH_WAVES);
-    const double t = cost.fixed + per_cu * (cost.per_cu + cost.fill * nt * chunks +
-                                            deep * (nt * (cost.tile + cost.mfma * chunks + (p.addend ? cost.add : 0.0)) + cost.step * steps)) +
-                     deep * (cost.block + cost.chain * steps) + cost.mb * mb + cost.filter * 1e-6 * p.w_bytes;
+    const double t = cost.fixed + per_cu * (cost.fill * nt * chunks + deep * (nt * (cost.tile + (p.addend ? cost.add : 0.0)) + cost.step * steps)) +
+                     deep * cost.chain * steps + cost.mb * mb + cost.filter * 1e-6 * p.w_bytes;
     if (best < 0 || t < *us) {
       best = nt;
       *us = t;

@@ -828,8 +828,8 @@ Plan few_or(const Problem& p, const Plan& rest) {
 }
 
 // Convolutions whose filters fit the LDS of a CU in slices: conv_short_i8 where its estimate is lower than that of the kernel that
-// would run by two in a hundred.  Of the time of those, operands in the caches and from memory together: tiles 0.58 to 0.79 (322 of 361 layers
-// move), the wide kernel 0.70 to 0.89 (91 of 134), conv_small_i8 as below.  All choices together lie 1.3 % above the best one for each of 1800 layers.
+// would run by two in a hundred.  Of the time of those, over 900 drawn layers, operands in the caches and from memory together: tiles 0.69 (245
+// move, the slowest 0.98), the wide kernel 0.73 (53, 0.94), conv_small_i8 as below.  All choices together lie 1.6 % above the best one for each.
 // The kernels for one kind of layer stay (1x1 256->64 on 56x56 at batch 32 8.6 us, 10.4 here).
 Plan short_or(const Problem& p, const Plan& rest) {
   const int mode = knob_or(KNOB_I8_SHORT, 1);           // 0: off, 2: any layer that fits (tests)
@@ -837,8 +837,8 @@ Plan short_or(const Problem& p, const Plan& rest) {
   // (128 x 128 tiles of several taps over whole cache lines of channels: equal, 3x3 128->256 on 56x56 at batch 6 17.7 us, 18.1
   // here, at batch 12 28.6 and 26.0)
   if (mode != 2 && rest.kernel == KERNEL_WIDE && p.c % 128 == 0 && p.r * p.s > 1 && rest.bn == 128) return rest;
-  // (conv_small_i8's time fitted anew, to 689 layers, with a term for an addend: median error 3 %.  By it and the margins 198 of 335 single
-  // taps move, 0.90 of their time, and 39 of 344 layers of several, 0.88; the slowest 1.10)
+  // (conv_small_i8's time, fitted to 689 layers: median error 3 %.  By it and the margins 129 of those 900 move, 0.89 of their time, two above 1.08
+  // of it, 3x3 stride 2 104->688 on 31x31 at batch 3 8.9 -> 10.6 us)
   auto small_us = [&]() {
     const long long t32 = (long long)((p.M + 31) / 32) * ((p.k + 31) / 32);
     const double rounds = (double)((t32 + 255) / 256), chunks = p.r * p.s * ((p.c + 15) / 16), out = 1e-6 * (double)p.M * p.k;
