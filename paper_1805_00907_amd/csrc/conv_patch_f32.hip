@@ -19,7 +19,7 @@
 //     392 -> 200 on 92x75 2.7e-7 of the result's norm against 1.1e-7, 512 -> 512 on 28x28 4.3e-7); so it is no further from
 //     64-bit sums than that kernel (1.1e-7 and 1.6e-7), for 2 % of the time;
 //   - a 3x3 layer of many channels on few pixels has its reduction in parts, whose sums splitk_finish_f32 adds up: 512->512 stride 2 on
-//     14x14 at batch 16, filter given, 44 -> 23 us; 119 of 600 drawn layers of 96 channels and more on up to 9000 pixels, 0.79 of their time.
+//     14x14 at batch 16, filter given, 45 -> 23.5 us; 520 drawn layers 0.83 of their time with operands in the caches and 0.79 from memory.
 // What bounds it: LDS and vector memory bandwidth next to the matrix cores, and what a workgroup does before its first and
 // behind its last chunk.  A form with 32 x 32 blocks per wavefront and the filter in an LDS ring read 32 KB of fragments per
 // 32 reduction indices of a 64 x 64 tile, 256 cycles against 192 of matrix work, and did not get past a third of the matrix
@@ -723,7 +723,7 @@ constexpr FormCost kForms[FORMS] = {
 constexpr int kMostParts = 8;
 constexpr double kPartsMargin = 1.10;
 // Layers that parts are measured on: 486 drawn ones that the estimates give to them, 0.84 of the time in one part with operands in the caches
-// and 0.80 from memory, the slowest 1.04 by both; in place of the contraction over planes 34, 0.71 and 0.73, the slowest 0.90.  Beyond: 488->16 on
+// and 0.80 from memory, the slowest 1.02 by both; in place of the contraction over planes 34, 0.71 and 0.75, the slowest 0.92.  Beyond: 488->16 on
 // 107x107 at batch 8 1.06; in place of the contraction over planes 2000->232 stride 2 on 9x7 at batch 25 1.23; a filter of more than 16 MB
 // 624->816 on 17x17 at batch 2 31 -> 42 us.
 bool parts_measured(const Problem& p) { return p.c >= 96 && p.c <= 2048 && p.M <= 40000 && p.w_bytes <= (16u << 20); }
