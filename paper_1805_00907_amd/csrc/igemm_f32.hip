@@ -890,10 +890,13 @@ Plan fc_few_or(const Problem& p, const Plan& rest) {
   }
   FcFewForms few;
   if (!fc_few_f32_forms(p, &few)) return rest;
-  // Smaller tiles where those of 16 x 16 do not pay: 727 calls of the weight stream's 0.90 of their time with the weights in the caches and
-  // from memory together, the slowest 1.03.
-  if (mode != 2 && (one_row ? few.any == few.whole : 1.1 * few.whole_us > other && 1.1 * few.any_us > other)) return rest;
-  return instead_of(p, rest, KERNEL_FC_FEW, few.any);
+  // Smaller tiles than 16 x 16 where their estimate is lower, by a twelfth up to 350 inputs: of 255 drawn calls of so few whose estimates lie nearer
+  // they take 1.06 of the time, up to 1.19 (80x176x400 3.5 -> 4.1 us), of 76 of more 0.96, and 0.88 over 302 that lie further apart.  They also go where
+  // those of 16 x 16 do not pay: 727 calls of the weight stream's 0.90 of their time with the weights in the caches and from memory together, the
+  // slowest 1.03.
+  const bool smaller = few.any != few.whole && (one_row || few.any_us <= (p.Kgemm <= 350 ? 0.92 : 1.0) * few.whole_us);
+  if (mode != 2 && (one_row ? !smaller : 1.1 * few.whole_us > other && !(smaller && 1.1 * few.any_us <= other))) return rest;
+  return instead_of(p, rest, KERNEL_FC_FEW, smaller ? few.any : few.whole);
 }
 // conv_patch_f32 with the reduction in parts in place of itself and of the contraction over planes, which multiply the same two fp16 pieces of
 // an operand.  What runs on fp32 operands (tiles, slices, conv_few_f32) stays there: 24 bits of each, and an infinity reaches no other outputs

@@ -292,3 +292,11 @@ def test_less_room_than_the_parts_take_is_no_room_for_them(probe, knobs):
             assert plans[2].kernel == "patch" if whole == "patch" else plans[2].kernel not in PIECE_KERNELS, (_is(d), whole, plans[2])
         seen.add((packed, whole))
     assert seen == {(False, "patch"), (False, "p3"), (True, "patch"), (True, "p3")} and len(layers) > 60
+
+
+@pytest.mark.parametrize("m,k,n,form", [(80, 176, 400, 0), (308, 112, 96, 0), (3, 134, 2736, 0), (18, 304, 1032, 1),
+                                        (1, 2048, 1000, 6), (4, 2048, 1000, 4), (13, 1320, 208, 6), (44, 4007, 48, 6)])
+def test_smaller_tiles_only_where_they_gain_more_than_the_estimates_miss(probe, m, k, n, form):
+    """FullyConnected on tiles of 16 x 16 (forms 0 to 2): the first four calls 3.4 to 3.9 us there, 3.8 to 4.4 on smaller ones."""
+    plan = probe.fc(m, k, n)
+    assert plan.kernel == "fc_few" and plan.tile == form, plan
