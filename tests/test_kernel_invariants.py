@@ -198,3 +198,16 @@ def test_every_line_of_a_kernels_arguments_is_asked_for_at_its_start(tmp_path, s
         assert got >= set(range(0, max(ends), 64)), (m.group(1), max(ends), sorted(got))
         assert max(got) < max(ends)
     assert seen == kernels, seen
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_two_workgroups_of_fc_few_f32_fit_a_compute_unit(tmp_path):
+    """Sixteen wavefronts are four to a SIMD, whose 512 registers a lane hold eight of 64 each: with more than 256 tiles a kernel of 70 registers
+    takes a second round."""
+    asm = _compile(tmp_path, "fc_few_f32")
+    counts = {}
+    for block in re.split(r"\n  - \.a", asm):
+        name, regs = re.search(r"\.name:\s+(\S+)", block), re.search(r"\.vgpr_count:\s+(\d+)", block)
+        if name and regs and "fc_few_f32_kernel" in name.group(1):
+            counts[name.group(1)] = int(regs.group(1)), int(re.search(r"\.vgpr_spill_count:\s+(\d+)", block).group(1))
+    assert len(counts) == 7 and all(regs <= 64 and spilled == 0 for regs, spilled in counts.values()), counts
